@@ -55,6 +55,7 @@ enum {
     SL_PRIV_LIST,                                        // privileged jobs of the loop: the queued guaranteed jobs
     SL_SIM_PLACES,                                       // simulation over nodes: where the jobs are, where they go
     SL_ND_NODES, SL_ND_U32, SL_ND_F32, SL_ND_U64,        // the Schedule loop over nodes: node tables and their copy; per-job words
+    SL_FIT_NEXT,                                         // model fitting: the next model to take
     SL_COUNT
 };
 static_assert(SL_COUNT <= RK_SCRATCH_SLOTS, "more scratch slots than the context holds");

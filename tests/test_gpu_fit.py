@@ -214,3 +214,26 @@ def test_fit_edge_cases(gpu, orc):
         rk.rk_fit_models(run.ctx, run.jobs, run.env, smp, res, refit_threshold=-1.0)
     assert e.value.code == rk.RK_ERR_INVALID_ARG
     run.close()
+
+
+@pytest.mark.parametrize("n_samples,n_offload", [(8, 3), (9, 9), (16, 5), (17, 0), (33, 12)])
+def test_a_models_fit_does_not_depend_on_its_neighbours(gpu, orc, n_samples, n_offload):
+    """A descent sits in whichever slot of a wavefront becomes free and models come off a shared counter: the result of
+    every model is the same, bit for bit, whether 700 models are fitted together or a few on their own.  The numbers of
+    runs lie at the edges of the group widths; offloaded runs from none to all of them."""
+    case = FitCase(orc, 700, n_samples, sigma=0.05, n_offload=n_offload)
+    whole = case.fit_on_gpu(gpu)
+    for lo, hi in ((0, 1), (1, 6), (350, 373), (699, 700)):
+        part = FitCase.__new__(FitCase)
+        part.__dict__.update(case.__dict__)
+        part.n_models = hi - lo
+        part.wl = case.wl.subset(np.arange(lo, hi))
+        part.coef0, part.theta0, part.y = case.coef0[lo:hi], case.theta0[lo:hi], case.y[lo:hi]
+        part.d, part.t, part.p = case.d[lo:hi], case.t[lo:hi], case.p[lo:hi]
+        part.dr = workloads.FitDraws(*(getattr(case.dr, f)[lo:hi] if f != "start_offsets" else case.dr.start_offsets
+                                       for f in ("u_triple", "option", "cpus", "noise_z", "start_factor", "start_offsets")))
+        alone = part.fit_on_gpu(gpu)
+        for key in ("theta", "before", "after", "iters"):
+            assert np.array_equal(alone[key], whole[key][lo:hi]), (key, lo, hi)
+    e = [case.oracle_rmsle(j, whole["theta"][j]) for j in range(0, 700, 50)]
+    assert np.all(np.abs(whole["after"][::50] - e) <= 1e-6 * (1 + np.array(e)))
