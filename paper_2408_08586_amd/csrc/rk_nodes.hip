@@ -17,6 +17,8 @@
 // gives up elsewhere (a suffix sum over the nodes), the look-ahead that passes over jobs with nothing to do, and
 // everything about memory and the records.
 // Before a step touches anything the node tables are copied; a step that is not committed copies them back.
+#include <type_traits>
+
 #include "rk_internal.h"
 #include "rk_model.h"
 #include "rk_loop.h"
@@ -27,6 +29,8 @@ constexpr int ND_THREADS = 1024;
 constexpr int ND_WAVES = ND_THREADS / 64;
 constexpr uint32_t ND_NONE = 0xFFFFFFFFu;
 constexpr uint32_t ND_PER = (RK_MAX_NODES + ND_THREADS - 1) / ND_THREADS;   // nodes per thread, at most
+constexpr int ND_SMALL_THREADS = 256;
+constexpr size_t ND_LDS_MOST = 156 * 1024;                                    // dynamic LDS of a workgroup: 160 KiB less what the kernels declare
 constexpr uint32_t ND_MAX_GPUS = 1u << 20;                                   // nodes x GPUs per node
 
 struct NdCurves {
@@ -52,8 +56,9 @@ struct NdBody {
     const uint32_t *prev_off;        // may be null (then nobody may hold anything)
     const rk_place_entry *prev_entries;
     uint64_t n_prev;                 // records in prev_entries
-    // nodes: one block of words [free_g | free_c | cnt | res_job | res_k], and its copy
-    uint32_t *free_g, *free_c, *cnt, *res_job, *res_k;
+    // nodes: one block of words [free_g | free_c | cnt | res], and its copy; a resident is (job << 16 | its GPUs here),
+    // ND_EMPTY past a node's last one (in the tables kept in LDS)
+    uint32_t *free_g, *free_c, *cnt, *res;
     uint32_t *keep_nodes;
     uint32_t nodes_words;
     // per job: cached slopes (see rk_loop.h), the order, what a step touched
@@ -63,15 +68,16 @@ struct NdBody {
     uint32_t *lvl_g, *lvl_c, *any;   // the CPU level each step ends on, bit 0 / 1: there is a GPU / CPU step
     uint32_t *udg, *touched, *stamp, *first, *keep_ci, *np, *tmp_off, *tier;
     int32_t *keep_gi;
-    unsigned long long *udc_g, *udc_c;
+    unsigned long long *udc_c;
     uint32_t *plist;                 // parts of one job: (node, GPUs) pairs, ascending node
-    uint32_t *tmp_parts;             // parts of all jobs, grouped by job, in no order
+    uint32_t *tmp_parts;             // parts of all jobs, (node << 16 | GPUs), grouped by job, in no order
     rk_assign *assign;
     uint32_t *place_off;
     rk_place_entry *entries;
     float *total;
     uint32_t *stats;                 // may be null
-    uint32_t *flags;                 // one word: non-zero when some job's parts are no placement
+    const uint32_t *seg_off;         // the plan table's, or its copy in LDS
+    bool book;                       // k_nd_prepare books the parts on the nodes (the kernel with the nodes in LDS does it itself)
 };
 // What the device code sees: the body by value (registers), the table, grid and curves where the kernel arguments
 // hold them (a copy of the grid's level arrays would live in scratch memory).
@@ -86,23 +92,23 @@ __device__ __forceinline__ uint32_t nd_cpl(const NdArgs &A, uint32_t lvl) { retu
 // where job `job` is in node n's list, -1: not there
 __device__ __forceinline__ int nd_find(const NdArgs &A, uint32_t n, uint32_t job) {
     const uint32_t c = A.cnt[n];
-    const uint32_t *rj = A.res_job + (size_t)n * A.gpn;
+    const uint32_t *r = A.res + (size_t)n * A.gpn;
     for (uint32_t i = 0; i < c; ++i)
-        if (rj[i] == job) return (int)i;
+        if ((r[i] >> 16) == job) return (int)i;
     return -1;
 }
 __device__ __forceinline__ uint32_t nd_part(const NdArgs &A, uint32_t n, uint32_t job) {
     const int i = nd_find(A, n, job);
-    return i < 0 ? 0u : A.res_k[(size_t)n * A.gpn + (uint32_t)i];
+    return i < 0 ? 0u : A.res[(size_t)n * A.gpn + (uint32_t)i] & 0xFFFFu;
 }
 // job takes k free GPUs of node n, each with per_gpu CPUs (the caller has checked that they are free)
 __device__ __forceinline__ void nd_add(const NdArgs &A, uint32_t n, uint32_t job, uint32_t k, uint32_t per_gpu) {
     A.free_g[n] -= k; A.free_c[n] -= k * per_gpu;
     const size_t base = (size_t)n * A.gpn;
     const int i = nd_find(A, n, job);
-    if (i >= 0) { A.res_k[base + (uint32_t)i] += k; return; }
+    if (i >= 0) { A.res[base + (uint32_t)i] += k; return; }
     const uint32_t c = A.cnt[n];
-    if (c < A.gpn) { A.res_job[base + c] = job; A.res_k[base + c] = k; A.cnt[n] = c + 1u; }   // (always: a resident holds a GPU)
+    if (c < A.gpn) { A.res[base + c] = (job << 16) | k; A.cnt[n] = c + 1u; }   // (always: a resident holds a GPU)
 }
 // job gives k GPUs of node n back, each with per_gpu CPUs
 __device__ __forceinline__ void nd_drop(const NdArgs &A, uint32_t n, uint32_t job, uint32_t k, uint32_t per_gpu) {
@@ -110,10 +116,10 @@ __device__ __forceinline__ void nd_drop(const NdArgs &A, uint32_t n, uint32_t jo
     if (i < 0) return;
     const size_t base = (size_t)n * A.gpn;
     A.free_g[n] += k; A.free_c[n] += k * per_gpu;
-    const uint32_t left = A.res_k[base + (uint32_t)i] - k;
-    if (left) { A.res_k[base + (uint32_t)i] = left; return; }
+    const uint32_t left = (A.res[base + (uint32_t)i] & 0xFFFFu) - k;
+    if (left) { A.res[base + (uint32_t)i] = (job << 16) | left; return; }
     const uint32_t c = A.cnt[n] - 1u;
-    A.res_job[base + (uint32_t)i] = A.res_job[base + c]; A.res_k[base + (uint32_t)i] = A.res_k[base + c];
+    A.res[base + (uint32_t)i] = A.res[base + c];
     A.cnt[n] = c;
 }
 // GetLowestSlopeOverMinJob(n, resType): lowest cached slope among the residents of n other than j (infinite: gives
@@ -123,9 +129,9 @@ __device__ __forceinline__ float nd_lowest_on(const NdArgs &A, uint32_t n, uint3
     float best = INF;
     who = ND_NONE;
     const uint32_t c = A.cnt[n];
-    const uint32_t *rj = A.res_job + (size_t)n * A.gpn;
+    const uint32_t *r = A.res + (size_t)n * A.gpn;
     for (uint32_t i = 0; i < c; ++i) {
-        const uint32_t v = rj[i];
+        const uint32_t v = r[i] >> 16;
         if (v == j) continue;
         const float s = ds[v];
         if (s < best || (s == best && s < INF && v < who)) { best = s; who = v; }
@@ -138,11 +144,11 @@ __device__ __forceinline__ float nd_lowest_on_wave(const NdArgs &A, uint32_t n, 
                                                    uint32_t lane) {
     const float INF = __int_as_float(0x7F800000);
     const uint32_t c = A.cnt[n];
-    const uint32_t *rj = A.res_job + (size_t)n * A.gpn;
+    const uint32_t *r = A.res + (size_t)n * A.gpn;
     unsigned long long low = ~0ull;                          // (slope as a word that orders like it, job)
     for (uint32_t b = 0; b < c; b += 64u) {
         const uint32_t i = b + lane;
-        const uint32_t v = i < c ? rj[i] : j;
+        const uint32_t v = i < c ? r[i] >> 16 : j;
         const float s = v != j ? ds[v] : INF;
         const unsigned long long key = ((unsigned long long)rs_ordered(s) << 32) | v;
         if (s < INF && key < low) low = key;
@@ -160,18 +166,16 @@ __device__ __forceinline__ void nd_refresh(const NdArgs &A, uint32_t v, uint32_t
     if (lane != 0) return;
     A.ds_g[v] = a.any ? a.slope : __int_as_float(0x7F800000);
     A.ds_c[v] = b.any ? b.slope : __int_as_float(0x7F800000);
-    A.ug[v] = ug.any ? ug.slope : 0.f; A.udg[v] = (uint32_t)ug.dg; A.udc_g[v] = ug.dc;   // (a step that exists has its slope here)
+    A.ug[v] = ug.any ? ug.slope : 0.f; A.udg[v] = (uint32_t)ug.dg;   // (a step that exists has its slope here)
     A.uc[v] = uc.any ? uc.slope : 0.f; A.udc_c[v] = uc.dc;
     A.gain_g[v] = ug.gain; A.gain_c[v] = uc.gain; A.tgt_g[v] = ug.tgt; A.lvl_g[v] = ug.lvl; A.lvl_c[v] = uc.lvl;
     A.any[v] = (ug.any ? 1u : 0u) | (uc.any ? 2u : 0u);
 }
 // nd_refresh for a whole wavefront: a job of at most 64 amounts that is not below its floor has its rows loaded at
 // once, an amount per lane, and every step comes from the registers (rs_rows)
-__device__ __forceinline__ void nd_refresh_wave(const NdArgs &A, uint32_t v, uint32_t lane) {
-    const int32_t gi = A.st.gi[v];
-    const uint32_t ci = A.st.ci[v];
+__device__ __forceinline__ void nd_refresh_wave(const NdArgs &A, uint32_t v, int32_t gi, uint32_t ci, uint32_t lane) {
     const int32_t fl = rs_fl_s(A, v);
-    const uint32_t so = A.X.tb.seg_off[v], ns = A.X.tb.seg_off[v + 1] - so;
+    const uint32_t so = A.seg_off[v], ns = A.seg_off[v + 1] - so;
     if (ns > 64u || (fl >= 0 && gi < fl)) { nd_refresh(A, v, lane, 64); return; }
     const RsRows R = rs_rows(A, v, so, ns, gi, ci, lane);
     const RsGive a = rs_down_gpu_rows(A, R, R.curve, gi, ci, lane);
@@ -180,7 +184,7 @@ __device__ __forceinline__ void nd_refresh_wave(const NdArgs &A, uint32_t v, uin
     if (lane != 0) return;
     A.ds_g[v] = a.any ? a.slope : __int_as_float(0x7F800000);
     A.ds_c[v] = b.any ? b.slope : __int_as_float(0x7F800000);
-    A.ug[v] = ug.any ? ug.slope : 0.f; A.udg[v] = (uint32_t)ug.dg; A.udc_g[v] = ug.dc;
+    A.ug[v] = ug.any ? ug.slope : 0.f; A.udg[v] = (uint32_t)ug.dg;
     A.uc[v] = uc.any ? uc.slope : 0.f; A.udc_c[v] = uc.dc;
     A.gain_g[v] = ug.gain; A.gain_c[v] = uc.gain; A.tgt_g[v] = ug.tgt; A.lvl_g[v] = ug.lvl; A.lvl_c[v] = uc.lvl;
     A.any[v] = (ug.any ? 1u : 0u) | (uc.any ? 2u : 0u);
@@ -190,7 +194,7 @@ __device__ __forceinline__ RsStep nd_cached_step(const NdArgs &A, uint32_t j, ui
     RsStep st;
     if (res == 0) {
         st.any = A.any[j] & 1u; st.tgt = A.tgt_g[j]; st.lvl = A.lvl_g[j]; st.slope = A.ug[j]; st.gain = A.gain_g[j];
-        st.dg = A.udg[j]; st.dc = A.udc_g[j];
+        st.dg = A.udg[j]; st.dc = 0ull;        // (a GPU step's CPUs come with its GPUs)
     } else {
         st.any = (A.any[j] >> 1) & 1u; st.tgt = A.st.gi[j]; st.lvl = A.lvl_c[j]; st.slope = A.uc[j]; st.gain = A.gain_c[j];
         st.dg = 0ull; st.dc = A.udc_c[j];
@@ -198,59 +202,754 @@ __device__ __forceinline__ RsStep nd_cached_step(const NdArgs &A, uint32_t j, ui
     return st;
 }
 
-// The nodes, all free and empty.
+// The nodes, all free and empty (for k_reschedule_nodes).
 __global__ void k_nd_init(NdKernArgs K) {
     const NdArgs A(K.b, K.X);
     const uint32_t n = blockIdx.x * blockDim.x + threadIdx.x;
     if (n < A.n_nodes) { A.free_g[n] = A.gpn; A.free_c[n] = A.cpn; A.cnt[n] = 0u; }
-    if (n == 0) A.flags[0] = 0u;
 }
 
-// Every job on its own, any number of workgroups: what it holds, whether it comes first, its parts booked on the
-// nodes (atomics; a node that ends up holding more than it has is seen by the main kernel), its cached slopes.
+// Every job on its own, a wavefront per job: what it holds, whether it comes first (bit 0 of `first`), whether its
+// parts are a placement (bit 1: they are not), its cached slopes; with A.book its parts are booked on the nodes (atomics;
+// a node that ends up holding more than it has is seen by the main kernel).
 __global__ void k_nd_prepare(NdKernArgs K) {
     const NdArgs A(K.b, K.X);
-    const uint32_t j = blockIdx.x * blockDim.x + threadIdx.x;
+    const uint32_t j = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, lane = threadIdx.x & 63u;
     if (j >= A.n_jobs) return;
     const uint32_t N = A.n_nodes;
     int32_t gi = -1;
     uint32_t ci = 0;
-    if (rs_holds(A, j) && A.cur_seg[j] >= 0 && (uint32_t)A.cur_seg[j] < rs_ns(A, j) && A.cur_c[j] < A.X.grid.n_cpu) {
-        gi = A.cur_seg[j]; ci = A.cur_c[j];
-    }
-    A.st.gi[j] = gi; A.st.ci[j] = ci;
-    A.stamp[j] = 0u;
+    const int32_t seg = A.cur_seg[j];
+    const uint32_t lvl = A.cur_c[j];
+    if (rs_holds(A, j) && seg >= 0 && (uint32_t)seg < rs_ns(A, j) && lvl < A.X.grid.n_cpu) { gi = seg; ci = lvl; }
     const int32_t fl = rs_fl_s(A, j);
-    A.first[j] = (rs_part(A, j) && fl >= 0 && gi < fl) ? 1u : 0u;
+    bool good = true;
     if (gi >= 0) {
-        bool good = A.prev_off != nullptr && A.prev_entries != nullptr;
+        good = A.prev_off != nullptr && A.prev_entries != nullptr;
+        const uint32_t a = good ? A.prev_off[j] : 0u, b = good ? A.prev_off[j + 1] : 0u;
+        if (a > b || b > A.n_prev) good = false;
         if (good) {
             const uint32_t per_gpu = nd_cpl(A, ci);
-            const uint32_t a = A.prev_off[j], b = A.prev_off[j + 1];
-            if (a > b || b > A.n_prev) good = false;
             unsigned long long sum = 0;
-            long long last = -1;
-            for (uint32_t i = a; i < b && good; ++i) {
+            bool ok = true;
+            for (uint32_t i = a + lane; i < b; i += 64u) {
                 const rk_place_entry e = A.prev_entries[i];
+                const long long last = i > a ? (long long)A.prev_entries[i - 1].node : -1;
                 if (e.node >= N || (long long)e.node <= last || e.g == 0u || e.g > A.gpn || e.c > A.cpn ||
-                    (unsigned long long)e.c != (unsigned long long)per_gpu * e.g) { good = false; break; }
-                last = e.node; sum += e.g;
+                    (unsigned long long)e.c != (unsigned long long)per_gpu * e.g) ok = false;
+                sum += e.g;
             }
-            if (good && sum != rs_g(A, j, gi)) good = false;
-            for (uint32_t i = a; i < b && good; ++i) {
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off, 64);
+            good = __ballot(!ok) == 0ull && sum == rs_g(A, j, gi);
+        }
+        if (good && A.book)
+            for (uint32_t i = a + lane; i < b; i += 64u) {
                 const rk_place_entry e = A.prev_entries[i];
                 const uint32_t slot = atomicAdd(&A.cnt[e.node], 1u);
-                if (slot < A.gpn) {
-                    A.res_job[(size_t)e.node * A.gpn + slot] = j; A.res_k[(size_t)e.node * A.gpn + slot] = e.g;
-                }
+                if (slot < A.gpn) A.res[(size_t)e.node * A.gpn + slot] = (j << 16) | e.g;
                 // (wraps below zero when the node holds more than it has; the main kernel sees that)
                 atomicSub(&A.free_g[e.node], e.g);
                 atomicSub(&A.free_c[e.node], e.c);
             }
-        }
-        if (!good) atomicOr(&A.flags[0], 1u);
     }
-    nd_refresh(A, j, 0, 1);
+    if (lane == 0) {
+        A.st.gi[j] = gi; A.st.ci[j] = ci;
+        A.first[j] = ((rs_part(A, j) && fl >= 0 && gi < fl) ? 1u : 0u) | (good ? 0u : 2u);
+    }
+    asm volatile("" ::: "memory");               // (nd_refresh's other lanes read what the first one stored)
+    nd_refresh_wave(A, j, gi, ci, lane);
+}
+
+// exclusive prefix sum over the threads of the workgroup (thread order) and the sum of all; all threads call it
+template <int THREADS>
+__device__ __forceinline__ uint32_t nd_block_scan(uint32_t val, uint32_t &all, uint32_t *sh_scan) {
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    uint32_t inc = val;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t o = __shfl_up(inc, off, 64);
+        if ((int)lane >= off) inc += o;
+    }
+    if (lane == 63) sh_scan[wave] = inc;
+    __syncthreads();
+    uint32_t base = 0;
+    all = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < THREADS / 64; ++w) { const uint32_t x = sh_scan[w]; if (w < wave) base += x; all += x; }
+    __syncthreads();
+    return base + inc - val;
+}
+
+// Nothing is scheduled: the state is no placement on these nodes.
+template <int THREADS>
+__device__ __forceinline__ void nd_refuse(const NdArgs &A) {
+    for (uint32_t j = threadIdx.x; j < A.n_jobs; j += THREADS) {
+        A.assign[j] = rk_assign{0u, 0u, 0.f, RK_NO_PLAN, 0.f};
+        A.place_off[j] = 0u;
+    }
+    if (threadIdx.x == 0) {
+        A.place_off[A.n_jobs] = 0u; *A.total = 0.f;
+        if (A.stats) { A.stats[0] = 0u; A.stats[1] = 0u; A.stats[2] = 0u; A.stats[3] = 0u; A.stats[4] = 1u; }
+    }
+}
+
+// Memory, then the records, from what the jobs hold and who is on the nodes.  np and off [n_jobs], parts [GPUs of all
+// nodes], tier and touched [n_jobs] and mem [n_nodes] are working memory, in LDS or not.  All threads call it.
+template <int THREADS>
+__device__ __forceinline__ void nd_finish(const NdArgs &A, uint32_t *np, uint32_t *off, uint32_t *parts, float *mem, uint32_t *sh_scan) {
+    constexpr uint32_t WAVES = THREADS / 64;
+    __shared__ uint32_t sh_fit, sh_wide;
+    __shared__ double sh_sum[WAVES];
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    const uint32_t J = A.n_jobs, N = A.n_nodes, gpus = N * A.gpn;
+    __syncthreads();
+    for (uint32_t j = tid; j < J; j += THREADS) np[j] = 0u;
+    for (uint32_t n = tid; n < N; n += THREADS) mem[n] = 0.f;
+    if (tid == 0) { sh_fit = A.gpn <= 4096u ? 1u : 0u; sh_wide = 0u; }       // sh_wide: jobs with many parts (their list: `touched`)
+    __syncthreads();
+    // the parts of all jobs, grouped by job (in no order yet): an entry of the nodes' tables per thread
+    for (uint32_t i = tid; i < gpus; i += THREADS) {
+        const uint32_t n = i / A.gpn;
+        if (i - n * A.gpn < A.cnt[n]) atomicAdd(&np[A.res[i] >> 16], 1u);
+    }
+    __syncthreads();
+    const uint32_t jobs_per_thread = (J + THREADS - 1) / THREADS;
+    {
+        uint32_t local = 0, all;
+        for (uint32_t i = 0; i < jobs_per_thread; ++i) {
+            const uint32_t j = tid * jobs_per_thread + i;
+            if (j < J) local += np[j];
+        }
+        uint32_t at = nd_block_scan<THREADS>(local, all, sh_scan);
+        for (uint32_t i = 0; i < jobs_per_thread; ++i) {
+            const uint32_t j = tid * jobs_per_thread + i;
+            if (j < J) { off[j] = at; at += np[j]; }
+        }
+    }
+    __syncthreads();
+    for (uint32_t i = tid; i < gpus; i += THREADS) {                         // (moves off[j] to the end of job j's parts)
+        const uint32_t n = i / A.gpn;
+        if (i - n * A.gpn < A.cnt[n]) {
+            const uint32_t word = A.res[i];
+            parts[atomicAdd(&off[word >> 16], 1u)] = (n << 16) | (word & 0xFFFFu);
+        }
+    }
+    __syncthreads();
+    const uint64_t rows = (uint64_t)A.X.grid.n_cpu * A.X.grid.n_mem;
+    auto tier_cost = [&](uint32_t m, uint32_t g) {
+        float v = A.X.grid.mem_levels_gb[m];
+        if (A.X.grid.mem_mode) v = v * (float)g;
+        return v;
+    };
+    auto slot_of = [&](uint32_t j, uint32_t m) {                             // of what job j holds, at tier m, in the curves' layout
+        const uint32_t so = A.seg_off[j], ns = A.seg_off[j + 1] - so;
+        return rows * so + ((uint64_t)A.st.ci[j] * A.X.grid.n_mem + m) * ns + (uint32_t)A.st.gi[j];
+    };
+    auto gpus_of = [&](uint32_t j) { return A.X.tb.seg_g[A.seg_off[j] + (uint32_t)A.st.gi[j]]; };
+    // the tier every job would like (highest throughput, smallest such tier), and what that asks of the nodes
+    for (uint32_t j = tid; j < J; j += THREADS) {
+        uint32_t bm = ND_NONE;
+        if (A.st.gi[j] >= 0) {
+            float bv = 0.f;
+            for (uint32_t m = 0; m < A.X.grid.n_mem; ++m) {
+                const float v = A.X.best_thr[slot_of(j, m)];
+                if (v > bv) { bv = v; bm = m; }
+            }
+            if (bm != ND_NONE) {
+                const uint32_t g = gpus_of(j);
+                const float cost = tier_cost(bm, g);
+                for (uint32_t i = off[j] - np[j]; i < off[j]; ++i)
+                    atomicAdd(&mem[parts[i] >> 16], (cost * (float)(parts[i] & 0xFFFFu)) / (float)g);
+            }
+        }
+        A.tier[j] = bm;
+    }
+    __syncthreads();
+    for (uint32_t n = tid; n < N; n += THREADS)
+        if (!(mem[n] <= A.mem_gb * 0.999f)) atomicAnd(&sh_fit, 0u);
+    __syncthreads();
+    if (!sh_fit) {                                           // some node's memory can bind: job by job, in order
+        for (uint32_t n = tid; n < N; n += THREADS) mem[n] = A.mem_gb;
+        __syncthreads();
+        if (wave == 0) {
+            for (uint32_t j = 0; j < J; ++j) {
+                if (A.st.gi[j] < 0) continue;
+                const uint32_t g = gpus_of(j);
+                const uint32_t P = np[j], a = off[j] - P;
+                float bv = 0.f;
+                uint32_t bm = ND_NONE;
+                for (uint32_t m = 0; m < A.X.grid.n_mem; ++m) {
+                    const float cost = tier_cost(m, g);
+                    bool bad = false;
+                    for (uint32_t i = lane; i < P; i += 64u)
+                        if (!((cost * (float)(parts[a + i] & 0xFFFFu)) / (float)g <= mem[parts[a + i] >> 16])) bad = true;
+                    if (__ballot(bad)) continue;
+                    const float v = A.X.best_thr[slot_of(j, m)];
+                    if (v > bv) { bv = v; bm = m; }
+                }
+                if (bm != ND_NONE) {
+                    const float cost = tier_cost(bm, g);
+                    for (uint32_t i = lane; i < P; i += 64u) {
+                        const uint32_t n = parts[a + i] >> 16;
+                        mem[n] = mem[n] - (cost * (float)(parts[a + i] & 0xFFFFu)) / (float)g;
+                    }
+                }
+                if (lane == 0) A.tier[j] = bm;
+                asm volatile("" ::: "memory");   // (the next job's lanes read what these ones stored)
+            }
+        }
+        __syncthreads();
+    }
+    // the records: a job's parts in node order
+    {
+        uint32_t local = 0, all;
+        for (uint32_t i = 0; i < jobs_per_thread; ++i) {
+            const uint32_t j = tid * jobs_per_thread + i;
+            if (j < J && A.tier[j] != ND_NONE) local += np[j];
+        }
+        uint32_t at = nd_block_scan<THREADS>(local, all, sh_scan);
+        for (uint32_t i = 0; i < jobs_per_thread; ++i) {
+            const uint32_t j = tid * jobs_per_thread + i;
+            if (j >= J) break;
+            A.place_off[j] = at;
+            if (A.tier[j] != ND_NONE) at += np[j];
+        }
+        if (tid == 0) A.place_off[J] = all;
+    }
+    __syncthreads();
+    double sum = 0.0;
+    for (uint32_t j = tid; j < J; j += THREADS) {
+        rk_assign out = {0u, 0u, 0.f, RK_NO_PLAN, 0.f};
+        const uint32_t m = A.tier[j];
+        if (m != ND_NONE) {
+            const uint32_t g = gpus_of(j);
+            const uint32_t per_gpu = nd_cpl(A, A.st.ci[j]);
+            const float cost = tier_cost(m, g);
+            out.g = g; out.c = per_gpu * g; out.mem_gb = cost;
+            out.plan = A.X.best_plan[slot_of(j, m)];
+            out.thr = A.X.best_thr[slot_of(j, m)];
+            sum += (double)out.thr / (double)A.X.ref_thr[j];
+            const uint32_t P = np[j], a = off[j] - P, to = A.place_off[j];
+            if (P <= 8u) {                                   // few parts: this thread ranks them
+                for (uint32_t i = 0; i < P; ++i) {
+                    const uint32_t node = parts[a + i] >> 16, k = parts[a + i] & 0xFFFFu;
+                    uint32_t rank = 0;
+                    for (uint32_t q = 0; q < P; ++q) rank += (parts[a + q] >> 16) < node ? 1u : 0u;
+                    A.entries[to + rank] = rk_place_entry{node, k, per_gpu * k, (cost * (float)k) / (float)g};
+                }
+            } else {
+                A.touched[atomicAdd(&sh_wide, 1u)] = j;
+            }
+        }
+        A.assign[j] = out;
+    }
+    __syncthreads();
+    const uint32_t n_wide = sh_wide;
+    for (uint32_t w = wave; w < n_wide; w += WAVES) {         // many parts: a wavefront ranks them
+        const uint32_t j = A.touched[w];
+        const uint32_t m = A.tier[j], P = np[j];
+        const uint32_t g = gpus_of(j);
+        const uint32_t per_gpu = nd_cpl(A, A.st.ci[j]);
+        const float cost = tier_cost(m, g);
+        const uint32_t a = off[j] - P, to = A.place_off[j];
+        for (uint32_t i = lane; i < P; i += 64u) {
+            const uint32_t node = parts[a + i] >> 16, k = parts[a + i] & 0xFFFFu;
+            uint32_t rank = 0;
+            for (uint32_t q = 0; q < P; ++q) rank += (parts[a + q] >> 16) < node ? 1u : 0u;
+            A.entries[to + rank] = rk_place_entry{node, k, per_gpu * k, (cost * (float)k) / (float)g};
+        }
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) sum += __shfl_xor(sum, o, 64);
+    if (lane == 0) sh_sum[wave] = sum;
+    __syncthreads();
+    if (tid == 0) {
+        double s = 0.0;
+        for (uint32_t w = 0; w < WAVES; ++w) s += sh_sum[w];
+        *A.total = (float)s;
+    }
+}
+
+// Inclusive prefix sum over the wavefront: within rows of 16 lanes by row shifts, then each row's sum is broadcast to
+// the rows behind it.  All 64 lanes must be active.
+__device__ __forceinline__ uint32_t nd_wave_scan(uint32_t v) {
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);     // row_shr:1
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);     // row_shr:2
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);     // row_shr:4
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);     // row_shr:8
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);     // row_bcast:15 into rows 1 and 3
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);     // row_bcast:31 into rows 2 and 3
+    return v;
+}
+__device__ __forceinline__ uint32_t nd_wave_sum(uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)nd_wave_scan(v), 63); }
+
+// What the lanes of a wavefront stored so far is seen by all its lanes from here on: the hardware keeps a wavefront's
+// accesses in order, so only the compiler has to.
+__device__ __forceinline__ void nd_wave_order() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// Words of dynamic LDS that k_nodes_lds needs: the nodes and their copy, the cached slopes, memory, and (LJ) everything
+// else a job has.
+constexpr uint32_t ND_LDS_JOB_WORDS = 24;
+static inline size_t nd_lds_words(size_t J, size_t N, size_t nodes_words, bool lj) {
+    return 2 * nodes_words + 2 * J + N + (lj ? ND_LDS_JOB_WORDS * J + 1 : 0);
+}
+
+// The loop with the nodes in LDS.  It is a chain of small decisions, so what bounds it is the latency of one after
+// the other.  Here the first wavefront makes a whole step of ScheduleJob by itself, a node per lane on the walk, a
+// resident per lane where somebody is shrunk, 64 entries of the nodes' tables at a time where a job's parts are
+// looked up: nothing is exchanged between wavefronts within a step, every table it reads and writes is in LDS, and
+// what the others do (the look for the next job, the slopes of the jobs that a step changed, the copy of the nodes)
+// stands between two barriers after it.  LJ: what the jobs hold and their cached steps are in LDS too.
+template <int THREADS, bool LJ>
+__global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
+    extern __shared__ uint4 sh_raw[];
+    constexpr uint32_t WAVES = THREADS / 64;
+    __shared__ uint32_t sh_scan[WAVES], sh_take[RK_MAX_CPU_LEVELS], sh_free_c, sh_cpl[RK_MAX_CPU_LEVELS];
+    __shared__ unsigned long long sh_pick_key[WAVES + 1];
+    __shared__ uint32_t sh_pick_j[WAVES + 1];
+    __shared__ unsigned long long sh_two_k[2 * (WAVES + 1)];
+    __shared__ uint32_t sh_two_s[2 * (WAVES + 1)];
+    __shared__ RsMin sh_min[2];
+    __shared__ uint32_t sh_did, sh_touched;                 // what the first wavefront's steps ended in
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    NdArgs A(K.b, K.X);
+    const uint32_t J = A.n_jobs, N = A.n_nodes, gpn = A.gpn, gpus = N * gpn;
+    const float INF = __int_as_float(0x7F800000);
+
+    // ---- everything into LDS
+    uint32_t *const nodes = reinterpret_cast<uint32_t *>(sh_raw);
+    uint32_t *const keep = nodes + A.nodes_words;
+    uint32_t *at = keep + A.nodes_words;
+    auto take = [&](size_t words) { uint32_t *p = at; at += words; return p; };
+    A.free_g = nodes; A.free_c = nodes + N; A.cnt = nodes + 2 * N; A.res = nodes + 3 * N;
+    unsigned long long *const sh_udc = LJ ? reinterpret_cast<unsigned long long *>(take(2 * (size_t)J)) : nullptr;
+    float *const sh_ds = reinterpret_cast<float *>(take(2 * (size_t)J));
+    float *const sh_mem = reinterpret_cast<float *>(take(N));
+    for (uint32_t i = tid; i < A.nodes_words; i += THREADS) nodes[i] = i < N ? gpn : i < 2 * N ? A.cpn : i < 3 * N ? 0u : ND_NONE;
+    if (tid < A.X.grid.n_cpu) sh_cpl[tid] = A.X.grid.cpu_levels[tid];
+    if constexpr (LJ) {
+        for (uint32_t j = tid; j < J; j += THREADS) sh_udc[j] = A.udc_c[j];
+        A.udc_c = sh_udc;
+        auto load = [&](auto &p) {                           // a per-job array of words moves to LDS
+            auto *q = reinterpret_cast<std::decay_t<decltype(p)>>(take(J));
+            for (uint32_t j = tid; j < J; j += THREADS) q[j] = p[j];
+            p = q;
+        };
+        load(A.st.gi); load(A.st.ci); load(A.ug); load(A.uc); load(A.udg); load(A.gain_g); load(A.gain_c);
+        load(A.tgt_g); load(A.lvl_g); load(A.lvl_c); load(A.any); load(A.first);
+        A.sg = reinterpret_cast<float *>(take(J)); A.sc = reinterpret_cast<float *>(take(J));
+        A.stamp = take(J); A.keep_gi = reinterpret_cast<int32_t *>(take(J)); A.keep_ci = take(J);
+        A.keep_ds = reinterpret_cast<float *>(take(2 * (size_t)J)); A.touched = take(J); A.tier = take(J);
+        uint32_t *const so = take((size_t)J + 1);
+        for (uint32_t j = tid; j <= J; j += THREADS) so[j] = A.X.tb.seg_off[j];
+        A.seg_off = so;
+    }
+    uint32_t bad = 0, any_first = 0;
+    for (uint32_t j = tid; j < J; j += THREADS) {
+        sh_ds[j] = A.ds_g[j]; sh_ds[J + j] = A.ds_c[j];
+        A.stamp[j] = 0u;
+        bad |= A.first[j] & 2u; any_first |= A.first[j] & 1u;
+    }
+    A.ds_g = sh_ds; A.ds_c = sh_ds + J;
+    __syncthreads();
+    for (uint32_t j0 = tid; j0 < J; j0 += 4 * THREADS) {     // the jobs' parts are booked, four jobs' offsets in flight
+        uint32_t a[4], b[4];
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) {
+            const uint32_t j = j0 + k * THREADS;
+            const bool holds = j < J && A.st.gi[j] >= 0 && !(A.first[j] & 2u);
+            a[k] = holds ? A.prev_off[j] : 0u;
+            b[k] = holds ? A.prev_off[j + 1] : 0u;
+        }
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k)
+            for (uint32_t i = a[k]; i < b[k]; ++i) {         // (checked by k_nd_prepare: the node is one, e.g <= gpn)
+                const rk_place_entry e = A.prev_entries[i];
+                const uint32_t slot = atomicAdd(&A.cnt[e.node], 1u);
+                if (slot < gpn) A.res[e.node * gpn + slot] = ((j0 + k * THREADS) << 16) | e.g;
+                atomicSub(&A.free_g[e.node], e.g);           // (wraps below zero when the node holds more than it has)
+                atomicSub(&A.free_c[e.node], e.c);
+            }
+    }
+    __syncthreads();
+    for (uint32_t n = tid; n < N; n += THREADS)
+        if (A.cnt[n] > gpn || A.free_g[n] > gpn || A.free_c[n] > A.cpn) bad |= 1u;
+    if (__syncthreads_or((int)bad)) { nd_refuse<THREADS>(A); return; }
+    const bool with_first = __syncthreads_or((int)any_first) != 0;
+    auto copy_nodes = [&](uint32_t *to, const uint32_t *from) {          // (nodes_words is a multiple of four)
+        const uint4 *src = reinterpret_cast<const uint4 *>(from);
+        uint4 *dst = reinterpret_cast<uint4 *>(to);
+        for (uint32_t i = tid; i < A.nodes_words / 4u; i += THREADS) dst[i] = src[i];
+    };
+    copy_nodes(keep, nodes);
+    __syncthreads();
+
+    // ---- the first wavefront's part: a step of ScheduleJob.  Values without a lane are the same in all lanes.
+    uint32_t moves = 0, full = 0, shrinks = 0, undone = 0, epoch = 0;        // (the first wavefront's counts)
+    uint32_t touched = 0;                                    // jobs this step has changed so far
+    float lost = 0.f;
+    bool dirty = false;                                      // the nodes are not as they were when the step began
+    auto remember = [&](uint32_t v, int32_t gi, uint32_t ci, uint32_t stamp) {       // (of job v before the step)
+        if (stamp == epoch) return;
+        if (lane == 0) {
+            A.stamp[v] = epoch;
+            A.keep_gi[v] = gi; A.keep_ci[v] = ci;
+            A.keep_ds[2 * v] = A.ds_g[v]; A.keep_ds[2 * v + 1] = A.ds_c[v];
+            A.touched[touched] = v;
+        }
+        touched += 1u;
+    };
+    auto put_jobs_back = [&]() {
+        nd_wave_order();
+        for (uint32_t i = lane; i < touched; i += 64u) {
+            const uint32_t v = A.touched[i];
+            A.st.gi[v] = A.keep_gi[v]; A.st.ci[v] = A.keep_ci[v];
+            A.ds_g[v] = A.keep_ds[2 * v]; A.ds_c[v] = A.keep_ds[2 * v + 1];
+        }
+        undone += touched ? 1u : 0u;
+    };
+    // job v's entries of the nodes' tables in ascending order: what(mask of lanes that have one, first entry of the chunk, entry)
+    auto for_parts = [&](uint32_t v, auto what) {
+        for (uint32_t b = 0; b < gpus; b += 64u) {
+            const uint32_t word = b + lane < gpus ? A.res[b + lane] : ND_NONE;
+            const unsigned long long m = __ballot((word >> 16) == v);
+            if (m && !what(m, b, word)) return;
+        }
+    };
+    enum : uint32_t { DID_NOTHING = 0, DID_GPUS = 1, DID_CPUS = 2, DID_UNDO = 4 };
+    // A GPU step of job j: DID_GPUS when it is committed, else DID_NOTHING (jobs put back; the nodes are `dirty` or as before)
+    auto gpu_step = [&](uint32_t j) -> uint32_t {
+        dirty = false;
+        const RsStep st = nd_cached_step(A, j, 0);
+        if (!st.any) return DID_NOTHING;
+        epoch += 1u; touched = 0u; lost = 0.f;
+        const int32_t fl = rs_fl_s(A, j), gi_j = A.st.gi[j];
+        const uint32_t ci_j = A.st.ci[j];
+        const bool below_min = fl >= 0 && gi_j < fl;
+        const uint32_t per_gpu = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh_cpl[st.lvl]);
+        uint32_t lack = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)st.dg);
+        bool ok = true;
+        if (gi_j >= 0 && st.lvl != ci_j) {                   // its parts go to the step's level: their CPUs must be free
+            const uint32_t more = per_gpu - sh_cpl[ci_j];
+            dirty = true;
+            for_parts(j, [&](unsigned long long m, uint32_t b, uint32_t word) {
+                bool short_of = false;
+                if ((m >> lane) & 1ull) {
+                    const uint32_t n = (b + lane) / gpn, have = A.free_c[n];
+                    const unsigned long long need = (unsigned long long)more * (word & 0xFFFFu);
+                    if (have < need) short_of = true;
+                    else A.free_c[n] = have - (uint32_t)need;
+                }
+                if (__ballot(short_of)) ok = false;
+                return ok;
+            });
+            nd_wave_order();
+        }
+        uint32_t n0 = 0;
+        while (ok && lack > 0 && n0 < N) {                   // the walk over the nodes, a node per lane
+            const uint32_t n = n0 + lane;
+            const bool in = n < N;
+            uint32_t offer = 0, c = 0;
+            float low = INF;                                 // the lowest slope among the others on the node
+            if (in) {
+                const uint32_t fg = A.free_g[n], by_cpu = A.free_c[n] / per_gpu;
+                offer = fg < by_cpu ? fg : by_cpu;
+                c = A.cnt[n];
+                const uint32_t *r = A.res + n * gpn;
+                for (uint32_t i = 0; i < c; i += 4u) {       // four residents at a time (past the last one: nobody)
+                    uint32_t w[4];
+                    float sl[4];
+#pragma unroll
+                    for (uint32_t k = 0; k < 4; ++k) w[k] = i + k < c ? r[i + k] >> 16 : j;
+#pragma unroll
+                    for (uint32_t k = 0; k < 4; ++k) sl[k] = w[k] != j ? A.ds_g[w[k]] : INF;
+#pragma unroll
+                    for (uint32_t k = 0; k < 4; ++k) low = sl[k] < low ? sl[k] : low;
+                }
+            }
+            const bool ask = low < INF && (below_min || st.slope > low);     // somebody here may be shrunk
+            const uint32_t upto = nd_wave_scan(offer), before = upto - offer;
+            const unsigned long long done_m = __ballot(in && upto >= lack), ask_m = __ballot(ask && upto < lack);
+            const uint32_t done_t = done_m ? (uint32_t)__ffsll((long long)done_m) - 1u : 64u;
+            const uint32_t ask_t = ask_m ? (uint32_t)__ffsll((long long)ask_m) - 1u : 64u;
+            const uint32_t last = done_t < ask_t ? done_t : ask_t;           // the nodes up to here give what they offer
+            if (__ballot(lane <= last && offer > 0u)) dirty = true;
+            if (lane <= last && offer) {
+                const uint32_t k = offer < lack - before ? offer : lack - before;
+                if (gi_j >= 0) nd_add(A, n, j, k, per_gpu);
+                else if (c < gpn) {                          // it is on no node yet, and on a walk's node only once
+                    A.free_g[n] -= k; A.free_c[n] -= k * per_gpu;
+                    A.res[n * gpn + c] = (j << 16) | k; A.cnt[n] = c + 1u;
+                }
+            }
+            const uint32_t got = wave_lane_u32(upto, last < 64u ? last : 63u);
+            lack -= got < lack ? got : lack;
+            nd_wave_order();
+            if (ask_t >= done_t) { n0 += 64u; continue; }    // (nobody to ask; when the step has its GPUs the walk ends)
+            const uint32_t f = n0 + ask_t, base = f * gpn;
+            n0 = f + 1u;
+            while (lack > 0) {                               // node f: a resident per lane (a node has at most 64 here)
+                const uint32_t cf = (uint32_t)__builtin_amdgcn_readfirstlane((int)A.cnt[f]);
+                const uint32_t free_g = A.free_g[f], free_c = A.free_c[f];
+                const uint32_t word = lane < cf ? A.res[base + lane] : ND_NONE;
+                const uint32_t rv = word >> 16;
+                const float sl = lane < cf && rv != j ? A.ds_g[rv] : INF;
+                unsigned long long key = ~0ull;              // (slope as a word that orders like it, job): lower job among equals
+                if (sl < INF) key = ((unsigned long long)rs_ordered(sl) << 32) | rv;
+                key = wave_min_u64_rows(key);
+                if (key == ~0ull || !(below_min || st.slope > rs_unordered((uint32_t)(key >> 32)))) break;
+                const uint32_t who = (uint32_t)key;
+                const int32_t gi0 = __builtin_amdgcn_readfirstlane(A.st.gi[who]);
+                const uint32_t ci0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)A.st.ci[who]);
+                const uint32_t so = (uint32_t)__builtin_amdgcn_readfirstlane((int)A.seg_off[who]);
+                const uint32_t ns = (uint32_t)__builtin_amdgcn_readfirstlane((int)A.seg_off[who + 1]) - so;
+                const uint32_t stamp = A.stamp[who];
+                const RsShrunk sk = rs_shrink_wave(A, who, so, ns, 0, gi0, ci0, lane);
+                const uint32_t slot = (uint32_t)__ffsll((long long)__ballot(lane < cf && rv == who)) - 1u;
+                const uint32_t here_has = wave_lane_u32(word, slot) & 0xFFFFu, per_v = sh_cpl[ci0];
+                const uint32_t dg = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)sk.gv.dg);
+                const uint32_t here = dg < here_has ? dg : here_has;
+                remember(who, gi0, ci0, stamp);
+                dirty = true;
+                shrinks += 1u;
+                lost = lost + sk.gv.loss;
+                // the node afterwards, from what the lanes hold: who gives `here` of its GPUs, j takes what it can
+                const uint32_t fg = free_g + here, fc = free_c + here * per_v;
+                const uint32_t by_cpu = fc / per_gpu, offer2 = fg < by_cpu ? fg : by_cpu;
+                const uint32_t t = offer2 < lack ? offer2 : lack;
+                const bool goes = here == here_has;          // it leaves the node: the last resident takes its entry
+                const uint32_t c1 = cf - (goes ? 1u : 0u);
+                const uint32_t last_word = wave_lane_u32(word, cf - 1u);
+                uint32_t mine = word;
+                if (lane == slot) mine = goes ? last_word : word - here;
+                if (lane >= c1) mine = ND_NONE;
+                const unsigned long long j_m = __ballot(lane < c1 && (mine >> 16) == j);
+                uint32_t c2 = c1;
+                if (t) {
+                    if (j_m) { if ((j_m >> lane) & 1ull) mine += t; }
+                    else if (c1 < gpn) { if (lane == c1) mine = (j << 16) | t; c2 = c1 + 1u; }
+                }
+                if (lane < gpn) A.res[base + lane] = mine;
+                if (lane == 0) {
+                    A.free_g[f] = fg - t; A.free_c[f] = fc - t * per_gpu; A.cnt[f] = c2;
+                    A.st.gi[who] = sk.gi; A.st.ci[who] = sk.ci;
+                    A.ds_g[who] = sk.ds_g; A.ds_c[who] = sk.ds_c;
+                }
+                lack -= t;
+                uint32_t rest = dg - here;
+                nd_wave_order();
+                for (uint32_t e = (gpus + 63u) & ~63u; rest > 0 && e > 0; e -= 64u) {     // the rest from its other parts, the last one first
+                    const uint32_t b = e - 64u;
+                    const uint32_t w = b + lane < gpus ? A.res[b + lane] : ND_NONE;
+                    unsigned long long m = __ballot((w >> 16) == who);
+                    while (m && rest > 0) {
+                        const uint32_t s = 63u - (uint32_t)__clzll((long long)m), i = b + s, n1 = i / gpn;
+                        m &= ~(1ull << s);
+                        const uint32_t k = wave_lane_u32(w, s) & 0xFFFFu, give = k < rest ? k : rest;
+                        if (lane == 0) {
+                            A.free_g[n1] += give; A.free_c[n1] += give * per_v;
+                            if (give < k) A.res[i] = (who << 16) | (k - give);
+                            else {                           // (a job is on a node once: no entry still to come moves)
+                                const uint32_t l = A.cnt[n1] - 1u;
+                                A.res[i] = A.res[n1 * gpn + l];
+                                A.res[n1 * gpn + l] = ND_NONE;
+                                A.cnt[n1] = l;
+                            }
+                        }
+                        rest -= give;
+                    }
+                    nd_wave_order();
+                }
+            }
+        }
+        if (ok && lack == 0u && (below_min || st.gain > lost)) {
+            if (lane == 0) { A.st.gi[j] = st.tgt; A.st.ci[j] = st.lvl; }
+            moves += 1u;
+            return DID_GPUS;
+        }
+        put_jobs_back();
+        return DID_NOTHING;
+    };
+    // A CPU step of job j likewise, on every node the job is on (DID_CPUS)
+    auto cpu_step = [&](uint32_t j) -> uint32_t {
+        dirty = false;
+        const RsStep st = nd_cached_step(A, j, 1);
+        if (!st.any) return DID_NOTHING;
+        epoch += 1u; touched = 0u; lost = 0.f;
+        const uint32_t more = sh_cpl[st.lvl] - sh_cpl[A.st.ci[j]];
+        bool ok = true;
+        for_parts(j, [&](unsigned long long m, uint32_t b, uint32_t word) {
+            while (m && ok) {
+                const uint32_t s = (uint32_t)__ffsll((long long)m) - 1u, n = (b + s) / gpn;
+                m &= m - 1ull;
+                const unsigned long long need = (unsigned long long)more * (wave_lane_u32(word, s) & 0xFFFFu);
+                for (;;) {
+                    const uint32_t free_here = A.free_c[n];
+                    if (free_here >= need) {
+                        if (lane == 0) A.free_c[n] = free_here - (uint32_t)need;
+                        dirty = true;
+                        nd_wave_order();
+                        break;
+                    }
+                    uint32_t who;
+                    const float low = nd_lowest_on_wave(A, n, j, A.ds_c, who, lane);
+                    if (who == ND_NONE || !(st.slope > low)) { ok = false; break; }
+                    const int32_t gi0 = __builtin_amdgcn_readfirstlane(A.st.gi[who]);
+                    const uint32_t ci0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)A.st.ci[who]);
+                    const uint32_t so = A.seg_off[who], ns = A.seg_off[who + 1] - so;
+                    const RsShrunk sk = rs_shrink_wave(A, who, so, ns, 1, gi0, ci0, lane);
+                    remember(who, gi0, ci0, A.stamp[who]);
+                    dirty = true;
+                    shrinks += 1u;
+                    lost = lost + sk.gv.loss;
+                    if (lane == 0) {
+                        A.st.ci[who] = sk.ci;
+                        A.ds_g[who] = sk.ds_g; A.ds_c[who] = sk.ds_c;
+                    }
+                    const uint32_t less = sh_cpl[ci0] - sh_cpl[ci0 - 1u];
+                    for_parts(who, [&](unsigned long long m2, uint32_t b2, uint32_t w2) {    // it gives a level on all its nodes
+                        if ((m2 >> lane) & 1ull) A.free_c[(b2 + lane) / gpn] += less * (w2 & 0xFFFFu);
+                        return true;
+                    });
+                    nd_wave_order();
+                }
+            }
+            return ok;
+        });
+        if (ok && st.gain > lost) {
+            if (lane == 0) A.st.ci[j] = st.lvl;
+            moves += 1u;
+            return DID_CPUS;
+        }
+        put_jobs_back();
+        return DID_NOTHING;
+    };
+
+    // ScheduleJob(j): the first wavefront steps, then all refresh what a committed step changed, or put the nodes back
+    auto schedule_job = [&](uint32_t j) {
+        bool gpus_done = false, done = false;                // (the first wavefront's)
+        for (;;) {
+            if (wave == 0) {
+                uint32_t did = DID_NOTHING;
+                if (!gpus_done) {
+                    did = gpu_step(j);
+                    if (did == DID_NOTHING) {
+                        gpus_done = true;
+                        if (dirty) {                         // (the CPU steps' turn comes when the nodes are back)
+                            did = DID_UNDO;
+                            done = !((A.any[j] >> 1) & 1u);
+                        }
+                    }
+                }
+                if (did == DID_NOTHING) {
+                    did = cpu_step(j);
+                    if (did == DID_NOTHING) { done = true; if (dirty) did = DID_UNDO; }
+                }
+                if (lane == 0) { sh_did = did | (done ? 8u : 0u); sh_touched = touched; }
+            }
+            __syncthreads();
+            const uint32_t did = sh_did, n_touched = sh_touched;
+            if (did & (DID_GPUS | DID_CPUS)) {
+                for (uint32_t i = wave; i <= n_touched; i += WAVES) {            // a wavefront per job whose state changed
+                    const uint32_t v = (uint32_t)__builtin_amdgcn_readfirstlane((int)(i < n_touched ? A.touched[i] : j));
+                    nd_refresh_wave(A, v, __builtin_amdgcn_readfirstlane(A.st.gi[v]), (uint32_t)__builtin_amdgcn_readfirstlane((int)A.st.ci[v]), lane);
+                }
+                copy_nodes(keep, nodes);
+            } else if (did & DID_UNDO) {
+                copy_nodes(nodes, keep);
+            }
+            __syncthreads();
+            if (did & 8u) break;
+        }
+    };
+
+    // ---- privileged jobs (below their floor) come first, in job order: their list (tmp_off serves as the list)
+    uint32_t n_first = 0;
+    if (with_first) {
+        for (uint32_t base = 0; base < J; base += THREADS) {
+            const uint32_t j = base + tid;
+            const bool is = j < J && A.first[j] != 0u;
+            uint32_t all;
+            const uint32_t to = nd_block_scan<THREADS>(is ? 1u : 0u, all, sh_scan);
+            if (is) A.tmp_off[n_first + to] = j;
+            n_first += all;
+        }
+        __syncthreads();
+        for (uint32_t k = 0; k < n_first; ++k) schedule_job((uint32_t)__builtin_amdgcn_readfirstlane((int)A.tmp_off[k]));
+    }
+    // ---- then the others, in an order that is fixed here; jobs with nothing to do are passed over (k_reschedule_nodes
+    // says when that is)
+    for (uint32_t j = tid; j < J; j += THREADS) {
+        const bool in = rs_part(A, j) && !A.first[j];
+        A.sg[j] = in ? A.ug[j] : -1.f;                       // the cached slopes are current; -1: not in the list
+        A.sc[j] = in ? A.uc[j] : -1.f;
+    }
+    auto comes_before = [&](float ga, float ca, uint32_t a, float gb, float cb, uint32_t b) {
+        return ga > gb || (ga == gb && (ca > cb || (ca == cb && a < b)));
+    };
+    float last_g = INF, last_c = INF;
+    uint32_t last_j = 0u;
+    bool fresh = true;                                       // a step was committed since the last look (or this is the first)
+    for (;;) {
+        if (fresh) {
+            RsMin two[2];
+            rs_two_lowest<WAVES, THREADS>(sh_ds, J, tid, lane, wave, sh_two_k, sh_two_s, two);
+            if (tid == 0) { sh_min[0] = two[0]; sh_min[1] = two[1]; }
+            // what the nodes can give at every CPU level, and all free CPUs: a wavefront per sum
+            for (uint32_t l = wave; l <= A.X.grid.n_cpu; l += WAVES) {
+                const uint32_t per_gpu = l < A.X.grid.n_cpu ? sh_cpl[l] : 1u;
+                uint32_t t = 0;
+                for (uint32_t n = lane; n < N; n += 64u) {
+                    const uint32_t by_cpu = A.free_c[n] / per_gpu;
+                    t += l == A.X.grid.n_cpu || by_cpu < A.free_g[n] ? by_cpu : A.free_g[n];
+                }
+                t = nd_wave_sum(t);
+                if (lane == 0) { if (l < A.X.grid.n_cpu) sh_take[l] = t; else sh_free_c = t; }
+            }
+            __syncthreads();
+        }
+        const RsMin mg = sh_min[0], mc = sh_min[1];
+        const uint32_t free_c = sh_free_c;
+        float best_g = -1.f, best_c = -1.f;
+        uint32_t best_j = ND_NONE;
+        for (uint32_t j0 = tid; j0 < J; j0 += 4 * THREADS) {             // four jobs' values in flight
+            float kg[4], kc[4], ug[4], uc[4];
+            uint32_t dg[4], lv[4];
+            unsigned long long dc[4];
+#pragma unroll
+            for (uint32_t k = 0; k < 4; ++k) {
+                const uint32_t j = j0 + k * THREADS;
+                const bool in = j < J;
+                kg[k] = in ? A.sg[j] : -1.f; kc[k] = in ? A.sc[j] : -1.f;
+                ug[k] = in ? A.ug[j] : 0.f; uc[k] = in ? A.uc[j] : 0.f;
+                dg[k] = in ? A.udg[j] : 0u; lv[k] = in ? A.st.ci[j] : 0u; dc[k] = in ? A.udc_c[j] : 0ull;
+            }
+#pragma unroll
+            for (uint32_t k = 0; k < 4; ++k) {
+                const uint32_t j = j0 + k * THREADS;
+                if (kg[k] < 0.f || !comes_before(last_g, last_c, last_j, kg[k], kc[k], j)) continue;
+                const float lowest_g = j == mg.i1 ? mg.m2 : mg.m1, lowest_c = j == mc.i1 ? mc.m2 : mc.m1;
+                const bool gpu_idle = !(ug[k] > 0.f) || (sh_take[lv[k]] < dg[k] && !(ug[k] > lowest_g));
+                const bool cpu_idle = !(uc[k] > 0.f) || (free_c < dc[k] && !(uc[k] > lowest_c));
+                if (gpu_idle && cpu_idle) continue;
+                if (best_j == ND_NONE || comes_before(kg[k], kc[k], j, best_g, best_c, best_j)) { best_g = kg[k]; best_c = kc[k]; best_j = j; }
+            }
+        }
+        const RsPick pick = rs_pick_first<WAVES>(best_g, best_c, best_j, lane, wave, sh_pick_key, sh_pick_j);
+        if (pick.j == ND_NONE) break;
+        last_g = pick.g; last_c = pick.c; last_j = (uint32_t)__builtin_amdgcn_readfirstlane((int)pick.j);
+        full += 1u;
+        const uint32_t before = moves;
+        schedule_job(last_j);
+        fresh = __syncthreads_or(wave == 0 && moves != before) != 0;
+    }
+    nd_finish<THREADS>(A, reinterpret_cast<uint32_t *>(sh_ds), reinterpret_cast<uint32_t *>(sh_ds) + J, keep, sh_mem, sh_scan);
+    if (tid == 0 && A.stats) { A.stats[0] = moves; A.stats[1] = full; A.stats[2] = shrinks; A.stats[3] = undone; A.stats[4] = 0u; }
 }
 
 __global__ __launch_bounds__(ND_THREADS) void k_reschedule_nodes(NdKernArgs K) {
@@ -268,54 +967,32 @@ __global__ __launch_bounds__(ND_THREADS) void k_reschedule_nodes(NdKernArgs K) {
     __shared__ float sh_lost;
     __shared__ unsigned long long sh_pick_key[ND_WAVES + 1];
     __shared__ uint32_t sh_pick_j[ND_WAVES + 1];
-    __shared__ uint32_t sh_widx[ND_WAVES], sh_scan[ND_WAVES];
+    __shared__ uint32_t sh_scan[ND_WAVES];
     __shared__ uint32_t sh_lack, sh_ok, sh_go, sh_touched, sh_epoch, sh_moves, sh_full, sh_shrinks, sh_undone;
-    __shared__ uint32_t sh_vnode, sh_next, sh_v, sh_rest, sh_per_v, sh_flag, sh_np, sh_bad, sh_fit, sh_done, sh_ask;
+    __shared__ uint32_t sh_vnode, sh_next, sh_v, sh_rest, sh_per_v, sh_flag, sh_np, sh_bad, sh_done, sh_ask;
     __shared__ unsigned long long sh_take[RK_MAX_CPU_LEVELS], sh_free_c;
     __shared__ RsMin sh_min[2];
     __shared__ unsigned long long sh_two_k[2 * (ND_WAVES + 1)];
     __shared__ uint32_t sh_two_s[2 * (ND_WAVES + 1)];
-    __shared__ double sh_sum[ND_WAVES];
     __shared__ float sh_mem[RK_MAX_NODES];                  // memory of the nodes: sums of wishes, then what is left
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     const uint32_t J = A.n_jobs, N = A.n_nodes;
     const float INF = __int_as_float(0x7F800000);
     const uint32_t per_thread = (N + ND_THREADS - 1) / ND_THREADS;          // <= ND_PER
 
-    // exclusive prefix sum over the threads of the workgroup (thread order); all threads call it
-    auto block_scan = [&](uint32_t val, uint32_t &all) {
-        uint32_t inc = val;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t o = __shfl_up(inc, off, 64);
-            if ((int)lane >= off) inc += o;
-        }
-        if (lane == 63) sh_scan[wave] = inc;
-        __syncthreads();
-        uint32_t base = 0;
-        all = 0;
-        for (uint32_t w = 0; w < ND_WAVES; ++w) { if (w < wave) base += sh_scan[w]; all += sh_scan[w]; }
-        __syncthreads();
-        return base + inc - val;
-    };
+    auto block_scan = [&](uint32_t val, uint32_t &all) { return nd_block_scan<ND_THREADS>(val, all, sh_scan); };
 
     // ---- the state the jobs are in has been loaded (k_nd_init, k_nd_prepare); no node may hold more than it has
-    if (tid == 0) { sh_bad = A.flags[0]; sh_epoch = 0u; sh_moves = 0u; sh_full = 0u; sh_shrinks = 0u; sh_undone = 0u; }
+    if (tid == 0) { sh_bad = 0u; sh_epoch = 0u; sh_moves = 0u; sh_full = 0u; sh_shrinks = 0u; sh_undone = 0u; }
     __syncthreads();
     for (uint32_t n = tid; n < N; n += ND_THREADS)
         if (A.cnt[n] > A.gpn || A.free_g[n] > A.gpn || A.free_c[n] > A.cpn) atomicOr(&sh_bad, 1u);
-    __syncthreads();
-    if (sh_bad) {                                            // not a placement on these nodes: nothing is scheduled
-        for (uint32_t j = tid; j < J; j += ND_THREADS) {
-            A.assign[j] = rk_assign{0u, 0u, 0.f, RK_NO_PLAN, 0.f};
-            A.place_off[j] = 0u;
-        }
-        if (tid == 0) {
-            A.place_off[J] = 0u; *A.total = 0.f;
-            if (A.stats) { A.stats[0] = 0u; A.stats[1] = 0u; A.stats[2] = 0u; A.stats[3] = 0u; A.stats[4] = 1u; }
-        }
-        return;
+    for (uint32_t j = tid; j < J; j += ND_THREADS) {
+        A.stamp[j] = 0u;
+        if (A.first[j] & 2u) atomicOr(&sh_bad, 1u);
     }
+    __syncthreads();
+    if (sh_bad) { nd_refuse<ND_THREADS>(A); return; }
     // the node tables and their copy, four words at a time, two pieces in flight (nodes_words is a multiple of four)
     auto copy_nodes = [&](uint32_t *to, const uint32_t *from) {
         const uint4 *src = reinterpret_cast<const uint4 *>(from);
@@ -348,6 +1025,7 @@ __global__ __launch_bounds__(ND_THREADS) void k_reschedule_nodes(NdKernArgs K) {
         sh_undone += sh_touched ? 1u : 0u;
     };
 
+    auto refresh = [&](uint32_t v) { nd_refresh_wave(A, v, A.st.gi[v], A.st.ci[v], lane); };
     // ScheduleJob(j); the same code path for all threads
     auto schedule_job = [&](uint32_t j) {
         for (;;) {                                           // ---- GPUs
@@ -434,8 +1112,8 @@ __global__ __launch_bounds__(ND_THREADS) void k_reschedule_nodes(NdKernArgs K) {
                             } else {
                                 // the node's list and what it has free, asked for together; then the residents' slopes
                                 const uint32_t free_g = A.free_g[f], free_c = A.free_c[f];
-                                const uint32_t rv = lane < c ? A.res_job[base + lane] : j;
-                                const uint32_t rk = lane < c ? A.res_k[base + lane] : 0u;
+                                const uint32_t word = lane < c ? A.res[base + lane] : j << 16;
+                                const uint32_t rv = word >> 16;
                                 const float sl = rv != j ? A.ds_g[rv] : INF;
                                 unsigned long long key = ~0ull;      // (slope as a word that orders like it, job): lower job among equals
                                 if (sl < INF) key = ((unsigned long long)rs_ordered(sl) << 32) | rv;
@@ -452,9 +1130,9 @@ __global__ __launch_bounds__(ND_THREADS) void k_reschedule_nodes(NdKernArgs K) {
                                     const uint32_t stamp = A.stamp[who];
                                     const float ds_c0 = A.ds_c[who];
                                     const uint32_t slot = (uint32_t)__ffsll((long long)__ballot(lane < c && rv == who)) - 1u;
-                                    const uint32_t here_has = wave_lane_u32(rk, slot);
+                                    const uint32_t here_has = wave_lane_u32(word, slot) & 0xFFFFu;
                                     const float ds_g0 = __uint_as_float(wave_lane_u32(__float_as_uint(sl), slot));
-                                    const uint32_t last_v = wave_lane_u32(rv, c - 1u), last_k = wave_lane_u32(rk, c - 1u);
+                                    const uint32_t last = wave_lane_u32(word, c - 1u);
                                     const RsShrunk sk = rs_shrink_wave(A, who, so, ns, 0, gi0, ci0, lane);
                                     if (lane == 0) {
                                         if (stamp != sh_epoch) {     // (remember)
@@ -466,8 +1144,8 @@ __global__ __launch_bounds__(ND_THREADS) void k_reschedule_nodes(NdKernArgs K) {
                                         const uint32_t per_v = nd_cpl(A, ci0);
                                         const uint32_t here = (uint32_t)sk.gv.dg < here_has ? (uint32_t)sk.gv.dg : here_has;
                                         A.free_g[f] = free_g + here; A.free_c[f] = free_c + here * per_v;      // (nd_drop)
-                                        if (here_has - here) A.res_k[base + slot] = here_has - here;
-                                        else { A.res_job[base + slot] = last_v; A.res_k[base + slot] = last_k; A.cnt[f] = c - 1u; }
+                                        if (here_has - here) A.res[base + slot] = (who << 16) | (here_has - here);
+                                        else { A.res[base + slot] = last; A.cnt[f] = c - 1u; }
                                         sh_rest = (uint32_t)sk.gv.dg - here; sh_per_v = per_v; sh_v = who;
                                         sh_lost = sh_lost + sk.gv.loss;
                                         A.st.gi[who] = sk.gi; A.st.ci[who] = sk.ci;
@@ -526,7 +1204,7 @@ __global__ __launch_bounds__(ND_THREADS) void k_reschedule_nodes(NdKernArgs K) {
             const uint32_t go = sh_go;
             if (go) {
                 const uint32_t n_changed = sh_touched + 1u;      // a wavefront per job whose state changed
-                for (uint32_t i = wave; i < n_changed; i += ND_WAVES) nd_refresh_wave(A, i < sh_touched ? A.touched[i] : j, lane);
+                for (uint32_t i = wave; i < n_changed; i += ND_WAVES) refresh(i < sh_touched ? A.touched[i] : j);
             } else {
                 restore_nodes();
             }
@@ -605,7 +1283,7 @@ __global__ __launch_bounds__(ND_THREADS) void k_reschedule_nodes(NdKernArgs K) {
             const uint32_t go = sh_go;
             if (go) {
                 const uint32_t n_changed = sh_touched + 1u;      // a wavefront per job whose state changed
-                for (uint32_t i = wave; i < n_changed; i += ND_WAVES) nd_refresh_wave(A, i < sh_touched ? A.touched[i] : j, lane);
+                for (uint32_t i = wave; i < n_changed; i += ND_WAVES) refresh(i < sh_touched ? A.touched[i] : j);
             } else {
                 restore_nodes();
             }
@@ -723,163 +1401,9 @@ __global__ __launch_bounds__(ND_THREADS) void k_reschedule_nodes(NdKernArgs K) {
     }
     __syncthreads();
 
-    // ---- memory, then the records.  Parts of all jobs, grouped by job (in no order yet)
-    for (uint32_t j = tid; j < J; j += ND_THREADS) A.np[j] = 0u;
-    __syncthreads();
-    for (uint32_t n = tid; n < N; n += ND_THREADS)
-        for (uint32_t i = 0; i < A.cnt[n]; ++i) atomicAdd(&A.np[A.res_job[(size_t)n * A.gpn + i]], 1u);
-    __syncthreads();
-    const uint32_t jobs_per_thread = (J + ND_THREADS - 1) / ND_THREADS;
-    auto scan_jobs = [&](const uint32_t *count, bool only_kept, uint32_t *off) {       // off[J] = the sum
-        uint32_t local = 0;
-        for (uint32_t i = 0; i < jobs_per_thread; ++i) {
-            const uint32_t j = tid * jobs_per_thread + i;
-            if (j < J && (!only_kept || A.tier[j] != ND_NONE)) local += count[j];
-        }
-        uint32_t all;
-        uint32_t at = block_scan(local, all);
-        for (uint32_t i = 0; i < jobs_per_thread; ++i) {
-            const uint32_t j = tid * jobs_per_thread + i;
-            if (j >= J) break;
-            off[j] = at;
-            if (!only_kept || A.tier[j] != ND_NONE) at += count[j];
-        }
-        if (tid == 0) off[J] = all;
-    };
-    scan_jobs(A.np, false, A.tmp_off);
-    for (uint32_t j = tid; j < J; j += ND_THREADS) A.stamp[j] = 0u;          // (cursor of the job's parts)
-    __syncthreads();
-    for (uint32_t n = tid; n < N; n += ND_THREADS)
-        for (uint32_t i = 0; i < A.cnt[n]; ++i) {
-            const uint32_t job = A.res_job[(size_t)n * A.gpn + i];
-            const uint32_t at = A.tmp_off[job] + atomicAdd(&A.stamp[job], 1u);
-            A.tmp_parts[2 * (size_t)at] = n; A.tmp_parts[2 * (size_t)at + 1] = A.res_k[(size_t)n * A.gpn + i];
-        }
-    for (uint32_t n = tid; n < N; n += ND_THREADS) sh_mem[n] = 0.f;
-    if (tid == 0) sh_fit = A.gpn <= 4096u ? 1u : 0u;
-    __syncthreads();
-    const uint64_t rows = (uint64_t)A.X.grid.n_cpu * A.X.grid.n_mem;
-    auto tier_cost = [&](uint32_t m, uint32_t g) {
-        float v = A.X.grid.mem_levels_gb[m];
-        if (A.X.grid.mem_mode) v = v * (float)g;
-        return v;
-    };
-    auto value_at = [&](uint32_t j, uint32_t m) {
-        return A.X.best_thr[rows * A.X.tb.seg_off[j] + ((uint64_t)A.st.ci[j] * A.X.grid.n_mem + m) * rs_ns(A, j) + (uint32_t)A.st.gi[j]];
-    };
-    // the tier every job would like (highest throughput, smallest such tier), and what that asks of the nodes
-    for (uint32_t j = tid; j < J; j += ND_THREADS) {
-        uint32_t bm = ND_NONE;
-        if (A.st.gi[j] >= 0) {
-            float bv = 0.f;
-            for (uint32_t m = 0; m < A.X.grid.n_mem; ++m) {
-                const float v = value_at(j, m);
-                if (v > bv) { bv = v; bm = m; }
-            }
-            if (bm != ND_NONE) {
-                const uint32_t g = (uint32_t)rs_g(A, j, A.st.gi[j]);
-                const float cost = tier_cost(bm, g);
-                for (uint32_t i = 0; i < A.np[j]; ++i) {
-                    const size_t at = 2 * (size_t)(A.tmp_off[j] + i);
-                    atomicAdd(&sh_mem[A.tmp_parts[at]], (cost * (float)A.tmp_parts[at + 1]) / (float)g);
-                }
-            }
-        }
-        A.tier[j] = bm;
-    }
-    __syncthreads();
-    for (uint32_t n = tid; n < N; n += ND_THREADS)
-        if (!(sh_mem[n] <= A.mem_gb * 0.999f)) atomicAnd(&sh_fit, 0u);
-    __syncthreads();
-    if (!sh_fit) {                                           // some node's memory can bind: job by job, in order
-        for (uint32_t n = tid; n < N; n += ND_THREADS) sh_mem[n] = A.mem_gb;
-        __syncthreads();
-        if (wave == 0) {
-            for (uint32_t j = 0; j < J; ++j) {
-                if (A.st.gi[j] < 0) continue;
-                const uint32_t g = (uint32_t)rs_g(A, j, A.st.gi[j]);
-                const uint32_t a = A.tmp_off[j], P = A.np[j];
-                float bv = 0.f;
-                uint32_t bm = ND_NONE;
-                for (uint32_t m = 0; m < A.X.grid.n_mem; ++m) {
-                    const float cost = tier_cost(m, g);
-                    bool bad = false;
-                    for (uint32_t i = lane; i < P; i += 64u) {
-                        const size_t at = 2 * (size_t)(a + i);
-                        if (!((cost * (float)A.tmp_parts[at + 1]) / (float)g <= sh_mem[A.tmp_parts[at]])) bad = true;
-                    }
-                    if (__ballot(bad)) continue;
-                    const float v = value_at(j, m);
-                    if (v > bv) { bv = v; bm = m; }
-                }
-                if (bm != ND_NONE) {
-                    const float cost = tier_cost(bm, g);
-                    for (uint32_t i = lane; i < P; i += 64u) {
-                        const size_t at = 2 * (size_t)(a + i);
-                        sh_mem[A.tmp_parts[at]] = sh_mem[A.tmp_parts[at]] - (cost * (float)A.tmp_parts[at + 1]) / (float)g;
-                    }
-                }
-                if (lane == 0) A.tier[j] = bm;
-            }
-        }
-        __syncthreads();
-    }
-    // the records: a job's parts in node order
-    scan_jobs(A.np, true, A.place_off);
-    if (tid == 0) sh_np = 0u;                                // jobs with many parts (their list: `touched`)
-    __syncthreads();
-    double sum = 0.0;
-    for (uint32_t j = tid; j < J; j += ND_THREADS) {
-        rk_assign out = {0u, 0u, 0.f, RK_NO_PLAN, 0.f};
-        const uint32_t m = A.tier[j];
-        if (m != ND_NONE) {
-            const uint32_t g = (uint32_t)rs_g(A, j, A.st.gi[j]);
-            const uint32_t per_gpu = nd_cpl(A, A.st.ci[j]);
-            const float cost = tier_cost(m, g);
-            out.g = g; out.c = per_gpu * g; out.mem_gb = cost;
-            out.plan = A.X.best_plan[rows * A.X.tb.seg_off[j] + ((uint64_t)A.st.ci[j] * A.X.grid.n_mem + m) * rs_ns(A, j) + (uint32_t)A.st.gi[j]];
-            out.thr = value_at(j, m);
-            sum += (double)out.thr / (double)A.X.ref_thr[j];
-            const uint32_t P = A.np[j], a = A.tmp_off[j], to = A.place_off[j];
-            if (P <= 8u) {                                   // few parts: this thread ranks them
-                for (uint32_t i = 0; i < P; ++i) {
-                    const uint32_t node = A.tmp_parts[2 * (size_t)(a + i)], k = A.tmp_parts[2 * (size_t)(a + i) + 1];
-                    uint32_t rank = 0;
-                    for (uint32_t q = 0; q < P; ++q) rank += A.tmp_parts[2 * (size_t)(a + q)] < node ? 1u : 0u;
-                    A.entries[to + rank] = rk_place_entry{node, k, per_gpu * k, (cost * (float)k) / (float)g};
-                }
-            } else {
-                A.touched[atomicAdd(&sh_np, 1u)] = j;
-            }
-        }
-        A.assign[j] = out;
-    }
-    __syncthreads();
-    const uint32_t n_wide = sh_np;
-    for (uint32_t w = wave; w < n_wide; w += ND_WAVES) {      // many parts: a wavefront ranks them
-        const uint32_t j = A.touched[w];
-        const uint32_t m = A.tier[j], P = A.np[j];
-        const uint32_t g = (uint32_t)rs_g(A, j, A.st.gi[j]);
-        const uint32_t per_gpu = nd_cpl(A, A.st.ci[j]);
-        const float cost = tier_cost(m, g);
-        const uint32_t a = A.tmp_off[j], to = A.place_off[j];
-        for (uint32_t i = lane; i < P; i += 64u) {
-            const uint32_t node = A.tmp_parts[2 * (size_t)(a + i)], k = A.tmp_parts[2 * (size_t)(a + i) + 1];
-            uint32_t rank = 0;
-            for (uint32_t q = 0; q < P; ++q) rank += A.tmp_parts[2 * (size_t)(a + q)] < node ? 1u : 0u;
-            A.entries[to + rank] = rk_place_entry{node, k, per_gpu * k, (cost * (float)k) / (float)g};
-        }
-    }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off, 64);
-    if (lane == 0) sh_sum[wave] = sum;
-    __syncthreads();
-    if (tid == 0) {
-        double s = 0.0;
-        for (uint32_t w = 0; w < ND_WAVES; ++w) s += sh_sum[w];
-        *A.total = (float)s;
-        if (A.stats) { A.stats[0] = sh_moves; A.stats[1] = sh_full; A.stats[2] = sh_shrinks; A.stats[3] = sh_undone; A.stats[4] = 0u; }
-    }
+    // ---- memory, then the records
+    nd_finish<ND_THREADS>(A, A.np, A.tmp_off, A.tmp_parts, sh_mem, sh_scan);
+    if (tid == 0 && A.stats) { A.stats[0] = sh_moves; A.stats[1] = sh_full; A.stats[2] = sh_shrinks; A.stats[3] = sh_undone; A.stats[4] = 0u; }
 }
 
 }  // namespace
@@ -929,14 +1453,14 @@ int32_t rk_launch_reschedule_nodes(rk_ctx *ctx, const float *ref_thr, const rk_p
     const uint64_t gpus = (uint64_t)nodes->n_nodes * nodes->gpus_per_node;
     int32_t rc;
     const size_t n = J ? J : 1, N = nodes->n_nodes;
-    const size_t nodes_words = (3 * N + 2 * (size_t)gpus + 3) & ~(size_t)3;      // whole 16-byte pieces: the copy moves four words at a time
+    const size_t nodes_words = (3 * N + (size_t)gpus + 3) & ~(size_t)3;          // whole 16-byte pieces: the copy moves four words at a time
     uint32_t *w_nodes, *w_jobs;
     float *f_jobs;
     unsigned long long *u64;
-    if ((rc = rk_scratch(ctx, SL_ND_NODES, (2 * nodes_words + 2 * N + 2 * (size_t)gpus) * sizeof(uint32_t), (void **)&w_nodes))) return rc;
-    if ((rc = rk_scratch(ctx, SL_ND_U32, (15 * n + 2) * sizeof(uint32_t), (void **)&w_jobs))) return rc;
+    if ((rc = rk_scratch(ctx, SL_ND_NODES, (2 * nodes_words + 2 * N + (size_t)gpus) * sizeof(uint32_t), (void **)&w_nodes))) return rc;
+    if ((rc = rk_scratch(ctx, SL_ND_U32, (15 * n + 1) * sizeof(uint32_t), (void **)&w_jobs))) return rc;
     if ((rc = rk_scratch(ctx, SL_ND_F32, 10 * n * sizeof(float), (void **)&f_jobs))) return rc;
-    if ((rc = rk_scratch(ctx, SL_ND_U64, 2 * n * sizeof(unsigned long long), (void **)&u64))) return rc;
+    if ((rc = rk_scratch(ctx, SL_ND_U64, n * sizeof(unsigned long long), (void **)&u64))) return rc;
     NdKernArgs K;
     NdBody &A = K.b;
     K.X.ref_thr = ref_thr; K.X.tb = table_dev(table); K.X.grid = grid_dev(grid);
@@ -947,34 +1471,43 @@ int32_t rk_launch_reschedule_nodes(rk_ctx *ctx, const float *ref_thr, const rk_p
     A.state = jobs_state->state; A.cur_seg = jobs_state->cur_seg; A.cur_c = jobs_state->cur_c;
     A.floor_seg = jobs_state->floor_seg; A.floor_c = jobs_state->floor_c;
     A.prev_off = prev_off; A.prev_entries = prev_entries; A.n_prev = n_prev_entries;
-    A.free_g = w_nodes; A.free_c = w_nodes + N; A.cnt = w_nodes + 2 * N; A.res_job = w_nodes + 3 * N;
-    A.res_k = A.res_job + gpus;
+    A.free_g = w_nodes; A.free_c = w_nodes + N; A.cnt = w_nodes + 2 * N; A.res = w_nodes + 3 * N;
     A.keep_nodes = w_nodes + nodes_words; A.nodes_words = (uint32_t)nodes_words;
     A.plist = w_nodes + 2 * nodes_words; A.tmp_parts = A.plist + 2 * N;
     A.st.gi = reinterpret_cast<int32_t *>(w_jobs); A.st.ci = w_jobs + n; A.udg = w_jobs + 2 * n; A.touched = w_jobs + 3 * n;
     A.stamp = w_jobs + 4 * n; A.first = w_jobs + 5 * n; A.keep_ci = w_jobs + 6 * n;
     A.keep_gi = reinterpret_cast<int32_t *>(w_jobs + 7 * n); A.np = w_jobs + 8 * n; A.tier = w_jobs + 9 * n;
     A.tmp_off = w_jobs + 10 * n;                             // n + 1 words
-    A.flags = w_jobs + 11 * n + 1;
-    uint32_t *more = w_jobs + 11 * n + 2;
+    A.seg_off = table->seg_off;
+    uint32_t *more = w_jobs + 11 * n + 1;
     A.tgt_g = reinterpret_cast<int32_t *>(more); A.lvl_g = more + n; A.lvl_c = more + 2 * n; A.any = more + 3 * n;
     A.ds_g = f_jobs; A.ds_c = f_jobs + n; A.ug = f_jobs + 2 * n; A.uc = f_jobs + 3 * n; A.sg = f_jobs + 4 * n;
     A.sc = f_jobs + 5 * n; A.keep_ds = f_jobs + 6 * n; A.gain_g = f_jobs + 8 * n; A.gain_c = f_jobs + 9 * n;
-    A.udc_g = u64; A.udc_c = u64 + n;
+    A.udc_c = u64;
     A.assign = assign; A.place_off = place_off; A.entries = entries; A.total = total; A.stats = stats;
-    k_nd_init<<<(uint32_t)((N + 255) / 256), 256, 0, ctx->stream>>>(K);
-    RK_CHECK_LAUNCH(ctx, "k_nd_init");
-    if (J > 0) {
-        k_nd_prepare<<<(J + 255) / 256, 256, 0, ctx->stream>>>(K);
-        RK_CHECK_LAUNCH(ctx, "k_nd_prepare");
-    }
-    const size_t lds = (size_t)2 * n * sizeof(float);                           // at most 96 KiB
-    if (lds > 64 * 1024 && !ctx->nodes_lds_raised) {
-        RK_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(k_reschedule_nodes),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, 2 * RK_MAX_JOBS_PER_ROUND * sizeof(float)));
+    // Where the nodes and their copy fit a CU's LDS beside the cached slopes (512 nodes of 8 GPUs and 10,000 jobs do), the
+    // loop runs on them there.
+    const size_t lds_lj = nd_lds_words(J, N, nodes_words, true) * sizeof(uint32_t), lds_l = nd_lds_words(J, N, nodes_words, false) * sizeof(uint32_t);
+    const bool in_lds = A.gpn <= 64u && lds_l <= ND_LDS_MOST, jobs_too = in_lds && lds_lj <= ND_LDS_MOST;
+    if (!ctx->nodes_lds_raised) {
+        const auto most = hipFuncAttributeMaxDynamicSharedMemorySize;
+        RK_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(k_nodes_lds<ND_SMALL_THREADS, true>), most, (int)ND_LDS_MOST));
+        RK_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(k_nodes_lds<ND_THREADS, false>), most, (int)ND_LDS_MOST));
+        RK_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(k_reschedule_nodes), most, 2 * RK_MAX_JOBS_PER_ROUND * sizeof(float)));
         ctx->nodes_lds_raised = true;
     }
-    k_reschedule_nodes<<<1, ND_THREADS, lds, ctx->stream>>>(K);
-    RK_CHECK_LAUNCH(ctx, "k_reschedule_nodes");
+    A.book = !in_lds;
+    if (A.book) {
+        k_nd_init<<<(uint32_t)((N + 255) / 256), 256, 0, ctx->stream>>>(K);
+        RK_CHECK_LAUNCH(ctx, "k_nd_init");
+    }
+    if (J > 0) {
+        k_nd_prepare<<<(J + 3) / 4, 256, 0, ctx->stream>>>(K);
+        RK_CHECK_LAUNCH(ctx, "k_nd_prepare");
+    }
+    if (jobs_too) k_nodes_lds<ND_SMALL_THREADS, true><<<1, ND_SMALL_THREADS, lds_lj, ctx->stream>>>(K);
+    else if (in_lds) k_nodes_lds<ND_THREADS, false><<<1, ND_THREADS, lds_l, ctx->stream>>>(K);
+    else k_reschedule_nodes<<<1, ND_THREADS, (size_t)2 * n * sizeof(float), ctx->stream>>>(K);           // at most 96 KiB
+    RK_CHECK_LAUNCH(ctx, "k_nodes_lds");
     return RK_OK;
 }
