@@ -42,6 +42,37 @@ __device__ __forceinline__ unsigned long long wave_max_u64_rows(unsigned long lo
 // The minimum likewise.
 __device__ __forceinline__ unsigned long long wave_min_u64_rows(unsigned long long v) { return ~wave_max_u64_rows(~v); }
 
+// Minimum and maximum of a word over the wavefront, in every lane; all 64 lanes must be active.  Within each row of 16
+// lanes as above, then every row's result into the rows behind it: an instruction per move, where a pair of words takes
+// five, so what is ordered by several words is reduced word by word.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t rs_dpp_u32(uint32_t none, uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)none, (int)v, CTRL, ROWS, 0xF, false);
+}
+__device__ __forceinline__ uint32_t rs_min_u32(uint32_t a, uint32_t b) { return a < b ? a : b; }
+__device__ __forceinline__ uint32_t rs_max_u32(uint32_t a, uint32_t b) { return a > b ? a : b; }
+__device__ __forceinline__ uint32_t row_min_u32(uint32_t v) {                        // within the rows of 16 lanes
+    v = rs_min_u32(v, rs_dpp_u32<0xB1, 0xF>(0xFFFFFFFFu, v));                        // quad_perm [1,0,3,2]
+    v = rs_min_u32(v, rs_dpp_u32<0x4E, 0xF>(0xFFFFFFFFu, v));                        // quad_perm [2,3,0,1]
+    v = rs_min_u32(v, rs_dpp_u32<0x141, 0xF>(0xFFFFFFFFu, v));                       // row_half_mirror
+    return rs_min_u32(v, rs_dpp_u32<0x140, 0xF>(0xFFFFFFFFu, v));                    // row_mirror
+}
+__device__ __forceinline__ uint32_t wave_min_u32_rows(uint32_t v) {
+    v = row_min_u32(v);
+    v = rs_min_u32(v, rs_dpp_u32<0x142, 0xA>(0xFFFFFFFFu, v));                       // row_bcast:15 into rows 1 and 3
+    v = rs_min_u32(v, rs_dpp_u32<0x143, 0xC>(0xFFFFFFFFu, v));                       // row_bcast:31 into rows 2 and 3
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+__device__ __forceinline__ uint32_t wave_max_u32_rows(uint32_t v) {
+    v = rs_max_u32(v, rs_dpp_u32<0xB1, 0xF>(0u, v));
+    v = rs_max_u32(v, rs_dpp_u32<0x4E, 0xF>(0u, v));
+    v = rs_max_u32(v, rs_dpp_u32<0x141, 0xF>(0u, v));
+    v = rs_max_u32(v, rs_dpp_u32<0x140, 0xF>(0u, v));
+    v = rs_max_u32(v, rs_dpp_u32<0x142, 0xA>(0u, v));
+    v = rs_max_u32(v, rs_dpp_u32<0x143, 0xC>(0u, v));
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
 // Lane s of a value whose index is the same in all lanes (through a scalar register).
 __device__ __forceinline__ uint32_t wave_lane_u32(uint32_t x, uint32_t s) {
     return (uint32_t)__builtin_amdgcn_readlane((int)x, __builtin_amdgcn_readfirstlane((int)s));
@@ -329,14 +360,14 @@ __device__ __forceinline__ RsStep rs_up_gpu_rows(const Args &A, const RsRows &R,
     RsStep st = {0u, -1, ci, 0.f, 0.f, 0ull, 0ull};
     const float cur = rs_lane_f(R.curve, gi);
     const uint32_t g_cur = rs_lane_u(R.g, gi);
-    unsigned long long key = 0;
+    uint32_t key = 0;                                      // slope bits; the smallest amount among equal slopes
     if ((int32_t)lane > gi && lane < R.ns && (unsigned long long)R.g <= A.G && R.curve > cur) {   // amounts ascend in GPUs
-        const float sl = ((R.curve - cur) / R.ref) / (float)((unsigned long long)R.g - g_cur);
-        if (sl > 0.f) key = ((unsigned long long)__float_as_uint(sl) << 32) | (0xFFFFFFFFu - lane);
+        const float sl = ((R.curve - cur) / R.ref) / (float)(R.g - g_cur);
+        if (sl > 0.f) key = __float_as_uint(sl);
     }
-    key = wave_max_u64_rows(key);
-    if (key) {
-        const int32_t s = (int32_t)(0xFFFFFFFFu - (uint32_t)key);
+    const uint32_t top = wave_max_u32_rows(key);
+    if (top) {
+        const int32_t s = (int32_t)__ffsll((long long)__ballot(key == top)) - 1;
         const uint32_t g_s = rs_lane_u(R.g, s);
         st.any = 1u; st.tgt = s;
         st.dg = (unsigned long long)g_s - g_cur;
@@ -354,14 +385,14 @@ __device__ __forceinline__ RsStep rs_up_cpu_rows(const Args &A, const RsRows &R,
     const float cur = rs_lane_f(R.best, gi);
     const uint32_t g = rs_lane_u(R.g, gi);
     const unsigned long long here = cpu_cost(A.X.grid, ci, g);
-    unsigned long long key = 0;
+    uint32_t key = 0;                                      // likewise, the lowest level among equal slopes
     if (lane > ci && lane < A.X.grid.n_cpu && R.col > cur) {
         const float sl = ((R.col - cur) / R.ref) / (float)(cpu_cost(A.X.grid, lane, g) - here);
-        if (sl > 0.f) key = ((unsigned long long)__float_as_uint(sl) << 32) | (0xFFFFFFFFu - lane);
+        if (sl > 0.f) key = __float_as_uint(sl);
     }
-    key = wave_max_u64_rows(key);
-    if (key) {
-        const uint32_t c = 0xFFFFFFFFu - (uint32_t)key;
+    const uint32_t top = wave_max_u32_rows(key);
+    if (top) {
+        const uint32_t c = (uint32_t)__ffsll((long long)__ballot(key == top)) - 1u;
         st.any = 1u; st.lvl = c;
         st.dc = cpu_cost(A.X.grid, c, g) - here;
         st.gain = (rs_lane_f(R.col, (int32_t)c) - cur) / R.ref;
@@ -448,26 +479,6 @@ __device__ __forceinline__ uint32_t rs_ordered(float x) {
 }
 __device__ __forceinline__ float rs_unordered(uint32_t u) { return __uint_as_float((u & 0x80000000u) ? (u & 0x7FFFFFFFu) : ~u); }
 
-// Minimum of a word over the wavefront, in every lane; all 64 lanes must be active (as wave_max_u64_rows).
-template <int CTRL>
-__device__ __forceinline__ uint32_t rs_dpp_u32(uint32_t v) {
-    return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xF, 0xF, false);
-}
-__device__ __forceinline__ uint32_t wave_min_u32_rows(uint32_t v) {
-    uint32_t o;
-    o = rs_dpp_u32<0xB1>(v);  v = o < v ? o : v;                // quad_perm [1,0,3,2]
-    o = rs_dpp_u32<0x4E>(v);  v = o < v ? o : v;                // quad_perm [2,3,0,1]
-    o = rs_dpp_u32<0x141>(v); v = o < v ? o : v;                // row_half_mirror
-    o = rs_dpp_u32<0x140>(v); v = o < v ? o : v;                // row_mirror
-    uint32_t m = 0xFFFFFFFFu;
-#pragma unroll
-    for (int r = 0; r < 64; r += 16) {
-        const uint32_t row = (uint32_t)__builtin_amdgcn_readlane((int)v, r);
-        m = row < m ? row : m;
-    }
-    return m;
-}
-
 // The job that comes first in the loops' order (GPU slope, then CPU slope, both descending, then the lower index)
 // among the candidates of a workgroup's threads (j == 0xFFFFFFFF: a thread without one; slopes are not negative).
 // All threads call and all get the result.  The slopes travel as one key of two words that order like them, the
@@ -477,17 +488,18 @@ template <int WAVES>
 __device__ __forceinline__ RsPick rs_pick_first(float g, float c, uint32_t j, uint32_t lane, uint32_t wave,
                                                 unsigned long long *sh_key, uint32_t *sh_j) {
     const uint32_t NONE = 0xFFFFFFFFu;
-    const unsigned long long key = j == NONE ? 0ull : ((unsigned long long)rs_ordered(g) << 32) | rs_ordered(c);
-    const unsigned long long top = wave_max_u64_rows(key);
-    const uint32_t first = wave_min_u32_rows(j != NONE && key == top ? j : NONE);
-    if (lane == 0) { sh_key[wave] = top; sh_j[wave] = first; }
+    const uint32_t kg = j == NONE ? 0u : rs_ordered(g), kc = j == NONE ? 0u : rs_ordered(c);
+    const uint32_t top_g = wave_max_u32_rows(kg), top_c = wave_max_u32_rows(kg == top_g ? kc : 0u);
+    const uint32_t first = wave_min_u32_rows(j != NONE && kg == top_g && kc == top_c ? j : NONE);
+    if (lane == 0) { sh_key[wave] = ((unsigned long long)top_g << 32) | top_c; sh_j[wave] = first; }
     rs_lds_barrier();
     if (wave == 0) {
         const unsigned long long k2 = lane < WAVES ? sh_key[lane] : 0ull;
         const uint32_t j2 = lane < WAVES ? sh_j[lane] : NONE;
-        const unsigned long long t2 = wave_max_u64_rows(k2);
-        const uint32_t f2 = wave_min_u32_rows(j2 != NONE && k2 == t2 ? j2 : NONE);
-        if (lane == 0) { sh_key[WAVES] = t2; sh_j[WAVES] = f2; }
+        const uint32_t g2 = (uint32_t)(k2 >> 32), c2 = (uint32_t)k2;
+        const uint32_t tg = wave_max_u32_rows(g2), tc = wave_max_u32_rows(g2 == tg ? c2 : 0u);
+        const uint32_t f2 = wave_min_u32_rows(g2 == tg && c2 == tc ? j2 : NONE);
+        if (lane == 0) { sh_key[WAVES] = ((unsigned long long)tg << 32) | tc; sh_j[WAVES] = f2; }
     }
     rs_lds_barrier();
     RsPick out;

@@ -65,10 +65,10 @@ struct NdBody {
     float *ds_g, *ds_c, *ug, *uc, *sg, *sc, *keep_ds;
     float *gain_g, *gain_c;          // ... and of a job's next GPU / CPU step: its gain,
     int32_t *tgt_g;                  // the GPU step's target amount,
-    uint32_t *lvl_g, *lvl_c, *any;   // the CPU level each step ends on, bit 0 / 1: there is a GPU / CPU step
-    uint32_t *udg, *touched, *stamp, *first, *keep_ci, *np, *tmp_off, *tier;
+    uint32_t *lvl_g, *lvl_c;         // the CPU level each step ends on (no GPU step: tgt_g -1; no CPU step: uc 0)
+    uint32_t *udg, *touched, *stamp, *first, *keep_ci, *np, *tmp_off;
     int32_t *keep_gi;
-    unsigned long long *udc_c;
+    unsigned long long *udc_c, *okey;   // okey: a job's place in the order (k_nodes_lds)
     uint32_t *plist;                 // parts of one job: (node, GPUs) pairs, ascending node
     uint32_t *tmp_parts;             // parts of all jobs, (node << 16 | GPUs), grouped by job, in no order
     rk_assign *assign;
@@ -169,34 +169,42 @@ __device__ __forceinline__ void nd_refresh(const NdArgs &A, uint32_t v, uint32_t
     A.ug[v] = ug.any ? ug.slope : 0.f; A.udg[v] = (uint32_t)ug.dg;   // (a step that exists has its slope here)
     A.uc[v] = uc.any ? uc.slope : 0.f; A.udc_c[v] = uc.dc;
     A.gain_g[v] = ug.gain; A.gain_c[v] = uc.gain; A.tgt_g[v] = ug.tgt; A.lvl_g[v] = ug.lvl; A.lvl_c[v] = uc.lvl;
-    A.any[v] = (ug.any ? 1u : 0u) | (uc.any ? 2u : 0u);
 }
 // nd_refresh for a whole wavefront: a job of at most 64 amounts that is not below its floor has its rows loaded at
-// once, an amount per lane, and every step comes from the registers (rs_rows)
-__device__ __forceinline__ void nd_refresh_wave(const NdArgs &A, uint32_t v, int32_t gi, uint32_t ci, uint32_t lane) {
+// once, an amount per lane, and every step comes from the registers (rs_rows).  The steps in GPUs and in CPUs may be
+// left to two wavefronts (with_g, with_c).
+__device__ __forceinline__ void nd_refresh_wave(const NdArgs &A, uint32_t v, int32_t gi, uint32_t ci, uint32_t lane, bool with_g = true, bool with_c = true) {
     const int32_t fl = rs_fl_s(A, v);
     const uint32_t so = A.seg_off[v], ns = A.seg_off[v + 1] - so;
-    if (ns > 64u || (fl >= 0 && gi < fl)) { nd_refresh(A, v, lane, 64); return; }
+    if (ns > 64u || (fl >= 0 && gi < fl)) { if (with_g) nd_refresh(A, v, lane, 64); return; }
     const RsRows R = rs_rows(A, v, so, ns, gi, ci, lane);
-    const RsGive a = rs_down_gpu_rows(A, R, R.curve, gi, ci, lane);
-    const RsGive b = rs_down_cpu_rows(A, R, gi, ci, rs_lane_f(R.best, gi), rs_lane_f(R.best_lo, gi));
-    const RsStep ug = rs_up_gpu_rows(A, R, gi, ci, lane), uc = rs_up_cpu_rows(A, R, gi, ci, lane);
-    if (lane != 0) return;
-    A.ds_g[v] = a.any ? a.slope : __int_as_float(0x7F800000);
-    A.ds_c[v] = b.any ? b.slope : __int_as_float(0x7F800000);
-    A.ug[v] = ug.any ? ug.slope : 0.f; A.udg[v] = (uint32_t)ug.dg;
-    A.uc[v] = uc.any ? uc.slope : 0.f; A.udc_c[v] = uc.dc;
-    A.gain_g[v] = ug.gain; A.gain_c[v] = uc.gain; A.tgt_g[v] = ug.tgt; A.lvl_g[v] = ug.lvl; A.lvl_c[v] = uc.lvl;
-    A.any[v] = (ug.any ? 1u : 0u) | (uc.any ? 2u : 0u);
+    if (with_g) {
+        const RsGive a = rs_down_gpu_rows(A, R, R.curve, gi, ci, lane);
+        const RsStep ug = rs_up_gpu_rows(A, R, gi, ci, lane);
+        if (lane == 0) {
+            A.ds_g[v] = a.any ? a.slope : __int_as_float(0x7F800000);
+            A.ug[v] = ug.any ? ug.slope : 0.f; A.udg[v] = (uint32_t)ug.dg;
+            A.gain_g[v] = ug.gain; A.tgt_g[v] = ug.tgt; A.lvl_g[v] = ug.lvl;
+        }
+    }
+    if (with_c) {
+        const RsGive b = rs_down_cpu_rows(A, R, gi, ci, rs_lane_f(R.best, gi), rs_lane_f(R.best_lo, gi));
+        const RsStep uc = rs_up_cpu_rows(A, R, gi, ci, lane);
+        if (lane == 0) {
+            A.ds_c[v] = b.any ? b.slope : __int_as_float(0x7F800000);
+            A.uc[v] = uc.any ? uc.slope : 0.f; A.udc_c[v] = uc.dc;
+            A.gain_c[v] = uc.gain; A.lvl_c[v] = uc.lvl;
+        }
+    }
 }
 // the cached next step of job j: res 0 GPUs, 1 CPU level
 __device__ __forceinline__ RsStep nd_cached_step(const NdArgs &A, uint32_t j, uint32_t res) {
     RsStep st;
     if (res == 0) {
-        st.any = A.any[j] & 1u; st.tgt = A.tgt_g[j]; st.lvl = A.lvl_g[j]; st.slope = A.ug[j]; st.gain = A.gain_g[j];
+        st.tgt = A.tgt_g[j]; st.any = st.tgt >= 0 ? 1u : 0u; st.lvl = A.lvl_g[j]; st.slope = A.ug[j]; st.gain = A.gain_g[j];
         st.dg = A.udg[j]; st.dc = 0ull;        // (a GPU step's CPUs come with its GPUs)
     } else {
-        st.any = (A.any[j] >> 1) & 1u; st.tgt = A.st.gi[j]; st.lvl = A.lvl_c[j]; st.slope = A.uc[j]; st.gain = A.gain_c[j];
+        st.tgt = A.st.gi[j]; st.lvl = A.lvl_c[j]; st.slope = A.uc[j]; st.any = st.slope > 0.f ? 1u : 0u; st.gain = A.gain_c[j];
         st.dg = 0ull; st.dc = A.udc_c[j];
     }
     return st;
@@ -294,19 +302,19 @@ __device__ __forceinline__ void nd_refuse(const NdArgs &A) {
     }
 }
 
-// Memory, then the records, from what the jobs hold and who is on the nodes.  np and off [n_jobs], parts [GPUs of all
-// nodes], tier and touched [n_jobs] and mem [n_nodes] are working memory, in LDS or not.  All threads call it.
+// Memory, then the records, from what the jobs hold and who is on the nodes.  np, off [n_jobs], parts [GPUs of all
+// nodes], wish [n_jobs] and mem [n_nodes] are working memory, in LDS or not.  All threads call it.
 template <int THREADS>
-__device__ __forceinline__ void nd_finish(const NdArgs &A, uint32_t *np, uint32_t *off, uint32_t *parts, float *mem, uint32_t *sh_scan) {
+__device__ __forceinline__ void nd_finish(const NdArgs &A, uint32_t *np, uint32_t *off, uint32_t *parts, uint32_t *wish, float *mem, uint32_t *sh_scan) {
     constexpr uint32_t WAVES = THREADS / 64;
-    __shared__ uint32_t sh_fit, sh_wide;
+    __shared__ uint32_t sh_fit, sh_wide, sh_list;
     __shared__ double sh_sum[WAVES];
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     const uint32_t J = A.n_jobs, N = A.n_nodes, gpus = N * A.gpn;
     __syncthreads();
     for (uint32_t j = tid; j < J; j += THREADS) np[j] = 0u;
     for (uint32_t n = tid; n < N; n += THREADS) mem[n] = 0.f;
-    if (tid == 0) { sh_fit = A.gpn <= 4096u ? 1u : 0u; sh_wide = 0u; }       // sh_wide: jobs with many parts (their list: `touched`)
+    if (tid == 0) { sh_fit = A.gpn <= 4096u ? 1u : 0u; sh_wide = 0u; sh_list = 0u; }
     __syncthreads();
     // the parts of all jobs, grouped by job (in no order yet): an entry of the nodes' tables per thread
     for (uint32_t i = tid; i < gpus; i += THREADS) {
@@ -315,18 +323,20 @@ __device__ __forceinline__ void nd_finish(const NdArgs &A, uint32_t *np, uint32_
     }
     __syncthreads();
     const uint32_t jobs_per_thread = (J + THREADS - 1) / THREADS;
-    {
+    auto offsets = [&](uint32_t *to) {                                       // where every job's parts begin; returns their number
         uint32_t local = 0, all;
         for (uint32_t i = 0; i < jobs_per_thread; ++i) {
             const uint32_t j = tid * jobs_per_thread + i;
-            if (j < J) local += np[j];
+            if (j < J) local += np[j] & 0xFFFFu;
         }
         uint32_t at = nd_block_scan<THREADS>(local, all, sh_scan);
         for (uint32_t i = 0; i < jobs_per_thread; ++i) {
             const uint32_t j = tid * jobs_per_thread + i;
-            if (j < J) { off[j] = at; at += np[j]; }
+            if (j < J) { to[j] = at; at += np[j] & 0xFFFFu; }
         }
-    }
+        return all;
+    };
+    offsets(off);
     __syncthreads();
     for (uint32_t i = tid; i < gpus; i += THREADS) {                         // (moves off[j] to the end of job j's parts)
         const uint32_t n = i / A.gpn;
@@ -336,7 +346,22 @@ __device__ __forceinline__ void nd_finish(const NdArgs &A, uint32_t *np, uint32_
         }
     }
     __syncthreads();
+    // the jobs that hold something, listed (in no order) where the residents were; the others' records
+    uint32_t *const list = A.res;
+    for (uint32_t j0 = 0; j0 < J; j0 += THREADS) {
+        const uint32_t j = j0 + tid;
+        const bool holds = j < J && np[j] != 0u;
+        const unsigned long long m = __ballot(holds);
+        uint32_t base = 0;
+        if (lane == 0 && m) base = atomicAdd(&sh_list, (uint32_t)__popcll(m));
+        base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+        if (holds) list[base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = j;
+        else if (j < J) A.assign[j] = rk_assign{0u, 0u, 0.f, RK_NO_PLAN, 0.f};
+    }
+    __syncthreads();
+    const uint32_t n_list = sh_list;
     const uint64_t rows = (uint64_t)A.X.grid.n_cpu * A.X.grid.n_mem;
+    const uint32_t n_mem = A.X.grid.n_mem;
     auto tier_cost = [&](uint32_t m, uint32_t g) {
         float v = A.X.grid.mem_levels_gb[m];
         if (A.X.grid.mem_mode) v = v * (float)g;
@@ -344,85 +369,97 @@ __device__ __forceinline__ void nd_finish(const NdArgs &A, uint32_t *np, uint32_
     };
     auto slot_of = [&](uint32_t j, uint32_t m) {                             // of what job j holds, at tier m, in the curves' layout
         const uint32_t so = A.seg_off[j], ns = A.seg_off[j + 1] - so;
-        return rows * so + ((uint64_t)A.st.ci[j] * A.X.grid.n_mem + m) * ns + (uint32_t)A.st.gi[j];
+        return rows * so + ((uint64_t)A.st.ci[j] * n_mem + m) * ns + (uint32_t)A.st.gi[j];
     };
     auto gpus_of = [&](uint32_t j) { return A.X.tb.seg_g[A.seg_off[j] + (uint32_t)A.st.gi[j]]; };
+    // np[j] holds the job's tier above its parts; a job without a tier is dropped: it has no parts
+    auto settle = [&](uint32_t j, uint32_t bm) {
+        if (bm != ND_NONE) np[j] = (np[j] & 0xFFFFu) | (bm << 16);
+        else { off[j] -= np[j] & 0xFFFFu; np[j] = 0u; }
+    };
     // the tier every job would like (highest throughput, smallest such tier), and what that asks of the nodes
-    for (uint32_t j = tid; j < J; j += THREADS) {
+    for (uint32_t h = tid; h < n_list; h += THREADS) {
+        const uint32_t j = list[h], P = np[j], a = off[j] - P, g = gpus_of(j);
         uint32_t bm = ND_NONE;
-        if (A.st.gi[j] >= 0) {
-            float bv = 0.f;
-            for (uint32_t m = 0; m < A.X.grid.n_mem; ++m) {
-                const float v = A.X.best_thr[slot_of(j, m)];
-                if (v > bv) { bv = v; bm = m; }
-            }
-            if (bm != ND_NONE) {
-                const uint32_t g = gpus_of(j);
-                const float cost = tier_cost(bm, g);
-                for (uint32_t i = off[j] - np[j]; i < off[j]; ++i)
-                    atomicAdd(&mem[parts[i] >> 16], (cost * (float)(parts[i] & 0xFFFFu)) / (float)g);
-            }
+        float bv = 0.f;
+        for (uint32_t m = 0; m < n_mem; ++m) {
+            const float v = A.X.best_thr[slot_of(j, m)];
+            if (v > bv) { bv = v; bm = m; }
         }
-        A.tier[j] = bm;
+        if (bm != ND_NONE) {
+            const float cost = tier_cost(bm, g);
+            for (uint32_t i = a; i < a + P; ++i) atomicAdd(&mem[parts[i] >> 16], (cost * (float)(parts[i] & 0xFFFFu)) / (float)g);
+        }
+        wish[h] = bm;
     }
     __syncthreads();
     for (uint32_t n = tid; n < N; n += THREADS)
         if (!(mem[n] <= A.mem_gb * 0.999f)) atomicAnd(&sh_fit, 0u);
     __syncthreads();
-    if (!sh_fit) {                                           // some node's memory can bind: job by job, in order
+    if (sh_fit) {
+        for (uint32_t h = tid; h < n_list; h += THREADS) settle(list[h], wish[h]);
+    } else {                                                 // some node's memory can bind: job by job, in order
         for (uint32_t n = tid; n < N; n += THREADS) mem[n] = A.mem_gb;
         __syncthreads();
         if (wave == 0) {
-            for (uint32_t j = 0; j < J; ++j) {
-                if (A.st.gi[j] < 0) continue;
-                const uint32_t g = gpus_of(j);
-                const uint32_t P = np[j], a = off[j] - P;
-                float bv = 0.f;
-                uint32_t bm = ND_NONE;
-                for (uint32_t m = 0; m < A.X.grid.n_mem; ++m) {
-                    const float cost = tier_cost(m, g);
-                    bool bad = false;
-                    for (uint32_t i = lane; i < P; i += 64u)
-                        if (!((cost * (float)(parts[a + i] & 0xFFFFu)) / (float)g <= mem[parts[a + i] >> 16])) bad = true;
-                    if (__ballot(bad)) continue;
-                    const float v = A.X.best_thr[slot_of(j, m)];
-                    if (v > bv) { bv = v; bm = m; }
+            for (uint32_t j0 = 0; j0 < J; j0 += 64u) {       // what 64 jobs have to say is loaded together, a job per lane
+                const uint32_t mine = j0 + lane;
+                const bool holds = mine < J && np[mine] != 0u;
+                unsigned long long todo = __ballot(holds);
+                if (!todo) continue;
+                const uint32_t my_p = holds ? np[mine] : 0u, my_a = holds ? off[mine] - my_p : 0u, my_g = holds ? gpus_of(mine) : 1u;
+                float my_v[RK_MAX_MEM_LEVELS];
+#pragma unroll
+                for (uint32_t m = 0; m < RK_MAX_MEM_LEVELS; ++m) {
+                    my_v[m] = 0.f;
+                    if (m < n_mem && holds) my_v[m] = A.X.best_thr[slot_of(mine, m)];
                 }
-                if (bm != ND_NONE) {
-                    const float cost = tier_cost(bm, g);
-                    for (uint32_t i = lane; i < P; i += 64u) {
-                        const uint32_t n = parts[a + i] >> 16;
-                        mem[n] = mem[n] - (cost * (float)(parts[a + i] & 0xFFFFu)) / (float)g;
+                uint32_t my_tier = ND_NONE;
+                while (todo) {
+                    const uint32_t s = (uint32_t)__ffsll((long long)todo) - 1u;
+                    todo &= todo - 1ull;
+                    const uint32_t P = wave_lane_u32(my_p, s), a = wave_lane_u32(my_a, s), g = wave_lane_u32(my_g, s);
+                    float bv = 0.f;
+                    uint32_t bm = ND_NONE;
+#pragma unroll
+                    for (uint32_t m = 0; m < RK_MAX_MEM_LEVELS; ++m) {
+                        if (m >= n_mem) break;
+                        const float v = rs_lane_f(my_v[m], (int32_t)s);
+                        if (!(v > bv)) continue;
+                        const float cost = tier_cost(m, g);
+                        bool bad = false;
+                        for (uint32_t i = lane; i < P; i += 64u)
+                            if (!((cost * (float)(parts[a + i] & 0xFFFFu)) / (float)g <= mem[parts[a + i] >> 16])) bad = true;
+                        if (__ballot(bad)) continue;
+                        bv = v; bm = m;
                     }
+                    if (bm != ND_NONE) {
+                        const float cost = tier_cost(bm, g);
+                        for (uint32_t i = lane; i < P; i += 64u) {
+                            const uint32_t n = parts[a + i] >> 16;
+                            mem[n] = mem[n] - (cost * (float)(parts[a + i] & 0xFFFFu)) / (float)g;
+                        }
+                    }
+                    if (lane == s) my_tier = bm;
+                    asm volatile("" ::: "memory");           // (the next job's lanes read what these ones stored)
                 }
-                if (lane == 0) A.tier[j] = bm;
-                asm volatile("" ::: "memory");   // (the next job's lanes read what these ones stored)
+                if (holds) settle(mine, my_tier);
             }
         }
-        __syncthreads();
     }
+    __syncthreads();
     // the records: a job's parts in node order
     {
-        uint32_t local = 0, all;
-        for (uint32_t i = 0; i < jobs_per_thread; ++i) {
-            const uint32_t j = tid * jobs_per_thread + i;
-            if (j < J && A.tier[j] != ND_NONE) local += np[j];
-        }
-        uint32_t at = nd_block_scan<THREADS>(local, all, sh_scan);
-        for (uint32_t i = 0; i < jobs_per_thread; ++i) {
-            const uint32_t j = tid * jobs_per_thread + i;
-            if (j >= J) break;
-            A.place_off[j] = at;
-            if (A.tier[j] != ND_NONE) at += np[j];
-        }
+        const uint32_t all = offsets(A.place_off);
         if (tid == 0) A.place_off[J] = all;
     }
     __syncthreads();
     double sum = 0.0;
-    for (uint32_t j = tid; j < J; j += THREADS) {
+    for (uint32_t h = tid; h < n_list; h += THREADS) {
+        const uint32_t j = list[h];
         rk_assign out = {0u, 0u, 0.f, RK_NO_PLAN, 0.f};
-        const uint32_t m = A.tier[j];
-        if (m != ND_NONE) {
+        const uint32_t m = np[j] >> 16, P = np[j] & 0xFFFFu, a = off[j] - P;
+        if (P) {
             const uint32_t g = gpus_of(j);
             const uint32_t per_gpu = nd_cpl(A, A.st.ci[j]);
             const float cost = tier_cost(m, g);
@@ -430,7 +467,7 @@ __device__ __forceinline__ void nd_finish(const NdArgs &A, uint32_t *np, uint32_
             out.plan = A.X.best_plan[slot_of(j, m)];
             out.thr = A.X.best_thr[slot_of(j, m)];
             sum += (double)out.thr / (double)A.X.ref_thr[j];
-            const uint32_t P = np[j], a = off[j] - P, to = A.place_off[j];
+            const uint32_t to = A.place_off[j];
             if (P <= 8u) {                                   // few parts: this thread ranks them
                 for (uint32_t i = 0; i < P; ++i) {
                     const uint32_t node = parts[a + i] >> 16, k = parts[a + i] & 0xFFFFu;
@@ -439,7 +476,7 @@ __device__ __forceinline__ void nd_finish(const NdArgs &A, uint32_t *np, uint32_
                     A.entries[to + rank] = rk_place_entry{node, k, per_gpu * k, (cost * (float)k) / (float)g};
                 }
             } else {
-                A.touched[atomicAdd(&sh_wide, 1u)] = j;
+                wish[atomicAdd(&sh_wide, 1u)] = j;           // (the wishes have been read)
             }
         }
         A.assign[j] = out;
@@ -447,8 +484,8 @@ __device__ __forceinline__ void nd_finish(const NdArgs &A, uint32_t *np, uint32_
     __syncthreads();
     const uint32_t n_wide = sh_wide;
     for (uint32_t w = wave; w < n_wide; w += WAVES) {         // many parts: a wavefront ranks them
-        const uint32_t j = A.touched[w];
-        const uint32_t m = A.tier[j], P = np[j];
+        const uint32_t j = wish[w];
+        const uint32_t m = np[j] >> 16, P = np[j] & 0xFFFFu;
         const uint32_t g = gpus_of(j);
         const uint32_t per_gpu = nd_cpl(A, A.st.ci[j]);
         const float cost = tier_cost(m, g);
@@ -494,9 +531,9 @@ __device__ __forceinline__ void nd_wave_order() {
 
 // Words of dynamic LDS that k_nodes_lds needs: the nodes and their copy, the cached slopes, memory, and (LJ) everything
 // else a job has.
-constexpr uint32_t ND_LDS_JOB_WORDS = 24;
+constexpr uint32_t ND_LDS_JOB_WORDS = 22;
 static inline size_t nd_lds_words(size_t J, size_t N, size_t nodes_words, bool lj) {
-    return 2 * nodes_words + 2 * J + N + (lj ? ND_LDS_JOB_WORDS * J + 1 : 0);
+    return 2 * nodes_words + 2 * (J + 1) + N + (lj ? ND_LDS_JOB_WORDS * J + 1 : 0);
 }
 
 // The loop with the nodes in LDS.  It is a chain of small decisions, so what bounds it is the latency of one after
@@ -509,16 +546,15 @@ template <int THREADS, bool LJ>
 __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
     extern __shared__ uint4 sh_raw[];
     constexpr uint32_t WAVES = THREADS / 64;
-    __shared__ uint32_t sh_scan[WAVES], sh_take[RK_MAX_CPU_LEVELS], sh_free_c, sh_cpl[RK_MAX_CPU_LEVELS];
-    __shared__ unsigned long long sh_pick_key[WAVES + 1];
-    __shared__ uint32_t sh_pick_j[WAVES + 1];
-    __shared__ unsigned long long sh_two_k[2 * (WAVES + 1)];
-    __shared__ uint32_t sh_two_s[2 * (WAVES + 1)];
-    __shared__ RsMin sh_min[2];
+    __shared__ uint32_t sh_scan[WAVES], sh_take[RK_MAX_CPU_LEVELS], sh_free_c, sh_cpl[RK_MAX_CPU_LEVELS], sh_list;
+    __shared__ float sh_rcp[RK_MAX_CPU_LEVELS];             // 1 / a level's CPUs per GPU
+    __shared__ unsigned long long sh_pick_key[WAVES];
+    __shared__ uint32_t sh_pick_j[WAVES], sh_low[2][WAVES][3];
     __shared__ uint32_t sh_did, sh_touched;                 // what the first wavefront's steps ended in
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
     NdArgs A(K.b, K.X);
     const uint32_t J = A.n_jobs, N = A.n_nodes, gpn = A.gpn, gpus = N * gpn;
+    const uint32_t EMPTY = (J << 16) | 0xFFFFu;              // no resident: a job that has no index, whose slopes are infinite
     const float INF = __int_as_float(0x7F800000);
 
     // ---- everything into LDS
@@ -526,38 +562,52 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
     uint32_t *const keep = nodes + A.nodes_words;
     uint32_t *at = keep + A.nodes_words;
     auto take = [&](size_t words) { uint32_t *p = at; at += words; return p; };
-    A.free_g = nodes; A.free_c = nodes + N; A.cnt = nodes + 2 * N; A.res = nodes + 3 * N;
-    unsigned long long *const sh_udc = LJ ? reinterpret_cast<unsigned long long *>(take(2 * (size_t)J)) : nullptr;
-    float *const sh_ds = reinterpret_cast<float *>(take(2 * (size_t)J));
+    A.free_g = nodes; A.free_c = nodes + N; A.cnt = nodes + 2 * N; A.res = nodes + ((3 * N + 3) & ~3u);
+    if constexpr (LJ) { A.udc_c = reinterpret_cast<unsigned long long *>(take(2 * (size_t)J)); A.okey = reinterpret_cast<unsigned long long *>(take(2 * (size_t)J)); }
+    float *const sh_ds = reinterpret_cast<float *>(take(2 * ((size_t)J + 1)));
     float *const sh_mem = reinterpret_cast<float *>(take(N));
-    for (uint32_t i = tid; i < A.nodes_words; i += THREADS) nodes[i] = i < N ? gpn : i < 2 * N ? A.cpn : i < 3 * N ? 0u : ND_NONE;
-    if (tid < A.X.grid.n_cpu) sh_cpl[tid] = A.X.grid.cpu_levels[tid];
+    for (uint32_t i = tid; i < A.nodes_words; i += THREADS) nodes[i] = i < N ? gpn : i < 2 * N ? A.cpn : i < 3 * N ? 0u : EMPTY;
+    if (tid < A.X.grid.n_cpu) {
+        const uint32_t l = A.X.grid.cpu_levels[tid];
+        sh_cpl[tid] = l; sh_rcp[tid] = 1.f / (float)l;
+    }
+    if (tid == 0) sh_list = 0u;
     if constexpr (LJ) {
-        for (uint32_t j = tid; j < J; j += THREADS) sh_udc[j] = A.udc_c[j];
-        A.udc_c = sh_udc;
-        auto load = [&](auto &p) {                           // a per-job array of words moves to LDS
-            auto *q = reinterpret_cast<std::decay_t<decltype(p)>>(take(J));
-            for (uint32_t j = tid; j < J; j += THREADS) q[j] = p[j];
-            p = q;
-        };
-        load(A.st.gi); load(A.st.ci); load(A.ug); load(A.uc); load(A.udg); load(A.gain_g); load(A.gain_c);
-        load(A.tgt_g); load(A.lvl_g); load(A.lvl_c); load(A.any); load(A.first);
-        A.sg = reinterpret_cast<float *>(take(J)); A.sc = reinterpret_cast<float *>(take(J));
-        A.stamp = take(J); A.keep_gi = reinterpret_cast<int32_t *>(take(J)); A.keep_ci = take(J);
-        A.keep_ds = reinterpret_cast<float *>(take(2 * (size_t)J)); A.touched = take(J); A.tier = take(J);
+        auto words = [&](auto &p) { p = reinterpret_cast<std::decay_t<decltype(p)>>(take(J)); };         // a per-job array of words in LDS
+        words(A.st.gi); words(A.st.ci); words(A.ug); words(A.uc); words(A.udg); words(A.gain_g); words(A.gain_c);
+        words(A.tgt_g); words(A.lvl_g); words(A.lvl_c); words(A.first);
+        words(A.stamp); words(A.keep_gi); words(A.keep_ci); words(A.touched);
+        A.keep_ds = reinterpret_cast<float *>(take(2 * (size_t)J));
         uint32_t *const so = take((size_t)J + 1);
-        for (uint32_t j = tid; j <= J; j += THREADS) so[j] = A.X.tb.seg_off[j];
+        for (uint32_t j = tid; j < J; j += THREADS) {        // (all of a job's loads before the first store)
+            const NdBody &b = K.b;
+            const int32_t gi = b.st.gi[j], tgt = b.tgt_g[j];
+            const uint32_t ci = b.st.ci[j], udg = b.udg[j], lg = b.lvl_g[j], lc = b.lvl_c[j], first = b.first[j], o = K.X.tb.seg_off[j];
+            const float ug = b.ug[j], uc = b.uc[j], gg = b.gain_g[j], gc = b.gain_c[j];
+            const unsigned long long dc = b.udc_c[j];
+            A.st.gi[j] = gi; A.st.ci[j] = ci; A.ug[j] = ug; A.uc[j] = uc; A.udg[j] = udg; A.gain_g[j] = gg; A.gain_c[j] = gc;
+            A.tgt_g[j] = tgt; A.lvl_g[j] = lg; A.lvl_c[j] = lc; A.first[j] = first; A.udc_c[j] = dc; so[j] = o;
+        }
+        if (tid == 0) so[J] = A.X.tb.seg_off[J];
         A.seg_off = so;
     }
     uint32_t bad = 0, any_first = 0;
     for (uint32_t j = tid; j < J; j += THREADS) {
-        sh_ds[j] = A.ds_g[j]; sh_ds[J + j] = A.ds_c[j];
+        sh_ds[j] = A.ds_g[j]; sh_ds[J + 1 + j] = A.ds_c[j];
         A.stamp[j] = 0u;
         bad |= A.first[j] & 2u; any_first |= A.first[j] & 1u;
     }
-    A.ds_g = sh_ds; A.ds_c = sh_ds + J;
+    A.ds_g = sh_ds; A.ds_c = sh_ds + J + 1;
+    if (tid == 0) sh_ds[J] = sh_ds[2 * J + 1] = INF;
     __syncthreads();
-    for (uint32_t j0 = tid; j0 < J; j0 += 4 * THREADS) {     // the jobs' parts are booked, four jobs' offsets in flight
+    // the jobs' parts are booked (k_nd_prepare has checked them): a job per thread, or a wavefront where a job has many
+    auto book = [&](uint32_t j, const rk_place_entry &e) {
+        const uint32_t slot = atomicAdd(&A.cnt[e.node], 1u);
+        if (slot < gpn) A.res[e.node * gpn + slot] = (j << 16) | e.g;
+        atomicSub(&A.free_g[e.node], e.g);                   // (wraps below zero when the node holds more than it has)
+        atomicSub(&A.free_c[e.node], e.c);
+    };
+    for (uint32_t j0 = tid; j0 < J; j0 += 4 * THREADS) {     // (four jobs' offsets, then four parts, in flight)
         uint32_t a[4], b[4];
 #pragma unroll
         for (uint32_t k = 0; k < 4; ++k) {
@@ -566,15 +616,22 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
             a[k] = holds ? A.prev_off[j] : 0u;
             b[k] = holds ? A.prev_off[j + 1] : 0u;
         }
+        rk_place_entry e[4];
 #pragma unroll
-        for (uint32_t k = 0; k < 4; ++k)
-            for (uint32_t i = a[k]; i < b[k]; ++i) {         // (checked by k_nd_prepare: the node is one, e.g <= gpn)
-                const rk_place_entry e = A.prev_entries[i];
-                const uint32_t slot = atomicAdd(&A.cnt[e.node], 1u);
-                if (slot < gpn) A.res[e.node * gpn + slot] = ((j0 + k * THREADS) << 16) | e.g;
-                atomicSub(&A.free_g[e.node], e.g);           // (wraps below zero when the node holds more than it has)
-                atomicSub(&A.free_c[e.node], e.c);
-            }
+        for (uint32_t k = 0; k < 4; ++k) if (a[k] < b[k] && b[k] - a[k] <= 2u) e[k] = A.prev_entries[a[k]];
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) {
+            const uint32_t j = j0 + k * THREADS;
+            if (b[k] - a[k] > 2u) { keep[atomicAdd(&sh_list, 1u)] = j; continue; }      // (three parts are three GPUs: fewer jobs than GPUs)
+            if (a[k] < b[k]) book(j, e[k]);
+            if (a[k] + 1u < b[k]) book(j, A.prev_entries[a[k] + 1u]);
+        }
+    }
+    __syncthreads();
+    for (uint32_t i = wave; i < sh_list; i += WAVES) {
+        const uint32_t j = keep[i];
+        const uint32_t a = A.prev_off[j], b = A.prev_off[j + 1];
+        for (uint32_t x = a + lane; x < b; x += 64u) book(j, A.prev_entries[x]);
     }
     __syncthreads();
     for (uint32_t n = tid; n < N; n += THREADS)
@@ -613,14 +670,44 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
         }
         undone += touched ? 1u : 0u;
     };
-    // job v's entries of the nodes' tables in ascending order: what(mask of lanes that have one, first entry of the chunk, entry)
-    auto for_parts = [&](uint32_t v, auto what) {
-        for (uint32_t b = 0; b < gpus; b += 64u) {
-            const uint32_t word = b + lane < gpus ? A.res[b + lane] : ND_NONE;
-            const unsigned long long m = __ballot((word >> 16) == v);
-            if (m && !what(m, b, word)) return;
+    // job v's entries of the nodes' tables, in ascending order of the nodes (DOWN: descending), until what(first entry of a
+    // chunk of 64, the lane's entry, the lanes that have one of v's) says no.  1,024 entries are looked through at a time,
+    // four loads of a lane in flight.
+    const uint4 *const res4 = reinterpret_cast<const uint4 *>(A.res);
+    const uint32_t n4 = (gpus + 3u) / 4u;
+    auto for_parts = [&](uint32_t v, auto down, auto what) {
+        constexpr bool DOWN = decltype(down)::value;
+        const uint32_t blocks = (n4 + 255u) / 256u;
+        for (uint32_t x = 0; x < blocks; ++x) {
+            const uint32_t blk = DOWN ? blocks - 1u - x : x;
+            uint32_t with = 0;                               // which of the four groups of 256 entries hold some of the job
+            {
+                uint4 q[4];
+#pragma unroll
+                for (uint32_t u = 0; u < 4; ++u) {
+                    const uint32_t at4 = blk * 256u + u * 64u + lane;
+                    q[u] = at4 < n4 ? res4[at4] : uint4{EMPTY, EMPTY, EMPTY, EMPTY};
+                }
+#pragma unroll
+                for (uint32_t u = 0; u < 4; ++u)
+                    if (__ballot((q[u].x >> 16) == v || (q[u].y >> 16) == v || (q[u].z >> 16) == v || (q[u].w >> 16) == v)) with |= 1u << u;
+            }
+            while (with) {
+                const uint32_t u = DOWN ? 31u - (uint32_t)__clz((int)with) : (uint32_t)__ffs((int)with) - 1u;
+                with &= ~(1u << u);
+#pragma unroll 1
+                for (uint32_t y = 0; y < 4; ++y) {           // ... and where
+                    const uint32_t b = 4u * (blk * 256u + u * 64u) + 64u * (DOWN ? 3u - y : y);
+                    const uint32_t word = b + lane < gpus ? A.res[b + lane] : EMPTY;
+                    const unsigned long long m = __ballot((word >> 16) == v);
+                    if (m && !what(b, word, m)) return;
+                }
+            }
         }
     };
+    // a / b from 1 / b for a < 2^21: (a + 1/2) / b is further from a whole number than the product's error
+    auto over = [&](uint32_t a, float rcp) { return (uint32_t)(((float)a + 0.5f) * rcp); };
+    const float rcp_gpn = 1.f / (float)gpn;
     enum : uint32_t { DID_NOTHING = 0, DID_GPUS = 1, DID_CPUS = 2, DID_UNDO = 4 };
     // A GPU step of job j: DID_GPUS when it is committed, else DID_NOTHING (jobs put back; the nodes are `dirty` or as before)
     auto gpu_step = [&](uint32_t j) -> uint32_t {
@@ -632,15 +719,16 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
         const uint32_t ci_j = A.st.ci[j];
         const bool below_min = fl >= 0 && gi_j < fl;
         const uint32_t per_gpu = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh_cpl[st.lvl]);
+        const float rcp = sh_rcp[st.lvl];
         uint32_t lack = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)st.dg);
         bool ok = true;
         if (gi_j >= 0 && st.lvl != ci_j) {                   // its parts go to the step's level: their CPUs must be free
             const uint32_t more = per_gpu - sh_cpl[ci_j];
             dirty = true;
-            for_parts(j, [&](unsigned long long m, uint32_t b, uint32_t word) {
+            for_parts(j, std::false_type{}, [&](uint32_t b, uint32_t word, unsigned long long m) {
                 bool short_of = false;
                 if ((m >> lane) & 1ull) {
-                    const uint32_t n = (b + lane) / gpn, have = A.free_c[n];
+                    const uint32_t n = over(b + lane, rcp_gpn), have = A.free_c[n];
                     const unsigned long long need = (unsigned long long)more * (word & 0xFFFFu);
                     if (have < need) short_of = true;
                     else A.free_c[n] = have - (uint32_t)need;
@@ -650,27 +738,31 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
             });
             nd_wave_order();
         }
+        const float own = A.ds_g[j];                         // j gives nothing to itself
+        nd_wave_order();
+        if (lane == 0) A.ds_g[j] = INF;
+        nd_wave_order();
         uint32_t n0 = 0;
         while (ok && lack > 0 && n0 < N) {                   // the walk over the nodes, a node per lane
             const uint32_t n = n0 + lane;
             const bool in = n < N;
-            uint32_t offer = 0, c = 0;
-            float low = INF;                                 // the lowest slope among the others on the node
+            uint32_t offer = 0, c = 0, fg = 0, fc = 0;
+            float low = INF;                                 // the lowest slope among the others on the node (j's own is infinite now)
+            const uint32_t base_n = n * gpn;
             if (in) {
-                const uint32_t fg = A.free_g[n], by_cpu = A.free_c[n] / per_gpu;
-                offer = fg < by_cpu ? fg : by_cpu;
-                c = A.cnt[n];
-                const uint32_t *r = A.res + n * gpn;
-                for (uint32_t i = 0; i < c; i += 4u) {       // four residents at a time (past the last one: nobody)
-                    uint32_t w[4];
-                    float sl[4];
-#pragma unroll
-                    for (uint32_t k = 0; k < 4; ++k) w[k] = i + k < c ? r[i + k] >> 16 : j;
-#pragma unroll
-                    for (uint32_t k = 0; k < 4; ++k) sl[k] = w[k] != j ? A.ds_g[w[k]] : INF;
-#pragma unroll
-                    for (uint32_t k = 0; k < 4; ++k) low = sl[k] < low ? sl[k] : low;
+                fg = A.free_g[n]; fc = A.free_c[n]; c = A.cnt[n];
+                if ((gpn & 7u) == 0u) {                      // eight residents at a time, all their loads unconditional
+                    for (uint32_t i = 0; i < gpn; i += 8u) {
+                        const uint4 q = res4[(base_n + i) / 4u], r = res4[(base_n + i) / 4u + 1u];
+                        const float s0 = A.ds_g[q.x >> 16], s1 = A.ds_g[q.y >> 16], s2 = A.ds_g[q.z >> 16], s3 = A.ds_g[q.w >> 16];
+                        const float s4 = A.ds_g[r.x >> 16], s5 = A.ds_g[r.y >> 16], s6 = A.ds_g[r.z >> 16], s7 = A.ds_g[r.w >> 16];
+                        low = fminf(fminf(fminf(low, fminf(s0, s1)), fminf(s2, s3)), fminf(fminf(s4, s5), fminf(s6, s7)));
+                    }
+                } else {
+                    for (uint32_t i = 0; i < c; ++i) low = fminf(low, A.ds_g[A.res[base_n + i] >> 16]);
                 }
+                const uint32_t by_cpu = over(fc, rcp);
+                offer = fg < by_cpu ? fg : by_cpu;
             }
             const bool ask = low < INF && (below_min || st.slope > low);     // somebody here may be shrunk
             const uint32_t upto = nd_wave_scan(offer), before = upto - offer;
@@ -681,11 +773,10 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
             if (__ballot(lane <= last && offer > 0u)) dirty = true;
             if (lane <= last && offer) {
                 const uint32_t k = offer < lack - before ? offer : lack - before;
-                if (gi_j >= 0) nd_add(A, n, j, k, per_gpu);
-                else if (c < gpn) {                          // it is on no node yet, and on a walk's node only once
-                    A.free_g[n] -= k; A.free_c[n] -= k * per_gpu;
-                    A.res[n * gpn + c] = (j << 16) | k; A.cnt[n] = c + 1u;
-                }
+                A.free_g[n] = fg - k; A.free_c[n] = fc - k * per_gpu;
+                const int at = gi_j >= 0 ? nd_find(A, n, j) : -1;        // (a newcomer is on no node that the walk comes to)
+                if (at >= 0) A.res[base_n + (uint32_t)at] += k;
+                else if (c < gpn) { A.res[base_n + c] = (j << 16) | k; A.cnt[n] = c + 1u; }
             }
             const uint32_t got = wave_lane_u32(upto, last < 64u ? last : 63u);
             lack -= got < lack ? got : lack;
@@ -696,14 +787,19 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
             while (lack > 0) {                               // node f: a resident per lane (a node has at most 64 here)
                 const uint32_t cf = (uint32_t)__builtin_amdgcn_readfirstlane((int)A.cnt[f]);
                 const uint32_t free_g = A.free_g[f], free_c = A.free_c[f];
-                const uint32_t word = lane < cf ? A.res[base + lane] : ND_NONE;
+                const uint32_t word = lane < gpn ? A.res[base + lane] : EMPTY;
                 const uint32_t rv = word >> 16;
-                const float sl = lane < cf && rv != j ? A.ds_g[rv] : INF;
-                unsigned long long key = ~0ull;              // (slope as a word that orders like it, job): lower job among equals
-                if (sl < INF) key = ((unsigned long long)rs_ordered(sl) << 32) | rv;
-                key = wave_min_u64_rows(key);
-                if (key == ~0ull || !(below_min || st.slope > rs_unordered((uint32_t)(key >> 32)))) break;
-                const uint32_t who = (uint32_t)key;
+                const float sl = A.ds_g[rv];
+                // the lowest slope (as a word that orders like it), then the lowest job that has it
+                uint32_t key = sl < INF ? rs_ordered(sl) : ND_NONE, least, who;
+                if (gpn <= 16u) {
+                    least = (uint32_t)__builtin_amdgcn_readlane((int)row_min_u32(key), 0);
+                    who = (uint32_t)__builtin_amdgcn_readlane((int)row_min_u32(key == least ? rv : ND_NONE), 0);
+                } else {
+                    least = wave_min_u32_rows(key);
+                    who = wave_min_u32_rows(key == least ? rv : ND_NONE);
+                }
+                if (least == ND_NONE || !(below_min || st.slope > rs_unordered(least))) break;
                 const int32_t gi0 = __builtin_amdgcn_readfirstlane(A.st.gi[who]);
                 const uint32_t ci0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)A.st.ci[who]);
                 const uint32_t so = (uint32_t)__builtin_amdgcn_readfirstlane((int)A.seg_off[who]);
@@ -720,14 +816,14 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
                 lost = lost + sk.gv.loss;
                 // the node afterwards, from what the lanes hold: who gives `here` of its GPUs, j takes what it can
                 const uint32_t fg = free_g + here, fc = free_c + here * per_v;
-                const uint32_t by_cpu = fc / per_gpu, offer2 = fg < by_cpu ? fg : by_cpu;
+                const uint32_t by_cpu = over(fc, rcp), offer2 = fg < by_cpu ? fg : by_cpu;
                 const uint32_t t = offer2 < lack ? offer2 : lack;
                 const bool goes = here == here_has;          // it leaves the node: the last resident takes its entry
                 const uint32_t c1 = cf - (goes ? 1u : 0u);
                 const uint32_t last_word = wave_lane_u32(word, cf - 1u);
                 uint32_t mine = word;
                 if (lane == slot) mine = goes ? last_word : word - here;
-                if (lane >= c1) mine = ND_NONE;
+                if (lane >= c1) mine = EMPTY;
                 const unsigned long long j_m = __ballot(lane < c1 && (mine >> 16) == j);
                 uint32_t c2 = c1;
                 if (t) {
@@ -743,30 +839,29 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
                 lack -= t;
                 uint32_t rest = dg - here;
                 nd_wave_order();
-                for (uint32_t e = (gpus + 63u) & ~63u; rest > 0 && e > 0; e -= 64u) {     // the rest from its other parts, the last one first
-                    const uint32_t b = e - 64u;
-                    const uint32_t w = b + lane < gpus ? A.res[b + lane] : ND_NONE;
-                    unsigned long long m = __ballot((w >> 16) == who);
-                    while (m && rest > 0) {
-                        const uint32_t s = 63u - (uint32_t)__clzll((long long)m), i = b + s, n1 = i / gpn;
-                        m &= ~(1ull << s);
-                        const uint32_t k = wave_lane_u32(w, s) & 0xFFFFu, give = k < rest ? k : rest;
-                        if (lane == 0) {
+                if (rest > 0)                                // the rest from its other parts, the last one first
+                    for_parts(who, std::true_type{}, [&](uint32_t b, uint32_t w, unsigned long long m) {
+                        const uint32_t k = (m >> lane) & 1ull ? w & 0xFFFFu : 0u, upto = nd_wave_scan(k), all = wave_lane_u32(upto, 63u);
+                        const uint32_t behind = all - upto;  // what the entries after this one have
+                        if (k && behind < rest) {
+                            const uint32_t give = k < rest - behind ? k : rest - behind, i = b + lane, n1 = over(i, rcp_gpn);
                             A.free_g[n1] += give; A.free_c[n1] += give * per_v;
-                            if (give < k) A.res[i] = (who << 16) | (k - give);
-                            else {                           // (a job is on a node once: no entry still to come moves)
+                            if (give < k) A.res[i] = w - give;
+                            else {                           // (a job is on a node once: no other lane's node, no entry still to come)
                                 const uint32_t l = A.cnt[n1] - 1u;
                                 A.res[i] = A.res[n1 * gpn + l];
-                                A.res[n1 * gpn + l] = ND_NONE;
+                                A.res[n1 * gpn + l] = EMPTY;
                                 A.cnt[n1] = l;
                             }
                         }
-                        rest -= give;
-                    }
-                    nd_wave_order();
-                }
+                        nd_wave_order();
+                        rest -= all < rest ? all : rest;
+                        return rest > 0;
+                    });
+                nd_wave_order();
             }
         }
+        if (lane == 0) A.ds_g[j] = own;
         if (ok && lack == 0u && (below_min || st.gain > lost)) {
             if (lane == 0) { A.st.gi[j] = st.tgt; A.st.ci[j] = st.lvl; }
             moves += 1u;
@@ -783,8 +878,8 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
         epoch += 1u; touched = 0u; lost = 0.f;
         const uint32_t more = sh_cpl[st.lvl] - sh_cpl[A.st.ci[j]];
         bool ok = true;
-        for_parts(j, [&](unsigned long long m, uint32_t b, uint32_t word) {
-            while (m && ok) {
+        for_parts(j, std::false_type{}, [&](uint32_t b, uint32_t word, unsigned long long m) {
+            while (m) {
                 const uint32_t s = (uint32_t)__ffsll((long long)m) - 1u, n = (b + s) / gpn;
                 m &= m - 1ull;
                 const unsigned long long need = (unsigned long long)more * (wave_lane_u32(word, s) & 0xFFFFu);
@@ -798,7 +893,7 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
                     }
                     uint32_t who;
                     const float low = nd_lowest_on_wave(A, n, j, A.ds_c, who, lane);
-                    if (who == ND_NONE || !(st.slope > low)) { ok = false; break; }
+                    if (who == ND_NONE || !(st.slope > low)) { ok = false; return false; }
                     const int32_t gi0 = __builtin_amdgcn_readfirstlane(A.st.gi[who]);
                     const uint32_t ci0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)A.st.ci[who]);
                     const uint32_t so = A.seg_off[who], ns = A.seg_off[who + 1] - so;
@@ -812,14 +907,14 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
                         A.ds_g[who] = sk.ds_g; A.ds_c[who] = sk.ds_c;
                     }
                     const uint32_t less = sh_cpl[ci0] - sh_cpl[ci0 - 1u];
-                    for_parts(who, [&](unsigned long long m2, uint32_t b2, uint32_t w2) {    // it gives a level on all its nodes
-                        if ((m2 >> lane) & 1ull) A.free_c[(b2 + lane) / gpn] += less * (w2 & 0xFFFFu);
+                    for_parts(who, std::false_type{}, [&](uint32_t b2, uint32_t w2, unsigned long long m2) {     // it gives a level on all its nodes
+                        if ((m2 >> lane) & 1ull) A.free_c[over(b2 + lane, rcp_gpn)] += less * (w2 & 0xFFFFu);
                         return true;
                     });
                     nd_wave_order();
                 }
             }
-            return ok;
+            return true;
         });
         if (ok && st.gain > lost) {
             if (lane == 0) A.st.ci[j] = st.lvl;
@@ -842,7 +937,7 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
                         gpus_done = true;
                         if (dirty) {                         // (the CPU steps' turn comes when the nodes are back)
                             did = DID_UNDO;
-                            done = !((A.any[j] >> 1) & 1u);
+                            done = !(A.uc[j] > 0.f);
                         }
                     }
                 }
@@ -855,9 +950,10 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
             __syncthreads();
             const uint32_t did = sh_did, n_touched = sh_touched;
             if (did & (DID_GPUS | DID_CPUS)) {
-                for (uint32_t i = wave; i <= n_touched; i += WAVES) {            // a wavefront per job whose state changed
-                    const uint32_t v = (uint32_t)__builtin_amdgcn_readfirstlane((int)(i < n_touched ? A.touched[i] : j));
-                    nd_refresh_wave(A, v, __builtin_amdgcn_readfirstlane(A.st.gi[v]), (uint32_t)__builtin_amdgcn_readfirstlane((int)A.st.ci[v]), lane);
+                for (uint32_t i = wave; i < 2u * (n_touched + 1u); i += WAVES) { // two wavefronts per job whose state changed: GPUs, CPUs
+                    const uint32_t v = (uint32_t)__builtin_amdgcn_readfirstlane((int)(i < 2u * n_touched ? A.touched[i >> 1] : j));
+                    nd_refresh_wave(A, v, __builtin_amdgcn_readfirstlane(A.st.gi[v]), (uint32_t)__builtin_amdgcn_readfirstlane((int)A.st.ci[v]), lane,
+                                    (i & 1u) == 0u, (i & 1u) != 0u);
                 }
                 copy_nodes(keep, nodes);
             } else if (did & DID_UNDO) {
@@ -882,73 +978,121 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
         __syncthreads();
         for (uint32_t k = 0; k < n_first; ++k) schedule_job((uint32_t)__builtin_amdgcn_readfirstlane((int)A.tmp_off[k]));
     }
-    // ---- then the others, in an order that is fixed here; jobs with nothing to do are passed over (k_reschedule_nodes
-    // says when that is)
-    for (uint32_t j = tid; j < J; j += THREADS) {
-        const bool in = rs_part(A, j) && !A.first[j];
-        A.sg[j] = in ? A.ug[j] : -1.f;                       // the cached slopes are current; -1: not in the list
-        A.sc[j] = in ? A.uc[j] : -1.f;
-    }
-    auto comes_before = [&](float ga, float ca, uint32_t a, float gb, float cb, uint32_t b) {
-        return ga > gb || (ga == gb && (ca > cb || (ca == cb && a < b)));
-    };
-    float last_g = INF, last_c = INF;
-    uint32_t last_j = 0u;
+    // ---- then the others, in an order that is fixed here (by slopes; the cached ones are current); jobs with nothing to
+    // do are passed over (k_reschedule_nodes says when that is)
+    for (uint32_t j = tid; j < J; j += THREADS)              // 0: not in the list
+        A.okey[j] = rs_part(A, j) && !A.first[j] ? ((unsigned long long)rs_ordered(A.ug[j]) << 32) | rs_ordered(A.uc[j]) : 0ull;
+    unsigned long long last_key = ~0ull, my_key = 0ull;      // my_*: the first job of this thread's to serve
+    uint32_t last_j = 0u, my_j = ND_NONE;
     bool fresh = true;                                       // a step was committed since the last look (or this is the first)
+    RsMin low[2];                                            // the two lowest slopes per resource, and whose the lowest is
+    low[0] = low[1] = RsMin{INF, INF, ND_NONE};
     for (;;) {
         if (fresh) {
-            RsMin two[2];
-            rs_two_lowest<WAVES, THREADS>(sh_ds, J, tid, lane, wave, sh_two_k, sh_two_s, two);
-            if (tid == 0) { sh_min[0] = two[0]; sh_min[1] = two[1]; }
             // what the nodes can give at every CPU level, and all free CPUs: a wavefront per sum
             for (uint32_t l = wave; l <= A.X.grid.n_cpu; l += WAVES) {
-                const uint32_t per_gpu = l < A.X.grid.n_cpu ? sh_cpl[l] : 1u;
+                const bool cpus = l == A.X.grid.n_cpu;
+                const float rcp = cpus ? 1.f : sh_rcp[l];
                 uint32_t t = 0;
                 for (uint32_t n = lane; n < N; n += 64u) {
-                    const uint32_t by_cpu = A.free_c[n] / per_gpu;
-                    t += l == A.X.grid.n_cpu || by_cpu < A.free_g[n] ? by_cpu : A.free_g[n];
+                    const uint32_t by_cpu = over(A.free_c[n], rcp), fg = A.free_g[n];
+                    t += cpus || by_cpu < fg ? by_cpu : fg;
                 }
                 t = nd_wave_sum(t);
-                if (lane == 0) { if (l < A.X.grid.n_cpu) sh_take[l] = t; else sh_free_c = t; }
+                if (lane == 0) { if (cpus) sh_free_c = t; else sh_take[l] = t; }
             }
-            __syncthreads();
+            // the two lowest slopes (as words that order like them) and the job of the lowest: every thread's, every
+            // wavefront's, then all wavefronts' by everybody
+            float a[2] = {INF, INF}, b[2] = {INF, INF};
+            uint32_t ia[2] = {ND_NONE, ND_NONE};
+            for (uint32_t v = tid; v < J; v += THREADS)
+#pragma unroll
+                for (uint32_t r = 0; r < 2; ++r) {           // ascending jobs: the lower one stays among equals
+                    const float y = sh_ds[r * (J + 1) + v];
+                    if (y < a[r]) { b[r] = a[r]; a[r] = y; ia[r] = v; }
+                    else if (y < b[r]) b[r] = y;
+                }
+#pragma unroll
+            for (uint32_t r = 0; r < 2; ++r) {
+                const uint32_t mine = rs_ordered(a[r]), least = wave_min_u32_rows(mine);
+                const uint32_t whose = wave_min_u32_rows(mine == least ? ia[r] : ND_NONE);
+                const uint32_t second = wave_min_u32_rows(ia[r] != ND_NONE && ia[r] == whose ? rs_ordered(b[r]) : mine);
+                if (lane == 0) { sh_low[r][wave][0] = least; sh_low[r][wave][1] = whose; sh_low[r][wave][2] = second; }
+            }
+            rs_lds_barrier();
+#pragma unroll
+            for (uint32_t r = 0; r < 2; ++r) {
+                const uint32_t w = lane < WAVES ? lane : 0u;
+                const uint32_t mine = sh_low[r][w][0], i = sh_low[r][w][1], s2 = sh_low[r][w][2];
+                const uint32_t least = (uint32_t)__builtin_amdgcn_readlane((int)row_min_u32(mine), 0);
+                low[r].i1 = (uint32_t)__builtin_amdgcn_readlane((int)row_min_u32(mine == least ? i : ND_NONE), 0);
+                low[r].m1 = rs_unordered(least);
+                low[r].m2 = rs_unordered((uint32_t)__builtin_amdgcn_readlane((int)row_min_u32(i == low[r].i1 ? s2 : mine), 0));
+            }
         }
-        const RsMin mg = sh_min[0], mc = sh_min[1];
+        // the job's place in the order when it is still to be served and finds something to do, else 0
         const uint32_t free_c = sh_free_c;
-        float best_g = -1.f, best_c = -1.f;
-        uint32_t best_j = ND_NONE;
-        for (uint32_t j0 = tid; j0 < J; j0 += 4 * THREADS) {             // four jobs' values in flight
-            float kg[4], kc[4], ug[4], uc[4];
-            uint32_t dg[4], lv[4];
-            unsigned long long dc[4];
+        auto place_of = [&](uint32_t j, unsigned long long key, float ug, float uc, uint32_t dg, uint32_t lv, unsigned long long dc) {
+            const float lowest_g = j == low[0].i1 ? low[0].m2 : low[0].m1, lowest_c = j == low[1].i1 ? low[1].m2 : low[1].m1;
+            const bool gpu_idle = !(ug > 0.f) || (sh_take[lv] < dg && !(ug > lowest_g));
+            const bool cpu_idle = !(uc > 0.f) || (free_c < dc && !(uc > lowest_c));
+            return (gpu_idle && cpu_idle) || key > last_key || (key == last_key && j <= last_j) ? 0ull : key;
+        };
+        if (fresh) {
+            constexpr uint32_t UN = 4;                       // jobs whose values are in flight
+            my_key = 0ull; my_j = ND_NONE;
+            for (uint32_t j0 = tid; j0 < J; j0 += UN * THREADS) {
+                unsigned long long key[UN], dc[UN];
+                float ug[UN], uc[UN];
+                uint32_t dg[UN], lv[UN];
 #pragma unroll
-            for (uint32_t k = 0; k < 4; ++k) {
-                const uint32_t j = j0 + k * THREADS;
-                const bool in = j < J;
-                kg[k] = in ? A.sg[j] : -1.f; kc[k] = in ? A.sc[j] : -1.f;
-                ug[k] = in ? A.ug[j] : 0.f; uc[k] = in ? A.uc[j] : 0.f;
-                dg[k] = in ? A.udg[j] : 0u; lv[k] = in ? A.st.ci[j] : 0u; dc[k] = in ? A.udc_c[j] : 0ull;
-            }
+                for (uint32_t k = 0; k < UN; ++k) {
+                    const uint32_t j = j0 + k * THREADS;
+                    const bool in = j < J;
+                    key[k] = in ? A.okey[j] : 0ull;
+                    ug[k] = in ? A.ug[j] : 0.f; uc[k] = in ? A.uc[j] : 0.f;
+                    dg[k] = in ? A.udg[j] : 0u; lv[k] = in ? A.st.ci[j] : 0u; dc[k] = in ? A.udc_c[j] : 0ull;
+                }
 #pragma unroll
-            for (uint32_t k = 0; k < 4; ++k) {
-                const uint32_t j = j0 + k * THREADS;
-                if (kg[k] < 0.f || !comes_before(last_g, last_c, last_j, kg[k], kc[k], j)) continue;
-                const float lowest_g = j == mg.i1 ? mg.m2 : mg.m1, lowest_c = j == mc.i1 ? mc.m2 : mc.m1;
-                const bool gpu_idle = !(ug[k] > 0.f) || (sh_take[lv[k]] < dg[k] && !(ug[k] > lowest_g));
-                const bool cpu_idle = !(uc[k] > 0.f) || (free_c < dc[k] && !(uc[k] > lowest_c));
-                if (gpu_idle && cpu_idle) continue;
-                if (best_j == ND_NONE || comes_before(kg[k], kc[k], j, best_g, best_c, best_j)) { best_g = kg[k]; best_c = kc[k]; best_j = j; }
+                for (uint32_t k = 0; k < UN; ++k) {
+                    const uint32_t j = j0 + k * THREADS;
+                    const unsigned long long place = place_of(j, key[k], ug[k], uc[k], dg[k], lv[k], dc[k]);
+                    if (place > my_key) { my_key = place; my_j = j; }        // (ascending jobs)
+                }
             }
+        } else if (wave == (last_j % THREADS) / 64u) {
+            // nothing was committed: every thread's first job stays it, but the one's that has been served.  Its wavefront
+            // looks through that thread's jobs, a job per lane (at most 48)
+            const uint32_t owner = last_j % THREADS, j = owner + lane * THREADS;
+            unsigned long long place = 0ull;
+            if (j < J) place = place_of(j, A.okey[j], A.ug[j], A.uc[j], A.udg[j], A.st.ci[j], A.udc_c[j]);
+            const uint32_t hi = (uint32_t)(place >> 32), lo = (uint32_t)place;
+            const uint32_t top_hi = wave_max_u32_rows(hi), top_lo = wave_max_u32_rows(hi == top_hi ? lo : 0u);
+            const unsigned long long top = ((unsigned long long)top_hi << 32) | top_lo;
+            const uint32_t first = wave_min_u32_rows(top && place == top ? j : ND_NONE);
+            if (tid == owner) { my_key = top; my_j = first; }
         }
-        const RsPick pick = rs_pick_first<WAVES>(best_g, best_c, best_j, lane, wave, sh_pick_key, sh_pick_j);
-        if (pick.j == ND_NONE) break;
-        last_g = pick.g; last_c = pick.c; last_j = (uint32_t)__builtin_amdgcn_readfirstlane((int)pick.j);
+        {                                                    // the first of the threads' jobs in the order
+            const uint32_t hi = (uint32_t)(my_key >> 32), lo = (uint32_t)my_key;
+            const uint32_t top_hi = wave_max_u32_rows(hi), top_lo = wave_max_u32_rows(hi == top_hi ? lo : 0u);
+            const uint32_t first = wave_min_u32_rows(hi == top_hi && lo == top_lo ? my_j : ND_NONE);
+            if (lane == 0) { sh_pick_key[wave] = ((unsigned long long)top_hi << 32) | top_lo; sh_pick_j[wave] = first; }
+            rs_lds_barrier();
+            const uint32_t w = lane < WAVES ? lane : 0u;     // (at most 16 wavefronts: a row of lanes)
+            const unsigned long long k2 = sh_pick_key[w];
+            const uint32_t j2 = sh_pick_j[w], hi2 = (uint32_t)(k2 >> 32), lo2 = (uint32_t)k2;
+            const uint32_t best_hi = 0xFFFFFFFFu - (uint32_t)__builtin_amdgcn_readlane((int)row_min_u32(0xFFFFFFFFu - hi2), 0);
+            const uint32_t best_lo = 0xFFFFFFFFu - (uint32_t)__builtin_amdgcn_readlane((int)row_min_u32(hi2 == best_hi ? 0xFFFFFFFFu - lo2 : 0xFFFFFFFFu), 0);
+            last_key = ((unsigned long long)best_hi << 32) | best_lo;
+            last_j = (uint32_t)__builtin_amdgcn_readlane((int)row_min_u32(k2 == last_key ? j2 : ND_NONE), 0);
+        }
+        if (last_j == ND_NONE) break;
         full += 1u;
         const uint32_t before = moves;
         schedule_job(last_j);
         fresh = __syncthreads_or(wave == 0 && moves != before) != 0;
     }
-    nd_finish<THREADS>(A, reinterpret_cast<uint32_t *>(sh_ds), reinterpret_cast<uint32_t *>(sh_ds) + J, keep, sh_mem, sh_scan);
+    nd_finish<THREADS>(A, reinterpret_cast<uint32_t *>(sh_ds), reinterpret_cast<uint32_t *>(sh_ds) + J, keep, A.touched, sh_mem, sh_scan);
     if (tid == 0 && A.stats) { A.stats[0] = moves; A.stats[1] = full; A.stats[2] = shrinks; A.stats[3] = undone; A.stats[4] = 0u; }
 }
 
@@ -1402,7 +1546,7 @@ __global__ __launch_bounds__(ND_THREADS) void k_reschedule_nodes(NdKernArgs K) {
     __syncthreads();
 
     // ---- memory, then the records
-    nd_finish<ND_THREADS>(A, A.np, A.tmp_off, A.tmp_parts, sh_mem, sh_scan);
+    nd_finish<ND_THREADS>(A, A.np, A.tmp_off, A.tmp_parts, A.touched, sh_mem, sh_scan);
     if (tid == 0 && A.stats) { A.stats[0] = sh_moves; A.stats[1] = sh_full; A.stats[2] = sh_shrinks; A.stats[3] = sh_undone; A.stats[4] = 0u; }
 }
 
@@ -1453,14 +1597,14 @@ int32_t rk_launch_reschedule_nodes(rk_ctx *ctx, const float *ref_thr, const rk_p
     const uint64_t gpus = (uint64_t)nodes->n_nodes * nodes->gpus_per_node;
     int32_t rc;
     const size_t n = J ? J : 1, N = nodes->n_nodes;
-    const size_t nodes_words = (3 * N + (size_t)gpus + 3) & ~(size_t)3;          // whole 16-byte pieces: the copy moves four words at a time
+    const size_t nodes_words = (((3 * N + 3) & ~(size_t)3) + (size_t)gpus + 3) & ~(size_t)3;   // whole 16-byte pieces: copied and searched four words at a time
     uint32_t *w_nodes, *w_jobs;
     float *f_jobs;
     unsigned long long *u64;
     if ((rc = rk_scratch(ctx, SL_ND_NODES, (2 * nodes_words + 2 * N + (size_t)gpus) * sizeof(uint32_t), (void **)&w_nodes))) return rc;
-    if ((rc = rk_scratch(ctx, SL_ND_U32, (15 * n + 1) * sizeof(uint32_t), (void **)&w_jobs))) return rc;
+    if ((rc = rk_scratch(ctx, SL_ND_U32, (14 * n + 1) * sizeof(uint32_t), (void **)&w_jobs))) return rc;
     if ((rc = rk_scratch(ctx, SL_ND_F32, 10 * n * sizeof(float), (void **)&f_jobs))) return rc;
-    if ((rc = rk_scratch(ctx, SL_ND_U64, n * sizeof(unsigned long long), (void **)&u64))) return rc;
+    if ((rc = rk_scratch(ctx, SL_ND_U64, 2 * n * sizeof(unsigned long long), (void **)&u64))) return rc;
     NdKernArgs K;
     NdBody &A = K.b;
     K.X.ref_thr = ref_thr; K.X.tb = table_dev(table); K.X.grid = grid_dev(grid);
@@ -1471,19 +1615,19 @@ int32_t rk_launch_reschedule_nodes(rk_ctx *ctx, const float *ref_thr, const rk_p
     A.state = jobs_state->state; A.cur_seg = jobs_state->cur_seg; A.cur_c = jobs_state->cur_c;
     A.floor_seg = jobs_state->floor_seg; A.floor_c = jobs_state->floor_c;
     A.prev_off = prev_off; A.prev_entries = prev_entries; A.n_prev = n_prev_entries;
-    A.free_g = w_nodes; A.free_c = w_nodes + N; A.cnt = w_nodes + 2 * N; A.res = w_nodes + 3 * N;
+    A.free_g = w_nodes; A.free_c = w_nodes + N; A.cnt = w_nodes + 2 * N; A.res = w_nodes + ((3 * N + 3) & ~(size_t)3);
     A.keep_nodes = w_nodes + nodes_words; A.nodes_words = (uint32_t)nodes_words;
     A.plist = w_nodes + 2 * nodes_words; A.tmp_parts = A.plist + 2 * N;
     A.st.gi = reinterpret_cast<int32_t *>(w_jobs); A.st.ci = w_jobs + n; A.udg = w_jobs + 2 * n; A.touched = w_jobs + 3 * n;
     A.stamp = w_jobs + 4 * n; A.first = w_jobs + 5 * n; A.keep_ci = w_jobs + 6 * n;
-    A.keep_gi = reinterpret_cast<int32_t *>(w_jobs + 7 * n); A.np = w_jobs + 8 * n; A.tier = w_jobs + 9 * n;
+    A.keep_gi = reinterpret_cast<int32_t *>(w_jobs + 7 * n); A.np = w_jobs + 8 * n;
     A.tmp_off = w_jobs + 10 * n;                             // n + 1 words
     A.seg_off = table->seg_off;
     uint32_t *more = w_jobs + 11 * n + 1;
-    A.tgt_g = reinterpret_cast<int32_t *>(more); A.lvl_g = more + n; A.lvl_c = more + 2 * n; A.any = more + 3 * n;
+    A.tgt_g = reinterpret_cast<int32_t *>(more); A.lvl_g = more + n; A.lvl_c = more + 2 * n;
     A.ds_g = f_jobs; A.ds_c = f_jobs + n; A.ug = f_jobs + 2 * n; A.uc = f_jobs + 3 * n; A.sg = f_jobs + 4 * n;
     A.sc = f_jobs + 5 * n; A.keep_ds = f_jobs + 6 * n; A.gain_g = f_jobs + 8 * n; A.gain_c = f_jobs + 9 * n;
-    A.udc_c = u64;
+    A.udc_c = u64; A.okey = u64 + n;
     A.assign = assign; A.place_off = place_off; A.entries = entries; A.total = total; A.stats = stats;
     // Where the nodes and their copy fit a CU's LDS beside the cached slopes (512 nodes of 8 GPUs and 10,000 jobs do), the
     // loop runs on them there.
