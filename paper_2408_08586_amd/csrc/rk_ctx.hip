@@ -119,16 +119,15 @@ int32_t rk_destroy(rk_ctx *ctx) {
     if (!ctx) return RK_ERR_INVALID_ARG;
     (void)hipSetDevice(ctx->device);
     (void)hipStreamSynchronize(ctx->stream);
+    if (ctx->sim_stream) (void)hipStreamSynchronize(ctx->sim_stream);
     for (int i = 0; i < RK_SCRATCH_SLOTS; ++i)
         if (ctx->scratch[i]) (void)hipFree(ctx->scratch[i]);
     if (ctx->h_pinned) (void)hipHostFree(ctx->h_pinned);
     if (ctx->h_stage) (void)hipHostFree(ctx->h_stage);
     if (ctx->counts_ev) (void)hipEventDestroy(ctx->counts_ev);
     if (ctx->sim_stream) {
-        (void)hipStreamSynchronize(ctx->sim_stream);
         (void)hipStreamDestroy(ctx->sim_stream);
-        (void)hipEventDestroy(ctx->sim_ev[0]);
-        (void)hipEventDestroy(ctx->sim_ev[1]);
+        for (hipEvent_t ev : ctx->sim_ev) if (ev) (void)hipEventDestroy(ev);
     }
     free(ctx);
     return RK_OK;

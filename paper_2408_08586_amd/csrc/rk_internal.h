@@ -23,7 +23,7 @@ struct rk_ctx {
     uint32_t park_stride;                   // enumeration: words per job between its two passes
     hipEvent_t counts_ev;                   // enumeration: the counts have reached the host (made on demand)
     hipStream_t sim_stream;                 // simulation: its own stream (a tick is captured as a graph), made on demand
-    hipEvent_t sim_ev[2];                   // ... ordered after and before the context's stream with these
+    hipEvent_t sim_ev[4];                   // ... ordered after and before the context's stream with the first two; its batches of ticks
     bool fused_lds_raised;                  // fused kernel: its dynamic LDS limit has been raised for this context
     bool loop_lds_raised;                   // the Schedule loop over totals: likewise
     bool nodes_lds_raised;                  // the Schedule loop over nodes: likewise

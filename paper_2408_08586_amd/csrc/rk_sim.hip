@@ -2,23 +2,31 @@
 // the reconfiguration-penalty gate (paper Sec. 5.2 "Incorporating
 // reconfiguration penalty", Sec. 7.4).  The curves are computed once by the
 // caller; a tick is
-//   k_sim_begin   (one workgroup) advances the tick counter; per-job state of
-//                 the tick: inactive, frozen or free to move; floors of the
-//                 frozen jobs; capacity left
-//   the allocation kernels from these floors
-//   k_sim_commit  (thread per job) reconfiguration count and cost, progress,
-//                 completion; remembers what every job holds
+//   the allocation kernels from the floors of the tick
+//   k_sim_step    (one workgroup) closes the tick: reconfiguration count and
+//                 cost, progress, completion, what every job holds; then opens
+//                 the next one: per-job state (inactive, frozen or free to
+//                 move), floors of the frozen jobs, capacity left.
+// A round is a function of what it starts from.  Where the next tick starts
+// from exactly what the last round started from (nobody arrived, left or
+// thawed, and for the loops nobody moved: 185 to 251 of the 720 ticks of the
+// 406-job trace), its result is the one at hand, and k_sim_step closes that
+// tick as well instead of handing it to the round's kernels (720 ticks: 35.9 ->
+// 27.1 ms under the greedy, 73.0 -> 46.3 ms over the nodes, of which one kernel
+// launch less per tick is about 2 ms).
 // The tick counter lives on the device, so every tick is the same sequence of
 // launches with the same arguments: the first tick runs eagerly (it also sizes
 // the scratch memory), the sequence is then captured once as a HIP graph on a
-// stream of the simulation's own and replayed for the remaining ticks.
+// stream of the simulation's own and replayed until the counter, which
+// k_sim_step also writes to pinned host memory, has reached the last tick.
 #include "rk_internal.h"
 #include "rk_model.h"
 
 namespace {
 
 constexpr int SIM_THREADS = 1024;
-constexpr int COMMIT_THREADS = 256;
+constexpr uint32_t SIM_BATCH = 4;              // replays between two looks at the tick counter
+constexpr int H_TICK = 63;                     // word of the context's pinned memory that holds it
 
 struct SimState {               // per job, between the ticks
     uint32_t *g, *c, *plan;     // what the job holds (g = 0: nothing)
@@ -32,13 +40,15 @@ struct SimArgs {
     TableDev tb;
     GridDev grid;
     rk_cluster cl;
-    uint32_t n_jobs;
+    uint32_t n_jobs, n_ticks;
+    uint32_t loop;              // the round starts from what every job holds (policies 1 and 2), not the frozen ones only
     const double *arrival, *work, *delta;
     double dt, gate;
     SimState S;
     FloorsDev F;
     const rk_assign *assign;
-    uint32_t *tick;             // device counter, advanced by k_sim_begin
+    uint32_t *tick;             // device counter: the tick whose round comes next
+    uint32_t *h_tick;           // its copy in pinned host memory
     float *tick_total;          // the allocation's total of the current tick
     rk_sim_result out;
     double *held;               // result arrays or scratch when the caller passes none
@@ -48,6 +58,7 @@ struct SimArgs {
     uint32_t *at_off, *now_off;
     rk_place_entry *at_ent, *now_ent;
 };
+static_assert(sizeof(rk_place_entry) == sizeof(uint4), "a part is compared and copied as one piece");
 
 __global__ __launch_bounds__(SIM_THREADS) void k_sim_init(SimArgs A) {
     const uint32_t j = blockIdx.x * SIM_THREADS + threadIdx.x;
@@ -55,126 +66,162 @@ __global__ __launch_bounds__(SIM_THREADS) void k_sim_init(SimArgs A) {
     A.S.g[j] = 0; A.S.c[j] = 0; A.S.plan[j] = RK_NO_PLAN; A.S.seg[j] = -1; A.S.lvl[j] = 0;
     A.S.owed[j] = 0.0; A.S.done[j] = 0;
     A.held[j] = 0.0; A.progress[j] = 0.0; A.finish[j] = -1.0; A.n_reconf[j] = 0;
-    if (j == 0) *A.tick = 0xFFFFFFFFu;                    // the first k_sim_begin makes it 0
+    if (j == 0) *A.tick = 0u;
     if (A.at_off) { A.at_off[j] = 0u; if (j == 0) A.at_off[A.n_jobs] = 0u; }   // nobody is anywhere yet
 }
 
-// the placement this tick made is where the jobs are when the next tick begins
-__global__ void k_sim_keep_placement(SimArgs A) {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i <= A.n_jobs) A.at_off[i] = A.now_off[i];
-    if (i < A.now_off[A.n_jobs]) A.at_ent[i] = A.now_ent[i];
+// Closes a tick for job j; true when the job holds other amounts than before it.
+__device__ __forceinline__ bool commit_job(const SimArgs &A, uint32_t j, double t, uint32_t &g_used) {
+    const rk_assign a = A.assign[j];
+    uint32_t g = a.g;
+    g_used += g;
+    const uint32_t g_prev = A.S.g[j], c_prev = A.S.c[j];
+    const bool same_amounts = g == g_prev && a.c == c_prev;
+    if (g_prev > 0 && g > 0 && (!same_amounts || a.plan != A.S.plan[j])) {
+        A.n_reconf[j] += 1;
+        A.S.owed[j] = A.S.owed[j] + A.delta[j];
+    }
+    if (g > 0) {
+        A.held[j] = A.held[j] + A.dt;
+        const double owed = A.S.owed[j];
+        const double paid = owed < A.dt ? owed : A.dt;
+        A.S.owed[j] = owed - paid;
+        const double train = A.dt - paid;
+        const double thr = (double)a.thr;
+        const double gain = thr * train;
+        const double progress = A.progress[j], work = A.work[j];
+        if (progress + gain >= work) {
+            A.finish[j] = t + paid + (work - progress) / thr;
+            A.progress[j] = work;
+            A.S.done[j] = 1;
+            g = 0;
+        } else {
+            A.progress[j] = progress + gain;
+        }
+    }
+    if (g == 0) {
+        if (g_prev == 0) return false;
+        A.S.g[j] = 0; A.S.c[j] = 0; A.S.plan[j] = RK_NO_PLAN; A.S.seg[j] = -1; A.S.lvl[j] = 0;
+        return true;
+    }
+    A.S.plan[j] = a.plan;
+    if (same_amounts) return false;
+    // segment index of g (the job's counts ascend) and the CPU level that costs a.c
+    const uint32_t s0 = A.tb.seg_off[j], ns = A.tb.seg_off[j + 1] - s0;
+    uint32_t lo = 0, hi = ns;
+    while (lo < hi) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (A.tb.seg_g[s0 + mid] < g) lo = mid + 1; else hi = mid;
+    }
+    uint32_t lvl = 0;
+    for (uint32_t i = 0; i < A.grid.n_cpu; ++i)
+        if (cpus_of(A.grid, i, g) == a.c) { lvl = i; break; }
+    A.S.g[j] = g; A.S.c[j] = a.c; A.S.seg[j] = (int32_t)lo; A.S.lvl[j] = lvl;
+    return true;
 }
 
-__global__ __launch_bounds__(SIM_THREADS) void k_sim_begin(SimArgs A) {
-    __shared__ unsigned long long red_g[SIM_THREADS / 64], red_c[SIM_THREADS / 64];
-    __shared__ uint32_t red_f[SIM_THREADS / 64];
-    __shared__ uint32_t tick_now;
-    const uint32_t tid = threadIdx.x;
-    if (tid == 0) { tick_now = *A.tick + 1u; *A.tick = tick_now; }
-    __syncthreads();
-    const uint32_t tick = tick_now;
-    const double t = (double)tick * A.dt;
-    unsigned long long held_g = 0, held_c = 0;
-    uint32_t n_frozen = 0;
-    for (uint32_t j = tid; j < A.n_jobs; j += SIM_THREADS) {
-        const bool active = A.arrival[j] <= t && !A.S.done[j];
-        const uint32_t g = A.S.g[j];
-        uint8_t state = RK_JOB_OUT;
-        int32_t gi = -1;
-        uint32_t ci = 0;
-        if (active) {
-            state = RK_JOB_NORMAL;
-            if (g > 0) {
-                const double T = A.held[j];
-                const bool may_move = T - ((double)A.n_reconf[j] + 1.0) * A.delta[j] > A.gate * T;
-                if (!may_move) {
-                    state = RK_JOB_FROZEN;
-                    gi = A.S.seg[j];
-                    ci = A.S.lvl[j];
-                    held_g += g;
-                    held_c += A.grid.cpu_mode ? (unsigned long long)A.grid.cpu_levels[ci] * g
-                                              : (unsigned long long)A.grid.cpu_levels[ci];
-                    ++n_frozen;
+// One workgroup, a thread per job (and every SIM_THREADS-th after it): what a thread writes of its jobs only it reads.
+// first: there is no tick to close yet.  Bound by the round trips to memory of the per-job words; at 406 jobs it takes
+// the place of two kernels, and a tick that needs no round costs one turn of its loop.
+__global__ __launch_bounds__(SIM_THREADS) void k_sim_step(SimArgs A, uint32_t first) {
+    __shared__ unsigned long long sum_g, sum_c;
+    __shared__ uint32_t sum_f, sum_used, moved;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u;
+    uint32_t tick = *A.tick;
+    if (tick >= A.n_ticks) return;                            // replays past the last tick have nothing to close
+    bool round_needed = first != 0u;                          // the same in all threads
+    if (!first && A.at_off) {
+        // the placement this tick made is where the jobs are when the next tick begins
+        bool other = false;
+        for (uint32_t i = tid; i <= A.n_jobs; i += SIM_THREADS) {
+            const uint32_t now = A.now_off[i];
+            other |= A.at_off[i] != now;
+            A.at_off[i] = now;
+        }
+        const uint32_t n = A.now_off[A.n_jobs];
+        const uint4 *now_ent = reinterpret_cast<const uint4 *>(A.now_ent);
+        uint4 *at_ent = reinterpret_cast<uint4 *>(A.at_ent);
+        for (uint32_t i = tid; i < n; i += SIM_THREADS) {
+            const uint4 now = now_ent[i], at = at_ent[i];     // (a slot never written compares as it may: at worst a round more)
+            other |= at.x != now.x || at.y != now.y || at.z != now.z || at.w != now.w;
+            at_ent[i] = now;
+        }
+        round_needed = __syncthreads_or(other) != 0;
+    }
+    for (;;) {
+        if (tid == 0) { sum_g = 0ull; sum_c = 0ull; sum_f = 0u; sum_used = 0u; moved = 0u; }
+        __syncthreads();
+        if (!first) {
+            const double t = (double)tick * A.dt;
+            uint32_t g_used = 0;
+            bool other = false;
+            for (uint32_t j = tid; j < A.n_jobs; j += SIM_THREADS)
+                if (A.F.state[j] != RK_JOB_OUT) other |= commit_job(A, j, t, g_used);
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) g_used += __shfl_xor(g_used, off, 64);
+            if (lane == 0 && g_used) atomicAdd(&sum_used, g_used);
+            if (A.loop && __ballot(other) && lane == 0) moved = 1u;
+            __syncthreads();
+            if (tid == 0) {
+                if (A.out.gpus_in_use) A.out.gpus_in_use[tick] = sum_used;
+                if (A.out.totals) A.out.totals[tick] = *A.tick_total;
+            }
+            if (moved) round_needed = true;
+            if (++tick == A.n_ticks) break;
+        }
+        const double t = (double)tick * A.dt;
+        unsigned long long held_g = 0, held_c = 0;
+        uint32_t n_frozen = 0;
+        bool other = false;
+        for (uint32_t j = tid; j < A.n_jobs; j += SIM_THREADS) {
+            const bool active = A.arrival[j] <= t && !A.S.done[j];
+            const uint32_t g = A.S.g[j];
+            uint8_t state = RK_JOB_OUT;
+            int32_t gi = -1;
+            uint32_t ci = 0;
+            if (active) {
+                state = RK_JOB_NORMAL;
+                if (g > 0) {
+                    const double T = A.held[j];
+                    const bool may_move = T - ((double)A.n_reconf[j] + 1.0) * A.delta[j] > A.gate * T;
+                    if (!may_move) {
+                        state = RK_JOB_FROZEN;
+                        gi = A.S.seg[j];
+                        ci = A.S.lvl[j];
+                        held_g += g;
+                        held_c += A.grid.cpu_mode ? (unsigned long long)A.grid.cpu_levels[ci] * g
+                                                  : (unsigned long long)A.grid.cpu_levels[ci];
+                        ++n_frozen;
+                    }
                 }
             }
+            if (first || A.F.state[j] != state || A.F.gi[j] != gi || A.F.ci[j] != ci) {
+                A.F.state[j] = state;
+                A.F.gi[j] = gi;
+                A.F.ci[j] = ci;
+                other = true;
+            }
         }
-        A.F.state[j] = state;
-        A.F.gi[j] = gi;
-        A.F.ci[j] = ci;
-    }
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        held_g += __shfl_xor(held_g, off, 64);
-        held_c += __shfl_xor(held_c, off, 64);
-        n_frozen += __shfl_xor(n_frozen, off, 64);
+        for (int off = 32; off >= 1; off >>= 1) {
+            held_g += __shfl_xor(held_g, off, 64);
+            held_c += __shfl_xor(held_c, off, 64);
+            n_frozen += __shfl_xor(n_frozen, off, 64);
+        }
+        if (lane == 0 && n_frozen) { atomicAdd(&sum_g, held_g); atomicAdd(&sum_c, held_c); atomicAdd(&sum_f, n_frozen); }
+        if (__syncthreads_or(other)) round_needed = true;
+        if (tid == 0) {
+            const unsigned long long hg = sum_g, hc = sum_c;
+            A.F.cap0[0] = hg < A.cl.G ? A.cl.G - hg : 0ull;   // frozen jobs are charged first
+            A.F.cap0[1] = hc < A.cl.C ? A.cl.C - hc : 0ull;
+            if (A.out.frozen) A.out.frozen[tick] = sum_f;
+        }
+        if (round_needed) break;
+        __syncthreads();                                      // the sums are read before they are cleared
     }
-    if ((tid & 63u) == 0) { red_g[tid >> 6] = held_g; red_c[tid >> 6] = held_c; red_f[tid >> 6] = n_frozen; }
-    __syncthreads();
     if (tid == 0) {
-        unsigned long long hg = 0, hc = 0;
-        uint32_t nf = 0;
-        for (int w = 0; w < SIM_THREADS / 64; ++w) { hg += red_g[w]; hc += red_c[w]; nf += red_f[w]; }
-        A.F.cap0[0] = hg < A.cl.G ? A.cl.G - hg : 0ull;       // frozen jobs are charged first
-        A.F.cap0[1] = hc < A.cl.C ? A.cl.C - hc : 0ull;
-        if (A.out.frozen) A.out.frozen[tick] = nf;
-        if (A.out.gpus_in_use) A.out.gpus_in_use[tick] = 0u;  // summed by k_sim_commit
-    }
-}
-
-__global__ __launch_bounds__(COMMIT_THREADS) void k_sim_commit(SimArgs A) {
-    const uint32_t j = blockIdx.x * COMMIT_THREADS + threadIdx.x;
-    const uint32_t tick = *A.tick;
-    if (j == 0 && A.out.totals) A.out.totals[tick] = *A.tick_total;
-    uint32_t g_used = 0;
-    if (j < A.n_jobs && A.F.state[j] != RK_JOB_OUT) {
-        const double t = (double)tick * A.dt;
-        const rk_assign a = A.assign[j];
-        uint32_t g = a.g;
-        g_used = g;
-        const uint32_t g_prev = A.S.g[j];
-        if (g_prev > 0 && g > 0 && (g != g_prev || a.c != A.S.c[j] || a.plan != A.S.plan[j])) {
-            A.n_reconf[j] += 1;
-            A.S.owed[j] = A.S.owed[j] + A.delta[j];
-        }
-        if (g > 0) {
-            A.held[j] = A.held[j] + A.dt;
-            const double owed = A.S.owed[j];
-            const double paid = owed < A.dt ? owed : A.dt;
-            A.S.owed[j] = owed - paid;
-            const double train = A.dt - paid;
-            const double thr = (double)a.thr;
-            const double gain = thr * train;
-            const double progress = A.progress[j], work = A.work[j];
-            if (progress + gain >= work) {
-                A.finish[j] = t + paid + (work - progress) / thr;
-                A.progress[j] = work;
-                A.S.done[j] = 1;
-                g = 0;
-            } else {
-                A.progress[j] = progress + gain;
-            }
-        }
-        if (g > 0) {
-            // segment index of g (the job's counts ascend) and the CPU level that costs a.c
-            const uint32_t s0 = A.tb.seg_off[j], ns = A.tb.seg_off[j + 1] - s0;
-            uint32_t lo = 0, hi = ns;
-            while (lo < hi) {
-                const uint32_t mid = (lo + hi) >> 1;
-                if (A.tb.seg_g[s0 + mid] < g) lo = mid + 1; else hi = mid;
-            }
-            uint32_t lvl = 0;
-            for (uint32_t i = 0; i < A.grid.n_cpu; ++i)
-                if (cpus_of(A.grid, i, g) == a.c) { lvl = i; break; }
-            A.S.g[j] = g; A.S.c[j] = a.c; A.S.plan[j] = a.plan; A.S.seg[j] = (int32_t)lo; A.S.lvl[j] = lvl;
-        } else {
-            A.S.g[j] = 0; A.S.c[j] = 0; A.S.plan[j] = RK_NO_PLAN; A.S.seg[j] = -1; A.S.lvl[j] = 0;
-        }
-    }
-    if (A.out.gpus_in_use) {
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) g_used += __shfl_xor(g_used, off, 64);
-        if ((threadIdx.x & 63u) == 0 && g_used) atomicAdd(&A.out.gpus_in_use[tick], g_used);
+        *A.tick = tick;
+        __hip_atomic_store(A.h_tick, tick, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 
@@ -227,7 +274,12 @@ extern "C" int32_t rk_simulate(rk_ctx *ctx, const float *ref_thr, const rk_plan_
     SimArgs A;
     A.tb = table_dev(table); A.grid = grid_dev(grid); A.cl = *cluster; A.n_jobs = J;
     A.arrival = trace->arrival; A.work = trace->work; A.delta = trace->delta;
-    A.dt = options->dt; A.gate = options->gate;
+    A.dt = options->dt; A.gate = options->gate; A.n_ticks = options->n_ticks; A.loop = options->policy != 0u;
+    void *h_tick;
+    RK_HIP(ctx, hipHostGetDevicePointer(&h_tick, ctx->h_pinned + H_TICK, 0));
+    A.h_tick = static_cast<uint32_t *>(h_tick);
+    // (of earlier simulations only one of a single tick may still run: it can put 1 there, which ends no loop below)
+    __atomic_store_n(ctx->h_pinned + H_TICK, 0u, __ATOMIC_RELEASE);
     A.S.owed = (double *)take(n8);
     double *s_held = (double *)take(n8), *s_prog = (double *)take(n8), *s_fin = (double *)take(n8);
     A.F.cap0 = (unsigned long long *)take(256);
@@ -258,16 +310,13 @@ extern "C" int32_t rk_simulate(rk_ctx *ctx, const float *ref_thr, const rk_plan_
     // the simulation's own stream, ordered after what the context's stream holds
     if (!ctx->sim_stream) {
         RK_HIP(ctx, hipStreamCreateWithFlags(&ctx->sim_stream, hipStreamNonBlocking));
-        RK_HIP(ctx, hipEventCreateWithFlags(&ctx->sim_ev[0], hipEventDisableTiming));
-        RK_HIP(ctx, hipEventCreateWithFlags(&ctx->sim_ev[1], hipEventDisableTiming));
+        for (hipEvent_t &ev : ctx->sim_ev) RK_HIP(ctx, hipEventCreateWithFlags(&ev, hipEventDisableTiming));
     }
     hipStream_t user = ctx->stream, s = ctx->sim_stream;
     RK_HIP(ctx, hipEventRecord(ctx->sim_ev[0], user));
     RK_HIP(ctx, hipStreamWaitEvent(s, ctx->sim_ev[0], 0));
 
     auto tick_body = [&]() -> int32_t {
-        k_sim_begin<<<1, SIM_THREADS, 0, s>>>(A);
-        RK_CHECK_LAUNCH(ctx, "k_sim_begin");
         ctx->stream = s;                                       // the allocation enqueues on the context's stream
         int32_t r;
         if (options->policy == 2u) {                           // ... searching node by node, from where the jobs are
@@ -285,18 +334,15 @@ extern "C" int32_t rk_simulate(rk_ctx *ctx, const float *ref_thr, const rk_plan_
         }
         ctx->stream = user;
         if (r) return r;
-        k_sim_commit<<<(J + COMMIT_THREADS - 1) / COMMIT_THREADS, COMMIT_THREADS, 0, s>>>(A);
-        RK_CHECK_LAUNCH(ctx, "k_sim_commit");
-        if (nodes) {
-            const uint64_t most = cap_parts > J + 1 ? cap_parts : J + 1;
-            k_sim_keep_placement<<<(uint32_t)((most + 255) / 256), 256, 0, s>>>(A);
-            RK_CHECK_LAUNCH(ctx, "k_sim_keep_placement");
-        }
+        k_sim_step<<<1, SIM_THREADS, 0, s>>>(A, 0u);
+        RK_CHECK_LAUNCH(ctx, "k_sim_step");
         return RK_OK;
     };
 
     k_sim_init<<<(J + SIM_THREADS - 1) / SIM_THREADS, SIM_THREADS, 0, s>>>(A);
     RK_CHECK_LAUNCH(ctx, "k_sim_init");
+    k_sim_step<<<1, SIM_THREADS, 0, s>>>(A, 1u);
+    RK_CHECK_LAUNCH(ctx, "k_sim_step");
     if ((rc = tick_body())) return rc;                         // tick 0, eagerly
     if (options->n_ticks > 1) {
         hipGraph_t graph = nullptr;
@@ -307,7 +353,21 @@ extern "C" int32_t rk_simulate(rk_ctx *ctx, const float *ref_thr, const rk_plan_
         if (rc) { if (graph) (void)hipGraphDestroy(graph); return rc; }
         if (e_end != hipSuccess) return rk_fail(ctx, RK_ERR_DEVICE, "hipStreamEndCapture: %s", hipGetErrorString(e_end));
         hipError_t e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-        for (uint32_t k = 1; e == hipSuccess && k < options->n_ticks; ++k) e = hipGraphLaunch(exec, s);
+        // Replays go out in batches, one batch ahead of the counter that is read back, never more of them than ticks
+        // are left.  A replay past the last tick repeats the last round and changes nothing.
+        const uint32_t n = options->n_ticks;
+        uint32_t sent = 1, run = 0, closed = 0;                // rounds enqueued, rounds known to have run, ticks closed by then
+        uint32_t sent_by[2] = {0u, 0u};                        // rounds enqueued when an event was recorded
+        for (uint32_t b = 0; e == hipSuccess && closed < n; b ^= 1u) {
+            const uint32_t before = sent;
+            for (uint32_t k = 0; e == hipSuccess && k < SIM_BATCH && sent - run < n - closed; ++k, ++sent) e = hipGraphLaunch(exec, s);
+            if (e == hipSuccess) e = hipEventRecord(ctx->sim_ev[2 + b], s);
+            sent_by[b] = sent;
+            const uint32_t w = sent > before ? b ^ 1u : b;     // the batch before this one; this one where nothing could be sent
+            if (e == hipSuccess) e = hipEventSynchronize(ctx->sim_ev[2 + w]);
+            run = sent_by[w] > run ? sent_by[w] : run;
+            closed = __atomic_load_n(ctx->h_pinned + H_TICK, __ATOMIC_ACQUIRE);
+        }
         if (e == hipSuccess) e = hipStreamSynchronize(s);      // the graph must outlive its launches
         if (exec) (void)hipGraphExecDestroy(exec);
         (void)hipGraphDestroy(graph);

@@ -236,3 +236,26 @@ def test_simulation_with_more_jobs_than_one_workgroup_selects(gpu, orc):
           f"{int(want['frozen'].sum())} frozen job-ticks, GPUs in use at the end {int(want['gpus_in_use'][-1])}")
     assert want["frozen"].sum() > 0 and (want["finish"] >= 0).sum() > 0
     run.close()
+
+
+@pytest.mark.parametrize("policy", [0, 1, 2])
+def test_simulation_of_few_ticks_and_idle_stretches(gpu, orc, policy):
+    """A tick that starts from what the last round started from is closed without a round of its own; tick counts around
+    the replays that go out together, traces that are mostly idle and ones in which every tick differs."""
+    wl = workloads.tiny()
+    wl.grid = workloads.Grid(np.array([1, 2, 4], np.uint32), 1, wl.grid.mem_levels_gb, 0)
+    nodes = (2, wl.cluster.G // 2, 4 * wl.cluster.G // 2, wl.cluster.host_mem_gb / 2)
+    wl.cluster = workloads.Cluster(wl.cluster.G, 4 * wl.cluster.G, wl.cluster.host_mem_gb)
+    r = orc.schedule_round(wl, n_threads=4)
+    J = wl.n_jobs
+    run = gpu(wl)
+    run.enumerate()
+    for arrival, seconds in ((np.zeros(J), 1e9), (np.arange(J) * 55.0, 100.0), (np.where(np.arange(J) % 2, 40.0, 300.0), 70.0)):
+        work, delta = seconds * wl.coef[:, 16], np.full(J, 3.0)
+        for n_ticks in (1, 2, 4, 5, 8, 9, 40):
+            kw = dict(policy=("greedy", "loop", "nodes")[policy], nodes=nodes if policy == 2 else None)
+            want = orc.simulator.simulate(wl.coef[:, 16], r["table"], wl.grid, wl.cluster, r["best_thr"], r["best_plan"],
+                                          r["curve_thr"], arrival, work, delta, 10.0, n_ticks, **kw)
+            got = run_on_gpu(run, r, arrival, work, delta, 10.0, n_ticks, 0.97, policy=policy, nodes=kw["nodes"])
+            same(got, want)
+    run.close()
