@@ -18,7 +18,11 @@
 //     one node each, 64 nodes at a time from the first node that still has a
 //     free GPU; a lane finds the most GPUs its node can give, a prefix sum
 //     over the lanes cuts the offers at what the job still lacks, and the
-//     parts are booked only when the whole amount has been found.
+//     parts are booked only when the whole amount has been found.  A walk that
+//     fails has seen what all nodes have left; amounts beyond that are not
+//     looked for again (the jobs a full cluster has no memory for asked every
+//     node again for each of their smaller counts: 297 -> 177 us on the round
+//     named at k_place, together with the records' lookup ahead of stage 1).
 //
 // rk_place_plans adds what Algorithm 1 does with a placement: a job that does
 // not find its amount falls back to its next smaller valid GPU count (k_place
@@ -173,6 +177,10 @@ __device__ __forceinline__ uint32_t cpus_booked(uint32_t c, uint32_t done, uint3
 
 constexpr uint32_t PLACE_PER = 8;                         // jobs per thread in the first stage
 
+// REGS: 64-node groups that the first wavefront of stage 2 keeps in registers, a node per lane and group; 0: any number
+// of nodes, in LDS.  A job is a chain of instructions on one wavefront, and from LDS most of the chain is waiting for it
+// (a round of 1,000 jobs, 79 placed and 29 not, 128 nodes: 165 us, and 111 us with the nodes in registers).
+template <int REGS>
 __global__ __launch_bounds__(PLACE_THREADS) void k_place(PlaceArgs A) {
     extern __shared__ uint32_t lds[];
     uint32_t *nodeA = lds;                               // stage 1: CPUs needed per node; stage 2: free GPUs
@@ -187,6 +195,18 @@ __global__ __launch_bounds__(PLACE_THREADS) void k_place(PlaceArgs A) {
     for (uint32_t n = tid; n < A.n_nodes; n += PLACE_THREADS) { nodeA[n] = 0u; nodeM[n] = 0.f; }
     if (tid == 0) redo = 0u;
     __syncthreads();
+
+    // Which records are no allocation here (status 3): a thread per job, once for both stages, because a record's lookup
+    // is a chain of loads (as part of the eight jobs of a stage-1 thread and again job by job these chains took a third
+    // of the kernel's time at 1,000 jobs).
+    if (A.retry.on) {
+        for (uint32_t j = tid; j < A.n_jobs; j += PLACE_THREADS) {
+            const uint32_t g = A.assign[j].g, c = A.assign[j].c;
+            const float mem = A.assign[j].mem_gb;
+            A.status[j] = g > 0 && !on_the_grid(A.retry, j, g, c, mem) ? 3u : 0u;
+        }
+        __syncthreads();
+    }
 
     // ---- stage 1: the jobs end to end on the GPU slots; a thread takes eight neighbouring jobs.  Not with an earlier
     // placement to respect: the kept jobs sit where they sat, so the others go job by job into what is left.
@@ -223,7 +243,7 @@ __global__ __launch_bounds__(PLACE_THREADS) void k_place(PlaceArgs A) {
         if (A.retry.on) {
 #pragma unroll
             for (uint32_t i = 0; i < PLACE_PER; ++i)
-                if (g[i] > 0 && !on_the_grid(A.retry, j0 + i, g[i], c[i], mem[i])) { off_grid |= 1u << i; g[i] = 0; }
+                if (g[i] > 0 && A.status[j0 + i] == 3u) { off_grid |= 1u << i; g[i] = 0; }
             n_off += (uint32_t)__popc(off_grid);
         }
 #pragma unroll
@@ -334,7 +354,7 @@ __global__ __launch_bounds__(PLACE_THREADS) void k_place(PlaceArgs A) {
             const uint32_t g = A.assign[j].g, c = A.assign[j].c;
             const float mem = A.assign[j].mem_gb;
             const uint32_t a = A.keep.prev_off[j], b = A.keep.prev_off[j + 1];
-            bool same = g > 0 && b > a && (!A.retry.on || on_the_grid(A.retry, j, g, c, mem));
+            bool same = g > 0 && b > a && (!A.retry.on || A.status[j] != 3u);
             uint32_t done = 0;
             for (uint32_t i = a; i < b && same; ++i) {
                 const rk_place_entry e = A.keep.prev_entries[i];
@@ -385,13 +405,46 @@ __global__ __launch_bounds__(PLACE_THREADS) void k_place(PlaceArgs A) {
             free_gpus = slots;
         }
     }
+    // What the cluster can still give, as bounds: a walk over the nodes that does not find the amount has seen all free
+    // memory and CPUs, and from then on they only shrink.  Two pairs: of all nodes with a free GPU, and of those with a
+    // free CPU as well, which is what a job that needs CPUs walks.
+    float mem_any = __uint_as_float(0x7F800000u), mem_cpu = mem_any;
+    unsigned long long cpu_cap = ~0ull;
+    // the parts of jm GiB and jc CPUs add up to no less than these (a part is rounded once per operation, a bound is a
+    // float32 sum: together far below the 0.1 %; parts of an amount near the smallest float32 values lose more than that
+    // and are always looked for), so beyond a bound the nodes need not be asked
+    auto mem_out = [&](uint32_t c, float m) { return m > 1e-20f && m * 0.999f > (c > 0 ? mem_cpu : mem_any); };
+    auto cpu_out = [&](uint32_t c) { return c > cpu_cap; };
+    uint32_t g_next = 0, c_next = 0, s_next = 0;
+    float mem_next = 0.f;
+    auto fetch = [&](uint32_t base) {                     // the records of the 64 jobs from `base` on, a lane each
+        const uint32_t j = base + lane;
+        g_next = 0; c_next = 0; s_next = 0; mem_next = 0.f;
+        if (j < A.n_jobs) {
+            g_next = A.assign[j].g; c_next = A.assign[j].c; mem_next = A.assign[j].mem_gb;
+            if (A.retry.on) s_next = A.status[j];
+        }
+    };
+    constexpr int NR = REGS > 0 ? REGS : 1;
+    uint32_t node_g[NR], node_c[NR], node_take[NR], node_before[NR];
+    float node_m[NR];
+    if constexpr (REGS > 0) {
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            const uint32_t n = 64u * (uint32_t)r + lane;
+            node_g[r] = 0u; node_c[r] = 0u; node_m[r] = 0.f;   // (a node past the last one has no GPU to give)
+            if (n < A.n_nodes) { node_g[r] = nodeA[n]; node_c[r] = nodeB[n]; node_m[r] = nodeM[n]; }
+        }
+    }
+    fetch(0);
     for (uint32_t base = 0; base < A.n_jobs; base += 64) {
         const uint32_t j = base + lane;
-        uint32_t g = 0, c = 0;
-        float mem = 0.f;
-        if (j < A.n_jobs) { g = A.assign[j].g; c = A.assign[j].c; mem = A.assign[j].mem_gb; }
+        uint32_t g = g_next;
+        const uint32_t c = c_next;
+        const float mem = mem_next;
         uint32_t my_off = 0, my_status = 0;
-        if (A.retry.on && g > 0 && !on_the_grid(A.retry, j, g, c, mem)) { g = 0; my_status = 3u; }   // no allocation here
+        if (g > 0 && s_next == 3u) { g = 0; my_status = 3u; }   // no allocation here
+        if (base + 64 < A.n_jobs) fetch(base + 64);           // on its way while these jobs are placed
         n_failed += (uint32_t)__popcll(__ballot(my_status == 3u));
         bool have_off = false;
         unsigned long long todo = __ballot(g > 0);
@@ -412,6 +465,8 @@ __global__ __launch_bounds__(PLACE_THREADS) void k_place(PlaceArgs A) {
                 continue;
             }
             GridPos pos = {-2, -1, -1};                    // -2: not looked up yet
+            uint32_t seg = 0;                              // lane s: the job's s-th GPU count, if it has at most 64
+            unsigned long long may = 0;                    // ... bit s: it has a feasible plan there and is not below the floor
             uint32_t tries = 0, first, left, end;
             for (;;) {                                     // the amount asked for, then smaller ones if allowed
             // the offers of the nodes, cut at what the job still lacks (none are asked when the cluster has too few);
@@ -419,52 +474,116 @@ __global__ __launch_bounds__(PLACE_THREADS) void k_place(PlaceArgs A) {
             first = jc > 0 ? first_gc : first_g;
             left = jg;
             end = first;
-            for (uint32_t nb = first; nb < A.n_nodes && left > 0 && jg <= free_gpus; nb += 64) {
-                const uint32_t n = nb + lane;
-                uint32_t k = 0;
-                if (n < A.n_nodes) {
-                    // the most GPUs whose CPUs and memory are free here; both needs grow with k, so a bisection finds it
-                    const uint32_t fc = nodeB[n];
-                    const float fm = nodeM[n];
-                    auto fits = [&](uint32_t x) { return cpus_needed(jc, x, jg) <= fc && mem_of_part(jm, x, jg) <= fm; };
-                    uint32_t lo = 0, hi = nodeA[n] < jg ? nodeA[n] : jg;
-                    if (hi > 0 && !fits(hi)) {
-                        while (hi - lo > 1) {
-                            const uint32_t mid = lo + (hi - lo) / 2;
-                            if (fits(mid)) lo = mid; else hi = mid;
+            if (jg <= free_gpus && !mem_out(jc, jm) && !cpu_out(jc)) {
+                float mem_seen = 0.f;
+                uint32_t cpu_seen = 0;                     // (at most 65,535 per node)
+                // GPUs a free CPU and a free GiB carry, 4e-6 more than that: far above the error of the reciprocals and
+                // of a part's roundings; infinite (no bound) where a reciprocal could leave float32's range
+                const float none = __uint_as_float(0x7F800000u), up = 1.f + 4e-6f;
+                const float per_c = jc > 0 ? (float)jg * __builtin_amdgcn_rcpf((float)jc) * up : none;
+                const float per_m = jm > 1e-20f && jm < 1e30f ? (float)jg * __builtin_amdgcn_rcpf(jm) * up : none;
+                // the most GPUs of `hi` whose CPUs and memory are among the free ones: ceil(c*x/g) <= free as a product,
+                // and both needs grow with x
+                auto offer = [&](uint32_t hi, uint32_t fc, float fm) -> uint32_t {
+                    const unsigned long long lim = (unsigned long long)fc * jg;
+                    auto fits = [&](uint32_t x) { return (unsigned long long)jc * x <= lim && mem_of_part(jm, x, jg) <= fm; };
+                    const float most_c = (float)fc * per_c, most_m = fm * per_m;   // no less than the answer
+                    if (most_c < (float)hi) hi = (uint32_t)most_c;
+                    if (most_m < (float)hi) hi = (uint32_t)most_m;
+                    if (hi > 0 && !fits(hi)) {             // mostly the answer, otherwise mostly the one below
+                        uint32_t lo = 0;
+                        if (--hi > 0 && !fits(hi)) {
+                            while (hi - lo > 1) {
+                                const uint32_t mid = lo + (hi - lo) / 2;
+                                if (fits(mid)) lo = mid; else hi = mid;
+                            }
+                            hi = lo;
                         }
-                        hi = lo;
                     }
-                    k = hi;
+                    return hi;
+                };
+                // ... cut at what the job still lacks; done = its GPUs on earlier nodes
+                auto cut = [&](uint32_t k, uint32_t &done) -> uint32_t {
+                    const uint32_t incl = wave_incl_scan_u32(k, lane), excl = incl - k;
+                    const uint32_t room = left > excl ? left - excl : 0u;
+                    done = (jg - left) + excl;
+                    const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+                    left -= all < left ? all : left;
+                    return k < room ? k : room;
+                };
+                if constexpr (REGS > 0) {
+#pragma unroll
+                    for (int r = 0; r < NR; ++r) {
+                        node_take[r] = 0u;
+                        const bool open = node_g[r] > 0 && (jc == 0 || node_c[r] > 0);
+                        if (left == 0 || !__ballot(open)) continue;
+                        uint32_t k = 0;
+                        if (open) {
+                            mem_seen += node_m[r]; cpu_seen += node_c[r];
+                            k = offer(node_g[r] < jg ? node_g[r] : jg, node_c[r], node_m[r]);
+                        }
+                        if (__ballot(k > 0)) node_take[r] = cut(k, node_before[r]);
+                    }
+                } else {
+                    for (uint32_t nb = first; nb < A.n_nodes && left > 0; nb += 64) {
+                        const uint32_t n = nb + lane;
+                        uint32_t k = 0, done = 0;
+                        if (n < A.n_nodes) {
+                            const uint32_t fc = nodeB[n], hi = nodeA[n] < jg ? nodeA[n] : jg;
+                            const float fm = nodeM[n];
+                            if (hi > 0) { mem_seen += fm; cpu_seen += fc; k = offer(hi, fc, fm); }
+                        }
+                        if (__ballot(k > 0)) k = cut(k, done);
+                        if (n < A.n_nodes) { take[n] = k; before[n] = done; }
+                        end = nb + 64;
+                    }
                 }
-                const uint32_t incl = wave_incl_scan_u32(k, lane), excl = incl - k;
-                const uint32_t room = left > excl ? left - excl : 0u;
-                k = k < room ? k : room;
-                if (n < A.n_nodes) { take[n] = k; before[n] = (jg - left) + excl; }
-                const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-                left -= all < left ? all : left;
-                end = nb + 64;
+                if (left > 0) {                            // every node from `first` on has been asked: what they have left
+                    unsigned long long cpus = cpu_seen;
+#pragma unroll
+                    for (int off = 32; off >= 1; off >>= 1) {
+                        mem_seen += __shfl_xor(mem_seen, off, 64);
+                        cpus += __shfl_xor(cpus, off, 64);
+                    }
+                    mem_cpu = mem_seen < mem_cpu ? mem_seen : mem_cpu;
+                    if (jc == 0) mem_any = mem_seen < mem_any ? mem_seen : mem_any;   // (it asked the nodes without a free CPU too)
+                    cpu_cap = cpus < cpu_cap ? cpus : cpu_cap;
+                }
             }
             if (left == 0 || !A.retry.on) break;
             {                                             // not found: the next smaller count the job may run on
                 const Retry &R = A.retry;
+                // memory or CPUs that do not depend on the GPU count stay out of reach
+                if ((R.grid.mem_mode == 0u && mem_out(jc, jm)) || (R.grid.cpu_mode == 0u && cpu_out(jc))) break;
                 const uint32_t jj = base + (uint32_t)turn;
                 const uint32_t s_off = R.seg_off[jj], ns = R.seg_off[jj + 1] - s_off;
-                if (pos.s == -2) pos = locate(R.grid, R.seg_g, s_off, ns, jg, jc, jm, lane);
+                const int32_t floor_s = R.min_seg && R.min_seg[jj] > 0 ? R.min_seg[jj] : 0;
+                const bool looked = pos.s != -2;
+                if (!looked) pos = locate(R.grid, R.seg_g, s_off, ns, jg, jc, jm, lane);
                 int32_t next = -1;
                 if (pos.s >= 0 && pos.ci >= 0 && pos.mi >= 0) {
-                    const int32_t floor_s = R.min_seg && R.min_seg[jj] > 0 ? R.min_seg[jj] : 0;
                     const uint64_t row = (uint64_t)R.grid.n_cpu * R.grid.n_mem * s_off +
                                          ((uint64_t)pos.ci * R.grid.n_mem + pos.mi) * ns;
-                    for (int32_t hi = pos.s - 1; hi >= floor_s && next < 0; hi -= 64) {
-                        const int32_t s = hi - (int32_t)lane;                 // lane 0 looks at the nearest count
-                        const unsigned long long ok = __ballot(s >= floor_s && R.best_thr[row + (uint32_t)(s < 0 ? 0 : s)] > 0.f);
-                        if (ok) next = hi - ((int32_t)__ffsll((long long)ok) - 1);
+                    if (ns <= 64u) {                       // all counts at once, kept for further tries
+                        if (!looked) {
+                            const bool in = lane < ns;
+                            seg = in ? R.seg_g[s_off + lane] : 0u;
+                            may = __ballot(in && (int32_t)lane >= floor_s && R.best_thr[row + (in ? lane : 0u)] > 0.f);
+                        }
+                        const unsigned long long below = may & ((1ull << pos.s) - 1ull);
+                        if (below) next = 63 - __clzll((long long)below);
+                    } else {
+                        for (int32_t hi = pos.s - 1; hi >= floor_s && next < 0; hi -= 64) {
+                            const int32_t s = hi - (int32_t)lane;                 // lane 0 looks at the nearest count
+                            const unsigned long long ok = __ballot(s >= floor_s && R.best_thr[row + (uint32_t)(s < 0 ? 0 : s)] > 0.f);
+                            if (ok) next = hi - ((int32_t)__ffsll((long long)ok) - 1);
+                        }
                     }
                 }
                 if (next < 0) break;
                 pos.s = next;
-                jg = R.seg_g[s_off + (uint32_t)next];
+                jg = ns <= 64u ? (uint32_t)__builtin_amdgcn_readlane((int)seg, __builtin_amdgcn_readfirstlane(next))
+                               : R.seg_g[s_off + (uint32_t)next];
                 jc = cpus_of(R.grid, (uint32_t)pos.ci, jg);
                 jm = tier_gib(R.grid, (uint32_t)pos.mi, jg);
                 ++tries;
@@ -478,39 +597,63 @@ __global__ __launch_bounds__(PLACE_THREADS) void k_place(PlaceArgs A) {
             if ((int)lane == turn) my_status = tries ? 2u : 1u;
             ++n_placed;
             free_gpus -= jg;
-            for (uint32_t nb = first; nb < end; nb += 64) {
-                const uint32_t n = nb + lane;
-                const uint32_t k = n < A.n_nodes ? take[n] : 0u;
-                const unsigned long long with = __ballot(k > 0);
-                if (k > 0) {
-                    rk_place_entry e;
-                    e.node = n;
-                    e.g = k;
-                    e.c = cpus_booked(jc, before[n], k, jg);
-                    e.mem_gb = mem_of_part(jm, k, jg);
-                    nodeA[n] -= k;
-                    nodeB[n] -= e.c;
-                    nodeM[n] = nodeM[n] - e.mem_gb;
-                    A.entries[cursor + (uint32_t)__popcll(with & ((1ull << lane) - 1ull))] = e;
+            const uint32_t each = jc / jg;                // CPUs per GPU where they come out even: the levels per GPU
+            const bool even = each * jg == jc;
+            // k GPUs of the job go to node n, behind `done` on earlier nodes: its part, one of those of the lanes in `with`
+            auto part = [&](uint32_t n, uint32_t k, uint32_t done, unsigned long long with) {
+                rk_place_entry e;
+                e.node = n;
+                e.g = k;
+                e.c = even ? each * k : cpus_booked(jc, done, k, jg);
+                e.mem_gb = mem_of_part(jm, k, jg);
+                A.entries[cursor + (uint32_t)__popcll(with & ((1ull << lane) - 1ull))] = e;
+                return e;
+            };
+            if constexpr (REGS > 0) {
+#pragma unroll
+                for (int r = 0; r < NR; ++r) {
+                    const uint32_t k = node_take[r];
+                    const unsigned long long with = __ballot(k > 0);
+                    if (!with) continue;
+                    if (k > 0) {
+                        const rk_place_entry e = part(64u * (uint32_t)r + lane, k, node_before[r], with);
+                        node_g[r] -= k;
+                        node_c[r] -= e.c;
+                        node_m[r] = node_m[r] - e.mem_gb;
+                    }
+                    cursor += (uint32_t)__popcll(with);
                 }
-                cursor += (uint32_t)__popcll(with);
+            } else {
+                for (uint32_t nb = first; nb < end; nb += 64) {
+                    const uint32_t n = nb + lane;
+                    const uint32_t k = n < A.n_nodes ? take[n] : 0u;
+                    const unsigned long long with = __ballot(k > 0);
+                    if (!with) continue;
+                    if (k > 0) {
+                        const rk_place_entry e = part(n, k, before[n], with);
+                        nodeA[n] -= k;
+                        nodeB[n] -= e.c;
+                        nodeM[n] = nodeM[n] - e.mem_gb;
+                    }
+                    cursor += (uint32_t)__popcll(with);
+                }
+                // the first nodes that are still of use
+                while (first_g < A.n_nodes) {
+                    const uint32_t n = first_g + lane;
+                    const unsigned long long open = __ballot(n < A.n_nodes && nodeA[n] > 0);
+                    if (open) { first_g += (uint32_t)__ffsll((long long)open) - 1u; break; }
+                    first_g += 64;
+                }
+                if (first_g > A.n_nodes) first_g = A.n_nodes;
+                if (first_gc < first_g) first_gc = first_g;
+                while (first_gc < A.n_nodes) {
+                    const uint32_t n = first_gc + lane;
+                    const unsigned long long open = __ballot(n < A.n_nodes && nodeA[n] > 0 && nodeB[n] > 0);
+                    if (open) { first_gc += (uint32_t)__ffsll((long long)open) - 1u; break; }
+                    first_gc += 64;
+                }
+                if (first_gc > A.n_nodes) first_gc = A.n_nodes;
             }
-            // the first nodes that are still of use
-            while (first_g < A.n_nodes) {
-                const uint32_t n = first_g + lane;
-                const unsigned long long open = __ballot(n < A.n_nodes && nodeA[n] > 0);
-                if (open) { first_g += (uint32_t)__ffsll((long long)open) - 1u; break; }
-                first_g += 64;
-            }
-            if (first_g > A.n_nodes) first_g = A.n_nodes;
-            if (first_gc < first_g) first_gc = first_g;
-            while (first_gc < A.n_nodes) {
-                const uint32_t n = first_gc + lane;
-                const unsigned long long open = __ballot(n < A.n_nodes && nodeA[n] > 0 && nodeB[n] > 0);
-                if (open) { first_gc += (uint32_t)__ffsll((long long)open) - 1u; break; }
-                first_gc += 64;
-            }
-            if (first_gc > A.n_nodes) first_gc = A.n_nodes;
         }
         if (!have_off) my_off = cursor;
         if (j < A.n_jobs) { A.place_off[j] = my_off; A.status[j] = my_status; }
@@ -675,11 +818,14 @@ int32_t launch_place(rk_ctx *ctx, const rk_nodes *nodes, uint32_t n_jobs, const 
     if ((rc = rk_scratch(ctx, SL_PLACE_RESULT, 4 * sizeof(uint32_t), (void **)&A.result))) return rc;
     const size_t lds = (size_t)A.n_nodes * 5 * sizeof(uint32_t);
     if (lds > 48 * 1024 && !ctx->place_lds_raised) {
-        RK_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(k_place),
+        RK_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(k_place<0>),
                                         hipFuncAttributeMaxDynamicSharedMemorySize, RK_MAX_NODES * 5 * sizeof(uint32_t)));
         ctx->place_lds_raised = true;
     }
-    k_place<<<1, PLACE_THREADS, lds, ctx->stream>>>(A);
+    // the fewest groups of 64 nodes that hold them: a group costs every job a few instructions (LDS above 512 nodes)
+    if (A.n_nodes <= 128) k_place<2><<<1, PLACE_THREADS, lds, ctx->stream>>>(A);
+    else if (A.n_nodes <= 512) k_place<8><<<1, PLACE_THREADS, lds, ctx->stream>>>(A);
+    else k_place<0><<<1, PLACE_THREADS, lds, ctx->stream>>>(A);
     RK_CHECK_LAUNCH(ctx, "k_place");
     (void)result;
     return RK_OK;

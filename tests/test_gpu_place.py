@@ -178,3 +178,32 @@ def test_edge_cases(orc, placer):
     with pytest.raises(rk.RkError) as e:
         placer.place(jobs(orc, [1], [1], [0.0]), 5000, 8, 96, 1600.0)
     assert e.value.code == rk.RK_ERR_UNSUPPORTED
+
+
+@pytest.mark.parametrize("n_nodes", [1, 64, 65, 128, 129, 511, 512, 513])
+@pytest.mark.parametrize("gpn", [1, 8, 1000])
+def test_job_by_job_at_the_node_counts_where_the_walk_changes(orc, placer, n_nodes, gpn):
+    """Nodes in registers (two or eight groups of 64) or in LDS; rounds that run out of GPUs, CPUs or memory half way, jobs
+    that find nothing followed by jobs that need less, amounts that divide unevenly, no CPUs, no memory, and memory at
+    both ends of float32 (what is decided without asking the nodes has to be what asking them gives)."""
+    rng = np.random.default_rng(1000 * n_nodes + gpn)
+    G = n_nodes * gpn
+    for trial in range(12):
+        J = int(rng.integers(1, 200))
+        g = np.minimum(rng.integers(1, max(2, min(4 * gpn, G) + 1), size=J), G).astype(np.uint32)
+        g[rng.random(J) < 0.3] = 0
+        per = rng.choice([0, 1, 2, 3, 5], size=J)
+        c = (g * per + (rng.random(J) < 0.3) * rng.integers(0, 4, size=J)).astype(np.uint32)
+        kind = trial % 4
+        if kind == 0:
+            mem = g * rng.choice([0.0, 10.0, 33.3], size=J)
+        elif kind == 1:
+            mem = rng.choice([0.0, 50.0, 200.0, 1000.0], size=J)             # the same at every count
+        elif kind == 2:
+            mem = rng.choice([1e-45, 1e-38, 1e-30, 1e-19, 7.0], size=J)
+        else:
+            mem = rng.choice([1e31, 3e38, 100.0, 2.5], size=J)
+        mem = np.where(g > 0, mem, 0).astype(np.float32)
+        cpn = int(rng.choice([0, gpn, 2 * gpn, min(65535, 5 * gpn)]))
+        mpn = float(rng.choice([0.0, 20.0, 33.3 * gpn, 1000.0, 3e38]))
+        same(orc, placer, jobs(orc, g, c, mem), n_nodes, gpn, cpn, mpn)
