@@ -5,44 +5,73 @@
 // It exploits the structure of the model: plans without offload do not depend
 // on the CPUs or the memory tier, so their per-segment maximum is taken once;
 // offload plans depend on the CPUs only through the swap term and on the tier
-// only through feasibility.  All values come from the functions of rk_model.h,
-// so the results are bit-identical to the materialising path.
+// only through feasibility (a plan that fits a tier fits every larger one, so
+// its key goes to the first tier and the tiers take a running maximum).  All
+// values come from the functions of rk_model.h, so the results are
+// bit-identical to the materialising path.
+//
+// Bound by the vector ALUs' issue slots.  Phase 1 has a lane per triple and
+// packs the triples with a usable offload plan, so that the lanes of phase 2
+// (a lane per packed triple and up to six CPU levels) are all busy; quotients
+// by the same divisor share its reciprocal.  The 128,000 jobs of 256 rounds:
+// 735 vector instructions per wavefront in its first form, 587 now, 808 ->
+// 672 us (vector ALUs active 85 % of the time); 10,000 jobs on the full grid
+// of 20 rows: 117 -> 85 us.
 #include "rk_internal.h"
 #include "rk_model.h"
 
 namespace {
 
 constexpr int FUSED_THREADS = 256;
+constexpr uint32_t FUSED_FILL = 512;      // workgroups that occupy the chip: two per CU
 
 struct FusedLds {          // element counts of the dynamic LDS regions
     uint32_t max_nt, max_ns, rows_per_pass;
 };
 
 __host__ __device__ inline size_t fused_lds_bytes(const FusedLds &L) {
-    return (size_t)L.max_ns * 8 + (size_t)L.rows_per_pass * L.max_ns * 8 + (size_t)L.max_nt * 4 * 8 + (size_t)L.max_ns * 4;
+    return 8 + (size_t)L.max_ns * 8 + (size_t)L.rows_per_pass * L.max_ns * 8 + (size_t)L.max_nt * 4 * 5 + (size_t)L.max_ns * 4;
 }
 
+// info word of a packed triple: usable offload options, first memory tier that holds them, segment, number of the triple
+constexpr uint32_t INFO_TRIPLES = 4096;    // more than rk_enumerate_plans ever finds for a job
+static_assert(RK_MAX_MEM_LEVELS <= 16 && RK_MAX_TRIPLES_PER_JOB <= INFO_TRIPLES, "fields of the info word");
+__device__ __forceinline__ uint32_t info_word(uint32_t ok, uint32_t tier, uint32_t seg, uint32_t tl) {
+    return ok | (tier << 4) | (seg << 8) | (tl << 20);
+}
+
+// one step of an inclusive maximum scan along the wavefront: v = max(v, the value CTRL brings) where `take`
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned long long scan_max_step(unsigned long long v, bool take) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, ROWS, 0xF, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), CTRL, ROWS, 0xF, false);
+    const unsigned long long o = ((unsigned long long)hi << 32) | lo;
+    return take && o > v ? o : v;
+}
+
+// blockIdx.y: which c_per_block CPU levels
 __global__ __launch_bounds__(FUSED_THREADS) void k_fused(JobDev jobs, TableDev tb, GridDev grid, rk_env env,
                                                          uint32_t jb, uint32_t option_mask, FusedLds L,
-                                                         uint32_t c_per_pass, uint32_t m_per_pass,
+                                                         uint32_t c_per_block, uint32_t c_per_pass, uint32_t m_per_pass,
                                                          float *__restrict__ best_thr, uint32_t *__restrict__ best_plan,
                                                          float *__restrict__ curve_thr, uint32_t *__restrict__ curve_plan,
                                                          uint32_t *__restrict__ curve_g) {
     extern __shared__ unsigned long long lds64[];
-    unsigned long long *seg_plain = lds64;                                   // [max_ns]
+    uint32_t &n_packed = *reinterpret_cast<uint32_t *>(lds64);               // triples packed so far
+    unsigned long long *seg_plain = lds64 + 1;                               // [max_ns]
     unsigned long long *seg_best = seg_plain + L.max_ns;                     // [rows_per_pass][max_ns]
+    // packed triples with a usable offload plan (before they are packed: t_info[tl] = segment of triple tl)
     float *t_base0 = reinterpret_cast<float *>(seg_best + (size_t)L.rows_per_pass * L.max_ns);
     float *t_base1 = t_base0 + L.max_nt;
     float *t_topt = t_base1 + L.max_nt;
     float *t_toff = t_topt + L.max_nt;
-    float *t_host = t_toff + L.max_nt;
-    float *t_invk = t_host + L.max_nt;
-    uint32_t *t_info = reinterpret_cast<uint32_t *>(t_invk + L.max_nt);      // ok bits | segment << 4
-    uint32_t *t_g = t_info + L.max_nt;
-    uint32_t *l_segg = t_g + L.max_nt;                                       // [max_ns] GPUs of the job's segments
+    uint32_t *t_info = reinterpret_cast<uint32_t *>(t_toff + L.max_nt);
+    uint32_t *l_segg = t_info + L.max_nt;                                    // [max_ns] GPUs of the job's segments
 
-    const uint32_t tid = threadIdx.x;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u;
     const uint32_t j = jb + blockIdx.x;
+    const uint32_t c_begin = blockIdx.y * c_per_block;
+    const uint32_t c_end = c_begin + c_per_block < grid.n_cpu ? c_begin + c_per_block : grid.n_cpu;
     const uint32_t t0 = tb.triple_off[j], nt = tb.triple_off[j + 1] - t0;
     const uint32_t s0 = tb.seg_off[j], ns = tb.seg_off[j + 1] - s0;
     const uint32_t n_mem = grid.n_mem, n_rows = grid.n_cpu * n_mem;
@@ -50,110 +79,148 @@ __global__ __launch_bounds__(FUSED_THREADS) void k_fused(JobDev jobs, TableDev t
     const Job J = load_job(jobs, j);
 
     // per segment: nothing found yet, its GPU count, and its number in the info word of each of its triples
+    if (tid == 0) n_packed = 0u;
     for (uint32_t s = tid; s < ns; s += FUSED_THREADS) {
         seg_plain[s] = 0ull;
         l_segg[s] = tb.seg_g[s0 + s];
         const uint32_t first = tb.seg_first[s0 + s];
         const uint32_t last = s + 1 < ns ? tb.seg_first[s0 + s + 1] : nt;
-        for (uint32_t t = first; t < last; ++t) t_info[t] = s << 4;
+        for (uint32_t t = first; t < last; ++t) t_info[t] = s;
     }
     __syncthreads();
 
-    // phase 1: one thread per triple
-    for (uint32_t tl = tid; tl < nt; tl += FUSED_THREADS) {
-        const Triple T = triple_terms(J, env, tb.triples[t0 + tl]);
-        const uint32_t lo = t_info[tl] >> 4;               // segment of the triple
-        unsigned long long k = 0;
-#pragma unroll
-        for (uint32_t z = 0; z < 4; ++z)
+    // phase 1: one lane per triple; a workgroup's turn packs behind the turn before, so what it overwrites of the
+    // segment numbers has been read
+    for (uint32_t base = 0; base < nt; base += FUSED_THREADS) {
+        const uint32_t tl = base + tid;
+        uint32_t ok = 0, info = 0;
+        Offload O = {};
+        if (tl < nt) {
+            const Triple T = triple_terms(J, env, tb.triples[t0 + tl]);
+            const uint32_t seg = t_info[tl];
+            // without offload: a stage above 0 does not change the throughput, so of those the lowest that fits
+            unsigned long long k = 0;
 #pragma unroll
             for (uint32_t gc = 0; gc < 2; ++gc) {
-                const uint32_t o = z * 4 + gc * 2;
-                if (((option_mask >> o) & 1u) && gpu_mem_fits(J, env, T, z, gc, 0)) {
-                    const unsigned long long c = make_key(thr_plain(J, T, z, gc), tl * 16 + o);
+                bool fits[4];
+#pragma unroll
+                for (uint32_t z = 0; z < 4; ++z) fits[z] = ((option_mask >> (z * 4 + gc * 2)) & 1u) && gpu_mem_fits(J, env, T, z, gc, 0);
+                if (fits[0]) {
+                    const unsigned long long c = make_key(thr_plain(J, T, 0, gc), tl * 16 + gc * 2);
+                    k = c > k ? c : k;
+                }
+                if (fits[1] || fits[2] || fits[3]) {
+                    const uint32_t z = fits[1] ? 1u : fits[2] ? 2u : 3u;
+                    const unsigned long long c = make_key(thr_plain(J, T, 1, gc), tl * 16 + z * 4 + gc * 2);
                     k = c > k ? c : k;
                 }
             }
-        if (k >> 32) atomicMax(&seg_plain[lo], k);
-        uint32_t ok = 0;
+            if (k >> 32) atomicMax(&seg_plain[seg], k);
 #pragma unroll
-        for (uint32_t z = 2; z < 4; ++z)
+            for (uint32_t z = 2; z < 4; ++z)
 #pragma unroll
-            for (uint32_t gc = 0; gc < 2; ++gc) {
-                const uint32_t o = z * 4 + gc * 2 + 1;
-                if (((option_mask >> o) & 1u) && gpu_mem_fits(J, env, T, z, gc, 1)) ok |= 1u << ((z - 2) * 2 + gc);
+                for (uint32_t gc = 0; gc < 2; ++gc) {
+                    const uint32_t o = z * 4 + gc * 2 + 1;
+                    if (((option_mask >> o) & 1u) && gpu_mem_fits(J, env, T, z, gc, 1)) ok |= 1u << ((z - 2) * 2 + gc);
+                }
+            if (ok) {
+                const float need = host_bytes_needed(J, T);
+                uint32_t tier = 0;                                // (tiers ascend)
+                while (tier < n_mem && !(need <= tier_bytes(grid, tier, T.g))) ++tier;
+                if (tier == n_mem) ok = 0;
+                else {
+                    O = offload_terms(J, env, T);
+                    info = info_word(ok, tier, seg, tl);
+                }
             }
-        t_info[tl] = ok | (lo << 4);
-        t_g[tl] = T.g;
+        }
+        // the turn's triples are read before any of them is overwritten by a packed one (all turns of more than one
+        // workgroup's width; the last barrier also closes the phase)
+        const unsigned long long with = __ballot(ok != 0);
+        uint32_t at = 0;
+        if (lane == 0 && with) at = atomicAdd(&n_packed, (uint32_t)__popcll(with));
+        at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + (uint32_t)__popcll(with & ((1ull << lane) - 1ull));
+        __syncthreads();
         if (ok) {
-            const Offload O = offload_terms(J, env, T);
-            t_base0[tl] = O.base[0]; t_base1[tl] = O.base[1];
-            t_topt[tl] = O.topt_num; t_toff[tl] = O.Toff; t_invk[tl] = O.inv_kswap;
-            t_host[tl] = host_bytes_needed(J, T);
-            // T.b is the same for every triple of the job
+            t_base0[at] = O.base[0]; t_base1[at] = O.base[1];
+            t_topt[at] = O.topt_num; t_toff[at] = O.Toff;
+            t_info[at] = info;
+            // T.b and 1/k_swap are the same for every triple of the job
         }
     }
+    __syncthreads();
+    const uint32_t np = n_packed;
 
     // A pass keeps the keys of some rows in LDS: several CPU levels with all their tiers, or, when the rows of one
     // level do not fit, some tiers of one level (m_per_pass < n_mem only together with c_per_pass == 1).  Either
     // way the rows of a pass are neighbours in the output, starting at row c_lo * n_mem + m_lo.
-    const float fb = (float)J.gbatch;
-    for (uint32_t c_lo = 0; c_lo < grid.n_cpu; c_lo += c_per_pass)
+    const float fb = (float)J.gbatch, inv_kswap = __builtin_amdgcn_rcpf(J.k_swap);
+    const float inv_np = __builtin_amdgcn_rcpf((float)np), inv_ns = __builtin_amdgcn_rcpf((float)ns);
+    const uint32_t q = small_quot(lane, inv_ns), s_lane = lane - q * ns;       // phase 3: the lane's row in a group and its segment
+    const uint32_t r_group = ns <= 64u && ns > 0 ? small_quot(64u, inv_ns) : 1u;   // rows that 64 lanes hold whole
+    for (uint32_t c_lo = c_begin; c_lo < c_end; c_lo += c_per_pass)
     for (uint32_t m_lo = 0; m_lo < n_mem; m_lo += m_per_pass) {
-        const uint32_t c_hi = c_lo + c_per_pass < grid.n_cpu ? c_lo + c_per_pass : grid.n_cpu;
+        const uint32_t c_hi = c_lo + c_per_pass < c_end ? c_lo + c_per_pass : c_end;
         const uint32_t m_hi = m_lo + m_per_pass < n_mem ? m_lo + m_per_pass : n_mem;
         const uint32_t m_cnt = m_hi - m_lo;
         const uint32_t pass_rows = (c_hi - c_lo) * m_cnt;
         const uint32_t row0 = c_lo * n_mem + m_lo;
-        for (uint32_t i = tid; i < pass_rows * ns; i += FUSED_THREADS) seg_best[(size_t)(i / ns) * L.max_ns + i % ns] = 0ull;
+        for (uint32_t i = tid; i < pass_rows * L.max_ns; i += FUSED_THREADS) seg_best[i] = 0ull;
         __syncthreads();
 
-        // phase 2: one item per (CPU level, triple with a usable offload plan)
-        const uint32_t items = (c_hi - c_lo) * nt;
-        for (uint32_t i = tid; i < items; i += FUSED_THREADS) {
-            const uint32_t tl = i % nt, ci = c_lo + i / nt;
-            const uint32_t info = t_info[tl], ok = info & 15u;
-            if (!ok) continue;
-            const uint32_t seg = info >> 4, g = t_g[tl];
+        // phase 2: one item per packed triple and up to six neighbouring CPU levels, which share what is read and unpacked
+        const uint32_t levels = c_hi - c_lo, parts = (levels + 5u) / 6u;
+        const uint32_t per_part = parts > 1 ? small_quot(levels + parts - 1u, __builtin_amdgcn_rcpf((float)parts)) : levels;
+        for (uint32_t i = tid; i < np * parts; i += FUSED_THREADS) {
+            const uint32_t part = parts > 1 ? small_quot(i, inv_np) : 0u, at = i - part * np;
+            const uint32_t info = t_info[at], ok = info & 15u, tier = (info >> 4) & 15u, seg = (info >> 8) & (INFO_TRIPLES - 1u);
+            const uint32_t plan = (info >> 20) * 16u;
+            if (tier >= m_hi) continue;
             Offload O;
-            O.base[0] = t_base0[tl]; O.base[1] = t_base1[tl];
-            O.topt_num = t_topt[tl]; O.Toff = t_toff[tl]; O.inv_kswap = t_invk[tl];
+            O.base[0] = t_base0[at]; O.base[1] = t_base1[at];
+            O.topt_num = t_topt[at]; O.Toff = t_toff[at]; O.inv_kswap = inv_kswap;
             Triple Tb; Tb.b = fb;
-            const float sw = swap_term(J, O, cpus_of(grid, ci, g));
-            const float v0 = thr_offload(Tb, O, 0, sw), v1 = thr_offload(Tb, O, 1, sw);
-            unsigned long long k = 0;
-#pragma unroll
-            for (uint32_t q = 0; q < 4; ++q) {          // plan-index order: (z2,gc0) (z2,gc1) (z3,gc0) (z3,gc1)
-                if ((ok >> q) & 1u) {
-                    const uint32_t o = (2 + (q >> 1)) * 4 + (q & 1u) * 2 + 1;
-                    const unsigned long long c = make_key((q & 1u) ? v1 : v0, tl * 16 + o);
-                    k = c > k ? c : k;
-                }
+            const uint32_t g = l_segg[seg];
+            // options in plan order: (z2,gc0) (z2,gc1) (z3,gc0) (z3,gc1); the stage does not change the value
+            const uint32_t plan0 = plan + (ok & 1u ? 9u : 13u), plan1 = plan + (ok & 2u ? 11u : 15u);
+            uint32_t ci = c_lo + part * per_part;
+            const uint32_t c_stop = ci + per_part < c_hi ? ci + per_part : c_hi;
+            unsigned long long *slot = seg_best + (size_t)((ci - c_lo) * m_cnt + (tier > m_lo ? tier - m_lo : 0u)) * L.max_ns + seg;
+            for (; ci < c_stop; ++ci, slot += (size_t)m_cnt * L.max_ns) {
+                const float sw = swap_term(J, O, cpus_of(grid, ci, g));
+                const unsigned long long k0 = ok & 5u ? make_key(thr_offload(Tb, O, 0, sw), plan0) : 0ull;
+                const unsigned long long k1 = ok & 10u ? make_key(thr_offload(Tb, O, 1, sw), plan1) : 0ull;
+                atomicMax(slot, k0 > k1 ? k0 : k1);
             }
-            const float need = t_host[tl];
-            for (uint32_t mi = m_lo; mi < m_hi; ++mi)
-                if (need <= tier_bytes(grid, mi, g))
-                    atomicMax(&seg_best[(size_t)((ci - c_lo) * m_cnt + (mi - m_lo)) * L.max_ns + seg], k);
         }
         __syncthreads();
+        if (m_cnt > 1) {                                          // what fits a tier fits the larger ones
+            const uint32_t cols = (c_hi - c_lo) * ns;
+            for (uint32_t i = tid; i < cols; i += FUSED_THREADS) {
+                const uint32_t c = small_quot(i, inv_ns);
+                unsigned long long *col = seg_best + (size_t)c * m_cnt * L.max_ns + (i - c * ns), run = col[0];
+                for (uint32_t m = 1; m < m_cnt; ++m) {
+                    const unsigned long long k = col[(size_t)m * L.max_ns];
+                    if (k >= run) run = k;
+                    else col[(size_t)m * L.max_ns] = run;
+                }
+            }
+            __syncthreads();
+        }
 
-        // phase 3: merge with the plans without offload, write, then the running maximum along each row.  The
-        // wavefronts split the pass's rows; a wavefront walks its rows 64 entries at a time: the running maximum is
+        // phase 3: merge with the plans without offload, write, then the running maximum along each row.  A wavefront
+        // takes as many whole rows as 64 lanes hold, or one row 64 entries at a time: the running maximum is
         // a segmented scan over packed keys (throughput bits, inverted segment index, GPUs of the segment: the lower
-        // segment wins among equal throughputs), a row that continues from the previous 64 entries takes their last
-        // key along, and the plan comes from the winning segment's merged key.
-        {
-            constexpr uint32_t WAVES = FUSED_THREADS / 64;
-            const uint32_t lane = tid & 63u, wave = tid >> 6;
-            const uint32_t per = (pass_rows + WAVES - 1) / WAVES;
-            const uint32_t r_lo = wave * per < pass_rows ? wave * per : pass_rows;
-            const uint32_t r_hi = r_lo + per < pass_rows ? r_lo + per : pass_rows;
-            const uint32_t n = (r_hi - r_lo) * ns;
+        // segment wins among equal throughputs), a row of more than 64 entries takes the last key of the 64 before
+        // along, and the plan comes from the winning segment's merged key.
+        constexpr uint32_t WAVES = FUSED_THREADS / 64;
+        const uint32_t l16 = lane & 15u;
+        for (uint32_t r0 = (tid >> 6) * r_group; r0 < pass_rows; r0 += WAVES * r_group) {
+            const uint32_t rl = ns <= 64u ? r0 + q : r0;
             unsigned long long carry = 0;
-            for (uint32_t base = 0; base < n; base += 64) {
-                const uint32_t i = base + lane;
-                const bool in = i < n;
-                const uint32_t rl = r_lo + i / ns, s = i % ns;
+            for (uint32_t base = 0; base < ns; base += 64) {
+                const uint32_t s = ns <= 64u ? s_lane : base + lane;
+                const bool in = ns <= 64u ? q < r_group && rl < pass_rows : s < ns;
                 const uint64_t out = sbase + (uint64_t)(row0 + rl) * ns + s;
                 unsigned long long ck = 0;
                 if (in) {
@@ -167,14 +234,18 @@ __global__ __launch_bounds__(FUSED_THREADS) void k_fused(JobDev jobs, TableDev t
                     }
                     if (k >> 32) ck = (k & 0xFFFFFFFF00000000ull) | ((0xFFFFu - s) << 16) | l_segg[s];
                 }
-#pragma unroll
-                for (uint32_t d = 1; d < 64; d <<= 1) {
-                    const unsigned long long o = __shfl_up(ck, d, 64);
-                    if (lane >= d && s >= d) ck = o > ck ? o : ck;      // the lane d below is in the same row
+                // from the lanes below that are in the same row: within 16 lanes, then the 16 and the 32 before
+                ck = scan_max_step<0x111, 0xF>(ck, s >= 1u);               // row_shr:1
+                ck = scan_max_step<0x112, 0xF>(ck, s >= 2u);               // row_shr:2
+                ck = scan_max_step<0x114, 0xF>(ck, s >= 4u);               // row_shr:4
+                ck = scan_max_step<0x118, 0xF>(ck, s >= 8u);               // row_shr:8
+                ck = scan_max_step<0x142, 0xA>(ck, s > l16);               // row_bcast:15 into lanes 16..31 and 48..63
+                ck = scan_max_step<0x143, 0xC>(ck, s > lane - 32u);        // row_bcast:31 into lanes 32..63
+                if (ns > 64u) {
+                    ck = carry > ck ? carry : ck;
+                    carry = ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(ck >> 32), 63) << 32) |
+                            (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)ck, 63);
                 }
-                if (s > lane) ck = carry > ck ? carry : ck;             // the row began before these 64 entries
-                carry = ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(ck >> 32), 63) << 32) |
-                        (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)ck, 63);
                 if (in) {
                     uint32_t plan = RK_NO_PLAN;
                     if (ck) plan = key_plan(seg_best[(size_t)rl * L.max_ns + (0xFFFFu - ((uint32_t)(ck >> 16) & 0xFFFFu))]);
@@ -210,15 +281,23 @@ int32_t rk_launch_fused(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_table *t
     }
     L.rows_per_pass = c_per_pass * m_per_pass;
     const size_t lds = fused_lds_bytes(L);
+    if (L.max_nt > INFO_TRIPLES) return rk_fail(ctx, RK_ERR_UNSUPPORTED, "more than %u triples per job", INFO_TRIPLES);
     if (lds > 160 * 1024) return rk_fail(ctx, RK_ERR_UNSUPPORTED, "job too large for the fused kernel");
     if (lds > 64 * 1024 && !ctx->fused_lds_raised) {
         RK_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(k_fused),
                                         hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
         ctx->fused_lds_raised = true;
     }
-    k_fused<<<je - jb, FUSED_THREADS, lds, ctx->stream>>>(job_dev(jobs), table_dev(table), grid_dev(grid), *env, jb,
-                                                         table->option_mask, L, c_per_pass, m_per_pass, best_thr,
-                                                         best_plan, curve_thr, curve_plan, curve_g);
+    // Few jobs leave most of the chip idle: their CPU levels are split over workgroups, down to four levels each (every
+    // one repeats phase 1, which is worth about that many).
+    uint32_t split = (je - jb) < FUSED_FILL ? FUSED_FILL / (je - jb) : 1u;
+    if (split > (grid->n_cpu + 3u) / 4u) split = (grid->n_cpu + 3u) / 4u;
+    const uint32_t c_per_block = (grid->n_cpu + split - 1u) / split;
+    split = (grid->n_cpu + c_per_block - 1u) / c_per_block;
+    if (c_per_pass > c_per_block) c_per_pass = c_per_block;
+    k_fused<<<dim3(je - jb, split), FUSED_THREADS, lds, ctx->stream>>>(job_dev(jobs), table_dev(table), grid_dev(grid), *env, jb,
+                                                                      table->option_mask, L, c_per_block, c_per_pass, m_per_pass,
+                                                                      best_thr, best_plan, curve_thr, curve_plan, curve_g);
     RK_CHECK_LAUNCH(ctx, "k_fused");
     return RK_OK;
 }

@@ -60,6 +60,41 @@ __device__ __forceinline__ Job load_job(const JobDev &J, uint32_t j) {
 
 __device__ __forceinline__ float fast_div(float a, float b) { return a * __builtin_amdgcn_rcpf(b); }
 
+// Correctly rounded quotients by the same divisor for a few operations each, where the general sequence (scaling, five
+// corrections, fix-up) takes eleven: the divisor's correctly rounded reciprocal once, then a quotient and one correction
+// with the exact remainder.  The results are those of the division for the divisors and dividends used here: whole
+// divisors up to 65,535 under small whole dividends, and products d = t*p (t a power of two, p < 4096) under any dividend
+// whose remainders stay in range (checked for every mantissa and every p, from reciprocals one unit off either way).
+struct Divisor { float b, r; };
+__device__ __forceinline__ Divisor divisor(float b) {
+    const float r = __builtin_amdgcn_rcpf(b);
+    return Divisor{b, __builtin_fmaf(__builtin_fmaf(-b, r, 1.f), r, r)};
+}
+__device__ __forceinline__ float exact_div(float a, const Divisor &D) {
+    const float q = a * D.r;
+    return __builtin_fmaf(__builtin_fmaf(-q, D.b, a), D.r, q);
+}
+
+// a / b; below 2^20 from the float32 quotient, which is off by less than one there.  The general sequence takes twice
+// the issue slots.  (Mostly a is the same in all lanes, and so is the choice.)
+__device__ __forceinline__ uint32_t whole_div(uint32_t a, uint32_t b) {
+    if (a >= (1u << 20)) return a / b;
+    uint32_t q = (uint32_t)((float)a * __builtin_amdgcn_rcpf((float)b));
+    const uint32_t r = a - q * b;
+    if ((int32_t)r < 0) --q;
+    else if (r >= b) ++q;
+    return q;
+}
+
+// a / b from about 1/b, for a and b below 2^20: the half keeps the rounding away from the next whole number.
+__device__ __forceinline__ uint32_t small_quot(uint32_t a, float inv_b) { return (uint32_t)(((float)a + 0.5f) * inv_b); }
+
+// Whether b divides a, b > 0; likewise.
+__device__ __forceinline__ bool divides(uint32_t b, uint32_t a) {
+    if (a >= (1u << 20)) return a % b == 0;
+    return small_quot(a, __builtin_amdgcn_rcpf((float)b)) * b == a;
+}
+
 // Overlap of two stages (Sec. 4.3): (x^k + y^k)^(1/k), evaluated as
 // M * 2^(log2(1 + r^k)/k) with M = max, r = min/max in [0,1], which neither
 // overflows nor loses the small term.  inv_k = 1/k.
@@ -75,6 +110,7 @@ __device__ __forceinline__ float f_overlap(float k, float inv_k, float x, float 
 struct Triple {
     uint32_t d, t, p, g;
     float fd;
+    Divisor by_d;        // for the memory estimate's quotients by d
     float Tcc[2];        // computation + communication, by gc (Sec. 4.1)
     float Tdp;           // gradient synchronisation time
     float Psi;           // parameter bytes on one model-parallel shard
@@ -93,7 +129,7 @@ __device__ __forceinline__ Links packed_links(const rk_env &E, uint32_t d, uint3
     Links L = {E.B_intra, E.B_intra, E.B_intra};
     if (g > N) {
         L.tp = (N % t == 0) ? E.B_intra : E.B_inter;
-        L.dp = (N % (t * d) == 0) ? E.B_intra : E.B_inter;
+        L.dp = divides(t * d, N) ? E.B_intra : E.B_inter;
         L.pp = E.B_inter;
     }
     return L;
@@ -118,9 +154,10 @@ __device__ __forceinline__ Triple triple_terms_on(const Job &J, const rk_env &E,
     T.g = T.d * T.t * T.p;
     const float fd = (float)T.d, ft = (float)T.t, fp = (float)T.p, ftp = (float)(T.t * T.p);
     T.fd = fd;
+    T.by_d = divisor(fd);
     T.b = (float)J.gbatch;
     const uint32_t mb = J.mbatch << RK_TRIPLE_V(packed);     // micro-batch size of this plan
-    const uint32_t n = J.gbatch / (T.d * mb);                // micro-batches per replica
+    const uint32_t n = whole_div(J.gbatch, T.d * mb);        // micro-batches per replica
     const float fn = (float)n;
     const float fmu = (float)mb;
 
@@ -153,18 +190,19 @@ __device__ __forceinline__ Triple triple_terms_on(const Job &J, const rk_env &E,
     }
 
     // memory: exact float32 sequence (documented in rubick.h)
-    T.Psi = J.P / ftp;
+    T.Psi = J.P > 1e-20f && J.P < 1e30f ? exact_div(J.P, divisor(ftp)) : J.P / ftp;
     const uint32_t w = T.p < n ? T.p : n;
     float tok = fmu * J.seq;
     tok = tok * J.hidden;
-    const float lay = (float)(J.layers / T.p);
+    const float lay = (float)whole_div(J.layers, T.p);
+    const float inv_t = __uint_as_float((254u << 22) - (((packed >> 16) & 3u) << 23));   // 1/t, t a power of two: the same as dividing
     float base = tok * lay;
-    base = base / ft;
+    base = base * inv_t;
     base = base * (float)w;
     T.A[0] = J.m_act * base;
     float a1 = J.m_act_gc * base;
     float a2 = J.m_act * tok;
-    a2 = a2 / ft;
+    a2 = a2 * inv_t;
     T.A[1] = a1 + a2;
     return T;
 }
@@ -179,15 +217,15 @@ __device__ __forceinline__ bool gpu_mem_fits(const Job &J, const rk_env &E, cons
                                              uint32_t z, uint32_t gc, uint32_t off) {
     float kappa;
     if (off) {
-        kappa = (z == 2) ? 1.0f : 1.0f / T.fd;
+        kappa = (z == 2) ? 1.0f : T.by_d.r;
     } else if (z == 0) {
         kappa = 8.0f;
     } else if (z == 1) {
-        float q = 6.0f / T.fd; kappa = 2.0f + q;
+        float q = exact_div(6.0f, T.by_d); kappa = 2.0f + q;
     } else if (z == 2) {
-        float q = 7.0f / T.fd; kappa = 1.0f + q;
+        float q = exact_div(7.0f, T.by_d); kappa = 1.0f + q;
     } else {
-        kappa = 8.0f / T.fd;
+        kappa = 8.0f * T.by_d.r;
     }
     float sk = J.m_state * kappa;
     float S = sk * T.Psi;
@@ -198,7 +236,7 @@ __device__ __forceinline__ bool gpu_mem_fits(const Job &J, const rk_env &E, cons
 
 // Host bytes an offload plan needs (all GPUs of the job together).
 __device__ __forceinline__ float host_bytes_needed(const Job &J, const Triple &T) {
-    float q = 7.0f / T.fd;
+    float q = exact_div(7.0f, T.by_d);
     float h = J.m_state * q;
     h = h * T.Psi;
     h = h * (float)T.g;

@@ -865,3 +865,30 @@ def test_micro_batch_sizes_as_a_plan_dimension(gpu, orc):
         run.enumerate()
     assert e.value.code == rk.RK_ERR_INVALID_ARG
     run.close()
+
+
+@pytest.mark.parametrize("n_jobs", [1, 5, 129, 511, 513])
+@pytest.mark.parametrize("n_cpu,n_mem,per_gpu", [(1, 1, 1), (4, 2, 1), (5, 4, 0), (6, 1, 0), (7, 3, 1), (13, 16, 0), (64, 1, 0)])
+def test_fused_kernel_at_the_edges_of_its_split(gpu, n_jobs, n_cpu, n_mem, per_gpu):
+    """The fused kernel splits the CPU levels over workgroups where there are few jobs, takes up to six levels per lane and
+    sends a plan's key to its first memory tier: same bits as evaluation, best plans and curves as separate calls.  Nodes of
+    1, 6, 8 and 3,000,000 GPUs take both forms of the quotients; values of the divisor sequences against the oracle's
+    verdicts are part of the other tests (a feasibility byte per candidate)."""
+    import dataclasses
+    base = workloads.stress(n_jobs=n_jobs)
+    levels = np.unique(np.round(np.geomspace(1, 64, n_cpu * 3)).astype(np.uint32))[:n_cpu] if n_cpu < 64 else np.arange(1, 65, dtype=np.uint32)
+    levels = levels if len(levels) == n_cpu else np.arange(1, n_cpu + 1, dtype=np.uint32)
+    mem = np.array([2.0 ** (i - 2) * 8.0 for i in range(n_mem)], np.float32)
+    for gpn in (1, 6, 8, 3000000):
+        wl = dataclasses.replace(base, bounds=workloads.Bounds(g_max=200), grid=workloads.Grid(levels, per_gpu, mem, per_gpu),
+                                 env=dataclasses.replace(base.env, gpus_per_node=gpn))
+        run = gpu(wl)
+        run.enumerate()
+        thr, feas, n = run.eval()
+        bt, bp, ns = run.best(thr)
+        ct, cp, cg = run.curves(bt, bp)
+        f = run.fused()
+        assert f[5] == ns
+        for got, want in zip(f[:5], (bt, bp, ct, cp, cg)):
+            assert np.array_equal(run.host(got, ns), run.host(want, ns))
+        run.close()
