@@ -8,15 +8,24 @@
 // (g, t, p, v) in LDS: a bitmap of the GPU counts that occur gives every key
 // its segment (rank of its g among the distinct counts = a population count),
 // the keys are gathered by segment, and only the few keys of one segment are
-// compared with each other.  The counting pass also parks the
-// sorted keys in a scratch buffer; after the exclusive scan of the counts the
-// fill pass only decodes them into place (it repeats the search only when the
-// scratch buffer was too small).  Jobs whose searches would be identical (same
-// layer count, same number of micro-batches per step) share one: a hash table
-// names a leader for each such group, only leaders search, the others take
-// the leader's counts and decode the leader's parked keys.  The fill pass is launched while the counts
-// are still on their way to the host: it checks on the device that the table
-// is large enough and leaves it alone otherwise.
+// compared with each other.  The counting pass also parks what it found, in
+// the table's own words, in a scratch buffer; after the exclusive scan of the
+// counts the fill pass (k_fill) only copies them into place, a wavefront per
+// job (the search is repeated only when the scratch buffer was too small).
+// Jobs whose searches would be identical (same layer count, same number of
+// micro-batches per step) share one: a hash table names a leader for each such
+// group, only leaders search, the others take the leader's counts and copy the
+// leader's parked words.  The fill pass is launched while the counts are still
+// on their way to the host: it checks on the device that the table is large
+// enough and leaves it alone otherwise.
+//
+// Small calls are bound by their launches, so up to ENUM_SELF_SCAN jobs are
+// scanned by the workgroup that finishes its search last, which also writes
+// the totals straight to pinned host memory (two launches instead of four and
+// a copy); large ones by all workgroups of k_scan_tiles from the sums that
+// k_spread_counts leaves (128,000 jobs: 73 us with one workgroup, 4 us).  The
+// fill was 114 us for them while it decoded keys and counted segments in LDS
+// again, 28 us as a copy; 10,000 jobs: 14 -> 8 us and the scan 13 -> 4 us.
 #include <cstring>
 
 #include "rk_internal.h"
@@ -27,9 +36,38 @@ constexpr int ENUM_THREADS = 256;
 constexpr uint32_t MAX_T = RK_MAX_TRIPLES_PER_JOB;
 constexpr uint32_t MAX_DIV = 1024;
 
-enum { TOT_NT_LO = 0, TOT_NT_HI, TOT_NS_LO, TOT_NS_HI, TOT_MAX_T, TOT_MAX_S, TOT_ERR, TOT_CURSOR, TOT_WORDS };
+enum { TOT_NT_LO = 0, TOT_NT_HI, TOT_NS_LO, TOT_NS_HI, TOT_MAX_T, TOT_MAX_S, TOT_ERR, TOT_DONE, TOT_WORDS };
 enum { ERR_TOO_MANY_TRIPLES = 1, ERR_TOO_MANY_DIVISORS = 2, ERR_PARK_FULL = 4 };
-enum { MODE_COUNT = 0, MODE_FILL_SEARCH = 1, MODE_FILL_PARKED = 2 };
+enum { MODE_COUNT = 0, MODE_FILL_SEARCH = 1 };
+
+// a job's word in cnt_t: its triples and the flags its search raised (so nothing has to be cleared between calls)
+constexpr uint32_t CNT_MASK = 0xFFFFFFu, CNT_FLAGS = 24u;
+static_assert(MAX_T <= CNT_MASK, "the count and the flags share a word");
+// a job's slot in the parked words: `stride` triples, then stride / 2 segments as (GPUs | first triple << 16)
+__host__ __device__ inline size_t park_words(uint32_t stride) { return (size_t)stride + stride / 2u; }
+
+// What the scan of the counts leaves: offsets in the table, totals for the fill pass, and both for the host.
+struct ScanOut {
+    uint32_t *off_t, *off_s;   // n_jobs + 1 each
+    uint32_t *totals;
+    uint32_t *back;            // [16 words of totals | n_jobs + 1 triple offsets | n_jobs + 1 segment offsets], one piece for the host
+    uint32_t back_offsets;     // ... the offsets only when the host keeps mirrors of them
+};
+
+__device__ __forceinline__ void write_totals(const ScanOut &S, uint32_t n_jobs, uint64_t nt, uint64_t ns, uint32_t mt, uint32_t ms,
+                                             uint32_t err) {
+    S.off_t[n_jobs] = (uint32_t)nt; S.off_s[n_jobs] = (uint32_t)ns;
+    for (uint32_t *to : {S.totals, S.back}) {
+        to[TOT_NT_LO] = (uint32_t)nt; to[TOT_NT_HI] = (uint32_t)(nt >> 32);
+        to[TOT_NS_LO] = (uint32_t)ns; to[TOT_NS_HI] = (uint32_t)(ns >> 32);
+        to[TOT_MAX_T] = mt; to[TOT_MAX_S] = ms; to[TOT_ERR] = err;
+    }
+    if (S.back_offsets) { S.back[16 + n_jobs] = (uint32_t)nt; S.back[16 + 2 * n_jobs + 1] = (uint32_t)ns; }
+}
+__device__ __forceinline__ void write_offsets(const ScanOut &S, uint32_t n_jobs, uint32_t j, uint32_t t, uint32_t s) {
+    S.off_t[j] = t; S.off_s[j] = s;
+    if (S.back_offsets) { S.back[16 + j] = t; S.back[16 + n_jobs + 1 + j] = s; }
+}
 
 // exclusive prefix sum of one value per thread over the workgroup (all threads call it): inside the
 // wavefronts by shuffles, then the wavefronts' totals through LDS (lds: one word per wavefront)
@@ -76,6 +114,9 @@ __device__ __forceinline__ uint32_t search_hash(uint32_t kl, uint32_t kn) {
 // Equal jobs of a workgroup first elect one of them through a table in LDS; only that one goes to the global table.
 constexpr int LEAD_THREADS = 256;
 constexpr uint32_t SHARE_MIN_JOBS = 2048;                  // calls with fewer jobs do not look for equal ones
+constexpr uint32_t SCAN_MOST_TILES = 4096;                 // beyond 2^20 jobs one workgroup scans (every tile reads all before it)
+constexpr uint32_t ENUM_SELF_SCAN = ENUM_THREADS;          // a thread per job; more would queue at the counter as well
+constexpr size_t BACK_DIRECT_WORDS = 4096;
 
 __global__ __launch_bounds__(LEAD_THREADS) void k_enum_leaders(const uint32_t *__restrict__ layers,
                                                                const uint32_t *__restrict__ gbatch,
@@ -120,27 +161,88 @@ __global__ __launch_bounds__(LEAD_THREADS) void k_enum_leaders(const uint32_t *_
     if (valid) leader[j] = s_lead[rep];
 }
 
-// the counts of a job that did not search are its leader's
+// the counts of a job that did not search are its leader's; sums and maxima of every workgroup's jobs for k_scan_tiles
+struct TileSum { unsigned long long t, s; uint32_t mt, ms, err, pad; };
+
 __global__ __launch_bounds__(LEAD_THREADS) void k_spread_counts(const uint32_t *__restrict__ leader, uint32_t n_jobs,
-                                                                uint32_t *__restrict__ cnt_t, uint32_t *__restrict__ cnt_s) {
+                                                                uint32_t *__restrict__ cnt_t, uint32_t *__restrict__ cnt_s,
+                                                                TileSum *__restrict__ sums) {
+    __shared__ uint32_t w_t[LEAD_THREADS / 64], w_s[LEAD_THREADS / 64], w_mt[LEAD_THREADS / 64], w_ms[LEAD_THREADS / 64], w_e[LEAD_THREADS / 64];
     const uint32_t j = blockIdx.x * LEAD_THREADS + threadIdx.x;
-    if (j >= n_jobs) return;
-    const uint32_t l = leader[j];
-    if (l != j) {
-        cnt_t[j] = cnt_t[l];
-        cnt_s[j] = cnt_s[l];
+    uint32_t ct = 0, cs = 0;
+    if (j < n_jobs) {
+        const uint32_t l = leader[j];
+        ct = cnt_t[l]; cs = cnt_s[l];
+        if (l != j) { cnt_t[j] = ct; cnt_s[j] = cs; }
+    }
+    uint32_t err = ct >> CNT_FLAGS, st = ct & CNT_MASK, ss = cs, mt = st, ms = cs;   // (256 jobs of at most 2,048 triples)
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        const uint32_t a = __shfl_xor(mt, off, 64), b = __shfl_xor(ms, off, 64);
+        mt = a > mt ? a : mt; ms = b > ms ? b : ms;
+        st += __shfl_xor(st, off, 64); ss += __shfl_xor(ss, off, 64); err |= __shfl_xor(err, off, 64);
+    }
+    const uint32_t w = threadIdx.x >> 6;
+    if ((threadIdx.x & 63u) == 0) { w_t[w] = st; w_s[w] = ss; w_mt[w] = mt; w_ms[w] = ms; w_e[w] = err; }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        TileSum o = {0ull, 0ull, 0u, 0u, 0u, 0u};
+        for (uint32_t k = 0; k < LEAD_THREADS / 64; ++k) {
+            o.t += w_t[k]; o.s += w_s[k]; o.err |= w_e[k];
+            o.mt = w_mt[k] > o.mt ? w_mt[k] : o.mt; o.ms = w_ms[k] > o.ms ? w_ms[k] : o.ms;
+        }
+        sums[blockIdx.x] = o;
     }
 }
 
+// Exclusive scan of the counts, a workgroup per LEAD_THREADS jobs: what lies before them is the sum over the workgroups
+// before (a few loads per thread up to the 4,096 workgroups this is used for), the rest a scan of its own.
+__global__ __launch_bounds__(LEAD_THREADS) void k_scan_tiles(const uint32_t *__restrict__ cnt_t, const uint32_t *__restrict__ cnt_s,
+                                                             uint32_t n_jobs, const TileSum *__restrict__ sums, ScanOut S) {
+    static_assert(LEAD_THREADS == ENUM_THREADS, "block_excl_scan");
+    __shared__ uint32_t tmp[ENUM_THREADS / 64];
+    __shared__ unsigned long long b_t[LEAD_THREADS / 64], b_s[LEAD_THREADS / 64];
+    __shared__ uint32_t b_mt[LEAD_THREADS / 64], b_ms[LEAD_THREADS / 64], b_e[LEAD_THREADS / 64];
+    const uint32_t tid = threadIdx.x, j = blockIdx.x * LEAD_THREADS + tid;
+    const bool last = blockIdx.x == gridDim.x - 1;
+    const uint32_t ct = j < n_jobs ? cnt_t[j] & CNT_MASK : 0u, cs = j < n_jobs ? cnt_s[j] : 0u;
+    unsigned long long bt = 0, bs = 0;
+    uint32_t mt = 0, ms = 0, err = 0;
+    for (uint32_t k = tid; k < blockIdx.x + (last ? 1u : 0u); k += LEAD_THREADS) {   // (the last one also closes the totals)
+        const TileSum o = sums[k];
+        if (k < blockIdx.x) { bt += o.t; bs += o.s; }
+        mt = o.mt > mt ? o.mt : mt; ms = o.ms > ms ? o.ms : ms; err |= o.err;
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        const uint32_t a = __shfl_xor(mt, off, 64), b = __shfl_xor(ms, off, 64);
+        mt = a > mt ? a : mt; ms = b > ms ? b : ms;
+        bt += __shfl_xor(bt, off, 64); bs += __shfl_xor(bs, off, 64); err |= __shfl_xor(err, off, 64);
+    }
+    const uint32_t w = tid >> 6;
+    if ((tid & 63u) == 0) { b_t[w] = bt; b_s[w] = bs; b_mt[w] = mt; b_ms[w] = ms; b_e[w] = err; }
+    uint32_t all_t, all_s;
+    const uint32_t et = block_excl_scan(ct, tmp, &all_t), es = block_excl_scan(cs, tmp, &all_s);   // (also the barrier after b_*)
+    bt = 0; bs = 0; mt = 0; ms = 0; err = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < LEAD_THREADS / 64; ++k) {
+        bt += b_t[k]; bs += b_s[k]; err |= b_e[k];
+        mt = b_mt[k] > mt ? b_mt[k] : mt; ms = b_ms[k] > ms ? b_ms[k] : ms;
+    }
+    if (j < n_jobs) write_offsets(S, n_jobs, j, (uint32_t)(bt + et), (uint32_t)(bs + es));
+    if (last && tid == 0) write_totals(S, n_jobs, bt + all_t, bs + all_s, mt, ms, err);
+}
+
+// self_scan != 0: the workgroup that ends last also scans the counts (n_jobs <= ENUM_SELF_SCAN = ENUM_THREADS, no leaders).
+// done0 = value of the counter of finished workgroups before this launch: it only ever counts up.
 template <int MODE>
 __global__ __launch_bounds__(ENUM_THREADS) void k_enumerate(
     const uint32_t *__restrict__ layers, const uint32_t *__restrict__ gbatch,
     const uint32_t *__restrict__ mbatch, rk_plan_bounds bounds, const uint32_t *__restrict__ leader,
-    uint32_t *__restrict__ cnt_t, uint32_t *__restrict__ cnt_s,
-    uint32_t *__restrict__ park, uint32_t park_stride,
+    uint32_t *cnt_t, uint32_t *cnt_s, uint32_t *__restrict__ park, uint32_t park_stride,
     const uint32_t *__restrict__ triple_off, const uint32_t *__restrict__ seg_off,
     uint32_t *__restrict__ triples, uint32_t *__restrict__ seg_g, uint32_t *__restrict__ seg_first,
-    uint32_t *__restrict__ totals, uint64_t cap_triples, uint64_t cap_segs) {
+    uint32_t self_scan, uint32_t done0, ScanOut S) {
     extern __shared__ uint32_t gmap[];                      // counting and search modes: bitmap of the GPU counts, word prefixes
     // Two arrays serve everything (a third would cost occupancy): `lists` holds the two divisor lists and later
     // the keys gathered by segment; `keys` holds the keys as they are found, then (once every thread has its keys
@@ -156,17 +258,7 @@ __global__ __launch_bounds__(ENUM_THREADS) void k_enumerate(
     const uint32_t j = blockIdx.x, tid = threadIdx.x;
     if (MODE == MODE_COUNT && leader && leader[j] != j) return;   // (whole workgroup) the leader searches for this job
     uint32_t cnt, err = 0;
-    if (MODE == MODE_FILL_PARKED) {
-        // launched before the host has seen the totals: nothing is written unless the
-        // counting pass raised no flag and the table takes everything (same in all threads)
-        const uint64_t nt = ((uint64_t)totals[TOT_NT_HI] << 32) | totals[TOT_NT_LO];
-        const uint64_t ns = ((uint64_t)totals[TOT_NS_HI] << 32) | totals[TOT_NS_LO];
-        if (totals[TOT_ERR] != 0u || nt > 0xFFFFFFFFull || nt > cap_triples || ns > cap_segs) return;
-        cnt = cnt_t[j];
-        const size_t at = (size_t)(leader ? leader[j] : j) * park_stride;   // the keys were parked by the job that searched
-        for (uint32_t i = tid; i < cnt; i += ENUM_THREADS) keys[i] = park[at + i];
-        __syncthreads();
-    } else {
+    {
         const uint32_t l = layers[j], b = gbatch[j], mu = mbatch[j];
         if (tid == 0) { nd = 0; np = 0; nk = 0; }
         __syncthreads();
@@ -296,31 +388,86 @@ __global__ __launch_bounds__(ENUM_THREADS) void k_enumerate(
     uint32_t nseg;
     uint32_t sidx = block_excl_scan(starts, scan_tmp, &nseg);
 
-    if (MODE == MODE_COUNT) {
-        if (tid == 0) {
-            cnt_t[j] = cnt;
-            cnt_s[j] = nseg;
-            if (cnt > park_stride) err |= ERR_PARK_FULL;
-            if (err) atomicOr(&totals[TOT_ERR], err);
-        }
-        // park the sorted keys in the job's slot for the fill pass, if they fit
-        if (cnt <= park_stride) {
-            const size_t at = (size_t)j * park_stride;
-            for (uint32_t i = tid; i < cnt; i += ENUM_THREADS) park[at + i] = fin[i];
-        }
-        return;
-    }
-    const uint32_t t0 = triple_off[j], s0 = seg_off[j];
-    for (uint32_t i = lo; i < hi; ++i) {
+    // the job's words go to its place in the table or, if they fit, to its slot of the parked words
+    const bool room = MODE != MODE_COUNT || (cnt <= park_stride && nseg <= park_stride / 2u);
+    const size_t at = MODE == MODE_COUNT ? (size_t)j * park_words(park_stride) : triple_off[j];
+    const uint32_t s0 = MODE == MODE_COUNT ? 0u : seg_off[j];
+    for (uint32_t i = lo; i < hi && room; ++i) {
         const uint32_t k = fin[i];
         const uint32_t g = k >> 16, lt = (k >> 14) & 3u, p = (k >> 2) & 0xFFFu, v = k & 3u;
-        const uint32_t d = g / (p << lt);
-        triples[t0 + i] = d | (lt << 16) | (p << 18) | (v << 30);
+        const uint32_t d = g / (p << lt), word = d | (lt << 16) | (p << 18) | (v << 30);
+        if (MODE == MODE_COUNT) park[at + i] = word; else triples[at + i] = word;
         if (i == 0 || g != (fin[i - 1] >> 16)) {
-            seg_g[s0 + sidx] = g;
-            seg_first[s0 + sidx] = i;
+            if (MODE == MODE_COUNT) park[at + park_stride + sidx] = g | (i << 16);
+            else { seg_g[s0 + sidx] = g; seg_first[s0 + sidx] = i; }
             ++sidx;
         }
+    }
+    if (MODE != MODE_COUNT) return;
+    if (!room) err |= ERR_PARK_FULL;
+    if (!self_scan) {
+        if (tid == 0) { cnt_t[j] = cnt | (err << CNT_FLAGS); cnt_s[j] = nseg; }
+        return;
+    }
+    // Counts, then a release and the counter, at the device's scope (the workgroups sit on several L2 caches); the one
+    // that brings the counter to its end acquires and reads them all.
+    __shared__ uint32_t ends;
+    if (tid == 0) {
+        __hip_atomic_store(&cnt_t[j], cnt | (err << CNT_FLAGS), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&cnt_s[j], nseg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        ends = __hip_atomic_fetch_add(&S.totals[TOT_DONE], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (ends - done0 != gridDim.x - 1u) return;
+    uint32_t ct = 0, cs = 0;
+    if (tid < gridDim.x) {
+        ct = __hip_atomic_load(&cnt_t[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        cs = __hip_atomic_load(&cnt_s[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    uint32_t mt = ct & CNT_MASK, ms = cs, flags = ct >> CNT_FLAGS, all_t, all_s;
+    ct &= CNT_MASK;
+    const uint32_t et = block_excl_scan(ct, scan_tmp, &all_t), es = block_excl_scan(cs, scan_tmp, &all_s);
+    if (tid < gridDim.x) write_offsets(S, gridDim.x, tid, et, es);
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        const uint32_t a = __shfl_xor(mt, off, 64), b = __shfl_xor(ms, off, 64);
+        mt = a > mt ? a : mt; ms = b > ms ? b : ms;
+        flags |= __shfl_xor(flags, off, 64);
+    }
+    if ((tid & 63u) == 0) { scan_tmp[tid >> 6] = mt; scan_tmp[4 + (tid >> 6)] = ms; scan_tmp[8 + (tid >> 6)] = flags; }
+    __syncthreads();
+    if (tid == 0) {
+        for (uint32_t w = 1; w < ENUM_THREADS / 64; ++w) {
+            mt = scan_tmp[w] > mt ? scan_tmp[w] : mt;
+            ms = scan_tmp[4 + w] > ms ? scan_tmp[4 + w] : ms;
+            flags |= scan_tmp[8 + w];
+        }
+        write_totals(S, gridDim.x, all_t, all_s, mt, ms, flags);
+    }
+}
+
+// The table from the parked words, a wavefront per job.  Launched before the host has seen the totals: nothing is
+// written unless the counting pass raised no flag and the table takes everything (the same in all threads).
+constexpr int FILL_THREADS = 256;
+
+__global__ __launch_bounds__(FILL_THREADS) void k_fill(uint32_t n_jobs, const uint32_t *__restrict__ leader,
+                                                       const uint32_t *__restrict__ park, uint32_t park_stride,
+                                                       const uint32_t *__restrict__ triple_off, const uint32_t *__restrict__ seg_off,
+                                                       uint32_t *__restrict__ triples, uint32_t *__restrict__ seg_g,
+                                                       uint32_t *__restrict__ seg_first, const uint32_t *__restrict__ totals,
+                                                       uint64_t cap_triples, uint64_t cap_segs) {
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t j = blockIdx.x * (FILL_THREADS / 64) + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint64_t nt = ((uint64_t)totals[TOT_NT_HI] << 32) | totals[TOT_NT_LO];
+    const uint64_t ns = ((uint64_t)totals[TOT_NS_HI] << 32) | totals[TOT_NS_LO];
+    if (j >= n_jobs || totals[TOT_ERR] != 0u || nt > 0xFFFFFFFFull || nt > cap_triples || ns > cap_segs) return;
+    const uint32_t t0 = triple_off[j], t_n = triple_off[j + 1] - t0, s0 = seg_off[j], s_n = seg_off[j + 1] - s0;
+    const uint32_t *from = park + (size_t)(leader ? leader[j] : j) * park_words(park_stride);   // parked by the job that searched
+    for (uint32_t i = lane; i < t_n; i += 64) triples[(size_t)t0 + i] = from[i];
+    for (uint32_t i = lane; i < s_n; i += 64) {
+        const uint32_t w = from[park_stride + i];
+        seg_g[(size_t)s0 + i] = w & 0xFFFFu;
+        seg_first[(size_t)s0 + i] = w >> 16;
     }
 }
 
@@ -330,8 +477,6 @@ __global__ __launch_bounds__(ENUM_THREADS) void k_enumerate(
 // one is scanned); a thread sums its eight, the sums are scanned inside the
 // wavefronts by shuffles and across them through LDS, and the offsets leave
 // through LDS so that the stores are coalesced too.
-// back: [16 words of totals | n_jobs + 1 triple offsets | n_jobs + 1 segment offsets], one piece for the host
-// (the offsets only when the host keeps mirrors of them: back_offsets)
 constexpr uint32_t SCAN_PER = 8, SCAN_TILE = 1024 * SCAN_PER;
 
 struct Eight { uint32_t v[SCAN_PER]; };
@@ -351,19 +496,17 @@ __device__ __forceinline__ Eight load_eight(const uint32_t *__restrict__ cnt, ui
 }
 
 __global__ __launch_bounds__(1024) void k_scan_counts(const uint32_t *__restrict__ cnt_t,
-                                                      const uint32_t *__restrict__ cnt_s, uint32_t n_jobs,
-                                                      uint32_t *__restrict__ off_t, uint32_t *__restrict__ off_s,
-                                                      uint32_t *__restrict__ totals, uint32_t *__restrict__ back,
-                                                      bool back_offsets) {
+                                                      const uint32_t *__restrict__ cnt_s, uint32_t n_jobs, ScanOut S) {
     __shared__ __align__(16) uint32_t buf_t[SCAN_TILE], buf_s[SCAN_TILE];
     __shared__ unsigned long long wave_t[16], wave_s[16];
-    __shared__ uint32_t wave_mt[16], wave_ms[16];
+    __shared__ uint32_t wave_mt[16], wave_ms[16], wave_e[16];
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     unsigned long long carry_t = 0, carry_s = 0;            // everything before the tile (same in every thread)
-    uint32_t mt = 0, ms = 0;                                // running maxima of this thread's elements
+    uint32_t mt = 0, ms = 0, err = 0;                       // running maxima and flags of this thread's elements
     Eight nt_next = load_eight(cnt_t, tid * SCAN_PER, n_jobs), ns_next = load_eight(cnt_s, tid * SCAN_PER, n_jobs);
     for (uint32_t base = 0; base < n_jobs; base += SCAN_TILE) {
-        const Eight ct = nt_next, cs = ns_next;
+        Eight ct = nt_next;
+        const Eight cs = ns_next;
         if (base + SCAN_TILE < n_jobs) {
             nt_next = load_eight(cnt_t, base + SCAN_TILE + tid * SCAN_PER, n_jobs);
             ns_next = load_eight(cnt_s, base + SCAN_TILE + tid * SCAN_PER, n_jobs);
@@ -371,6 +514,8 @@ __global__ __launch_bounds__(1024) void k_scan_counts(const uint32_t *__restrict
         unsigned long long sum_t = 0, sum_s = 0;
 #pragma unroll
         for (uint32_t i = 0; i < SCAN_PER; ++i) {
+            err |= ct.v[i] >> CNT_FLAGS;
+            ct.v[i] &= CNT_MASK;
             sum_t += ct.v[i]; sum_s += cs.v[i];
             mt = ct.v[i] > mt ? ct.v[i] : mt;
             ms = cs.v[i] > ms ? cs.v[i] : ms;
@@ -404,13 +549,7 @@ __global__ __launch_bounds__(1024) void k_scan_counts(const uint32_t *__restrict
         for (uint32_t i = 0; i < SCAN_PER; ++i) {
             const uint32_t at = i * 1024 + tid, j = base + at;
             if (j < n_jobs) {
-                const uint32_t a = buf_t[at], b = buf_s[at];
-                off_t[j] = a;
-                off_s[j] = b;
-                if (back_offsets) {
-                    back[16 + j] = a;
-                    back[16 + n_jobs + 1 + j] = b;
-                }
+                write_offsets(S, n_jobs, j, buf_t[at], buf_s[at]);
             }
         }
         carry_t += all_t; carry_s += all_s;
@@ -420,20 +559,16 @@ __global__ __launch_bounds__(1024) void k_scan_counts(const uint32_t *__restrict
     for (int off = 32; off >= 1; off >>= 1) {
         const uint32_t a = __shfl_xor(mt, off, 64), b = __shfl_xor(ms, off, 64);
         mt = a > mt ? a : mt; ms = b > ms ? b : ms;
+        err |= __shfl_xor(err, off, 64);
     }
-    if (lane == 0) { wave_mt[wave] = mt; wave_ms[wave] = ms; }
+    if (lane == 0) { wave_mt[wave] = mt; wave_ms[wave] = ms; wave_e[wave] = err; }
     __syncthreads();
     if (tid == 0) {
-        for (uint32_t w = 0; w < 16; ++w) { mt = wave_mt[w] > mt ? wave_mt[w] : mt; ms = wave_ms[w] > ms ? wave_ms[w] : ms; }
-        off_t[n_jobs] = (uint32_t)carry_t; off_s[n_jobs] = (uint32_t)carry_s;
-        totals[TOT_NT_LO] = (uint32_t)carry_t; totals[TOT_NT_HI] = (uint32_t)(carry_t >> 32);
-        totals[TOT_NS_LO] = (uint32_t)carry_s; totals[TOT_NS_HI] = (uint32_t)(carry_s >> 32);
-        totals[TOT_MAX_T] = mt; totals[TOT_MAX_S] = ms;
-        back[16 + n_jobs] = (uint32_t)carry_t; back[16 + 2 * n_jobs + 1] = (uint32_t)carry_s;
-        back[TOT_NT_LO] = (uint32_t)carry_t; back[TOT_NT_HI] = (uint32_t)(carry_t >> 32);
-        back[TOT_NS_LO] = (uint32_t)carry_s; back[TOT_NS_HI] = (uint32_t)(carry_s >> 32);
-        back[TOT_MAX_T] = mt; back[TOT_MAX_S] = ms;
-        back[TOT_ERR] = totals[TOT_ERR];                    // flags of the counting pass
+        for (uint32_t w = 0; w < 16; ++w) {
+            mt = wave_mt[w] > mt ? wave_mt[w] : mt; ms = wave_ms[w] > ms ? wave_ms[w] : ms;
+            err |= wave_e[w];
+        }
+        write_totals(S, n_jobs, carry_t, carry_s, mt, ms, err);
     }
 }
 
@@ -469,32 +604,41 @@ extern "C" int32_t rk_enumerate_plans(rk_ctx *ctx, const rk_jobs *jobs, const rk
     table->n_triples = table->n_segs = 0;
     table->max_triples_per_job = table->max_segs_per_job = 0;
 
-    uint32_t *cnt_t, *cnt_s, *totals, *off_t, *off_s, *park, *back;
+    uint32_t *cnt_t, *cnt_s, *totals, *off_t, *off_s, *park;
     int32_t rc;
     if ((rc = rk_scratch(ctx, SL_CNT_T, (size_t)(2 * (size_t)J + 2) * 4, (void **)&cnt_t))) return rc;
     if ((rc = rk_scratch(ctx, SL_CNT_S, (size_t)(2 * (size_t)J + 2) * 4, (void **)&cnt_s))) return rc;
-    // totals (16 words) and the leaders' hash table (a power of two, at least twice the jobs) are cleared together
-    uint64_t tab_slots = 64;
-    while (tab_slots < 2 * (uint64_t)J) tab_slots <<= 1;
     // (a call with few jobs searches for each of them: two more launches would cost more than they save)
     const bool share = J >= SHARE_MIN_JOBS;
-    if (!share) tab_slots = 0;
-    uint32_t *tab, *leader = nullptr;
-    if ((rc = rk_scratch(ctx, SL_TOTALS, (size_t)(16 + tab_slots) * 4, (void **)&totals))) return rc;
-    tab = totals + 16;
-    if (share && (rc = rk_scratch(ctx, SL_ENUM_LEADER, ((size_t)J + 1) * 4, (void **)&leader))) return rc;
-    // one slot per job for the parked keys: as wide as the widest job seen so far, or a first guess
+    uint64_t tab_slots = 64;                                  // leaders' hash table: a power of two, at least twice the jobs
+    while (tab_slots < 2 * (uint64_t)J) tab_slots <<= 1;
+    const uint32_t job_blocks = (J + LEAD_THREADS - 1) / LEAD_THREADS;
+    const bool tiles = share && job_blocks <= SCAN_MOST_TILES;
+    uint32_t *tab = nullptr, *leader = nullptr;
+    TileSum *sums = nullptr;
+    if (!ctx->scratch[SL_TOTALS]) {                           // never grows; the counter in it starts at zero
+        if ((rc = rk_scratch(ctx, SL_TOTALS, 16 * sizeof(uint32_t), (void **)&totals))) return rc;
+        k_zero_words<<<1, 64, 0, ctx->stream>>>(totals, 16u);
+        RK_CHECK_LAUNCH(ctx, "k_zero_words");
+        ctx->enum_done = 0;
+    }
+    totals = static_cast<uint32_t *>(ctx->scratch[SL_TOTALS]);
+    if (share) {
+        if ((rc = rk_scratch(ctx, SL_ENUM_TAB, (size_t)tab_slots * 4, (void **)&tab))) return rc;
+        if ((rc = rk_scratch(ctx, SL_ENUM_LEADER, ((size_t)J + 1) * 4, (void **)&leader))) return rc;
+        if ((rc = rk_scratch(ctx, SL_ENUM_SUMS, (size_t)job_blocks * sizeof(TileSum), (void **)&sums))) return rc;
+    }
+    // one slot per job for the parked words: as wide as the widest job seen so far, or a first guess
     if (ctx->park_stride == 0) ctx->park_stride = 512;
     const uint32_t park_stride = ctx->park_stride;
-    if ((rc = rk_scratch(ctx, SL_PARK, ((size_t)J * park_stride + 1) * 4, (void **)&park))) return rc;
+    if ((rc = rk_scratch(ctx, SL_PARK, ((size_t)J * park_words(park_stride) + 1) * 4, (void **)&park))) return rc;
     const bool fill = table->triples != nullptr;              // otherwise a sizing call
     if (fill && (!table->triple_off || !table->seg_off || !table->seg_g || !table->seg_first))
         return rk_fail(ctx, RK_ERR_INVALID_ARG, "table buffer is null");
     off_t = fill ? table->triple_off : cnt_t + J;             // offsets go straight into the table
     off_s = fill ? table->seg_off : cnt_s + J;
-    // what comes back in one piece: totals, then the two offset arrays (pinned staging on the host)
+    // what comes back in one piece: totals, then the two offset arrays (pinned host memory that the scan writes)
     const size_t words_back = 16 + 2 * ((size_t)J + 1);
-    if ((rc = rk_scratch(ctx, SL_ENUM_BACK, words_back * 4, (void **)&back))) return rc;
     if (ctx->h_stage_words < words_back) {
         if (ctx->h_stage) RK_HIP(ctx, hipHostFree(ctx->h_stage));
         ctx->h_stage = nullptr; ctx->h_stage_words = 0;
@@ -504,36 +648,46 @@ extern "C" int32_t rk_enumerate_plans(rk_ctx *ctx, const rk_jobs *jobs, const rk
     uint32_t *h = ctx->h_stage;
     if (!ctx->counts_ev) RK_HIP(ctx, hipEventCreateWithFlags(&ctx->counts_ev, hipEventDisableTiming));
 
+    const bool mirrors = fill && table->h_triple_off && table->h_seg_off;
+    // Few words go straight to the host; the offsets of many jobs in one copy (single words over the bus are slow).
+    const bool direct = words_back <= BACK_DIRECT_WORDS || !mirrors;
+    uint32_t *back;
+    if (direct) RK_HIP(ctx, hipHostGetDevicePointer((void **)&back, h, 0));
+    else if ((rc = rk_scratch(ctx, SL_ENUM_BACK, words_back * 4, (void **)&back))) return rc;
+    const ScanOut S = {off_t, off_s, totals, back, mirrors ? 1u : 0u};
+
     const size_t gmap_bytes = (size_t)((bounds->g_max >> 5) + 1u) * 2 * sizeof(uint32_t);   // bitmap + word prefixes
-    k_zero_words<<<(uint32_t)((16 + tab_slots + 255) / 256), 256, 0, ctx->stream>>>(totals, (uint32_t)(16 + tab_slots));
+    const bool self_scan = J > 0 && J <= ENUM_SELF_SCAN;
+    if (share) {
+        k_zero_words<<<(uint32_t)((tab_slots + 255) / 256), 256, 0, ctx->stream>>>(tab, (uint32_t)tab_slots);
+        k_enum_leaders<<<job_blocks, LEAD_THREADS, 0, ctx->stream>>>(jobs->layers, jobs->gbatch, jobs->mbatch, J, tab,
+                                                                    (uint32_t)(tab_slots - 1), leader);
+        RK_CHECK_LAUNCH(ctx, "k_enum_leaders");
+    }
     if (J > 0) {
-        const uint32_t job_blocks = (J + LEAD_THREADS - 1) / LEAD_THREADS;
-        if (share) {
-            k_enum_leaders<<<job_blocks, LEAD_THREADS, 0, ctx->stream>>>(jobs->layers, jobs->gbatch, jobs->mbatch, J, tab,
-                                                                        (uint32_t)(tab_slots - 1), leader);
-            RK_CHECK_LAUNCH(ctx, "k_enum_leaders");
-        }
         k_enumerate<MODE_COUNT><<<J, ENUM_THREADS, gmap_bytes, ctx->stream>>>(
             jobs->layers, jobs->gbatch, jobs->mbatch, *bounds, leader, cnt_t, cnt_s, park, park_stride,
-            nullptr, nullptr, nullptr, nullptr, nullptr, totals, 0, 0);
+            nullptr, nullptr, nullptr, nullptr, nullptr, self_scan ? 1u : 0u, ctx->enum_done, S);
         RK_CHECK_LAUNCH(ctx, "k_enumerate<count>");
-        if (share) {
-            k_spread_counts<<<job_blocks, LEAD_THREADS, 0, ctx->stream>>>(leader, J, cnt_t, cnt_s);
-            RK_CHECK_LAUNCH(ctx, "k_spread_counts");
-        }
+        if (self_scan) ctx->enum_done += J;
     }
-    const bool mirrors = fill && table->h_triple_off && table->h_seg_off;
-    k_scan_counts<<<1, 1024, 0, ctx->stream>>>(cnt_t, cnt_s, J, off_t, off_s, totals, back, mirrors);
+    if (share) {
+        k_spread_counts<<<job_blocks, LEAD_THREADS, 0, ctx->stream>>>(leader, J, cnt_t, cnt_s, sums);
+        RK_CHECK_LAUNCH(ctx, "k_spread_counts");
+    }
+    if (tiles) k_scan_tiles<<<job_blocks, LEAD_THREADS, 0, ctx->stream>>>(cnt_t, cnt_s, J, sums, S);
+    else if (!self_scan) k_scan_counts<<<1, 1024, 0, ctx->stream>>>(cnt_t, cnt_s, J, S);
     RK_CHECK_LAUNCH(ctx, "k_scan_counts");
-    RK_HIP(ctx, hipMemcpyAsync(h, back, (mirrors ? words_back : 16) * 4, hipMemcpyDeviceToHost, ctx->stream));
+    if (!direct) RK_HIP(ctx, hipMemcpyAsync(h, back, words_back * 4, hipMemcpyDeviceToHost, ctx->stream));
     RK_HIP(ctx, hipEventRecord(ctx->counts_ev, ctx->stream));
     // The fill pass goes out before the host knows the totals, so that the device does not wait for the
     // round trip: the kernel itself checks the flags and the table's capacity.
     if (fill && J > 0) {
-        k_enumerate<MODE_FILL_PARKED><<<J, ENUM_THREADS, 0, ctx->stream>>>(
-            jobs->layers, jobs->gbatch, jobs->mbatch, *bounds, leader, cnt_t, cnt_s, park, park_stride,
-            off_t, off_s, table->triples, table->seg_g, table->seg_first, totals, table->cap_triples, table->cap_segs);
-        RK_CHECK_LAUNCH(ctx, "k_enumerate<fill>");
+        constexpr uint32_t PER = FILL_THREADS / 64;
+        k_fill<<<(J + PER - 1) / PER, FILL_THREADS, 0, ctx->stream>>>(J, leader, park, park_stride, off_t, off_s, table->triples,
+                                                                     table->seg_g, table->seg_first, totals, table->cap_triples,
+                                                                     table->cap_segs);
+        RK_CHECK_LAUNCH(ctx, "k_fill");
     }
     RK_HIP(ctx, hipEventSynchronize(ctx->counts_ev));
 
@@ -548,9 +702,10 @@ extern "C" int32_t rk_enumerate_plans(rk_ctx *ctx, const rk_jobs *jobs, const rk
     table->max_segs_per_job = h[TOT_MAX_S];
     const bool parked = !(h[TOT_ERR] & ERR_PARK_FULL);
     if (!parked) {                                            // next time the slots will be wide enough
-        uint32_t want = h[TOT_MAX_T] + h[TOT_MAX_T] / 4;
+        uint32_t want = h[TOT_MAX_T] > 2 * h[TOT_MAX_S] ? h[TOT_MAX_T] : 2 * h[TOT_MAX_S];
+        want += want / 4;
         want = (want + 63u) & ~63u;
-        ctx->park_stride = want > MAX_T ? MAX_T : want;
+        ctx->park_stride = want > 2 * MAX_T ? 2 * MAX_T : want;
     }
 
     if (!fill) return RK_OK;
@@ -564,7 +719,7 @@ extern "C" int32_t rk_enumerate_plans(rk_ctx *ctx, const rk_jobs *jobs, const rk
     if (J > 0 && !parked) {                                   // the parked keys were incomplete: search again
         k_enumerate<MODE_FILL_SEARCH><<<J, ENUM_THREADS, gmap_bytes, ctx->stream>>>(
             jobs->layers, jobs->gbatch, jobs->mbatch, *bounds, leader, cnt_t, cnt_s, park, park_stride,
-            off_t, off_s, table->triples, table->seg_g, table->seg_first, totals, 0, 0);
+            off_t, off_s, table->triples, table->seg_g, table->seg_first, 0u, 0u, S);
         RK_CHECK_LAUNCH(ctx, "k_enumerate<fill>");
     }
     return RK_OK;

@@ -9,7 +9,7 @@
 
 #include "rubick.h"
 
-enum { RK_SCRATCH_SLOTS = 56 };
+enum { RK_SCRATCH_SLOTS = 64 };
 
 struct rk_ctx {
     int device;
@@ -21,6 +21,7 @@ struct rk_ctx {
     uint32_t *h_stage;                      // pinned staging for the plan-table offsets, grown on demand
     size_t h_stage_words;
     uint32_t park_stride;                   // enumeration: words per job between its two passes
+    uint32_t enum_done;                     // enumeration: the device's counter of finished searches, as the launches so far leave it
     hipEvent_t counts_ev;                   // enumeration: the counts have reached the host (made on demand)
     hipStream_t sim_stream;                 // simulation: its own stream (a tick is captured as a graph), made on demand
     hipEvent_t sim_ev[4];                   // ... ordered after and before the context's stream with the first two; its batches of ticks
@@ -48,7 +49,7 @@ enum {
     SL_JMAP,                                             // rounds that share jobs: slot -> job
     SL_ENUM_BACK,                                        // enumeration: totals and offsets in one piece for the host
     SL_PLACE_RESULT,                                     // placement: its four summary words
-    SL_ENUM_LEADER,                                      // enumeration: the job whose search a job shares
+    SL_ENUM_LEADER, SL_ENUM_TAB, SL_ENUM_SUMS,           // enumeration: the job whose search a job shares, their hash table, sums per workgroup
     SL_RS_F32, SL_RS_U32, SL_RS_U64,                     // the Schedule loop: cached slopes; order, marks and saved states; CPU needs
     SL_EVAL_PARTIAL,                                     // evaluation with best plan: keys of the segments that span tiles
     SL_PLACE_KEEP,                                       // placement: which jobs keep their earlier parts

@@ -892,3 +892,34 @@ def test_fused_kernel_at_the_edges_of_its_split(gpu, n_jobs, n_cpu, n_mem, per_g
         for got, want in zip(f[:5], (bt, bp, ct, cp, cg)):
             assert np.array_equal(run.host(got, ns), run.host(want, ns))
         run.close()
+
+
+def test_enumeration_at_the_job_counts_where_the_scan_changes(gpu, orc):
+    """The last search to end scans up to 256 jobs, one workgroup below 2,048, all workgroups from there on; one context
+    takes them in turn, with a refused call, wide jobs (more words than a job's first slot) and a sizing call in between."""
+    import paper_2408_08586_amd as rk
+    rng = np.random.default_rng(7)
+    run = gpu(workloads.tiny())
+    kinds = np.array([[l, b, m] for l in (1, 12, 24, 40, 96) for b in (32, 64, 96, 128) for m in (1, 2, 3, 4)], np.uint32)
+    wide = np.array([[1, 21621600, 1], [24, 5040, 1]], np.uint32)              # up to 576 divisors; many GPU counts
+    bounds = workloads.Bounds(g_max=4096)
+
+    def check(ints, b):
+        ot = orc.enumerate_plans(ints, b)
+        jobs = rk.Jobs(np.ones((len(ints), 17), np.float32), ints, run.device)
+        t = rk.enumerate_to_table(run.ctx, jobs, rk.make_bounds(b), run.device)
+        got = dict(triple_off=rk.u32(t.triple_off), triples=t.unpack_triples(), seg_off=rk.u32(t.seg_off),
+                   seg_g=rk.u32(t.seg_g)[:t.n_segs], seg_first=rk.u32(t.seg_first)[:t.n_segs])
+        oracle_table_equal(got, ot)
+        assert np.array_equal(t.h_triple_off, ot.triple_off) and np.array_equal(t.h_seg_off, ot.seg_off)
+        assert t.c.max_triples_per_job == np.diff(ot.triple_off).max() and t.c.max_segs_per_job == np.diff(ot.seg_off).max()
+
+    for n in (1, 2, 255, 256, 257, 2047, 2048, 2049, 3, 300, 256):
+        check(kinds[rng.integers(0, len(kinds), size=n)], bounds)
+        if n in (2, 257, 2048):
+            with pytest.raises(rk.RkError) as e:                               # more triples per job than the library takes
+                check(np.concatenate([kinds[:n - 2], np.repeat(np.array([[40320, 21621600, 1]], np.uint32), 2, 0)]),
+                      workloads.Bounds(g_max=60000, mu_mask=15))
+            assert e.value.code == rk.RK_ERR_UNSUPPORTED
+            check(np.concatenate([kinds[:n], wide]), workloads.Bounds(g_max=20000, tp_max=2, pp_max=2))
+    run.close()
