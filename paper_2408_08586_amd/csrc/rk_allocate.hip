@@ -47,6 +47,10 @@ constexpr int TAIL_THREADS = 1024;
 constexpr int HULL_THREADS = 256;
 constexpr int JOB_THREADS = 256;           // kernels with one thread per job
 constexpr uint32_t BINS = 4096;            // 12 key bits per histogram level
+// Where bin b is kept: the threads of find_cut take sixteen neighbouring bins each, and laid out like this their i-th
+// bins are neighbours (from plain order every load met a 16- to 32-way bank conflict in LDS, or as many cache lines as
+// lanes in memory).
+__device__ __forceinline__ uint32_t bin_at(uint32_t b) { return (b % (BINS / JOB_THREADS)) * JOB_THREADS + b / (BINS / JOB_THREADS); }
 
 struct HullBuf {             // walk steps, entry (k, job) at k*stride + job (job relative to the call's first job)
     uint32_t *key;           // float bits of the running-minimum slope; 0 from the end of the walk on
@@ -284,21 +288,20 @@ __global__ __launch_bounds__(HULL_THREADS) void k_hull(Ctx X, JobState st, HullB
 // The same walks with several jobs per wavefront, for calls in which no job has
 // more than LANES amounts (LANES = 16 or 32): a job takes LANES neighbouring
 // lanes, the wavefront loops until the last of its jobs has finished, and a
-// job's maximum is taken over its own lanes only.
+// job's maximum is taken over its own lanes only.  Bound by instructions: the
+// maximum is of one word, the amount that reaches it comes from a ballot, and
+// a step stays in the lane of its number until the walk is over (pairs of
+// words and five stores per step: 123 us for 128,000 jobs with up to 32
+// amounts, now 90).
 template <int LANES>
-__device__ __forceinline__ unsigned long long group_max_u64(unsigned long long v, uint32_t lane) {
-    unsigned long long o;
-    o = dpp_u64<0xB1>(v);  v = o > v ? o : v;                   // quad_perm [1,0,3,2]
-    o = dpp_u64<0x4E>(v);  v = o > v ? o : v;                   // quad_perm [2,3,0,1]
-    o = dpp_u64<0x141>(v); v = o > v ? o : v;                   // row_half_mirror
-    o = dpp_u64<0x140>(v); v = o > v ? o : v;                   // row_mirror: every row of 16 lanes holds its maximum
+__device__ __forceinline__ uint32_t group_max_u32(uint32_t v, uint32_t lane) {
+    v = rs_max_u32(v, rs_dpp_u32<0xB1, 0xF>(0u, v));               // quad_perm [1,0,3,2]
+    v = rs_max_u32(v, rs_dpp_u32<0x4E, 0xF>(0u, v));               // quad_perm [2,3,0,1]
+    v = rs_max_u32(v, rs_dpp_u32<0x141, 0xF>(0u, v));              // row_half_mirror
+    v = rs_max_u32(v, rs_dpp_u32<0x140, 0xF>(0u, v));              // row_mirror: every row of 16 lanes holds its maximum
     if (LANES == 16) return v;
-    unsigned long long row[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-        row[r] = ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), 16 * r) << 32) |
-                 (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, 16 * r);
-    const unsigned long long lo = row[0] > row[1] ? row[0] : row[1], hi = row[2] > row[3] ? row[2] : row[3];
+    const uint32_t lo = rs_max_u32((uint32_t)__builtin_amdgcn_readlane((int)v, 0), (uint32_t)__builtin_amdgcn_readlane((int)v, 16));
+    const uint32_t hi = rs_max_u32((uint32_t)__builtin_amdgcn_readlane((int)v, 32), (uint32_t)__builtin_amdgcn_readlane((int)v, 48));
     return lane < 32 ? lo : hi;
 }
 
@@ -366,47 +369,50 @@ __global__ __launch_bounds__(HULL_THREADS) void k_hull_groups(Ctx X, JobState st
 
     uint32_t k = 0;
     float prev = __uint_as_float(0x7F800000u);
-    bool walking = npts > 0;                               // the same in all lanes of a job
-    while (__ballot(walking && k < H.width)) {             // until the wavefront's last job has finished
-        unsigned long long best = 0;
-        if (walking && k < H.width && can && (int32_t)sub > cur_i && val0 > cur) {
+    // the lane's step of the walk: step number = lane number within the job
+    uint32_t my_key = 0, my_raw = 0, my_tgt = 0;
+    unsigned long long my_from = 0, my_to = 0;             // its costs before and after
+    bool walking = npts > 0;                               // the same in all lanes of a job (H.width is at least 1)
+    while (__ballot(walking)) {                            // until the wavefront's last job has finished
+        uint32_t best = 0;
+        if (walking && can && (int32_t)sub > cur_i && val0 > cur) {
             float sl = (val0 - cur) / ref;
             sl = sl / (float)(cost0 - cost_cur);
-            best = ((unsigned long long)__float_as_uint(sl) << 32) | (0xFFFFFFFFu - sub);
+            best = __float_as_uint(sl);
         }
-        best = group_max_u64<LANES>(best, lane);
-        const bool step = walking && k < H.width && (best >> 32) != 0;
-        const float top = __uint_as_float((uint32_t)(best >> 32));
-        const uint32_t top_s = step ? 0xFFFFFFFFu - (uint32_t)best : 0u;
-        const int src = (int)(group_base + top_s);        // the lane that holds the chosen amount
-        const unsigned long long top_cost = ((unsigned long long)(uint32_t)__shfl((int)(uint32_t)(cost0 >> 32), src, 64) << 32) |
-                                            (uint32_t)__shfl((int)(uint32_t)cost0, src, 64);
+        const uint32_t top = group_max_u32<LANES>(best, lane);
+        walking = walking && top != 0u;
+        // the smallest amount that reaches it, and what the lane that holds it knows
+        const uint32_t reach = (uint32_t)(__ballot(best == top) >> group_base) & (LANES == 16 ? 0xFFFFu : 0xFFFFFFFFu);
+        const uint32_t top_s = reach ? (uint32_t)__ffs((int)reach) - 1u : 0u;
+        const int src = (int)(group_base + top_s);
+        unsigned long long top_cost = (uint32_t)__shfl((int)(uint32_t)cost0, src, 64);
+        if (PASS == 1) top_cost |= (unsigned long long)(uint32_t)__shfl((int)(uint32_t)(cost0 >> 32), src, 64) << 32;
         const float top_val = __shfl(val0, src, 64);
-        if (step) {
-            prev = top < prev ? top : prev;
-            if (sub == 0) {
-                const size_t e = (size_t)k * H.stride + jrel;
-                H.key[e] = __float_as_uint(prev);
-                H.raw[e] = top;
-                H.tgt[e] = (uint16_t)top_s;
-                if (PASS == 0) {
-                    H.dg[e] = (uint32_t)(top_cost - cost_cur);
-                    H.dc[e] = cpu_cost(grid, c_fixed, (uint32_t)top_cost) - (cost_cur ? cpu_cost(grid, c_fixed, (uint32_t)cost_cur) : 0ull);
-                } else {
-                    H.dg[e] = 0u;
-                    H.dc[e] = top_cost - cost_cur;
-                }
-            }
+        if (walking) {
+            prev = __uint_as_float(top) < prev ? __uint_as_float(top) : prev;
+            if (sub == k) { my_key = __float_as_uint(prev); my_raw = top; my_tgt = top_s; my_from = cost_cur; my_to = top_cost; }
             cur = top_val;
             cur_i = (int32_t)top_s;
             cost_cur = top_cost;
             ++k;
-        } else {
-            walking = false;
+            walking = k < H.width;
         }
     }
     if (valid) {
-        for (uint32_t kk = k + sub; kk < H.width; kk += LANES) H.key[(size_t)kk * H.stride + jrel] = 0u;   // unused positions
+        if (sub < k) {                                     // (a walk has no more steps than the job has lanes)
+            const size_t e = (size_t)sub * H.stride + jrel;
+            H.raw[e] = __uint_as_float(my_raw);
+            H.tgt[e] = (uint16_t)my_tgt;
+            if (PASS == 0) {
+                H.dg[e] = (uint32_t)(my_to - my_from);
+                H.dc[e] = cpu_cost(grid, c_fixed, (uint32_t)my_to) - (my_from ? cpu_cost(grid, c_fixed, (uint32_t)my_from) : 0ull);
+            } else {
+                H.dg[e] = 0u;
+                H.dc[e] = my_to - my_from;
+            }
+        }
+        for (uint32_t kk = sub; kk < H.width; kk += LANES) H.key[(size_t)kk * H.stride + jrel] = kk < k ? my_key : 0u;
         if (PASS == 1 && k > 0 && sub == 0) st.cpu_steps[rnd] = 1u;
     }
 }
@@ -438,8 +444,8 @@ __device__ Cut find_cut(const uint32_t *__restrict__ hG, const unsigned long lon
     unsigned long long sg = 0, sc = 0;
 #pragma unroll
     for (uint32_t i = 0; i < PER; ++i) {
-        vg[i] = part ? hG[top - i] : 0u;
-        vc[i] = part ? hC[top - i] : 0ull;
+        vg[i] = part ? hG[bin_at(top - i)] : 0u;
+        vc[i] = part ? hC[bin_at(top - i)] : 0ull;
         sg += vg[i]; sc += vc[i];
     }
     // inclusive scan over the threads: inside the wavefront by shuffles, then the wavefronts' totals
@@ -520,8 +526,8 @@ __device__ __forceinline__ void hist_add(const Ctx &X, const HullBuf &H, uint32_
                 if ((int32_t)(key[u] >> 20) < want_top) return;   // keys only decrease along a walk
                 bin = (key[u] >> 8) & (BINS - 1);
             }
-            if (dg[u]) atomicAdd(&lg[bin], dg[u]);
-            if (dc[u]) atomicAdd(&lc[bin], dc[u]);
+            if (dg[u]) atomicAdd(&lg[bin_at(bin)], dg[u]);
+            if (dc[u]) atomicAdd(&lc[bin_at(bin)], dc[u]);
         }
     }
 }
@@ -787,13 +793,14 @@ __device__ __forceinline__ Step best_step_wave(const Ctx &X, uint32_t j, int32_t
             if (__ballot(in && !fits)) break;                   // levels ascend
         }
     }
-    const unsigned long long best = wave_max_u64_rows(mine);
+    const uint32_t mine_sl = (uint32_t)(mine >> 32), mine_s = 0xFFFFFFFFu - (uint32_t)mine;
+    const uint32_t best = wave_max_u32_rows(mine_sl);
     Step out = {0.f, 0u, 0u};
-    if (best >> 32) {                                           // a positive slope
-        out.slope = __uint_as_float((uint32_t)(best >> 32));
-        out.tgt = 0xFFFFFFFFu - (uint32_t)best;
+    if (best) {                                                 // a positive slope; the lowest target that has it
+        out.slope = __uint_as_float(best);
+        out.tgt = wave_min_u32_rows(mine_sl == best ? mine_s : 0xFFFFFFFFu);
         if (PASS == 0) {
-            const unsigned long long holder = __ballot(mine == best);   // one lane: keys differ in the target
+            const unsigned long long holder = __ballot(mine_sl == best && mine_s == out.tgt);   // one lane
             out.dg = (uint32_t)__builtin_amdgcn_readlane((int)mine_dg, __builtin_amdgcn_readfirstlane((int)__ffsll((long long)holder) - 1));
         }
     }
@@ -906,9 +913,12 @@ __device__ __forceinline__ void tail_run(const Ctx &X, const JobState &st, uint3
             if (v > vf) { vf = v; jf = jl; }
             if (-v > vs) { vs = -v; js = jl; }
         }
-        unsigned long long kf = vf > 0.f ? key_of(vf, jf) : 0ull, ks = vs > 0.f ? key_of(vs, js) : 0ull;
-        kf = wave_max_u64_rows(kf);
-        ks = wave_max_u64_rows(ks);
+        // word by word: the wavefront's highest slope, then the lowest job among those that have it
+        const uint32_t bf = __float_as_uint(vf), bs = __float_as_uint(vs);
+        const uint32_t mf = wave_max_u32_rows(bf), ms = wave_max_u32_rows(bs);
+        unsigned long long kf = 0, ks = 0;
+        if (mf) kf = ((unsigned long long)mf << 32) | (0xFFFFFFFFu - wave_min_u32_rows(bf == mf ? jf : 0xFFFFFFFFu));
+        if (ms) ks = ((unsigned long long)ms << 32) | (0xFFFFFFFFu - wave_min_u32_rows(bs == ms ? js : 0xFFFFFFFFu));
         unsigned long long *both = red + 2 * turn;              // three copies in turn: the next one is cleared meanwhile
         turn = turn == 2 ? 0u : turn + 1u;
         if (lane == 0) {
