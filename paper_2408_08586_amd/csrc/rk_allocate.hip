@@ -47,10 +47,11 @@ constexpr int TAIL_THREADS = 1024;
 constexpr int HULL_THREADS = 256;
 constexpr int JOB_THREADS = 256;           // kernels with one thread per job
 constexpr uint32_t BINS = 4096;            // 12 key bits per histogram level
-// Where bin b is kept: the threads of find_cut take sixteen neighbouring bins each, and laid out like this their i-th
-// bins are neighbours (from plain order every load met a 16- to 32-way bank conflict in LDS, or as many cache lines as
-// lanes in memory).
-__device__ __forceinline__ uint32_t bin_at(uint32_t b) { return (b % (BINS / JOB_THREADS)) * JOB_THREADS + b / (BINS / JOB_THREADS); }
+// Where bin b is kept: the T threads of find_cut take BINS / T neighbouring bins each, and laid out like this their
+// i-th bins are neighbours (from plain order every load met a 16- to 32-way bank conflict in LDS, or as many cache lines
+// as lanes in memory).
+template <int T>
+__device__ __forceinline__ uint32_t bin_at(uint32_t b) { return (b % (BINS / T)) * T + b / (BINS / T); }
 
 struct HullBuf {             // walk steps, entry (k, job) at k*stride + job (job relative to the call's first job)
     uint32_t *key;           // float bits of the running-minimum slope; 0 from the end of the walk on
@@ -423,73 +424,82 @@ __global__ __launch_bounds__(HULL_THREADS) void k_hull_groups(Ctx X, JobState st
 struct Cut { int32_t bin; unsigned long long baseG, baseC; };
 
 struct CutScratch {
-    unsigned long long wave_g[JOB_THREADS / 64], wave_c[JOB_THREADS / 64];   // totals of the wavefronts
-    unsigned long long mask[JOB_THREADS / 64];                               // lanes that found a failing bin
-    int32_t cand[JOB_THREADS];
-    unsigned long long candG[JOB_THREADS], candC[JOB_THREADS];
+    uint32_t wave_g[16];                     // totals of the wavefronts
+    unsigned long long wave_c[16];
+    int32_t first[16];                       // their first thread with a failing bin (-1: none), and what lies above its bins
+    unsigned long long firstG[16], firstC[16];
 };
 
-// Workgroup-wide: the first JOB_THREADS threads do the work (thread t owns the
-// bins BINS-1-16t downwards), every thread of the workgroup must call it
-// (barriers) and gets the result.
+// Inclusive sums along the rows of 16 lanes, and over the whole wavefront (all 64 lanes active).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ void scan_add(uint32_t &g, unsigned long long &c) {
+    const uint32_t lo = rs_dpp_u32<CTRL, ROWS>(0u, (uint32_t)c), hi = rs_dpp_u32<CTRL, ROWS>(0u, (uint32_t)(c >> 32));
+    g += rs_dpp_u32<CTRL, ROWS>(0u, g);
+    c += ((unsigned long long)hi << 32) | lo;
+}
+__device__ __forceinline__ void row_scan(uint32_t &g, unsigned long long &c) {
+    scan_add<0x111, 0xF>(g, c); scan_add<0x112, 0xF>(g, c); scan_add<0x114, 0xF>(g, c); scan_add<0x118, 0xF>(g, c);
+}
+__device__ __forceinline__ void wave_scan(uint32_t &g, unsigned long long &c) {
+    row_scan(g, c);
+    scan_add<0x142, 0xA>(g, c);              // row_bcast:15 into rows 1 and 3
+    scan_add<0x143, 0xC>(g, c);              // row_bcast:31 into rows 2 and 3
+}
+__device__ __forceinline__ unsigned long long wave_lane_u64(unsigned long long x, uint32_t s) {
+    return ((unsigned long long)wave_lane_u32((uint32_t)(x >> 32), s) << 32) | wave_lane_u32((uint32_t)x, s);
+}
+
+// Workgroup-wide, T threads: thread t owns the BINS / T bins from BINS-1-t*BINS/T downwards; every thread must call it
+// (two barriers; the histogram may be written again after one more) and gets the result.  A chain on the way of every
+// pass: sums by data-parallel-primitive moves, and the bins of the one thread where the sum goes beyond the capacity
+// looked at by sixteen lanes of every wavefront (shuffled pairs, sixteen bins per thread one after the other and three
+// barriers took 3.3 to 4.2 us, this takes 1.4).  GPU costs of a round fit 32 bits (jobs * RK_MAX_G).
+template <int T>
 __device__ Cut find_cut(const uint32_t *__restrict__ hG, const unsigned long long *__restrict__ hC,
                         unsigned long long baseG, unsigned long long baseC, unsigned long long capG,
                         unsigned long long capC, CutScratch &S) {
-    constexpr uint32_t PER = BINS / JOB_THREADS, NW = JOB_THREADS / 64;
-    const uint32_t tid = threadIdx.x, lane = tid & 63u;
-    const bool part = tid < JOB_THREADS;
-    const uint32_t top = BINS - 1 - (part ? tid : 0u) * PER;
-    uint32_t vg[PER];
-    unsigned long long vc[PER];
-    unsigned long long sg = 0, sc = 0;
+    constexpr uint32_t PER = BINS / T, NW = T / 64;
+    static_assert(PER <= 16 && NW <= 16 && (unsigned long long)RK_MAX_JOBS_PER_ROUND * RK_MAX_G < (1ull << 32), "one row of lanes; 32-bit sums");
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    const uint32_t top = BINS - 1 - tid * PER;
+    uint32_t sg = 0;
+    unsigned long long sc = 0;
 #pragma unroll
-    for (uint32_t i = 0; i < PER; ++i) {
-        vg[i] = part ? hG[bin_at(top - i)] : 0u;
-        vc[i] = part ? hC[bin_at(top - i)] : 0ull;
-        sg += vg[i]; sc += vc[i];
-    }
-    // inclusive scan over the threads: inside the wavefront by shuffles, then the wavefronts' totals
-    unsigned long long ig = sg, ic = sc;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const unsigned long long ag = __shfl_up(ig, off, 64), ac = __shfl_up(ic, off, 64);
-        if ((int)lane >= off) { ig += ag; ic += ac; }
-    }
-    if (part && lane == 63u) { S.wave_g[tid >> 6] = ig; S.wave_c[tid >> 6] = ic; }
+    for (uint32_t i = 0; i < PER; ++i) { sg += hG[bin_at<T>(top - i)]; sc += hC[bin_at<T>(top - i)]; }
+    uint32_t ig = sg;
+    unsigned long long ic = sc;
+    wave_scan(ig, ic);
+    if (lane == 63u) { S.wave_g[wave] = ig; S.wave_c[wave] = ic; }
     __syncthreads();
-    unsigned long long allG = 0, allC = 0, beforeG = 0, beforeC = 0;
-#pragma unroll
-    for (uint32_t w = 0; w < NW; ++w) {
-        if (w < (tid >> 6)) { beforeG += S.wave_g[w]; beforeC += S.wave_c[w]; }
-        allG += S.wave_g[w]; allC += S.wave_c[w];
-    }
-    unsigned long long cg = baseG + beforeG + ig - sg, cc = baseC + beforeC + ic - sc;   // everything above this thread's bins
-    int32_t cand = -1;
-#pragma unroll
-    for (uint32_t i = 0; i < PER; ++i) {
-        if (cand < 0) {
-            if (cg + vg[i] > capG || cc + vc[i] > capC) cand = (int32_t)(top - i);
-            else { cg += vg[i]; cc += vc[i]; }
-        }
-    }
-    const unsigned long long found = __ballot(part && cand >= 0);
-    if (part) {
-        if (cand >= 0) { S.cand[tid] = cand; S.candG[tid] = cg; S.candC[tid] = cc; }
-        if (lane == 0) S.mask[tid >> 6] = found;
+    uint32_t wg = (lane & 15u) < NW ? S.wave_g[lane & 15u] : 0u;
+    unsigned long long wc = (lane & 15u) < NW ? S.wave_c[lane & 15u] : 0ull;
+    row_scan(wg, wc);
+    const uint32_t allG = wave_lane_u32(wg, 15u);
+    const unsigned long long allC = wave_lane_u64(wc, 15u);
+    const uint32_t w1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave);
+    const unsigned long long aboveG = baseG + (w1 ? wave_lane_u32(wg, w1 - 1u) : 0u) + (ig - sg);    // everything above this thread's bins
+    const unsigned long long aboveC = baseC + (w1 ? wave_lane_u64(wc, w1 - 1u) : 0ull) + (ic - sc);
+    const unsigned long long over = __ballot(aboveG + sg > capG || aboveC + sc > capC);
+    if (over ? lane == (uint32_t)__ffsll((long long)over) - 1u : lane == 0u) {
+        S.first[wave] = over ? (int32_t)tid : -1;
+        S.firstG[wave] = aboveG; S.firstC[wave] = aboveC;
     }
     __syncthreads();
-    Cut out;
-    out.bin = -1;
-    out.baseG = baseG + allG;
-    out.baseC = baseC + allC;
-    int32_t first = -1;                                   // the first thread (highest bins) with a failing bin
-#pragma unroll
-    for (uint32_t w = 0; w < NW; ++w) {
-        const unsigned long long m = S.mask[w];
-        if (first < 0 && m) first = (int32_t)(w * 64 + (uint32_t)__ffsll((long long)m) - 1u);
-    }
-    if (first >= 0) { out.bin = S.cand[first]; out.baseG = S.candG[first]; out.baseC = S.candC[first]; }
-    __syncthreads();
+    Cut out = {-1, baseG + allG, baseC + allC};
+    const unsigned long long with = __ballot(lane < NW && S.first[lane < NW ? lane : 0u] >= 0);
+    if (!with) return out;                                 // all bins fit
+    const uint32_t w0 = (uint32_t)__ffsll((long long)with) - 1u;
+    const int32_t first = S.first[w0];
+    const unsigned long long g0 = S.firstG[w0], c0 = S.firstC[w0];
+    const uint32_t at = BINS - 1u - (uint32_t)first * PER - (lane < PER ? lane : 0u);
+    const uint32_t vg = lane < PER ? hG[bin_at<T>(at)] : 0u;
+    const unsigned long long vc = lane < PER ? hC[bin_at<T>(at)] : 0ull;
+    ig = vg; ic = vc;
+    row_scan(ig, ic);
+    const uint32_t i0 = (uint32_t)__ffsll((long long)__ballot(lane < PER && (g0 + ig > capG || c0 + ic > capC))) - 1u;
+    out.bin = (int32_t)(BINS - 1u - (uint32_t)first * PER - i0);
+    out.baseG = g0 + wave_lane_u32(ig - vg, i0);
+    out.baseC = c0 + wave_lane_u64(ic - vc, i0);
     return out;
 }
 
@@ -501,7 +511,7 @@ __device__ __forceinline__ uint32_t walk_width(const Ctx &X, const HullBuf &H) {
 // Adds the steps of one job's walk to a histogram in LDS.  The walk is read
 // four steps at a time (all twelve loads go out together; positions past the
 // walk's end are inside the buffers and ignored).
-template <int PASS, int LEVEL>
+template <int PASS, int LEVEL, int T>
 __device__ __forceinline__ void hist_add(const Ctx &X, const HullBuf &H, uint32_t jrel, int32_t want_top, uint32_t *lg,
                                          unsigned long long *lc) {
     const uint32_t width = walk_width<PASS>(X, H);
@@ -526,8 +536,8 @@ __device__ __forceinline__ void hist_add(const Ctx &X, const HullBuf &H, uint32_
                 if ((int32_t)(key[u] >> 20) < want_top) return;   // keys only decrease along a walk
                 bin = (key[u] >> 8) & (BINS - 1);
             }
-            if (dg[u]) atomicAdd(&lg[bin_at(bin)], dg[u]);
-            if (dc[u]) atomicAdd(&lc[bin_at(bin)], dc[u]);
+            if (dg[u]) atomicAdd(&lg[bin_at<T>(bin)], dg[u]);
+            if (dc[u]) atomicAdd(&lc[bin_at<T>(bin)], dc[u]);
         }
     }
 }
@@ -549,14 +559,14 @@ __global__ __launch_bounds__(JOB_THREADS) void k_hist(Ctx X, JobState st, HullBu
         unsigned long long capG, capC;
         pass_caps<PASS>(X.R, cl, st, rnd, capG, capC);
         const size_t h0 = hist_at(rnd, PASS, 0);
-        const Cut c0 = find_cut(hist.g + h0, hist.c + h0, 0, 0, capG, capC, cs);
+        const Cut c0 = find_cut<JOB_THREADS>(hist.g + h0, hist.c + h0, 0, 0, capG, capC, cs);
         if (c0.bin < 0) return;                           // everything fits: no second level needed
         want_top = c0.bin;
     }
     for (uint32_t i = tid; i < BINS; i += JOB_THREADS) { lg[i] = 0; lc[i] = 0; }
     __syncthreads();
     const uint32_t jl = blockIdx.x * JOB_THREADS + tid;
-    if (J0 + jl < J1) hist_add<PASS, LEVEL>(X, H, J0 + jl - X.jb, want_top, lg, lc);
+    if (J0 + jl < J1) hist_add<PASS, LEVEL, JOB_THREADS>(X, H, J0 + jl - X.jb, want_top, lg, lc);
     __syncthreads();
     const size_t h = hist_at(rnd, PASS, LEVEL);
     for (uint32_t i = tid; i < BINS; i += JOB_THREADS) {
@@ -645,12 +655,12 @@ struct Selection { long long thr24; unsigned long long freeG, freeC; };
 __device__ Selection select_threshold(const uint32_t *h0g, const unsigned long long *h0c, const uint32_t *h1g,
                                       const unsigned long long *h1c, unsigned long long capG, unsigned long long capC,
                                       CutScratch &cs) {
-    const Cut c0 = find_cut(h0g, h0c, 0, 0, capG, capC, cs);
+    const Cut c0 = find_cut<JOB_THREADS>(h0g, h0c, 0, 0, capG, capC, cs);
     Selection sel;
     sel.thr24 = -1;
     unsigned long long usedG = c0.baseG, usedC = c0.baseC;
     if (c0.bin >= 0) {
-        const Cut c1 = find_cut(h1g, h1c, c0.baseG, c0.baseC, capG, capC, cs);
+        const Cut c1 = find_cut<JOB_THREADS>(h1g, h1c, c0.baseG, c0.baseC, capG, capC, cs);
         sel.thr24 = ((long long)c0.bin << 12) + (long long)c1.bin;   // c1.bin = -1: the whole of c0.bin fits as well
         usedG = c1.baseG; usedC = c1.baseC;
     }
@@ -807,16 +817,75 @@ __device__ __forceinline__ Step best_step_wave(const Ctx &X, uint32_t j, int32_t
     return out;
 }
 
-// LDS words tail_run needs beside its per-job scratch: the two key maxima in
-// three copies used in turn, the winner's two costs, and the CPU levels.
-constexpr int TAIL_RED_WORDS = 3 * 2 + 2 + RK_MAX_CPU_LEVELS / 2;
+// What a wavefront has read of the job with its best step: a lane per amount, in registers.
+struct TailJob {
+    uint32_t jl;             // the job (~0: none); with more than 64 amounts it is not kept
+    uint32_t g;              // GPU pass: GPUs of the lane's amount
+    float v, ref;            // value of the lane's amount; the job's reference throughput
+};
+
+// best_step_wave from what has been read: the same search, `at` = the amount the job is at.
+template <int PASS>
+__device__ __forceinline__ Step best_step_kept(const Ctx &X, const TailJob &T, uint32_t at, uint32_t ns, uint32_t g_held, uint32_t ci,
+                                               unsigned long long freeG, unsigned long long freeC) {
+    const GridDev &grid = X.grid;
+    const uint32_t lane = threadIdx.x & 63u;
+    const float cur = __uint_as_float(wave_lane_u32(__float_as_uint(T.v), at));
+    uint32_t mine = 0, dg = 0;
+    if (PASS == 0) {
+        const uint32_t g_cur = wave_lane_u32(T.g, at);
+        dg = T.g - g_cur;
+        if (lane > at && lane < ns && T.v > cur && dg <= freeG &&
+            cpu_cost(grid, ci, g_cur + dg) - cpu_cost(grid, ci, g_cur) <= freeC) {
+            float sl = (T.v - cur) / T.ref;
+            sl = sl / (float)dg;
+            mine = __float_as_uint(sl);
+        }
+    } else if (lane > at && lane < grid.n_cpu && T.v > cur) {
+        const unsigned long long dc = cpu_cost(grid, lane, g_held) - cpu_cost(grid, at, g_held);
+        if (dc <= freeC) {
+            float sl = (T.v - cur) / T.ref;
+            sl = sl / (float)dc;
+            mine = __float_as_uint(sl);
+        }
+    }
+    const uint32_t best = wave_max_u32_rows(mine);
+    Step out = {0.f, 0u, 0u};
+    if (best) {
+        out.slope = __uint_as_float(best);
+        out.tgt = (uint32_t)__ffsll((long long)__ballot(mine == best)) - 1u;       // the lowest lane is the smallest amount
+        out.dg = PASS == 0 ? wave_lane_u32(dg, out.tgt) : 0u;
+    }
+    return out;
+}
+
+// A barrier that orders LDS only: loads from memory that are on their way stay there.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// LDS words tail_run needs beside its per-job scratch: what every wavefront offers, in two copies used in turn, and the
+// CPU levels.
+struct TailOffer { uint32_t slope, job, dg, dc, bound, bound_job; };
+constexpr int TAIL_WAVES = TAIL_THREADS / 64;
+constexpr int TAIL_RED_WORDS = (2 * TAIL_WAVES * (int)sizeof(TailOffer) + RK_MAX_CPU_LEVELS * 4) / 8;
 
 // Workgroup of TAIL_THREADS threads; lds = max_jobs * 12 bytes of scratch, red =
 // TAIL_RED_WORDS words; at most KMAX * TAIL_THREADS jobs.  Starts from the
 // state k_apply / apply_job left in st.  Thread t owns jobs t, t +
 // TAIL_THREADS, ...: their cached steps stay in its registers, and only it
-// (and, for the winner's new search, its wavefront) touches their LDS entries,
-// so a step needs two barriers: one for the maxima, one for the winner's costs.
+// (and, for the winner's new search, its wavefront) touches their LDS entries.
+//
+// A step is a chain that nothing else hides, so what counts is its length: one
+// barrier, of LDS alone (every wavefront offers its best step with its costs,
+// and each finds the best offer for itself); a wavefront looks through its jobs
+// again only when its best step was taken or no longer fits; and what it needs
+// to find its best job's next step is on its way before that job wins (without
+// this 65 us instead of 56 for 256 rounds of 500 jobs, the CPU and GPU passes
+// of the selection; 31 instead of 29 for 10,000 jobs, where the nine turns are
+// mostly looks through all jobs).
 template <int PASS, int KMAX>
 __device__ __forceinline__ void tail_run(const Ctx &X, const JobState &st, uint32_t rnd, uint32_t J0, uint32_t J1,
                                          unsigned long long freeG, unsigned long long freeC, uint32_t max_jobs,
@@ -826,8 +895,8 @@ __device__ __forceinline__ void tail_run(const Ctx &X, const JobState &st, uint3
     uint16_t *ci = reinterpret_cast<uint16_t *>(gi + max_jobs);    // granted CPU level
     uint16_t *gh = ci + max_jobs;                                  // GPUs held (CPU pass); GPUs of a new step (GPU pass)
     float *found = reinterpret_cast<float *>(gh + max_jobs);       // slope of a new step on its way to the registers
-    unsigned long long *win = red + 6;                             // GPUs and CPUs the winning step costs
-    uint32_t *lvl = reinterpret_cast<uint32_t *>(red + 8);         // CPU levels, for indexing by lane
+    TailOffer *offers = reinterpret_cast<TailOffer *>(red);
+    uint32_t *lvl = reinterpret_cast<uint32_t *>(offers + 2 * TAIL_WAVES);   // CPU levels, for indexing by lane
 
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     const uint32_t nj = J1 - J0, jrel0 = J0 - X.jb;
@@ -851,7 +920,6 @@ __device__ __forceinline__ void tail_run(const Ctx &X, const JobState &st, uint3
         return;
     }
     if (tid < RK_MAX_CPU_LEVELS) lvl[tid] = grid.cpu_levels[tid];
-    if (tid < 6) red[tid] = 0ull;
     float slope[KMAX];                                             // cached best step of the thread's jobs:
     uint32_t dg[KMAX], dc[KMAX];                                   // > 0 exact, < 0 an upper bound, 0 none; its GPUs, CPUs
     {
@@ -895,41 +963,92 @@ __device__ __forceinline__ void tail_run(const Ctx &X, const JobState &st, uint3
         return ((unsigned long long)__float_as_uint(v) << 32) | (0xFFFFFFFFu - jl);
     };
     uint32_t turn = 0, moved = 0;                               // moved: bit k = the thread's k-th job took a step here
+    const uint32_t n_mem = grid.n_mem, n_rows = grid.n_cpu * n_mem, first_seg = X.tb.seg_off[X.jb];
+    TailJob kept = {~0u, 0u, 0.f, 1.f};
+    uint32_t seen = ~0u, seg_lo = 0, seg_hi = 0, kept_ns = 0;   // the job last looked up and where its GPU counts are
+    bool asked = false;
+    // The thread's best exact step and best bound, and the wavefront's: they stand until the step no longer fits, or a job
+    // of theirs took a step or was searched anew (a step that stops fitting below the thread's best one is not missed: as
+    // a bound it would be below that one too).
+    float vf = 0.f, vs = 0.f;
+    uint32_t jf = 0, js = 0, df = 0, cf = 0;
+    uint32_t mf = 0, ms = 0, jm = 0, jb = 0, dgm = 0, dcm = 0;
+    bool stale = true;
     for (;;) {
         if (PASS == 0 ? freeG == 0 : freeC == 0) break;         // nothing can fit any more
-        // the thread's best exact step and best bound: plain float compares (its jobs come in rising order, so the
-        // first of equal slopes is the lower job), the two keys are built once at the end
         const uint32_t roomG = freeG > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)freeG;
         const uint32_t roomC = freeC > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)freeC;
-        float vf = 0.f, vs = 0.f;
-        uint32_t jf = 0, js = 0;
+        stale = stale || (vf > 0.f && ((PASS == 0 && df > roomG) || cf > roomC));
+        if (__ballot(stale)) {
+            // plain float compares (a thread's jobs come in rising order, so the first of equal slopes is the lower job)
+            vf = 0.f; vs = 0.f;
+            jf = 0; js = 0; df = 0; cf = 0;
 #pragma unroll
-        for (int k = 0; k < KMAX; ++k) {
-            const uint32_t jl = tid + (uint32_t)k * TAIL_THREADS;
-            float v = slope[k];
-            const bool stopped = v > 0.f && ((PASS == 0 && dg[k] > roomG) || dc[k] > roomC);
-            v = stopped ? -v : v;
-            slope[k] = v;
-            if (v > vf) { vf = v; jf = jl; }
-            if (-v > vs) { vs = -v; js = jl; }
+            for (int k = 0; k < KMAX; ++k) {
+                const uint32_t jl = tid + (uint32_t)k * TAIL_THREADS;
+                float v = slope[k];
+                const bool stopped = v > 0.f && ((PASS == 0 && dg[k] > roomG) || dc[k] > roomC);
+                v = stopped ? -v : v;
+                slope[k] = v;
+                if (v > vf) { vf = v; jf = jl; df = dg[k]; cf = dc[k]; }
+                if (-v > vs) { vs = -v; js = jl; }
+            }
+            stale = false;
+            // word by word: the wavefront's highest slope, then the lowest job among those that have it
+            const uint32_t bf = __float_as_uint(vf), bs = __float_as_uint(vs);
+            mf = wave_max_u32_rows(bf);
+            ms = wave_max_u32_rows(bs);
+            if (mf) {
+                jm = wave_min_u32_rows(bf == mf ? jf : 0xFFFFFFFFu);
+                const uint32_t at = jm & 63u;                   // (thread t owns jobs t + k * TAIL_THREADS: a multiple of 64)
+                dgm = wave_lane_u32(df, at);
+                dcm = wave_lane_u32(cf, at);
+            }
+            if (ms) jb = wave_min_u32_rows(bs == ms ? js : 0xFFFFFFFFu);
         }
-        // word by word: the wavefront's highest slope, then the lowest job among those that have it
-        const uint32_t bf = __float_as_uint(vf), bs = __float_as_uint(vs);
-        const uint32_t mf = wave_max_u32_rows(bf), ms = wave_max_u32_rows(bs);
-        unsigned long long kf = 0, ks = 0;
-        if (mf) kf = ((unsigned long long)mf << 32) | (0xFFFFFFFFu - wave_min_u32_rows(bf == mf ? jf : 0xFFFFFFFFu));
-        if (ms) ks = ((unsigned long long)ms << 32) | (0xFFFFFFFFu - wave_min_u32_rows(bs == ms ? js : 0xFFFFFFFFu));
-        unsigned long long *both = red + 2 * turn;              // three copies in turn: the next one is cleared meanwhile
-        turn = turn == 2 ? 0u : turn + 1u;
-        if (lane == 0) {
-            if (kf) atomicMax(&both[0], kf);
-            if (ks) atomicMax(&both[1], ks);
+        turn ^= 1u;
+        if (lane == 0) offers[turn * TAIL_WAVES + wave] = TailOffer{mf, jm, dgm, dcm, ms, jb};
+        // What this wavefront will need should its best job win: where the job's counts are and, a turn later (in the first
+        // turn at once), amounts and values.  Nothing waits for the loads here: they are made by all lanes, even of what is
+        // the same for all, so that what comes through LDS does not wait for them, and the barrier is one for LDS alone.
+        if (mf && seen != jm) {
+            uint32_t slot = J0 + jm;
+            asm volatile("" : "+v"(slot));
+            slot = job_of(X, slot);
+            kept.ref = X.ref_thr[slot];
+            kept.jl = ~0u;
+            asked = seen == ~0u;
+            seg_lo = X.tb.seg_off[slot];
+            seg_hi = X.tb.seg_off[slot + 1];
+            seen = jm;
+        } else {
+            asked = mf != 0u && kept.jl == ~0u;
         }
-        if (tid == TAIL_THREADS - 1) { red[2 * turn] = 0ull; red[2 * turn + 1] = 0ull; }
-        __syncthreads();
-        kf = both[0];
-        ks = both[1];
-        if (ks > kf) {                                          // a bound could still win: make those exact
+        if (asked) {
+            const uint32_t s0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)seg_lo);
+            const uint32_t ns = (uint32_t)__builtin_amdgcn_readfirstlane((int)(seg_hi - seg_lo));
+            if (ns <= 64u || PASS == 1) {
+                const uint64_t base = (uint64_t)n_rows * (s0 - first_seg);
+                kept.jl = jm;
+                kept_ns = ns;
+                if (PASS == 0) {
+                    const uint32_t s = lane < ns ? lane : ns - 1u;
+                    kept.g = X.tb.seg_g[s0 + s];
+                    kept.v = X.curve_thr[base + (uint64_t)(ci[jm] * n_mem + n_mem - 1u) * ns + s];
+                } else {
+                    const uint32_t c = lane < grid.n_cpu ? lane : grid.n_cpu - 1u;
+                    kept.v = X.best_thr[base + (uint64_t)(c * n_mem + n_mem - 1u) * ns + (uint32_t)gi[jm]];
+                }
+            }
+        }
+        lds_barrier();
+        const TailOffer o = offers[turn * TAIL_WAVES + (lane & (TAIL_WAVES - 1))];   // every row of 16 lanes has all of them
+        const uint32_t top = (uint32_t)__builtin_amdgcn_readfirstlane((int)row_max_u32(o.slope));
+        const uint32_t jw = (uint32_t)__builtin_amdgcn_readfirstlane((int)row_min_u32(o.slope == top ? o.job : 0xFFFFFFFFu));
+        const uint32_t bound = (uint32_t)__builtin_amdgcn_readfirstlane((int)row_max_u32(o.bound));
+        const uint32_t jbound = (uint32_t)__builtin_amdgcn_readfirstlane((int)row_min_u32(o.bound == bound ? o.bound_job : 0xFFFFFFFFu));
+        if (bound && (bound > top || (bound == top && jbound < jw))) {   // a bound could still win: make those exact
+            const unsigned long long kf = top ? key_of(__uint_as_float(top), jw) : 0ull;
             uint32_t todo = 0;
 #pragma unroll
             for (int k = 0; k < KMAX; ++k) {
@@ -953,31 +1072,25 @@ __device__ __forceinline__ void tail_run(const Ctx &X, const JobState &st, uint3
                     dc[k] = need_cpus(gi[jl], ci[jl], tgt[jl], gh[jl]);
                 }
             }
+            stale = todo != 0u;
             continue;
         }
-        if (!(kf >> 32)) break;                                 // no positive slope left
-        const uint32_t jw = 0xFFFFFFFFu - (uint32_t)kf;
-        const uint32_t owner = jw % TAIL_THREADS;
-        const uint32_t kw = (uint32_t)__builtin_amdgcn_readfirstlane((int)(jw / TAIL_THREADS));   // same in all lanes
-        if (tid == owner) {
-            uint32_t a = 0, b = 0;
-#pragma unroll
-            for (int k = 0; k < KMAX; ++k) if ((uint32_t)k == kw) { a = dg[k]; b = dc[k]; }
-            win[0] = a;
-            win[1] = b;
-        }
-        __syncthreads();
-        if (PASS == 0) freeG -= win[0];
-        freeC -= win[1];
-        if (wave == owner / 64u) {                              // the owner's wavefront searches the winner's next step
+        if (!top) break;                                        // no positive slope left
+        const uint32_t owner = jw % TAIL_THREADS, kw = jw / TAIL_THREADS;
+        const uint32_t won = owner / 64u;                       // the wavefront whose offer it was
+        if (PASS == 0) freeG -= wave_lane_u32(o.dg, won);
+        freeC -= wave_lane_u32(o.dc, won);
+        if (wave == won) {                                      // ... finds the winner's next step
             int32_t g_i = gi[jw];
             uint32_t c_i = ci[jw];
             if (PASS == 0) g_i = (int32_t)tgt[jw]; else c_i = tgt[jw];
             const uint32_t held = PASS == 0 ? 0u : gh[jw];
-            const Step nx = best_step_wave<PASS>(X, J0 + jw, g_i, held, c_i, freeG, freeC);
+            const Step nx = kept.jl == jw ? best_step_kept<PASS>(X, kept, PASS == 0 ? (uint32_t)g_i : c_i, kept_ns, held, c_i, freeG, freeC)
+                                          : best_step_wave<PASS>(X, J0 + jw, g_i, held, c_i, freeG, freeC);
             if (tid == owner) {
                 if (PASS == 0) gi[jw] = (int16_t)g_i; else ci[jw] = (uint16_t)c_i;
                 moved |= 1u << kw;
+                stale = true;
                 tgt[jw] = (uint16_t)nx.tgt;
                 const uint32_t need = need_cpus(g_i, c_i, nx.tgt, PASS == 0 ? nx.dg : held);
 #pragma unroll
@@ -1047,25 +1160,34 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_select_small(Ctx X, uint32_t m
     rk_cluster cl;
     round_of(X.R, rnd, J0, J1, cl);
     const uint32_t nj = J1 - J0;
-    // a large round knows whether any job's CPU walk has a step at all (same in all threads)
-    const bool empty_pass = PASS == 1 && KMAX == TAIL_KMAX && st.cpu_steps[rnd] == 0u;
+    // whether any job's CPU walk has a step at all (same in all threads): a large round knows it
+    bool empty_pass = false;
+    if (PASS == 1) {
+        if (KMAX == TAIL_KMAX) empty_pass = st.cpu_steps[rnd] == 0u;
+        else {
+            bool any = false;
+            for (uint32_t jl = tid; jl < nj; jl += TAIL_THREADS) any |= H.key[J0 + jl - X.jb] != 0u;
+            empty_pass = __syncthreads_or(any) == 0;
+        }
+    }
     if (!empty_pass) {
         unsigned long long capG, capC;
         pass_caps<PASS>(X.R, cl, st, rnd, capG, capC);
         for (uint32_t i = tid; i < BINS; i += TAIL_THREADS) { hg[i] = 0; hc[i] = 0; }
         __syncthreads();
-        for (uint32_t jl = tid; jl < nj; jl += TAIL_THREADS) hist_add<PASS, 0>(X, H, J0 + jl - X.jb, 0, hg, hc);
+        for (uint32_t jl = tid; jl < nj; jl += TAIL_THREADS) hist_add<PASS, 0, TAIL_THREADS>(X, H, J0 + jl - X.jb, 0, hg, hc);
         __syncthreads();
-        const Cut c0 = find_cut(hg, hc, 0, 0, capG, capC, cs);
+        const Cut c0 = find_cut<TAIL_THREADS>(hg, hc, 0, 0, capG, capC, cs);
         Selection sel;
         sel.thr24 = -1;
         unsigned long long usedG = c0.baseG, usedC = c0.baseC;
         if (c0.bin >= 0) {                                      // uniform over the workgroup
+            __syncthreads();                                    // the last look at level 0
             for (uint32_t i = tid; i < BINS; i += TAIL_THREADS) { hg[i] = 0; hc[i] = 0; }
             __syncthreads();
-            for (uint32_t jl = tid; jl < nj; jl += TAIL_THREADS) hist_add<PASS, 1>(X, H, J0 + jl - X.jb, c0.bin, hg, hc);
+            for (uint32_t jl = tid; jl < nj; jl += TAIL_THREADS) hist_add<PASS, 1, TAIL_THREADS>(X, H, J0 + jl - X.jb, c0.bin, hg, hc);
             __syncthreads();
-            const Cut c1 = find_cut(hg, hc, c0.baseG, c0.baseC, capG, capC, cs);
+            const Cut c1 = find_cut<TAIL_THREADS>(hg, hc, c0.baseG, c0.baseC, capG, capC, cs);
             sel.thr24 = ((long long)c0.bin << 12) + (long long)c1.bin;
             usedG = c1.baseG; usedC = c1.baseC;
         }

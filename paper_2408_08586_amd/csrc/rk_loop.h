@@ -63,11 +63,14 @@ __device__ __forceinline__ uint32_t wave_min_u32_rows(uint32_t v) {
     v = rs_min_u32(v, rs_dpp_u32<0x143, 0xC>(0xFFFFFFFFu, v));                       // row_bcast:31 into rows 2 and 3
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
-__device__ __forceinline__ uint32_t wave_max_u32_rows(uint32_t v) {
+__device__ __forceinline__ uint32_t row_max_u32(uint32_t v) {
     v = rs_max_u32(v, rs_dpp_u32<0xB1, 0xF>(0u, v));
     v = rs_max_u32(v, rs_dpp_u32<0x4E, 0xF>(0u, v));
     v = rs_max_u32(v, rs_dpp_u32<0x141, 0xF>(0u, v));
-    v = rs_max_u32(v, rs_dpp_u32<0x140, 0xF>(0u, v));
+    return rs_max_u32(v, rs_dpp_u32<0x140, 0xF>(0u, v));
+}
+__device__ __forceinline__ uint32_t wave_max_u32_rows(uint32_t v) {
+    v = row_max_u32(v);
     v = rs_max_u32(v, rs_dpp_u32<0x142, 0xA>(0u, v));
     v = rs_max_u32(v, rs_dpp_u32<0x143, 0xC>(0u, v));
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
