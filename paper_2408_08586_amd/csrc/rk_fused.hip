@@ -13,24 +13,30 @@
 // Bound by the vector ALUs' issue slots.  Phase 1 has a lane per triple and
 // packs the triples with a usable offload plan, so that the lanes of phase 2
 // (a lane per packed triple and up to six CPU levels) are all busy; quotients
-// by the same divisor share its reciprocal.  The 128,000 jobs of 256 rounds:
-// 735 vector instructions per wavefront in its first form, 587 now, 808 ->
-// 672 us (vector ALUs active 85 % of the time); 10,000 jobs on the full grid
-// of 20 rows: 117 -> 85 us.
+// by the same divisor share its reciprocal.  Many jobs take a wavefront each
+// (DIRECT), whose lanes go from phase 1 straight to the CPU levels.  The
+// 128,000 jobs of 256 rounds took 808 us in the first form (a lane per triple
+// and level, a key per tier), 10,000 jobs on the full grid of 20 rows 117 us;
+// now 402 and 69 us.
 #include "rk_internal.h"
 #include "rk_model.h"
 
 namespace {
 
-constexpr int FUSED_THREADS = 256;
+// Every wavefront of a job loads it and works out the same indexes, so where the jobs fill the chip several times one
+// wavefront per job (DIRECT) costs the least: 402 us for 128,000 jobs with five rows against 672 with four wavefronts, 69
+// against 85 us for 10,000 jobs with twenty, 55 against 62 for 7,000, 41.6 against 43.4 for 4,500.  Below that it is the
+// single job that counts, and four wavefronts finish it sooner: 29.7 us against 32.1 for 3,000 jobs, 13 against 20 for 1,000.
+constexpr int FEW_JOBS = 256;
+constexpr uint32_t FUSED_MANY = 4096;
 constexpr uint32_t FUSED_FILL = 512;      // workgroups that occupy the chip: two per CU
 
 struct FusedLds {          // element counts of the dynamic LDS regions
     uint32_t max_nt, max_ns, rows_per_pass;
 };
 
-__host__ __device__ inline size_t fused_lds_bytes(const FusedLds &L) {
-    return 8 + (size_t)L.max_ns * 8 + (size_t)L.rows_per_pass * L.max_ns * 8 + (size_t)L.max_nt * 4 * 5 + (size_t)L.max_ns * 4;
+__host__ __device__ inline size_t fused_lds_bytes(const FusedLds &L, bool direct) {
+    return 8 + (size_t)L.max_ns * 8 + (size_t)L.rows_per_pass * L.max_ns * 8 + (size_t)L.max_nt * (direct ? 2 : 4 * 5) + (size_t)L.max_ns * 4;
 }
 
 // info word of a packed triple: usable offload options, first memory tier that holds them, segment, number of the triple
@@ -50,7 +56,10 @@ __device__ __forceinline__ unsigned long long scan_max_step(unsigned long long v
 }
 
 // blockIdx.y: which c_per_block CPU levels
-__global__ __launch_bounds__(FUSED_THREADS) void k_fused(JobDev jobs, TableDev tb, GridDev grid, rk_env env,
+// DIRECT: one wavefront, all rows in one pass; a lane goes from its triple straight to the CPU levels, nothing of a
+// triple is kept in LDS and no barrier is needed.
+template <int THREADS, bool DIRECT>
+__global__ __launch_bounds__(THREADS) void k_fused(JobDev jobs, TableDev tb, GridDev grid, rk_env env,
                                                          uint32_t jb, uint32_t option_mask, FusedLds L,
                                                          uint32_t c_per_block, uint32_t c_per_pass, uint32_t m_per_pass,
                                                          float *__restrict__ best_thr, uint32_t *__restrict__ best_plan,
@@ -66,7 +75,8 @@ __global__ __launch_bounds__(FUSED_THREADS) void k_fused(JobDev jobs, TableDev t
     float *t_topt = t_base1 + L.max_nt;
     float *t_toff = t_topt + L.max_nt;
     uint32_t *t_info = reinterpret_cast<uint32_t *>(t_toff + L.max_nt);
-    uint32_t *l_segg = t_info + L.max_nt;                                    // [max_ns] GPUs of the job's segments
+    uint32_t *l_segg = DIRECT ? reinterpret_cast<uint32_t *>(t_base0) : t_info + L.max_nt;   // [max_ns] GPUs of the job's segments
+    uint16_t *t_seg = reinterpret_cast<uint16_t *>(l_segg + L.max_ns);       // [max_nt] DIRECT: segment of a triple
 
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
     const uint32_t j = jb + blockIdx.x;
@@ -80,24 +90,42 @@ __global__ __launch_bounds__(FUSED_THREADS) void k_fused(JobDev jobs, TableDev t
 
     // per segment: nothing found yet, its GPU count, and its number in the info word of each of its triples
     if (tid == 0) n_packed = 0u;
-    for (uint32_t s = tid; s < ns; s += FUSED_THREADS) {
+    for (uint32_t s = tid; s < ns; s += THREADS) {
         seg_plain[s] = 0ull;
         l_segg[s] = tb.seg_g[s0 + s];
         const uint32_t first = tb.seg_first[s0 + s];
         const uint32_t last = s + 1 < ns ? tb.seg_first[s0 + s + 1] : nt;
-        for (uint32_t t = first; t < last; ++t) t_info[t] = s;
+        for (uint32_t t = first; t < last; ++t) {
+            if (DIRECT) t_seg[t] = (uint16_t)s; else t_info[t] = s;
+        }
     }
+    const float fb = (float)J.gbatch, inv_kswap = __builtin_amdgcn_rcpf(J.k_swap);
+    // The key of an offload plan at `levels` neighbouring CPU levels from ci on, in the rows from `slot` on.  Options in
+    // plan order: (z2,gc0) (z2,gc1) (z3,gc0) (z3,gc1); the stage does not change the value.
+    auto over_levels = [&](const Offload &O, uint32_t ok, uint32_t plan, uint32_t g, uint32_t ci, uint32_t c_stop,
+                           unsigned long long *slot, size_t stride) {
+        Triple Tb; Tb.b = fb;
+        const uint32_t plan0 = plan + (ok & 1u ? 9u : 13u), plan1 = plan + (ok & 2u ? 11u : 15u);
+        for (; ci < c_stop; ++ci, slot += stride) {
+            const float sw = swap_term(J, O, cpus_of(grid, ci, g));
+            const unsigned long long k0 = ok & 5u ? make_key(thr_offload(Tb, O, 0, sw), plan0) : 0ull;
+            const unsigned long long k1 = ok & 10u ? make_key(thr_offload(Tb, O, 1, sw), plan1) : 0ull;
+            atomicMax(slot, k0 > k1 ? k0 : k1);
+        }
+    };
+    if (DIRECT)
+        for (uint32_t i = tid; i < (c_end - c_begin) * n_mem * L.max_ns; i += THREADS) seg_best[i] = 0ull;
     __syncthreads();
 
     // phase 1: one lane per triple; a workgroup's turn packs behind the turn before, so what it overwrites of the
     // segment numbers has been read
-    for (uint32_t base = 0; base < nt; base += FUSED_THREADS) {
+    for (uint32_t base = 0; base < nt; base += THREADS) {
         const uint32_t tl = base + tid;
         uint32_t ok = 0, info = 0;
         Offload O = {};
         if (tl < nt) {
             const Triple T = triple_terms(J, env, tb.triples[t0 + tl]);
-            const uint32_t seg = t_info[tl];
+            const uint32_t seg = DIRECT ? t_seg[tl] : t_info[tl];
             // without offload: a stage above 0 does not change the throughput, so of those the lowest that fits
             unsigned long long k = 0;
 #pragma unroll
@@ -130,10 +158,12 @@ __global__ __launch_bounds__(FUSED_THREADS) void k_fused(JobDev jobs, TableDev t
                 if (tier == n_mem) ok = 0;
                 else {
                     O = offload_terms(J, env, T);
-                    info = info_word(ok, tier, seg, tl);
+                    if (!DIRECT) info = info_word(ok, tier, seg, tl);
+                    else over_levels(O, ok, tl * 16u, T.g, c_begin, c_end, seg_best + (size_t)tier * L.max_ns + seg, (size_t)n_mem * L.max_ns);
                 }
             }
         }
+        if (DIRECT) continue;
         // the turn's triples are read before any of them is overwritten by a packed one (all turns of more than one
         // workgroup's width; the last barrier also closes the phase)
         const unsigned long long with = __ballot(ok != 0);
@@ -154,7 +184,6 @@ __global__ __launch_bounds__(FUSED_THREADS) void k_fused(JobDev jobs, TableDev t
     // A pass keeps the keys of some rows in LDS: several CPU levels with all their tiers, or, when the rows of one
     // level do not fit, some tiers of one level (m_per_pass < n_mem only together with c_per_pass == 1).  Either
     // way the rows of a pass are neighbours in the output, starting at row c_lo * n_mem + m_lo.
-    const float fb = (float)J.gbatch, inv_kswap = __builtin_amdgcn_rcpf(J.k_swap);
     const float inv_np = __builtin_amdgcn_rcpf((float)np), inv_ns = __builtin_amdgcn_rcpf((float)ns);
     const uint32_t q = small_quot(lane, inv_ns), s_lane = lane - q * ns;       // phase 3: the lane's row in a group and its segment
     const uint32_t r_group = ns <= 64u && ns > 0 ? small_quot(64u, inv_ns) : 1u;   // rows that 64 lanes hold whole
@@ -165,38 +194,31 @@ __global__ __launch_bounds__(FUSED_THREADS) void k_fused(JobDev jobs, TableDev t
         const uint32_t m_cnt = m_hi - m_lo;
         const uint32_t pass_rows = (c_hi - c_lo) * m_cnt;
         const uint32_t row0 = c_lo * n_mem + m_lo;
-        for (uint32_t i = tid; i < pass_rows * L.max_ns; i += FUSED_THREADS) seg_best[i] = 0ull;
-        __syncthreads();
+        if (!DIRECT) {
+            for (uint32_t i = tid; i < pass_rows * L.max_ns; i += THREADS) seg_best[i] = 0ull;
+            __syncthreads();
 
-        // phase 2: one item per packed triple and up to six neighbouring CPU levels, which share what is read and unpacked
-        const uint32_t levels = c_hi - c_lo, parts = (levels + 5u) / 6u;
-        const uint32_t per_part = parts > 1 ? small_quot(levels + parts - 1u, __builtin_amdgcn_rcpf((float)parts)) : levels;
-        for (uint32_t i = tid; i < np * parts; i += FUSED_THREADS) {
-            const uint32_t part = parts > 1 ? small_quot(i, inv_np) : 0u, at = i - part * np;
-            const uint32_t info = t_info[at], ok = info & 15u, tier = (info >> 4) & 15u, seg = (info >> 8) & (INFO_TRIPLES - 1u);
-            const uint32_t plan = (info >> 20) * 16u;
-            if (tier >= m_hi) continue;
-            Offload O;
-            O.base[0] = t_base0[at]; O.base[1] = t_base1[at];
-            O.topt_num = t_topt[at]; O.Toff = t_toff[at]; O.inv_kswap = inv_kswap;
-            Triple Tb; Tb.b = fb;
-            const uint32_t g = l_segg[seg];
-            // options in plan order: (z2,gc0) (z2,gc1) (z3,gc0) (z3,gc1); the stage does not change the value
-            const uint32_t plan0 = plan + (ok & 1u ? 9u : 13u), plan1 = plan + (ok & 2u ? 11u : 15u);
-            uint32_t ci = c_lo + part * per_part;
-            const uint32_t c_stop = ci + per_part < c_hi ? ci + per_part : c_hi;
-            unsigned long long *slot = seg_best + (size_t)((ci - c_lo) * m_cnt + (tier > m_lo ? tier - m_lo : 0u)) * L.max_ns + seg;
-            for (; ci < c_stop; ++ci, slot += (size_t)m_cnt * L.max_ns) {
-                const float sw = swap_term(J, O, cpus_of(grid, ci, g));
-                const unsigned long long k0 = ok & 5u ? make_key(thr_offload(Tb, O, 0, sw), plan0) : 0ull;
-                const unsigned long long k1 = ok & 10u ? make_key(thr_offload(Tb, O, 1, sw), plan1) : 0ull;
-                atomicMax(slot, k0 > k1 ? k0 : k1);
+            // phase 2: one item per packed triple and up to six neighbouring CPU levels, which share what is read and unpacked
+            const uint32_t levels = c_hi - c_lo, parts = (levels + 5u) / 6u;
+            const uint32_t per_part = parts > 1 ? small_quot(levels + parts - 1u, __builtin_amdgcn_rcpf((float)parts)) : levels;
+            for (uint32_t i = tid; i < np * parts; i += THREADS) {
+                const uint32_t part = parts > 1 ? small_quot(i, inv_np) : 0u, at = i - part * np;
+                const uint32_t info = t_info[at], ok = info & 15u, tier = (info >> 4) & 15u, seg = (info >> 8) & (INFO_TRIPLES - 1u);
+                const uint32_t plan = (info >> 20) * 16u;
+                if (tier >= m_hi) continue;
+                Offload O;
+                O.base[0] = t_base0[at]; O.base[1] = t_base1[at];
+                O.topt_num = t_topt[at]; O.Toff = t_toff[at]; O.inv_kswap = inv_kswap;
+                const uint32_t ci = c_lo + part * per_part;
+                over_levels(O, ok, plan, l_segg[seg], ci, ci + per_part < c_hi ? ci + per_part : c_hi,
+                            seg_best + (size_t)((ci - c_lo) * m_cnt + (tier > m_lo ? tier - m_lo : 0u)) * L.max_ns + seg,
+                            (size_t)m_cnt * L.max_ns);
             }
+            __syncthreads();
         }
-        __syncthreads();
         if (m_cnt > 1) {                                          // what fits a tier fits the larger ones
             const uint32_t cols = (c_hi - c_lo) * ns;
-            for (uint32_t i = tid; i < cols; i += FUSED_THREADS) {
+            for (uint32_t i = tid; i < cols; i += THREADS) {
                 const uint32_t c = small_quot(i, inv_ns);
                 unsigned long long *col = seg_best + (size_t)c * m_cnt * L.max_ns + (i - c * ns), run = col[0];
                 for (uint32_t m = 1; m < m_cnt; ++m) {
@@ -213,7 +235,7 @@ __global__ __launch_bounds__(FUSED_THREADS) void k_fused(JobDev jobs, TableDev t
         // a segmented scan over packed keys (throughput bits, inverted segment index, GPUs of the segment: the lower
         // segment wins among equal throughputs), a row of more than 64 entries takes the last key of the 64 before
         // along, and the plan comes from the winning segment's merged key.
-        constexpr uint32_t WAVES = FUSED_THREADS / 64;
+        constexpr uint32_t WAVES = THREADS / 64;
         const uint32_t l16 = lane & 15u;
         for (uint32_t r0 = (tid >> 6) * r_group; r0 < pass_rows; r0 += WAVES * r_group) {
             const uint32_t rl = ns <= 64u ? r0 + q : r0;
@@ -280,12 +302,13 @@ int32_t rk_launch_fused(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_table *t
         if (m_per_pass < 1) return rk_fail(ctx, RK_ERR_UNSUPPORTED, "more than 6144 segments per job");
     }
     L.rows_per_pass = c_per_pass * m_per_pass;
-    const size_t lds = fused_lds_bytes(L);
+    const bool direct = je - jb >= FUSED_MANY && c_per_pass >= grid->n_cpu && m_per_pass >= grid->n_mem && L.max_nt <= INFO_TRIPLES;
+    const size_t lds = fused_lds_bytes(L, direct);
     if (L.max_nt > INFO_TRIPLES) return rk_fail(ctx, RK_ERR_UNSUPPORTED, "more than %u triples per job", INFO_TRIPLES);
     if (lds > 160 * 1024) return rk_fail(ctx, RK_ERR_UNSUPPORTED, "job too large for the fused kernel");
     if (lds > 64 * 1024 && !ctx->fused_lds_raised) {
-        RK_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(k_fused),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
+        for (const void *f : {reinterpret_cast<const void *>(k_fused<FEW_JOBS, false>), reinterpret_cast<const void *>(k_fused<64, true>)})
+            RK_HIP(ctx, hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
         ctx->fused_lds_raised = true;
     }
     // Few jobs leave most of the chip idle: their CPU levels are split over workgroups, down to four levels each (every
@@ -295,9 +318,11 @@ int32_t rk_launch_fused(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_table *t
     const uint32_t c_per_block = (grid->n_cpu + split - 1u) / split;
     split = (grid->n_cpu + c_per_block - 1u) / c_per_block;
     if (c_per_pass > c_per_block) c_per_pass = c_per_block;
-    k_fused<<<dim3(je - jb, split), FUSED_THREADS, lds, ctx->stream>>>(job_dev(jobs), table_dev(table), grid_dev(grid), *env, jb,
-                                                                      table->option_mask, L, c_per_block, c_per_pass, m_per_pass,
-                                                                      best_thr, best_plan, curve_thr, curve_plan, curve_g);
+    const dim3 blocks(je - jb, split);
+    auto *kernel = direct ? k_fused<64, true> : k_fused<FEW_JOBS, false>;
+    kernel<<<blocks, direct ? 64 : FEW_JOBS, lds, ctx->stream>>>(job_dev(jobs), table_dev(table), grid_dev(grid), *env, jb,
+                                                                     table->option_mask, L, c_per_block, c_per_pass, m_per_pass,
+                                                                     best_thr, best_plan, curve_thr, curve_plan, curve_g);
     RK_CHECK_LAUNCH(ctx, "k_fused");
     return RK_OK;
 }

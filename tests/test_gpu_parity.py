@@ -894,6 +894,28 @@ def test_fused_kernel_at_the_edges_of_its_split(gpu, n_jobs, n_cpu, n_mem, per_g
         run.close()
 
 
+@pytest.mark.parametrize("n_jobs", [4095, 4096])
+@pytest.mark.parametrize("n_cpu,n_mem,per_gpu", [(1, 1, 1), (5, 4, 1), (13, 1, 0), (3, 16, 0)])
+def test_fused_kernel_with_a_wavefront_per_job(gpu, n_jobs, n_cpu, n_mem, per_gpu):
+    """From 4,096 jobs on a wavefront takes a job (and more than 64 segments in turns): same bits as the separate calls."""
+    import dataclasses
+    base = workloads.stress(n_jobs=n_jobs)
+    base.ints[7] = (1, 5040, 1)                                # some 60 data-parallel sizes, more GPU counts than lanes
+    base.ints[8] = (1, 1, 1)
+    mem = np.array([2.0 ** (i - 2) * 8.0 for i in range(n_mem)], np.float32)
+    wl = dataclasses.replace(base, bounds=workloads.Bounds(g_max=600 if n_cpu * n_mem < 10 else 100),
+                             grid=workloads.Grid(np.arange(1, n_cpu + 1, dtype=np.uint32), per_gpu, mem, per_gpu))
+    run = gpu(wl)
+    run.enumerate()
+    thr, feas, n = run.eval(want_feas=False)
+    bt, bp, ns = run.best(thr)
+    ct, cp, cg = run.curves(bt, bp)
+    for f in (run.fused(), run.fused(want_best=False)):
+        for got, want in zip(f[:5], (bt, bp, ct, cp, cg)):
+            assert got is None or run.torch.equal(got[:ns], want[:ns])
+    run.close()
+
+
 def test_enumeration_at_the_job_counts_where_the_scan_changes(gpu, orc):
     """The last search to end scans up to 256 jobs, one workgroup below 2,048, all workgroups from there on; one context
     takes them in turn, with a refused call, wide jobs (more words than a job's first slot) and a sizing call in between."""
