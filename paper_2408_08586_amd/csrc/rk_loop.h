@@ -440,12 +440,11 @@ __device__ __forceinline__ RsShrunk rs_shrink_wave(const Args &A, uint32_t v, ui
     return out;
 }
 
-// rs_refresh_lanes for a whole wavefront; with keep_next the next steps also go to next[0] (GPUs) and next[1] (CPUs),
-// and whether the job is below its floor to *next_below
+// rs_refresh_lanes for a whole wavefront and a job that holds (gi, ci), as memory says; with keep_next the next steps also
+// go to next[0] (GPUs) and next[1] (CPUs), and whether the job is below its floor to *next_below
 template <class Args>
-__device__ __forceinline__ void rs_refresh_wave(const Args &A, uint32_t v, uint32_t lane, RsStep *next, uint32_t *next_below, bool keep_next) {
-    const int32_t gi = A.st.gi[v];
-    const uint32_t ci = A.st.ci[v];
+__device__ __forceinline__ void rs_refresh_wave_at(const Args &A, uint32_t v, int32_t gi, uint32_t ci, uint32_t lane, RsStep *next,
+                                                   uint32_t *next_below, bool keep_next) {
     const int32_t fl = rs_fl_s(A, v);
     const uint32_t so = A.X.tb.seg_off[v], ns = A.X.tb.seg_off[v + 1] - so;
     if (ns > 64u || (fl >= 0 && gi < fl)) {
@@ -464,6 +463,10 @@ __device__ __forceinline__ void rs_refresh_wave(const Args &A, uint32_t v, uint3
     A.ug[v] = ug.any ? ug.slope : 0.f; A.udg[v] = (uint32_t)ug.dg; A.udc_g[v] = ug.dc;
     A.uc[v] = uc.any ? uc.slope : 0.f; A.udc_c[v] = uc.dc;
     if (keep_next) { next[0] = ug; next[1] = uc; *next_below = 0u; }
+}
+template <class Args>
+__device__ __forceinline__ void rs_refresh_wave(const Args &A, uint32_t v, uint32_t lane, RsStep *next, uint32_t *next_below, bool keep_next) {
+    rs_refresh_wave_at(A, v, A.st.gi[v], A.st.ci[v], lane, next, next_below, keep_next);
 }
 
 // A workgroup barrier that orders LDS traffic only: every wavefront waits for its own LDS operations, not for its
@@ -516,7 +519,7 @@ __device__ __forceinline__ RsPick rs_pick_first(float g, float c, uint32_t j, ui
 // The two lowest give-slopes over all jobs, per resource, and the job of the lowest (the lower index among equal
 // values; none: 0xFFFFFFFF with both values infinite).  ds holds the slopes [2][n_jobs] (LDS).  All THREADS threads of
 // the workgroup call and all get the result in out[0] (GPUs) and out[1] (CPUs).  Every thread keeps the two lowest
-// of its own jobs; the lowest goes through a DPP minimum of packed keys (slope as a word that orders like it, job),
+// of its own jobs; the lowest goes through DPP minima, first of the slope as a word that orders like it, then of the job,
 // the second lowest is the minimum of what the threads hold once the lowest's owner puts its own second in.
 // sh_k and sh_s hold 2 * (WAVES + 1) entries each.
 struct RsMin { float m1, m2; uint32_t i1; };
@@ -546,16 +549,18 @@ __device__ __forceinline__ void rs_two_lowest(const float *ds, uint32_t n_jobs, 
     }
 #pragma unroll
     for (uint32_t r = 0; r < 2; ++r) {
-        const unsigned long long key = ia[r] == NONE ? ~0ull : ((unsigned long long)rs_ordered(a[r]) << 32) | ia[r];
-        const unsigned long long w = wave_min_u64_rows(key);
-        if (lane == 0) sh_k[r * (WAVES + 1) + wave] = w;
+        const uint32_t low = ia[r] == NONE ? NONE : rs_ordered(a[r]), low_w = wave_min_u32_rows(low);
+        const uint32_t who_w = wave_min_u32_rows(low == low_w ? ia[r] : NONE);
+        if (lane == 0) sh_k[r * (WAVES + 1) + wave] = ((unsigned long long)low_w << 32) | who_w;
     }
     rs_lds_barrier();
     if (wave == 0) {
 #pragma unroll
         for (uint32_t r = 0; r < 2; ++r) {
-            const unsigned long long w = wave_min_u64_rows(lane < WAVES ? sh_k[r * (WAVES + 1) + lane] : ~0ull);
-            if (lane == 0) sh_k[r * (WAVES + 1) + WAVES] = w;
+            const unsigned long long k = lane < WAVES ? sh_k[r * (WAVES + 1) + lane] : ~0ull;
+            const uint32_t l2 = (uint32_t)(k >> 32), low = wave_min_u32_rows(l2);
+            const uint32_t who = wave_min_u32_rows(l2 == low ? (uint32_t)k : NONE);
+            if (lane == 0) sh_k[r * (WAVES + 1) + WAVES] = ((unsigned long long)low << 32) | who;
         }
     }
     rs_lds_barrier();

@@ -339,6 +339,33 @@ def test_many_rounds_at_once(gpu, orc):
         run.close()
 
 
+@pytest.mark.parametrize("J", (1023, 1025, 4095, 4097))
+def test_job_counts_around_the_passes(gpu, orc, J):
+    """The passes over all jobs take 4 x 1,024 at a time; the preparation a wavefront per job up to 49,152 jobs of a call
+    and a thread per job above: the same round on either side of that line, against the oracle."""
+    import torch
+    import paper_2408_08586_amd as rk
+    rng = np.random.default_rng(98100 + J)
+    wl, tb, bt, bp, ct, cur_seg, cur_c, floor_seg, floor_c, state = random_round(rng, orc, J, 8)
+    run = gpu(wl)
+    run.enumerate()
+    want = orc.reschedule(wl.coef[:, 16], tb, wl.grid, wl.cluster, bt, bp, ct, cur_seg, cur_c, floor_seg, floor_c, state=state)
+    same(on_gpu(run, bt, bp, ct, wl.cluster, cur_seg, cur_c, floor_seg, floor_c, state), want)
+    i32 = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.int32)).to(run.device)
+    for n_rounds in (49152 // J, 49152 // J + 1):
+        assign, totals = rk.new_assign(n_rounds * J, run.device), run.f32(n_rounds)
+        stats = torch.zeros(4 * n_rounds, dtype=torch.int32, device=run.device)
+        rk.rk_reschedule_rounds(run.ctx, run.jobs.ref_thr, run.table.c, run.grid, [rk.make_cluster(wl.cluster)] * n_rounds,
+                                run.dev_f32(bt), run.dev_u32(bp), run.dev_f32(ct), i32(cur_seg), run.dev_u32(cur_c), assign, totals,
+                                state=torch.from_numpy(np.ascontiguousarray(state, dtype=np.uint8)).to(run.device),
+                                floor_seg=i32(floor_seg), floor_c=run.dev_u32(floor_c), stats=stats)
+        rk.rk_sync(run.ctx)
+        got_a, got_t, got_s = rk.assign_to_numpy(assign).reshape(n_rounds, J), totals.cpu().numpy(), stats.cpu().numpy().reshape(n_rounds, 4)
+        for r in (0, n_rounds - 1):
+            same((got_a[r], float(got_t[r]), int(got_s[r, 0])), want)
+    run.close()
+
+
 def test_argument_errors(gpu, orc):
     import paper_2408_08586_amd as rk
     wl = workloads.tiny()
