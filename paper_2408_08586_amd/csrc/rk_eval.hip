@@ -20,7 +20,12 @@ constexpr int TRIPLES_PER_BLOCK = EVAL_THREADS / 4;
 // the CPU level: they are laid out once per tier in LDS (1 KiB for the tile),
 // and a row's are stored by one of the four wavefronts, 16 bytes a lane,
 // where each wavefront stored 4 bytes a lane of every row.  3,333 jobs with
-// four tiers 237 -> 218 us, 2,500 with three 119 -> 115 us, no change at 300.
+// four tiers 237 -> 218 us, 2,500 with three 119 -> 115 us.  A workgroup of
+// few rows (few jobs, whose CPU levels are split) has nothing to share, and the
+// copy and its barrier cost more than they save: 150 jobs with three tiers,
+// three rows, 12.0 us from the copy and 10.9 lane by lane; 300, six rows, 18.2
+// and 17.8; 600, nine rows, 23.9 and 23.5; even at ten rows (900 jobs).
+constexpr uint32_t FEAS_DIRECT_ROWS = 9;
 template <bool WITH_FEAS>
 __global__ __launch_bounds__(EVAL_THREADS) void k_eval(JobDev jobs, TableDev tb, GridDev grid, rk_env env,
                                                        uint32_t jb, uint32_t option_mask, uint32_t c_per_block,
@@ -33,7 +38,10 @@ __global__ __launch_bounds__(EVAL_THREADS) void k_eval(JobDev jobs, TableDev tb,
     if (tile_lo >= nt) return;
     const uint32_t tl = tile_lo + (threadIdx.x >> 2);
     const bool active = tl < nt;
-    if (!WITH_FEAS && !active) return;
+    const uint32_t c_lo = blockIdx.z * c_per_block;
+    const uint32_t c_hi = c_lo + c_per_block < grid.n_cpu ? c_lo + c_per_block : grid.n_cpu;
+    const bool staged = WITH_FEAS && (c_hi - c_lo) * grid.n_mem > FEAS_DIRECT_ROWS;
+    if (!staged && !active) return;
     const uint32_t z = threadIdx.x & 3u;
     const uint32_t n_rows = grid.n_cpu * grid.n_mem;
     const uint64_t cbase = 16ull * n_rows * (uint64_t)(t0 - tb.triple_off[jb]);
@@ -75,7 +83,7 @@ __global__ __launch_bounds__(EVAL_THREADS) void k_eval(JobDev jobs, TableDev tb,
         }
     };
     const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
-    if (WITH_FEAS) {
+    if (staged) {
         for (uint32_t mi = 0; mi < grid.n_mem; ++mi) {
             uint32_t w0, w1;
             off_reasons(mi, w0, w1);
@@ -84,8 +92,6 @@ __global__ __launch_bounds__(EVAL_THREADS) void k_eval(JobDev jobs, TableDev tb,
         __syncthreads();                                             // (no store is on its way yet)
     }
 
-    const uint32_t c_lo = blockIdx.z * c_per_block;
-    const uint32_t c_hi = c_lo + c_per_block < grid.n_cpu ? c_lo + c_per_block : grid.n_cpu;
     for (uint32_t ci = c_lo; ci < c_hi; ++ci) {
         float off_thr[2] = {0.f, 0.f};
         if (any_off) {
@@ -104,7 +110,9 @@ __global__ __launch_bounds__(EVAL_THREADS) void k_eval(JobDev jobs, TableDev tb,
             const uint32_t row = ci * grid.n_mem + mi;
             const uint64_t at = cbase + ((uint64_t)row * nt + tile_lo) * 16;
             if (active) *reinterpret_cast<v4f *>(thr + at + (tl - tile_lo) * 16 + z * 4) = v;
-            if (WITH_FEAS && (row & 3u) == wave && tile_lo + lane < nt)
+            if (WITH_FEAS && !staged && active)
+                *reinterpret_cast<uint32_t *>(feas + at + (tl - tile_lo) * 16 + z * 4) = why_plain[0] | (w0 << 8) | (why_plain[1] << 16) | (w1 << 24);
+            if (staged && (row & 3u) == wave && tile_lo + lane < nt)
                 *reinterpret_cast<uint4 *>(feas + at + lane * 16) = reinterpret_cast<const uint4 *>(reasons + mi * EVAL_THREADS)[lane];
         }
     }

@@ -174,6 +174,24 @@ def test_enumerate_stress_sample(gpu, orc):
     run.close()
 
 
+@pytest.mark.parametrize("tiers", [1, 9, 10, 16])
+def test_eval_reasons_by_rows_per_workgroup(gpu, orc, tiers):
+    """The reason bytes are stored lane by lane up to nine rows of a workgroup, from a copy per tier in LDS above (few jobs
+    leave a workgroup one CPU level, so its rows are the tiers): both forms, on tables that end inside a tile."""
+    base = workloads.large()
+    mem = np.concatenate([[0.0], np.geomspace(4.0, 2048.0, 15)])[:tiers].astype(np.float32)
+    wl = workloads.Workload("reasons", base.coef[:37], base.ints[:37], workloads.Bounds(g_max=64, mu_mask=3),
+                            workloads.Grid(base.grid.cpu_levels, base.grid.cpu_mode, mem, base.grid.mem_mode), base.env, base.cluster)
+    run = gpu(wl)
+    run.enumerate()
+    ot = orc.enumerate_plans(wl.ints, wl.bounds)
+    assert (np.diff(ot.triple_off) % 64 != 0).any()
+    o_thr, o_reason = orc.eval_jobs(wl.coef, wl.ints, wl.bounds, ot, wl.grid, wl.env, n_threads=8)
+    thr, feas, n = run.eval()
+    check_thr(run.host(thr, n), run.host(feas, n), o_thr, o_reason)
+    run.close()
+
+
 @pytest.mark.parametrize("name", ["tiny", "paper_scale", "large"])
 def test_eval_and_selection_full_configs(gpu, orc, name):
     wl = workloads.CONFIGS[name]()
