@@ -234,7 +234,8 @@ __global__ __launch_bounds__(LEAD_THREADS) void k_scan_tiles(const uint32_t *__r
 }
 
 // self_scan != 0: the workgroup that ends last also scans the counts (n_jobs <= ENUM_SELF_SCAN = ENUM_THREADS, no leaders).
-// done0 = value of the counter of finished workgroups before this launch: it only ever counts up.
+// The counter of finished workgroups starts at zero and is left at zero by the one that ends last: what it has to be is
+// known on the device alone, whatever became of the calls before (one that ended in an error, one that was only recorded).
 template <int MODE>
 __global__ __launch_bounds__(ENUM_THREADS) void k_enumerate(
     const uint32_t *__restrict__ layers, const uint32_t *__restrict__ gbatch,
@@ -242,7 +243,7 @@ __global__ __launch_bounds__(ENUM_THREADS) void k_enumerate(
     uint32_t *cnt_t, uint32_t *cnt_s, uint32_t *__restrict__ park, uint32_t park_stride,
     const uint32_t *__restrict__ triple_off, const uint32_t *__restrict__ seg_off,
     uint32_t *__restrict__ triples, uint32_t *__restrict__ seg_g, uint32_t *__restrict__ seg_first,
-    uint32_t self_scan, uint32_t done0, ScanOut S) {
+    uint32_t self_scan, ScanOut S) {
     extern __shared__ uint32_t gmap[];                      // counting and search modes: bitmap of the GPU counts, word prefixes
     // Two arrays serve everything (a third would cost occupancy): `lists` holds the two divisor lists and later
     // the keys gathered by segment; `keys` holds the keys as they are found, then (once every thread has its keys
@@ -418,7 +419,8 @@ __global__ __launch_bounds__(ENUM_THREADS) void k_enumerate(
         ends = __hip_atomic_fetch_add(&S.totals[TOT_DONE], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
-    if (ends - done0 != gridDim.x - 1u) return;
+    if (ends != gridDim.x - 1u) return;
+    if (tid == 0) S.totals[TOT_DONE] = 0u;                      // (for the next launch)
     uint32_t ct = 0, cs = 0;
     if (tid < gridDim.x) {
         ct = __hip_atomic_load(&cnt_t[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -616,13 +618,13 @@ extern "C" int32_t rk_enumerate_plans(rk_ctx *ctx, const rk_jobs *jobs, const rk
     const bool tiles = share && job_blocks <= SCAN_MOST_TILES;
     uint32_t *tab = nullptr, *leader = nullptr;
     TileSum *sums = nullptr;
-    if (!ctx->scratch[SL_TOTALS]) {                           // never grows; the counter in it starts at zero
-        if ((rc = rk_scratch(ctx, SL_TOTALS, 16 * sizeof(uint32_t), (void **)&totals))) return rc;
+    // The counter in the totals is zero where the last call came to its end (set below); otherwise it is cleared first.
+    if ((rc = rk_scratch(ctx, SL_TOTALS, 16 * sizeof(uint32_t), (void **)&totals))) return rc;
+    if (!ctx->enum_clear) {
         k_zero_words<<<1, 64, 0, ctx->stream>>>(totals, 16u);
         RK_CHECK_LAUNCH(ctx, "k_zero_words");
-        ctx->enum_done = 0;
     }
-    totals = static_cast<uint32_t *>(ctx->scratch[SL_TOTALS]);
+    ctx->enum_clear = false;
     if (share) {
         if ((rc = rk_scratch(ctx, SL_ENUM_TAB, (size_t)tab_slots * 4, (void **)&tab))) return rc;
         if ((rc = rk_scratch(ctx, SL_ENUM_LEADER, ((size_t)J + 1) * 4, (void **)&leader))) return rc;
@@ -667,9 +669,8 @@ extern "C" int32_t rk_enumerate_plans(rk_ctx *ctx, const rk_jobs *jobs, const rk
     if (J > 0) {
         k_enumerate<MODE_COUNT><<<J, ENUM_THREADS, gmap_bytes, ctx->stream>>>(
             jobs->layers, jobs->gbatch, jobs->mbatch, *bounds, leader, cnt_t, cnt_s, park, park_stride,
-            nullptr, nullptr, nullptr, nullptr, nullptr, self_scan ? 1u : 0u, ctx->enum_done, S);
+            nullptr, nullptr, nullptr, nullptr, nullptr, self_scan ? 1u : 0u, S);
         RK_CHECK_LAUNCH(ctx, "k_enumerate<count>");
-        if (self_scan) ctx->enum_done += J;
     }
     if (share) {
         k_spread_counts<<<job_blocks, LEAD_THREADS, 0, ctx->stream>>>(leader, J, cnt_t, cnt_s, sums);
@@ -690,6 +691,7 @@ extern "C" int32_t rk_enumerate_plans(rk_ctx *ctx, const rk_jobs *jobs, const rk
         RK_CHECK_LAUNCH(ctx, "k_fill");
     }
     RK_HIP(ctx, hipEventSynchronize(ctx->counts_ev));
+    ctx->enum_clear = true;                                   // the kernels before the event have run
 
     if (h[TOT_ERR] & ERR_TOO_MANY_TRIPLES) return rk_fail(ctx, RK_ERR_UNSUPPORTED, "a job has more than %u triples", MAX_T);
     if (h[TOT_ERR] & ERR_TOO_MANY_DIVISORS) return rk_fail(ctx, RK_ERR_UNSUPPORTED, "a job has more than %u candidate d or p sizes", MAX_DIV);
@@ -719,7 +721,7 @@ extern "C" int32_t rk_enumerate_plans(rk_ctx *ctx, const rk_jobs *jobs, const rk
     if (J > 0 && !parked) {                                   // the parked keys were incomplete: search again
         k_enumerate<MODE_FILL_SEARCH><<<J, ENUM_THREADS, gmap_bytes, ctx->stream>>>(
             jobs->layers, jobs->gbatch, jobs->mbatch, *bounds, leader, cnt_t, cnt_s, park, park_stride,
-            off_t, off_s, table->triples, table->seg_g, table->seg_first, 0u, 0u, S);
+            off_t, off_s, table->triples, table->seg_g, table->seg_first, 0u, S);
         RK_CHECK_LAUNCH(ctx, "k_enumerate<fill>");
     }
     return RK_OK;

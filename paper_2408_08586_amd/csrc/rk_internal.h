@@ -21,7 +21,7 @@ struct rk_ctx {
     uint32_t *h_stage;                      // pinned staging for the plan-table offsets, grown on demand
     size_t h_stage_words;
     uint32_t park_stride;                   // enumeration: words per job between its two passes
-    uint32_t enum_done;                     // enumeration: the device's counter of finished searches, as the launches so far leave it
+    bool enum_clear;                        // enumeration: the device's counter of finished searches is known to be zero
     hipEvent_t counts_ev;                   // enumeration: the counts have reached the host (made on demand)
     hipStream_t sim_stream;                 // simulation: its own stream (a tick is captured as a graph), made on demand
     hipEvent_t sim_ev[4];                   // ... ordered after and before the context's stream with the first two; its batches of ticks

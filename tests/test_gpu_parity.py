@@ -963,3 +963,40 @@ def test_enumeration_at_the_job_counts_where_the_scan_changes(gpu, orc):
             assert e.value.code == rk.RK_ERR_UNSUPPORTED
             check(np.concatenate([kinds[:n], wide]), workloads.Bounds(g_max=20000, tp_max=2, pp_max=2))
     run.close()
+
+
+def test_enumeration_after_a_call_that_ended_in_an_error(gpu, orc):
+    """A call may launch its kernels and still end in an error, one that an earlier HIP call of the program left behind:
+    the next call knows nothing of that."""
+    import ctypes as C
+    import torch
+    import paper_2408_08586_amd as rk
+    with open("/proc/self/maps") as f:
+        hip = C.CDLL(next(line.split()[-1] for line in f if "libamdhip64" in line))
+    kinds = np.array([[l, b, m] for l in (12, 24, 40) for b in (32, 64) for m in (1, 2)], np.uint32)
+    bounds = workloads.Bounds(g_max=64)
+    run = gpu(workloads.tiny())
+
+    def made(n):
+        ints = kinds[np.arange(n) % len(kinds)]
+        return ints, rk.Jobs(np.ones((n, 17), np.float32), ints, run.device), rk.PlanTable(n, n * 256, n * 64, run.device)
+
+    def right(n):
+        ints, jobs, t = made(n)
+        rk.rk_enumerate_plans(run.ctx, jobs, rk.make_bounds(bounds), t.c)
+        got = dict(triple_off=rk.u32(t.triple_off), triples=t.unpack_triples(), seg_off=rk.u32(t.seg_off),
+                   seg_g=rk.u32(t.seg_g)[:t.n_segs], seg_first=rk.u32(t.seg_first)[:t.n_segs])
+        oracle_table_equal(got, orc.enumerate_plans(ints, bounds))
+
+    right(8)
+    for n in (8, 256, 300, 3000):
+        _, jobs, table = made(n)                                           # (torch would report the error as its own)
+        torch.cuda.synchronize()
+        assert hip.hipSetDevice(C.c_int(1 << 20)) != 0
+        with pytest.raises(rk.RkError) as e:
+            rk.rk_enumerate_plans(run.ctx, jobs, rk.make_bounds(bounds), table.c)
+        assert e.value.code == rk.RK_ERR_DEVICE
+        torch.cuda.synchronize()
+        for m in (5, 256, 1, 300, n):
+            right(m)
+    run.close()
