@@ -308,7 +308,8 @@ template <int THREADS>
 __device__ __forceinline__ void nd_finish(const NdArgs &A, uint32_t *np, uint32_t *off, uint32_t *parts, uint32_t *wish, float *mem, uint32_t *sh_scan) {
     constexpr uint32_t WAVES = THREADS / 64;
     __shared__ uint32_t sh_fit, sh_wide, sh_list;
-    __shared__ double sh_sum[WAVES];
+    __shared__ double sh_sum[ND_WAVES];
+    double *const share = reinterpret_cast<double *>(A.okey);                // [n_jobs] thr / ref_thr (the order has been served)
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     const uint32_t J = A.n_jobs, N = A.n_nodes, gpus = N * A.gpn;
     __syncthreads();
@@ -454,7 +455,6 @@ __device__ __forceinline__ void nd_finish(const NdArgs &A, uint32_t *np, uint32_
         if (tid == 0) A.place_off[J] = all;
     }
     __syncthreads();
-    double sum = 0.0;
     for (uint32_t h = tid; h < n_list; h += THREADS) {
         const uint32_t j = list[h];
         rk_assign out = {0u, 0u, 0.f, RK_NO_PLAN, 0.f};
@@ -466,7 +466,7 @@ __device__ __forceinline__ void nd_finish(const NdArgs &A, uint32_t *np, uint32_
             out.g = g; out.c = per_gpu * g; out.mem_gb = cost;
             out.plan = A.X.best_plan[slot_of(j, m)];
             out.thr = A.X.best_thr[slot_of(j, m)];
-            sum += (double)out.thr / (double)A.X.ref_thr[j];
+            share[j] = (double)out.thr / (double)A.X.ref_thr[j];
             const uint32_t to = A.place_off[j];
             if (P <= 8u) {                                   // few parts: this thread ranks them
                 for (uint32_t i = 0; i < P; ++i) {
@@ -497,13 +497,30 @@ __device__ __forceinline__ void nd_finish(const NdArgs &A, uint32_t *np, uint32_
             A.entries[to + rank] = rk_place_entry{node, k, per_gpu * k, (cost * (float)k) / (float)g};
         }
     }
+    // The total, in one order of its float64 additions whatever THREADS is and in whatever order the list was made:
+    // ND_THREADS partial sums over the jobs, then over 64 lanes, then one after the other.
+    constexpr uint32_t PER = ND_WAVES / WAVES;
+    double sum[PER];
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) sum += __shfl_xor(sum, o, 64);
-    if (lane == 0) sh_sum[wave] = sum;
+    for (uint32_t k = 0; k < PER; ++k) {
+        sum[k] = 0.0;
+        for (uint32_t j = tid + k * THREADS; j < J; j += ND_THREADS) {
+            const uint32_t some = np[j];
+            const double x = share[j];                       // (nothing of use where the job has no parts)
+            sum[k] += some ? x : 0.0;
+        }
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1)
+#pragma unroll
+        for (uint32_t k = 0; k < PER; ++k) sum[k] += __shfl_xor(sum[k], o, 64);
+#pragma unroll
+    for (uint32_t k = 0; k < PER; ++k) if (lane == 0) sh_sum[k * WAVES + wave] = sum[k];
     __syncthreads();
     if (tid == 0) {
         double s = 0.0;
-        for (uint32_t w = 0; w < WAVES; ++w) s += sh_sum[w];
+#pragma unroll
+        for (uint32_t w = 0; w < ND_WAVES; ++w) s += sh_sum[w];
         *A.total = (float)s;
     }
 }

@@ -187,6 +187,43 @@ def test_shapes_at_the_limits(gpu, orc):
         assert want is not None
 
 
+@pytest.mark.parametrize("J,gpn", [(1400, 8), (4000, 8), (1400, 128)])
+def test_the_total_is_added_in_one_order(gpu, orc, J, gpn):
+    """The total is a float64 sum in a fixed order, whichever kernel runs the loop: 1,024 partial sums of every 1,024th
+    job, their pairs within 64 lanes, then the 16 of these one after the other.  The quotients here are such that another
+    order gives another float32: the two smallest reach the sum only when they have been added to each other first."""
+    rng = np.random.default_rng(J + gpn)
+    wl, tb, bt, bp, ct, nodes, cur_seg, cur_c, prev, floor_seg, floor_c, state = node_round(rng, orc, J, 2, roomy=True, gpn=gpn,
+                                                                                            n_nodes=-(-J // gpn))
+    ref = np.full(J, 2.0 ** 100, np.float32)
+    ref[5], ref[1029], ref[261], ref[1285] = 2.0 ** -24, 1.0, 2.0 ** 29, 2.0 ** 29
+    wl.coef[:, 16] = ref
+    bt = np.ones_like(bt)
+    ct, _, _ = orc.curves(tb, wl.grid, bt, bp)
+    cur_seg, cur_c, state = np.zeros(J, np.int32), np.zeros(J, np.uint32), np.full(J, 2, np.uint8)   # all keep their GPU
+    ent = np.array([(j // gpn, 1, int(wl.grid.cpu_levels[0]), 0.0) for j in range(J)], orc.PLACE_DTYPE)
+    prev = (np.arange(J + 1, dtype=np.uint32), ent)
+    q = np.zeros(-(-J // 1024) * 1024)
+    q[:J] = 1.0 / ref.astype(np.float64)
+    part = np.zeros(1024)
+    for row in q.reshape(-1, 1024):
+        part = part + row
+    part = part.reshape(16, 64)
+    for off in (32, 16, 8, 4, 2, 1):
+        part = part + part[:, np.arange(64) ^ off]
+    want = 0.0
+    for w in part[:, 0]:
+        want += w
+    assert np.float32(want) == 2.0 ** 24 + 2
+    run = gpu(wl)
+    run.enumerate()
+    for _ in range(5):
+        a, _, _, total, stats = on_gpu(run, bt, bp, ct, (nodes[0], gpn, nodes[2], 1e6), cur_seg, cur_c, prev, None, None, state)
+        assert stats[4] == 0 and (a["g"] == 1).all()
+        assert total == np.float32(want)
+    run.close()
+
+
 def test_states_that_are_no_placement(gpu, orc):
     n_bad = 0
     for seed in range(40):
