@@ -36,15 +36,12 @@ struct FusedLds {          // element counts of the dynamic LDS regions
 };
 
 __host__ __device__ inline size_t fused_lds_bytes(const FusedLds &L, bool direct) {
-    return 8 + (size_t)L.max_ns * 8 + (size_t)L.rows_per_pass * L.max_ns * 8 + (size_t)L.max_nt * (direct ? 2 : 4 * 5) + (size_t)L.max_ns * 4;
+    return 8 + (size_t)L.max_ns * 8 + (size_t)L.rows_per_pass * L.max_ns * 8 + (size_t)L.max_nt * (direct ? 2 : 4 * 5 + 2) + (size_t)L.max_ns * 4;
 }
 
-// info word of a packed triple: usable offload options, first memory tier that holds them, segment, number of the triple
-constexpr uint32_t INFO_TRIPLES = 4096;    // more than rk_enumerate_plans ever finds for a job
-static_assert(RK_MAX_MEM_LEVELS <= 16 && RK_MAX_TRIPLES_PER_JOB <= INFO_TRIPLES, "fields of the info word");
-__device__ __forceinline__ uint32_t info_word(uint32_t ok, uint32_t tier, uint32_t seg, uint32_t tl) {
-    return ok | (tier << 4) | (seg << 8) | (tl << 20);
-}
+// info word of a packed triple: usable offload options, first memory tier that holds them, segment
+static_assert(RK_MAX_MEM_LEVELS <= 16, "fields of the info word");
+__device__ __forceinline__ uint32_t info_word(uint32_t ok, uint32_t tier, uint32_t seg) { return ok | (tier << 4) | (seg << 8); }
 
 // one step of an inclusive maximum scan along the wavefront: v = max(v, the value CTRL brings) where `take`
 template <int CTRL, int ROWS>
@@ -76,7 +73,7 @@ __global__ __launch_bounds__(THREADS) void k_fused(JobDev jobs, TableDev tb, Gri
     float *t_toff = t_topt + L.max_nt;
     uint32_t *t_info = reinterpret_cast<uint32_t *>(t_toff + L.max_nt);
     uint32_t *l_segg = DIRECT ? reinterpret_cast<uint32_t *>(t_base0) : t_info + L.max_nt;   // [max_ns] GPUs of the job's segments
-    uint16_t *t_seg = reinterpret_cast<uint16_t *>(l_segg + L.max_ns);       // [max_nt] DIRECT: segment of a triple
+    uint16_t *t_16 = reinterpret_cast<uint16_t *>(l_segg + L.max_ns);        // [max_nt] number of a packed triple; DIRECT: segment of a triple
 
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
     const uint32_t j = jb + blockIdx.x;
@@ -96,7 +93,7 @@ __global__ __launch_bounds__(THREADS) void k_fused(JobDev jobs, TableDev tb, Gri
         const uint32_t first = tb.seg_first[s0 + s];
         const uint32_t last = s + 1 < ns ? tb.seg_first[s0 + s + 1] : nt;
         for (uint32_t t = first; t < last; ++t) {
-            if (DIRECT) t_seg[t] = (uint16_t)s; else t_info[t] = s;
+            if (DIRECT) t_16[t] = (uint16_t)s; else t_info[t] = s;
         }
     }
     const float fb = (float)J.gbatch, inv_kswap = __builtin_amdgcn_rcpf(J.k_swap);
@@ -125,7 +122,7 @@ __global__ __launch_bounds__(THREADS) void k_fused(JobDev jobs, TableDev tb, Gri
         Offload O = {};
         if (tl < nt) {
             const Triple T = triple_terms(J, env, tb.triples[t0 + tl]);
-            const uint32_t seg = DIRECT ? t_seg[tl] : t_info[tl];
+            const uint32_t seg = DIRECT ? t_16[tl] : t_info[tl];
             // without offload: a stage above 0 does not change the throughput, so of those the lowest that fits
             unsigned long long k = 0;
 #pragma unroll
@@ -158,7 +155,7 @@ __global__ __launch_bounds__(THREADS) void k_fused(JobDev jobs, TableDev tb, Gri
                 if (tier == n_mem) ok = 0;
                 else {
                     O = offload_terms(J, env, T);
-                    if (!DIRECT) info = info_word(ok, tier, seg, tl);
+                    if (!DIRECT) info = info_word(ok, tier, seg);
                     else over_levels(O, ok, tl * 16u, T.g, c_begin, c_end, seg_best + (size_t)tier * L.max_ns + seg, (size_t)n_mem * L.max_ns);
                 }
             }
@@ -174,7 +171,7 @@ __global__ __launch_bounds__(THREADS) void k_fused(JobDev jobs, TableDev tb, Gri
         if (ok) {
             t_base0[at] = O.base[0]; t_base1[at] = O.base[1];
             t_topt[at] = O.topt_num; t_toff[at] = O.Toff;
-            t_info[at] = info;
+            t_info[at] = info; t_16[at] = (uint16_t)tl;
             // T.b and 1/k_swap are the same for every triple of the job
         }
     }
@@ -203,8 +200,8 @@ __global__ __launch_bounds__(THREADS) void k_fused(JobDev jobs, TableDev tb, Gri
             const uint32_t per_part = parts > 1 ? small_quot(levels + parts - 1u, __builtin_amdgcn_rcpf((float)parts)) : levels;
             for (uint32_t i = tid; i < np * parts; i += THREADS) {
                 const uint32_t part = parts > 1 ? small_quot(i, inv_np) : 0u, at = i - part * np;
-                const uint32_t info = t_info[at], ok = info & 15u, tier = (info >> 4) & 15u, seg = (info >> 8) & (INFO_TRIPLES - 1u);
-                const uint32_t plan = (info >> 20) * 16u;
+                const uint32_t info = t_info[at], ok = info & 15u, tier = (info >> 4) & 15u, seg = info >> 8;
+                const uint32_t plan = (uint32_t)t_16[at] * 16u;
                 if (tier >= m_hi) continue;
                 Offload O;
                 O.base[0] = t_base0[at]; O.base[1] = t_base1[at];
@@ -302,10 +299,10 @@ int32_t rk_launch_fused(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_table *t
         if (m_per_pass < 1) return rk_fail(ctx, RK_ERR_UNSUPPORTED, "more than 6144 segments per job");
     }
     L.rows_per_pass = c_per_pass * m_per_pass;
-    const bool direct = je - jb >= FUSED_MANY && c_per_pass >= grid->n_cpu && m_per_pass >= grid->n_mem && L.max_nt <= INFO_TRIPLES;
+    const bool direct = je - jb >= FUSED_MANY && c_per_pass >= grid->n_cpu && m_per_pass >= grid->n_mem;
     const size_t lds = fused_lds_bytes(L, direct);
-    if (L.max_nt > INFO_TRIPLES) return rk_fail(ctx, RK_ERR_UNSUPPORTED, "more than %u triples per job", INFO_TRIPLES);
-    if (lds > 160 * 1024) return rk_fail(ctx, RK_ERR_UNSUPPORTED, "job too large for the fused kernel");
+    if (fused_lds_bytes(L, false) > 160 * 1024)                 // (so a job's triples and segments number less than 2^16)
+        return rk_fail(ctx, RK_ERR_UNSUPPORTED, "job too large for the fused kernel");
     if (lds > 64 * 1024 && !ctx->fused_lds_raised) {
         for (const void *f : {reinterpret_cast<const void *>(k_fused<FEW_JOBS, false>), reinterpret_cast<const void *>(k_fused<64, true>)})
             RK_HIP(ctx, hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));

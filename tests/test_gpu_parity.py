@@ -934,6 +934,54 @@ def test_fused_kernel_with_a_wavefront_per_job(gpu, n_jobs, n_cpu, n_mem, per_gp
     run.close()
 
 
+@pytest.mark.parametrize("nt,ns,n_jobs", [(300, 40, 3), (4096, 100, 2), (4097, 100, 2), (4700, 12, 2), (2900, 4500, 2), (2700, 5200, 1), (4700, 1000, 4100)])
+def test_fused_kernel_on_a_table_wider_than_the_library_makes(gpu, nt, ns, n_jobs):
+    """A program may bring a plan table of its own, with more triples per job than enumeration finds (2,048), the same
+    triple in several places and segments without any: the curves are those of the evaluated candidates."""
+    import dataclasses
+    import paper_2408_08586_amd as rk
+    rng = np.random.default_rng(nt + ns)
+    base = workloads.stress(n_jobs=n_jobs)
+    wl = dataclasses.replace(base, env=dataclasses.replace(base.env, gpu_mem_cap=2e10),
+                             grid=workloads.Grid(np.array([1, 4], np.uint32), 1, np.array([64.0, 4096.0], np.float32), 0))
+    run = gpu(wl)
+    kinds = np.array([(d, t, p) for d in (1, 2, 4, 8) for t in (1, 2, 4, 8) for p in (1, 2)], np.uint32)   # every job may run these
+    kinds = kinds[np.argsort(kinds.prod(1), kind="stable")]
+    d, t, p = kinds[np.sort(rng.integers(0, len(kinds), size=nt))].T
+    cuts = np.append(0, np.flatnonzero(np.diff(d * t * p)) + 1)  # a segment's triples use the same number of GPUs
+    first = np.sort(np.append(cuts, rng.integers(0, nt, size=ns - len(cuts))))   # (of segments that begin together all but the last are empty)
+    run.table = table = rk.PlanTable(n_jobs, n_jobs * nt, n_jobs * ns, run.device)
+    off_t, off_s = (np.arange(n_jobs + 1) * n for n in (nt, ns))
+    for to, a in ((table.triple_off, off_t), (table.seg_off, off_s), (table.triples, np.tile(rk.pack_triples(d, t, p), n_jobs)),
+                  (table.seg_g, np.tile((d * t * p)[first], n_jobs)), (table.seg_first, np.tile(first, n_jobs))):
+        to.copy_(run.dev_u32(a))
+    table.h_triple_off[:], table.h_seg_off[:] = off_t, off_s
+    c = table.c
+    c.n_triples, c.n_segs, c.max_triples_per_job, c.max_segs_per_job, c.option_mask = n_jobs * nt, n_jobs * ns, nt, ns, 0xFFFF
+    f = run.fused()
+    bt, bp, ct, cp, cg = (run.host(x, f[5]).reshape(n_jobs, run.n_rows, ns) for x in f[:5])
+    last = np.append(first[1:], nt)
+    seg = np.repeat(np.arange(ns), (last - first) * 16)         # of every plan of a row
+    for j in sorted({0, n_jobs // 2, n_jobs - 1}):
+        thr, _, n = run.eval(j, j + 1, want_feas=False)
+        thr = run.host(thr, n).reshape(run.n_rows, nt * 16)
+        assert (thr > 0).any() and (thr[-1] != thr[0]).any()    # (offloaded plans among them)
+        for r in range(run.n_rows):
+            best = np.zeros(ns, np.float32)
+            np.maximum.at(best, seg, thr[r])
+            assert np.array_equal(bt[j, r], best)
+            plan = np.full(ns, rk.RK_NO_PLAN, np.uint32)        # the lowest plan that reaches it
+            hit = np.flatnonzero((thr[r] == best[seg]) & (best[seg] > 0))[::-1]
+            plan[seg[hit]] = hit
+            assert np.array_equal(bp[j, r].view(np.uint32), plan)
+            run_max = np.maximum.accumulate(best)
+            top = np.maximum.accumulate(np.where(best > np.append(np.float32(0), run_max[:-1]), np.arange(ns), -1))
+            assert np.array_equal(ct[j, r], run_max)
+            assert np.array_equal(cp[j, r].view(np.uint32), np.where(top >= 0, plan[top], rk.RK_NO_PLAN))
+            assert np.array_equal(cg[j, r], np.where(top >= 0, (d * t * p)[first][top], 0))
+    run.close()
+
+
 def test_enumeration_at_the_job_counts_where_the_scan_changes(gpu, orc):
     """The last search to end scans up to 256 jobs, one workgroup below 2,048, all workgroups from there on; one context
     takes them in turn, with a refused call, wide jobs (more words than a job's first slot) and a sizing call in between."""
