@@ -617,7 +617,9 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
     A.ds_g = sh_ds; A.ds_c = sh_ds + J + 1;
     if (tid == 0) sh_ds[J] = sh_ds[2 * J + 1] = INF;
     __syncthreads();
-    // the jobs' parts are booked (k_nd_prepare has checked them): a job per thread, or a wavefront where a job has many
+    // the jobs' parts are booked (k_nd_prepare has checked them): a job per thread, or a wavefront where a job has many.
+    // These are listed where the copy of the nodes will be; parts that fit the nodes are three GPUs or more a job, so a
+    // list that is too long says that the nodes are booked beyond what they have.
     auto book = [&](uint32_t j, const rk_place_entry &e) {
         const uint32_t slot = atomicAdd(&A.cnt[e.node], 1u);
         if (slot < gpn) A.res[e.node * gpn + slot] = (j << 16) | e.g;
@@ -639,13 +641,19 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
 #pragma unroll
         for (uint32_t k = 0; k < 4; ++k) {
             const uint32_t j = j0 + k * THREADS;
-            if (b[k] - a[k] > 2u) { keep[atomicAdd(&sh_list, 1u)] = j; continue; }      // (three parts are three GPUs: fewer jobs than GPUs)
+            if (b[k] - a[k] > 2u) {
+                const uint32_t to = atomicAdd(&sh_list, 1u);
+                if (to < A.nodes_words) keep[to] = j;
+                else bad |= 1u;
+                continue;
+            }
             if (a[k] < b[k]) book(j, e[k]);
             if (a[k] + 1u < b[k]) book(j, A.prev_entries[a[k] + 1u]);
         }
     }
     __syncthreads();
-    for (uint32_t i = wave; i < sh_list; i += WAVES) {
+    const uint32_t listed = sh_list < A.nodes_words ? sh_list : A.nodes_words;
+    for (uint32_t i = wave; i < listed; i += WAVES) {
         const uint32_t j = keep[i];
         const uint32_t a = A.prev_off[j], b = A.prev_off[j + 1];
         for (uint32_t x = a + lane; x < b; x += 64u) book(j, A.prev_entries[x]);

@@ -246,6 +246,30 @@ def test_states_that_are_no_placement(gpu, orc):
     assert n_bad > 20
 
 
+@pytest.mark.parametrize("J,gpn,n_nodes", [(300, 8, 8), (2000, 3, 100), (6000, 8, 40), (12288, 64, 64), (300, 128, 8)])
+def test_many_jobs_whose_parts_overbook_the_nodes(gpu, orc, J, gpn, n_nodes):
+    """Every job's parts are a placement by themselves, three GPUs on the same three nodes, and together they are more than
+    the nodes have: refused, however many such jobs there are, by each of the three kernels.  The next call starts afresh."""
+    rng = np.random.default_rng(J)
+    wl, tb, bt, bp, ct, nodes, _, _, _, _, _, _ = node_round(rng, orc, J, 4, roomy=True, gpn=gpn, n_nodes=n_nodes)
+    lvl = int(wl.grid.cpu_levels[0])
+    run = gpu(wl)
+    run.enumerate()
+    few = 1                                                    # (one job alone fits, and one in each three nodes)
+    for hold in (J, few, J - 1, n_nodes // 3):
+        cur_seg, cur_c = np.full(J, -1, np.int32), np.zeros(J, np.uint32)
+        cur_seg[:hold] = 2                                     # three GPUs
+        at = (lambda j: 0) if hold >= J - 1 else (lambda j: 3 * j)
+        ent = np.array([(at(j) + i, 1, lvl, 0.0) for j in range(hold) for i in range(3)], orc.PLACE_DTYPE)
+        prev = (np.minimum(np.arange(J + 1), hold).astype(np.uint32) * 3, ent)
+        state = np.full(J, 2, np.uint8)                        # (keep what they hold, or take no part)
+        want = orc.reschedule_nodes(wl.coef[:, 16], tb, wl.grid, *nodes, bt, bp, ct, cur_seg, cur_c, prev, None, None, state=state)
+        assert (want is None) == (hold >= J - 1)
+        print("jobs", J, "holding", hold, "nodes", nodes, flush=True)
+        same(on_gpu(run, bt, bp, ct, nodes, cur_seg, cur_c, prev, None, None, state), want)
+    run.close()
+
+
 @pytest.mark.parametrize("name", ["what_if", "stress"])
 def test_generated_rounds_from_a_running_state(gpu, orc, name):
     """The state a from-scratch round leaves, laid out on the nodes by first fit; then a tenth of the jobs leave and
