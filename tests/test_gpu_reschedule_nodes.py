@@ -125,6 +125,50 @@ def test_random_rounds_on_drawn_values(gpu, orc):
     assert n_moves > 1500 and n_spread > 100
 
 
+@pytest.mark.parametrize("gpn", [5, 9, 16, 17, 24, 33, 40, 63, 64, 65, 100, 128])
+def test_nodes_of_every_width(gpu, orc, gpn):
+    """Nodes of up to 64 GPUs are kept in LDS (16 residents to a row of lanes, eight at a time where they divide), wider ones
+    in memory: drawn rounds on nodes full of residents of one and two GPUs, and of jobs that reach over several nodes and
+    give GPUs on all of them."""
+    n_moves = n_shrinks = n_undone = n_full = n_spread = 0
+    for seed in range(16):
+        rng = np.random.default_rng(85000 + 100 * gpn + seed)
+        J, g_max = ((int(rng.integers(2 * gpn, 5 * gpn + 1)), 2 + seed % 3), (int(rng.integers(65, 200)), 22))[seed % 2]
+        n_nodes = max(3, J // gpn) if seed % 2 else None
+        wl, tb, bt, bp, ct, nodes, cur_seg, cur_c, prev, floor_seg, floor_c, state = node_round(
+            rng, orc, J, g_max, roomy=seed % 4 < 2, gpn=gpn, n_nodes=n_nodes)
+        if seed % 4 == 0:                                      # nodes full of jobs of one GPU, then whoever fits
+            free_g, free_c = [gpn] * nodes[0], [nodes[2]] * nodes[0]
+            off, ent = [0], []
+            for j in range(J):
+                cur_seg[j], cur_c[j] = (0, 0) if state[j] in (0, 2) else (-1, 0)
+                if floor_seg[j] > 0:
+                    floor_seg[j] = -1 if seed % 8 else floor_seg[j]
+                parts = first_fit(free_g, free_c, 1, int(wl.grid.cpu_levels[0])) if cur_seg[j] >= 0 else None
+                if parts is None:
+                    cur_seg[j] = -1
+                else:
+                    ent += [(n, k, int(wl.grid.cpu_levels[0]) * k, 0.0) for n, k in parts.items()]
+                off.append(len(ent))
+            prev = (np.array(off, np.uint32), np.array(ent, orc.PLACE_DTYPE))
+        on_node = np.bincount(prev[1]["node"], minlength=nodes[0]) if len(prev[1]) else np.zeros(1)
+        n_full += int((on_node == gpn).sum())
+        fs, fc = (floor_seg, floor_c) if seed % 3 else (None, None)
+        print("gpn", gpn, "seed", seed, "jobs", J, "nodes", nodes, flush=True)
+        want = orc.reschedule_nodes(wl.coef[:, 16], tb, wl.grid, *nodes, bt, bp, ct, cur_seg, cur_c, prev, fs, fc, state=state)
+        assert want is not None
+        run = gpu(wl)
+        run.enumerate()
+        got = on_gpu(run, bt, bp, ct, nodes, cur_seg, cur_c, prev, fs, fc, state)
+        run.close()
+        same(got, want)
+        n_moves, n_shrinks, n_undone = n_moves + int(got[4][0]), n_shrinks + int(got[4][2]), n_undone + int(got[4][3])
+        n_spread += int((np.diff(prev[0].astype(np.int64)) > 1).sum())
+    print(f"{n_moves} steps committed, {n_shrinks} shrinks, {n_undone} steps taken back, {n_full} nodes full of residents, "
+          f"{n_spread} jobs began on several nodes")
+    assert n_moves > 50 and n_shrinks > 20 and n_undone > 5 and n_full > 0 and n_spread > (20 if gpn < 40 else 8)
+
+
 def test_larger_drawn_rounds(gpu, orc):
     n_moves = 0
     for seed, J in enumerate([300, 1000, 1024, 1025, 2049, 3000] * 2):
