@@ -8,10 +8,12 @@
 // (g, t, p, v) in LDS: a bitmap of the GPU counts that occur gives every key
 // its segment (rank of its g among the distinct counts = a population count),
 // the keys are gathered by segment, and only the few keys of one segment are
-// compared with each other.  The counting pass also parks what it found, in
-// the table's own words, in a scratch buffer; after the exclusive scan of the
-// counts the fill pass (k_fill) only copies them into place, a wavefront per
-// job (the search is repeated only when the scratch buffer was too small).
+// compared with each other.  The counting pass also parks the triples it found,
+// in the table's own words, in a scratch buffer (512 words per job at first,
+// then the widest job's triples and a quarter more, at most 2,048); after the
+// exclusive scan of the counts the fill pass (k_fill) copies them into place, a
+// wavefront per job, and marks where a new GPU count begins (the search is
+// repeated only when the scratch buffer was too small).
 // Jobs whose searches would be identical (same layer count, same number of
 // micro-batches per step) share one: a hash table names a leader for each such
 // group, only leaders search, the others take the leader's counts and copy the
@@ -25,7 +27,8 @@
 // a copy); large ones by all workgroups of k_scan_tiles from the sums that
 // k_spread_counts leaves (128,000 jobs: 73 us with one workgroup, 4 us).  The
 // fill was 114 us for them while it decoded keys and counted segments in LDS
-// again, 28 us as a copy; 10,000 jobs: 14 -> 8 us and the scan 13 -> 4 us.
+// again, 31 us as a copy (28 us with the segments parked as well, for half as
+// much scratch again); 10,000 jobs: 14 -> 8 us and the scan 13 -> 4 us.
 #include <cstring>
 
 #include "rk_internal.h"
@@ -43,8 +46,8 @@ enum { MODE_COUNT = 0, MODE_FILL_SEARCH = 1 };
 // a job's word in cnt_t: its triples and the flags its search raised (so nothing has to be cleared between calls)
 constexpr uint32_t CNT_MASK = 0xFFFFFFu, CNT_FLAGS = 24u;
 static_assert(MAX_T <= CNT_MASK, "the count and the flags share a word");
-// a job's slot in the parked words: `stride` triples, then stride / 2 segments as (GPUs | first triple << 16)
-__host__ __device__ inline size_t park_words(uint32_t stride) { return (size_t)stride + stride / 2u; }
+// GPUs of a triple's word: a segment of a job's table begins where they differ from those of the word before
+__device__ __forceinline__ uint32_t word_gpus(uint32_t w) { return __umul24(w & 0xFFFFu, (w >> 18) & 0xFFFu) << ((w >> 16) & 3u); }
 
 // What the scan of the counts leaves: offsets in the table, totals for the fill pass, and both for the host.
 struct ScanOut {
@@ -389,18 +392,20 @@ __global__ __launch_bounds__(ENUM_THREADS) void k_enumerate(
     uint32_t nseg;
     uint32_t sidx = block_excl_scan(starts, scan_tmp, &nseg);
 
-    // the job's words go to its place in the table or, if they fit, to its slot of the parked words
-    const bool room = MODE != MODE_COUNT || (cnt <= park_stride && nseg <= park_stride / 2u);
-    const size_t at = MODE == MODE_COUNT ? (size_t)j * park_words(park_stride) : triple_off[j];
+    // the job's words go to its place in the table or, if they fit, to its slot of the parked words (k_fill finds the
+    // segments again)
+    const bool room = MODE != MODE_COUNT || cnt <= park_stride;
+    const size_t at = MODE == MODE_COUNT ? (size_t)j * park_stride : triple_off[j];
     const uint32_t s0 = MODE == MODE_COUNT ? 0u : seg_off[j];
     for (uint32_t i = lo; i < hi && room; ++i) {
         const uint32_t k = fin[i];
         const uint32_t g = k >> 16, lt = (k >> 14) & 3u, p = (k >> 2) & 0xFFFu, v = k & 3u;
         const uint32_t d = g / (p << lt), word = d | (lt << 16) | (p << 18) | (v << 30);
-        if (MODE == MODE_COUNT) park[at + i] = word; else triples[at + i] = word;
+        if (MODE == MODE_COUNT) { park[at + i] = word; continue; }
+        triples[at + i] = word;
         if (i == 0 || g != (fin[i - 1] >> 16)) {
-            if (MODE == MODE_COUNT) park[at + park_stride + sidx] = g | (i << 16);
-            else { seg_g[s0 + sidx] = g; seg_first[s0 + sidx] = i; }
+            seg_g[s0 + sidx] = g;
+            seg_first[s0 + sidx] = i;
             ++sidx;
         }
     }
@@ -451,6 +456,7 @@ __global__ __launch_bounds__(ENUM_THREADS) void k_enumerate(
 // The table from the parked words, a wavefront per job.  Launched before the host has seen the totals: nothing is
 // written unless the counting pass raised no flag and the table takes everything (the same in all threads).
 constexpr int FILL_THREADS = 256;
+constexpr uint32_t FILL_AHEAD = 4;         // loads of a lane in flight: jobs mostly have fewer than 256 triples (with two 32 us where this takes 31)
 
 __global__ __launch_bounds__(FILL_THREADS) void k_fill(uint32_t n_jobs, const uint32_t *__restrict__ leader,
                                                        const uint32_t *__restrict__ park, uint32_t park_stride,
@@ -463,13 +469,33 @@ __global__ __launch_bounds__(FILL_THREADS) void k_fill(uint32_t n_jobs, const ui
     const uint64_t nt = ((uint64_t)totals[TOT_NT_HI] << 32) | totals[TOT_NT_LO];
     const uint64_t ns = ((uint64_t)totals[TOT_NS_HI] << 32) | totals[TOT_NS_LO];
     if (j >= n_jobs || totals[TOT_ERR] != 0u || nt > 0xFFFFFFFFull || nt > cap_triples || ns > cap_segs) return;
-    const uint32_t t0 = triple_off[j], t_n = triple_off[j + 1] - t0, s0 = seg_off[j], s_n = seg_off[j + 1] - s0;
-    const uint32_t *from = park + (size_t)(leader ? leader[j] : j) * park_words(park_stride);   // parked by the job that searched
-    for (uint32_t i = lane; i < t_n; i += 64) triples[(size_t)t0 + i] = from[i];
-    for (uint32_t i = lane; i < s_n; i += 64) {
-        const uint32_t w = from[park_stride + i];
-        seg_g[(size_t)s0 + i] = w & 0xFFFFu;
-        seg_first[(size_t)s0 + i] = w >> 16;
+    const uint32_t t0 = triple_off[j], t_n = triple_off[j + 1] - t0, s0 = seg_off[j];
+    const uint32_t *from = park + (size_t)(leader ? leader[j] : j) * park_stride;   // parked by the job that searched
+    uint32_t *const to_t = triples + t0, *const to_g = seg_g + s0, *const to_f = seg_first + s0;
+    uint32_t seg = 0, last = 0;                            // segments so far, GPUs of the word before (no word has 0)
+    for (uint32_t base = 0; base < t_n; base += 64 * FILL_AHEAD) {
+        uint32_t w[FILL_AHEAD];
+#pragma unroll
+        for (uint32_t u = 0; u < FILL_AHEAD; ++u) {
+            const uint32_t i = base + 64 * u + lane;
+            w[u] = i < t_n ? from[i] : 0u;
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < FILL_AHEAD; ++u) {
+            if (base + 64 * u >= t_n) break;
+            const uint32_t i = base + 64 * u + lane, g = word_gpus(w[u]);
+            const uint32_t before = (uint32_t)__builtin_amdgcn_update_dpp((int)last, (int)g, 0x138, 0xF, 0xF, false);   // wave_shr:1
+            const bool in = i < t_n, starts = in && g != before;
+            const unsigned long long m = __ballot(starts);
+            if (in) to_t[i] = w[u];
+            if (starts) {
+                const uint32_t s = seg + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+                to_g[s] = g;
+                to_f[s] = i;
+            }
+            seg += (uint32_t)__popcll(m);
+            last = (uint32_t)__builtin_amdgcn_readlane((int)g, 63);
+        }
     }
 }
 
@@ -633,7 +659,7 @@ extern "C" int32_t rk_enumerate_plans(rk_ctx *ctx, const rk_jobs *jobs, const rk
     // one slot per job for the parked words: as wide as the widest job seen so far, or a first guess
     if (ctx->park_stride == 0) ctx->park_stride = 512;
     const uint32_t park_stride = ctx->park_stride;
-    if ((rc = rk_scratch(ctx, SL_PARK, ((size_t)J * park_words(park_stride) + 1) * 4, (void **)&park))) return rc;
+    if ((rc = rk_scratch(ctx, SL_PARK, ((size_t)J * park_stride + 1) * 4, (void **)&park))) return rc;
     const bool fill = table->triples != nullptr;              // otherwise a sizing call
     if (fill && (!table->triple_off || !table->seg_off || !table->seg_g || !table->seg_first))
         return rk_fail(ctx, RK_ERR_INVALID_ARG, "table buffer is null");
@@ -704,10 +730,9 @@ extern "C" int32_t rk_enumerate_plans(rk_ctx *ctx, const rk_jobs *jobs, const rk
     table->max_segs_per_job = h[TOT_MAX_S];
     const bool parked = !(h[TOT_ERR] & ERR_PARK_FULL);
     if (!parked) {                                            // next time the slots will be wide enough
-        uint32_t want = h[TOT_MAX_T] > 2 * h[TOT_MAX_S] ? h[TOT_MAX_T] : 2 * h[TOT_MAX_S];
-        want += want / 4;
+        uint32_t want = h[TOT_MAX_T] + h[TOT_MAX_T] / 4;
         want = (want + 63u) & ~63u;
-        ctx->park_stride = want > 2 * MAX_T ? 2 * MAX_T : want;
+        ctx->park_stride = want > MAX_T ? MAX_T : want;
     }
 
     if (!fill) return RK_OK;

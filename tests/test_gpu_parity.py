@@ -1013,6 +1013,42 @@ def test_enumeration_at_the_job_counts_where_the_scan_changes(gpu, orc):
     run.close()
 
 
+@pytest.mark.parametrize("wide", [0, 1])
+def test_scratch_of_an_enumeration(gpu, orc, wide):
+    """What the counting pass parks takes a word per triple: 512 words per job at first, and the widest job's triples and a
+    quarter more (2,048 words at most) once there was a wider one, however many segments it had."""
+    import torch
+    import paper_2408_08586_amd as rk
+    n = 128000 if not wide else 40000
+    kinds = np.array([[l, b, m] for l in (12, 24, 40) for b in (32, 64) for m in (1, 2)], np.uint32)
+    ints = kinds[np.arange(n) % len(kinds)]
+    if wide:
+        ints[7] = (2, 21621600, 1)                         # more than half as many segments as triples
+    bounds = workloads.Bounds(g_max=20000, tp_max=1)
+    run = gpu(workloads.tiny())
+    jobs = rk.Jobs(np.ones((n, 17), np.float32), ints, run.device)
+    t = rk.PlanTable(n, n * 64, n * 64, run.device)
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    for _ in range(3):
+        rk.rk_enumerate_plans(run.ctx, jobs, rk.make_bounds(bounds), t.c)
+    torch.cuda.synchronize()
+    took = before - torch.cuda.mem_get_info()[0]
+    most = int(t.c.max_triples_per_job)
+    assert (most > 512) == bool(wide) and (not wide or int(t.c.max_segs_per_job) * 2 > most)
+    words = min(2048, most * 5 // 4 + 64) if wide else 512
+    print(f"{n} jobs, up to {most} triples and {t.c.max_segs_per_job} segments: {took / 2 ** 20:.0f} MiB")
+    # besides: counts, offsets, leaders, their hash table (at most 4 words a job), the copy for the host; a quarter more of each
+    assert n * words * 4 <= took <= n * (words + 16) * 4 * 5 // 4 + (32 << 20)
+    off_t, off_s, triples = rk.u32(t.triple_off), rk.u32(t.seg_off), t.unpack_triples()
+    for at in (0, n // 2 // 12 * 12, n // 12 * 12 - 24):    # some of the jobs (12 kinds, one after the other)
+        a, b = (int(off_t[at]), int(off_t[at + 24])), (int(off_s[at]), int(off_s[at + 24]))
+        got = dict(triple_off=off_t[at:at + 25] - off_t[at], triples=triples[a[0]:a[1]], seg_off=off_s[at:at + 25] - off_s[at],
+                   seg_g=rk.u32(t.seg_g)[b[0]:b[1]], seg_first=rk.u32(t.seg_first)[b[0]:b[1]])
+        oracle_table_equal(got, orc.enumerate_plans(ints[at:at + 24], bounds))
+    run.close()
+
+
 def test_enumeration_after_a_call_that_ended_in_an_error(gpu, orc):
     """A call may launch its kernels and still end in an error, one that an earlier HIP call of the program left behind:
     the next call knows nothing of that."""
