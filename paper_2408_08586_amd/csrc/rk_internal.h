@@ -25,6 +25,7 @@ struct rk_ctx {
     hipEvent_t counts_ev;                   // enumeration: the counts have reached the host (made on demand)
     hipStream_t sim_stream;                 // simulation: its own stream (a tick is captured as a graph), made on demand
     hipEvent_t sim_ev[4];                   // ... ordered after and before the context's stream with the first two; its batches of ticks
+    bool sim_failed;                        // ... the last one ended in an error: its work may still be on the way
     bool fused_lds_raised;                  // fused kernel: its dynamic LDS limit has been raised for this context
     bool loop_lds_raised;                   // the Schedule loop over totals: likewise
     bool nodes_lds_raised;                  // the Schedule loop over nodes: likewise

@@ -278,7 +278,10 @@ extern "C" int32_t rk_simulate(rk_ctx *ctx, const float *ref_thr, const rk_plan_
     void *h_tick;
     RK_HIP(ctx, hipHostGetDevicePointer(&h_tick, ctx->h_pinned + H_TICK, 0));
     A.h_tick = static_cast<uint32_t *>(h_tick);
-    // (of earlier simulations only one of a single tick may still run: it can put 1 there, which ends no loop below)
+    // Of earlier simulations one of a single tick may still run: it can put 1 there, which ends no loop below.  One that
+    // ended in an error may have left more than that on its way.
+    if (ctx->sim_failed && ctx->sim_stream) RK_HIP(ctx, hipStreamSynchronize(ctx->sim_stream));
+    ctx->sim_failed = true;                                    // until this one has come to its end
     __atomic_store_n(ctx->h_pinned + H_TICK, 0u, __ATOMIC_RELEASE);
     A.S.owed = (double *)take(n8);
     double *s_held = (double *)take(n8), *s_prog = (double *)take(n8), *s_fin = (double *)take(n8);
@@ -368,12 +371,14 @@ extern "C" int32_t rk_simulate(rk_ctx *ctx, const float *ref_thr, const rk_plan_
             run = sent_by[w] > run ? sent_by[w] : run;
             closed = __atomic_load_n(ctx->h_pinned + H_TICK, __ATOMIC_ACQUIRE);
         }
-        if (e == hipSuccess) e = hipStreamSynchronize(s);      // the graph must outlive its launches
+        const hipError_t e_sync = hipStreamSynchronize(s);     // the graph must outlive its launches
+        if (e == hipSuccess) e = e_sync;
         if (exec) (void)hipGraphExecDestroy(exec);
         (void)hipGraphDestroy(graph);
         if (e != hipSuccess) return rk_fail(ctx, RK_ERR_DEVICE, "simulation graph: %s", hipGetErrorString(e));
     }
     RK_HIP(ctx, hipEventRecord(ctx->sim_ev[1], s));
     RK_HIP(ctx, hipStreamWaitEvent(user, ctx->sim_ev[1], 0));
+    ctx->sim_failed = false;
     return RK_OK;
 }

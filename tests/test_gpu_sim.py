@@ -259,3 +259,31 @@ def test_simulation_of_few_ticks_and_idle_stretches(gpu, orc, policy):
             got = run_on_gpu(run, r, arrival, work, delta, 10.0, n_ticks, 0.97, policy=policy, nodes=kw["nodes"])
             same(got, want)
     run.close()
+
+
+def test_simulations_one_after_the_other_without_waiting(gpu, orc):
+    """A simulation of a single tick may still run when the next one of the context begins, and a longer one looks at a
+    counter in host memory that every simulation writes: each has its own results."""
+    import paper_2408_08586_amd as rk
+    wl = workloads.tiny()
+    r = orc.schedule_round(wl, n_threads=4)
+    J = wl.n_jobs
+    run = gpu(wl)
+    run.enumerate()
+    f64 = lambda a: run.torch.from_numpy(np.ascontiguousarray(a, dtype=np.float64)).to(run.device)
+    values = run.dev_f32(r["best_thr"]), run.dev_u32(r["best_plan"]), run.dev_f32(r["curve_thr"])
+    arrival, work, delta = np.arange(J) * 35.0, 100.0 * wl.coef[:, 16], np.full(J, 3.0)
+    on_device = f64(arrival), f64(work), f64(delta)
+    ticks = (40, 1, 1, 1, 40, 2, 1, 25, 1, 40)
+    results = [rk.SimResult(J, n, run.device) for n in ticks]
+    rk.rk_sync(run.ctx)
+    for n, res in zip(ticks, results):
+        rk.rk_simulate(run.ctx, run.jobs.ref_thr, run.table.c, run.grid, run.cluster, *values, *on_device, 10.0, n, 0.97, res)
+    rk.rk_sync(run.ctx)
+    for n, res in zip(ticks, results):
+        want = orc.simulator.simulate(wl.coef[:, 16], r["table"], wl.grid, wl.cluster, r["best_thr"], r["best_plan"],
+                                      r["curve_thr"], arrival, work, delta, 10.0, n)
+        got = {k: getattr(res, k).cpu().numpy()[:J] for k in ("finish", "n_reconf", "progress", "held")}
+        got.update({k: getattr(res, k).cpu().numpy()[:n] for k in ("gpus_in_use", "totals", "frozen")})
+        same({k: v.view(np.uint32) if v.dtype == np.int32 else v for k, v in got.items()}, want)
+    run.close()
