@@ -606,8 +606,10 @@ extern "C" int32_t rk_fit_models(rk_ctx *ctx, const rk_jobs *jobs, const rk_env 
     A.most_runs = ms <= 8 ? 8u : ms <= 16 ? 16u : ms <= 32 ? 32u : 64u;
     // Workgroups: one or two wavefronts per SIMD of the 256 compute units.  The second makes every iteration of the
     // first slower and pays only when there is enough to do for both beyond the longest descents of the last models:
-    // 16 runs, 5 starting points, one against two: 3,000 models 5.7 against 6.5 ms, 6,000 7.5 against 7.7, 10,000 9.5
-    // against 9.0.
+    // 16 runs, 5 starting points, one against two: 3,000 models 5.7 against 6.5 ms, 6,000 7.4 against 7.3, 8,500 9.2
+    // against 8.2, 10,000 9.6 against 9.1.  Wider groups have fewer models to a wavefront, and the line is drawn at the same
+    // number of lanes; it could lie lower: 24 runs, 2,500 models 6.9 against 6.9, 3,500 7.8 against 7.5, 4,200 8.8 against
+    // 7.8; 48 runs, 1,500 models 6.9 against 6.4, 2,100 7.0 against 6.8, 3,000 8.5 against 7.4.
     const uint32_t width = A.most_runs < 16u ? 16u : A.most_runs;
     const uint32_t blocks = (uint64_t)A.n_fits * width > 8192ull * 16ull ? 512u : 256u;
     if (width == 16u) launch_fit<16>(A, blocks, ctx->stream);

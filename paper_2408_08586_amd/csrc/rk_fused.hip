@@ -27,6 +27,11 @@ namespace {
 // wavefront per job (DIRECT) costs the least: 402 us for 128,000 jobs with five rows against 672 with four wavefronts, 69
 // against 85 us for 10,000 jobs with twenty, 55 against 62 for 7,000, 41.6 against 43.4 for 4,500.  Below that it is the
 // single job that counts, and four wavefronts finish it sooner: 29.7 us against 32.1 for 3,000 jobs, 13 against 20 for 1,000.
+// The line is that of five and twenty rows.  With one row and eight it could lie lower (2,500 jobs 22 against 26 and 26
+// against 28 us), with more rows higher: 32 rows of 97 triples 51 against 49 us for 4,096 jobs and 82 against 86 for 10,000;
+// 64 rows 105 against 90 for 6,000, 136 against 127 for 10,000, 383 against 432 for 40,000.  One job's lanes wait longest
+// for each other where the rows are many and have tiers: 64 levels of three tiers, 302 against 204 us for 10,000 jobs and
+// 1,033 against 709 for 40,000, where four wavefronts would be the better form at every count.
 constexpr int FEW_JOBS = 256;
 constexpr uint32_t FUSED_MANY = 4096;
 constexpr uint32_t FUSED_FILL = 512;      // workgroups that occupy the chip: two per CU

@@ -64,7 +64,7 @@ __device__ __forceinline__ float fast_div(float a, float b) { return a * __built
 // corrections, fix-up) takes eleven: the divisor's correctly rounded reciprocal once, then a quotient and one correction
 // with the exact remainder.  The results are those of the division for the divisors and dividends used here: whole
 // divisors up to 65,535 under small whole dividends, and products d = t*p (t a power of two, p < 4096) under any dividend
-// whose remainders stay in range (checked for every mantissa and every p, from reciprocals one unit off either way).
+// whose remainders stay in range (tests/test_shared_reciprocals.py, from reciprocals one unit off either way).
 struct Divisor { float b, r; };
 __device__ __forceinline__ Divisor divisor(float b) {
     const float r = __builtin_amdgcn_rcpf(b);
