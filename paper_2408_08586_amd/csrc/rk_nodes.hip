@@ -644,7 +644,6 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
             if (b[k] - a[k] > 2u) {
                 const uint32_t to = atomicAdd(&sh_list, 1u);
                 if (to < A.nodes_words) keep[to] = j;
-                else bad |= 1u;
                 continue;
             }
             if (a[k] < b[k]) book(j, e[k]);
@@ -652,7 +651,8 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
         }
     }
     __syncthreads();
-    const uint32_t listed = sh_list < A.nodes_words ? sh_list : A.nodes_words;
+    const uint32_t listed = sh_list;
+    if (listed > A.nodes_words) { nd_refuse<THREADS>(A); return; }
     for (uint32_t i = wave; i < listed; i += WAVES) {
         const uint32_t j = keep[i];
         const uint32_t a = A.prev_off[j], b = A.prev_off[j + 1];
