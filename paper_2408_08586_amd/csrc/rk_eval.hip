@@ -26,7 +26,23 @@ constexpr int TRIPLES_PER_BLOCK = EVAL_THREADS / 4;
 // three rows, 12.0 us from the copy and 10.9 lane by lane; 300, six rows, 18.2
 // and 17.8; 600, nine rows, 23.9 and 23.5; even at ten rows (900 jobs).
 constexpr uint32_t FEAS_DIRECT_ROWS = 9;
-template <bool WITH_FEAS>
+
+// STREAM: the throughputs leave by streaming stores.  A tensor that outgrows the caches only drives what is in them out,
+// and the lines it leaves there are still on their way to memory when the next kernel starts.  One that the caches hold
+// is read back from them, or written over there by the next call, which streaming stores give up.  The lines lie at the
+// tensor's size.  k_eval, then k_best_plan on what it wrote (35 MB is about what the L2 caches hold): 35 MB 33.8 us with
+// plain and 35.2 with streaming stores, 53 MB 36.9 and 37.4, 70 MB 41.5 and 40.0, 105 MB 58.5 and 57.2, 210 MB 96.5 and
+// 89.7, 350 MB 148.6 and 134.7.  k_eval_best, which nothing reads after (the memory-side cache holds 256 MB): 135 MB
+// 123.6 and 126.0 us for the whole step, 270 MB 134.5 and 143.3, 350 MB 209.9 and 205.8, 540 MB 238.9 and 226.8, 900 MB
+// 390.0 and 363.4.  The reason bytes keep plain stores: streamed as well, 350 MB take 164 us instead of 135.
+constexpr uint64_t EVAL_STREAM_BYTES = 64ull << 20, EVAL_BEST_STREAM_BYTES = 320ull << 20;
+template <bool STREAM>
+__device__ __forceinline__ void store_thr(float *to, const v4f &v) {
+    if (STREAM) __builtin_nontemporal_store(v, reinterpret_cast<v4f *>(to));
+    else *reinterpret_cast<v4f *>(to) = v;
+}
+
+template <bool WITH_FEAS, bool STREAM>
 __global__ __launch_bounds__(EVAL_THREADS) void k_eval(JobDev jobs, TableDev tb, GridDev grid, rk_env env,
                                                        uint32_t jb, uint32_t option_mask, uint32_t c_per_block,
                                                        float *__restrict__ thr, uint8_t *__restrict__ feas) {
@@ -109,7 +125,7 @@ __global__ __launch_bounds__(EVAL_THREADS) void k_eval(JobDev jobs, TableDev tb,
             v.w = w1 ? 0.f : off_thr[1];
             const uint32_t row = ci * grid.n_mem + mi;
             const uint64_t at = cbase + ((uint64_t)row * nt + tile_lo) * 16;
-            if (active) *reinterpret_cast<v4f *>(thr + at + (tl - tile_lo) * 16 + z * 4) = v;
+            if (active) store_thr<STREAM>(thr + at + (tl - tile_lo) * 16 + z * 4, v);
             if (WITH_FEAS && !staged && active)
                 *reinterpret_cast<uint32_t *>(feas + at + (tl - tile_lo) * 16 + z * 4) = why_plain[0] | (w0 << 8) | (why_plain[1] << 16) | (w1 << 24);
             if (staged && (row & 3u) == wave && tile_lo + lane < nt)
@@ -239,7 +255,7 @@ __device__ __forceinline__ uint32_t tile_index(const TableDev &tb, uint32_t jb, 
     return (tb.triple_off[j] - tb.triple_off[jb]) / EB_TILE + (j - jb) + tile;
 }
 
-template <bool WITH_FEAS>
+template <bool WITH_FEAS, bool STREAM>
 __global__ __launch_bounds__(EB_THREADS) void k_eval_best(JobDev jobs, TableDev tb, GridDev grid, rk_env env, uint32_t jb,
                                                             uint32_t option_mask, uint32_t c_per_block, uint32_t key_stride,
                                                             float *__restrict__ thr, uint8_t *__restrict__ feas,
@@ -370,7 +386,7 @@ __global__ __launch_bounds__(EB_THREADS) void k_eval_best(JobDev jobs, TableDev 
                 v.z = plain[1];
                 v.w = w1 ? 0.f : off_thr[1];
                 const uint64_t idx = cbase + ((uint64_t)(ci * grid.n_mem + mi) * nt + tl) * 16 + z * 4;
-                *reinterpret_cast<v4f *>(thr + idx) = v;
+                store_thr<STREAM>(thr + idx, v);
                 if (WITH_FEAS) {
                     const uint32_t packed = why_plain[0] | (w0 << 8) | (why_plain[1] << 16) | (w1 << 24);
                     *reinterpret_cast<uint32_t *>(feas + idx) = packed;
@@ -554,10 +570,10 @@ int32_t rk_eval_candidates(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_table
     const JobDev jd = job_dev(jobs);
     const TableDev td = table_dev(table);
     const GridDev gd = grid_dev(grid);
-    if (feas)
-        k_eval<true><<<g3, EVAL_THREADS, grid->n_mem * EVAL_THREADS * 4, ctx->stream>>>(jd, td, gd, *env, jb, table->option_mask, c_per_block, thr, feas);
-    else
-        k_eval<false><<<g3, EVAL_THREADS, 0, ctx->stream>>>(jd, td, gd, *env, jb, table->option_mask, c_per_block, thr, nullptr);
+    const bool stream = need * 4 > EVAL_STREAM_BYTES;
+    auto *kernel = feas ? (stream ? k_eval<true, true> : k_eval<true, false>) : (stream ? k_eval<false, true> : k_eval<false, false>);
+    kernel<<<g3, EVAL_THREADS, feas ? grid->n_mem * EVAL_THREADS * 4 : 0, ctx->stream>>>(jd, td, gd, *env, jb, table->option_mask,
+                                                                                    c_per_block, thr, feas);
     RK_CHECK_LAUNCH(ctx, "k_eval");
     return RK_OK;
 }
@@ -650,12 +666,11 @@ int32_t rk_eval_best_plan(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_table 
     const JobDev jd = job_dev(jobs);
     const TableDev td = table_dev(table);
     const GridDev gd = grid_dev(grid);
-    if (feas)
-        k_eval_best<true><<<g3, EB_THREADS, lds, ctx->stream>>>(jd, td, gd, *env, jb, table->option_mask, c_per_block,
-                                                                 key_stride, thr, feas, best_thr, best_plan, partial);
-    else
-        k_eval_best<false><<<g3, EB_THREADS, lds, ctx->stream>>>(jd, td, gd, *env, jb, table->option_mask, c_per_block,
-                                                                  key_stride, thr, nullptr, best_thr, best_plan, partial);
+    const bool stream = need * 4 > EVAL_BEST_STREAM_BYTES;
+    auto *kernel = feas ? (stream ? k_eval_best<true, true> : k_eval_best<true, false>)
+                        : (stream ? k_eval_best<false, true> : k_eval_best<false, false>);
+    kernel<<<g3, EB_THREADS, lds, ctx->stream>>>(jd, td, gd, *env, jb, table->option_mask, c_per_block, key_stride, thr, feas,
+                                                 best_thr, best_plan, partial);
     RK_CHECK_LAUNCH(ctx, "k_eval_best");
     if (bx > 1) {
         const uint32_t per_block = MERGE_THREADS / MERGE_LANES;

@@ -92,6 +92,21 @@ def test_many_segments_and_tiers(gpu, orc):
         run.close()
 
 
+@pytest.mark.parametrize("n_jobs", [120, 500, 1400])
+def test_large_tensors_hold_what_small_ones_do(gpu, orc, n_jobs):
+    """Tensors of 30, 130 and 380 MB, below and above the sizes from which the two kernels store past the caches: every
+    job's values are those of a call over a few jobs, bit for bit."""
+    run = gpu(workloads.stress(n_jobs=n_jobs))
+    run.enumerate()
+    thr, feas, bt, bp, n, ns = same_as_two_calls(run)
+    for jb in (0, n_jobs // 2 - 7, n_jobs - 30):
+        t, f, b, p, m, ms = run.eval_best(jb, jb + 30)
+        at, s_at = run.table.n_candidates(run.n_rows, 0, jb), run.table.n_segments(run.n_rows, 0, jb)
+        for whole, part, first, count in ((thr, t, at, m), (feas, f, at, m), (bt, b, s_at, ms), (bp, p, s_at, ms)):
+            assert np.array_equal(run.host(whole[first:first + count]), run.host(part, count))
+    run.close()
+
+
 def test_argument_errors(gpu, orc):
     import paper_2408_08586_amd as rk
     wl = workloads.tiny()
