@@ -333,7 +333,7 @@ __global__ __launch_bounds__(HULL_THREADS) void k_hull_groups(Ctx X, JobState st
 
     uint32_t npts, g_fixed = 0, c_fixed = 0;
     int32_t cur_i;
-    unsigned long long cost_cur, cap_c, cap_g = 0;
+    unsigned long long cost_held, cap_c, cap_g = 0;
     float cur;
     int32_t gi = -1;
     if (PASS == 0) {
@@ -343,36 +343,39 @@ __global__ __launch_bounds__(HULL_THREADS) void k_hull_groups(Ctx X, JobState st
         c_fixed = fl.ci;
         npts = fl.state != RK_JOB_NORMAL ? 0u : ns;
         cur_i = fl.gi;
-        cost_cur = fl.gi < 0 ? 0ull : (unsigned long long)X.tb.seg_g[s0 + fl.gi];
+        cost_held = fl.gi < 0 ? 0ull : (unsigned long long)X.tb.seg_g[s0 + fl.gi];
         cur = fl.gi < 0 ? 0.f : vals[jbase + (uint64_t)(c_fixed * n_mem + n_mem - 1) * ns + fl.gi];
-        cap_g = startG + cost_cur;                       // the floor is already paid for
-        cap_c = startC + (fl.gi < 0 ? 0ull : cpu_cost(grid, c_fixed, (uint32_t)cost_cur));
+        cap_g = startG + cost_held;                      // the floor is already paid for
+        cap_c = startC + (fl.gi < 0 ? 0ull : cpu_cost(grid, c_fixed, (uint32_t)cost_held));
     } else {
         gi = st.gi[jrel];
         npts = (gi < 0 || (st.waits && st.waits[jrel] != RK_JOB_NORMAL)) ? 0u : grid.n_cpu;
         g_fixed = gi < 0 ? 0u : st.g[jrel];
         cur_i = (int32_t)st.ci[jrel];
-        cost_cur = cpu_cost(grid, (uint32_t)cur_i, g_fixed);
-        cap_c = st.free_c[rnd] + cost_cur;               // the level held is already paid for
+        cost_held = cpu_cost(grid, (uint32_t)cur_i, g_fixed);
+        cap_c = st.free_c[rnd] + cost_held;              // the level held is already paid for
         cur = gi < 0 ? 0.f : vals[jbase + (uint64_t)((uint32_t)cur_i * n_mem + n_mem - 1) * ns + gi];
     }
     if (!valid) npts = 0;
     // the lane's amount: cost in the pass's resource, value, and whether the round could ever afford it
-    unsigned long long cost0 = 0;
+    // (of the costs the walk takes the low words: a step that the round can afford fits one)
+    uint32_t cost0 = 0;
     float val0 = 0.f;
     bool can = false;
     if (sub < npts) {
-        cost0 = PASS == 0 ? (unsigned long long)X.tb.seg_g[s0 + sub] : cpu_cost(grid, sub, g_fixed);
+        const unsigned long long cost = PASS == 0 ? (unsigned long long)X.tb.seg_g[s0 + sub] : cpu_cost(grid, sub, g_fixed);
         val0 = PASS == 0 ? vals[jbase + (uint64_t)(c_fixed * n_mem + n_mem - 1) * ns + sub]
                          : vals[jbase + (uint64_t)(sub * n_mem + n_mem - 1) * ns + gi];
-        can = PASS == 0 ? (cost0 <= cap_g && cpu_cost(grid, c_fixed, (uint32_t)cost0) <= cap_c) : cost0 <= cap_c;
+        can = PASS == 0 ? (cost <= cap_g && cpu_cost(grid, c_fixed, (uint32_t)cost) <= cap_c) : cost <= cap_c;
+        cost0 = (uint32_t)cost;
     }
 
     uint32_t k = 0;
     float prev = __uint_as_float(0x7F800000u);
     // the lane's step of the walk: step number = lane number within the job
     uint32_t my_key = 0, my_raw = 0, my_tgt = 0;
-    unsigned long long my_from = 0, my_to = 0;             // its costs before and after
+    uint32_t my_from = 0, my_to = 0;                       // its costs before and after
+    uint32_t cost_cur = (uint32_t)cost_held;
     bool walking = npts > 0;                               // the same in all lanes of a job (H.width is at least 1)
     while (__ballot(walking)) {                            // until the wavefront's last job has finished
         uint32_t best = 0;
@@ -387,8 +390,7 @@ __global__ __launch_bounds__(HULL_THREADS) void k_hull_groups(Ctx X, JobState st
         const uint32_t reach = (uint32_t)(__ballot(best == top) >> group_base) & (LANES == 16 ? 0xFFFFu : 0xFFFFFFFFu);
         const uint32_t top_s = reach ? (uint32_t)__ffs((int)reach) - 1u : 0u;
         const int src = (int)(group_base + top_s);
-        unsigned long long top_cost = (uint32_t)__shfl((int)(uint32_t)cost0, src, 64);
-        if (PASS == 1) top_cost |= (unsigned long long)(uint32_t)__shfl((int)(uint32_t)(cost0 >> 32), src, 64) << 32;
+        const uint32_t top_cost = (uint32_t)__shfl((int)cost0, src, 64);
         const float top_val = __shfl(val0, src, 64);
         if (walking) {
             prev = __uint_as_float(top) < prev ? __uint_as_float(top) : prev;
@@ -406,8 +408,8 @@ __global__ __launch_bounds__(HULL_THREADS) void k_hull_groups(Ctx X, JobState st
             H.raw[e] = __uint_as_float(my_raw);
             H.tgt[e] = (uint16_t)my_tgt;
             if (PASS == 0) {
-                H.dg[e] = (uint32_t)(my_to - my_from);
-                H.dc[e] = cpu_cost(grid, c_fixed, (uint32_t)my_to) - (my_from ? cpu_cost(grid, c_fixed, (uint32_t)my_from) : 0ull);
+                H.dg[e] = my_to - my_from;
+                H.dc[e] = cpu_cost(grid, c_fixed, my_to) - (my_from ? cpu_cost(grid, c_fixed, my_from) : 0ull);
             } else {
                 H.dg[e] = 0u;
                 H.dc[e] = my_to - my_from;
@@ -1143,8 +1145,8 @@ constexpr size_t SELECT_HIST_BYTES = (size_t)BINS * 12;
 
 __device__ __forceinline__ void mem_wish_job(const Ctx &X, const JobState &st, uint32_t j, rk_assign *__restrict__ assign,
                                              double &cost_d, double &val_d);
-__device__ void mem_close_round(const Ctx &X, const JobState &st, uint32_t rnd, double wish, double val,
-                                rk_assign *__restrict__ assign, float *__restrict__ totals);
+__device__ void mem_close_round(const Ctx &X, const int32_t *gi_of, const uint32_t *g_of, const uint32_t *ci_of, uint32_t rnd,
+                                double wish, double val, rk_assign *__restrict__ assign, float *__restrict__ totals);
 
 template <int PASS, int KMAX>
 __global__ __launch_bounds__(TAIL_THREADS) void k_select_small(Ctx X, uint32_t max_jobs, JobState st, HullBuf H,
@@ -1210,7 +1212,8 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_select_small(Ctx X, uint32_t m
     if (tid < 64u) {
         const bool has = tid < TAIL_THREADS / 64;
         const double wish = wave_sum_f64(has ? sums[tid] : 0.0), val = wave_sum_f64(has ? sums[TAIL_THREADS / 64 + tid] : 0.0);
-        mem_close_round(X, st, rnd, wish, val, assign, totals);
+        const uint32_t jrel0 = J0 - X.jb;
+        mem_close_round(X, st.gi + jrel0, st.g + jrel0, st.ci + jrel0, rnd, wish, val, assign + jrel0, totals);
     }
 }
 
@@ -1223,36 +1226,45 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_select_small(Ctx X, uint32_t m
 // Large rounds: k_mem_wish (a thread per job) and k_mem_finish (a wavefront per
 // round); small rounds: the workgroup of the CPU pass's selection does both.
 
-// the wish of job j, written to its record; adds its cost and its normalised throughput to the two sums
-__device__ __forceinline__ void mem_wish_job(const Ctx &X, const JobState &st, uint32_t j, rk_assign *__restrict__ assign,
-                                             double &cost_d, double &val_d) {
+// the wish of a job that holds segment gi (-1: nothing) with g GPUs at CPU level c_lvl; s0, ns: its segments; adds its
+// cost and its normalised throughput to the two sums
+__device__ __forceinline__ rk_assign mem_wish(const Ctx &X, int32_t gi, uint32_t g, uint32_t c_lvl, uint32_t s0, uint32_t ns,
+                                              uint32_t first_seg, float ref, double &cost_d, double &val_d) {
     const GridDev &grid = X.grid;
     const uint32_t n_mem = grid.n_mem, n_rows = grid.n_cpu * n_mem;
+    rk_assign out = {0u, 0u, 0.f, RK_NO_PLAN, 0.f};
+    if (gi < 0) return out;
+    const uint64_t base = (uint64_t)n_rows * (s0 - first_seg) + (uint64_t)(c_lvl * n_mem) * ns + (uint32_t)gi;
+    float bv = 0.f;
+    uint32_t bm = 0;
+    for (uint32_t m = 0; m < n_mem; ++m) {
+        const float v = X.best_thr[base + (uint64_t)m * ns];
+        if (v > bv) { bv = v; bm = m; }
+    }
+    if (bv > 0.f) {
+        float cost = grid.mem_levels_gb[bm];
+        if (grid.mem_mode) cost = cost * (float)g;
+        out.g = g;
+        out.c = (uint32_t)cpu_cost(grid, c_lvl, g);
+        out.mem_gb = cost;
+        out.plan = X.best_plan[base + (uint64_t)bm * ns];
+        out.thr = bv;
+        cost_d += (double)cost;
+        val_d += (double)bv / (double)ref;
+    }
+    return out;
+}
+
+// ... of job j, written to its record
+__device__ __forceinline__ void mem_wish_job(const Ctx &X, const JobState &st, uint32_t j, rk_assign *__restrict__ assign,
+                                             double &cost_d, double &val_d) {
     const uint32_t jrel = j - X.jb;
     rk_assign out = {0u, 0u, 0.f, RK_NO_PLAN, 0.f};
     const int32_t gi = st.gi[jrel];
     if (gi >= 0) {
-        const uint32_t g = st.g[jrel], c_lvl = st.ci[jrel];
         const uint32_t ju = job_of(X, j);
         const uint32_t s0 = X.tb.seg_off[ju], ns = X.tb.seg_off[ju + 1] - s0;
-        const uint64_t base = (uint64_t)n_rows * (s0 - X.tb.seg_off[X.jb]) + (uint64_t)(c_lvl * n_mem) * ns + gi;
-        float bv = 0.f;
-        uint32_t bm = 0;
-        for (uint32_t m = 0; m < n_mem; ++m) {
-            const float v = X.best_thr[base + (uint64_t)m * ns];
-            if (v > bv) { bv = v; bm = m; }
-        }
-        if (bv > 0.f) {
-            float cost = grid.mem_levels_gb[bm];
-            if (grid.mem_mode) cost = cost * (float)g;
-            out.g = g;
-            out.c = (uint32_t)cpu_cost(grid, c_lvl, g);
-            out.mem_gb = cost;
-            out.plan = X.best_plan[base + (uint64_t)bm * ns];
-            out.thr = bv;
-            cost_d += (double)cost;
-            val_d += (double)bv / (double)X.ref_thr[job_of(X, j)];
-        }
+        out = mem_wish(X, gi, st.g[jrel], st.ci[jrel], s0, ns, X.tb.seg_off[X.jb], X.ref_thr[ju], cost_d, val_d);
     }
     assign[jrel] = out;
 }
@@ -1279,14 +1291,15 @@ __global__ __launch_bounds__(JOB_THREADS) void k_mem_wish(Ctx X, JobState st, rk
 }
 
 // One wavefront (threadIdx.x = lane) closes a round whose wishes sum to `wish` GiB and `val` normalised throughput.
-__device__ void mem_close_round(const Ctx &X, const JobState &st, uint32_t rnd, double wish, double val,
-                                rk_assign *__restrict__ assign, float *__restrict__ totals) {
+// gi_of, g_of, ci_of: what the round's jobs hold, assign: their records, from its first job on.
+__device__ void mem_close_round(const Ctx &X, const int32_t *gi_of, const uint32_t *g_of, const uint32_t *ci_of, uint32_t rnd,
+                                double wish, double val, rk_assign *__restrict__ assign, float *__restrict__ totals) {
     const uint32_t tid = threadIdx.x;
     uint32_t J0, J1;
     rk_cluster cl;
     round_of(X.R, rnd, J0, J1, cl);
     const GridDev &grid = X.grid;
-    const uint32_t nj = J1 - J0, jrel0 = J0 - X.jb;
+    const uint32_t nj = J1 - J0;
     const uint32_t n_mem = grid.n_mem, n_rows = grid.n_cpu * n_mem;
     if (wish <= 0.99 * (double)cl.host_mem_gb) {
         if (tid == 0) totals[rnd] = (float)val;
@@ -1297,7 +1310,7 @@ __device__ void mem_close_round(const Ctx &X, const JobState &st, uint32_t rnd, 
     double sum = 0.0;
     for (uint32_t base = 0; base < nj; base += 64) {
         const uint32_t jl = base + tid;
-        const bool have = jl < nj && st.gi[jrel0 + jl] >= 0;
+        const bool have = jl < nj && gi_of[jl] >= 0;
         uint32_t g = 0, c_lvl = 0, ns = 0;
         uint64_t at0 = 0;
         unsigned long long choice = 0;      // 4 bits per prefix length: best tier among tiers 0..k
@@ -1307,11 +1320,11 @@ __device__ void mem_close_round(const Ctx &X, const JobState &st, uint32_t rnd, 
         for (uint32_t m = 0; m < RK_MAX_MEM_LEVELS; ++m) thr_m[m] = 0.f;
         if (have) {
             const uint32_t j = J0 + jl;
-            g = st.g[jrel0 + jl]; c_lvl = st.ci[jrel0 + jl];
+            g = g_of[jl]; c_lvl = ci_of[jl];
             const uint32_t ju = job_of(X, j);
             const uint32_t s0 = X.tb.seg_off[ju];
             ns = X.tb.seg_off[ju + 1] - s0;
-            at0 = (uint64_t)n_rows * (s0 - X.tb.seg_off[X.jb]) + (uint64_t)(c_lvl * n_mem) * ns + (uint32_t)st.gi[jrel0 + jl];
+            at0 = (uint64_t)n_rows * (s0 - X.tb.seg_off[X.jb]) + (uint64_t)(c_lvl * n_mem) * ns + (uint32_t)gi_of[jl];
             float bv = 0.f;
             uint32_t bm = 0;
 #pragma unroll
@@ -1354,7 +1367,7 @@ __device__ void mem_close_round(const Ctx &X, const JobState &st, uint32_t rnd, 
             spent = __shfl(spent, (int)turn, 64);
             freeM = freeM - spent;
         }
-        if (jl < nj) assign[jrel0 + jl] = out;
+        if (jl < nj) assign[jl] = out;
     }
     sum = wave_sum_f64(sum);
     if (tid == 0) totals[rnd] = (float)sum;
@@ -1375,7 +1388,508 @@ __global__ __launch_bounds__(64) void k_mem_finish(Ctx X, JobState st, rk_assign
     }
     wish = wave_sum_f64(wish);
     val = wave_sum_f64(val);
-    mem_close_round(X, st, rnd, wish, val, assign, totals);
+    const uint32_t jrel0 = J0 - X.jb;
+    mem_close_round(X, st.gi + jrel0, st.g + jrel0, st.ci + jrel0, rnd, wish, val, assign + jrel0, totals);
+}
+
+// ------------------------------------------------------------------ rounds of few jobs
+// The whole allocation of a round whose walks take a few turns of one workgroup's wavefronts, in one launch: walks,
+// histogram, threshold, application, the steps on what is left and the memory step of both passes.  Such a round is a
+// chain of latencies, so everything a step of the chain hands to the next lies in LDS: a pass compacts the jobs that take
+// part in it, a job takes 16, 32 or 64 neighbouring lanes (at least its amounts), and its amounts, values and walk stay
+// where those lanes can read them.  The steps on what is left are taken by one wavefront without barriers; the others
+// come in where cached steps that stopped fitting have to be made exact.
+// The lines: a wavefront takes the GPU walks of 64 / lanes jobs in about 2.7 us, bound by its instructions, while a launch
+// of its own over the whole chip takes 4 to 5 us for any number of jobs that comes into question.  Whole rounds on jobs
+// with up to 16 GPU counts, four launches and one: 8 jobs 48 and 39 us, 64 jobs 56 and 44, 128 jobs 58 and 52, 192 jobs
+// 64 and 62, 256 jobs 67 and 72.  Leaving the walks of larger rounds to a launch in front of this one brings nothing:
+// their threads wait for memory in every step instead (500 jobs 68 and 74 us, 1,000 jobs 79 and 92).
+constexpr int FEW_THREADS = 1024, FEW_WAVES = FEW_THREADS / 64;
+constexpr uint32_t FEW_JOBS = FEW_THREADS;        // at most a job per thread
+constexpr uint32_t FEW_GPU_LANES = 2048, FEW_CPU_LANES = 4096;   // of a round: jobs times lanes of a job
+constexpr uint32_t FEW_BINS = 1024, FEW_FINE = 128;
+
+struct FewMem {                  // per round, in LDS
+    unsigned long long *hc;      // histogram of a pass: CPUs and GPUs of the steps per bin
+    uint32_t *hg;
+    uint32_t *lvl;               // CPU levels
+    uint32_t *range;             // highest and lowest key of the pass's walks
+    // per job of the round: where its segments are, its reference throughput, what it holds
+    uint32_t *s0, *ns;
+    float *ref;
+    int32_t *gi;
+    uint32_t *g, *ci;
+    // per job that takes part in the pass, in job order: the job, its cached next step (slope > 0 exact, < 0 an upper
+    // bound, 0 none; target | GPUs << 16; CPUs)
+    uint32_t *part, *to;
+    float *slope;
+    uint32_t *dc;
+    uint32_t *cnt;               // FEW_WAVES words: the wavefronts' counts
+    unsigned long long *box;     // what the first wavefront tells the others
+};
+// Per lane of a job that takes part: its value and amount (GPUs, GPU pass), and the walk's step of the lane's number:
+// key (0: none), slope, target | GPUs << 16, CPUs.  In LDS, or in memory where a pass's do not fit there.
+struct FewLanes {
+    uint4 *step;
+    float *val;
+    uint32_t *amt;
+};
+constexpr size_t FEW_FIXED_BYTES = (size_t)FEW_BINS * 12 + (RK_MAX_CPU_LEVELS + FEW_WAVES + 4) * 4 + 4 * 8;
+constexpr size_t FEW_JOB_BYTES = 10 * 4, FEW_LANE_BYTES = 16 + 2 * 4;
+
+// The per-job words of `jobs` jobs (rounded up to four); *end: the LDS behind them.
+__device__ __forceinline__ FewMem few_mem(unsigned long long *lds, uint32_t jobs, uint32_t **end) {
+    FewMem M;
+    M.hc = lds;
+    M.box = M.hc + FEW_BINS;
+    uint32_t *p = reinterpret_cast<uint32_t *>(M.box + 4);
+    auto take = [&](uint32_t n) { uint32_t *q = p; p += n; return q; };
+    M.hg = take(FEW_BINS); M.lvl = take(RK_MAX_CPU_LEVELS); M.cnt = take(FEW_WAVES); M.range = take(4);
+    jobs = (jobs + 3u) & ~3u;
+    M.s0 = take(jobs); M.ns = take(jobs); M.ref = reinterpret_cast<float *>(take(jobs));
+    M.gi = reinterpret_cast<int32_t *>(take(jobs)); M.g = take(jobs); M.ci = take(jobs);
+    M.part = take(jobs); M.to = take(jobs); M.slope = reinterpret_cast<float *>(take(jobs)); M.dc = take(jobs);
+    *end = p;
+    return M;
+}
+// (n a multiple of four)
+__device__ __forceinline__ FewLanes few_lane_mem(uint32_t *p, uint32_t n) {
+    return FewLanes{reinterpret_cast<uint4 *>(p), reinterpret_cast<float *>(p + 4 * (size_t)n), p + 5 * (size_t)n};
+}
+
+// Lanes a job takes: `amounts` <= 64.
+inline uint32_t few_lanes(uint32_t amounts) { return amounts <= 16u ? 16u : amounts <= 32u ? 32u : 64u; }
+
+// Maximum over the 16, 32 or 64 neighbouring lanes of a job; all 64 lanes must be active.
+__device__ __forceinline__ uint32_t few_max(uint32_t v, uint32_t lanes, uint32_t lane) {
+    v = row_max_u32(v);
+    if (lanes == 16u) return v;
+    const uint32_t lo = rs_max_u32(wave_lane_u32(v, 0u), wave_lane_u32(v, 16u));
+    const uint32_t hi = rs_max_u32(wave_lane_u32(v, 32u), wave_lane_u32(v, 48u));
+    return lanes == 64u ? rs_max_u32(lo, hi) : lane < 32u ? lo : hi;
+}
+__device__ __forceinline__ uint32_t few_bits(unsigned long long ballot, uint32_t base, uint32_t lanes) {   // first lane + 1, 0: none
+    return (uint32_t)__ffsll((long long)((ballot >> base) & (~0ull >> (64u - lanes))));
+}
+
+// Best next step of the job whose lanes these are, from where it is (`at`), under what is free: best_step's search.
+// v, amt: the lane's value (0 beyond the job's amounts) and GPU count.
+template <int PASS>
+__device__ __forceinline__ Step few_search(const GridDev &grid, const uint32_t *lvl, uint32_t lanes, float v, uint32_t amt, int32_t at,
+                                           uint32_t g_held, uint32_t ci, float ref, unsigned long long freeG,
+                                           unsigned long long freeC, uint32_t &dc_out) {
+    const uint32_t lane = threadIdx.x & 63u, sub = lane & (lanes - 1u), base = lane - sub;
+    const int from = (int)(base + (at < 0 ? 0u : (uint32_t)at));
+    const float v_at = __shfl(v, from, 64);
+    const float cur = at < 0 ? 0.f : v_at;
+    uint32_t dg = 0;
+    unsigned long long dc;
+    if (PASS == 0) {
+        const uint32_t g_at = (uint32_t)__shfl((int)amt, from, 64);
+        dg = amt - (at < 0 ? 0u : g_at);
+        dc = (unsigned long long)lvl[ci] * (grid.cpu_mode ? dg : (at < 0 ? 1u : 0u));
+    } else {
+        const unsigned long long times = grid.cpu_mode ? g_held : 1u;
+        dc = (unsigned long long)lvl[sub] * times - (unsigned long long)lvl[at] * times;
+    }
+    uint32_t bits = 0;
+    if ((int32_t)sub > at && v > cur && (PASS == 1 || dg <= freeG) && dc <= freeC) {
+        float sl = (v - cur) / ref;
+        sl = sl / (PASS == 0 ? (float)dg : (float)dc);
+        bits = sl > 0.f ? __float_as_uint(sl) : 0u;
+    }
+    const uint32_t top = few_max(bits, lanes, lane);
+    Step out = {0.f, 0u, 0u};
+    const uint32_t holder = few_bits(__ballot(bits == top), base, lanes) - 1u;       // the lowest lane is the smallest amount
+    const uint32_t dg_top = PASS == 0 ? (uint32_t)__shfl((int)dg, (int)(base + holder), 64) : 0u;
+    dc_out = (uint32_t)__shfl((int)(uint32_t)dc, (int)(base + holder), 64);          // (what fits the free CPUs fits a word)
+    if (top) { out.slope = __uint_as_float(top); out.tgt = holder; out.dg = dg_top; }
+    return out;
+}
+
+// The jobs of the round with take(job) in job order; returns how many.  Two barriers per FEW_THREADS jobs.
+template <class F>
+__device__ __forceinline__ uint32_t few_compact(const FewMem &M, uint32_t nj, F take) {
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    const bool in = tid < nj && take(tid);
+    const unsigned long long b = __ballot(in);
+    if (lane == 0) M.cnt[wave] = (uint32_t)__popcll(b);
+    __syncthreads();
+    uint32_t before = 0, all = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < FEW_WAVES; ++w) { const uint32_t n = M.cnt[w]; before += w < wave ? n : 0u; all += n; }
+    if (in) M.part[before + (uint32_t)__popcll(b & ((1ull << lane) - 1ull))] = tid;
+    __syncthreads();
+    return all;
+}
+
+// Where bin b is kept: lane l of few_cut takes the FEW_BINS / 64 bins from (FEW_BINS / 64) l on, one at a time.
+__device__ __forceinline__ uint32_t few_bin_at(uint32_t b) { return (b % (FEW_BINS / 64u)) * 64u + b / (FEW_BINS / 64u); }
+
+__device__ __forceinline__ void few_clear(const FewMem &M) {
+    for (uint32_t i = threadIdx.x; i < FEW_BINS; i += FEW_THREADS) { M.hg[i] = 0u; M.hc[i] = 0ull; }
+    if (threadIdx.x == 0) { M.range[0] = 0u; M.range[1] = 0xFFFFFFFFu; }
+}
+
+// One wavefront: the first bin (bin 0 holds the highest keys) whose steps, with everything before it, no longer fit
+// (FEW_BINS: all fit); usedG, usedC: the cost of the bins before it.
+__device__ __forceinline__ uint32_t few_cut(const FewMem &M, unsigned long long capG, unsigned long long capC,
+                                            unsigned long long &usedG, unsigned long long &usedC) {
+    constexpr uint32_t PER = FEW_BINS / 64u;
+    static_assert(PER <= 16u, "a row of lanes looks through one lane's bins");
+    const uint32_t lane = threadIdx.x & 63u;
+    uint32_t sg = 0;
+    unsigned long long sc = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < PER; ++i) { sg += M.hg[i * 64u + lane]; sc += M.hc[i * 64u + lane]; }
+    uint32_t ig = sg;
+    unsigned long long ic = sc;
+    wave_scan(ig, ic);
+    const unsigned long long over = __ballot(ig > capG || ic > capC);
+    if (!over) { usedG = wave_lane_u32(ig, 63u); usedC = wave_lane_u64(ic, 63u); return FEW_BINS; }
+    const uint32_t l0 = (uint32_t)__ffsll((long long)over) - 1u;
+    const unsigned long long g0 = wave_lane_u32(ig - sg, l0), c0 = wave_lane_u64(ic - sc, l0);
+    const uint32_t vg = lane < PER ? M.hg[lane * 64u + l0] : 0u;
+    const unsigned long long vc = lane < PER ? M.hc[lane * 64u + l0] : 0ull;
+    ig = vg; ic = vc;
+    row_scan(ig, ic);
+    const uint32_t i0 = (uint32_t)__ffsll((long long)__ballot(lane < PER && (g0 + ig > capG || c0 + ic > capC))) - 1u;
+    usedG = g0 + wave_lane_u32(ig - vg, i0);
+    usedC = c0 + wave_lane_u64(ic - vc, i0);
+    return l0 * PER + i0;
+}
+
+// A pass over the P jobs in M.part.  On entry the histogram is clear; on return (behind a barrier) M.gi, M.g and M.ci
+// hold what the pass leaves, freeG / freeC what is left.
+template <int PASS>
+__device__ __forceinline__ void few_pass(const Ctx &X, const FewMem &M, const FewLanes &L, uint32_t P, uint32_t lanes,
+                                         uint32_t first_seg, unsigned long long &freeG, unsigned long long &freeC) {
+    const GridDev &grid = X.grid;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    const uint32_t sub = lane & (lanes - 1u), base = lane - sub, per = 64u / lanes, mine = base / lanes;
+    const uint32_t n_mem = grid.n_mem, n_rows = grid.n_cpu * n_mem, m_top = n_mem - 1u;
+    const unsigned long long capG = freeG, capC = freeC;
+    const float *__restrict__ vals = PASS == 0 ? X.curve_thr : X.best_thr;
+    // a job per thread: the jobs in turn over the wavefronts, so that few jobs are spread over all of them
+    const uint32_t own = lane * FEW_WAVES + wave;
+    static_assert(FEW_JOBS <= FEW_THREADS, "a job per thread");
+
+    // the walks (k_hull_groups).  Costs by their low words: a step within the capacity fits a word.
+    uint32_t high = 0, low = 0xFFFFFFFFu;
+    for (uint32_t p0 = wave * per; p0 < P; p0 += FEW_WAVES * per) {
+        const bool valid = p0 + mine < P;
+        const uint32_t p = valid ? p0 + mine : P - 1u, j = M.part[p];
+        const float ref = M.ref[j];
+        const uint32_t ci = M.ci[j], g_held = PASS == 0 ? 0u : M.g[j];
+        const uint32_t npts = PASS == 0 ? M.ns[j] : grid.n_cpu;
+        const uint32_t s0 = M.s0[j], ns = M.ns[j];
+        const uint64_t jbase = (uint64_t)n_rows * (s0 - first_seg);
+        uint32_t amt = 0;
+        float v = 0.f;
+        if (sub < npts) {
+            if (PASS == 0) amt = X.tb.seg_g[s0 + sub];
+            v = PASS == 0 ? vals[jbase + (uint64_t)(ci * n_mem + m_top) * ns + sub]
+                          : vals[jbase + (uint64_t)(sub * n_mem + m_top) * ns + (uint32_t)M.gi[j]];
+        }
+        const int32_t start = PASS == 0 ? M.gi[j] : (int32_t)ci;
+        const int from = (int)(base + (start < 0 ? 0u : (uint32_t)start));
+        const float v_at = __shfl(v, from, 64);
+        float cur = start < 0 ? 0.f : v_at;
+        // the amount's cost in the pass's resource and in CPUs, and those of what the job holds (paid for already)
+        const uint32_t level = M.lvl[PASS == 0 ? ci : sub];
+        const uint32_t times = PASS == 0 ? (grid.cpu_mode ? amt : 1u) : (grid.cpu_mode ? g_held : 1u);
+        const unsigned long long cpus = (unsigned long long)level * times;
+        const uint32_t cost = PASS == 0 ? amt : (uint32_t)cpus;
+        const uint32_t cost_at = (uint32_t)__shfl((int)cost, from, 64);
+        const unsigned long long cpus_at = ((unsigned long long)(uint32_t)__shfl((int)(uint32_t)(cpus >> 32), from, 64) << 32) |
+                                           (uint32_t)__shfl((int)(uint32_t)cpus, from, 64);
+        uint32_t cost_cur = start < 0 ? 0u : cost_at;
+        const bool can = sub < npts && (PASS == 1 || amt <= capG + cost_cur) && cpus <= capC + (start < 0 ? 0ull : cpus_at);
+        int32_t cur_i = start;
+        uint32_t k = 0, my_key = 0, my_raw = 0, my_at = 0, my_from = 0, my_to = 0;
+        int32_t my_before = -1;
+        float prev = __uint_as_float(0x7F800000u);
+        bool walking = valid;
+        while (__ballot(walking)) {
+            uint32_t best = 0;
+            if (walking && can && (int32_t)sub > cur_i && v > cur) {
+                float sl = (v - cur) / ref;
+                sl = sl / (float)(cost - cost_cur);
+                best = __float_as_uint(sl);
+            }
+            const uint32_t top = few_max(best, lanes, lane);
+            walking = walking && top != 0u;
+            const uint32_t holder = few_bits(__ballot(best == top), base, lanes);
+            const int src = (int)(base + (holder ? holder - 1u : 0u));
+            const uint32_t top_cost = (uint32_t)__shfl((int)cost, src, 64);
+            const float top_val = __shfl(v, src, 64);
+            if (walking) {
+                prev = __uint_as_float(top) < prev ? __uint_as_float(top) : prev;
+                if (sub == k) {
+                    my_key = __float_as_uint(prev); my_raw = top; my_at = (uint32_t)src - base;
+                    my_before = cur_i; my_from = cost_cur; my_to = top_cost;
+                }
+                cur = top_val;
+                cur_i = src - (int)base;
+                cost_cur = top_cost;
+                ++k;
+            }
+        }
+        if (valid) {
+            uint32_t dg = 0, dc = 0;
+            if (sub < k) {
+                if (PASS == 0) {
+                    dg = my_to - my_from;
+                    dc = M.lvl[ci] * (grid.cpu_mode ? dg : my_before < 0 ? 1u : 0u);
+                } else {
+                    dc = my_to - my_from;
+                }
+                high = my_key > high ? my_key : high;
+                low = my_key < low ? my_key : low;
+            }
+            const uint32_t e = p * lanes + sub;
+            L.val[e] = v;
+            if (PASS == 0) L.amt[e] = amt;
+            L.step[e] = make_uint4(sub < k ? my_key : 0u, my_raw, my_at | dg << 16, dc);
+        }
+    }
+    high = wave_max_u32_rows(high);
+    low = wave_min_u32_rows(low);
+    if (lane == 0 && high) { atomicMax(&M.range[0], high); atomicMin(&M.range[1], low); }
+    __syncthreads();
+    // The threshold: steps whose key lies less than `limit` below the highest one.  Any threshold whose whole set of steps
+    // fits selects a prefix of the order: FEW_BINS bins over the keys that occur, and what is left of the bin where the
+    // capacity ends is taken step by step.  With more than FEW_FINE jobs that bin is divided once more, which takes 1.2 us
+    // and saves turns of 1 to 3 us (1,000 jobs: 10 turns without, 2 with).  (4,096 bins, scanned by all wavefronts: 3.7 us
+    // for two levels, this 1.0 for one.)
+    const uint32_t top_key = M.range[0];
+    uint32_t shift = 0, from = 0;                              // bins are 2^shift wide and begin `from` below the highest key
+    if (top_key) { const uint32_t span = top_key - M.range[1]; shift = span < FEW_BINS ? 0u : 22u - (uint32_t)__clz((int)span); }
+    auto count = [&](const uint4 &s) {
+        const uint32_t at = top_key - s.x - from;
+        if (at >> shift >= FEW_BINS) return;
+        const uint32_t bin = few_bin_at(at >> shift);
+        if (PASS == 0 && s.z >> 16) atomicAdd(&M.hg[bin], s.z >> 16);
+        if (s.w) atomicAdd(&M.hc[bin], (unsigned long long)s.w);
+    };
+    unsigned long long limit;
+    for (uint32_t level = 0;; ++level) {
+        for (uint32_t e = tid; e < P * lanes; e += FEW_THREADS) {
+            const uint4 s = L.step[e];
+            if (s.x) count(s);
+        }
+        __syncthreads();
+        if (wave == 0) {
+            unsigned long long usedG, usedC;
+            const uint32_t cut = few_cut(M, freeG, freeC, usedG, usedC);
+            if (lane == 0) { M.box[0] = freeG - usedG; M.box[1] = freeC - usedC; M.box[2] = cut; }
+        }
+        __syncthreads();
+        freeG = M.box[0];
+        freeC = M.box[1];
+        const uint32_t cut = (uint32_t)M.box[2];
+        limit = ((unsigned long long)cut << shift) + from;
+        if (level == 1u || cut == FEW_BINS || shift == 0u || P <= FEW_FINE) break;
+        from = (uint32_t)limit;                                // the bin that did not fit, divided
+        shift = shift > 10u ? shift - 10u : 0u;
+        for (uint32_t i = tid; i < FEW_BINS; i += FEW_THREADS) { M.hg[i] = 0u; M.hc[i] = 0ull; }
+        __syncthreads();
+    }
+    // the prefix goes to every job at once; its next step: the walk's if it still fits, else a search (apply_job)
+    for (uint32_t p0 = wave * per; p0 < P; p0 += FEW_WAVES * per) {
+        const bool valid = p0 + mine < P;
+        const uint32_t p = valid ? p0 + mine : P - 1u, j = M.part[p], e0 = p * lanes;
+        const uint4 s = L.step[e0 + sub];
+        const uint32_t n = (uint32_t)__popcll((__ballot(s.x && top_key - s.x < limit) >> base) & (~0ull >> (64u - lanes)));
+        int32_t at = PASS == 0 ? M.gi[j] : (int32_t)M.ci[j];
+        const uint32_t g_held = PASS == 0 ? 0u : M.g[j], ci = M.ci[j];
+        if (n) at = (int32_t)(L.step[e0 + n - 1u].z & 0xFFFFu);
+        const uint4 next = n < lanes ? L.step[e0 + n] : make_uint4(0u, 0u, 0u, 0u);
+        Step nx = {0.f, 0u, 0u};
+        uint32_t dc = next.w;
+        bool search = false;
+        if (next.x) {
+            nx = Step{__uint_as_float(next.y), next.z & 0xFFFFu, next.z >> 16};
+            search = nx.dg > freeG || dc > freeC;
+        }
+        if (__ballot(search)) {
+            uint32_t dc2;
+            const Step found = few_search<PASS>(grid, M.lvl, lanes, L.val[e0 + sub], PASS == 0 ? L.amt[e0 + sub] : 0u, at, g_held, ci,
+                                                M.ref[j], freeG, freeC, dc2);
+            if (search) { nx = found; dc = dc2; }
+        }
+        if (valid && sub == 0) {
+            if (n) {
+                if (PASS == 0) { M.gi[j] = at; M.g[j] = L.amt[e0 + (uint32_t)at]; }
+                else M.ci[j] = (uint32_t)at;
+            }
+            M.slope[p] = nx.slope;
+            M.to[p] = nx.tgt | nx.dg << 16;
+            M.dc[p] = dc;
+        }
+    }
+    __syncthreads();
+    // Step by step on what is left, by the first wavefront: the highest slope, the lower job among equals.  A step that
+    // no longer fits stays as an upper bound of what its job can still do; where a bound comes out highest, all
+    // wavefronts make the bounds that could win exact (tail_run's rule).
+    for (;;) {
+        if (wave == 0) {
+            uint32_t command = 0, exact = 0, exact_p = 0;
+            while (PASS == 0 ? freeG != 0 : freeC != 0) {
+                uint32_t best = 0, best_p = 0, sure = 0, sure_p = 0;
+                for (uint32_t p0 = lane; p0 < P; p0 += 256u) {   // four of the lane's jobs per round of reads
+                    float sl[4];
+                    uint32_t to[4], dc[4];
+#pragma unroll
+                    for (uint32_t u = 0; u < 4; ++u) {
+                        const uint32_t p = p0 + 64u * u < P ? p0 + 64u * u : p0;
+                        sl[u] = M.slope[p]; to[u] = M.to[p]; dc[u] = M.dc[p];
+                    }
+#pragma unroll
+                    for (uint32_t u = 0; u < 4; ++u) {
+                        const uint32_t p = p0 + 64u * u;
+                        if (p >= P) continue;
+                        if (sl[u] > 0.f && ((to[u] >> 16) > freeG || dc[u] > freeC)) { sl[u] = -sl[u]; M.slope[p] = sl[u]; }
+                        const uint32_t b = __float_as_uint(sl[u]) & 0x7FFFFFFFu;
+                        if (b > best) { best = b; best_p = p; }
+                        if (sl[u] > 0.f && b > sure) { sure = b; sure_p = p; }
+                    }
+                }
+                const uint32_t top = wave_max_u32_rows(best);
+                if (!top) break;
+                const uint32_t p = wave_min_u32_rows(best == top ? best_p : 0xFFFFFFFFu);
+                if (!(M.slope[p] > 0.f)) {                     // a bound
+                    exact = wave_max_u32_rows(sure);
+                    exact_p = wave_min_u32_rows(exact && sure == exact ? sure_p : 0xFFFFFFFFu);
+                    command = 1;
+                    break;
+                }
+                const uint32_t to = M.to[p], j = M.part[p], e = p * lanes + sub;
+                freeG -= to >> 16;
+                freeC -= M.dc[p];
+                const int32_t at = (int32_t)(to & 0xFFFFu);
+                const uint32_t ci = PASS == 0 ? M.ci[j] : 0u, g_held = PASS == 0 ? 0u : M.g[j];
+                const uint32_t amt = PASS == 0 ? L.amt[e] : 0u;
+                uint32_t dc;
+                const Step nx = few_search<PASS>(grid, M.lvl, lanes, L.val[e], amt, at, g_held, ci, M.ref[j], freeG, freeC, dc);
+                const uint32_t g_at = (uint32_t)__shfl((int)amt, (int)(base + (uint32_t)at), 64);
+                if (lane == 0) {
+                    if (PASS == 0) { M.gi[j] = at; M.g[j] = g_at; }
+                    else M.ci[j] = (uint32_t)at;
+                    M.slope[p] = nx.slope;
+                    M.to[p] = nx.tgt | nx.dg << 16;
+                    M.dc[p] = dc;
+                }
+                __builtin_amdgcn_wave_barrier();               // the lanes read each other's words in the next turn
+            }
+            if (lane == 0) {
+                M.box[0] = freeG;
+                M.box[1] = freeC;
+                M.box[2] = ((unsigned long long)command << 32) | exact;
+                M.box[3] = exact_p;
+            }
+        }
+        __syncthreads();
+        freeG = M.box[0];
+        freeC = M.box[1];
+        const unsigned long long told = M.box[2];
+        const uint32_t exact = (uint32_t)told, exact_p = (uint32_t)M.box[3];
+        if (!(told >> 32)) break;
+        const float sl_own = own < P ? M.slope[own] : 0.f;
+        const uint32_t b_own = __float_as_uint(-sl_own);
+        unsigned long long todo = __ballot(sl_own < 0.f && (b_own > exact || (b_own == exact && own < exact_p)));
+        while (todo) {                                         // 64 / lanes of the wavefront's jobs at a time
+            uint32_t l = 64u;
+            for (uint32_t g = 0; g < per && todo; ++g) {
+                const uint32_t first = (uint32_t)__ffsll((long long)todo) - 1u;
+                todo &= todo - 1ull;
+                if (g == mine) l = first;
+            }
+            const bool need = l < 64u;
+            const uint32_t p = (need ? l : 0u) * FEW_WAVES + wave, j = M.part[need ? p : 0u];
+            uint32_t dc;
+            const int32_t at = PASS == 0 ? M.gi[j] : (int32_t)M.ci[j];
+            const uint32_t ci = M.ci[j], g_held = PASS == 0 ? 0u : M.g[j];
+            const float v = need ? L.val[p * lanes + sub] : 0.f;
+            const uint32_t amt = PASS == 0 && need ? L.amt[p * lanes + sub] : 0u;
+            const Step nx = few_search<PASS>(grid, M.lvl, lanes, v, amt, at, g_held, ci, M.ref[j], freeG, freeC, dc);
+            if (need && sub == 0) {
+                M.slope[p] = nx.slope;
+                M.to[p] = nx.tgt | nx.dg << 16;
+                M.dc[p] = dc;
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// Where the round's jobs' segments are; for a job per thread (tid < nj).
+__device__ __forceinline__ void few_jobs(const Ctx &X, const FewMem &M, uint32_t J0, uint32_t nj) {
+    const uint32_t tid = threadIdx.x;
+    if (tid < RK_MAX_CPU_LEVELS) M.lvl[tid] = X.grid.cpu_levels[tid];
+    if (tid < nj) {
+        const uint32_t ju = job_of(X, J0 + tid);
+        const uint32_t s0 = X.tb.seg_off[ju];
+        M.s0[tid] = s0;
+        M.ns[tid] = X.tb.seg_off[ju + 1] - s0;
+        M.ref[tid] = X.ref_thr[ju];
+    }
+}
+
+// The memory step that ends a round: every thread writes its job's wish (a record per job of the round in `assign`), the
+// first wavefront closes the round.  The thread's wish is returned.  sums: 2 * FEW_WAVES doubles in LDS.
+__device__ __forceinline__ rk_assign few_memory(const Ctx &X, const FewMem &M, uint32_t rnd, uint32_t nj, uint32_t first_seg,
+                                                double *sums, rk_assign *assign, float *totals) {
+    const uint32_t tid = threadIdx.x;
+    double cost_d = 0.0, val_d = 0.0;
+    rk_assign out = {0u, 0u, 0.f, RK_NO_PLAN, 0.f};
+    if (tid < nj) {
+        out = mem_wish(X, M.gi[tid], M.g[tid], M.ci[tid], M.s0[tid], M.ns[tid], first_seg, M.ref[tid], cost_d, val_d);
+        assign[tid] = out;
+    }
+    cost_d = wave_sum_f64(cost_d);
+    val_d = wave_sum_f64(val_d);
+    if ((tid & 63u) == 0) { sums[tid >> 6] = cost_d; sums[FEW_WAVES + (tid >> 6)] = val_d; }
+    __syncthreads();
+    if (tid < 64u) {
+        const bool has = tid < FEW_WAVES;
+        const double wish = wave_sum_f64(has ? sums[tid] : 0.0), val = wave_sum_f64(has ? sums[FEW_WAVES + tid] : 0.0);
+        mem_close_round(X, M.gi, M.g, M.ci, rnd, wish, val, assign, totals);
+    }
+    return out;
+}
+
+// One workgroup per round; near: per-lane words in LDS.
+__global__ __launch_bounds__(FEW_THREADS) void k_round_few(Ctx X, JobState st, uint32_t max_jobs, uint32_t lanes0, uint32_t lanes1,
+                                                           uint32_t near, rk_assign *__restrict__ assign,
+                                                           float *__restrict__ totals) {
+    extern __shared__ __align__(16) unsigned long long lds_few[];
+    __shared__ double sums[2 * FEW_WAVES];
+    const uint32_t rnd = blockIdx.x, tid = threadIdx.x;
+    uint32_t J0, J1;
+    rk_cluster cl;
+    round_of(X.R, rnd, J0, J1, cl);
+    const uint32_t nj = J1 - J0, jrel0 = J0 - X.jb, first_seg = X.tb.seg_off[X.jb];
+    uint32_t *lds_lanes;
+    const FewMem M = few_mem(lds_few, max_jobs, &lds_lanes);
+    const FewLanes L = few_lane_mem(lds_lanes, near);
+    few_jobs(X, M, J0, nj);
+    Floor fl = {-1, 0u, RK_JOB_OUT};
+    if (tid < nj) {
+        fl = floor_of(st, jrel0 + tid);
+        M.gi[tid] = fl.gi;
+        M.g[tid] = fl.gi < 0 ? 0u : X.tb.seg_g[M.s0[tid] + (uint32_t)fl.gi];
+        M.ci[tid] = fl.ci;
+    }
+    unsigned long long freeG, freeC;
+    pass_caps<0>(X.R, cl, st, rnd, freeG, freeC);
+    few_clear(M);
+    uint32_t P = few_compact(M, nj, [&](uint32_t) { return fl.state == RK_JOB_NORMAL && freeG != 0; });
+    if (P) few_pass<0>(X, M, L, P, lanes0, first_seg, freeG, freeC);
+    few_clear(M);
+    P = few_compact(M, nj, [&](uint32_t j) { return fl.state == RK_JOB_NORMAL && M.gi[j] >= 0 && freeC != 0; });
+    if (P) few_pass<1>(X, M, L, P, lanes1, first_seg, freeG, freeC);
+    few_memory(X, M, rnd, nj, first_seg, sums, assign + jrel0, totals);
 }
 
 // ------------------------------------------------------------------ service-level floors
@@ -2019,6 +2533,7 @@ int32_t rk_allocate_setup(rk_ctx *ctx) {
     for (const void *f : big) RK_HIP(ctx, hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 152 * 1024));
     const void *small[] = {reinterpret_cast<const void *>(k_select_small<0, SMALL_ROUND_JOBS / TAIL_THREADS>),
                            reinterpret_cast<const void *>(k_select_small<1, SMALL_ROUND_JOBS / TAIL_THREADS>)};
+    RK_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(k_round_few), hipFuncAttributeMaxDynamicSharedMemorySize, 144 * 1024));
     for (const void *f : small) RK_HIP(ctx, hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024));
     return RK_OK;
 }
@@ -2045,7 +2560,12 @@ int32_t rk_launch_allocate(rk_ctx *ctx, const float *ref_thr, const TableDev &tb
     H.stride = n_jobs ? n_jobs : 1;
     H.width = max_segs_per_job > grid->n_cpu ? max_segs_per_job : grid->n_cpu;   // the longest walk of either pass
     if (H.width == 0) H.width = 1;
-    const size_t entries = (size_t)H.stride * H.width;
+    // Rounds of few jobs take one launch, and none of the walk buffers and histograms.
+    const uint32_t lanes0 = few_lanes(max_segs_per_job), lanes1 = few_lanes(grid->n_cpu);
+    const uint32_t holders = one_cluster && !given && one_cluster->G < max_jobs ? one_cluster->G : max_jobs;   // jobs with GPUs
+    const bool few = max_jobs > 0 && max_jobs <= FEW_JOBS && max_segs_per_job <= 64u &&
+                     (uint64_t)max_jobs * lanes0 <= FEW_GPU_LANES && (uint64_t)holders * lanes1 <= FEW_CPU_LANES;
+    const size_t entries = few ? 0 : (size_t)H.stride * H.width;
     if ((rc = scratch_typed(ctx, arena, SL_HULL_KEY, entries, &H.key))) return rc;
     if ((rc = scratch_typed(ctx, arena, SL_HULL_RAW, entries, &H.raw))) return rc;
     if ((rc = scratch_typed(ctx, arena, SL_HULL_TGT, entries, &H.tgt))) return rc;
@@ -2074,7 +2594,7 @@ int32_t rk_launch_allocate(rk_ctx *ctx, const float *ref_thr, const TableDev &tb
         if ((rc = scratch_typed(ctx, arena, SL_FL_CAP0, (size_t)n_rounds * 2, &st.cap0))) return rc;
     }
     Hist hist;
-    const size_t hist_bins = (size_t)n_rounds * 4 * BINS;
+    const size_t hist_bins = few ? 0 : (size_t)n_rounds * 4 * BINS;
     if ((rc = scratch_typed(ctx, arena, SL_HIST_G, hist_bins, &hist.g))) return rc;
     if ((rc = scratch_typed(ctx, arena, SL_HIST_C, hist_bins, &hist.c))) return rc;
 
@@ -2097,6 +2617,13 @@ int32_t rk_launch_allocate(rk_ctx *ctx, const float *ref_thr, const TableDev &tb
     if (sla && !given) {
         k_floors<<<n_rounds, FLOOR_THREADS, (size_t)mj * 8, s>>>(X, st, *sla, mj);
         RK_CHECK_LAUNCH(ctx, "k_floors");
+    }
+    if (few) {
+        const uint32_t jobs = (max_jobs + 3u) & ~3u, gpu = max_jobs * lanes0, cpu = holders * lanes1, near = gpu > cpu ? gpu : cpu;
+        const size_t few_lds = FEW_FIXED_BYTES + (size_t)jobs * FEW_JOB_BYTES + (size_t)near * FEW_LANE_BYTES;
+        k_round_few<<<n_rounds, FEW_THREADS, few_lds, s>>>(X, st, max_jobs, lanes0, lanes1, near, assign, totals);
+        RK_CHECK_LAUNCH(ctx, "k_round_few");
+        return RK_OK;
     }
     bool closed = false;
     if ((rc = launch_pass<0>(ctx, X, st, H, hist, n_rounds, n_jobs, mj, max_segs_per_job, lds, hists ? hist_bins : 0, assign,

@@ -1,0 +1,52 @@
+"""Rounds that one workgroup takes whole (k_round_few): job counts and amounts around the lines that lead there, against
+the oracle's greedy on the same drawn curves, record for record.  Values are coarse, so slopes tie exactly."""
+import numpy as np
+import pytest
+
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+
+def drawn_curves(orc, wl, ot, rng):
+    n_rows = len(wl.grid.cpu_levels) * len(wl.grid.mem_levels_gb)
+    n = ot.n_segments(n_rows)
+    g_of = np.concatenate([np.tile(ot.seg_g[ot.seg_off[j]:ot.seg_off[j + 1]], n_rows) for j in range(wl.n_jobs)])
+    bt = (g_of ** rng.uniform(0.3, 1.0, n)) * rng.uniform(0.5, 1.5, n)
+    bt = np.round(bt * 8) / 8
+    bt[rng.uniform(size=n) < 0.15] = 0
+    bt = bt.astype(np.float32)
+    bp = rng.integers(0, 1000, n).astype(np.uint32)
+    bp[bt == 0] = 0xFFFFFFFF
+    return bt, bp, orc.curves(ot, wl.grid, bt, bp)[0]
+
+
+@pytest.mark.parametrize("n_jobs,g_max,most", [(1, 16, 16), (3, 256, 64), (31, 256, 64), (33, 256, 64), (63, 64, 32), (65, 64, 32),
+                                               (127, 16, 16), (128, 16, 16), (129, 16, 16)])
+@pytest.mark.parametrize("n_cpu,per_gpu", [(1, 1), (5, 1), (16, 0), (17, 1), (33, 0), (64, 1)])
+def test_rounds_of_few_jobs(orc, n_jobs, g_max, most, n_cpu, per_gpu):
+    import paper_2408_08586_amd as rk
+    from gpu_harness import DeviceRun
+    rng = np.random.default_rng(1000 * n_jobs + n_cpu)
+    base = workloads.tiny()
+    kinds = np.array([[96, 1680, 1], [24, 64, 1], [12, 32, 1], [32, 128, 2]], np.uint32)
+    ints = kinds[rng.integers(0, len(kinds), n_jobs)]
+    ints[0] = kinds[0]
+    coef = np.tile(base.coef[:1], (n_jobs, 1))
+    coef[:, 16] = rng.uniform(0.5, 4.0, n_jobs).astype(np.float32)
+    grid = workloads.Grid(np.arange(1, n_cpu + 1, dtype=np.uint32), per_gpu, np.array([64.0, 256.0], np.float32), 0)
+    wl = workloads.Workload("few", coef, ints, workloads.Bounds(g_max=g_max), grid, workloads.Env(), workloads.Cluster(8, 8, 64.0))
+    ot = orc.enumerate_plans(wl.ints, wl.bounds)
+    assert most // 2 < np.diff(ot.seg_off).max() <= most
+    bt, bp, ct = drawn_curves(orc, wl, ot, rng)
+    run = DeviceRun(wl)
+    run.enumerate()
+    d_bt, d_bp, d_ct = run.dev_f32(bt), run.dev_u32(bp), run.dev_f32(ct)
+    for G, C, M in ((n_jobs, 3 * n_jobs, 1e9), (4 * n_jobs, 10 ** 6, 1e9), (7, 40, 300.0), (40 * n_jobs, 5 * n_jobs, 1e4), (0, 5, 64.0),
+                    (2 ** 20, 2 ** 32 - 1, 1e9)):
+        cl = workloads.Cluster(G, C, M)
+        e_assign, e_total, _ = orc.greedy(wl.coef[:, 16], ot, wl.grid, cl, bt, bp, ct)
+        assign, total = run.allocate(d_bt, d_bp, d_ct, cluster=rk.make_cluster(cl))
+        assert np.array_equal(assign, e_assign), (G, C, M)
+        assert total == pytest.approx(e_total, rel=1e-6, abs=1e-12)
+    run.close()
