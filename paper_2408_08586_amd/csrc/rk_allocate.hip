@@ -40,6 +40,7 @@
 #include "rk_internal.h"
 #include "rk_model.h"
 #include "rk_loop.h"
+#include "rk_sim.h"
 
 namespace {
 
@@ -1145,7 +1146,7 @@ constexpr size_t SELECT_HIST_BYTES = (size_t)BINS * 12;
 
 __device__ __forceinline__ void mem_wish_job(const Ctx &X, const JobState &st, uint32_t j, rk_assign *__restrict__ assign,
                                              double &cost_d, double &val_d);
-__device__ void mem_close_round(const Ctx &X, const int32_t *gi_of, const uint32_t *g_of, const uint32_t *ci_of, uint32_t rnd,
+__device__ bool mem_close_round(const Ctx &X, const int32_t *gi_of, const uint32_t *g_of, const uint32_t *ci_of, uint32_t rnd,
                                 double wish, double val, rk_assign *__restrict__ assign, float *__restrict__ totals);
 
 template <int PASS, int KMAX>
@@ -1226,26 +1227,25 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_select_small(Ctx X, uint32_t m
 // Large rounds: k_mem_wish (a thread per job) and k_mem_finish (a wavefront per
 // round); small rounds: the workgroup of the CPU pass's selection does both.
 
-// the wish of a job that holds segment gi (-1: nothing) with g GPUs at CPU level c_lvl; s0, ns: its segments; adds its
-// cost and its normalised throughput to the two sums
-__device__ __forceinline__ rk_assign mem_wish(const Ctx &X, int32_t gi, uint32_t g, uint32_t c_lvl, uint32_t s0, uint32_t ns,
-                                              uint32_t first_seg, float ref, double &cost_d, double &val_d) {
+// the wish of a job that holds segment gi (-1: nothing) with g GPUs at CPU level c_lvl of level_cpus CPUs; s0, ns: its
+// segments; adds its cost and its normalised throughput to the two sums
+__device__ __forceinline__ rk_assign mem_wish(const Ctx &X, int32_t gi, uint32_t g, uint32_t c_lvl, uint32_t level_cpus, uint32_t s0,
+                                              uint32_t ns, uint32_t first_seg, float ref, double &cost_d, double &val_d) {
     const GridDev &grid = X.grid;
     const uint32_t n_mem = grid.n_mem, n_rows = grid.n_cpu * n_mem;
     rk_assign out = {0u, 0u, 0.f, RK_NO_PLAN, 0.f};
     if (gi < 0) return out;
     const uint64_t base = (uint64_t)n_rows * (s0 - first_seg) + (uint64_t)(c_lvl * n_mem) * ns + (uint32_t)gi;
-    float bv = 0.f;
+    float bv = 0.f, cost = 0.f;
     uint32_t bm = 0;
     for (uint32_t m = 0; m < n_mem; ++m) {
         const float v = X.best_thr[base + (uint64_t)m * ns];
-        if (v > bv) { bv = v; bm = m; }
+        if (v > bv) { bv = v; bm = m; cost = grid.mem_levels_gb[m]; }
     }
     if (bv > 0.f) {
-        float cost = grid.mem_levels_gb[bm];
         if (grid.mem_mode) cost = cost * (float)g;
         out.g = g;
-        out.c = (uint32_t)cpu_cost(grid, c_lvl, g);
+        out.c = grid.cpu_mode ? level_cpus * g : level_cpus;
         out.mem_gb = cost;
         out.plan = X.best_plan[base + (uint64_t)bm * ns];
         out.thr = bv;
@@ -1264,7 +1264,8 @@ __device__ __forceinline__ void mem_wish_job(const Ctx &X, const JobState &st, u
     if (gi >= 0) {
         const uint32_t ju = job_of(X, j);
         const uint32_t s0 = X.tb.seg_off[ju], ns = X.tb.seg_off[ju + 1] - s0;
-        out = mem_wish(X, gi, st.g[jrel], st.ci[jrel], s0, ns, X.tb.seg_off[X.jb], X.ref_thr[ju], cost_d, val_d);
+        const uint32_t c_lvl = st.ci[jrel];
+        out = mem_wish(X, gi, st.g[jrel], c_lvl, X.grid.cpu_levels[c_lvl], s0, ns, X.tb.seg_off[X.jb], X.ref_thr[ju], cost_d, val_d);
     }
     assign[jrel] = out;
 }
@@ -1291,8 +1292,9 @@ __global__ __launch_bounds__(JOB_THREADS) void k_mem_wish(Ctx X, JobState st, rk
 }
 
 // One wavefront (threadIdx.x = lane) closes a round whose wishes sum to `wish` GiB and `val` normalised throughput.
-// gi_of, g_of, ci_of: what the round's jobs hold, assign: their records, from its first job on.
-__device__ void mem_close_round(const Ctx &X, const int32_t *gi_of, const uint32_t *g_of, const uint32_t *ci_of, uint32_t rnd,
+// gi_of, g_of, ci_of: what the round's jobs hold, assign: their records, from its first job on.  True: the records were
+// decided in job order and replace the wishes.
+__device__ bool mem_close_round(const Ctx &X, const int32_t *gi_of, const uint32_t *g_of, const uint32_t *ci_of, uint32_t rnd,
                                 double wish, double val, rk_assign *__restrict__ assign, float *__restrict__ totals) {
     const uint32_t tid = threadIdx.x;
     uint32_t J0, J1;
@@ -1303,7 +1305,7 @@ __device__ void mem_close_round(const Ctx &X, const int32_t *gi_of, const uint32
     const uint32_t n_mem = grid.n_mem, n_rows = grid.n_cpu * n_mem;
     if (wish <= 0.99 * (double)cl.host_mem_gb) {
         if (tid == 0) totals[rnd] = (float)val;
-        return;
+        return false;
     }
     // in job order: lanes load a batch of 64 jobs, then take their decisions one after the other
     float freeM = cl.host_mem_gb;
@@ -1371,6 +1373,7 @@ __device__ void mem_close_round(const Ctx &X, const int32_t *gi_of, const uint32
     }
     sum = wave_sum_f64(sum);
     if (tid == 0) totals[rnd] = (float)sum;
+    return true;
 }
 
 // One wavefront per round.
@@ -1408,6 +1411,8 @@ constexpr int FEW_THREADS = 1024, FEW_WAVES = FEW_THREADS / 64;
 constexpr uint32_t FEW_JOBS = FEW_THREADS;        // at most a job per thread
 constexpr uint32_t FEW_GPU_LANES = 2048, FEW_CPU_LANES = 4096;   // of a round: jobs times lanes of a job
 constexpr uint32_t FEW_BINS = 1024, FEW_FINE = 128;
+constexpr uint32_t FEW_SIM_LANES = 16384;         // of a simulation (most of its jobs have come and gone, or are yet to come)
+constexpr size_t FEW_SIM_LDS = 152 * 1024;
 
 struct FewMem {                  // per round, in LDS
     unsigned long long *hc;      // histogram of a pass: CPUs and GPUs of the steps per bin
@@ -1837,14 +1842,15 @@ __device__ __forceinline__ void few_jobs(const Ctx &X, const FewMem &M, uint32_t
 }
 
 // The memory step that ends a round: every thread writes its job's wish (a record per job of the round in `assign`), the
-// first wavefront closes the round.  The thread's wish is returned.  sums: 2 * FEW_WAVES doubles in LDS.
+// first wavefront closes the round.  The thread's wish is returned; M.box[0], behind the next barrier: the records in `assign`
+// are others.  sums: 2 * FEW_WAVES doubles in LDS.
 __device__ __forceinline__ rk_assign few_memory(const Ctx &X, const FewMem &M, uint32_t rnd, uint32_t nj, uint32_t first_seg,
                                                 double *sums, rk_assign *assign, float *totals) {
     const uint32_t tid = threadIdx.x;
     double cost_d = 0.0, val_d = 0.0;
     rk_assign out = {0u, 0u, 0.f, RK_NO_PLAN, 0.f};
     if (tid < nj) {
-        out = mem_wish(X, M.gi[tid], M.g[tid], M.ci[tid], M.s0[tid], M.ns[tid], first_seg, M.ref[tid], cost_d, val_d);
+        out = mem_wish(X, M.gi[tid], M.g[tid], M.ci[tid], M.lvl[M.ci[tid]], M.s0[tid], M.ns[tid], first_seg, M.ref[tid], cost_d, val_d);
         assign[tid] = out;
     }
     cost_d = wave_sum_f64(cost_d);
@@ -1854,7 +1860,8 @@ __device__ __forceinline__ rk_assign few_memory(const Ctx &X, const FewMem &M, u
     if (tid < 64u) {
         const bool has = tid < FEW_WAVES;
         const double wish = wave_sum_f64(has ? sums[tid] : 0.0), val = wave_sum_f64(has ? sums[FEW_WAVES + tid] : 0.0);
-        mem_close_round(X, M.gi, M.g, M.ci, rnd, wish, val, assign, totals);
+        const bool anew = mem_close_round(X, M.gi, M.g, M.ci, rnd, wish, val, assign, totals);
+        if (tid == 0) M.box[0] = anew ? 1ull : 0ull;
     }
     return out;
 }
@@ -1890,6 +1897,111 @@ __global__ __launch_bounds__(FEW_THREADS) void k_round_few(Ctx X, JobState st, u
     P = few_compact(M, nj, [&](uint32_t j) { return fl.state == RK_JOB_NORMAL && M.gi[j] >= 0 && freeC != 0; });
     if (P) few_pass<1>(X, M, L, P, lanes1, first_seg, freeG, freeC);
     few_memory(X, M, rnd, nj, first_seg, sums, assign + jrel0, totals);
+}
+
+// A pass whose per-lane words lie in LDS where they fit, else in memory.
+template <int PASS>
+__device__ __forceinline__ void few_pass_anywhere(const Ctx &X, const FewMem &M, uint32_t *lds_lanes, uint32_t near, uint32_t *far,
+                                                  uint32_t n_far, uint32_t P, uint32_t lanes, uint32_t first_seg,
+                                                  unsigned long long &freeG, unsigned long long &freeC) {
+    if (P * lanes <= near) few_pass<PASS>(X, M, few_lane_mem(lds_lanes, near), P, lanes, first_seg, freeG, freeC);
+    else few_pass<PASS>(X, M, few_lane_mem(far, n_far), P, lanes, first_seg, freeG, freeC);
+}
+
+// Ticks [tick, end) of a simulation of at most FEW_JOBS jobs under the greedy, in one workgroup: what a job does between
+// the ticks stays in its thread's registers, a round is k_round_few's.  A tick that starts from what the last round started
+// from has that round's result.  As launches of their own (the round's four kernels and k_sim_step, replayed as a graph)
+// a tick with a round took 40 us, most of it launches and what one kernel leaves for the next in memory: 406 jobs on 64
+// GPUs, 720 ticks 19.3 ms then, 10.1 now; 30 jobs 8.2 us per tick and 2.7.  Every job queued at once is its longest: up to
+// 1,000 jobs on 64 GPUs, 300 ticks, 10.6 and 9.5 ms, on 512 GPUs 12.6 and 12.3, which is where FEW_SIM_LANES ends it.
+// first: the simulation begins with this launch; otherwise the state is where the launch before left it.
+__global__ __launch_bounds__(FEW_THREADS) void k_sim_few(Ctx X, SimArgs A, uint32_t tick, uint32_t end, uint32_t first, uint32_t lanes0,
+                                                         uint32_t lanes1, uint32_t near, uint32_t *far, uint32_t n_far,
+                                                         rk_assign *__restrict__ assign, float *__restrict__ tick_total) {
+    extern __shared__ __align__(16) unsigned long long lds_few[];
+    __shared__ double sums[2 * FEW_WAVES];
+    __shared__ unsigned long long frozen_c[2];
+    __shared__ uint32_t frozen_g[2], frozen_n[2], used_g[2];   // of a tick, in two copies used in turn
+    const uint32_t tid = threadIdx.x, J = A.n_jobs, first_seg = X.tb.seg_off[0];
+    uint32_t *lds_lanes;
+    const FewMem M = few_mem(lds_few, J, &lds_lanes);
+    few_jobs(X, M, 0u, J);
+    SimJob s = {0u, 0u, RK_NO_PLAN, 0u, 0.0, 0.0, 0.0, -1.0, false};
+    int32_t seg = -1;
+    uint32_t lvl = 0;
+    double arrival = 0.0, work = 0.0, delta = 0.0;
+    const bool mine = tid < J;
+    if (mine) {
+        arrival = A.arrival[tid]; work = A.work[tid]; delta = A.delta[tid];
+        if (!first) {
+            s = SimJob{A.S.g[tid], A.S.c[tid], A.S.plan[tid], A.n_reconf[tid], A.S.owed[tid], A.held[tid], A.progress[tid],
+                       A.finish[tid], A.S.done[tid] != 0};
+            seg = A.S.seg[tid]; lvl = A.S.lvl[tid];
+        }
+    }
+    if (tid < 2u) { frozen_c[tid] = 0ull; frozen_g[tid] = 0u; frozen_n[tid] = 0u; used_g[tid] = 0u; }
+    Floor fl = {-1, 0u, RK_JOB_OUT};
+    rk_assign a = {0u, 0u, 0.f, RK_NO_PLAN, 0.f};
+    float total = 0.f;
+    __syncthreads();
+    for (bool known = false; tick < end; ++tick, known = true) {
+        const double t = (double)tick * A.dt;
+        const uint32_t half = tick & 1u;
+        // opens the tick: who takes part, who is frozen and what they hold
+        Floor now = {-1, 0u, RK_JOB_OUT};
+        if (mine && arrival <= t && !s.done) {
+            now.state = RK_JOB_NORMAL;
+            if (sim_frozen(s.g, s.held, s.n_reconf, delta, A.gate)) now = Floor{seg, lvl, RK_JOB_FROZEN};
+        }
+        const bool frozen = now.state == RK_JOB_FROZEN;
+        if (frozen) {
+            atomicAdd(&frozen_g[half], s.g);
+            atomicAdd(&frozen_c[half], (unsigned long long)M.lvl[lvl] * (X.grid.cpu_mode ? s.g : 1u));
+            atomicAdd(&frozen_n[half], 1u);
+        }
+        const bool other = now.state != fl.state || now.gi != fl.gi || now.ci != fl.ci;
+        fl = now;
+        if (__syncthreads_or(other || !known)) {
+            const unsigned long long hg = frozen_g[half], hc = frozen_c[half];
+            unsigned long long freeG = hg < A.cl.G ? A.cl.G - hg : 0ull, freeC = hc < A.cl.C ? A.cl.C - hc : 0ull;
+            if (mine) {
+                M.gi[tid] = fl.gi;
+                M.g[tid] = frozen ? s.g : 0u;
+                M.ci[tid] = fl.ci;
+            }
+            few_clear(M);
+            uint32_t P = few_compact(M, J, [&](uint32_t) { return fl.state == RK_JOB_NORMAL && freeG != 0; });
+            if (P) few_pass_anywhere<0>(X, M, lds_lanes, near, far, n_far, P, lanes0, first_seg, freeG, freeC);
+            few_clear(M);
+            P = few_compact(M, J, [&](uint32_t j) { return fl.state == RK_JOB_NORMAL && M.gi[j] >= 0 && freeC != 0; });
+            if (P) few_pass_anywhere<1>(X, M, lds_lanes, near, far, n_far, P, lanes1, first_seg, freeG, freeC);
+            a = few_memory(X, M, 0u, J, first_seg, sums, assign, tick_total);
+            __syncthreads();                                   // the round is closed
+            if (M.box[0] && mine) a = assign[tid];             // ... by decisions in job order
+            if (tid == 0) total = *tick_total;                 // (its own store)
+        }
+        // closes it
+        if (fl.state != RK_JOB_OUT) {
+            if (a.g) atomicAdd(&used_g[half], a.g);
+            if (sim_close(s, a, t, A.dt, delta, work)) {
+                seg = s.g ? M.gi[tid] : -1;
+                lvl = s.g ? M.ci[tid] : 0u;
+            }
+        }
+        if (tid < 1u) { frozen_c[half ^ 1u] = 0ull; frozen_g[half ^ 1u] = 0u; }
+        __syncthreads();
+        if (tid == 0) {
+            if (A.out.gpus_in_use) A.out.gpus_in_use[tick] = used_g[half];
+            if (A.out.totals) A.out.totals[tick] = total;
+            if (A.out.frozen) A.out.frozen[tick] = frozen_n[half];
+            used_g[half] = 0u; frozen_n[half] = 0u;
+        }
+    }
+    if (mine) {
+        A.S.g[tid] = s.g; A.S.c[tid] = s.c; A.S.plan[tid] = s.plan; A.S.seg[tid] = seg; A.S.lvl[tid] = lvl;
+        A.S.owed[tid] = s.owed; A.S.done[tid] = s.done ? 1 : 0;
+        A.held[tid] = s.held; A.progress[tid] = s.progress; A.finish[tid] = s.finish; A.n_reconf[tid] = s.n_reconf;
+    }
 }
 
 // ------------------------------------------------------------------ service-level floors
@@ -2534,6 +2646,7 @@ int32_t rk_allocate_setup(rk_ctx *ctx) {
     const void *small[] = {reinterpret_cast<const void *>(k_select_small<0, SMALL_ROUND_JOBS / TAIL_THREADS>),
                            reinterpret_cast<const void *>(k_select_small<1, SMALL_ROUND_JOBS / TAIL_THREADS>)};
     RK_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(k_round_few), hipFuncAttributeMaxDynamicSharedMemorySize, 144 * 1024));
+    RK_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(k_sim_few), hipFuncAttributeMaxDynamicSharedMemorySize, FEW_SIM_LDS));
     for (const void *f : small) RK_HIP(ctx, hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024));
     return RK_OK;
 }
@@ -2637,6 +2750,31 @@ int32_t rk_launch_allocate(rk_ctx *ctx, const float *ref_thr, const TableDev &tb
     }
     k_mem_finish<<<n_rounds, 64, 0, s>>>(X, st, assign, totals);
     RK_CHECK_LAUNCH(ctx, "k_mem_finish");
+    return RK_OK;
+}
+
+int32_t rk_launch_sim_few(rk_ctx *ctx, const SimArgs &A, const float *ref_thr, const rk_alloc_grid *grid, uint32_t max_segs_per_job,
+                          const float *best_thr, const uint32_t *best_plan, const float *curve_thr, rk_assign *assign, bool *taken) {
+    const uint32_t J = A.n_jobs, lanes0 = few_lanes(max_segs_per_job), lanes1 = few_lanes(grid->n_cpu);
+    *taken = J <= FEW_JOBS && max_segs_per_job <= 64u && J * lanes0 <= FEW_SIM_LANES;
+    if (!*taken) return RK_OK;
+    Ctx X;
+    X.ref_thr = ref_thr; X.tb = A.tb; X.grid = A.grid; X.jb = 0; X.jmap = nullptr;
+    X.best_thr = best_thr; X.best_plan = best_plan; X.curve_thr = curve_thr;
+    X.R = RoundArgs{nullptr, nullptr, 1u, 1u, 0u, J, A.cl};
+    const uint32_t holders = A.cl.G < J ? A.cl.G : J, gpu = J * lanes0, cpu = holders * lanes1, most = gpu > cpu ? gpu : cpu;
+    const size_t job_lds = FEW_FIXED_BYTES + (size_t)((J + 3u) & ~3u) * FEW_JOB_BYTES;
+    const uint32_t room = (uint32_t)((FEW_SIM_LDS - job_lds) / FEW_LANE_BYTES) & ~63u, near = most < room ? most : room;
+    uint32_t *far = nullptr;
+    int32_t rc;
+    if (most > near && (rc = rk_scratch(ctx, SL_HULL_KEY, (size_t)most * FEW_LANE_BYTES, (void **)&far))) return rc;
+    for (uint32_t t = 0; t < A.n_ticks;) {
+        const uint32_t end = A.n_ticks - t > SIM_FEW_TICKS ? t + SIM_FEW_TICKS : A.n_ticks;
+        k_sim_few<<<1, FEW_THREADS, job_lds + (size_t)near * FEW_LANE_BYTES, ctx->stream>>>(X, A, t, end, t == 0 ? 1u : 0u, lanes0, lanes1,
+                                                                                         near, far, most, assign, A.tick_total);
+        RK_CHECK_LAUNCH(ctx, "k_sim_few");
+        t = end;
+    }
     return RK_OK;
 }
 

@@ -14,13 +14,14 @@
 // tick as well instead of handing it to the round's kernels (720 ticks: 35.9 ->
 // 27.1 ms under the greedy, 73.0 -> 46.3 ms over the nodes, of which one kernel
 // launch less per tick is about 2 ms).
+// Under the greedy up to about 1,000 jobs need none of this: k_sim_few runs
+// whole ticks in one workgroup (rk_allocate.hip).
 // The tick counter lives on the device, so every tick is the same sequence of
 // launches with the same arguments: the first tick runs eagerly (it also sizes
 // the scratch memory), the sequence is then captured once as a HIP graph on a
 // stream of the simulation's own and replayed until the counter, which
 // k_sim_step also writes to pinned host memory, has reached the last tick.
-#include "rk_internal.h"
-#include "rk_model.h"
+#include "rk_sim.h"
 
 namespace {
 
@@ -28,36 +29,6 @@ constexpr int SIM_THREADS = 1024;
 constexpr uint32_t SIM_BATCH = 4;              // replays between two looks at the tick counter
 constexpr int H_TICK = 63;                     // word of the context's pinned memory that holds it
 
-struct SimState {               // per job, between the ticks
-    uint32_t *g, *c, *plan;     // what the job holds (g = 0: nothing)
-    int32_t *seg;               // ... as segment index
-    uint32_t *lvl;              // ... and CPU level
-    double *owed;               // checkpoint-resume seconds still to pay
-    uint8_t *done;
-};
-
-struct SimArgs {
-    TableDev tb;
-    GridDev grid;
-    rk_cluster cl;
-    uint32_t n_jobs, n_ticks;
-    uint32_t loop;              // the round starts from what every job holds (policies 1 and 2), not the frozen ones only
-    const double *arrival, *work, *delta;
-    double dt, gate;
-    SimState S;
-    FloorsDev F;
-    const rk_assign *assign;
-    uint32_t *tick;             // device counter: the tick whose round comes next
-    uint32_t *h_tick;           // its copy in pinned host memory
-    float *tick_total;          // the allocation's total of the current tick
-    rk_sim_result out;
-    double *held;               // result arrays or scratch when the caller passes none
-    double *progress, *finish;
-    uint32_t *n_reconf;
-    // the search over nodes only: where the jobs are (left by the last tick) and where this tick puts them
-    uint32_t *at_off, *now_off;
-    rk_place_entry *at_ent, *now_ent;
-};
 static_assert(sizeof(rk_place_entry) == sizeof(uint4), "a part is compared and copied as one piece");
 
 __global__ __launch_bounds__(SIM_THREADS) void k_sim_init(SimArgs A) {
@@ -73,50 +44,31 @@ __global__ __launch_bounds__(SIM_THREADS) void k_sim_init(SimArgs A) {
 // Closes a tick for job j; true when the job holds other amounts than before it.
 __device__ __forceinline__ bool commit_job(const SimArgs &A, uint32_t j, double t, uint32_t &g_used) {
     const rk_assign a = A.assign[j];
-    uint32_t g = a.g;
-    g_used += g;
-    const uint32_t g_prev = A.S.g[j], c_prev = A.S.c[j];
-    const bool same_amounts = g == g_prev && a.c == c_prev;
-    if (g_prev > 0 && g > 0 && (!same_amounts || a.plan != A.S.plan[j])) {
-        A.n_reconf[j] += 1;
-        A.S.owed[j] = A.S.owed[j] + A.delta[j];
+    g_used += a.g;
+    SimJob s = {A.S.g[j], A.S.c[j], A.S.plan[j], A.n_reconf[j], A.S.owed[j], A.held[j], A.progress[j], 0.0, false};
+    const uint32_t n_reconf = s.n_reconf;
+    const bool moved = sim_close(s, a, t, A.dt, A.delta[j], A.work[j]);
+    if (s.n_reconf != n_reconf) A.n_reconf[j] = s.n_reconf;
+    if (a.g > 0) {
+        A.S.owed[j] = s.owed; A.held[j] = s.held; A.progress[j] = s.progress;
+        if (s.done) { A.finish[j] = s.finish; A.S.done[j] = 1; }
     }
-    if (g > 0) {
-        A.held[j] = A.held[j] + A.dt;
-        const double owed = A.S.owed[j];
-        const double paid = owed < A.dt ? owed : A.dt;
-        A.S.owed[j] = owed - paid;
-        const double train = A.dt - paid;
-        const double thr = (double)a.thr;
-        const double gain = thr * train;
-        const double progress = A.progress[j], work = A.work[j];
-        if (progress + gain >= work) {
-            A.finish[j] = t + paid + (work - progress) / thr;
-            A.progress[j] = work;
-            A.S.done[j] = 1;
-            g = 0;
-        } else {
-            A.progress[j] = progress + gain;
+    if (s.g > 0) A.S.plan[j] = s.plan;
+    if (!moved) return false;
+    uint32_t seg = 0xFFFFFFFFu, lvl = 0;
+    if (s.g > 0) {
+        // segment index of g (the job's counts ascend) and the CPU level that costs a.c
+        const uint32_t s0 = A.tb.seg_off[j], ns = A.tb.seg_off[j + 1] - s0;
+        uint32_t hi = ns;
+        seg = 0;
+        while (seg < hi) {
+            const uint32_t mid = (seg + hi) >> 1;
+            if (A.tb.seg_g[s0 + mid] < s.g) seg = mid + 1; else hi = mid;
         }
+        for (uint32_t i = 0; i < A.grid.n_cpu; ++i)
+            if (cpus_of(A.grid, i, s.g) == s.c) { lvl = i; break; }
     }
-    if (g == 0) {
-        if (g_prev == 0) return false;
-        A.S.g[j] = 0; A.S.c[j] = 0; A.S.plan[j] = RK_NO_PLAN; A.S.seg[j] = -1; A.S.lvl[j] = 0;
-        return true;
-    }
-    A.S.plan[j] = a.plan;
-    if (same_amounts) return false;
-    // segment index of g (the job's counts ascend) and the CPU level that costs a.c
-    const uint32_t s0 = A.tb.seg_off[j], ns = A.tb.seg_off[j + 1] - s0;
-    uint32_t lo = 0, hi = ns;
-    while (lo < hi) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (A.tb.seg_g[s0 + mid] < g) lo = mid + 1; else hi = mid;
-    }
-    uint32_t lvl = 0;
-    for (uint32_t i = 0; i < A.grid.n_cpu; ++i)
-        if (cpus_of(A.grid, i, g) == a.c) { lvl = i; break; }
-    A.S.g[j] = g; A.S.c[j] = a.c; A.S.seg[j] = (int32_t)lo; A.S.lvl[j] = lvl;
+    A.S.g[j] = s.g; A.S.c[j] = s.c; A.S.plan[j] = s.plan; A.S.seg[j] = (int32_t)seg; A.S.lvl[j] = lvl;
     return true;
 }
 
@@ -181,18 +133,14 @@ __global__ __launch_bounds__(SIM_THREADS) void k_sim_step(SimArgs A, uint32_t fi
             uint32_t ci = 0;
             if (active) {
                 state = RK_JOB_NORMAL;
-                if (g > 0) {
-                    const double T = A.held[j];
-                    const bool may_move = T - ((double)A.n_reconf[j] + 1.0) * A.delta[j] > A.gate * T;
-                    if (!may_move) {
-                        state = RK_JOB_FROZEN;
-                        gi = A.S.seg[j];
-                        ci = A.S.lvl[j];
-                        held_g += g;
-                        held_c += A.grid.cpu_mode ? (unsigned long long)A.grid.cpu_levels[ci] * g
-                                                  : (unsigned long long)A.grid.cpu_levels[ci];
-                        ++n_frozen;
-                    }
+                if (sim_frozen(g, A.held[j], A.n_reconf[j], A.delta[j], A.gate)) {
+                    state = RK_JOB_FROZEN;
+                    gi = A.S.seg[j];
+                    ci = A.S.lvl[j];
+                    held_g += g;
+                    held_c += A.grid.cpu_mode ? (unsigned long long)A.grid.cpu_levels[ci] * g
+                                              : (unsigned long long)A.grid.cpu_levels[ci];
+                    ++n_frozen;
                 }
             }
             if (first || A.F.state[j] != state || A.F.gi[j] != gi || A.F.ci[j] != ci) {
@@ -275,14 +223,7 @@ extern "C" int32_t rk_simulate(rk_ctx *ctx, const float *ref_thr, const rk_plan_
     A.tb = table_dev(table); A.grid = grid_dev(grid); A.cl = *cluster; A.n_jobs = J;
     A.arrival = trace->arrival; A.work = trace->work; A.delta = trace->delta;
     A.dt = options->dt; A.gate = options->gate; A.n_ticks = options->n_ticks; A.loop = options->policy != 0u;
-    void *h_tick;
-    RK_HIP(ctx, hipHostGetDevicePointer(&h_tick, ctx->h_pinned + H_TICK, 0));
-    A.h_tick = static_cast<uint32_t *>(h_tick);
-    // Of earlier simulations one of a single tick may still run: it can put 1 there, which ends no loop below.  One that
-    // ended in an error may have left more than that on its way.
-    if (ctx->sim_failed && ctx->sim_stream) RK_HIP(ctx, hipStreamSynchronize(ctx->sim_stream));
-    ctx->sim_failed = true;                                    // until this one has come to its end
-    __atomic_store_n(ctx->h_pinned + H_TICK, 0u, __ATOMIC_RELEASE);
+    A.h_tick = nullptr;
     A.S.owed = (double *)take(n8);
     double *s_held = (double *)take(n8), *s_prog = (double *)take(n8), *s_fin = (double *)take(n8);
     A.F.cap0 = (unsigned long long *)take(256);
@@ -309,6 +250,23 @@ extern "C" int32_t rk_simulate(rk_ctx *ctx, const float *ref_thr, const rk_plan_
     }
     A.tick = reinterpret_cast<uint32_t *>(A.F.cap0 + 4);       // inside the 256-byte capacity block
     A.tick_total = reinterpret_cast<float *>(A.F.cap0 + 5);
+
+    // a simulation that ended in an error may have left work on its way
+    if (ctx->sim_failed && ctx->sim_stream) RK_HIP(ctx, hipStreamSynchronize(ctx->sim_stream));
+    if (options->policy == 0u) {                               // few jobs: whole ticks in one kernel
+        bool taken = false;
+        if ((rc = rk_launch_sim_few(ctx, A, ref_thr, grid, table->max_segs_per_job, best_thr, best_plan, curve_thr, assign, &taken))) return rc;
+        if (taken) {
+            if (options->n_ticks > 1) RK_HIP(ctx, hipStreamSynchronize(ctx->stream));
+            return RK_OK;
+        }
+    }
+    void *h_tick;
+    RK_HIP(ctx, hipHostGetDevicePointer(&h_tick, ctx->h_pinned + H_TICK, 0));
+    A.h_tick = static_cast<uint32_t *>(h_tick);
+    // (of earlier simulations one of a single tick may still run: it can put 1 there, which ends no loop below)
+    ctx->sim_failed = true;                                    // until this one has come to its end
+    __atomic_store_n(ctx->h_pinned + H_TICK, 0u, __ATOMIC_RELEASE);
 
     // the simulation's own stream, ordered after what the context's stream holds
     if (!ctx->sim_stream) {

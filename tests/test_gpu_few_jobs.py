@@ -50,3 +50,30 @@ def test_rounds_of_few_jobs(orc, n_jobs, g_max, most, n_cpu, per_gpu):
         assert np.array_equal(assign, e_assign), (G, C, M)
         assert total == pytest.approx(e_total, rel=1e-6, abs=1e-12)
     run.close()
+
+
+@pytest.mark.parametrize("n_jobs,n_ticks", [(1, 1), (2, 129), (300, 127), (300, 128), (700, 257), (1024, 40), (1025, 40)])
+@pytest.mark.parametrize("scarce", [False, True])
+def test_ticks_in_one_launch(orc, n_jobs, n_ticks, scarce):
+    """k_sim_few: job counts whose walks lie in LDS and beyond, ticks around the end of a launch, memory decided in job
+    order.  Nearly everybody queues."""
+    from gpu_harness import DeviceRun
+    from test_gpu_sim import run_on_gpu, same
+    base = workloads.trace_scale()
+    coef, ints = np.resize(base.coef, (n_jobs, base.coef.shape[1])), np.resize(base.ints, (n_jobs, base.ints.shape[1]))
+    grid = workloads.Grid(np.array([1, 2, 4, 8, 16], np.uint32), 1, np.array([64.0, 256.0], np.float32), 0)
+    cluster = workloads.Cluster(24 if scarce else 96, 100 if scarce else 2000, 700.0 if scarce else 1e6)
+    wl = workloads.Workload("few", coef, ints, base.bounds, grid, base.env, cluster)
+    r = orc.schedule_round(wl, n_threads=16)
+    rng = np.random.default_rng(n_jobs)
+    arrival = np.sort(rng.uniform(0.0, 60.0 * n_ticks * 0.3, n_jobs))
+    arrival[: 1 + n_jobs // 2] = 0.0
+    work = coef[:, 16] * rng.uniform(60.0, 4000.0, n_jobs)
+    delta = rng.uniform(0.0, 90.0, n_jobs)
+    run = DeviceRun(wl)
+    run.enumerate()
+    assert np.diff(run.table_numpy()["seg_off"].astype(np.int64)).max() <= 16
+    want = orc.simulator.simulate(coef[:, 16], r["table"], grid, cluster, r["best_thr"], r["best_plan"], r["curve_thr"], arrival, work,
+                                  delta, 60.0, n_ticks, gate=0.9)
+    same(run_on_gpu(run, r, arrival, work, delta, 60.0, n_ticks, 0.9), want)
+    run.close()
