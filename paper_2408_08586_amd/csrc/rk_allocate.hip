@@ -2138,13 +2138,25 @@ __global__ __launch_bounds__(FLOOR_THREADS) void k_floors(Ctx X, JobState st, Sl
 // the taker is below its floor, and the step is committed when all was found and (unless the taker is below its
 // floor) the taker gains more than the others lose; otherwise everything is put back.
 //
-// One workgroup: the rule is sequential.  What is parallel is the search for a job's next step and the step down of
-// the job that gives (a wavefront over its amounts, the job's rows in its registers), the search for the job to
-// shrink (all threads over the cached give-slopes, which the round keeps in LDS) and the look for the next job that
-// has something to do (all threads; no sort).  Control flow is the same for all threads; the first wavefront takes
-// the decisions, LDS and barriers carry them.  A phase between two barriers costs its longest chain of dependent
-// loads plus its instructions on one wavefront, so the phases ask for what they read in as few rounds as they can.
-constexpr int RS_THREADS = 1024;
+// One workgroup: the rule is sequential.  Its first wavefront makes a whole step of ScheduleJob by itself: the slopes of
+// the jobs that can give stand together in LDS (a few hundred of thousands hold something), and a job's own steps and
+// its first step down were found when its state last changed (RsNext, RsGives), so a step is a search over LDS and one
+// round of loads per job that gives.  Between two barriers after a committed step all wavefronts find these again for the
+// jobs that it changed; the look for the next job that has something to do needs no sort, and every thread has the values
+// it asks of its own jobs in registers.
+constexpr uint32_t RS_TOUCHED = 512;      // jobs changed by a step whose list is in LDS
+constexpr uint32_t RS_UPDATES = 64;        // ... whose new values go from LDS to the threads that have them (beyond: from memory)
+constexpr uint32_t RS_JOB_BITS = 14;       // a job or a place in the list of holders
+static_assert(RK_MAX_JOBS_PER_ROUND <= 1u << RS_JOB_BITS, "a job and its place share a word");
+
+// Threads of the workgroup and, at most, jobs of a thread (whose values are in its registers: two words each, so that
+// twelve jobs a thread at 1,024 threads would leave too few registers for the rest).  Up to 1,024 jobs four wavefronts
+// are enough, and their barriers are cheaper.
+constexpr int RS_THREADS = 512, RS_PER = RK_MAX_JOBS_PER_ROUND / RS_THREADS;
+constexpr int RS_SMALL_THREADS = 256, RS_SMALL_PER = 4;
+
+constexpr uint32_t RS_HAS_CPU = 1u << 22, RS_HOLDS = 1u << 23;       // the job has a CPU step; it holds something
+static_assert(RK_MAX_G <= 0xFFFFu && RK_MAX_CPU_LEVELS <= 64, "a step's GPUs and a level fit a word");
 
 struct RsRound {                 // what a round of the loop works on
     JobState st;                 // gi, g, ci: the state the loop works on (and the memory step reads)
@@ -2155,15 +2167,12 @@ struct RsRound {                 // what a round of the loop works on
     const uint32_t *cur_c;
     const int32_t *floor_seg;    // may be null
     const uint32_t *floor_c;     // may be null
-    float *ds_g, *ds_c;          // per job: what it loses per GPU / CPU it gives (infinite: gives nothing)
-    float *sg, *sc;              // per job: slopes the order is taken from
-    float *ug, *uc;              // per job, kept current: slope of its next GPU / CPU step (0: none)
-    uint32_t *udg;               // ... GPUs its next GPU step adds
-    unsigned long long *udc_g, *udc_c;   // ... CPUs its next GPU step / CPU step adds
-    uint32_t *order, *touched, *stamp, *first;
-    int32_t *keep_gi;
-    uint32_t *keep_ci;
-    float *keep_ds;              // the two give-slopes of a job before a step touched it
+    float *ug;                   // per job, as the call finds it: slope of its next GPU step (0: none)
+    uint32_t *about;             // ... GPUs that step adds | level << 16 | RS_HAS_CPU | RS_HOLDS
+    unsigned long long *okey;    // its place in the order (0: not in it)
+    RsNext *next;                // its steps up, kept current
+    RsGives *gives;              // its steps down, kept current
+    uint32_t *order, *touched, *first;
     uint32_t *stats;             // may be null: steps committed, jobs on the full path, shrinks applied, steps taken back
 };
 
@@ -2172,6 +2181,7 @@ struct RsArgs {                  // the kernels' argument
     RsRound r;
     // several independent rounds over the same jobs (a workgroup per round): round k works on the slice [k * n_jobs, ...)
     // of every per-job array of r, reads the state arrays from k * state_stride on and its cluster from d_clusters[k]
+    uint32_t near;                   // places in the list of holders whose steps down are kept in LDS
     uint32_t state_stride;
     const rk_cluster *d_clusters;    // null: the single round's G and C
 };
@@ -2193,8 +2203,8 @@ __device__ __forceinline__ RsView rs_round(const RsArgs &K, uint32_t r) {
     A.cur_seg += from; A.cur_c += from;
     if (B.floor_seg) A.floor_seg += from;
     if (B.floor_c) A.floor_c += from;
-    A.ds_g += at; A.ds_c += at; A.sg += at; A.sc += at; A.ug += at; A.uc += at; A.udg += at; A.udc_g += at; A.udc_c += at;
-    A.order += at; A.touched += at; A.stamp += at; A.first += at; A.keep_gi += at; A.keep_ci += at; A.keep_ds += 2 * at;
+    A.ug += at; A.about += at; A.okey += at; A.next += at; A.gives += at;
+    A.order += at; A.touched += at; A.first += at;
     if (B.stats) A.stats += 4 * (size_t)r;
     if (K.d_clusters) { A.G = K.d_clusters[r].G; A.C = K.d_clusters[r].C; }
     return A;
@@ -2214,6 +2224,11 @@ constexpr uint64_t RS_WAVE_JOBS = 49152;
 
 // Every job on its own, any number of workgroups: what it holds, whether it comes first (a floor it is below), its
 // cached slopes and steps.  LANES: 64, a wavefront per job, which has the job's rows at once (RsRows), or 1.
+// A job's place in the order: GPU slope, then CPU slope, both descending (then index).
+__device__ __forceinline__ unsigned long long rs_order_key(float ug, float uc) {
+    return ((unsigned long long)rs_ordered(ug) << 32) | rs_ordered(uc);
+}
+
 template <uint32_t LANES>
 __global__ void k_rs_prepare(RsArgs B) {
     const uint32_t j = (blockIdx.x * blockDim.x + threadIdx.x) / LANES, lane = threadIdx.x % LANES;
@@ -2226,334 +2241,525 @@ __global__ void k_rs_prepare(RsArgs B) {
     }
     const int32_t fl = rs_fl_s(A, j);
     const bool below = fl >= 0 && gi < fl;
-    const uint32_t g = (uint32_t)rs_g(A, j, gi);
+    const uint32_t so = A.X.tb.seg_off[j], ns = A.X.tb.seg_off[j + 1] - so;
+    const RsKept k = rs_keep<LANES>(A, j, so, ns, gi, ci, -1, lane, true, true, A.gives + j, nullptr);
     if (lane == 0) {
-        A.st.gi[j] = gi; A.st.ci[j] = ci; A.st.g[j] = g;
-        A.stamp[j] = 0u;
-        A.first[j] = (rs_part(A, j) && below) ? 1u : 0u;
-    }
-    if constexpr (LANES == 1) {
-        rs_refresh(A, j);
-    } else {
-        __threadfence_block();                       // (a job that rs_rows does not suit reads what the first lane wrote)
-        rs_refresh_wave_at(A, j, gi, ci, lane, nullptr, nullptr, false);
+        const bool part = rs_part(A, j);
+        A.st.gi[j] = gi; A.st.ci[j] = ci; A.st.g[j] = k.g;
+        A.first[j] = part && below ? 1u : 0u;
+        A.ug[j] = k.ug; A.about[j] = k.dg | (ci << 16) | (k.uc > 0.f ? RS_HAS_CPU : 0u) | (gi >= 0 ? RS_HOLDS : 0u);
+        A.okey[j] = part && !below ? rs_order_key(k.ug, k.uc) : 0ull;
     }
 }
 
-// Bound by the latency of one small decision after the other, so by barriers, dependent loads and instructions on one
-// wavefront.  10,000 jobs, 512 nodes' totals: 405 -> 356 us on one drawn state with the per-job passes four jobs at a time,
-// the pass over privileged jobs only where there are some, a step taken back by a lane per job, no barrier on a look that
-// finds nothing changed, and reductions word by word.
-__global__ __launch_bounds__(RS_THREADS) void k_reschedule(RsArgs B) {
-    // what every job loses per GPU / CPU it gives, [2][n_jobs]: read by all threads at every search for a job to
-    // shrink, so the round keeps them in LDS (k_rs_prepare left them in memory)
-    extern __shared__ float sh_ds[];
-    RsView A = rs_round(B, blockIdx.x);
-    __shared__ RsStep sh_step, sh_next[2];
-    __shared__ unsigned long long sh_free[2], sh_avail[2], sh_held[2][RS_THREADS / 64];
-    __shared__ float sh_lost;
-    __shared__ unsigned long long sh_pick_key[RS_THREADS / 64 + 1];
-    __shared__ uint32_t sh_pick_j[RS_THREADS / 64 + 1];
-    __shared__ unsigned long long sh_wlow[RS_THREADS / 64];
-    __shared__ uint32_t sh_below, sh_next_below;
-    __shared__ uint32_t sh_widx[RS_THREADS / 64];
-    __shared__ uint32_t sh_ok, sh_go, sh_touched, sh_epoch, sh_moves, sh_nb, sh_full, sh_shrinks, sh_undone;
-    __shared__ RsMin sh_min[2];
-    __shared__ unsigned long long sh_two_k[2 * (RS_THREADS / 64 + 1)];
-    __shared__ uint32_t sh_two_s[2 * (RS_THREADS / 64 + 1)];
-    constexpr uint32_t RS_LIST = 2048;                     // jobs with something to do, as the last look over all jobs found them
-    __shared__ uint32_t sh_listed, sh_list_j[RS_LIST];
-    __shared__ float sh_list_g[RS_LIST], sh_list_c[RS_LIST];
-    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
-    const uint32_t J = A.n_jobs;
-    const float INF = __int_as_float(0x7F800000);
+// Dynamic LDS of k_reschedule: two slopes and the job (half a word) of every place in the list of holders; and what the
+// jobs in the first places give, as many as there is room for up to RS_NEAR (the others' is in memory).
+constexpr size_t RS_LDS_MOST = 136 * 1024;                  // 160 KiB less what the kernel declares
+constexpr uint32_t RS_NEAR = 512;
+static inline size_t rs_list_bytes(size_t J) { return ((J + 7) & ~(size_t)7) * (2 * sizeof(float) + sizeof(uint16_t)); }
+static inline uint32_t rs_near(size_t J) {
+    const size_t fit = (RS_LDS_MOST - rs_list_bytes(J)) / sizeof(RsGives), most = J < RS_NEAR ? J : RS_NEAR;
+    return (uint32_t)(fit < most ? fit : most);
+}
 
-    // the state the jobs are in has been loaded (k_rs_prepare); what they hold together, and whether anyone is privileged
-    unsigned long long hg = 0, hc = 0;
-    uint32_t privileged = 0;
-    for (uint32_t j0 = tid; j0 < J; j0 += 4 * RS_THREADS) {       // four jobs' values in flight
-        float dg[4], dc[4];
-        uint32_t g[4], c[4], f[4];
-#pragma unroll
-        for (uint32_t k = 0; k < 4; ++k) {
-            const uint32_t j = j0 + k * RS_THREADS;
-            const bool in = j < J;
-            dg[k] = in ? A.ds_g[j] : INF; dc[k] = in ? A.ds_c[j] : INF;
-            g[k] = in ? A.st.g[j] : 0u; c[k] = in ? A.st.ci[j] : 0u;
-            f[k] = in ? A.first[j] : 0u;
-        }
-#pragma unroll
-        for (uint32_t k = 0; k < 4; ++k) {
-            const uint32_t j = j0 + k * RS_THREADS;
-            if (j < J) { sh_ds[j] = dg[k]; sh_ds[J + j] = dc[k]; }
-            if (g[k]) { hg += g[k]; hc += cpu_cost(A.X.grid, c[k], g[k]); }
-            privileged |= f[k];
-        }
+// Bound by the latency of one small decision after the other: about 0.4 us for a search for the job to shrink, 0.5 us for
+// what it gives, 2.5 us for a committed step's new values (a job's rows come from memory that other chiplets wrote), 4 us
+// for a look after one.  10,000 jobs on 4,096 GPUs, 15 jobs on the full path, 22 steps committed, 49 shrinks: 374 -> 242 us;
+// 9,999 jobs with floors, several hundred steps: 4.2 -> 3.4 ms; while all wavefronts searched all jobs, with a barrier on
+// either side of every decision, and a look read seven values of every job from memory.
+template <int THREADS, int PER>
+__global__ __launch_bounds__(THREADS) void k_reschedule(RsArgs B) {
+    constexpr uint32_t WAVES = THREADS / 64, NONE = 0xFFFFFFFFu, JOB = (1u << RS_JOB_BITS) - 1u, MARK = 0x8000u;
+    static_assert(WAVES >= 2 && WAVES <= 16, "two wavefronts find the lowest slopes, a row of 16 lanes reduces what all found");
+    extern __shared__ uint4 sh_raw[];
+    RsView A = rs_round(B, blockIdx.x);
+    __shared__ RsNext sh_next;
+    // the jobs that the step under way has changed: place << RS_JOB_BITS | job, amounts << 16 | level and the two slopes
+    // before it; and the amounts << 16 | level now
+    __shared__ uint4 sh_touched[RS_TOUCHED];
+    __shared__ uint32_t sh_now[RS_TOUCHED], sh_so[RS_TOUCHED];          // ... where their amounts begin, and how many they are
+    __shared__ uint16_t sh_ns[RS_TOUCHED];
+    __shared__ uint32_t sh_upd[RS_UPDATES][4], sh_most[RK_MAX_CPU_LEVELS];
+    __shared__ unsigned long long sh_free[2], sh_held[2][WAVES], sh_pick_key[WAVES];
+    __shared__ uint32_t sh_pick_j[WAVES], sh_widx[WAVES];
+    __shared__ RsMin sh_min[2];
+    __shared__ uint32_t sh_holders, sh_changed[2], sh_nb;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    const uint32_t J = A.n_jobs, room = (J + 7u) & ~7u, near = B.near;
+    const float INF = __int_as_float(0x7F800000);
+    // a place in the list of holders: what its job loses per GPU and per CPU it gives (infinite: nothing to give, or nobody
+    // here), and the job, marked when the step under way has changed it
+    float *const low_g = reinterpret_cast<float *>(sh_raw), *const low_c = low_g + room;
+    uint16_t *const who = reinterpret_cast<uint16_t *>(low_c + room);
+    RsGives *const near_gives = reinterpret_cast<RsGives *>(who + room);
+
+    for (uint32_t i = tid; i < room / 2u; i += THREADS) {
+        const uint32_t inf = 0x7F800000u;
+        sh_raw[i] = uint4{inf, inf, inf, inf};
     }
-    A.ds_g = sh_ds;
-    A.ds_c = sh_ds + J;
+    if (tid == 0) { sh_holders = 0u; sh_nb = 0u; }
+    __syncthreads();
+    // the state the jobs are in has been loaded (k_rs_prepare): the steps of a thread's jobs, who holds something, and what
+    // they hold together
+    float ug[PER];
+    uint32_t about[PER];
+#pragma unroll
+    for (uint32_t k = 0; k < PER; ++k) {
+        const uint32_t j = tid + k * THREADS;
+        ug[k] = j < J ? A.ug[j] : 0.f; about[k] = j < J ? A.about[j] : 0u;
+        if (k % 8u == 7u) asm volatile("" ::: "memory");     // (addresses of a few jobs at a time in registers)
+    }
+    uint32_t changed_once = 0;                              // which of a thread's jobs have had another state
+    unsigned long long hg = 0, hc = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < PER; ++k) {
+        const unsigned long long m = __ballot((about[k] & RS_HOLDS) != 0u);
+        if (!m) continue;
+        uint32_t base = 0;
+        if (lane == 0) base = atomicAdd(&sh_holders, (uint32_t)__popcll(m));
+        base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+        if (about[k] & RS_HOLDS) who[base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)(tid + k * THREADS);
+    }
+    __syncthreads();
+    for (uint32_t i = tid; i < sh_holders; i += THREADS) {
+        const uint32_t j = who[i], g = A.st.g[j], c = A.st.ci[j];
+        const uint4 *const from = reinterpret_cast<const uint4 *>(A.gives + j);
+        const uint4 n0 = from[0], n1 = from[1], n2 = from[2], n3 = from[3];
+        low_g[i] = __uint_as_float(n1.y); low_c[i] = __uint_as_float(n2.w);      // (ds_g, ds_c)
+        if (i < near) {
+            uint4 *const to = reinterpret_cast<uint4 *>(near_gives + i);
+            to[0] = n0; to[1] = n1; to[2] = n2; to[3] = n3;
+        }
+        A.next[j].slot = (int32_t)i;
+        hg += g; hc += cpu_cost(A.X.grid, c, g);
+    }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) { hg += __shfl_xor(hg, off, 64); hc += __shfl_xor(hc, off, 64); }
     if (lane == 0) { sh_held[0][wave] = hg; sh_held[1][wave] = hc; }
     __syncthreads();
     if (tid == 0) {
         unsigned long long g = 0, c = 0;
-        for (uint32_t w = 0; w < RS_THREADS / 64; ++w) { g += sh_held[0][w]; c += sh_held[1][w]; }
+        for (uint32_t w = 0; w < WAVES; ++w) { g += sh_held[0][w]; c += sh_held[1][w]; }
         sh_free[0] = g < A.G ? A.G - g : 0ull;
         sh_free[1] = c < A.C ? A.C - c : 0ull;
-        sh_epoch = 0u; sh_moves = 0u; sh_full = 0u; sh_shrinks = 0u; sh_undone = 0u;
     }
     __syncthreads();
 
-    // ScheduleJob(j); the same code path for all threads
-    auto schedule_job = [&](uint32_t j) {
-        // The job's next steps (GPUs, CPUs) and whether it is below its floor are kept in LDS: found here for the job as
-        // it is (its cached values are written again, unchanged), and again by the refresh after every committed step.
-        if (wave == 0) rs_refresh_wave(A, j, lane, sh_next, &sh_next_below, true);
-        rs_lds_barrier();
-        for (uint32_t res = 0; res < 2; ++res) {
-            for (;;) {
-                if (wave == 0) {
-                    const RsStep st = sh_next[res];
-                    const bool below = res == 0 && sh_next_below != 0u;     // below its floor: it takes at a loss
-                    if (lane == 0) {
-                        sh_step = st;
-                        sh_below = below ? 1u : 0u;
-                        sh_avail[0] = sh_free[0]; sh_avail[1] = sh_free[1];
-                        sh_lost = 0.f; sh_ok = 1u; sh_touched = 0u; sh_epoch += 1u;
-                    }
-                }
-                __syncthreads();
-                const RsStep st = sh_step;
-                if (!st.any) { __syncthreads(); break; }
-                const bool below_min = sh_below != 0u;
-                const unsigned long long need = res == 0 ? st.dg : st.dc;
-                while (sh_ok && sh_avail[res] < need) {
-                    // the job with the lowest slope among those that can give (GetLowestSlopeOverMinJob); ties: lower index
-                    const float *ds = sh_ds + res * J;
-                    float best = INF;
-                    uint32_t who = 0xFFFFFFFFu;
-                    for (uint32_t v0 = tid; v0 < J; v0 += 4 * RS_THREADS) {      // four loads in flight
-                        float x[4];
+    // A wavefront finds the place with the lowest slope (the lower job among equal slopes); false: nobody gives.  Four places
+    // per lane and load; a list of at most 256 places is looked at once.
+    auto lowest = [&](const float *low, uint32_t n, float &slope, uint32_t &place) -> bool {
+        const uint32_t n4 = (n + 3u) / 4u;
+        const float4 *const q4 = reinterpret_cast<const float4 *>(low);
+        float4 q = lane < n4 ? q4[lane] : float4{INF, INF, INF, INF};
+        float least = fminf(fminf(q.x, q.y), fminf(q.z, q.w));
+        for (uint32_t i = lane + 64u; i < n4; i += 64u) {
+            const float4 r = q4[i];
+            least = fminf(least, fminf(fminf(r.x, r.y), fminf(r.z, r.w)));
+        }
+        const uint32_t top = wave_min_u32_rows(least < INF ? rs_ordered(least) : NONE);
+        if (top == NONE) return false;
+        slope = rs_unordered(top);
+        uint32_t job = NONE, at = 0u;
+        if (n4 <= 64u) {
+            const unsigned long long mx = __ballot(q.x == slope), my = __ballot(q.y == slope), mz = __ballot(q.z == slope), mw = __ballot(q.w == slope);
+            const unsigned long long any = mx | my | mz | mw;
+            if (!(any & (any - 1ull)) && !((mx & my) | ((mx | my) & mz) | ((mx | my | mz) & mw))) {      // one place has it
+                place = 4u * ((uint32_t)__ffsll((long long)any) - 1u) + (mx ? 0u : my ? 1u : mz ? 2u : 3u);
+                return true;
+            }
+        }
+        for (uint32_t i = lane; i < n4; i += 64u) {
+            if (i != lane) q = q4[i];
+            const float x[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
-                        for (uint32_t k = 0; k < 4; ++k) x[k] = v0 + k * RS_THREADS < J ? ds[v0 + k * RS_THREADS] : INF;
+            for (uint32_t c = 0; c < 4; ++c)
+                if (x[c] == slope) {
+                    const uint32_t w = who[4u * i + c] & JOB;
+                    if (w < job) { job = w; at = 4u * i + c; }
+                }
+        }
+        const uint32_t first = wave_min_u32_rows(job);
+        place = wave_lane_u32(at, (uint32_t)__ffsll((long long)__ballot(job == first)) - 1u);
+        return true;
+    };
+
+    // ---- the first wavefront's part: a step of ScheduleJob(j).  Values without a lane are the same in all lanes.
+    uint32_t moves = 0, full = 0, shrinks = 0, undone = 0, holders = sh_holders;
+    unsigned long long free_g = sh_free[0], free_c = sh_free[1];
+    uint32_t turn = 0;                                       // which of sh_changed: the first wavefront may be a turn ahead
+    auto one = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); };
+    auto onef = [](float x) { return __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(x))); };
+    auto two = [&](unsigned long long x) { return ((unsigned long long)one((uint32_t)(x >> 32)) << 32) | one((uint32_t)x); };
+    // a job's four pieces (RsNext or RsGives), from LDS or from memory: loads of their own, for one that may be either waits
+    // for both kinds
+    auto pieces = [](bool near_by, const void *lds, const void *mem, uint4 (&n)[4]) {
+        if (near_by) {
+            const uint4 *const from = static_cast<const uint4 *>(lds);
+            n[0] = from[0]; n[1] = from[1]; n[2] = from[2]; n[3] = from[3];
+            asm volatile("");
+        } else {
+            const uint4 *const from = static_cast<const uint4 *>(mem);
+            n[0] = from[0]; n[1] = from[1]; n[2] = from[2]; n[3] = from[3];
+        }
+    };
+    // res 0: GPUs, 1: CPUs; true: committed (and the jobs it changed are listed, j the last one)
+    auto step = [&](uint32_t j, const RsNext &N, uint32_t res) -> bool {
+        if (!(res == 0 ? N.tgt_g >= 0 : N.uc > 0.f)) return false;
+        const bool below_min = res == 0 && (N.below_ns & RS_BELOW) != 0u;
+        const float slope = res == 0 ? N.ug : N.uc, gain = res == 0 ? N.gain_g : N.gain_c;
+        const unsigned long long need_g = res == 0 ? N.dg : 0u, need_c = res == 0 ? N.dcg : N.dcc, need = res == 0 ? need_g : need_c;
+        int32_t slot = N.slot;
+        float *const low = res == 0 ? low_g : low_c;
+        float own = 0.f;
+        if (slot >= 0 && (res == 0 ? free_g : free_c) < need) {              // j gives nothing to itself
+            own = low[slot];
+            rs_wave_order();
+            if (lane == 0) low[slot] = INF;
+            rs_wave_order();
+        }
+        unsigned long long av_g = free_g, av_c = free_c;
+        float lost = 0.f;
+        uint32_t touched = 0;
+        bool ok = true;
+        const unsigned long long had = res == 0 ? free_g : free_c;
+        bool again = false;                                  // a job gave more than once
+        auto list = [&](uint32_t place, uint32_t v, uint32_t before, float sg, float sc, uint32_t now, uint32_t so, uint32_t ns) {
+            const uint32_t word = (place << RS_JOB_BITS) | v;
+            if (lane == 0) {
+                if (touched < RS_TOUCHED) {
+                    sh_touched[touched] = uint4{word, before, __float_as_uint(sg), __float_as_uint(sc)};
+                    sh_now[touched] = now; sh_so[touched] = so; sh_ns[touched] = (uint16_t)ns;
+                } else {
+                    A.touched[touched] = word;
+                }
+            }
+            touched += 1u;
+        };
+        while ((res == 0 ? av_g : av_c) < need) {
+            // the job with the lowest slope among those that can give (GetLowestSlopeOverMinJob)
+            float s;
+            uint32_t place;
+            if (!lowest(low, holders, s, place) || !(below_min || slope > s)) { ok = false; break; }
+            const uint32_t word = one(who[place]), v = word & JOB;
+            unsigned long long dg0 = 0, dc0;
+            float loss, ds_g, ds_c;
+            int32_t gi;
+            uint32_t ci;
+            if (!(word & MARK)) {                            // its step down is known
+                uint4 n[4];
+                pieces(place < near, near_gives + place, A.gives + v, n);
+                const RsGives gv = __builtin_bit_cast(RsGives, n);
+                const uint32_t gis = one(gv.gis), ci0 = one(gv.ci_ns) & 0xFFu, ns = one(gv.ci_ns) >> 8;
+                if (res == 0) {
+                    dg0 = one(gv.dg0); dc0 = two(gv.dc0); loss = onef(gv.loss0); ds_g = gv.ds_g0; ds_c = gv.ds_c0;
+                    gi = (int32_t)(int16_t)(gis & 0xFFFFu); ci = gi < 0 ? 0u : ci0;
+                } else {
+                    dc0 = two(gv.dc1); loss = onef(gv.loss1); ds_g = gv.ds_g1; ds_c = gv.ds_c1;
+                    gi = (int32_t)(gis >> 16); ci = ci0 - 1u;
+                }
+                list(place, v, (gis & 0xFFFF0000u) | ci0, gv.ds_g, gv.ds_c, ((uint32_t)gi << 16) | ci, one(gv.so), ns);
+            } else {                                         // it has given in this step
+                const int32_t gi0 = (int32_t)one((uint32_t)A.st.gi[v]);
+                const uint32_t ci0 = one(A.st.ci[v]), so = one(A.X.tb.seg_off[v]), ns = one(A.X.tb.seg_off[v + 1]) - so;
+                const RsShrunk sk = rs_shrink_wave(A, v, so, ns, res, gi0, ci0, lane);
+                dg0 = two(sk.gv.dg); dc0 = two(sk.gv.dc); loss = onef(sk.gv.loss); ds_g = sk.ds_g; ds_c = sk.ds_c;
+                gi = sk.gi; ci = sk.ci;
+                again = true;
+            }
+            if (lane == 0) {
+                who[place] = (uint16_t)(v | MARK);
+                low_g[place] = ds_g; low_c[place] = ds_c;
+                A.st.gi[v] = gi; A.st.ci[v] = ci;
+            }
+            av_g += dg0; av_c += dc0;
+            lost = lost + loss;
+            shrinks += 1u;
+            rs_wave_order();
+        }
+        if (ok && (av_g < need_g || av_c < need_c)) ok = false;
+        if (ok && !below_min && !(gain > lost)) ok = false;
+        rs_wave_order();
+        for (uint32_t i = lane; i < touched; i += 64u) {     // a job per lane: no longer changed, and if need be as it was
+            const bool far = i >= RS_TOUCHED;
+            uint4 e = sh_touched[far ? 0u : i];
+            if (far) e.x = A.touched[i];
+            const uint32_t v = e.x & JOB, place = e.x >> RS_JOB_BITS;
+            who[place] = (uint16_t)v;
+            if (ok) {
+                if (again && !far) sh_now[i] = ((uint32_t)A.st.gi[v] << 16) | A.st.ci[v];
+                continue;
+            }
+            if (far) {
+                uint4 n[4];
+                pieces(place < near, near_gives + place, A.gives + v, n);
+                const RsGives gv = __builtin_bit_cast(RsGives, n);
+                e.y = (gv.gis & 0xFFFF0000u) | (gv.ci_ns & 0xFFu); e.z = __float_as_uint(gv.ds_g); e.w = __float_as_uint(gv.ds_c);
+            }
+            A.st.gi[v] = (int32_t)(e.y >> 16); A.st.ci[v] = e.y & 0xFFFFu;
+            low_g[place] = __uint_as_float(e.z); low_c[place] = __uint_as_float(e.w);
+        }
+        if (slot >= 0 && had < need && lane == 0) low[slot] = own;
+        rs_wave_order();
+        if (!ok) { undone += touched ? 1u : 0u; return false; }
+        free_g = av_g - need_g; free_c = av_c - need_c;
+        if (slot < 0) {
+            slot = (int32_t)holders;
+            holders += 1u;
+            if (lane == 0) { who[slot] = (uint16_t)j; sh_holders = holders; }
+        }
+        const int32_t gi_j = res == 0 ? N.tgt_g : N.gi;
+        const uint32_t ci_j = res == 0 ? N.lvl_g : N.lvl_c;
+        if (lane == 0) {
+            A.st.gi[j] = gi_j; A.st.ci[j] = ci_j;
+            sh_free[0] = free_g; sh_free[1] = free_c;
+            sh_changed[turn] = touched + 1u;
+        }
+        list((uint32_t)slot, j, 0u, 0.f, 0.f, ((uint32_t)gi_j << 16) | ci_j, N.so, N.below_ns & ~RS_BELOW);
+        if (touched > RS_TOUCHED) __threadfence_block();     // (part of the list, and what the jobs hold now, is in memory)
+        moves += 1u;
+        return true;
+    };
+
+    bool others = false;                                  // the privileged jobs are through
+    // ScheduleJob(j): the first wavefront steps, then all find the steps of the jobs that a committed step changed.  True
+    // when one was.
+    auto schedule_job = [&](uint32_t j) -> bool {
+        bool any = false;
+        uint32_t res = 0;
+        for (;;) {
+            if (wave == 0) {
+                uint4 n[4];
+                pieces(any, &sh_next, A.next + j, n);
 #pragma unroll
-                        for (uint32_t k = 0; k < 4; ++k) {                        // ascending: the lower job stays among equal slopes
-                            const uint32_t v = v0 + k * RS_THREADS;
-                            if (v != j && x[k] < best) { best = x[k]; who = v; }
-                        }
+                for (uint32_t i = 0; i < 4; ++i) n[i] = uint4{one(n[i].x), one(n[i].y), one(n[i].z), one(n[i].w)};
+                const RsNext N = __builtin_bit_cast(RsNext, n);
+                while (res < 2u && !step(j, N, res)) ++res;
+                if (res == 2u && lane == 0) sh_changed[turn] = 0u;
+            } else if (any) {
+                __threadfence_block();                       // (what this wavefront stored of the jobs that it refreshed)
+            }
+            rs_lds_barrier();
+            const uint32_t changed = one(sh_changed[turn]);
+            turn ^= 1u;
+            if (!changed) return any;
+            any = true;
+            for (uint32_t i = wave; i < 2u * changed; i += WAVES) {          // two wavefronts per job: GPUs, CPUs
+                const uint32_t at = i >> 1;
+                const bool far = at >= RS_TOUCHED, gpus = (i & 1u) == 0u;
+                const uint32_t e = one(far ? A.touched[at] : sh_touched[at].x), v = e & JOB, place = e >> RS_JOB_BITS;
+                const uint32_t now = one(far ? ((uint32_t)A.st.gi[v] << 16) | A.st.ci[v] : sh_now[at]);
+                const int32_t gi = (int32_t)(int16_t)(now >> 16);
+                const uint32_t so = one(far ? A.X.tb.seg_off[v] : sh_so[at]), ns = one(far ? A.X.tb.seg_off[v + 1] - so : (uint32_t)sh_ns[at]);
+                const RsKept k = rs_keep<64>(A, v, so, ns, gi, now & 0xFFFFu, (int32_t)place, lane, gpus, !gpus,
+                                             place < near ? near_gives + place : A.gives + v, v == j ? &sh_next : nullptr);
+                if (lane == 0) {
+                    uint32_t *const u = at < RS_UPDATES ? sh_upd[at] : nullptr;
+                    if (gpus) {
+                        low_g[place] = k.ds_g; A.st.g[v] = k.g;
+                        if (u) { u[0] = v; u[1] = __float_as_uint(k.ug); u[2] = k.dg | ((now & 0xFFFFu) << 16) | (gi >= 0 ? RS_HOLDS : 0u); }
+                    } else {
+                        low_c[place] = k.ds_c;
+                        if (u) u[3] = k.uc > 0.f ? RS_HAS_CPU : 0u;
                     }
-                    // (slope, job), the slope as a word that orders like it, reduced word by word
-                    const uint32_t low = who == 0xFFFFFFFFu ? ~0u : rs_ordered(best);
-                    const uint32_t low_w = wave_min_u32_rows(low), who_w = wave_min_u32_rows(low == low_w ? who : 0xFFFFFFFFu);
-                    if (lane == 0) sh_wlow[wave] = ((unsigned long long)low_w << 32) | who_w;
-                    rs_lds_barrier();
-                    if (wave == 0) {                           // the first wavefront takes the decision and the step down
-                        static_assert(RS_THREADS / 64 == 16, "a row of 16 lanes reduces what the wavefronts found");
-                        const unsigned long long kw = sh_wlow[lane & 15u];
-                        const uint32_t l2 = (uint32_t)(kw >> 32), low2 = wave_lane_u32(row_min_u32(l2), 0u);
-                        const uint32_t w2 = wave_lane_u32(row_min_u32(l2 == low2 ? (uint32_t)kw : 0xFFFFFFFFu), 0u);
-                        const float b2 = rs_unordered(low2);
-                        // what the step down reads first, asked for together
-                        const bool some = w2 != 0xFFFFFFFFu;
-                        const uint32_t stamp2 = some ? A.stamp[w2] : 0u;
-                        const int32_t gi0 = some ? A.st.gi[w2] : -1;
-                        const uint32_t ci0 = some ? A.st.ci[w2] : 0u;
-                        const uint32_t so2 = some ? A.X.tb.seg_off[w2] : 0u, ns2 = some ? A.X.tb.seg_off[w2 + 1] - so2 : 0u;
-                        if (!some || !(below_min || st.slope > b2)) {
-                            if (lane == 0) sh_ok = 0u;
-                        } else {
-                            const RsShrunk sk = rs_shrink_wave(A, w2, so2, ns2, res, gi0, ci0, lane);
-                            if (lane == 0) {
-                                if (stamp2 != sh_epoch) {           // first time this job gives in this step: remember its state
-                                    A.stamp[w2] = sh_epoch;
-                                    A.keep_gi[w2] = gi0; A.keep_ci[w2] = ci0;
-                                    A.keep_ds[2 * w2] = A.ds_g[w2]; A.keep_ds[2 * w2 + 1] = A.ds_c[w2];
-                                    A.touched[sh_touched++] = w2;
-                                }
-                                sh_avail[0] += sk.gv.dg; sh_avail[1] += sk.gv.dc;
-                                sh_lost = sh_lost + sk.gv.loss;
-                                A.st.gi[w2] = sk.gi; A.st.ci[w2] = sk.ci;
-                                A.ds_g[w2] = sk.ds_g; A.ds_c[w2] = sk.ds_c;   // (its own next steps are brought up to date on commit)
-                                sh_shrinks += 1u;
-                            }
-                        }
+                    if (!others) {                           // (the order is not yet fixed)
+                        uint32_t *const key = reinterpret_cast<uint32_t *>(A.okey + v);
+                        if (rs_part(A, v) && !A.first[v]) key[gpus ? 1 : 0] = rs_ordered(gpus ? k.ug : k.uc);
                     }
-                    // (what the first wavefront wrote to memory, the state of the job that gave, is read again by itself only,
-                    // until the barrier that follows the loop)
-                    rs_lds_barrier();
+                    // (what is read behind the barrier that follows; the rest is waited for before the next one)
+                    if (place >= near || changed > RS_UPDATES) __threadfence_block();
                 }
-                if (wave == 0) {
-                    bool ok = sh_ok != 0u;
-                    if (ok && (sh_avail[0] < st.dg || sh_avail[1] < st.dc)) ok = false;
-                    if (ok && !below_min && !(st.gain > sh_lost)) ok = false;
-                    const uint32_t n_touched = sh_touched;
-                    if (!ok) {                                              // everything back as it was, a job per lane
-                        __threadfence_block();                              // (the first lane wrote what is read here)
-                        for (uint32_t i = lane; i < n_touched; i += 64u) {
-                            const uint32_t v = A.touched[i];
-                            A.st.gi[v] = A.keep_gi[v]; A.st.ci[v] = A.keep_ci[v];
-                            A.ds_g[v] = A.keep_ds[2 * v]; A.ds_c[v] = A.keep_ds[2 * v + 1];
-                        }
-                        if (lane == 0) sh_undone += n_touched ? 1u : 0u;
-                    } else if (lane == 0) {
-                        sh_free[0] = sh_avail[0] - st.dg; sh_free[1] = sh_avail[1] - st.dc;
-                        if (res == 0) A.st.gi[j] = st.tgt;
-                        A.st.ci[j] = st.lvl;
-                        sh_moves += 1u;
+            }
+            rs_lds_barrier();
+            if (changed > RS_UPDATES) {                      // (too many for the list: all jobs' again)
+                uint32_t tid_k = tid;
+                asm volatile("" : "+v"(tid_k));
+#pragma unroll
+                for (uint32_t k = 0; k < PER; ++k) {
+                    const uint32_t j = tid_k + k * THREADS;
+                    if (j < J) {
+                        const RsNext &N = A.next[j];
+                        ug[k] = N.ug;
+                        about[k] = N.dg | (A.st.ci[j] << 16) | (N.uc > 0.f ? RS_HAS_CPU : 0u) | (N.gi >= 0 ? RS_HOLDS : 0u);
                     }
-                    if (lane == 0) sh_go = ok ? 1u : 0u;
+                    asm volatile("" ::: "memory");
                 }
-                __syncthreads();
-                const uint32_t go = sh_go;
-                if (go) {                                       // the jobs whose state changed: all their cached values
-                    const uint32_t n_touched = sh_touched;           // a wavefront per job
-                    for (uint32_t i = wave; i < n_touched + 1u; i += RS_THREADS / 64)
-                        rs_refresh_wave(A, i < n_touched ? A.touched[i] : j, lane, sh_next, &sh_next_below, i >= n_touched);
-                }
-                __syncthreads();
-                if (!go) break;
+                changed_once = ~0u;
+                continue;
+            }
+            const uint32_t mine = lane < changed ? sh_upd[lane][0] : NONE;   // the threads that have these jobs
+            unsigned long long m = __ballot(mine != NONE && (mine % THREADS) / 64u == wave);
+            while (m) {
+                const uint32_t i = (uint32_t)__ffsll((long long)m) - 1u, v = wave_lane_u32(mine, i);
+                m &= m - 1ull;
+                const float g = __uint_as_float(sh_upd[i][1]);
+                const uint32_t d = sh_upd[i][2] | sh_upd[i][3];
+#pragma unroll
+                for (uint32_t k = 0; k < PER; ++k)
+                    if (tid + k * THREADS == v) { ug[k] = g; about[k] = d; changed_once |= 1u << k; }
             }
         }
     };
 
     // privileged jobs, in job order.  Who they are is known from the start: a job never gives below its floor, so
     // only a job that begins below it can be below it.
-    if (tid == 0) sh_nb = 0u;
-    const bool any_privileged = __syncthreads_or((int)(privileged != 0u)) != 0;
-    for (uint32_t base = 0; any_privileged && base < J; base += RS_THREADS) {   // their list, in job order: 1,024 jobs at a time
-        const uint32_t j = base + tid;
-        const bool is = j < J && A.first[j] != 0u;
-        const unsigned long long in_wave = __ballot(is);
-        if (lane == 0) sh_widx[wave] = (uint32_t)__popcll(in_wave);
-        __syncthreads();
-        uint32_t before = sh_nb, all = 0;
-        for (uint32_t w = 0; w < RS_THREADS / 64; ++w) {
-            if (w < wave) before += sh_widx[w];
-            all += sh_widx[w];
-        }
-        if (is) A.order[before + (uint32_t)__popcll(in_wave & ((1ull << lane) - 1ull))] = j;
-        __syncthreads();
-        if (tid == 0) sh_nb += all;
-    }
-    __syncthreads();
-    const uint32_t na = sh_nb;
-    for (uint32_t k = 0; k < na; ++k) schedule_job(A.order[k]);
-    __syncthreads();
-    // the others: their order is fixed once, by GPU slope, then CPU slope (both descending), then index
-    for (uint32_t j0 = tid; j0 < J; j0 += 4 * RS_THREADS) {
-        float ug[4], uc[4];
-        bool in[4];
-#pragma unroll
-        for (uint32_t k = 0; k < 4; ++k) {
-            const uint32_t j = j0 + k * RS_THREADS, at = j < J ? j : tid;
-            const bool part = rs_part(A, at);
-            const uint32_t first = A.first[at];
-            ug[k] = A.ug[at]; uc[k] = A.uc[at];
-            in[k] = part && !first;
-        }
-#pragma unroll
-        for (uint32_t k = 0; k < 4; ++k) {
-            const uint32_t j = j0 + k * RS_THREADS;
-            if (j >= J) continue;
-            A.sg[j] = in[k] ? ug[k] : -1.f;                     // the cached slopes are current; -1: not in the list
-            A.sc[j] = in[k] ? uc[k] : -1.f;
+    if (A.floor_seg) {
+        for (uint32_t base = 0; base < J; base += THREADS) {                 // their list, in job order
+            const uint32_t j = base + tid;
+            const bool is = j < J && A.first[j] != 0u;
+            const unsigned long long in_wave = __ballot(is);
+            if (lane == 0) sh_widx[wave] = (uint32_t)__popcll(in_wave);
+            __syncthreads();
+            uint32_t before = sh_nb, all = 0;
+            for (uint32_t w = 0; w < WAVES; ++w) {
+                if (w < wave) before += sh_widx[w];
+                all += sh_widx[w];
+            }
+            if (is) A.order[before + (uint32_t)__popcll(in_wave & ((1ull << lane) - 1ull))] = j;
+            __syncthreads();
+            if (tid == 0) sh_nb += all;
         }
     }
     __syncthreads();
+    const uint32_t n_first = sh_nb;
+    uint32_t k_first = 0;
     // Most jobs of a large round find nothing to do when their turn comes: no step, or a step that needs more than is
     // free while no other job's slope is lower than theirs.  Whether that is so follows from values that change only
     // when a step is committed: the job's own next steps (kept current for every job), what is free, and the two
     // lowest slopes among the jobs that can give.  Passing over such a job changes nothing, so the jobs need not be
     // sorted: all threads look for the first job in the order, after the one served last, that is not of that kind,
     // it is served in full, and the search starts again from the new state.
-    auto comes_before = [&](float ga, float ca, uint32_t a, float gb, float cb, uint32_t b) {
-        return ga > gb || (ga == gb && (ca > cb || (ca == cb && a < b)));
-    };
-    float last_g = INF, last_c = INF;                     // key of the job served last (before every job at first)
-    uint32_t last_j = 0u, moves_seen = 0xFFFFFFFFu;
-    for (;;) {
-        // (schedule_job, and what stands before the loop, end with a barrier behind everything that is read here; what is
-        // written here was last read before the barriers of rs_pick_first)
-        const bool fresh = sh_moves != moves_seen;        // a step was committed since the last look (or this is the first)
-        moves_seen = sh_moves;
-        if (fresh) {                                      // otherwise the lowest slopes are what they were
-            RsMin two[2];
-            rs_two_lowest<RS_THREADS / 64, RS_THREADS>(sh_ds, J, tid, lane, wave, sh_two_k, sh_two_s, two);
-            if (tid == 0) { sh_min[0] = two[0]; sh_min[1] = two[1]; }
-            if (tid == 2) sh_listed = 0u;
-            __syncthreads();
-        }
-        const unsigned long long free_g = sh_free[0], free_c = sh_free[1];
+    bool fresh = true;                                    // a step was committed since the last look (or this is the first)
+    uint32_t maybe = 0, yes = 0, passed = 0;              // a thread's jobs that may have something to do, that have, whose turn is over or never comes,
+    unsigned long long my_key = 0ull, last_key = ~0ull;   // and the first of the second kind; last_*: the job served last (before every job at first)
+    uint32_t my_j = NONE, last_j = 0u;
+    static_assert(PER <= 32, "a thread's jobs are the bits of a word");
+    // A wavefront asks those of its jobs that may have something to do whether they have, each thread the one with the highest
+    // slope first, until none is left that could come before the first that has (a thread's jobs are in its registers by an
+    // index the compiler knows; what is not there is asked of memory).
+    auto settle = [&]() {
+        const unsigned long long fr_g = sh_free[0], fr_c = sh_free[1];
         const RsMin mg = sh_min[0], mc = sh_min[1];
-        float best_g = -1.f, best_c = -1.f;                // -1: none found
-        uint32_t best_j = 0xFFFFFFFFu;
-        // A look after a committed step goes over all jobs and lists those that have something to do; until the next
-        // committed step the later looks go over that list only (if it held them all): nothing they depend on changes.
-        if (fresh || sh_listed > RS_LIST) {
-            for (uint32_t j0 = tid; j0 < J; j0 += 4 * RS_THREADS) {      // four jobs' values in flight
-                float kg[4], kc[4], ug[4], uc[4];
-                uint32_t dg[4];
-                unsigned long long dcg[4], dcc[4];
+        for (;;) {
+            float top = -1.f;
+            uint32_t at = 0;
 #pragma unroll
-                for (uint32_t k = 0; k < 4; ++k) {
-                    const uint32_t j = j0 + k * RS_THREADS;
-                    const bool in = j < J;
-                    kg[k] = in ? A.sg[j] : -1.f; kc[k] = in ? A.sc[j] : -1.f;
-                    ug[k] = in ? A.ug[j] : 0.f; uc[k] = in ? A.uc[j] : 0.f;
-                    dg[k] = in ? A.udg[j] : 0u; dcg[k] = in ? A.udc_g[j] : 0ull; dcc[k] = in ? A.udc_c[j] : 0ull;
+            for (uint32_t k = 0; k < PER; ++k) {          // (the slope of a job that has not changed is its place in the order)
+                const float x = (changed_once >> k) & 1u ? INF : ug[k];
+                const bool more = (((maybe >> k) & 1u) != 0u) & (x > top);
+                top = more ? x : top; at = more ? k : at;
+            }
+            const uint32_t first = wave_max_u32_rows((uint32_t)(my_key >> 32));
+            const bool ask = (top >= 0.f) & (rs_ordered(top) >= first);
+            if (!__any(ask)) break;
+            if (!ask) continue;
+            const uint32_t j = tid + at * THREADS, bit = 1u << at;
+            const RsNext *const N = A.next + j;
+            const unsigned long long key = A.okey[j], cg = N->dcg, cc = N->dcc;
+            const float up_g = N->ug, up_c = N->uc;
+            const uint32_t dg = N->dg;
+            const float lowest_g = j == mg.i1 ? mg.m2 : mg.m1, lowest_c = j == mc.i1 ? mc.m2 : mc.m1;
+            // GPU step: none; or GPUs are short and nobody may be shrunk for it; or the GPUs are there and its CPUs are not
+            const bool gpu_idle = !(up_g > 0.f) | (fr_g < dg ? !(up_g > lowest_g) : fr_c < cg);
+            const bool cpu_idle = !(up_c > 0.f) | ((fr_c < cc) & !(up_c > lowest_c));
+            const bool served = (key > last_key) | ((key == last_key) & (j <= last_j)) | (key == 0ull);
+            maybe &= ~bit;
+            passed |= served ? bit : 0u;
+            if ((gpu_idle & cpu_idle) | served) continue;
+            yes |= bit;
+            if (key > my_key || (key == my_key && j < my_j)) { my_key = key; my_j = j; }
+        }
+    };
+    auto look = [&]() {
+        if (!others) {                                    // the others: their order is what the slopes are now
+            others = true;
+            __syncthreads();                              // (they were stored by whoever found them)
+        }
+        bool settle_now = false;
+        if (fresh) {
+            if (wave < 2u) {                              // the two lowest slopes, and whose the lowest is: GPUs, CPUs
+                const float *const low = wave == 0u ? low_g : low_c;
+                const uint32_t n = one(sh_holders);
+                RsMin m = {INF, INF, NONE};
+                uint32_t place;
+                if (lowest(low, n, m.m1, place)) {
+                    m.i1 = one(who[place]);
+                    float rest = INF;
+                    for (uint32_t i = lane; i < n; i += 64u) rest = i != place ? fminf(rest, low[i]) : rest;
+                    m.m2 = rs_unordered(wave_min_u32_rows(rs_ordered(rest)));
                 }
+                if (lane == 0) sh_min[wave] = m;
+            }
+            if (wave == WAVES - 1u && lane < A.X.grid.n_cpu) {               // the GPUs whose CPUs are free, at every level
+                const unsigned long long fr = sh_free[1], l = A.X.grid.cpu_levels[lane];
+                const unsigned long long most = A.X.grid.cpu_mode ? fr / l : fr >= l ? RK_MAX_G : 0ull;
+                sh_most[lane] = most < RK_MAX_G ? (uint32_t)most : RK_MAX_G;
+            }
+            __syncthreads();
+            const uint32_t fr_g = sh_free[0] < RK_MAX_G ? (uint32_t)sh_free[0] : RK_MAX_G;       // (no step adds more)
+            const float lowest_g = sh_min[0].m1, last_ug = last_key == ~0ull ? INF : rs_unordered((uint32_t)(last_key >> 32));
+            const uint32_t held = A.X.grid.cpu_mode ? 0u : RS_HOLDS;         // CPUs that a job's amounts share: who holds something has them
+            maybe = 0u;
 #pragma unroll
-                for (uint32_t k = 0; k < 4; ++k) {
-                    const uint32_t j = j0 + k * RS_THREADS;
-                    if (kg[k] < 0.f || !comes_before(last_g, last_c, last_j, kg[k], kc[k], j)) continue;   // not in the list, or served
-                    const float lowest_g = j == mg.i1 ? mg.m2 : mg.m1, lowest_c = j == mc.i1 ? mc.m2 : mc.m1;
-                    // GPU step: none; or GPUs are short and nobody may be shrunk for it; or the GPUs are there and its CPUs are not
-                    const bool gpu_idle = !(ug[k] > 0.f) || (free_g < dg[k] ? !(ug[k] > lowest_g) : free_c < dcg[k]);
-                    const bool cpu_idle = !(uc[k] > 0.f) || (free_c < dcc[k] && !(uc[k] > lowest_c));
-                    if (gpu_idle && cpu_idle) continue;
-                    if (fresh) {
-                        const uint32_t at = atomicAdd(&sh_listed, 1u);
-                        if (at < RS_LIST) { sh_list_j[at] = j; sh_list_g[at] = kg[k]; sh_list_c[at] = kc[k]; }
-                    }
-                    if (best_j == 0xFFFFFFFFu || comes_before(kg[k], kc[k], j, best_g, best_c, best_j)) { best_g = kg[k]; best_c = kc[k]; best_j = j; }
+            for (uint32_t k = 0; k < PER; ++k) {          // who may have something to do, by what the registers say
+                const uint32_t w = about[k], dg = w & 0xFFFFu;
+                const bool cpus = (dg <= sh_most[(w >> 16) & 63u]) | ((w & held) != 0u);
+                const bool gpus = (ug[k] > 0.f) & ((fr_g < dg) ? (ug[k] > lowest_g) : cpus);
+                const bool later = (((changed_once >> k) & 1u) != 0u) | !(ug[k] > last_ug);
+                maybe |= ((gpus | ((w & RS_HAS_CPU) != 0u)) & later) ? 1u << k : 0u;
+                if (k % 4u == 3u) asm volatile("" ::: "memory");
+            }
+            maybe &= ~passed;
+            yes = 0u; my_key = 0ull; my_j = NONE;
+            settle_now = true;
+        } else if (wave == (last_j % THREADS) / 64u) {    // nothing was committed: only the thread whose job it was has another
+            if (tid == last_j % THREADS) {
+                yes &= ~(1u << (last_j / THREADS));
+                my_key = 0ull; my_j = NONE;
+                for (uint32_t m = yes; m; m &= m - 1u) {
+                    const uint32_t j = tid + ((uint32_t)__ffs((int)m) - 1u) * THREADS;
+                    const unsigned long long key = A.okey[j];
+                    if (key > my_key) { my_key = key; my_j = j; }            // (ascending jobs)
                 }
             }
+            settle_now = true;
+        }
+        // the first of the threads' jobs in the order
+        if (settle_now) {
+            settle();
+            unsigned long long key = 0ull;
+            uint32_t j = NONE;
+            if (__any(my_j != NONE)) {
+                const uint32_t hi = (uint32_t)(my_key >> 32), lo = (uint32_t)my_key;
+                const uint32_t top_hi = wave_max_u32_rows(hi), top_lo = wave_max_u32_rows(hi == top_hi ? lo : 0u);
+                j = wave_min_u32_rows(hi == top_hi && lo == top_lo ? my_j : NONE);
+                key = ((unsigned long long)top_hi << 32) | top_lo;
+            }
+            if (lane == 0) { sh_pick_key[wave] = key; sh_pick_j[wave] = j; }
+        }
+        rs_lds_barrier();
+        {
+            const uint32_t w = lane < WAVES ? lane : 0u;
+            const unsigned long long k2 = sh_pick_key[w];
+            const uint32_t j2 = sh_pick_j[w], hi2 = (uint32_t)(k2 >> 32), lo2 = (uint32_t)k2;
+            const uint32_t hi = NONE - wave_lane_u32(row_min_u32(NONE - hi2), 0u), lo = NONE - wave_lane_u32(row_min_u32(hi2 == hi ? NONE - lo2 : NONE), 0u);
+            last_key = ((unsigned long long)hi << 32) | lo;
+            last_j = wave_lane_u32(row_min_u32(k2 == last_key ? j2 : NONE), 0u);
+        }
+    };
+    for (;;) {                                            // one job per turn; ScheduleJob appears once in the code
+        uint32_t j;
+        if (k_first < n_first) {
+            j = one(A.order[k_first++]);
         } else {
-            const uint32_t listed = sh_listed;
-            for (uint32_t i = tid; i < listed; i += RS_THREADS) {
-                const uint32_t j = sh_list_j[i];
-                const float kg = sh_list_g[i], kc = sh_list_c[i];
-                if (!comes_before(last_g, last_c, last_j, kg, kc, j)) continue;                            // served
-                if (best_j == 0xFFFFFFFFu || comes_before(kg, kc, j, best_g, best_c, best_j)) { best_g = kg; best_c = kc; best_j = j; }
-            }
+            look();
+            if (last_j == NONE) break;
+            full += 1u;
+            j = last_j;
         }
-        {                                                    // the first of the threads' candidates in the order
-            const RsPick pick = rs_pick_first<RS_THREADS / 64>(best_g, best_c, best_j, lane, wave, sh_pick_key, sh_pick_j);
-            best_g = pick.g; best_c = pick.c; best_j = pick.j;
-        }
-        if (best_j == 0xFFFFFFFFu) break;
-        if (tid == 0) sh_full += 1u;
-        schedule_job(best_j);
-        last_g = best_g; last_c = best_c; last_j = best_j;
+        const bool any = schedule_job(j);
+        fresh = any || !others;
     }
-    __syncthreads();
-    for (uint32_t j0 = tid; j0 < J; j0 += 4 * RS_THREADS) {
-        int32_t gi[4];
-        uint32_t so[4], g[4];
-#pragma unroll
-        for (uint32_t k = 0; k < 4; ++k) {
-            const uint32_t j = j0 + k * RS_THREADS, at = j < J ? j : tid;
-            gi[k] = A.st.gi[at];
-            so[k] = A.X.tb.seg_off[at];
-        }
-#pragma unroll
-        for (uint32_t k = 0; k < 4; ++k) g[k] = gi[k] < 0 ? 0u : A.X.tb.seg_g[so[k] + (uint32_t)gi[k]];
-#pragma unroll
-        for (uint32_t k = 0; k < 4; ++k)
-            if (j0 + k * RS_THREADS < J) A.st.g[j0 + k * RS_THREADS] = g[k];
-    }
-    if (tid == 0 && A.stats) { A.stats[0] = sh_moves; A.stats[1] = sh_full; A.stats[2] = sh_shrinks; A.stats[3] = sh_undone; }
+    if (tid == 0 && A.stats) { A.stats[0] = moves; A.stats[1] = full; A.stats[2] = shrinks; A.stats[3] = undone; }
 }
 
 // Scratch of rk_allocate_static: one array in the library's image, so every device the library is loaded on holds
@@ -2821,17 +3027,13 @@ static int32_t launch_reschedule_rounds(rk_ctx *ctx, const float *ref_thr, const
     if ((rc = scratch_typed(ctx, arena, SL_ST_G, all, &st.g))) return rc;
     if ((rc = scratch_typed(ctx, arena, SL_ST_CI, all, &st.ci))) return rc;
     if ((rc = scratch_typed(ctx, arena, SL_ST_PARTIAL, (size_t)st.blocks_per_round * 2 * n_rounds, &st.partial))) return rc;
-    float *f32;
     uint32_t *u32;
-    unsigned long long *u64;
-    if ((rc = scratch_typed(ctx, arena, SL_RS_F32, all * 8, &f32))) return rc;
-    if ((rc = scratch_typed(ctx, arena, SL_RS_U32, all * 7, &u32))) return rc;
-    if ((rc = scratch_typed(ctx, arena, SL_RS_U64, all * 2, &u64))) return rc;
-    A.ds_g = f32; A.ds_c = f32 + all; A.sg = f32 + 2 * all; A.sc = f32 + 3 * all; A.ug = f32 + 4 * all; A.uc = f32 + 5 * all;
-    A.keep_ds = f32 + 6 * all;
-    A.order = u32; A.touched = u32 + all; A.stamp = u32 + 2 * all; A.first = u32 + 3 * all;
-    A.keep_gi = reinterpret_cast<int32_t *>(u32 + 4 * all); A.keep_ci = u32 + 5 * all; A.udg = u32 + 6 * all;
-    A.udc_g = u64; A.udc_c = u64 + all;
+    if ((rc = scratch_typed(ctx, arena, SL_RS_U32, all * 5, &u32))) return rc;
+    if ((rc = scratch_typed(ctx, arena, SL_RS_U64, all, &A.okey))) return rc;
+    if ((rc = scratch_typed(ctx, arena, SL_RS_NEXT, all, &A.next))) return rc;
+    if ((rc = scratch_typed(ctx, arena, SL_RS_GIVES, all, &A.gives))) return rc;
+    A.ug = reinterpret_cast<float *>(u32);
+    A.about = u32 + all; A.order = u32 + 2 * all; A.touched = u32 + 3 * all; A.first = u32 + 4 * all;
     Ctx &X = K.X;
     X.ref_thr = ref_thr; X.tb = table_dev(table); X.grid = grid_dev(grid); X.jb = 0; X.jmap = nullptr;
     X.best_thr = best_thr; X.best_plan = best_plan; X.curve_thr = curve_thr;
@@ -2864,13 +3066,16 @@ static int32_t launch_reschedule_rounds(rk_ctx *ctx, const float *ref_thr, const
         else k_rs_prepare<1><<<dim3((J + 255) / 256, n_rounds), 256, 0, s>>>(K);
         RK_CHECK_LAUNCH(ctx, "k_rs_prepare");
     }
-    const size_t lds = (size_t)2 * (J ? J : 1u) * sizeof(float);                // at most 96 KiB
-    if (lds > 64 * 1024 && !ctx->loop_lds_raised) {
-        RK_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(k_reschedule),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, 2 * RK_MAX_JOBS_PER_ROUND * sizeof(float)));
+    K.near = rs_near(J);
+    const size_t lds = rs_list_bytes(J ? J : 1u) + (size_t)K.near * sizeof(RsGives);
+    if (lds > 32 * 1024 && !ctx->loop_lds_raised) {
+        const auto most = hipFuncAttributeMaxDynamicSharedMemorySize;
+        RK_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(k_reschedule<RS_THREADS, RS_PER>), most, (int)RS_LDS_MOST));
+        RK_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(k_reschedule<RS_SMALL_THREADS, RS_SMALL_PER>), most, (int)RS_LDS_MOST));
         ctx->loop_lds_raised = true;
     }
-    k_reschedule<<<n_rounds, RS_THREADS, lds, s>>>(K);
+    if (J <= RS_SMALL_THREADS * RS_SMALL_PER) k_reschedule<RS_SMALL_THREADS, RS_SMALL_PER><<<n_rounds, RS_SMALL_THREADS, lds, s>>>(K);
+    else k_reschedule<RS_THREADS, RS_PER><<<n_rounds, RS_THREADS, lds, s>>>(K);
     RK_CHECK_LAUNCH(ctx, "k_reschedule");
     if (J > 0) {
         k_mem_wish<<<dim3(st.blocks_per_round, n_rounds), JOB_THREADS, 0, s>>>(X, st, assign);

@@ -51,7 +51,7 @@ enum {
     SL_ENUM_BACK,                                        // enumeration: totals and offsets in one piece for the host
     SL_PLACE_RESULT,                                     // placement: its four summary words
     SL_ENUM_LEADER, SL_ENUM_TAB, SL_ENUM_SUMS,           // enumeration: the job whose search a job shares, their hash table, sums per workgroup
-    SL_RS_F32, SL_RS_U32, SL_RS_U64,                     // the Schedule loop: cached slopes; order, marks and saved states; CPU needs
+    SL_RS_U32, SL_RS_U64, SL_RS_NEXT, SL_RS_GIVES,       // the Schedule loop: slopes, order and marks; places in the order; steps up and down
     SL_EVAL_PARTIAL,                                     // evaluation with best plan: keys of the segments that span tiles
     SL_PLACE_KEEP,                                       // placement: which jobs keep their earlier parts
     SL_PRIV_LIST,                                        // privileged jobs of the loop: the queued guaranteed jobs

@@ -5,7 +5,8 @@
 //   st.gi, st.ci                                       what every job holds: index of its GPU count (-1: nothing), CPU level
 //   G                                                  GPUs of the cluster (no step goes beyond)
 //   state, floor_seg, floor_c                          per job, each may be null
-//   ds_g, ds_c, ug, udg, udc_g, uc, udc_c              per job, for the cached values (rs_refresh*)
+//   ds_g, ds_c                                         per job, for the cached slopes (rs_refresh_give)
+//   next, gives                                        per job, for what is kept of it between its steps (rs_keep)
 #pragma once
 #include "rk_internal.h"
 #include "rk_model.h"
@@ -125,13 +126,11 @@ __device__ __forceinline__ uint32_t rs_fl_c(const Args &A, uint32_t j) {
     return c < A.X.grid.n_cpu ? c : A.X.grid.n_cpu - 1u;
 }
 
-// Next GPU step of job j.  `lanes` threads share the candidates (1: the calling thread alone; 64: a wavefront, all
+// Next GPU step of job j, which holds (gi, ci).  `lanes` threads share the candidates (1: the calling thread alone; 64: a wavefront, all
 // lanes get the result).  Highest slope, the smaller amount among equal slopes.
 template <class Args>
-__device__ RsStep rs_up_gpu(const Args &A, uint32_t j, uint32_t lane, uint32_t lanes) {
-    RsStep st = {0u, -1, A.st.ci[j], 0.f, 0.f, 0ull, 0ull};
-    const int32_t gi = A.st.gi[j];
-    const uint32_t ci = A.st.ci[j];
+__device__ RsStep rs_up_gpu(const Args &A, uint32_t j, int32_t gi, uint32_t ci, uint32_t lane, uint32_t lanes) {
+    RsStep st = {0u, -1, ci, 0.f, 0.f, 0ull, 0ull};
     const float ref = A.X.ref_thr[j];
     const float cur = rs_at(A, A.X.curve_thr, j, ci, gi);
     const int32_t fl = rs_fl_s(A, j);
@@ -172,9 +171,7 @@ __device__ RsStep rs_up_gpu(const Args &A, uint32_t j, uint32_t lane, uint32_t l
 }
 
 template <class Args>
-__device__ RsStep rs_up_cpu(const Args &A, uint32_t j, uint32_t lane, uint32_t lanes) {
-    const int32_t gi = A.st.gi[j];
-    const uint32_t ci = A.st.ci[j];
+__device__ RsStep rs_up_cpu(const Args &A, uint32_t j, int32_t gi, uint32_t ci, uint32_t lane, uint32_t lanes) {
     RsStep st = {0u, gi, ci, 0.f, 0.f, 0ull, 0ull};
     if (gi < 0) return st;
     const float ref = A.X.ref_thr[j];
@@ -261,31 +258,13 @@ __device__ RsGive rs_down_cpu_at(const Args &A, uint32_t v, int32_t gi, uint32_t
 template <class Args>
 __device__ __forceinline__ RsGive rs_down_cpu(const Args &A, uint32_t v) { return rs_down_cpu_at(A, v, A.st.gi[v], A.st.ci[v]); }
 
-// the cached slopes of job v after its state changed to (gi, ci): what it loses per unit it gives ...
+// the cached slopes of job v after its state changed to (gi, ci): what it loses per unit it gives
 template <class Args>
-__device__ __forceinline__ void rs_refresh_give_at(const Args &A, uint32_t v, int32_t gi, uint32_t ci, uint32_t lane, uint32_t lanes) {
-    const RsGive a = rs_down_gpu_at(A, v, gi, ci, lane, lanes), b = rs_down_cpu_at(A, v, gi, ci);
-    if (lane != 0) return;
+__device__ __forceinline__ void rs_refresh_give(const Args &A, uint32_t v) {
+    const RsGive a = rs_down_gpu(A, v), b = rs_down_cpu(A, v);
     A.ds_g[v] = a.any ? a.slope : __int_as_float(0x7F800000);
     A.ds_c[v] = b.any ? b.slope : __int_as_float(0x7F800000);
 }
-template <class Args>
-__device__ __forceinline__ void rs_refresh_give(const Args &A, uint32_t v) { rs_refresh_give_at(A, v, A.st.gi[v], A.st.ci[v], 0, 1); }
-// ... and its own next steps as well; `lanes` threads share the search for them (1, or the 64 of a wavefront).  The
-// steps themselves go to next[0] (GPUs) and next[1] (CPUs) when the caller wants them.
-template <class Args>
-__device__ __forceinline__ void rs_refresh_lanes(const Args &A, uint32_t v, uint32_t lane, uint32_t lanes, RsStep *next = nullptr) {
-    const RsGive a = rs_down_gpu(A, v, lane, lanes), b = rs_down_cpu(A, v);
-    const RsStep ug = rs_up_gpu(A, v, lane, lanes), uc = rs_up_cpu(A, v, lane, lanes);
-    if (lane != 0) return;
-    A.ds_g[v] = a.any ? a.slope : __int_as_float(0x7F800000);
-    A.ds_c[v] = b.any ? b.slope : __int_as_float(0x7F800000);
-    A.ug[v] = ug.any ? ug.slope : 0.f; A.udg[v] = (uint32_t)ug.dg; A.udc_g[v] = ug.dc;
-    A.uc[v] = uc.any ? uc.slope : 0.f; A.udc_c[v] = uc.dc;
-    if (next) { next[0] = ug; next[1] = uc; }
-}
-template <class Args>
-__device__ __forceinline__ void rs_refresh(const Args &A, uint32_t v) { rs_refresh_lanes(A, v, 0, 1); }
 
 // ---- the same steps for a wavefront that holds the job's rows in its registers
 // The searches above follow one load with the next.  A job of at most 64 amounts fits a wavefront, an amount per lane:
@@ -405,68 +384,141 @@ __device__ __forceinline__ RsStep rs_up_cpu_rows(const Args &A, const RsRows &R,
 }
 
 // Job v, which holds (gi, ci), steps down in GPUs (res 0) or one CPU level (res 1): what it gives, what it holds then,
-// and what it would lose per GPU / CPU given after that (infinite: nothing to give).  A whole wavefront calls; every
-// lane gets the result.
+// and what it would lose per GPU / CPU given after that (infinite: nothing to give).
 struct RsShrunk { RsGive gv; int32_t gi; uint32_t ci; float ds_g, ds_c; };
+// ... after it gave gv, `lanes` threads sharing the searches (1, or the 64 of a wavefront)
 template <class Args>
-__device__ __forceinline__ RsShrunk rs_shrink_wave(const Args &A, uint32_t v, uint32_t so, uint32_t ns, uint32_t res, int32_t gi, uint32_t ci,
+__device__ __forceinline__ RsShrunk rs_shrunk_at(const Args &A, uint32_t v, uint32_t res, int32_t gi, uint32_t ci, const RsGive &gv,
+                                                 uint32_t lane, uint32_t lanes) {
+    RsShrunk out;
+    out.gv = gv;
+    out.gi = res == 0 ? gv.tgt : gi;
+    out.ci = res == 0 ? (gv.tgt < 0 ? 0u : ci) : ci - 1u;           // (with nothing left, every step down is none)
+    const RsGive a = rs_down_gpu_at(A, v, out.gi, out.ci, lane, lanes), b = rs_down_cpu_at(A, v, out.gi, out.ci);
+    out.ds_g = a.any ? a.slope : __int_as_float(0x7F800000);
+    out.ds_c = b.any ? b.slope : __int_as_float(0x7F800000);
+    return out;
+}
+// ... for a wavefront that has the job's rows
+template <class Args>
+__device__ __forceinline__ RsShrunk rs_shrunk_rows(const Args &A, const RsRows &R, uint32_t res, int32_t gi, uint32_t ci, const RsGive &gv,
                                                    uint32_t lane) {
     RsShrunk out;
     RsGive a, b;
-    if (ns > 64u) {
-        out.gv = res == 0 ? rs_down_gpu_at(A, v, gi, ci, lane, 64) : rs_down_cpu_at(A, v, gi, ci);
-        out.gi = res == 0 ? out.gv.tgt : gi;
-        out.ci = res == 0 ? (out.gv.tgt < 0 ? 0u : ci) : ci - 1u;
-        a = rs_down_gpu_at(A, v, out.gi, out.ci, lane, 64);
-        b = rs_down_cpu_at(A, v, out.gi, out.ci);
+    out.gv = gv;
+    if (res == 0) {
+        out.gi = gv.tgt;
+        out.ci = gv.tgt < 0 ? 0u : ci;
+        a = rs_down_gpu_rows(A, R, R.curve, out.gi, ci, lane);
+        b = rs_down_cpu_rows(A, R, out.gi, out.ci, rs_lane_f(R.best, out.gi), rs_lane_f(R.best_lo, out.gi));
     } else {
-        const RsRows R = rs_rows(A, v, so, ns, gi, ci, lane);
-        if (res == 0) {
-            out.gv = rs_down_gpu_rows(A, R, R.curve, gi, ci, lane);
-            out.gi = out.gv.tgt;
-            out.ci = out.gv.tgt < 0 ? 0u : ci;                      // (with nothing left, every step down is none)
-            a = rs_down_gpu_rows(A, R, R.curve, out.gi, ci, lane);
-            b = rs_down_cpu_rows(A, R, out.gi, out.ci, rs_lane_f(R.best, out.gi), rs_lane_f(R.best_lo, out.gi));
-        } else {
-            out.gv = rs_down_cpu_rows(A, R, gi, ci, rs_lane_f(R.best, gi), rs_lane_f(R.best_lo, gi));
-            out.gi = gi;
-            out.ci = ci - 1u;
-            a = rs_down_gpu_rows(A, R, R.curve_lo, gi, out.ci, lane);
-            b = rs_down_cpu_rows(A, R, gi, out.ci, rs_lane_f(R.col, (int32_t)out.ci), rs_lane_f(R.col, (int32_t)out.ci - 1));
-        }
+        out.gi = gi;
+        out.ci = ci - 1u;
+        a = rs_down_gpu_rows(A, R, R.curve_lo, gi, out.ci, lane);
+        b = rs_down_cpu_rows(A, R, gi, out.ci, rs_lane_f(R.col, (int32_t)out.ci), rs_lane_f(R.col, (int32_t)out.ci - 1));
     }
     out.ds_g = a.any ? a.slope : __int_as_float(0x7F800000);
     out.ds_c = b.any ? b.slope : __int_as_float(0x7F800000);
     return out;
 }
-
-// rs_refresh_lanes for a whole wavefront and a job that holds (gi, ci), as memory says; with keep_next the next steps also
-// go to next[0] (GPUs) and next[1] (CPUs), and whether the job is below its floor to *next_below
+// A whole wavefront calls; every lane gets the result.
 template <class Args>
-__device__ __forceinline__ void rs_refresh_wave_at(const Args &A, uint32_t v, int32_t gi, uint32_t ci, uint32_t lane, RsStep *next,
-                                                   uint32_t *next_below, bool keep_next) {
-    const int32_t fl = rs_fl_s(A, v);
-    const uint32_t so = A.X.tb.seg_off[v], ns = A.X.tb.seg_off[v + 1] - so;
-    if (ns > 64u || (fl >= 0 && gi < fl)) {
-        RsStep up[2];
-        rs_refresh_lanes(A, v, lane, 64, up);
-        if (lane == 0 && keep_next) { next[0] = up[0]; next[1] = up[1]; *next_below = (fl >= 0 && gi < fl) ? 1u : 0u; }
-        return;
+__device__ __forceinline__ RsShrunk rs_shrink_wave(const Args &A, uint32_t v, uint32_t so, uint32_t ns, uint32_t res, int32_t gi, uint32_t ci,
+                                                   uint32_t lane) {
+    if (ns > 64u) {
+        const RsGive gv = res == 0 ? rs_down_gpu_at(A, v, gi, ci, lane, 64) : rs_down_cpu_at(A, v, gi, ci);
+        return rs_shrunk_at(A, v, res, gi, ci, gv, lane, 64);
     }
     const RsRows R = rs_rows(A, v, so, ns, gi, ci, lane);
-    const RsGive a = rs_down_gpu_rows(A, R, R.curve, gi, ci, lane);
-    const RsGive b = rs_down_cpu_rows(A, R, gi, ci, rs_lane_f(R.best, gi), rs_lane_f(R.best_lo, gi));
-    const RsStep ug = rs_up_gpu_rows(A, R, gi, ci, lane), uc = rs_up_cpu_rows(A, R, gi, ci, lane);
-    if (lane != 0) return;
-    A.ds_g[v] = a.any ? a.slope : __int_as_float(0x7F800000);
-    A.ds_c[v] = b.any ? b.slope : __int_as_float(0x7F800000);
-    A.ug[v] = ug.any ? ug.slope : 0.f; A.udg[v] = (uint32_t)ug.dg; A.udc_g[v] = ug.dc;
-    A.uc[v] = uc.any ? uc.slope : 0.f; A.udc_c[v] = uc.dc;
-    if (keep_next) { next[0] = ug; next[1] = uc; *next_below = 0u; }
+    const RsGive gv = res == 0 ? rs_down_gpu_rows(A, R, R.curve, gi, ci, lane)
+                               : rs_down_cpu_rows(A, R, gi, ci, rs_lane_f(R.best, gi), rs_lane_f(R.best_lo, gi));
+    return rs_shrunk_rows(A, R, res, gi, ci, gv, lane);
 }
-template <class Args>
-__device__ __forceinline__ void rs_refresh_wave(const Args &A, uint32_t v, uint32_t lane, RsStep *next, uint32_t *next_below, bool keep_next) {
-    rs_refresh_wave_at(A, v, A.st.gi[v], A.st.ci[v], lane, next, next_below, keep_next);
+
+// What the loop over totals keeps of a job in the state a step finds it in, so that neither its own next steps nor the
+// first step down that it is asked for wait for its rows: both steps up, and both steps down with the slopes after them.
+// The halves are written by whoever finds the steps in GPUs and in CPUs, 16 bytes at a time.
+struct __align__(16) RsNext {
+    float ug; uint32_t dg; float gain_g; int32_t tgt_g;              // the GPU step (tgt_g -1: none)
+    uint32_t lvl_g, below_ns; unsigned long long dcg;                // below_ns: its number of amounts, RS_BELOW when it is below its floor
+    float uc, gain_c; uint32_t lvl_c; int32_t slot;                  // the CPU step (uc 0: none); the job's place in the list of holders, -1: none
+    unsigned long long dcc; int32_t gi; uint32_t so;                 // the amount it holds; where its amounts begin in the plan table
+};
+struct __align__(16) RsGives {                                        // (of a job that holds something)
+    uint32_t dg0; float loss0; uint32_t gis; float ds_g0;            // a step down in GPUs; gis: amounts before << 16 | after (0xFFFF: none)
+    float ds_c0, ds_g; unsigned long long dc0;                       // ds_g, ds_c: the slopes in this state, ds_*0 and ds_*1 after the step
+    float loss1, ds_g1, ds_c1, ds_c;                                 // a CPU level down
+    unsigned long long dc1; uint32_t ci_ns, so;                      // the level before, its number of amounts << 8, where they begin
+};
+static_assert(sizeof(RsNext) == 64 && sizeof(RsGives) == 64, "four pieces each");
+constexpr uint32_t RS_BELOW = 0x80000000u;
+struct RsKept { float ds_g, ds_c, ug, uc; uint32_t dg, g; };
+
+// Finds and stores it for job v, which holds (gi, ci); LANES: the 64 of a wavefront, which has the rows
+// of a job of at most 64 amounts at once, or 1.  so, ns: where the job's amounts begin and how many they are; with_g, with_c:
+// the halves to do; gives: where the steps down go; also: where else the steps up go, or null.  (g: the GPUs it holds, with_g.)
+template <uint32_t LANES, class Args>
+__device__ __forceinline__ RsKept rs_keep(const Args &A, uint32_t v, uint32_t so, uint32_t ns, int32_t gi, uint32_t ci, int32_t slot, uint32_t lane,
+                                          bool with_g, bool with_c, RsGives *gives, RsNext *also) {
+    const float INF = __int_as_float(0x7F800000);
+    const int32_t fl = rs_fl_s(A, v);
+    const bool below = fl >= 0 && gi < fl, rows = LANES == 64u && ns <= 64u && !below;
+    RsRows R = {};
+    if (rows) R = rs_rows(A, v, so, ns, gi, ci, lane);
+    RsKept k = {INF, INF, 0.f, 0.f, 0u, 0u};
+    auto store = [](void *to, uint32_t a, uint32_t b, uint32_t c, uint32_t d) { *static_cast<uint4 *>(to) = uint4{a, b, c, d}; };
+    if (with_g) {
+        const RsGive a = rows ? rs_down_gpu_rows(A, R, R.curve, gi, ci, lane) : rs_down_gpu_at(A, v, gi, ci, lane, LANES);
+        const RsStep u = rows ? rs_up_gpu_rows(A, R, gi, ci, lane) : rs_up_gpu(A, v, gi, ci, lane, LANES);
+        k.g = rows ? rs_lane_u(R.g, gi) : (uint32_t)rs_g(A, v, gi);
+        k.ds_g = a.any ? a.slope : INF;
+        k.ug = u.any ? u.slope : 0.f; k.dg = (uint32_t)u.dg;
+        RsShrunk s = {a, -1, 0u, INF, INF};
+        if (a.any) s = rows ? rs_shrunk_rows(A, R, 0, gi, ci, a, lane) : rs_shrunk_at(A, v, 0, gi, ci, a, lane, LANES);
+        if (lane == 0) {
+            auto up = [&](RsNext *to) {
+                store(&to->ug, __float_as_uint(k.ug), k.dg, __float_as_uint(u.gain), u.any ? (uint32_t)u.tgt : 0xFFFFFFFFu);
+                store(&to->lvl_g, u.lvl, ns | (below ? RS_BELOW : 0u), (uint32_t)u.dc, (uint32_t)(u.dc >> 32));
+            };
+            up(A.next + v);
+            if (also) up(also);
+            if (gi >= 0) {
+                RsGives *to = gives;
+                store(&to->dg0, (uint32_t)a.dg, __float_as_uint(a.loss), ((uint32_t)gi << 16) | ((uint32_t)s.gi & 0xFFFFu), __float_as_uint(s.ds_g));
+                store(&to->ds_c0, __float_as_uint(s.ds_c), __float_as_uint(k.ds_g), (uint32_t)a.dc, (uint32_t)(a.dc >> 32));
+            }
+        }
+    }
+    if (with_c) {
+        const RsGive b = rows ? rs_down_cpu_rows(A, R, gi, ci, rs_lane_f(R.best, gi), rs_lane_f(R.best_lo, gi)) : rs_down_cpu_at(A, v, gi, ci);
+        const RsStep u = rows ? rs_up_cpu_rows(A, R, gi, ci, lane) : rs_up_cpu(A, v, gi, ci, lane, LANES);
+        k.ds_c = b.any ? b.slope : INF;
+        k.uc = u.any ? u.slope : 0.f;
+        RsShrunk s = {b, -1, 0u, INF, INF};
+        if (b.any) s = rows ? rs_shrunk_rows(A, R, 1, gi, ci, b, lane) : rs_shrunk_at(A, v, 1, gi, ci, b, lane, LANES);
+        if (lane == 0) {
+            auto up = [&](RsNext *to) {
+                store(&to->uc, __float_as_uint(k.uc), __float_as_uint(u.gain), u.lvl, (uint32_t)slot);
+                store(&to->dcc, (uint32_t)u.dc, (uint32_t)(u.dc >> 32), (uint32_t)gi, so);
+            };
+            up(A.next + v);
+            if (also) up(also);
+            if (gi >= 0) {
+                RsGives *to = gives;
+                store(&to->loss1, __float_as_uint(b.loss), __float_as_uint(s.ds_g), __float_as_uint(s.ds_c), __float_as_uint(k.ds_c));
+                store(&to->dc1, (uint32_t)b.dc, (uint32_t)(b.dc >> 32), ci | (ns << 8), so);
+            }
+        }
+    }
+    return k;
+}
+
+// What the lanes of a wavefront stored so far is seen by all its lanes from here on: the hardware keeps a wavefront's
+// accesses in order, so only the compiler has to.
+__device__ __forceinline__ void rs_wave_order() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+    asm volatile("" ::: "memory");
 }
 
 // A workgroup barrier that orders LDS traffic only: every wavefront waits for its own LDS operations, not for its

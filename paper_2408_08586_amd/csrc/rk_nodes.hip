@@ -162,7 +162,9 @@ __device__ __forceinline__ float nd_lowest_on_wave(const NdArgs &A, uint32_t n, 
 // that ScheduleJob need not search them again.  `lanes` threads share the search (1, or the 64 of a wavefront).
 __device__ __forceinline__ void nd_refresh(const NdArgs &A, uint32_t v, uint32_t lane, uint32_t lanes) {
     const RsGive a = rs_down_gpu(A, v), b = rs_down_cpu(A, v);
-    const RsStep ug = rs_up_gpu(A, v, lane, lanes), uc = rs_up_cpu(A, v, lane, lanes);
+    const int32_t gi = A.st.gi[v];
+    const uint32_t ci = A.st.ci[v];
+    const RsStep ug = rs_up_gpu(A, v, gi, ci, lane, lanes), uc = rs_up_cpu(A, v, gi, ci, lane, lanes);
     if (lane != 0) return;
     A.ds_g[v] = a.any ? a.slope : __int_as_float(0x7F800000);
     A.ds_c[v] = b.any ? b.slope : __int_as_float(0x7F800000);
@@ -538,14 +540,6 @@ __device__ __forceinline__ uint32_t nd_wave_scan(uint32_t v) {
 }
 __device__ __forceinline__ uint32_t nd_wave_sum(uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)nd_wave_scan(v), 63); }
 
-// What the lanes of a wavefront stored so far is seen by all its lanes from here on: the hardware keeps a wavefront's
-// accesses in order, so only the compiler has to.
-__device__ __forceinline__ void nd_wave_order() {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_wave_barrier();
-    asm volatile("" ::: "memory");
-}
-
 // Words of dynamic LDS that k_nodes_lds needs: the nodes and their copy, the cached slopes, memory, and (LJ) everything
 // else a job has.
 constexpr uint32_t ND_LDS_JOB_WORDS = 22;
@@ -687,7 +681,7 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
         touched += 1u;
     };
     auto put_jobs_back = [&]() {
-        nd_wave_order();
+        rs_wave_order();
         for (uint32_t i = lane; i < touched; i += 64u) {
             const uint32_t v = A.touched[i];
             A.st.gi[v] = A.keep_gi[v]; A.st.ci[v] = A.keep_ci[v];
@@ -761,12 +755,12 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
                 if (__ballot(short_of)) ok = false;
                 return ok;
             });
-            nd_wave_order();
+            rs_wave_order();
         }
         const float own = A.ds_g[j];                         // j gives nothing to itself
-        nd_wave_order();
+        rs_wave_order();
         if (lane == 0) A.ds_g[j] = INF;
-        nd_wave_order();
+        rs_wave_order();
         uint32_t n0 = 0;
         while (ok && lack > 0 && n0 < N) {                   // the walk over the nodes, a node per lane
             const uint32_t n = n0 + lane;
@@ -805,7 +799,7 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
             }
             const uint32_t got = wave_lane_u32(upto, last < 64u ? last : 63u);
             lack -= got < lack ? got : lack;
-            nd_wave_order();
+            rs_wave_order();
             if (ask_t >= done_t) { n0 += 64u; continue; }    // (nobody to ask; when the step has its GPUs the walk ends)
             const uint32_t f = n0 + ask_t, base = f * gpn;
             n0 = f + 1u;
@@ -863,7 +857,7 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
                 }
                 lack -= t;
                 uint32_t rest = dg - here;
-                nd_wave_order();
+                rs_wave_order();
                 if (rest > 0)                                // the rest from its other parts, the last one first
                     for_parts(who, std::true_type{}, [&](uint32_t b, uint32_t w, unsigned long long m) {
                         const uint32_t k = (m >> lane) & 1ull ? w & 0xFFFFu : 0u, upto = nd_wave_scan(k), all = wave_lane_u32(upto, 63u);
@@ -879,11 +873,11 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
                                 A.cnt[n1] = l;
                             }
                         }
-                        nd_wave_order();
+                        rs_wave_order();
                         rest -= all < rest ? all : rest;
                         return rest > 0;
                     });
-                nd_wave_order();
+                rs_wave_order();
             }
         }
         if (lane == 0) A.ds_g[j] = own;
@@ -913,7 +907,7 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
                     if (free_here >= need) {
                         if (lane == 0) A.free_c[n] = free_here - (uint32_t)need;
                         dirty = true;
-                        nd_wave_order();
+                        rs_wave_order();
                         break;
                     }
                     uint32_t who;
@@ -936,7 +930,7 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
                         if ((m2 >> lane) & 1ull) A.free_c[over(b2 + lane, rcp_gpn)] += less * (w2 & 0xFFFFu);
                         return true;
                     });
-                    nd_wave_order();
+                    rs_wave_order();
                 }
             }
             return true;

@@ -366,6 +366,44 @@ def test_job_counts_around_the_passes(gpu, orc, J):
     run.close()
 
 
+@pytest.mark.parametrize("J,take,each", [(70, 63, 1), (70, 64, 1), (70, 65, 1), (600, 511, 1), (600, 513, 1), (600, 599, 1),
+                                         (300, 420, 2), (900, 1400, 2), (5000, 4092, 1)])
+def test_a_step_that_many_jobs_give_to(gpu, orc, J, take, each):
+    """One job below its floor takes `take` GPUs from jobs of equal slopes that hold `each`: steps that change as many jobs as
+    the kernel's lists in LDS hold and one more, jobs that give twice in a step, lists of holders beyond what a load
+    covers.  Then every job has its turn, and the steps that fail put everything back."""
+    rng = np.random.default_rng(98300 + take)
+    bounds = workloads.Bounds(g_max=take, tp_max=1)
+    ints = np.tile(np.array([[1, 4 if take % 4 else 8, 1]], np.uint32), (J, 1))
+    ints[0, 1] = take
+    tb = orc.enumerate_plans(ints, bounds)
+    grid = workloads.Grid(np.array([1, 2], np.uint32), 1, np.array([1.0], np.float32), 0)
+    vals = []
+    for j in range(J):
+        g = np.asarray(tb.seg_g[tb.seg_off[j]:tb.seg_off[j + 1]], np.float64)
+        v = np.where(g == take, 8.0, 0.25) if j == 0 else np.minimum(g, 4) * (1.0 if j % 7 else 1.5)
+        vals += [v, v * (1.0 if j % 3 else 1.125)]
+    bt = np.concatenate(vals).astype(np.float32)
+    bp = rng.integers(0, 1000, bt.size).astype(np.uint32)
+    ct, _, _ = orc.curves(tb, grid, bt, bp)
+    cur_seg = np.full(J, each - 1, np.int32)                     # their amounts are 1, 2, 4 ...
+    cur_seg[0] = -1
+    cur_c = rng.integers(0, 2, J).astype(np.uint32)
+    floor_seg, floor_c = np.full(J, -1, np.int32), np.zeros(J, np.uint32)
+    floor_seg[0] = int(tb.seg_off[1]) - 1
+    cl = workloads.Cluster(each * (J - 1), 4 * each * J, 1e9)
+    coef = np.tile(workloads.tiny().coef[:1], (J, 1))
+    coef[:, 16] = 1.0
+    wl = workloads.Workload("many", coef, ints, bounds, grid, workloads.Env(), cl)
+    want = orc.reschedule(coef[:, 16], tb, grid, cl, bt, bp, ct, cur_seg, cur_c, floor_seg, floor_c)
+    run = gpu(wl)
+    run.enumerate()
+    got = on_gpu(run, bt, bp, ct, cl, cur_seg, cur_c, floor_seg, floor_c, None)
+    run.close()
+    same(got, want)
+    assert want[0]["g"][0] == take and np.sum(want[0]["g"][1:] < each) >= take // 2
+
+
 def test_argument_errors(gpu, orc):
     import paper_2408_08586_amd as rk
     wl = workloads.tiny()
