@@ -29,7 +29,10 @@ constexpr int ND_THREADS = 1024;
 constexpr int ND_WAVES = ND_THREADS / 64;
 constexpr uint32_t ND_NONE = 0xFFFFFFFFu;
 constexpr uint32_t ND_PER = (RK_MAX_NODES + ND_THREADS - 1) / ND_THREADS;   // nodes per thread, at most
-constexpr int ND_SMALL_THREADS = 256;
+// The workgroup of rounds whose jobs are in LDS too: 512 threads find the new values of up to four jobs at once after a
+// committed step (406 jobs: 256 threads are 3 % slower), 256 have the cheaper barriers where a thread has one job at most
+// (60 jobs: 512 threads are 2 % slower).
+constexpr int ND_SMALL_THREADS = 512, ND_FEW_THREADS = 256;
 constexpr size_t ND_LDS_MOST = 156 * 1024;                                    // dynamic LDS of a workgroup: 160 KiB less what the kernels declare
 constexpr uint32_t ND_MAX_GPUS = 1u << 20;                                   // nodes x GPUs per node
 
@@ -68,6 +71,9 @@ struct NdBody {
     uint32_t *lvl_g, *lvl_c;         // the CPU level each step ends on (no GPU step: tgt_g -1; no CPU step: uc 0)
     uint32_t *udg, *touched, *stamp, *first, *keep_ci, *np, *tmp_off;
     int32_t *keep_gi;
+    RsGives *gives;                  // its step down in GPUs, kept for the first time a step asks for it (k_nodes_lds; the first half and
+    uint4 *give;                     // `ci_ns, so`); in LDS with the jobs: GPUs, loss, amount after, slope after,
+    float *give_c;                   // and CPU slope after (then give is not null)
     unsigned long long *udc_c, *okey;   // okey: a job's place in the order (k_nodes_lds)
     uint32_t *plist;                 // parts of one job: (node, GPUs) pairs, ascending node
     uint32_t *tmp_parts;             // parts of all jobs, (node << 16 | GPUs), grouped by job, in no order
@@ -158,14 +164,29 @@ __device__ __forceinline__ float nd_lowest_on_wave(const NdArgs &A, uint32_t n, 
     return low == ~0ull ? INF : rs_unordered((uint32_t)(low >> 32));
 }
 
+// What job v, which holds (gi, ci), gives as a: kept for k_nodes_lds.
+__device__ __forceinline__ void nd_keep_give(const NdArgs &A, uint32_t v, uint32_t so, uint32_t ns, int32_t gi, uint32_t ci, const RsGive &a, const RsShrunk &s) {
+    if (A.give) {
+        A.give[v] = uint4{(uint32_t)a.dg, __float_as_uint(a.loss), (uint32_t)s.gi, __float_as_uint(s.ds_g)};
+        A.give_c[v] = s.ds_c;
+    } else if (gi >= 0) {
+        uint4 *const to = reinterpret_cast<uint4 *>(A.gives + v);
+        to[0] = uint4{(uint32_t)a.dg, __float_as_uint(a.loss), ((uint32_t)gi << 16) | ((uint32_t)s.gi & 0xFFFFu), __float_as_uint(s.ds_g)};
+        to[1] = uint4{__float_as_uint(s.ds_c), __float_as_uint(a.any ? a.slope : __int_as_float(0x7F800000)), ci | (ns << 8), so};
+    }
+}
+
 // All cached values of job v from its present state: what it gives (rs_refresh_give) and its next steps in full, so
 // that ScheduleJob need not search them again.  `lanes` threads share the search (1, or the 64 of a wavefront).
 __device__ __forceinline__ void nd_refresh(const NdArgs &A, uint32_t v, uint32_t lane, uint32_t lanes) {
-    const RsGive a = rs_down_gpu(A, v), b = rs_down_cpu(A, v);
     const int32_t gi = A.st.gi[v];
-    const uint32_t ci = A.st.ci[v];
+    const uint32_t ci = A.st.ci[v], so = A.seg_off[v], ns = A.seg_off[v + 1] - so;
+    const RsGive a = rs_down_gpu_at(A, v, gi, ci, lane, lanes), b = rs_down_cpu_at(A, v, gi, ci);
     const RsStep ug = rs_up_gpu(A, v, gi, ci, lane, lanes), uc = rs_up_cpu(A, v, gi, ci, lane, lanes);
+    RsShrunk s = {a, -1, 0u, 0.f, 0.f};
+    if (a.any) s = rs_shrunk_at(A, v, 0, gi, ci, a, lane, lanes);
     if (lane != 0) return;
+    nd_keep_give(A, v, so, ns, gi, ci, a, s);
     A.ds_g[v] = a.any ? a.slope : __int_as_float(0x7F800000);
     A.ds_c[v] = b.any ? b.slope : __int_as_float(0x7F800000);
     A.ug[v] = ug.any ? ug.slope : 0.f; A.udg[v] = (uint32_t)ug.dg;   // (a step that exists has its slope here)
@@ -183,7 +204,10 @@ __device__ __forceinline__ void nd_refresh_wave(const NdArgs &A, uint32_t v, int
     if (with_g) {
         const RsGive a = rs_down_gpu_rows(A, R, R.curve, gi, ci, lane);
         const RsStep ug = rs_up_gpu_rows(A, R, gi, ci, lane);
+        RsShrunk s = {a, -1, 0u, 0.f, 0.f};
+        if (a.any) s = rs_shrunk_rows(A, R, 0, gi, ci, a, lane);
         if (lane == 0) {
+            nd_keep_give(A, v, so, ns, gi, ci, a, s);
             A.ds_g[v] = a.any ? a.slope : __int_as_float(0x7F800000);
             A.ug[v] = ug.any ? ug.slope : 0.f; A.udg[v] = (uint32_t)ug.dg;
             A.gain_g[v] = ug.gain; A.tgt_g[v] = ug.tgt; A.lvl_g[v] = ug.lvl;
@@ -543,8 +567,9 @@ __device__ __forceinline__ uint32_t nd_wave_sum(uint32_t v) { return (uint32_t)_
 // Words of dynamic LDS that k_nodes_lds needs: the nodes and their copy, the cached slopes, memory, and (LJ) everything
 // else a job has.
 constexpr uint32_t ND_LDS_JOB_WORDS = 22;
+constexpr uint32_t ND_TOUCHED = 64;                        // jobs changed by a step that are remembered in registers (the others in memory)
 static inline size_t nd_lds_words(size_t J, size_t N, size_t nodes_words, bool lj) {
-    return 2 * nodes_words + 2 * (J + 1) + N + (lj ? ND_LDS_JOB_WORDS * J + 1 : 0);
+    return 2 * nodes_words + 2 * (J + 1) + N + (J + 31) / 32 + (lj ? ND_LDS_JOB_WORDS * J + 1 : 0);
 }
 
 // The loop with the nodes in LDS.  It is a chain of small decisions, so what bounds it is the latency of one after
@@ -553,6 +578,9 @@ static inline size_t nd_lds_words(size_t J, size_t N, size_t nodes_words, bool l
 // looked up: nothing is exchanged between wavefronts within a step, every table it reads and writes is in LDS, and
 // what the others do (the look for the next job, the slopes of the jobs that a step changed, the copy of the nodes)
 // stands between two barriers after it.  LJ: what the jobs hold and their cached steps are in LDS too.
+// What a job gives first in a step was found when its state last changed (nd_keep_give), what a step changed is
+// remembered a job per lane, and a shrunk job's other parts are looked for 256 entries at a time: 10,000 jobs on 512 nodes,
+// the round from the descriptors: 1,174 -> 1,058 and 2,980 -> 2,620 us on two drawn states.
 template <int THREADS, bool LJ>
 __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
     extern __shared__ uint4 sh_raw[];
@@ -574,9 +602,12 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
     uint32_t *at = keep + A.nodes_words;
     auto take = [&](size_t words) { uint32_t *p = at; at += words; return p; };
     A.free_g = nodes; A.free_c = nodes + N; A.cnt = nodes + 2 * N; A.res = nodes + ((3 * N + 3) & ~3u);
+    if constexpr (LJ) A.give = reinterpret_cast<uint4 *>(take(4 * (size_t)J));
     if constexpr (LJ) { A.udc_c = reinterpret_cast<unsigned long long *>(take(2 * (size_t)J)); A.okey = reinterpret_cast<unsigned long long *>(take(2 * (size_t)J)); }
     float *const sh_ds = reinterpret_cast<float *>(take(2 * ((size_t)J + 1)));
     float *const sh_mem = reinterpret_cast<float *>(take(N));
+    uint32_t *const sh_mark = take((J + 31u) / 32u);         // a bit per job: changed by the step under way and remembered in memory
+    for (uint32_t i = tid; i < (J + 31u) / 32u; i += THREADS) sh_mark[i] = 0u;
     for (uint32_t i = tid; i < A.nodes_words; i += THREADS) nodes[i] = i < N ? gpn : i < 2 * N ? A.cpn : i < 3 * N ? 0u : EMPTY;
     if (tid < A.X.grid.n_cpu) {
         const uint32_t l = A.X.grid.cpu_levels[tid];
@@ -587,8 +618,7 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
         auto words = [&](auto &p) { p = reinterpret_cast<std::decay_t<decltype(p)>>(take(J)); };         // a per-job array of words in LDS
         words(A.st.gi); words(A.st.ci); words(A.ug); words(A.uc); words(A.udg); words(A.gain_g); words(A.gain_c);
         words(A.tgt_g); words(A.lvl_g); words(A.lvl_c); words(A.first);
-        words(A.stamp); words(A.keep_gi); words(A.keep_ci); words(A.touched);
-        A.keep_ds = reinterpret_cast<float *>(take(2 * (size_t)J));
+        words(A.touched); words(A.give_c);
         uint32_t *const so = take((size_t)J + 1);
         for (uint32_t j = tid; j < J; j += THREADS) {        // (all of a job's loads before the first store)
             const NdBody &b = K.b;
@@ -596,6 +626,10 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
             const uint32_t ci = b.st.ci[j], udg = b.udg[j], lg = b.lvl_g[j], lc = b.lvl_c[j], first = b.first[j], o = K.X.tb.seg_off[j];
             const float ug = b.ug[j], uc = b.uc[j], gg = b.gain_g[j], gc = b.gain_c[j];
             const unsigned long long dc = b.udc_c[j];
+            const uint4 *const gives = reinterpret_cast<const uint4 *>(b.gives + j);
+            const uint4 g0 = gi >= 0 ? gives[0] : uint4{0u, 0u, 0u, 0u};
+            const uint32_t g1 = gi >= 0 ? gives[1].x : 0u;
+            A.give[j] = uint4{g0.x, g0.y, (uint32_t)(int32_t)(int16_t)(g0.z & 0xFFFFu), g0.w}; A.give_c[j] = __uint_as_float(g1);
             A.st.gi[j] = gi; A.st.ci[j] = ci; A.ug[j] = ug; A.uc[j] = uc; A.udg[j] = udg; A.gain_g[j] = gg; A.gain_c[j] = gc;
             A.tgt_g[j] = tgt; A.lvl_g[j] = lg; A.lvl_c[j] = lc; A.first[j] = first; A.udc_c[j] = dc; so[j] = o;
         }
@@ -605,7 +639,6 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
     uint32_t bad = 0, any_first = 0;
     for (uint32_t j = tid; j < J; j += THREADS) {
         sh_ds[j] = A.ds_g[j]; sh_ds[J + 1 + j] = A.ds_c[j];
-        A.stamp[j] = 0u;
         bad |= A.first[j] & 2u; any_first |= A.first[j] & 1u;
     }
     A.ds_g = sh_ds; A.ds_c = sh_ds + J + 1;
@@ -666,32 +699,52 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
     __syncthreads();
 
     // ---- the first wavefront's part: a step of ScheduleJob.  Values without a lane are the same in all lanes.
-    uint32_t moves = 0, full = 0, shrinks = 0, undone = 0, epoch = 0;        // (the first wavefront's counts)
+    uint32_t moves = 0, full = 0, shrinks = 0, undone = 0;   // (the first wavefront's counts)
     uint32_t touched = 0;                                    // jobs this step has changed so far
     float lost = 0.f;
     bool dirty = false;                                      // the nodes are not as they were when the step began
-    auto remember = [&](uint32_t v, int32_t gi, uint32_t ci, uint32_t stamp) {       // (of job v before the step)
-        if (stamp == epoch) return;
-        if (lane == 0) {
-            A.stamp[v] = epoch;
-            A.keep_gi[v] = gi; A.keep_ci[v] = ci;
-            A.keep_ds[2 * v] = A.ds_g[v]; A.keep_ds[2 * v + 1] = A.ds_c[v];
-            A.touched[touched] = v;
+    // job v as it was before this step changed it for the first time: a job per lane, then in memory (all lanes call)
+    uint32_t was_j = ND_NONE, was = 0;                       // the job; its amount << 16 | level
+    float was_g = 0.f, was_c = 0.f;                          // its slopes
+    auto remember = [&](uint32_t v, int32_t gi, uint32_t ci) {
+        if (touched < ND_TOUCHED) {
+            if (lane == touched) { was_j = v; was = ((uint32_t)gi << 16) | ci; was_g = A.ds_g[v]; was_c = A.ds_c[v]; }
+        } else if (lane == 0) {
+            K.b.keep_gi[touched] = gi; K.b.keep_ci[touched] = ci;
+            K.b.keep_ds[2 * touched] = A.ds_g[v]; K.b.keep_ds[2 * touched + 1] = A.ds_c[v];
+            sh_mark[v >> 5] |= 1u << (v & 31u);
         }
+        if (lane == 0) A.touched[touched] = v;
         touched += 1u;
     };
-    auto put_jobs_back = [&]() {
+    auto remembered = [&](uint32_t v) {
+        return __ballot(was_j == v) != 0ull ||
+               (touched > ND_TOUCHED && (((uint32_t)__builtin_amdgcn_readfirstlane((int)sh_mark[v >> 5]) >> (v & 31u)) & 1u));
+    };
+    auto begin_jobs = [&]() { touched = 0u; lost = 0.f; was_j = ND_NONE; };
+    // the step is over: when it was not committed the jobs are as they were
+    auto end_jobs = [&](bool committed) {
         rs_wave_order();
-        for (uint32_t i = lane; i < touched; i += 64u) {
-            const uint32_t v = A.touched[i];
-            A.st.gi[v] = A.keep_gi[v]; A.st.ci[v] = A.keep_ci[v];
-            A.ds_g[v] = A.keep_ds[2 * v]; A.ds_c[v] = A.keep_ds[2 * v + 1];
+        if (touched > ND_TOUCHED) {
+            for (uint32_t i = ND_TOUCHED + lane; i < touched; i += 64u) {
+                const uint32_t v = A.touched[i];
+                atomicAnd(&sh_mark[v >> 5], ~(1u << (v & 31u)));
+                if (committed) continue;
+                A.st.gi[v] = K.b.keep_gi[i]; A.st.ci[v] = K.b.keep_ci[i];
+                A.ds_g[v] = K.b.keep_ds[2 * i]; A.ds_c[v] = K.b.keep_ds[2 * i + 1];
+            }
+            rs_wave_order();
+        }
+        if (committed) return;
+        if (was_j != ND_NONE) {
+            A.st.gi[was_j] = (int32_t)(was >> 16); A.st.ci[was_j] = was & 0xFFFFu;
+            A.ds_g[was_j] = was_g; A.ds_c[was_j] = was_c;
         }
         undone += touched ? 1u : 0u;
     };
-    // job v's entries of the nodes' tables, in ascending order of the nodes (DOWN: descending), until what(first entry of a
-    // chunk of 64, the lane's entry, the lanes that have one of v's) says no.  1,024 entries are looked through at a time,
-    // four loads of a lane in flight.
+    // job v's entries of the nodes' tables, in ascending order of the nodes (DOWN: descending), until what(index of the lane's
+    // entry, the entry, the lanes that have one of v's) says no.  1,024 entries are looked through at a time, four loads of
+    // a lane in flight; 256 of them are handed on together where a lane's four are one node's, of which v has one at most.
     const uint4 *const res4 = reinterpret_cast<const uint4 *>(A.res);
     const uint32_t n4 = (gpus + 3u) / 4u;
     auto for_parts = [&](uint32_t v, auto down, auto what) {
@@ -714,16 +767,28 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
             while (with) {
                 const uint32_t u = DOWN ? 31u - (uint32_t)__clz((int)with) : (uint32_t)__ffs((int)with) - 1u;
                 with &= ~(1u << u);
+                if ((gpn & 3u) == 0u) {
+                    const uint32_t at4 = blk * 256u + u * 64u + lane;
+                    const uint4 q = at4 < n4 ? res4[at4] : uint4{EMPTY, EMPTY, EMPTY, EMPTY};
+                    uint32_t word = q.x, c = 0u;
+                    if ((q.y >> 16) == v) { word = q.y; c = 1u; }
+                    if ((q.z >> 16) == v) { word = q.z; c = 2u; }
+                    if ((q.w >> 16) == v) { word = q.w; c = 3u; }
+                    if (!what(4u * at4 + c, word, __ballot((word >> 16) == v))) return;
+                    continue;
+                }
 #pragma unroll 1
                 for (uint32_t y = 0; y < 4; ++y) {           // ... and where
                     const uint32_t b = 4u * (blk * 256u + u * 64u) + 64u * (DOWN ? 3u - y : y);
                     const uint32_t word = b + lane < gpus ? A.res[b + lane] : EMPTY;
                     const unsigned long long m = __ballot((word >> 16) == v);
-                    if (m && !what(b, word, m)) return;
+                    if (m && !what(b + lane, word, m)) return;
                 }
             }
         }
     };
+    auto one = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); };
+    auto one_i = [](int32_t x) { return __builtin_amdgcn_readfirstlane(x); };
     // a / b from 1 / b for a < 2^21: (a + 1/2) / b is further from a whole number than the product's error
     auto over = [&](uint32_t a, float rcp) { return (uint32_t)(((float)a + 0.5f) * rcp); };
     const float rcp_gpn = 1.f / (float)gpn;
@@ -733,7 +798,7 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
         dirty = false;
         const RsStep st = nd_cached_step(A, j, 0);
         if (!st.any) return DID_NOTHING;
-        epoch += 1u; touched = 0u; lost = 0.f;
+        begin_jobs();
         const int32_t fl = rs_fl_s(A, j), gi_j = A.st.gi[j];
         const uint32_t ci_j = A.st.ci[j];
         const bool below_min = fl >= 0 && gi_j < fl;
@@ -744,10 +809,10 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
         if (gi_j >= 0 && st.lvl != ci_j) {                   // its parts go to the step's level: their CPUs must be free
             const uint32_t more = per_gpu - sh_cpl[ci_j];
             dirty = true;
-            for_parts(j, std::false_type{}, [&](uint32_t b, uint32_t word, unsigned long long m) {
+            for_parts(j, std::false_type{}, [&](uint32_t i, uint32_t word, unsigned long long m) {
                 bool short_of = false;
                 if ((m >> lane) & 1ull) {
-                    const uint32_t n = over(b + lane, rcp_gpn), have = A.free_c[n];
+                    const uint32_t n = over(i, rcp_gpn), have = A.free_c[n];
                     const unsigned long long need = (unsigned long long)more * (word & 0xFFFFu);
                     if (have < need) short_of = true;
                     else A.free_c[n] = have - (uint32_t)need;
@@ -793,7 +858,19 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
             if (lane <= last && offer) {
                 const uint32_t k = offer < lack - before ? offer : lack - before;
                 A.free_g[n] = fg - k; A.free_c[n] = fc - k * per_gpu;
-                const int at = gi_j >= 0 ? nd_find(A, n, j) : -1;        // (a newcomer is on no node that the walk comes to)
+                int at = -1;                             // (a newcomer is on no node that the walk comes to)
+                if (gi_j >= 0) {
+                    if ((gpn & 7u) == 0u) {
+                        for (uint32_t i = 0; i < gpn; i += 8u) {
+                            const uint4 q = res4[(base_n + i) / 4u], r = res4[(base_n + i) / 4u + 1u];
+                            const uint32_t w[8] = {q.x, q.y, q.z, q.w, r.x, r.y, r.z, r.w};
+#pragma unroll
+                            for (uint32_t x = 0; x < 8; ++x) at = (w[x] >> 16) == j ? (int)(i + x) : at;
+                        }
+                    } else {
+                        at = nd_find(A, n, j);
+                    }
+                }
                 if (at >= 0) A.res[base_n + (uint32_t)at] += k;
                 else if (c < gpn) { A.res[base_n + c] = (j << 16) | k; A.cnt[n] = c + 1u; }
             }
@@ -819,20 +896,37 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
                     who = wave_min_u32_rows(key == least ? rv : ND_NONE);
                 }
                 if (least == ND_NONE || !(below_min || st.slope > rs_unordered(least))) break;
-                const int32_t gi0 = __builtin_amdgcn_readfirstlane(A.st.gi[who]);
-                const uint32_t ci0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)A.st.ci[who]);
-                const uint32_t so = (uint32_t)__builtin_amdgcn_readfirstlane((int)A.seg_off[who]);
-                const uint32_t ns = (uint32_t)__builtin_amdgcn_readfirstlane((int)A.seg_off[who + 1]) - so;
-                const uint32_t stamp = A.stamp[who];
-                const RsShrunk sk = rs_shrink_wave(A, who, so, ns, 0, gi0, ci0, lane);
+                // what it gives: kept, unless this step has changed it already
+                const bool again = remembered(who);
+                int32_t gi0, gi1;
+                uint32_t ci0, dg;
+                float loss, ds_g1, ds_c1;
+                if (!again) {
+                    if constexpr (LJ) {
+                        const uint4 w = A.give[who];
+                        ds_c1 = A.give_c[who];
+                        gi0 = one_i(A.st.gi[who]); ci0 = one(A.st.ci[who]);
+                        dg = one(w.x); loss = __uint_as_float(one(w.y)); gi1 = one_i((int32_t)w.z); ds_g1 = __uint_as_float(w.w);
+                    } else {
+                        const uint4 *const from = reinterpret_cast<const uint4 *>(A.gives + who);
+                        const uint4 w = from[0], x = from[1];
+                        const uint32_t gis = one(w.z);
+                        dg = one(w.x); loss = __uint_as_float(one(w.y)); gi0 = (int32_t)(gis >> 16); gi1 = (int32_t)(int16_t)(gis & 0xFFFFu);
+                        ds_g1 = __uint_as_float(w.w); ds_c1 = __uint_as_float(x.x); ci0 = one(x.z) & 0xFFu;
+                    }
+                    remember(who, gi0, ci0);
+                } else {
+                    gi0 = one_i(A.st.gi[who]); ci0 = one(A.st.ci[who]);
+                    const uint32_t so = one(A.seg_off[who]), ns = one(A.seg_off[who + 1]) - so;
+                    const RsShrunk sk = rs_shrink_wave(A, who, so, ns, 0, gi0, ci0, lane);
+                    dg = one((uint32_t)sk.gv.dg); loss = sk.gv.loss; gi1 = sk.gi; ds_g1 = sk.ds_g; ds_c1 = sk.ds_c;
+                }
                 const uint32_t slot = (uint32_t)__ffsll((long long)__ballot(lane < cf && rv == who)) - 1u;
                 const uint32_t here_has = wave_lane_u32(word, slot) & 0xFFFFu, per_v = sh_cpl[ci0];
-                const uint32_t dg = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)sk.gv.dg);
                 const uint32_t here = dg < here_has ? dg : here_has;
-                remember(who, gi0, ci0, stamp);
                 dirty = true;
                 shrinks += 1u;
-                lost = lost + sk.gv.loss;
+                lost = lost + loss;
                 // the node afterwards, from what the lanes hold: who gives `here` of its GPUs, j takes what it can
                 const uint32_t fg = free_g + here, fc = free_c + here * per_v;
                 const uint32_t by_cpu = over(fc, rcp), offer2 = fg < by_cpu ? fg : by_cpu;
@@ -852,18 +946,18 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
                 if (lane < gpn) A.res[base + lane] = mine;
                 if (lane == 0) {
                     A.free_g[f] = fg - t; A.free_c[f] = fc - t * per_gpu; A.cnt[f] = c2;
-                    A.st.gi[who] = sk.gi; A.st.ci[who] = sk.ci;
-                    A.ds_g[who] = sk.ds_g; A.ds_c[who] = sk.ds_c;
+                    A.st.gi[who] = gi1; A.st.ci[who] = gi1 < 0 ? 0u : ci0;
+                    A.ds_g[who] = ds_g1; A.ds_c[who] = ds_c1;
                 }
                 lack -= t;
                 uint32_t rest = dg - here;
                 rs_wave_order();
                 if (rest > 0)                                // the rest from its other parts, the last one first
-                    for_parts(who, std::true_type{}, [&](uint32_t b, uint32_t w, unsigned long long m) {
+                    for_parts(who, std::true_type{}, [&](uint32_t i, uint32_t w, unsigned long long m) {
                         const uint32_t k = (m >> lane) & 1ull ? w & 0xFFFFu : 0u, upto = nd_wave_scan(k), all = wave_lane_u32(upto, 63u);
                         const uint32_t behind = all - upto;  // what the entries after this one have
                         if (k && behind < rest) {
-                            const uint32_t give = k < rest - behind ? k : rest - behind, i = b + lane, n1 = over(i, rcp_gpn);
+                            const uint32_t give = k < rest - behind ? k : rest - behind, n1 = over(i, rcp_gpn);
                             A.free_g[n1] += give; A.free_c[n1] += give * per_v;
                             if (give < k) A.res[i] = w - give;
                             else {                           // (a job is on a node once: no other lane's node, no entry still to come)
@@ -881,25 +975,24 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
             }
         }
         if (lane == 0) A.ds_g[j] = own;
-        if (ok && lack == 0u && (below_min || st.gain > lost)) {
-            if (lane == 0) { A.st.gi[j] = st.tgt; A.st.ci[j] = st.lvl; }
-            moves += 1u;
-            return DID_GPUS;
-        }
-        put_jobs_back();
-        return DID_NOTHING;
+        const bool committed = ok && lack == 0u && (below_min || st.gain > lost);
+        end_jobs(committed);
+        if (!committed) return DID_NOTHING;
+        if (lane == 0) { A.st.gi[j] = st.tgt; A.st.ci[j] = st.lvl; }
+        moves += 1u;
+        return DID_GPUS;
     };
     // A CPU step of job j likewise, on every node the job is on (DID_CPUS)
     auto cpu_step = [&](uint32_t j) -> uint32_t {
         dirty = false;
         const RsStep st = nd_cached_step(A, j, 1);
         if (!st.any) return DID_NOTHING;
-        epoch += 1u; touched = 0u; lost = 0.f;
+        begin_jobs();
         const uint32_t more = sh_cpl[st.lvl] - sh_cpl[A.st.ci[j]];
         bool ok = true;
-        for_parts(j, std::false_type{}, [&](uint32_t b, uint32_t word, unsigned long long m) {
+        for_parts(j, std::false_type{}, [&](uint32_t i, uint32_t word, unsigned long long m) {
             while (m) {
-                const uint32_t s = (uint32_t)__ffsll((long long)m) - 1u, n = (b + s) / gpn;
+                const uint32_t s = (uint32_t)__ffsll((long long)m) - 1u, n = over(wave_lane_u32(i, s), rcp_gpn);
                 m &= m - 1ull;
                 const unsigned long long need = (unsigned long long)more * (wave_lane_u32(word, s) & 0xFFFFu);
                 for (;;) {
@@ -917,7 +1010,7 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
                     const uint32_t ci0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)A.st.ci[who]);
                     const uint32_t so = A.seg_off[who], ns = A.seg_off[who + 1] - so;
                     const RsShrunk sk = rs_shrink_wave(A, who, so, ns, 1, gi0, ci0, lane);
-                    remember(who, gi0, ci0, A.stamp[who]);
+                    if (!remembered(who)) remember(who, gi0, ci0);
                     dirty = true;
                     shrinks += 1u;
                     lost = lost + sk.gv.loss;
@@ -926,8 +1019,8 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
                         A.ds_g[who] = sk.ds_g; A.ds_c[who] = sk.ds_c;
                     }
                     const uint32_t less = sh_cpl[ci0] - sh_cpl[ci0 - 1u];
-                    for_parts(who, std::false_type{}, [&](uint32_t b2, uint32_t w2, unsigned long long m2) {     // it gives a level on all its nodes
-                        if ((m2 >> lane) & 1ull) A.free_c[over(b2 + lane, rcp_gpn)] += less * (w2 & 0xFFFFu);
+                    for_parts(who, std::false_type{}, [&](uint32_t i2, uint32_t w2, unsigned long long m2) {     // it gives a level on all its nodes
+                        if ((m2 >> lane) & 1ull) A.free_c[over(i2, rcp_gpn)] += less * (w2 & 0xFFFFu);
                         return true;
                     });
                     rs_wave_order();
@@ -935,13 +1028,12 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
             }
             return true;
         });
-        if (ok && st.gain > lost) {
-            if (lane == 0) A.st.ci[j] = st.lvl;
-            moves += 1u;
-            return DID_CPUS;
-        }
-        put_jobs_back();
-        return DID_NOTHING;
+        const bool committed = ok && st.gain > lost;
+        end_jobs(committed);
+        if (!committed) return DID_NOTHING;
+        if (lane == 0) A.st.ci[j] = st.lvl;
+        moves += 1u;
+        return DID_CPUS;
     };
 
     // ScheduleJob(j): the first wavefront steps, then all refresh what a committed step changed, or put the nodes back
@@ -995,18 +1087,21 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
             n_first += all;
         }
         __syncthreads();
-        for (uint32_t k = 0; k < n_first; ++k) schedule_job((uint32_t)__builtin_amdgcn_readfirstlane((int)A.tmp_off[k]));
     }
-    // ---- then the others, in an order that is fixed here (by slopes; the cached ones are current); jobs with nothing to
-    // do are passed over (k_reschedule_nodes says when that is)
-    for (uint32_t j = tid; j < J; j += THREADS)              // 0: not in the list
-        A.okey[j] = rs_part(A, j) && !A.first[j] ? ((unsigned long long)rs_ordered(A.ug[j]) << 32) | rs_ordered(A.uc[j]) : 0ull;
+    // ---- then the others, in an order that is fixed when these are through (by slopes; the cached ones are current); jobs
+    // with nothing to do are passed over (k_reschedule_nodes says when that is)
     unsigned long long last_key = ~0ull, my_key = 0ull;      // my_*: the first job of this thread's to serve
     uint32_t last_j = 0u, my_j = ND_NONE;
     bool fresh = true;                                       // a step was committed since the last look (or this is the first)
     RsMin low[2];                                            // the two lowest slopes per resource, and whose the lowest is
     low[0] = low[1] = RsMin{INF, INF, ND_NONE};
-    for (;;) {
+    bool others = false;
+    auto look = [&]() {                                      // leaves the job to serve in last_j
+        if (!others) {
+            for (uint32_t j = tid; j < J; j += THREADS)      // 0: not in the list
+                A.okey[j] = rs_part(A, j) && !A.first[j] ? ((unsigned long long)rs_ordered(A.ug[j]) << 32) | rs_ordered(A.uc[j]) : 0ull;
+            others = true;
+        }
         if (fresh) {
             // what the nodes can give at every CPU level, and all free CPUs: a wavefront per sum
             for (uint32_t l = wave; l <= A.X.grid.n_cpu; l += WAVES) {
@@ -1105,11 +1200,21 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
             last_key = ((unsigned long long)best_hi << 32) | best_lo;
             last_j = (uint32_t)__builtin_amdgcn_readlane((int)row_min_u32(k2 == last_key ? j2 : ND_NONE), 0);
         }
-        if (last_j == ND_NONE) break;
-        full += 1u;
+    };
+    for (uint32_t k_first = 0;;) {                           // one job per turn; ScheduleJob appears once in the code, which
+        uint32_t j;                                          // the instruction cache then holds
+        const bool is_first = k_first < n_first;
+        if (is_first) {
+            j = one(A.tmp_off[k_first++]);
+        } else {
+            look();
+            if (last_j == ND_NONE) break;
+            full += 1u;
+            j = last_j;
+        }
         const uint32_t before = moves;
-        schedule_job(last_j);
-        fresh = __syncthreads_or(wave == 0 && moves != before) != 0;
+        schedule_job(j);
+        fresh = __syncthreads_or(is_first || (wave == 0 && moves != before)) != 0;
     }
     nd_finish<THREADS>(A, reinterpret_cast<uint32_t *>(sh_ds), reinterpret_cast<uint32_t *>(sh_ds) + J, keep, A.touched, sh_mem, sh_scan);
     if (tid == 0 && A.stats) { A.stats[0] = moves; A.stats[1] = full; A.stats[2] = shrinks; A.stats[3] = undone; A.stats[4] = 0u; }
@@ -1620,6 +1725,8 @@ int32_t rk_launch_reschedule_nodes(rk_ctx *ctx, const float *ref_thr, const rk_p
     uint32_t *w_nodes, *w_jobs;
     float *f_jobs;
     unsigned long long *u64;
+    RsGives *gives;
+    if ((rc = rk_scratch(ctx, SL_ND_GIVES, n * sizeof(RsGives), (void **)&gives))) return rc;
     if ((rc = rk_scratch(ctx, SL_ND_NODES, (2 * nodes_words + 2 * N + (size_t)gpus) * sizeof(uint32_t), (void **)&w_nodes))) return rc;
     if ((rc = rk_scratch(ctx, SL_ND_U32, (14 * n + 1) * sizeof(uint32_t), (void **)&w_jobs))) return rc;
     if ((rc = rk_scratch(ctx, SL_ND_F32, 10 * n * sizeof(float), (void **)&f_jobs))) return rc;
@@ -1647,6 +1754,7 @@ int32_t rk_launch_reschedule_nodes(rk_ctx *ctx, const float *ref_thr, const rk_p
     A.ds_g = f_jobs; A.ds_c = f_jobs + n; A.ug = f_jobs + 2 * n; A.uc = f_jobs + 3 * n; A.sg = f_jobs + 4 * n;
     A.sc = f_jobs + 5 * n; A.keep_ds = f_jobs + 6 * n; A.gain_g = f_jobs + 8 * n; A.gain_c = f_jobs + 9 * n;
     A.udc_c = u64; A.okey = u64 + n;
+    A.gives = gives; A.give = nullptr; A.give_c = nullptr;
     A.assign = assign; A.place_off = place_off; A.entries = entries; A.total = total; A.stats = stats;
     // Where the nodes and their copy fit a CU's LDS beside the cached slopes (512 nodes of 8 GPUs and 10,000 jobs do), the
     // loop runs on them there.
@@ -1655,6 +1763,7 @@ int32_t rk_launch_reschedule_nodes(rk_ctx *ctx, const float *ref_thr, const rk_p
     if (!ctx->nodes_lds_raised) {
         const auto most = hipFuncAttributeMaxDynamicSharedMemorySize;
         RK_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(k_nodes_lds<ND_SMALL_THREADS, true>), most, (int)ND_LDS_MOST));
+        RK_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(k_nodes_lds<ND_FEW_THREADS, true>), most, (int)ND_LDS_MOST));
         RK_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(k_nodes_lds<ND_THREADS, false>), most, (int)ND_LDS_MOST));
         RK_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(k_reschedule_nodes), most, 2 * RK_MAX_JOBS_PER_ROUND * sizeof(float)));
         ctx->nodes_lds_raised = true;
@@ -1668,7 +1777,8 @@ int32_t rk_launch_reschedule_nodes(rk_ctx *ctx, const float *ref_thr, const rk_p
         k_nd_prepare<<<(J + 3) / 4, 256, 0, ctx->stream>>>(K);
         RK_CHECK_LAUNCH(ctx, "k_nd_prepare");
     }
-    if (jobs_too) k_nodes_lds<ND_SMALL_THREADS, true><<<1, ND_SMALL_THREADS, lds_lj, ctx->stream>>>(K);
+    if (jobs_too && J <= ND_FEW_THREADS) k_nodes_lds<ND_FEW_THREADS, true><<<1, ND_FEW_THREADS, lds_lj, ctx->stream>>>(K);
+    else if (jobs_too) k_nodes_lds<ND_SMALL_THREADS, true><<<1, ND_SMALL_THREADS, lds_lj, ctx->stream>>>(K);
     else if (in_lds) k_nodes_lds<ND_THREADS, false><<<1, ND_THREADS, lds_l, ctx->stream>>>(K);
     else k_reschedule_nodes<<<1, ND_THREADS, (size_t)2 * n * sizeof(float), ctx->stream>>>(K);           // at most 96 KiB
     RK_CHECK_LAUNCH(ctx, "k_nodes_lds");

@@ -231,6 +231,49 @@ def test_shapes_at_the_limits(gpu, orc):
         assert want is not None
 
 
+@pytest.mark.parametrize("J,take,each,gpn", [(140, 63, 1, 8), (140, 64, 1, 8), (140, 65, 1, 6), (300, 256, 1, 4), (200, 360, 2, 8),
+                                             (200, 360, 2, 10), (2500, 640, 1, 8), (2500, 1260, 2, 12)])
+def test_a_step_that_many_jobs_give_to(gpu, orc, J, take, each, gpn):
+    """One job below its floor takes `take` GPUs from jobs of equal slopes that hold `each`: as many changed jobs as a wavefront
+    has lanes and more, jobs that give twice in a step, with the jobs' values in LDS and not; then the turns of the
+    others, whose steps are taken back from the same lists."""
+    rng = np.random.default_rng(98500 + take)
+    bounds = workloads.Bounds(g_max=take, tp_max=1)
+    ints = np.tile(np.array([[1, 4 if take % 4 else 8, 1]], np.uint32), (J, 1))
+    ints[0, 1] = take
+    tb = orc.enumerate_plans(ints, bounds)
+    grid = workloads.Grid(np.array([1, 2], np.uint32), 1, np.array([1.0], np.float32), 0)
+    vals = []
+    for j in range(J):
+        g = np.asarray(tb.seg_g[tb.seg_off[j]:tb.seg_off[j + 1]], np.float64)
+        v = np.where(g == take, 8.0, 0.25) if j == 0 else np.minimum(g, 4) * (1.0 if j % 7 else 1.5)
+        vals += [v, v * (1.0 if j % 3 else 1.125)]
+    bt = np.concatenate(vals).astype(np.float32)
+    bp = rng.integers(0, 1000, bt.size).astype(np.uint32)
+    ct, _, _ = orc.curves(tb, grid, bt, bp)
+    n_nodes = (each * (J - 1) + gpn - 1) // gpn
+    nodes = (n_nodes, gpn, 3 * gpn, 1e6)
+    cur_seg, cur_c = np.full(J, each - 1, np.int32), np.zeros(J, np.uint32)      # their amounts are 1, 2, 4 ...
+    cur_seg[0] = -1
+    free_g, free_c, off, ent = [gpn] * n_nodes, [3 * gpn] * n_nodes, [0, 0], []
+    for j in range(1, J):
+        ent += [(n, k, k, 0.0) for n, k in sorted(first_fit(free_g, free_c, each, 1).items())]
+        off.append(len(ent))
+    prev = (np.array(off, np.uint32), np.array(ent, orc.PLACE_DTYPE))
+    floor_seg, floor_c = np.full(J, -1, np.int32), np.zeros(J, np.uint32)
+    floor_seg[0] = int(tb.seg_off[1]) - 1
+    coef = np.tile(workloads.tiny().coef[:1], (J, 1))
+    coef[:, 16] = 1.0
+    wl = workloads.Workload("many", coef, ints, bounds, grid, workloads.Env(), workloads.Cluster(n_nodes * gpn, 3 * n_nodes * gpn, 1e9))
+    run = gpu(wl)
+    run.enumerate()
+    want = orc.reschedule_nodes(coef[:, 16], tb, grid, *nodes, bt, bp, ct, cur_seg, cur_c, prev, floor_seg, floor_c)
+    got = on_gpu(run, bt, bp, ct, nodes, cur_seg, cur_c, prev, floor_seg, floor_c, None)
+    run.close()
+    same(got, want)
+    assert want[0]["g"][0] == take
+
+
 @pytest.mark.parametrize("J,gpn", [(1400, 8), (4000, 8), (1400, 128)])
 def test_the_total_is_added_in_one_order(gpu, orc, J, gpn):
     """The total is a float64 sum in a fixed order, whichever kernel runs the loop: 1,024 partial sums of every 1,024th
