@@ -169,7 +169,10 @@ struct TileSum { unsigned long long t, s; uint32_t mt, ms, err, pad; };
 
 __global__ __launch_bounds__(LEAD_THREADS) void k_spread_counts(const uint32_t *__restrict__ leader, uint32_t n_jobs,
                                                                 uint32_t *__restrict__ cnt_t, uint32_t *__restrict__ cnt_s,
-                                                                TileSum *__restrict__ sums) {
+                                                                TileSum *__restrict__ sums, uint32_t *__restrict__ tab, uint32_t tab_slots) {
+    // the leaders' table has been read: zero for the next call (a launch of its own before it took 5 us)
+    for (uint32_t i = blockIdx.x * LEAD_THREADS + threadIdx.x; i < tab_slots / 4u; i += gridDim.x * LEAD_THREADS)
+        reinterpret_cast<uint4 *>(tab)[i] = uint4{0u, 0u, 0u, 0u};
     __shared__ uint32_t w_t[LEAD_THREADS / 64], w_s[LEAD_THREADS / 64], w_mt[LEAD_THREADS / 64], w_ms[LEAD_THREADS / 64], w_e[LEAD_THREADS / 64];
     const uint32_t j = blockIdx.x * LEAD_THREADS + threadIdx.x;
     uint32_t ct = 0, cs = 0;
@@ -652,9 +655,11 @@ extern "C" int32_t rk_enumerate_plans(rk_ctx *ctx, const rk_jobs *jobs, const rk
     }
     ctx->enum_clear = false;
     if (share) {
+        const size_t had = ctx->scratch_bytes[SL_ENUM_TAB];
         if ((rc = rk_scratch(ctx, SL_ENUM_TAB, (size_t)tab_slots * 4, (void **)&tab))) return rc;
         if ((rc = rk_scratch(ctx, SL_ENUM_LEADER, ((size_t)J + 1) * 4, (void **)&leader))) return rc;
         if ((rc = rk_scratch(ctx, SL_ENUM_SUMS, (size_t)job_blocks * sizeof(TileSum), (void **)&sums))) return rc;
+        if (ctx->scratch_bytes[SL_ENUM_TAB] != had) ctx->enum_tab_clear = 0;         // new memory
     }
     // one slot per job for the parked words: as wide as the widest job seen so far, or a first guess
     if (ctx->park_stride == 0) ctx->park_stride = 512;
@@ -686,8 +691,16 @@ extern "C" int32_t rk_enumerate_plans(rk_ctx *ctx, const rk_jobs *jobs, const rk
 
     const size_t gmap_bytes = (size_t)((bounds->g_max >> 5) + 1u) * 2 * sizeof(uint32_t);   // bitmap + word prefixes
     const bool self_scan = J > 0 && J <= ENUM_SELF_SCAN;
+    size_t tab_clear = 0;
     if (share) {
-        k_zero_words<<<(uint32_t)((tab_slots + 255) / 256), 256, 0, ctx->stream>>>(tab, (uint32_t)tab_slots);
+        // the table is zero where earlier calls came to their end; otherwise it is cleared first
+        const size_t clear = ctx->enum_tab_clear;
+        ctx->enum_tab_clear = 0;
+        if (clear < tab_slots) {
+            k_zero_words<<<(uint32_t)((tab_slots + 255) / 256), 256, 0, ctx->stream>>>(tab, (uint32_t)tab_slots);
+            RK_CHECK_LAUNCH(ctx, "k_zero_words");
+        }
+        tab_clear = clear < tab_slots ? (size_t)tab_slots : clear;
         k_enum_leaders<<<job_blocks, LEAD_THREADS, 0, ctx->stream>>>(jobs->layers, jobs->gbatch, jobs->mbatch, J, tab,
                                                                     (uint32_t)(tab_slots - 1), leader);
         RK_CHECK_LAUNCH(ctx, "k_enum_leaders");
@@ -699,7 +712,7 @@ extern "C" int32_t rk_enumerate_plans(rk_ctx *ctx, const rk_jobs *jobs, const rk
         RK_CHECK_LAUNCH(ctx, "k_enumerate<count>");
     }
     if (share) {
-        k_spread_counts<<<job_blocks, LEAD_THREADS, 0, ctx->stream>>>(leader, J, cnt_t, cnt_s, sums);
+        k_spread_counts<<<job_blocks, LEAD_THREADS, 0, ctx->stream>>>(leader, J, cnt_t, cnt_s, sums, tab, (uint32_t)tab_slots);
         RK_CHECK_LAUNCH(ctx, "k_spread_counts");
     }
     if (tiles) k_scan_tiles<<<job_blocks, LEAD_THREADS, 0, ctx->stream>>>(cnt_t, cnt_s, J, sums, S);
@@ -718,6 +731,7 @@ extern "C" int32_t rk_enumerate_plans(rk_ctx *ctx, const rk_jobs *jobs, const rk
     }
     RK_HIP(ctx, hipEventSynchronize(ctx->counts_ev));
     ctx->enum_clear = true;                                   // the kernels before the event have run
+    if (share) ctx->enum_tab_clear = tab_clear;
 
     if (h[TOT_ERR] & ERR_TOO_MANY_TRIPLES) return rk_fail(ctx, RK_ERR_UNSUPPORTED, "a job has more than %u triples", MAX_T);
     if (h[TOT_ERR] & ERR_TOO_MANY_DIVISORS) return rk_fail(ctx, RK_ERR_UNSUPPORTED, "a job has more than %u candidate d or p sizes", MAX_DIV);

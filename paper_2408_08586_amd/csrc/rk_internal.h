@@ -22,6 +22,7 @@ struct rk_ctx {
     size_t h_stage_words;
     uint32_t park_stride;                   // enumeration: words per job between its two passes
     bool enum_clear;                        // enumeration: the device's counter of finished searches is known to be zero
+    size_t enum_tab_clear;                  // ... and so many words of the leaders' table
     hipEvent_t counts_ev;                   // enumeration: the counts have reached the host (made on demand)
     hipStream_t sim_stream;                 // simulation: its own stream (a tick is captured as a graph), made on demand
     hipEvent_t sim_ev[4];                   // ... ordered after and before the context's stream with the first two; its batches of ticks

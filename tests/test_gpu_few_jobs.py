@@ -77,3 +77,28 @@ def test_ticks_in_one_launch(orc, n_jobs, n_ticks, scarce):
                                   delta, 60.0, n_ticks, gate=0.9)
     same(run_on_gpu(run, r, arrival, work, delta, 60.0, n_ticks, 0.9), want)
     run.close()
+
+
+def test_equal_jobs_are_found_again_in_later_calls(orc):
+    """The table of equal jobs is left empty by every call for the next one: calls of growing and shrinking size on one
+    context, each with kinds of jobs of its own, and one that ends in an error between them."""
+    import torch
+    import paper_2408_08586_amd as rk
+    ctx = rk.rk_create(0)
+    bounds = workloads.Bounds(g_max=64)
+    for i, n_jobs in enumerate((2048, 5000, 2048, 9000, 0, 3000)):
+        rng = np.random.default_rng(i)
+        kinds = np.stack([rng.integers(1, 97, 40), rng.integers(1, 200, 40), np.ones(40)], 1).astype(np.uint32)
+        ints = kinds[rng.integers(0, 40, max(n_jobs, 2500))]
+        jobs = rk.Jobs(np.tile(workloads.tiny().coef[:1], (len(ints), 1)), ints, "cuda:0")
+        if n_jobs == 0:                                         # a table without room
+            small = rk.PlanTable(len(ints), 8, 8, "cuda:0")
+            with pytest.raises(rk.RkError):
+                rk.rk_enumerate_plans(ctx, jobs, rk.make_bounds(bounds), small.c)
+            continue
+        t = rk.enumerate_to_table(ctx, jobs, rk.make_bounds(bounds), "cuda:0")
+        ot = orc.enumerate_plans(ints, bounds)
+        torch.cuda.synchronize()
+        assert np.array_equal(rk.u32(t.seg_off), ot.seg_off) and np.array_equal(rk.u32(t.seg_g)[:t.n_segs], ot.seg_g)
+        assert np.array_equal(rk.u32(t.triple_off), ot.triple_off)
+    rk.rk_destroy(ctx)
