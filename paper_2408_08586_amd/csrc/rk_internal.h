@@ -43,7 +43,7 @@ enum {
     SL_HULL_KEY, SL_HULL_RAW, SL_HULL_DG, SL_HULL_DC, SL_HULL_TGT,   // walk steps of the greedy allocation
     SL_ST_GI, SL_ST_G, SL_ST_CI, SL_ST_FREEC, SL_ST_PARTIAL,         // its per-job and per-round state
     SL_ST_STEP_SLOPE, SL_ST_STEP_TGT, SL_ST_STEP_DG, SL_ST_FREEG,
-    SL_HIST_G, SL_HIST_C,                                             // cost histograms over the step keys
+    SL_HIST_G, SL_HIST_C, SL_HIST_CUT,                                // cost histograms over the step keys; where they were cut
     SL_PARK,                                             // enumeration: sorted keys between its two passes
     SL_FL_GI, SL_FL_CI, SL_FL_WAITS, SL_FL_CAP0,         // service-level floors of the allocation
     SL_MIN_SEG, SL_MIN_C, SL_MIN_M,                      // minimum demands of a round

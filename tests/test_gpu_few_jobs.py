@@ -79,6 +79,34 @@ def test_ticks_in_one_launch(orc, n_jobs, n_ticks, scarce):
     run.close()
 
 
+@pytest.mark.parametrize("n_jobs,spread", [(2049, 0.0), (2049, 3.0), (3000, 1.0), (12288, 0.3)])
+def test_thresholds_of_many_jobs(orc, n_jobs, spread):
+    """Rounds whose histograms are in memory (more than 2,048 jobs): slopes in few bins (spread 0: a handful of values) and
+    over many groups of them, capacities that cut in the first group, in the middle, at the last step, and not at all."""
+    import paper_2408_08586_amd as rk
+    from gpu_harness import DeviceRun
+    rng = np.random.default_rng(n_jobs)
+    base = workloads.tiny()
+    coef = np.tile(base.coef[:1], (n_jobs, 1))
+    coef[:, 16] = (2.0 ** np.round(rng.normal(0.0, 4.0 * spread, n_jobs))).astype(np.float32)
+    grid = workloads.Grid(np.array([1, 2, 4], np.uint32), 1, np.array([64.0], np.float32), 0)
+    wl = workloads.Workload("many", coef, np.tile(np.array([[12, 32, 1]], np.uint32), (n_jobs, 1)), workloads.Bounds(g_max=32), grid,
+                            workloads.Env(), workloads.Cluster(8, 8, 64.0))
+    ot = orc.enumerate_plans(wl.ints, wl.bounds)
+    bt, bp, ct = drawn_curves(orc, wl, ot, rng)
+    run = DeviceRun(wl)
+    run.enumerate()
+    d_bt, d_bp, d_ct = run.dev_f32(bt), run.dev_u32(bp), run.dev_f32(ct)
+    for G, C in ((0, 0), (1, 1), (n_jobs // 3, 10 ** 7), (2 * n_jobs, 3 * n_jobs), (20 * n_jobs, 10 ** 7), (64 * n_jobs, 64 * n_jobs),
+                 (2 ** 31, 2 ** 32 - 1)):
+        cl = workloads.Cluster(G, C, 1e9)
+        e_assign, e_total, _ = orc.greedy(wl.coef[:, 16], ot, wl.grid, cl, bt, bp, ct)
+        assign, total = run.allocate(d_bt, d_bp, d_ct, cluster=rk.make_cluster(cl))
+        assert np.array_equal(assign, e_assign), (G, C)
+        assert total == pytest.approx(e_total, rel=1e-6, abs=1e-12)
+    run.close()
+
+
 def test_equal_jobs_are_found_again_in_later_calls(orc):
     """The table of equal jobs is left empty by every call for the next one: calls of growing and shrinking size on one
     context, each with kinds of jobs of its own, and one that ends in an error between them."""
