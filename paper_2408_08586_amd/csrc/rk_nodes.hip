@@ -22,6 +22,7 @@
 #include "rk_internal.h"
 #include "rk_model.h"
 #include "rk_loop.h"
+#include "rk_sim.h"
 
 namespace {
 
@@ -329,9 +330,11 @@ __device__ __forceinline__ void nd_refuse(const NdArgs &A) {
 }
 
 // Memory, then the records, from what the jobs hold and who is on the nodes.  np, off [n_jobs], parts [GPUs of all
-// nodes], wish [n_jobs] and mem [n_nodes] are working memory, in LDS or not.  All threads call it.
+// nodes], wish [n_jobs], list [jobs that hold something; may be where the residents are] and mem [n_nodes] are working
+// memory, in LDS or not.  All threads call it.
 template <int THREADS>
-__device__ __forceinline__ void nd_finish(const NdArgs &A, uint32_t *np, uint32_t *off, uint32_t *parts, uint32_t *wish, float *mem, uint32_t *sh_scan) {
+__device__ __forceinline__ void nd_finish(const NdArgs &A, uint32_t *np, uint32_t *off, uint32_t *parts, uint32_t *wish, uint32_t *list, float *mem,
+                                          uint32_t *sh_scan) {
     constexpr uint32_t WAVES = THREADS / 64;
     __shared__ uint32_t sh_fit, sh_wide, sh_list;
     __shared__ double sh_sum[ND_WAVES];
@@ -373,8 +376,7 @@ __device__ __forceinline__ void nd_finish(const NdArgs &A, uint32_t *np, uint32_
         }
     }
     __syncthreads();
-    // the jobs that hold something, listed (in no order) where the residents were; the others' records
-    uint32_t *const list = A.res;
+    // the jobs that hold something, listed in no order; the others' records
     for (uint32_t j0 = 0; j0 < J; j0 += THREADS) {
         const uint32_t j = j0 + tid;
         const bool holds = j < J && np[j] != 0u;
@@ -568,8 +570,11 @@ __device__ __forceinline__ uint32_t nd_wave_sum(uint32_t v) { return (uint32_t)_
 // else a job has.
 constexpr uint32_t ND_LDS_JOB_WORDS = 22;
 constexpr uint32_t ND_TOUCHED = 64;                        // jobs changed by a step that are remembered in registers (the others in memory)
-static inline size_t nd_lds_words(size_t J, size_t N, size_t nodes_words, bool lj) {
-    return 2 * nodes_words + 2 * (J + 1) + N + (J + 31) / 32 + (lj ? ND_LDS_JOB_WORDS * J + 1 : 0);
+constexpr uint32_t ND_LDS_SIM_WORDS = 4;                   // ... more per job for ticks of a simulation
+// whole 16-byte pieces: copied and searched four words at a time
+static inline size_t nd_nodes_words(size_t N, size_t gpus) { return (((3 * N + 3) & ~(size_t)3) + gpus + 3) & ~(size_t)3; }
+static inline size_t nd_lds_words(size_t J, size_t N, size_t nodes_words, bool lj, bool sim = false) {
+    return 2 * nodes_words + 2 * (J + 1) + N + (J + 31) / 32 + (lj ? ND_LDS_JOB_WORDS * J + 1 : 0) + (sim ? ND_LDS_SIM_WORDS * J : 0);
 }
 
 // The loop with the nodes in LDS.  It is a chain of small decisions, so what bounds it is the latency of one after
@@ -581,8 +586,14 @@ static inline size_t nd_lds_words(size_t J, size_t N, size_t nodes_words, bool l
 // What a job gives first in a step was found when its state last changed (nd_keep_give), what a step changed is
 // remembered a job per lane, and a shrunk job's other parts are looked for 256 entries at a time: 10,000 jobs on 512 nodes,
 // the round from the descriptors: 1,174 -> 1,058 and 2,980 -> 2,620 us on two drawn states.
-template <int THREADS, bool LJ>
-__global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
+// SIM (with LJ): a round is a tick of a simulation.  The ticks after it that need no round are closed, then the jobs'
+// values are brought up to date for the next round, up to S.rounds of them per launch: nodes, jobs and cached steps stay
+// where they are, and only jobs that came, went or thawed have theirs found again.  As launches of their own, replayed as
+// a graph, the preparation, the round and the tick took 5, 102 and 9 us with 9 us between them, of which loading the
+// nodes and jobs was 5; 406 jobs, 720 ticks: 57.4 -> 46.7 ms, 60 jobs, 100 ticks: 2.59 -> 1.56 ms.
+template <int THREADS, bool LJ, bool SIM, class KernArgs>
+__device__ __forceinline__ void nodes_lds(const KernArgs &K) {
+    static_assert(LJ || !SIM, "ticks of a simulation have the jobs in LDS");
     extern __shared__ uint4 sh_raw[];
     constexpr uint32_t WAVES = THREADS / 64;
     __shared__ uint32_t sh_scan[WAVES], sh_take[RK_MAX_CPU_LEVELS], sh_free_c, sh_cpl[RK_MAX_CPU_LEVELS], sh_list;
@@ -595,6 +606,11 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
     const uint32_t J = A.n_jobs, N = A.n_nodes, gpn = A.gpn, gpus = N * gpn;
     const uint32_t EMPTY = (J << 16) | 0xFFFFu;              // no resident: a job that has no index, whose slopes are infinite
     const float INF = __int_as_float(0x7F800000);
+    uint32_t tick = 0;
+    if constexpr (SIM) {
+        tick = *K.S.tick;
+        if (tick >= K.S.n_ticks) return;                     // (the simulation is over)
+    }
 
     // ---- everything into LDS
     uint32_t *const nodes = reinterpret_cast<uint32_t *>(sh_raw);
@@ -635,6 +651,11 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
         }
         if (tid == 0) so[J] = A.X.tb.seg_off[J];
         A.seg_off = so;
+    }
+    uint32_t *fin_np = reinterpret_cast<uint32_t *>(sh_ds), *fin_off = fin_np + J, *fin_list = A.res, *old_state = nullptr;
+    if constexpr (SIM) {                                     // (what the next round needs again is not working memory of this one's end)
+        fin_np = take(J); fin_off = take(J); fin_list = take(J); old_state = take(J);
+        for (uint32_t j = tid; j < J; j += THREADS) old_state[j] = A.state[j];
     }
     uint32_t bad = 0, any_first = 0;
     for (uint32_t j = tid; j < J; j += THREADS) {
@@ -1075,6 +1096,7 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
         }
     };
 
+    auto round = [&]() {
     // ---- privileged jobs (below their floor) come first, in job order: their list (tmp_off serves as the list)
     uint32_t n_first = 0;
     if (with_first) {
@@ -1216,9 +1238,69 @@ __global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) {
         schedule_job(j);
         fresh = __syncthreads_or(is_first || (wave == 0 && moves != before)) != 0;
     }
-    nd_finish<THREADS>(A, reinterpret_cast<uint32_t *>(sh_ds), reinterpret_cast<uint32_t *>(sh_ds) + J, keep, A.touched, sh_mem, sh_scan);
-    if (tid == 0 && A.stats) { A.stats[0] = moves; A.stats[1] = full; A.stats[2] = shrinks; A.stats[3] = undone; A.stats[4] = 0u; }
+    };
+    if constexpr (!SIM) {
+        round();
+        nd_finish<THREADS>(A, fin_np, fin_off, keep, A.touched, fin_list, sh_mem, sh_scan);
+        if (tid == 0 && A.stats) { A.stats[0] = moves; A.stats[1] = full; A.stats[2] = shrinks; A.stats[3] = undone; A.stats[4] = 0u; }
+    } else {
+        const SimArgs &S = K.S;
+        for (uint32_t done = 0;;) {
+            round();
+            nd_finish<THREADS>(A, fin_np, fin_off, keep, A.touched, fin_list, sh_mem, sh_scan);
+            __syncthreads();
+            const bool moved = sim_placed<THREADS>(S);
+            const bool more = sim_ticks<THREADS>(S, tick, false, moved);
+            if (tid == 0) sh_list = 0u;
+            __syncthreads();
+            if (!more || ++done == K.rounds) break;
+            // who holds something else than the round left them with, or takes part in another way
+            for (uint32_t j = tid; j < J; j += THREADS) {
+                const uint32_t state = A.state[j], lvl = A.cur_c[j], ci = A.st.ci[j];
+                const int32_t seg = A.cur_seg[j], gi = A.st.gi[j];
+                const bool holds = rs_holds(A, j) && seg >= 0 && (uint32_t)seg < A.seg_off[j + 1] - A.seg_off[j] && lvl < A.X.grid.n_cpu;
+                if (state != old_state[j] || (holds ? seg != gi || lvl != ci : gi >= 0)) fin_list[atomicAdd(&sh_list, 1u)] = j;
+                old_state[j] = state;
+                A.st.gi[j] = holds ? seg : -1;
+                if (holds) A.st.ci[j] = lvl;                 // (a job that leaves keeps its level until its parts are free)
+            }
+            __syncthreads();
+            for (uint32_t n = tid; n < N; n += THREADS) {    // the parts of those that left
+                uint32_t c = A.cnt[n], fg = 0, fc = 0;
+                for (uint32_t i = 0; i < c;) {
+                    const uint32_t word = A.res[n * gpn + i], v = word >> 16;
+                    if (A.st.gi[v] >= 0) { ++i; continue; }
+                    fg += word & 0xFFFFu; fc += (word & 0xFFFFu) * sh_cpl[A.st.ci[v]];
+                    c -= 1u;
+                    A.res[n * gpn + i] = A.res[n * gpn + c];
+                    A.res[n * gpn + c] = EMPTY;
+                }
+                if (fg) { A.cnt[n] = c; A.free_g[n] += fg; A.free_c[n] += fc; }
+            }
+            __syncthreads();
+            const uint32_t n_changed = sh_list;
+            for (uint32_t i = tid; i < n_changed; i += THREADS) if (A.st.gi[fin_list[i]] < 0) A.st.ci[fin_list[i]] = 0u;
+            copy_nodes(keep, nodes);
+            __syncthreads();
+            for (uint32_t i = wave; i < 2u * n_changed; i += WAVES) {
+                const uint32_t v = one(fin_list[i >> 1]);
+                nd_refresh_wave(A, v, one_i(A.st.gi[v]), one(A.st.ci[v]), lane, (i & 1u) == 0u, (i & 1u) != 0u);
+            }
+            __syncthreads();
+        }
+        if (tid == 0) {
+            *S.tick = tick;
+            __hip_atomic_store(S.h_tick, tick, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+    }
 }
+
+template <int THREADS, bool LJ>
+__global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) { nodes_lds<THREADS, LJ, false>(K); }
+
+struct NdSimArgs : NdKernArgs { SimArgs S; uint32_t rounds; };     // rounds of a launch, at most
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void k_sim_nodes(NdSimArgs K) { nodes_lds<THREADS, true, true>(K); }
 
 __global__ __launch_bounds__(ND_THREADS) void k_reschedule_nodes(NdKernArgs K) {
     // what every job loses per GPU / CPU it gives, [2][n_jobs]: read at every look at a node's residents and at every
@@ -1670,7 +1752,7 @@ __global__ __launch_bounds__(ND_THREADS) void k_reschedule_nodes(NdKernArgs K) {
     __syncthreads();
 
     // ---- memory, then the records
-    nd_finish<ND_THREADS>(A, A.np, A.tmp_off, A.tmp_parts, A.touched, sh_mem, sh_scan);
+    nd_finish<ND_THREADS>(A, A.np, A.tmp_off, A.tmp_parts, A.touched, A.res, sh_mem, sh_scan);
     if (tid == 0 && A.stats) { A.stats[0] = sh_moves; A.stats[1] = sh_full; A.stats[2] = sh_shrinks; A.stats[3] = sh_undone; A.stats[4] = 0u; }
 }
 
@@ -1711,17 +1793,17 @@ extern "C" int32_t rk_reschedule_nodes(rk_ctx *ctx, const float *ref_thr, const 
                                       prev_entries, n_prev_entries, assign, place_off, entries, total, stats);
 }
 
-int32_t rk_launch_reschedule_nodes(rk_ctx *ctx, const float *ref_thr, const rk_plan_table *table,
-                                   const rk_alloc_grid *grid, const rk_nodes *nodes, const float *best_thr,
-                                   const uint32_t *best_plan, const float *curve_thr, const rk_job_state *jobs_state,
-                                   const uint32_t *prev_off, const rk_place_entry *prev_entries, uint64_t n_prev_entries,
-                                   rk_assign *assign, uint32_t *place_off, rk_place_entry *entries, float *total,
-                                   uint32_t *stats) {
+// The kernels' argument, with the working memory it points to; *words: of the node tables.
+static int32_t nd_kernel_args(rk_ctx *ctx, const float *ref_thr, const rk_plan_table *table, const rk_alloc_grid *grid,
+                              const rk_nodes *nodes, const float *best_thr, const uint32_t *best_plan, const float *curve_thr,
+                              const rk_job_state *jobs_state, const uint32_t *prev_off, const rk_place_entry *prev_entries,
+                              uint64_t n_prev_entries, rk_assign *assign, uint32_t *place_off, rk_place_entry *entries,
+                              float *total, uint32_t *stats, NdKernArgs &K) {
     const uint32_t J = table->n_jobs;
     const uint64_t gpus = (uint64_t)nodes->n_nodes * nodes->gpus_per_node;
     int32_t rc;
     const size_t n = J ? J : 1, N = nodes->n_nodes;
-    const size_t nodes_words = (((3 * N + 3) & ~(size_t)3) + (size_t)gpus + 3) & ~(size_t)3;   // whole 16-byte pieces: copied and searched four words at a time
+    const size_t nodes_words = nd_nodes_words(N, (size_t)gpus);
     uint32_t *w_nodes, *w_jobs;
     float *f_jobs;
     unsigned long long *u64;
@@ -1731,7 +1813,6 @@ int32_t rk_launch_reschedule_nodes(rk_ctx *ctx, const float *ref_thr, const rk_p
     if ((rc = rk_scratch(ctx, SL_ND_U32, (14 * n + 1) * sizeof(uint32_t), (void **)&w_jobs))) return rc;
     if ((rc = rk_scratch(ctx, SL_ND_F32, 10 * n * sizeof(float), (void **)&f_jobs))) return rc;
     if ((rc = rk_scratch(ctx, SL_ND_U64, 2 * n * sizeof(unsigned long long), (void **)&u64))) return rc;
-    NdKernArgs K;
     NdBody &A = K.b;
     K.X.ref_thr = ref_thr; K.X.tb = table_dev(table); K.X.grid = grid_dev(grid);
     K.X.best_thr = best_thr; K.X.best_plan = best_plan; K.X.curve_thr = curve_thr;
@@ -1756,25 +1837,46 @@ int32_t rk_launch_reschedule_nodes(rk_ctx *ctx, const float *ref_thr, const rk_p
     A.udc_c = u64; A.okey = u64 + n;
     A.gives = gives; A.give = nullptr; A.give_c = nullptr;
     A.assign = assign; A.place_off = place_off; A.entries = entries; A.total = total; A.stats = stats;
+    return RK_OK;
+}
+
+// Dynamic LDS of k_nodes_lds and k_sim_nodes may be all of it: once per context.
+static int32_t nd_raise_lds(rk_ctx *ctx) {
+    if (ctx->nodes_lds_raised) return RK_OK;
+    const auto most = hipFuncAttributeMaxDynamicSharedMemorySize;
+    const void *const fs[] = {reinterpret_cast<const void *>(k_nodes_lds<ND_SMALL_THREADS, true>), reinterpret_cast<const void *>(k_nodes_lds<ND_FEW_THREADS, true>),
+                              reinterpret_cast<const void *>(k_nodes_lds<ND_THREADS, false>), reinterpret_cast<const void *>(k_sim_nodes<ND_SMALL_THREADS>),
+                              reinterpret_cast<const void *>(k_sim_nodes<ND_FEW_THREADS>)};
+    for (const void *f : fs) RK_HIP(ctx, hipFuncSetAttribute(f, most, (int)ND_LDS_MOST));
+    RK_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(k_reschedule_nodes), most, 2 * RK_MAX_JOBS_PER_ROUND * sizeof(float)));
+    ctx->nodes_lds_raised = true;
+    return RK_OK;
+}
+
+int32_t rk_launch_reschedule_nodes(rk_ctx *ctx, const float *ref_thr, const rk_plan_table *table,
+                                   const rk_alloc_grid *grid, const rk_nodes *nodes, const float *best_thr,
+                                   const uint32_t *best_plan, const float *curve_thr, const rk_job_state *jobs_state,
+                                   const uint32_t *prev_off, const rk_place_entry *prev_entries, uint64_t n_prev_entries,
+                                   rk_assign *assign, uint32_t *place_off, rk_place_entry *entries, float *total,
+                                   uint32_t *stats) {
+    NdKernArgs K;
+    NdBody &A = K.b;
+    int32_t rc;
+    if ((rc = nd_kernel_args(ctx, ref_thr, table, grid, nodes, best_thr, best_plan, curve_thr, jobs_state, prev_off, prev_entries,
+                             n_prev_entries, assign, place_off, entries, total, stats, K))) return rc;
+    if ((rc = nd_raise_lds(ctx))) return rc;
+    const size_t J = A.n_jobs, n = J ? J : 1, N = A.n_nodes, nodes_words = A.nodes_words;
     // Where the nodes and their copy fit a CU's LDS beside the cached slopes (512 nodes of 8 GPUs and 10,000 jobs do), the
     // loop runs on them there.
     const size_t lds_lj = nd_lds_words(J, N, nodes_words, true) * sizeof(uint32_t), lds_l = nd_lds_words(J, N, nodes_words, false) * sizeof(uint32_t);
     const bool in_lds = A.gpn <= 64u && lds_l <= ND_LDS_MOST, jobs_too = in_lds && lds_lj <= ND_LDS_MOST;
-    if (!ctx->nodes_lds_raised) {
-        const auto most = hipFuncAttributeMaxDynamicSharedMemorySize;
-        RK_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(k_nodes_lds<ND_SMALL_THREADS, true>), most, (int)ND_LDS_MOST));
-        RK_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(k_nodes_lds<ND_FEW_THREADS, true>), most, (int)ND_LDS_MOST));
-        RK_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(k_nodes_lds<ND_THREADS, false>), most, (int)ND_LDS_MOST));
-        RK_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(k_reschedule_nodes), most, 2 * RK_MAX_JOBS_PER_ROUND * sizeof(float)));
-        ctx->nodes_lds_raised = true;
-    }
     A.book = !in_lds;
     if (A.book) {
         k_nd_init<<<(uint32_t)((N + 255) / 256), 256, 0, ctx->stream>>>(K);
         RK_CHECK_LAUNCH(ctx, "k_nd_init");
     }
     if (J > 0) {
-        k_nd_prepare<<<(J + 3) / 4, 256, 0, ctx->stream>>>(K);
+        k_nd_prepare<<<(uint32_t)((J + 3) / 4), 256, 0, ctx->stream>>>(K);
         RK_CHECK_LAUNCH(ctx, "k_nd_prepare");
     }
     if (jobs_too && J <= ND_FEW_THREADS) k_nodes_lds<ND_FEW_THREADS, true><<<1, ND_FEW_THREADS, lds_lj, ctx->stream>>>(K);
@@ -1782,5 +1884,40 @@ int32_t rk_launch_reschedule_nodes(rk_ctx *ctx, const float *ref_thr, const rk_p
     else if (in_lds) k_nodes_lds<ND_THREADS, false><<<1, ND_THREADS, lds_l, ctx->stream>>>(K);
     else k_reschedule_nodes<<<1, ND_THREADS, (size_t)2 * n * sizeof(float), ctx->stream>>>(K);           // at most 96 KiB
     RK_CHECK_LAUNCH(ctx, "k_nodes_lds");
+    return RK_OK;
+}
+
+// Ticks of a simulation whose rounds search node by node, from the one that *A.tick says (k_sim_init and k_sim_step have
+// opened it): enough launches on the context's stream for all of them, a launch past the last tick returns at once.
+constexpr uint32_t SIM_NODES_ROUNDS = 64;        // rounds of a launch
+
+bool rk_sim_nodes_fit(uint32_t n_jobs, const rk_nodes *nodes) {
+    const size_t N = nodes->n_nodes, gpus = N * nodes->gpus_per_node;
+    return n_jobs > 0 && nodes->gpus_per_node <= 64u &&
+           nd_lds_words(n_jobs, N, nd_nodes_words(N, gpus), true, true) * sizeof(uint32_t) <= ND_LDS_MOST;
+}
+
+int32_t rk_launch_sim_nodes(rk_ctx *ctx, const SimArgs &S, const float *ref_thr, const rk_plan_table *table, const rk_alloc_grid *grid,
+                            const rk_nodes *nodes, const float *best_thr, const uint32_t *best_plan, const float *curve_thr,
+                            uint64_t cap_parts, rk_assign *assign) {
+    NdSimArgs K;
+    int32_t rc;
+    const rk_job_state held = {S.F.state, S.S.seg, S.S.lvl, nullptr, nullptr};
+    if ((rc = nd_kernel_args(ctx, ref_thr, table, grid, nodes, best_thr, best_plan, curve_thr, &held, S.at_off, S.at_ent, cap_parts,
+                             assign, S.now_off, S.now_ent, S.tick_total, nullptr, K))) return rc;
+    if ((rc = nd_raise_lds(ctx))) return rc;
+    K.S = S;
+    K.rounds = SIM_NODES_ROUNDS;
+    K.b.book = false;
+    const uint32_t J = K.b.n_jobs;
+    const size_t lds = nd_lds_words(J, K.b.n_nodes, K.b.nodes_words, true, true) * sizeof(uint32_t);
+    const NdKernArgs prepare = K;
+    for (uint32_t t = 0; t < S.n_ticks; t = S.n_ticks - t > SIM_NODES_ROUNDS ? t + SIM_NODES_ROUNDS : S.n_ticks) {
+        k_nd_prepare<<<(J + 3) / 4, 256, 0, ctx->stream>>>(prepare);
+        RK_CHECK_LAUNCH(ctx, "k_nd_prepare");
+        if (J <= ND_FEW_THREADS) k_sim_nodes<ND_FEW_THREADS><<<1, ND_FEW_THREADS, lds, ctx->stream>>>(K);
+        else k_sim_nodes<ND_SMALL_THREADS><<<1, ND_SMALL_THREADS, lds, ctx->stream>>>(K);
+        RK_CHECK_LAUNCH(ctx, "k_sim_nodes");
+    }
     return RK_OK;
 }

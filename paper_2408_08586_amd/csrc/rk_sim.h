@@ -82,6 +82,142 @@ __device__ __forceinline__ bool sim_frozen(uint32_t g, double held, uint32_t n_r
     return !may_move;
 }
 
+// Closes a tick for job j; true when the job holds other amounts than before it.
+__device__ __forceinline__ bool commit_job(const SimArgs &A, uint32_t j, double t, uint32_t &g_used) {
+    const rk_assign a = A.assign[j];
+    g_used += a.g;
+    SimJob s = {A.S.g[j], A.S.c[j], A.S.plan[j], A.n_reconf[j], A.S.owed[j], A.held[j], A.progress[j], 0.0, false};
+    const uint32_t n_reconf = s.n_reconf;
+    const bool moved = sim_close(s, a, t, A.dt, A.delta[j], A.work[j]);
+    if (s.n_reconf != n_reconf) A.n_reconf[j] = s.n_reconf;
+    if (a.g > 0) {
+        A.S.owed[j] = s.owed; A.held[j] = s.held; A.progress[j] = s.progress;
+        if (s.done) { A.finish[j] = s.finish; A.S.done[j] = 1; }
+    }
+    if (s.g > 0) A.S.plan[j] = s.plan;
+    if (!moved) return false;
+    uint32_t seg = 0xFFFFFFFFu, lvl = 0;
+    if (s.g > 0) {
+        // segment index of g (the job's counts ascend) and the CPU level that costs a.c
+        const uint32_t s0 = A.tb.seg_off[j], ns = A.tb.seg_off[j + 1] - s0;
+        uint32_t hi = ns;
+        seg = 0;
+        while (seg < hi) {
+            const uint32_t mid = (seg + hi) >> 1;
+            if (A.tb.seg_g[s0 + mid] < s.g) seg = mid + 1; else hi = mid;
+        }
+        for (uint32_t i = 0; i < A.grid.n_cpu; ++i)
+            if (cpus_of(A.grid, i, s.g) == s.c) { lvl = i; break; }
+    }
+    A.S.g[j] = s.g; A.S.c[j] = s.c; A.S.plan[j] = s.plan; A.S.seg[j] = (int32_t)seg; A.S.lvl[j] = lvl;
+    return true;
+}
+
+// The placement a tick made becomes where the jobs are when the next tick begins; true: they were somewhere else before.
+static_assert(sizeof(rk_place_entry) == sizeof(uint4), "a part is compared and copied as one piece");
+template <int THREADS>
+__device__ __forceinline__ bool sim_placed(const SimArgs &A) {
+    const uint32_t tid = threadIdx.x;
+    bool other = false;
+    for (uint32_t i = tid; i <= A.n_jobs; i += THREADS) {
+        const uint32_t now = A.now_off[i];
+        other |= A.at_off[i] != now;
+        A.at_off[i] = now;
+    }
+    const uint32_t n = A.now_off[A.n_jobs];
+    const uint4 *now_ent = reinterpret_cast<const uint4 *>(A.now_ent);
+    uint4 *at_ent = reinterpret_cast<uint4 *>(A.at_ent);
+    for (uint32_t i = tid; i < n; i += THREADS) {
+        const uint4 now = now_ent[i], at = at_ent[i];         // (a slot never written compares as it may: at worst a round more)
+        other |= at.x != now.x || at.y != now.y || at.z != now.z || at.w != now.w;
+        at_ent[i] = now;
+    }
+    return __syncthreads_or(other) != 0;
+}
+
+// A workgroup closes tick `tick`, whose round has run (first: there is none yet), and opens the next one; ticks that start
+// from exactly what the last round started from are closed at once.  True: the tick `tick` is open and needs a round
+// (round_needed: it does in any case); false: there are no more ticks.  What a thread writes of its jobs only it reads.
+template <int THREADS>
+__device__ __forceinline__ bool sim_ticks(const SimArgs &A, uint32_t &tick, bool first, bool round_needed) {
+    __shared__ unsigned long long sum_g, sum_c;
+    __shared__ uint32_t sum_f, sum_used, moved;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u;
+    for (;;) {
+        if (tid == 0) { sum_g = 0ull; sum_c = 0ull; sum_f = 0u; sum_used = 0u; moved = 0u; }
+        __syncthreads();
+        if (!first) {
+            const double t = (double)tick * A.dt;
+            uint32_t g_used = 0;
+            bool other = false;
+            for (uint32_t j = tid; j < A.n_jobs; j += THREADS)
+                if (A.F.state[j] != RK_JOB_OUT) other |= commit_job(A, j, t, g_used);
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) g_used += __shfl_xor(g_used, off, 64);
+            if (lane == 0 && g_used) atomicAdd(&sum_used, g_used);
+            if (A.loop && __ballot(other) && lane == 0) moved = 1u;
+            __syncthreads();
+            if (tid == 0) {
+                if (A.out.gpus_in_use) A.out.gpus_in_use[tick] = sum_used;
+                if (A.out.totals) A.out.totals[tick] = *A.tick_total;
+            }
+            if (moved) round_needed = true;
+            if (++tick == A.n_ticks) return false;
+        }
+        const double t = (double)tick * A.dt;
+        unsigned long long held_g = 0, held_c = 0;
+        uint32_t n_frozen = 0;
+        bool other = false;
+        for (uint32_t j = tid; j < A.n_jobs; j += THREADS) {
+            const bool active = A.arrival[j] <= t && !A.S.done[j];
+            const uint32_t g = A.S.g[j];
+            uint8_t state = RK_JOB_OUT;
+            int32_t gi = -1;
+            uint32_t ci = 0;
+            if (active) {
+                state = RK_JOB_NORMAL;
+                if (sim_frozen(g, A.held[j], A.n_reconf[j], A.delta[j], A.gate)) {
+                    state = RK_JOB_FROZEN;
+                    gi = A.S.seg[j];
+                    ci = A.S.lvl[j];
+                    held_g += g;
+                    held_c += A.grid.cpu_mode ? (unsigned long long)A.grid.cpu_levels[ci] * g
+                                              : (unsigned long long)A.grid.cpu_levels[ci];
+                    ++n_frozen;
+                }
+            }
+            if (first || A.F.state[j] != state || A.F.gi[j] != gi || A.F.ci[j] != ci) {
+                A.F.state[j] = state;
+                A.F.gi[j] = gi;
+                A.F.ci[j] = ci;
+                other = true;
+            }
+        }
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) {
+            held_g += __shfl_xor(held_g, off, 64);
+            held_c += __shfl_xor(held_c, off, 64);
+            n_frozen += __shfl_xor(n_frozen, off, 64);
+        }
+        if (lane == 0 && n_frozen) { atomicAdd(&sum_g, held_g); atomicAdd(&sum_c, held_c); atomicAdd(&sum_f, n_frozen); }
+        if (__syncthreads_or(other)) round_needed = true;
+        if (tid == 0) {
+            const unsigned long long hg = sum_g, hc = sum_c;
+            A.F.cap0[0] = hg < A.cl.G ? A.cl.G - hg : 0ull;   // frozen jobs are charged first
+            A.F.cap0[1] = hc < A.cl.C ? A.cl.C - hc : 0ull;
+            if (A.out.frozen) A.out.frozen[tick] = sum_f;
+        }
+        if (round_needed) return true;
+        __syncthreads();                                      // the sums are read before they are cleared
+    }
+}
+
 // Ticks [t0, t1) of a simulation under the greedy, on the context's stream; false in *taken: not a simulation for it.
 int32_t rk_launch_sim_few(rk_ctx *ctx, const SimArgs &A, const float *ref_thr, const rk_alloc_grid *grid, uint32_t max_segs_per_job,
                           const float *best_thr, const uint32_t *best_plan, const float *curve_thr, rk_assign *assign, bool *taken);
+
+// Whether a simulation over these nodes has its ticks in one workgroup's LDS, and all its ticks (rk_nodes.hip).
+bool rk_sim_nodes_fit(uint32_t n_jobs, const rk_nodes *nodes);
+int32_t rk_launch_sim_nodes(rk_ctx *ctx, const SimArgs &S, const float *ref_thr, const rk_plan_table *table, const rk_alloc_grid *grid,
+                            const rk_nodes *nodes, const float *best_thr, const uint32_t *best_plan, const float *curve_thr,
+                            uint64_t cap_parts, rk_assign *assign);

@@ -15,7 +15,9 @@
 // 27.1 ms under the greedy, 73.0 -> 46.3 ms over the nodes, of which one kernel
 // launch less per tick is about 2 ms).
 // Under the greedy up to about 1,000 jobs need none of this: k_sim_few runs
-// whole ticks in one workgroup (rk_allocate.hip).
+// whole ticks in one workgroup (rk_allocate.hip).  Over nodes up to about 1,300
+// jobs need none of it either: k_sim_nodes has nodes and jobs in LDS from tick
+// to tick (rk_nodes.hip).
 // The tick counter lives on the device, so every tick is the same sequence of
 // launches with the same arguments: the first tick runs eagerly (it also sizes
 // the scratch memory), the sequence is then captured once as a HIP graph on a
@@ -29,8 +31,6 @@ constexpr int SIM_THREADS = 1024;
 constexpr uint32_t SIM_BATCH = 4;              // replays between two looks at the tick counter
 constexpr int H_TICK = 63;                     // word of the context's pinned memory that holds it
 
-static_assert(sizeof(rk_place_entry) == sizeof(uint4), "a part is compared and copied as one piece");
-
 __global__ __launch_bounds__(SIM_THREADS) void k_sim_init(SimArgs A) {
     const uint32_t j = blockIdx.x * SIM_THREADS + threadIdx.x;
     if (j >= A.n_jobs) return;
@@ -41,132 +41,16 @@ __global__ __launch_bounds__(SIM_THREADS) void k_sim_init(SimArgs A) {
     if (A.at_off) { A.at_off[j] = 0u; if (j == 0) A.at_off[A.n_jobs] = 0u; }   // nobody is anywhere yet
 }
 
-// Closes a tick for job j; true when the job holds other amounts than before it.
-__device__ __forceinline__ bool commit_job(const SimArgs &A, uint32_t j, double t, uint32_t &g_used) {
-    const rk_assign a = A.assign[j];
-    g_used += a.g;
-    SimJob s = {A.S.g[j], A.S.c[j], A.S.plan[j], A.n_reconf[j], A.S.owed[j], A.held[j], A.progress[j], 0.0, false};
-    const uint32_t n_reconf = s.n_reconf;
-    const bool moved = sim_close(s, a, t, A.dt, A.delta[j], A.work[j]);
-    if (s.n_reconf != n_reconf) A.n_reconf[j] = s.n_reconf;
-    if (a.g > 0) {
-        A.S.owed[j] = s.owed; A.held[j] = s.held; A.progress[j] = s.progress;
-        if (s.done) { A.finish[j] = s.finish; A.S.done[j] = 1; }
-    }
-    if (s.g > 0) A.S.plan[j] = s.plan;
-    if (!moved) return false;
-    uint32_t seg = 0xFFFFFFFFu, lvl = 0;
-    if (s.g > 0) {
-        // segment index of g (the job's counts ascend) and the CPU level that costs a.c
-        const uint32_t s0 = A.tb.seg_off[j], ns = A.tb.seg_off[j + 1] - s0;
-        uint32_t hi = ns;
-        seg = 0;
-        while (seg < hi) {
-            const uint32_t mid = (seg + hi) >> 1;
-            if (A.tb.seg_g[s0 + mid] < s.g) seg = mid + 1; else hi = mid;
-        }
-        for (uint32_t i = 0; i < A.grid.n_cpu; ++i)
-            if (cpus_of(A.grid, i, s.g) == s.c) { lvl = i; break; }
-    }
-    A.S.g[j] = s.g; A.S.c[j] = s.c; A.S.plan[j] = s.plan; A.S.seg[j] = (int32_t)seg; A.S.lvl[j] = lvl;
-    return true;
-}
-
 // One workgroup, a thread per job (and every SIM_THREADS-th after it): what a thread writes of its jobs only it reads.
 // first: there is no tick to close yet.  Bound by the round trips to memory of the per-job words; at 406 jobs it takes
 // the place of two kernels, and a tick that needs no round costs one turn of its loop.
 __global__ __launch_bounds__(SIM_THREADS) void k_sim_step(SimArgs A, uint32_t first) {
-    __shared__ unsigned long long sum_g, sum_c;
-    __shared__ uint32_t sum_f, sum_used, moved;
-    const uint32_t tid = threadIdx.x, lane = tid & 63u;
+    const uint32_t tid = threadIdx.x;
     uint32_t tick = *A.tick;
     if (tick >= A.n_ticks) return;                            // replays past the last tick have nothing to close
     bool round_needed = first != 0u;                          // the same in all threads
-    if (!first && A.at_off) {
-        // the placement this tick made is where the jobs are when the next tick begins
-        bool other = false;
-        for (uint32_t i = tid; i <= A.n_jobs; i += SIM_THREADS) {
-            const uint32_t now = A.now_off[i];
-            other |= A.at_off[i] != now;
-            A.at_off[i] = now;
-        }
-        const uint32_t n = A.now_off[A.n_jobs];
-        const uint4 *now_ent = reinterpret_cast<const uint4 *>(A.now_ent);
-        uint4 *at_ent = reinterpret_cast<uint4 *>(A.at_ent);
-        for (uint32_t i = tid; i < n; i += SIM_THREADS) {
-            const uint4 now = now_ent[i], at = at_ent[i];     // (a slot never written compares as it may: at worst a round more)
-            other |= at.x != now.x || at.y != now.y || at.z != now.z || at.w != now.w;
-            at_ent[i] = now;
-        }
-        round_needed = __syncthreads_or(other) != 0;
-    }
-    for (;;) {
-        if (tid == 0) { sum_g = 0ull; sum_c = 0ull; sum_f = 0u; sum_used = 0u; moved = 0u; }
-        __syncthreads();
-        if (!first) {
-            const double t = (double)tick * A.dt;
-            uint32_t g_used = 0;
-            bool other = false;
-            for (uint32_t j = tid; j < A.n_jobs; j += SIM_THREADS)
-                if (A.F.state[j] != RK_JOB_OUT) other |= commit_job(A, j, t, g_used);
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) g_used += __shfl_xor(g_used, off, 64);
-            if (lane == 0 && g_used) atomicAdd(&sum_used, g_used);
-            if (A.loop && __ballot(other) && lane == 0) moved = 1u;
-            __syncthreads();
-            if (tid == 0) {
-                if (A.out.gpus_in_use) A.out.gpus_in_use[tick] = sum_used;
-                if (A.out.totals) A.out.totals[tick] = *A.tick_total;
-            }
-            if (moved) round_needed = true;
-            if (++tick == A.n_ticks) break;
-        }
-        const double t = (double)tick * A.dt;
-        unsigned long long held_g = 0, held_c = 0;
-        uint32_t n_frozen = 0;
-        bool other = false;
-        for (uint32_t j = tid; j < A.n_jobs; j += SIM_THREADS) {
-            const bool active = A.arrival[j] <= t && !A.S.done[j];
-            const uint32_t g = A.S.g[j];
-            uint8_t state = RK_JOB_OUT;
-            int32_t gi = -1;
-            uint32_t ci = 0;
-            if (active) {
-                state = RK_JOB_NORMAL;
-                if (sim_frozen(g, A.held[j], A.n_reconf[j], A.delta[j], A.gate)) {
-                    state = RK_JOB_FROZEN;
-                    gi = A.S.seg[j];
-                    ci = A.S.lvl[j];
-                    held_g += g;
-                    held_c += A.grid.cpu_mode ? (unsigned long long)A.grid.cpu_levels[ci] * g
-                                              : (unsigned long long)A.grid.cpu_levels[ci];
-                    ++n_frozen;
-                }
-            }
-            if (first || A.F.state[j] != state || A.F.gi[j] != gi || A.F.ci[j] != ci) {
-                A.F.state[j] = state;
-                A.F.gi[j] = gi;
-                A.F.ci[j] = ci;
-                other = true;
-            }
-        }
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) {
-            held_g += __shfl_xor(held_g, off, 64);
-            held_c += __shfl_xor(held_c, off, 64);
-            n_frozen += __shfl_xor(n_frozen, off, 64);
-        }
-        if (lane == 0 && n_frozen) { atomicAdd(&sum_g, held_g); atomicAdd(&sum_c, held_c); atomicAdd(&sum_f, n_frozen); }
-        if (__syncthreads_or(other)) round_needed = true;
-        if (tid == 0) {
-            const unsigned long long hg = sum_g, hc = sum_c;
-            A.F.cap0[0] = hg < A.cl.G ? A.cl.G - hg : 0ull;   // frozen jobs are charged first
-            A.F.cap0[1] = hc < A.cl.C ? A.cl.C - hc : 0ull;
-            if (A.out.frozen) A.out.frozen[tick] = sum_f;
-        }
-        if (round_needed) break;
-        __syncthreads();                                      // the sums are read before they are cleared
-    }
+    if (!first && A.at_off) round_needed = sim_placed<SIM_THREADS>(A);
+    (void)sim_ticks<SIM_THREADS>(A, tick, first != 0u, round_needed);
     if (tid == 0) {
         *A.tick = tick;
         __hip_atomic_store(A.h_tick, tick, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -264,6 +148,19 @@ extern "C" int32_t rk_simulate(rk_ctx *ctx, const float *ref_thr, const rk_plan_
     void *h_tick;
     RK_HIP(ctx, hipHostGetDevicePointer(&h_tick, ctx->h_pinned + H_TICK, 0));
     A.h_tick = static_cast<uint32_t *>(h_tick);
+    if (nodes && rk_sim_nodes_fit(J, nodes)) {                 // the nodes and jobs fit a workgroup's LDS: ticks without launches between them
+        k_sim_init<<<(J + SIM_THREADS - 1) / SIM_THREADS, SIM_THREADS, 0, ctx->stream>>>(A);
+        RK_CHECK_LAUNCH(ctx, "k_sim_init");
+        k_sim_step<<<1, SIM_THREADS, 0, ctx->stream>>>(A, 1u);
+        RK_CHECK_LAUNCH(ctx, "k_sim_step");
+        if ((rc = rk_launch_sim_nodes(ctx, A, ref_thr, table, grid, nodes, best_thr, best_plan, curve_thr, cap_parts, assign))) return rc;
+        if (options->n_ticks > 1) {
+            RK_HIP(ctx, hipStreamSynchronize(ctx->stream));
+            const uint32_t closed = __atomic_load_n(ctx->h_pinned + H_TICK, __ATOMIC_ACQUIRE);
+            if (closed != options->n_ticks) return rk_fail(ctx, RK_ERR_DEVICE, "the simulation ended after %u of %u ticks", closed, options->n_ticks);
+        }
+        return RK_OK;
+    }
     // (of earlier simulations one of a single tick may still run: it can put 1 there, which ends no loop below)
     ctx->sim_failed = true;                                    // until this one has come to its end
     __atomic_store_n(ctx->h_pinned + H_TICK, 0u, __ATOMIC_RELEASE);

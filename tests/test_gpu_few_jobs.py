@@ -79,6 +79,35 @@ def test_ticks_in_one_launch(orc, n_jobs, n_ticks, scarce):
     run.close()
 
 
+@pytest.mark.parametrize("n_jobs,n_ticks,gpn", [(1, 1, 8), (30, 64, 4), (60, 200, 8), (256, 65, 6), (257, 130, 8), (700, 60, 16), (1600, 20, 8)])
+@pytest.mark.parametrize("scarce", [False, True])
+def test_ticks_over_nodes_in_one_launch(orc, n_jobs, n_ticks, gpn, scarce):
+    """k_sim_nodes: rounds around the end of a launch, one job per thread and more, jobs whose values fit LDS and (1,600 of
+    them) do not; jobs that finish, thaw and lose their memory between the rounds."""
+    from gpu_harness import DeviceRun
+    from test_gpu_sim import run_on_gpu, same
+    base = workloads.trace_scale()
+    coef, ints = np.resize(base.coef, (n_jobs, base.coef.shape[1])), np.resize(base.ints, (n_jobs, base.ints.shape[1]))
+    grid = workloads.Grid(np.array([1, 2, 4, 8, 16], np.uint32), 1, np.array([64.0, 256.0], np.float32), 0)
+    n_nodes = 3 if scarce else 10
+    nodes = (n_nodes, gpn, (5 if scarce else 16) * gpn, 300.0 if scarce else 4096.0)
+    cluster = workloads.Cluster(n_nodes * gpn, n_nodes * nodes[2], n_nodes * nodes[3])
+    wl = workloads.Workload("few", coef, ints, base.bounds, grid, base.env, cluster)
+    r = orc.schedule_round(wl, n_threads=16)
+    rng = np.random.default_rng(n_jobs + n_ticks)
+    arrival = np.sort(rng.uniform(0.0, 60.0 * n_ticks * 0.6, n_jobs))
+    arrival[: 1 + n_jobs // 4] = 0.0
+    work = coef[:, 16] * rng.uniform(60.0, 4000.0, n_jobs)
+    delta = rng.uniform(0.0, 90.0, n_jobs)
+    run = DeviceRun(wl)
+    run.enumerate()
+    want = orc.simulator.simulate(coef[:, 16], r["table"], grid, cluster, r["best_thr"], r["best_plan"], r["curve_thr"], arrival, work,
+                                  delta, 60.0, n_ticks, gate=0.9, policy="nodes", nodes=nodes)
+    for _ in range(2):                                          # (the second one finds the first one's working memory)
+        same(run_on_gpu(run, r, arrival, work, delta, 60.0, n_ticks, 0.9, policy=2, nodes=nodes), want)
+    run.close()
+
+
 @pytest.mark.parametrize("n_jobs,spread", [(2049, 0.0), (2049, 3.0), (3000, 1.0), (12288, 0.3)])
 def test_thresholds_of_many_jobs(orc, n_jobs, spread):
     """Rounds whose histograms are in memory (more than 2,048 jobs): slopes in few bins (spread 0: a handful of values) and
