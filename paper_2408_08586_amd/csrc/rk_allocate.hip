@@ -918,13 +918,12 @@ __device__ __forceinline__ void lds_barrier() {
 // LDS words tail_run needs beside its per-job scratch: what every wavefront offers, in two copies used in turn, and the
 // CPU levels.
 struct TailOffer { uint32_t slope, job, dg, dc, bound, bound_job; };
-constexpr int TAIL_WAVES = TAIL_THREADS / 64;
-constexpr int TAIL_RED_WORDS = (2 * TAIL_WAVES * (int)sizeof(TailOffer) + RK_MAX_CPU_LEVELS * 4) / 8;
+constexpr int tail_red_words(int threads) { return (2 * (threads / 64) * (int)sizeof(TailOffer) + RK_MAX_CPU_LEVELS * 4) / 8; }
 
-// Workgroup of TAIL_THREADS threads; lds = max_jobs * 12 bytes of scratch, red =
-// TAIL_RED_WORDS words; at most KMAX * TAIL_THREADS jobs.  Starts from the
+// Workgroup of T threads; lds = max_jobs * 12 bytes of scratch, red =
+// tail_red_words(T) words; at most KMAX * T jobs.  Starts from the
 // state k_apply / apply_job left in st.  Thread t owns jobs t, t +
-// TAIL_THREADS, ...: their cached steps stay in its registers, and only it
+// T, ...: their cached steps stay in its registers, and only it
 // (and, for the winner's new search, its wavefront) touches their LDS entries.
 //
 // A step is a chain that nothing else hides, so what counts is its length: one
@@ -935,7 +934,7 @@ constexpr int TAIL_RED_WORDS = (2 * TAIL_WAVES * (int)sizeof(TailOffer) + RK_MAX
 // this 65 us instead of 56 for 256 rounds of 500 jobs, the CPU and GPU passes
 // of the selection; 31 instead of 29 for 10,000 jobs, where the nine turns are
 // mostly looks through all jobs).
-template <int PASS, int KMAX>
+template <int PASS, int KMAX, int T>
 __device__ __forceinline__ void tail_run(const Ctx &X, const JobState &st, uint32_t rnd, uint32_t J0, uint32_t J1,
                                          unsigned long long freeG, unsigned long long freeC, uint32_t max_jobs,
                                          float *lds, unsigned long long *red) {
@@ -945,7 +944,7 @@ __device__ __forceinline__ void tail_run(const Ctx &X, const JobState &st, uint3
     uint16_t *gh = ci + max_jobs;                                  // GPUs held (CPU pass); GPUs of a new step (GPU pass)
     float *found = reinterpret_cast<float *>(gh + max_jobs);       // slope of a new step on its way to the registers
     TailOffer *offers = reinterpret_cast<TailOffer *>(red);
-    uint32_t *lvl = reinterpret_cast<uint32_t *>(offers + 2 * TAIL_WAVES);   // CPU levels, for indexing by lane
+    uint32_t *lvl = reinterpret_cast<uint32_t *>(offers + 2 * (T / 64));   // CPU levels, for indexing by lane
 
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     const uint32_t nj = J1 - J0, jrel0 = J0 - X.jb;
@@ -976,7 +975,7 @@ __device__ __forceinline__ void tail_run(const Ctx &X, const JobState &st, uint3
         uint32_t c_i[KMAX], target[KMAX], gpus[KMAX];
 #pragma unroll
         for (int k = 0; k < KMAX; ++k) {                           // all loads go out before the first is used
-            const uint32_t jl = tid + (uint32_t)k * TAIL_THREADS;
+            const uint32_t jl = tid + (uint32_t)k * T;
             const uint32_t at = jrel0 + (jl < nj ? jl : nj - 1u);
             g_i[k] = st.gi[at];
             c_i[k] = st.ci[at];
@@ -987,7 +986,7 @@ __device__ __forceinline__ void tail_run(const Ctx &X, const JobState &st, uint3
         __syncthreads();                                           // the levels are in LDS
 #pragma unroll
         for (int k = 0; k < KMAX; ++k) {
-            const uint32_t jl = tid + (uint32_t)k * TAIL_THREADS;
+            const uint32_t jl = tid + (uint32_t)k * T;
             const bool have = jl < nj;
             const uint32_t need = need_cpus(g_i[k], c_i[k], target[k], gpus[k]);
             slope[k] = have ? slope[k] : 0.f;
@@ -1034,7 +1033,7 @@ __device__ __forceinline__ void tail_run(const Ctx &X, const JobState &st, uint3
             jf = 0; js = 0; df = 0; cf = 0;
 #pragma unroll
             for (int k = 0; k < KMAX; ++k) {
-                const uint32_t jl = tid + (uint32_t)k * TAIL_THREADS;
+                const uint32_t jl = tid + (uint32_t)k * T;
                 float v = slope[k];
                 const bool stopped = v > 0.f && ((PASS == 0 && dg[k] > roomG) || dc[k] > roomC);
                 v = stopped ? -v : v;
@@ -1049,14 +1048,14 @@ __device__ __forceinline__ void tail_run(const Ctx &X, const JobState &st, uint3
             ms = wave_max_u32_rows(bs);
             if (mf) {
                 jm = wave_min_u32_rows(bf == mf ? jf : 0xFFFFFFFFu);
-                const uint32_t at = jm & 63u;                   // (thread t owns jobs t + k * TAIL_THREADS: a multiple of 64)
+                const uint32_t at = jm & 63u;                   // (thread t owns jobs t + k * T: a multiple of 64)
                 dgm = wave_lane_u32(df, at);
                 dcm = wave_lane_u32(cf, at);
             }
             if (ms) jb = wave_min_u32_rows(bs == ms ? js : 0xFFFFFFFFu);
         }
         turn ^= 1u;
-        if (lane == 0) offers[turn * TAIL_WAVES + wave] = TailOffer{mf, jm, dgm, dcm, ms, jb};
+        if (lane == 0) offers[turn * (T / 64) + wave] = TailOffer{mf, jm, dgm, dcm, ms, jb};
         // What this wavefront will need should its best job win: where the job's counts are and, a turn later (in the first
         // turn at once), amounts and values.  Nothing waits for the loads here: they are made by all lanes, even of what is
         // the same for all, so that what comes through LDS does not wait for them, and the barrier is one for LDS alone.
@@ -1091,7 +1090,7 @@ __device__ __forceinline__ void tail_run(const Ctx &X, const JobState &st, uint3
             }
         }
         lds_barrier();
-        const TailOffer o = offers[turn * TAIL_WAVES + (lane & (TAIL_WAVES - 1))];   // every row of 16 lanes has all of them
+        const TailOffer o = offers[turn * (T / 64) + (lane & ((T / 64) - 1))];   // every row of 16 lanes has all of them
         const uint32_t top = (uint32_t)__builtin_amdgcn_readfirstlane((int)row_max_u32(o.slope));
         const uint32_t jw = (uint32_t)__builtin_amdgcn_readfirstlane((int)row_min_u32(o.slope == top ? o.job : 0xFFFFFFFFu));
         const uint32_t bound = (uint32_t)__builtin_amdgcn_readfirstlane((int)row_max_u32(o.bound));
@@ -1102,11 +1101,11 @@ __device__ __forceinline__ void tail_run(const Ctx &X, const JobState &st, uint3
 #pragma unroll
             for (int k = 0; k < KMAX; ++k) {
                 const float v = slope[k];
-                if (v < 0.f && key_of(-v, tid + (uint32_t)k * TAIL_THREADS) > kf) todo |= 1u << k;
+                if (v < 0.f && key_of(-v, tid + (uint32_t)k * T) > kf) todo |= 1u << k;
             }
             // the searches go through LDS so that the register arrays are only ever indexed by constants
             for (uint32_t rest = todo; rest; rest &= rest - 1u) {
-                const uint32_t jl = tid + ((uint32_t)__ffs((int)rest) - 1u) * TAIL_THREADS;
+                const uint32_t jl = tid + ((uint32_t)__ffs((int)rest) - 1u) * T;
                 const Step nx = best_step<PASS>(X, J0 + jl, gi[jl], PASS == 0 ? 0u : gh[jl], ci[jl], freeG, freeC);
                 found[jl] = nx.slope;
                 tgt[jl] = (uint16_t)nx.tgt;
@@ -1115,7 +1114,7 @@ __device__ __forceinline__ void tail_run(const Ctx &X, const JobState &st, uint3
 #pragma unroll
             for (int k = 0; k < KMAX; ++k) {
                 if (todo >> k & 1u) {
-                    const uint32_t jl = tid + (uint32_t)k * TAIL_THREADS;
+                    const uint32_t jl = tid + (uint32_t)k * T;
                     slope[k] = found[jl];
                     if (PASS == 0) dg[k] = gh[jl];
                     dc[k] = need_cpus(gi[jl], ci[jl], tgt[jl], gh[jl]);
@@ -1125,7 +1124,7 @@ __device__ __forceinline__ void tail_run(const Ctx &X, const JobState &st, uint3
             continue;
         }
         if (!top) break;                                        // no positive slope left
-        const uint32_t owner = jw % TAIL_THREADS, kw = jw / TAIL_THREADS;
+        const uint32_t owner = jw % T, kw = jw / T;
         const uint32_t won = owner / 64u;                       // the wavefront whose offer it was
         if (PASS == 0) freeG -= wave_lane_u32(o.dg, won);
         freeC -= wave_lane_u32(o.dc, won);
@@ -1149,7 +1148,7 @@ __device__ __forceinline__ void tail_run(const Ctx &X, const JobState &st, uint3
         }
     }
     for (; moved; moved &= moved - 1u) {                        // only the jobs that took a step here changed since k_apply
-        const uint32_t jl = tid + ((uint32_t)__ffs((int)moved) - 1u) * TAIL_THREADS;
+        const uint32_t jl = tid + ((uint32_t)__ffs((int)moved) - 1u) * T;
         if (PASS == 0) {
             const int32_t s_i = gi[jl];
             st.gi[jrel0 + jl] = s_i;
@@ -1166,13 +1165,13 @@ constexpr int TAIL_KMAX = (RK_MAX_JOBS_PER_ROUND + TAIL_THREADS - 1) / TAIL_THRE
 template <int PASS>
 __global__ __launch_bounds__(TAIL_THREADS) void k_tail(Ctx X, uint32_t max_jobs, JobState st) {
     extern __shared__ float lds_dyn[];
-    __shared__ unsigned long long red[TAIL_RED_WORDS];
+    __shared__ unsigned long long red[tail_red_words(TAIL_THREADS)];
     const uint32_t rnd = blockIdx.x;
     if (PASS == 1 && st.cpu_steps[rnd] == 0u) return;       // empty pass
     uint32_t J0, J1;
     rk_cluster cl;
     round_of(X.R, rnd, J0, J1, cl);
-    tail_run<PASS, TAIL_KMAX>(X, st, rnd, J0, J1, st.free_g[rnd], st.free_g[X.R.n_rounds + rnd], max_jobs, lds_dyn, red);
+    tail_run<PASS, TAIL_KMAX, TAIL_THREADS>(X, st, rnd, J0, J1, st.free_g[rnd], st.free_g[X.R.n_rounds + rnd], max_jobs, lds_dyn, red);
 }
 
 // ------------------------------------------------------------------ selection of a pass in one workgroup
@@ -1195,15 +1194,15 @@ __device__ __forceinline__ void mem_wish_job(const Ctx &X, const JobState &st, u
 __device__ bool mem_close_round(const Ctx &X, const int32_t *gi_of, const uint32_t *g_of, const uint32_t *ci_of, uint32_t rnd,
                                 double wish, double val, rk_assign *__restrict__ assign, float *__restrict__ totals);
 
-template <int PASS, int KMAX>
-__global__ __launch_bounds__(TAIL_THREADS) void k_select_small(Ctx X, uint32_t max_jobs, JobState st, HullBuf H,
+template <int PASS, int KMAX, int T>
+__global__ __launch_bounds__(T) void k_select_small(Ctx X, uint32_t max_jobs, JobState st, HullBuf H,
                                                               rk_assign *__restrict__ assign, float *__restrict__ totals) {
     extern __shared__ unsigned long long lds_sel[];             // the histogram, then the tail's scratch
     unsigned long long *hc = lds_sel;                           // one histogram, used for level 0 and then level 1
     uint32_t *hg = reinterpret_cast<uint32_t *>(hc + BINS);
     __shared__ CutScratch cs;
-    __shared__ unsigned long long red[TAIL_RED_WORDS];
-    __shared__ double sums[2 * (TAIL_THREADS / 64)];
+    __shared__ unsigned long long red[tail_red_words(T)];
+    __shared__ double sums[2 * (T / 64)];
     const uint32_t rnd = blockIdx.x, tid = threadIdx.x;
     uint32_t J0, J1;
     rk_cluster cl;
@@ -1215,50 +1214,50 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_select_small(Ctx X, uint32_t m
         if (KMAX == TAIL_KMAX) empty_pass = st.cpu_steps[rnd] == 0u;
         else {
             bool any = false;
-            for (uint32_t jl = tid; jl < nj; jl += TAIL_THREADS) any |= H.key[J0 + jl - X.jb] != 0u;
+            for (uint32_t jl = tid; jl < nj; jl += T) any |= H.key[J0 + jl - X.jb] != 0u;
             empty_pass = __syncthreads_or(any) == 0;
         }
     }
     if (!empty_pass) {
         unsigned long long capG, capC;
         pass_caps<PASS>(X.R, cl, st, rnd, capG, capC);
-        for (uint32_t i = tid; i < BINS; i += TAIL_THREADS) { hg[i] = 0; hc[i] = 0; }
+        for (uint32_t i = tid; i < BINS; i += T) { hg[i] = 0; hc[i] = 0; }
         __syncthreads();
-        for (uint32_t jl = tid; jl < nj; jl += TAIL_THREADS) hist_add<PASS, 0, TAIL_THREADS>(X, H, J0 + jl - X.jb, 0, hg, hc);
+        for (uint32_t jl = tid; jl < nj; jl += T) hist_add<PASS, 0, T>(X, H, J0 + jl - X.jb, 0, hg, hc);
         __syncthreads();
-        const Cut c0 = find_cut<TAIL_THREADS>(hg, hc, 0, 0, capG, capC, cs);
+        const Cut c0 = find_cut<T>(hg, hc, 0, 0, capG, capC, cs);
         Selection sel;
         sel.thr24 = -1;
         unsigned long long usedG = c0.baseG, usedC = c0.baseC;
         if (c0.bin >= 0) {                                      // uniform over the workgroup
             __syncthreads();                                    // the last look at level 0
-            for (uint32_t i = tid; i < BINS; i += TAIL_THREADS) { hg[i] = 0; hc[i] = 0; }
+            for (uint32_t i = tid; i < BINS; i += T) { hg[i] = 0; hc[i] = 0; }
             __syncthreads();
-            for (uint32_t jl = tid; jl < nj; jl += TAIL_THREADS) hist_add<PASS, 1, TAIL_THREADS>(X, H, J0 + jl - X.jb, c0.bin, hg, hc);
+            for (uint32_t jl = tid; jl < nj; jl += T) hist_add<PASS, 1, T>(X, H, J0 + jl - X.jb, c0.bin, hg, hc);
             __syncthreads();
-            const Cut c1 = find_cut<TAIL_THREADS>(hg, hc, c0.baseG, c0.baseC, capG, capC, cs);
+            const Cut c1 = find_cut<T>(hg, hc, c0.baseG, c0.baseC, capG, capC, cs);
             sel.thr24 = ((long long)c0.bin << 12) + (long long)c1.bin;
             usedG = c1.baseG; usedC = c1.baseC;
         }
         sel.freeG = capG - usedG;
         sel.freeC = capC - usedC;
-        for (uint32_t jl = tid; jl < nj; jl += TAIL_THREADS) apply_job<PASS>(X, st, H, J0 + jl, sel.thr24, sel.freeG, sel.freeC);
+        for (uint32_t jl = tid; jl < nj; jl += T) apply_job<PASS>(X, st, H, J0 + jl, sel.thr24, sel.freeG, sel.freeC);
         __syncthreads();                                        // the state in st is read back by the whole workgroup; the
                                                                 // histogram's LDS passes to the tail
-        tail_run<PASS, KMAX>(X, st, rnd, J0, J1, sel.freeG, sel.freeC, max_jobs, reinterpret_cast<float *>(lds_sel), red);
+        tail_run<PASS, KMAX, T>(X, st, rnd, J0, J1, sel.freeG, sel.freeC, max_jobs, reinterpret_cast<float *>(lds_sel), red);
     }
     if (PASS == 0 || KMAX == TAIL_KMAX) return;                 // (large rounds: a thread per job does it faster, k_mem_wish)
     // memory: every thread writes the wishes of its jobs, the first wavefront closes the round
     __syncthreads();                                            // the granted amounts are in st
     double cost_d = 0.0, val_d = 0.0;
-    for (uint32_t jl = tid; jl < nj; jl += TAIL_THREADS) mem_wish_job(X, st, J0 + jl, assign, cost_d, val_d);
+    for (uint32_t jl = tid; jl < nj; jl += T) mem_wish_job(X, st, J0 + jl, assign, cost_d, val_d);
     cost_d = wave_sum_f64(cost_d);
     val_d = wave_sum_f64(val_d);
-    if ((tid & 63u) == 0) { sums[tid >> 6] = cost_d; sums[TAIL_THREADS / 64 + (tid >> 6)] = val_d; }
+    if ((tid & 63u) == 0) { sums[tid >> 6] = cost_d; sums[T / 64 + (tid >> 6)] = val_d; }
     __syncthreads();                                            // also: the wishes are stored before anything replaces them
     if (tid < 64u) {
-        const bool has = tid < TAIL_THREADS / 64;
-        const double wish = wave_sum_f64(has ? sums[tid] : 0.0), val = wave_sum_f64(has ? sums[TAIL_THREADS / 64 + tid] : 0.0);
+        const bool has = tid < T / 64;
+        const double wish = wave_sum_f64(has ? sums[tid] : 0.0), val = wave_sum_f64(has ? sums[T / 64 + tid] : 0.0);
         const uint32_t jrel0 = J0 - X.jb;
         mem_close_round(X, st.gi + jrel0, st.g + jrel0, st.ci + jrel0, rnd, wish, val, assign + jrel0, totals);
     }
@@ -2857,14 +2856,17 @@ int32_t launch_pass(rk_ctx *ctx, const Ctx &X, const JobState &st, const HullBuf
     }
     const size_t sel_lds = tail_lds > SELECT_HIST_BYTES ? tail_lds : SELECT_HIST_BYTES;
     if (mj <= SMALL_ROUND_JOBS) {
-        k_select_small<PASS, SMALL_ROUND_JOBS / TAIL_THREADS><<<n_rounds, TAIL_THREADS, sel_lds, s>>>(X, mj, st, H, assign, totals);
+        // (as few wavefronts as give every job a thread: a step's barrier and reductions are theirs)
+        if (mj <= TAIL_THREADS / 2) k_select_small<PASS, 1, TAIL_THREADS / 2><<<n_rounds, TAIL_THREADS / 2, sel_lds, s>>>(X, mj, st, H, assign, totals);
+        else if (mj <= TAIL_THREADS) k_select_small<PASS, 1, TAIL_THREADS><<<n_rounds, TAIL_THREADS, sel_lds, s>>>(X, mj, st, H, assign, totals);
+        else k_select_small<PASS, SMALL_ROUND_JOBS / TAIL_THREADS, TAIL_THREADS><<<n_rounds, TAIL_THREADS, sel_lds, s>>>(X, mj, st, H, assign, totals);
         RK_CHECK_LAUNCH(ctx, "k_select_small");
         *closed = PASS == 1;
         return RK_OK;
     }
     if constexpr (PASS == 1) {
         if ((uint64_t)(X.grid.n_cpu - 1u) * mj <= CPU_ONE_WG_STEPS) {
-            k_select_small<1, TAIL_KMAX><<<n_rounds, TAIL_THREADS, sel_lds, s>>>(X, mj, st, H, assign, totals);
+            k_select_small<1, TAIL_KMAX, TAIL_THREADS><<<n_rounds, TAIL_THREADS, sel_lds, s>>>(X, mj, st, H, assign, totals);
             RK_CHECK_LAUNCH(ctx, "k_select_small");
             return RK_OK;
         }
@@ -2893,10 +2895,12 @@ int32_t rk_allocate_setup(rk_ctx *ctx) {
     ctx->static_scratch = static_cast<unsigned char *>(p);
     const void *big[] = {reinterpret_cast<const void *>(k_tail<0>), reinterpret_cast<const void *>(k_tail<1>),
                          reinterpret_cast<const void *>(k_floors),
-                         reinterpret_cast<const void *>(k_select_small<1, TAIL_KMAX>)};
+                         reinterpret_cast<const void *>(k_select_small<1, TAIL_KMAX, TAIL_THREADS>)};
     for (const void *f : big) RK_HIP(ctx, hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 152 * 1024));
-    const void *small[] = {reinterpret_cast<const void *>(k_select_small<0, SMALL_ROUND_JOBS / TAIL_THREADS>),
-                           reinterpret_cast<const void *>(k_select_small<1, SMALL_ROUND_JOBS / TAIL_THREADS>)};
+    const void *small[] = {reinterpret_cast<const void *>(k_select_small<0, SMALL_ROUND_JOBS / TAIL_THREADS, TAIL_THREADS>),
+                           reinterpret_cast<const void *>(k_select_small<1, SMALL_ROUND_JOBS / TAIL_THREADS, TAIL_THREADS>),
+                           reinterpret_cast<const void *>(k_select_small<0, 1, TAIL_THREADS>), reinterpret_cast<const void *>(k_select_small<1, 1, TAIL_THREADS>),
+                           reinterpret_cast<const void *>(k_select_small<0, 1, TAIL_THREADS / 2>), reinterpret_cast<const void *>(k_select_small<1, 1, TAIL_THREADS / 2>)};
     RK_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(k_round_few), hipFuncAttributeMaxDynamicSharedMemorySize, 144 * 1024));
     RK_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(k_sim_few), hipFuncAttributeMaxDynamicSharedMemorySize, FEW_SIM_LDS));
     for (const void *f : small) RK_HIP(ctx, hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024));

@@ -108,9 +108,11 @@ def test_ticks_over_nodes_in_one_launch(orc, n_jobs, n_ticks, gpn, scarce):
     run.close()
 
 
-@pytest.mark.parametrize("n_jobs,spread", [(2049, 0.0), (2049, 3.0), (3000, 1.0), (12288, 0.3)])
+@pytest.mark.parametrize("n_jobs,spread", [(511, 0.0), (512, 1.0), (513, 1.0), (1024, 1.0), (1025, 0.3), (2049, 0.0), (2049, 3.0),
+                                           (3000, 1.0), (12288, 0.3)])
 def test_thresholds_of_many_jobs(orc, n_jobs, spread):
-    """Rounds whose histograms are in memory (more than 2,048 jobs): slopes in few bins (spread 0: a handful of values) and
+    """Rounds around the lines between 512 and 1,024 threads and one and two jobs a thread, and rounds whose histograms are
+    in memory (more than 2,048 jobs): slopes in few bins (spread 0: a handful of values) and
     over many groups of them, capacities that cut in the first group, in the middle, at the last step, and not at all."""
     import paper_2408_08586_amd as rk
     from gpu_harness import DeviceRun
