@@ -1914,9 +1914,10 @@ __device__ __forceinline__ rk_assign few_memory(const Ctx &X, const FewMem &M, u
 // One workgroup per round; near: per-lane words in LDS.
 __global__ __launch_bounds__(FEW_THREADS) void k_round_few(Ctx X, JobState st, uint32_t max_jobs, uint32_t lanes0, uint32_t lanes1,
                                                            uint32_t near, rk_assign *__restrict__ assign,
-                                                           float *__restrict__ totals) {
+                                                           float *__restrict__ totals, TableGuard guard) {
     extern __shared__ __align__(16) unsigned long long lds_few[];
     __shared__ double sums[2 * FEW_WAVES];
+    if (!table_usable(guard)) return;
     const uint32_t rnd = blockIdx.x, tid = threadIdx.x;
     uint32_t J0, J1;
     rk_cluster cl;
@@ -2907,12 +2908,22 @@ int32_t rk_allocate_setup(rk_ctx *ctx) {
     return RK_OK;
 }
 
+// jobs of a round that may hold GPUs
+static uint32_t few_holders(uint32_t max_jobs, const rk_cluster *one_cluster, bool given) {
+    return one_cluster && !given && one_cluster->G < max_jobs ? one_cluster->G : max_jobs;
+}
+bool rk_round_is_few(const rk_alloc_grid *grid, uint32_t max_jobs, uint32_t max_segs_per_job, const rk_cluster *one_cluster, bool given) {
+    return max_jobs > 0 && max_jobs <= FEW_JOBS && max_segs_per_job <= 64u &&
+           (uint64_t)max_jobs * few_lanes(max_segs_per_job) <= FEW_GPU_LANES &&
+           (uint64_t)few_holders(max_jobs, one_cluster, given) * few_lanes(grid->n_cpu) <= FEW_CPU_LANES;
+}
+
 int32_t rk_launch_allocate(rk_ctx *ctx, const float *ref_thr, const TableDev &tb, const rk_alloc_grid *grid,
                            uint32_t n_rounds, const uint32_t *d_round_off, const rk_cluster *d_clusters,
                            const rk_cluster *one_cluster, uint32_t jb, uint32_t n_jobs, uint32_t max_jobs,
                            uint32_t max_segs_per_job, const float *best_thr, const uint32_t *best_plan,
                            const float *curve_thr, const SlaDev *sla, const FloorsDev *given, const uint32_t *d_jmap,
-                           rk_assign *assign, float *totals, bool static_scratch) {
+                           rk_assign *assign, float *totals, bool static_scratch, const TableGuard *guard) {
     if (n_rounds == 0) return RK_OK;
     Arena arena = {nullptr, 0, 0};
     if (static_scratch) {
@@ -2931,9 +2942,9 @@ int32_t rk_launch_allocate(rk_ctx *ctx, const float *ref_thr, const TableDev &tb
     if (H.width == 0) H.width = 1;
     // Rounds of few jobs take one launch, and none of the walk buffers and histograms.
     const uint32_t lanes0 = few_lanes(max_segs_per_job), lanes1 = few_lanes(grid->n_cpu);
-    const uint32_t holders = one_cluster && !given && one_cluster->G < max_jobs ? one_cluster->G : max_jobs;   // jobs with GPUs
-    const bool few = max_jobs > 0 && max_jobs <= FEW_JOBS && max_segs_per_job <= 64u &&
-                     (uint64_t)max_jobs * lanes0 <= FEW_GPU_LANES && (uint64_t)holders * lanes1 <= FEW_CPU_LANES;
+    const uint32_t holders = few_holders(max_jobs, one_cluster, given != nullptr);
+    const bool few = rk_round_is_few(grid, max_jobs, max_segs_per_job, one_cluster, given != nullptr);
+    if (guard && !few) return rk_fail(ctx, RK_ERR_UNSUPPORTED, "only the one launch of small rounds takes a guard");
     const size_t entries = few ? 0 : (size_t)H.stride * H.width;
     if ((rc = scratch_typed(ctx, arena, SL_HULL_KEY, entries, &H.key))) return rc;
     if ((rc = scratch_typed(ctx, arena, SL_HULL_RAW, entries, &H.raw))) return rc;
@@ -2991,7 +3002,7 @@ int32_t rk_launch_allocate(rk_ctx *ctx, const float *ref_thr, const TableDev &tb
     if (few) {
         const uint32_t jobs = (max_jobs + 3u) & ~3u, gpu = max_jobs * lanes0, cpu = holders * lanes1, near = gpu > cpu ? gpu : cpu;
         const size_t few_lds = FEW_FIXED_BYTES + (size_t)jobs * FEW_JOB_BYTES + (size_t)near * FEW_LANE_BYTES;
-        k_round_few<<<n_rounds, FEW_THREADS, few_lds, s>>>(X, st, max_jobs, lanes0, lanes1, near, assign, totals);
+        k_round_few<<<n_rounds, FEW_THREADS, few_lds, s>>>(X, st, max_jobs, lanes0, lanes1, near, assign, totals, guard ? *guard : TableGuard{});
         RK_CHECK_LAUNCH(ctx, "k_round_few");
         return RK_OK;
     }

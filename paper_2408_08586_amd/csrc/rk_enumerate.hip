@@ -39,7 +39,6 @@ constexpr int ENUM_THREADS = 256;
 constexpr uint32_t MAX_T = RK_MAX_TRIPLES_PER_JOB;
 constexpr uint32_t MAX_DIV = 1024;
 
-enum { TOT_NT_LO = 0, TOT_NT_HI, TOT_NS_LO, TOT_NS_HI, TOT_MAX_T, TOT_MAX_S, TOT_ERR, TOT_DONE, TOT_WORDS };
 enum { ERR_TOO_MANY_TRIPLES = 1, ERR_TOO_MANY_DIVISORS = 2, ERR_PARK_FULL = 4 };
 enum { MODE_COUNT = 0, MODE_FILL_SEARCH = 1 };
 
@@ -610,9 +609,7 @@ __global__ void k_zero_words(uint32_t *p, uint32_t n) {
 
 }  // namespace
 
-extern "C" int32_t rk_enumerate_plans(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_bounds *bounds,
-                                      rk_plan_table *table) {
-    if (!ctx) return RK_ERR_INVALID_ARG;
+int32_t rk_enumerate_begin(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_bounds *bounds, rk_plan_table *table, EnumPending &P) {
     if (!jobs || !bounds || !table) return rk_fail(ctx, RK_ERR_INVALID_ARG, "null argument");
     if (jobs->n_jobs > 0 && (!jobs->layers || !jobs->gbatch || !jobs->mbatch)) return rk_fail(ctx, RK_ERR_INVALID_ARG, "job arrays are null");
     if (bounds->g_max < 1 || bounds->g_max > RK_MAX_G) return rk_fail(ctx, RK_ERR_UNSUPPORTED, "g_max must be in 1..%u", RK_MAX_G);
@@ -729,9 +726,16 @@ extern "C" int32_t rk_enumerate_plans(rk_ctx *ctx, const rk_jobs *jobs, const rk
                                                                      table->cap_segs);
         RK_CHECK_LAUNCH(ctx, "k_fill");
     }
+    P = EnumPending{jobs, *bounds, leader, cnt_t, cnt_s, park, off_t, off_s, totals, park_stride, gmap_bytes, tab_clear, fill, mirrors, share, false};
+    return RK_OK;
+}
+
+int32_t rk_enumerate_end(rk_ctx *ctx, rk_plan_table *table, EnumPending &P) {
+    const uint32_t J = table->n_jobs;
+    const uint32_t *const h = ctx->h_stage;
     RK_HIP(ctx, hipEventSynchronize(ctx->counts_ev));
     ctx->enum_clear = true;                                   // the kernels before the event have run
-    if (share) ctx->enum_tab_clear = tab_clear;
+    if (P.share) ctx->enum_tab_clear = P.tab_clear;
 
     if (h[TOT_ERR] & ERR_TOO_MANY_TRIPLES) return rk_fail(ctx, RK_ERR_UNSUPPORTED, "a job has more than %u triples", MAX_T);
     if (h[TOT_ERR] & ERR_TOO_MANY_DIVISORS) return rk_fail(ctx, RK_ERR_UNSUPPORTED, "a job has more than %u candidate d or p sizes", MAX_DIV);
@@ -742,6 +746,8 @@ extern "C" int32_t rk_enumerate_plans(rk_ctx *ctx, const rk_jobs *jobs, const rk
     table->n_segs = ns;
     table->max_triples_per_job = h[TOT_MAX_T];
     table->max_segs_per_job = h[TOT_MAX_S];
+    ctx->seen_t[1] = ctx->seen_t[0]; ctx->seen_s[1] = ctx->seen_s[0];
+    ctx->seen_t[0] = h[TOT_MAX_T]; ctx->seen_s[0] = h[TOT_MAX_S];
     const bool parked = !(h[TOT_ERR] & ERR_PARK_FULL);
     if (!parked) {                                            // next time the slots will be wide enough
         uint32_t want = h[TOT_MAX_T] + h[TOT_MAX_T] / 4;
@@ -749,19 +755,29 @@ extern "C" int32_t rk_enumerate_plans(rk_ctx *ctx, const rk_jobs *jobs, const rk
         ctx->park_stride = want > MAX_T ? MAX_T : want;
     }
 
-    if (!fill) return RK_OK;
+    P.whole = h[TOT_ERR] == 0u;
+    if (!P.fill) return RK_OK;
     if (table->cap_triples < nt || table->cap_segs < ns)
         return rk_fail(ctx, RK_ERR_CAPACITY, "table too small: need %llu triples and %llu segments",
                        (unsigned long long)nt, (unsigned long long)ns);
-    if (mirrors) {
+    if (P.mirrors) {
         memcpy(table->h_triple_off, h + 16, ((size_t)J + 1) * 4);
         memcpy(table->h_seg_off, h + 16 + J + 1, ((size_t)J + 1) * 4);
     }
     if (J > 0 && !parked) {                                   // the parked keys were incomplete: search again
-        k_enumerate<MODE_FILL_SEARCH><<<J, ENUM_THREADS, gmap_bytes, ctx->stream>>>(
-            jobs->layers, jobs->gbatch, jobs->mbatch, *bounds, leader, cnt_t, cnt_s, park, park_stride,
-            off_t, off_s, table->triples, table->seg_g, table->seg_first, 0u, S);
+        const rk_jobs *const jobs = P.jobs;
+        k_enumerate<MODE_FILL_SEARCH><<<J, ENUM_THREADS, P.gmap_bytes, ctx->stream>>>(
+            jobs->layers, jobs->gbatch, jobs->mbatch, P.bounds, P.leader, P.cnt_t, P.cnt_s, P.park, P.park_stride,
+            P.off_t, P.off_s, table->triples, table->seg_g, table->seg_first, 0u, ScanOut{});
         RK_CHECK_LAUNCH(ctx, "k_enumerate<fill>");
     }
     return RK_OK;
+}
+
+extern "C" int32_t rk_enumerate_plans(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_bounds *bounds,
+                                      rk_plan_table *table) {
+    if (!ctx) return RK_ERR_INVALID_ARG;
+    EnumPending P;
+    const int32_t rc = rk_enumerate_begin(ctx, jobs, bounds, table, P);
+    return rc ? rc : rk_enumerate_end(ctx, table, P);
 }

@@ -66,7 +66,9 @@ __global__ __launch_bounds__(THREADS) void k_fused(JobDev jobs, TableDev tb, Gri
                                                          uint32_t c_per_block, uint32_t c_per_pass, uint32_t m_per_pass,
                                                          float *__restrict__ best_thr, uint32_t *__restrict__ best_plan,
                                                          float *__restrict__ curve_thr, uint32_t *__restrict__ curve_plan,
-                                                         uint32_t *__restrict__ curve_g) {
+                                                         uint32_t *__restrict__ curve_g,
+                                                    TableGuard guard) {
+    if (!table_usable(guard)) return;
     extern __shared__ unsigned long long lds64[];
     uint32_t &n_packed = *reinterpret_cast<uint32_t *>(lds64);               // triples packed so far
     unsigned long long *seg_plain = lds64 + 1;                               // [max_ns]
@@ -287,7 +289,7 @@ __global__ __launch_bounds__(THREADS) void k_fused(JobDev jobs, TableDev tb, Gri
 
 int32_t rk_launch_fused(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_table *table, const rk_alloc_grid *grid,
                         const rk_env *env, uint32_t jb, uint32_t je, float *best_thr, uint32_t *best_plan,
-                        float *curve_thr, uint32_t *curve_plan, uint32_t *curve_g) {
+                        float *curve_thr, uint32_t *curve_plan, uint32_t *curve_g, const TableGuard *guard) {
     if (je == jb) return RK_OK;
     FusedLds L;
     L.max_nt = table->max_triples_per_job ? table->max_triples_per_job : 1;
@@ -324,7 +326,7 @@ int32_t rk_launch_fused(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_table *t
     auto *kernel = direct ? k_fused<64, true> : k_fused<FEW_JOBS, false>;
     kernel<<<blocks, direct ? 64 : FEW_JOBS, lds, ctx->stream>>>(job_dev(jobs), table_dev(table), grid_dev(grid), *env, jb,
                                                                      table->option_mask, L, c_per_block, c_per_pass, m_per_pass,
-                                                                     best_thr, best_plan, curve_thr, curve_plan, curve_g);
+                                                                     best_thr, best_plan, curve_thr, curve_plan, curve_g, guard ? *guard : TableGuard{});
     RK_CHECK_LAUNCH(ctx, "k_fused");
     return RK_OK;
 }

@@ -21,6 +21,7 @@ struct rk_ctx {
     uint32_t *h_stage;                      // pinned staging for the plan-table offsets, grown on demand
     size_t h_stage_words;
     uint32_t park_stride;                   // enumeration: words per job between its two passes
+    uint32_t seen_t[2], seen_s[2];          // ... most triples and segments of a job in the last two calls (0: none)
     bool enum_clear;                        // enumeration: the device's counter of finished searches is known to be zero
     size_t enum_tab_clear;                  // ... and so many words of the leaders' table
     hipEvent_t counts_ev;                   // enumeration: the counts have reached the host (made on demand)
@@ -103,6 +104,38 @@ static inline TableDev table_dev(const rk_plan_table *t) {
     return TableDev{t->triple_off, t->triples, t->seg_off, t->seg_g, t->seg_first};
 }
 
+// Where the enumeration leaves what the scan of the counts found, on the device and for the host.
+enum { TOT_NT_LO = 0, TOT_NT_HI, TOT_NS_LO, TOT_NS_HI, TOT_MAX_T, TOT_MAX_S, TOT_ERR, TOT_DONE, TOT_WORDS };
+
+// Kernels that are launched behind an enumeration before the host has seen its totals: the sizes they are prepared for.
+// A table that is beyond them (or none, after an error) is left alone.
+struct TableGuard {
+    const uint32_t *totals;     // null: the table is known
+    uint64_t cap_triples, cap_segs;
+    uint32_t most_t, most_s;    // triples and segments of a job
+};
+__device__ __forceinline__ bool table_usable(const TableGuard &G) {
+    if (!G.totals) return true;
+    const uint32_t *const T = G.totals;
+    const uint64_t nt = ((uint64_t)T[TOT_NT_HI] << 32) | T[TOT_NT_LO], ns = ((uint64_t)T[TOT_NS_HI] << 32) | T[TOT_NS_LO];
+    return T[TOT_ERR] == 0u && nt <= G.cap_triples && ns <= G.cap_segs && T[TOT_MAX_T] <= G.most_t && T[TOT_MAX_S] <= G.most_s;
+}
+
+// An enumeration in two halves: what goes out to the device, and, when its counts have come back, what the host makes of
+// them.  rk_enumerate_plans is one after the other; nothing of the context's enumeration may come between them but
+// launches that a TableGuard protects.
+struct EnumPending {
+    const rk_jobs *jobs;
+    rk_plan_bounds bounds;
+    uint32_t *leader, *cnt_t, *cnt_s, *park, *off_t, *off_s, *totals;
+    uint32_t park_stride;
+    size_t gmap_bytes, tab_clear;
+    bool fill, mirrors, share;
+    bool whole;                 // set by the second half: no job's search has to be repeated
+};
+int32_t rk_enumerate_begin(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_bounds *bounds, rk_plan_table *table, EnumPending &P);
+int32_t rk_enumerate_end(rk_ctx *ctx, rk_plan_table *table, EnumPending &P);
+
 // service-level inputs of the allocation; min_seg / min_c are indexed from the call's first job
 struct SlaDev {
     const uint32_t *guaranteed, *tenant;
@@ -128,7 +161,7 @@ struct FloorsDev {
 int32_t rk_launch_fused(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_table *table,
                         const rk_alloc_grid *grid, const rk_env *env, uint32_t jb, uint32_t je,
                         float *best_thr, uint32_t *best_plan, float *curve_thr, uint32_t *curve_plan,
-                        uint32_t *curve_g);
+                        uint32_t *curve_g, const TableGuard *guard = nullptr);
 // one_cluster != NULL: a single round over [jb, jb + n_jobs) with that cluster, carried in the
 // kernel arguments; otherwise n_rounds rounds described by the device arrays.
 // sla != NULL: service-level floors first (the quotas apply to every round alike);
@@ -140,7 +173,9 @@ int32_t rk_launch_allocate(rk_ctx *ctx, const float *ref_thr, const TableDev &tb
                            const rk_cluster *one_cluster, uint32_t jb, uint32_t n_jobs, uint32_t max_jobs,
                            uint32_t max_segs_per_job, const float *best_thr, const uint32_t *best_plan,
                            const float *curve_thr, const SlaDev *sla, const FloorsDev *given, const uint32_t *d_jmap,
-                           rk_assign *assign, float *totals, bool static_scratch = false);
+                           rk_assign *assign, float *totals, bool static_scratch = false, const TableGuard *guard = nullptr);
+// Whether a single round takes the one launch of small rounds (only that one takes a guard).
+bool rk_round_is_few(const rk_alloc_grid *grid, uint32_t max_jobs, uint32_t max_segs_per_job, const rk_cluster *one_cluster, bool given);
 // static_scratch: the working buffers are pieces of the library's static device array (nothing is allocated; a
 // round that needs more than the array holds is refused) instead of the context's grow-only buffers.
 // Once per context, device current: finds this device's copy of that array and raises the LDS limits of the

@@ -161,3 +161,45 @@ def test_equal_jobs_are_found_again_in_later_calls(orc):
         assert np.array_equal(rk.u32(t.seg_off), ot.seg_off) and np.array_equal(rk.u32(t.seg_g)[:t.n_segs], ot.seg_g)
         assert np.array_equal(rk.u32(t.triple_off), ot.triple_off)
     rk.rk_destroy(ctx)
+
+
+def test_small_rounds_sent_before_their_table_is_known():
+    """Rounds on one context whose tables resemble the last two, are larger, smaller, wider than the parked words, in error
+    and of the first kind again: every one is what a fresh context makes of it, and a round in error leaves its records
+    alone."""
+    import torch
+    import paper_2408_08586_amd as rk
+    ctx = rk.rk_create(0)
+    base = workloads.tiny()
+    small, wide, wider = np.array([[12, 32, 1]], np.uint32), np.array([[96, 128, 1]], np.uint32), np.array([[96, 1680, 1]], np.uint32)
+    bad = np.array([[4095, 720720, 1]], np.uint32)
+    plan = [(small, 64)] * 4 + [(wide, 64)] * 3 + [(small, 64)] * 3 + [(wider, 256), (wider, 256), (small, 64), (small, 64), (small, 64),
+                                                                       (bad, 65535), (small, 64), (small, 16), (small, 16), (small, 64)]
+    for i, (kind, g_max) in enumerate(plan):
+        n_jobs = (20, 33, 7, 64)[i % 4]
+        rng = np.random.default_rng(i)
+        coef = base.coef[rng.integers(0, base.n_jobs, n_jobs)]
+        ints = np.repeat(kind, n_jobs, axis=0)
+        wl = workloads.Workload("seq", coef, ints, workloads.Bounds(g_max=g_max), base.grid, base.env,
+                                workloads.Cluster(3 * n_jobs, 12 * n_jobs, 1e4))
+        def on(c):
+            assign, total = rk.new_assign(n_jobs, "cuda:0"), torch.full((1,), -1.0, device="cuda:0")
+            assign.fill_(77)
+            try:
+                rk.rk_schedule_round(c, rk.Jobs(coef, ints, "cuda:0"), rk.make_bounds(wl.bounds), rk.make_grid(wl.grid),
+                                     rk.make_env(wl.env), rk.make_cluster(wl.cluster), assign, total)
+                code = 0
+            except rk.RkError as e:
+                code = e.code
+            rk.rk_sync(c)
+            return code, assign.cpu().numpy().copy(), float(total[0])
+        got = on(ctx)
+        fresh = rk.rk_create(0)
+        want = on(fresh)                                       # (a context that has seen no table sends nothing ahead)
+        rk.rk_destroy(fresh)
+        assert got[0] == want[0] and np.array_equal(got[1], want[1]) and got[2] == want[2], i
+        if kind is bad:
+            assert got[0] == rk.RK_ERR_UNSUPPORTED and (got[1] == 77).all() and got[2] == -1.0
+        else:
+            assert got[0] == 0 and got[2] > 0
+    rk.rk_destroy(ctx)
