@@ -121,10 +121,17 @@ def test_thresholds_of_many_jobs(orc, n_jobs, spread):
     coef = np.tile(base.coef[:1], (n_jobs, 1))
     coef[:, 16] = (2.0 ** np.round(rng.normal(0.0, 4.0 * spread, n_jobs))).astype(np.float32)
     grid = workloads.Grid(np.array([1, 2, 4], np.uint32), 1, np.array([64.0], np.float32), 0)
-    wl = workloads.Workload("many", coef, np.tile(np.array([[12, 32, 1]], np.uint32), (n_jobs, 1)), workloads.Bounds(g_max=32), grid,
+    wl = workloads.Workload("many", coef, np.tile(np.array([[96, 128, 1]], np.uint32), (n_jobs, 1)), workloads.Bounds(g_max=64), grid,
                             workloads.Env(), workloads.Cluster(8, 8, 64.0))
     ot = orc.enumerate_plans(wl.ints, wl.bounds)
     bt, bp, ct = drawn_curves(orc, wl, ot, rng)
+    # half of the jobs gain from every amount, less and less: walks as long as their lists (12 steps)
+    n_rows = len(grid.cpu_levels)
+    whole = int(ot.seg_off[n_jobs // 2])
+    g_of = np.concatenate([np.tile(ot.seg_g[ot.seg_off[j]:ot.seg_off[j + 1]], n_rows) for j in range(n_jobs // 2)])
+    bt[:whole * n_rows] = (np.sqrt(g_of) * 4).astype(np.float32)
+    bp[:whole * n_rows] = 1
+    ct = orc.curves(ot, wl.grid, bt, bp)[0]
     run = DeviceRun(wl)
     run.enumerate()
     d_bt, d_bp, d_ct = run.dev_f32(bt), run.dev_u32(bp), run.dev_f32(ct)
