@@ -30,11 +30,14 @@ constexpr uint32_t FEAS_DIRECT_ROWS = 9;
 // STREAM: the throughputs leave by streaming stores.  A tensor that outgrows the caches only drives what is in them out,
 // and the lines it leaves there are still on their way to memory when the next kernel starts.  One that the caches hold
 // is read back from them, or written over there by the next call, which streaming stores give up.  The lines lie at the
-// tensor's size.  k_eval, then k_best_plan on what it wrote (35 MB is about what the L2 caches hold): 35 MB 33.8 us with
-// plain and 35.2 with streaming stores, 53 MB 36.9 and 37.4, 70 MB 41.5 and 40.0, 105 MB 58.5 and 57.2, 210 MB 96.5 and
-// 89.7, 350 MB 148.6 and 134.7.  k_eval_best, which nothing reads after (the memory-side cache holds 256 MB): 135 MB
+// tensor's size.  k_eval with reason bytes, then k_best_plan on what it wrote (35 MB is about what the L2 caches hold):
+// 35 MB 33.8 us with plain and 35.2 with streaming stores, 53 MB 36.9 and 37.4, 70 MB 41.5 and 40.0, 105 MB 58.5 and
+// 57.2, 210 MB 96.5 and 89.7, 350 MB 148.6 and 134.7; the reason bytes keep plain stores: streamed as well, 350 MB take
+// 164 us instead of 135.  Without reason bytes k_eval alone is near a plain fill and what streaming takes from it is more
+// than k_best_plan gains: 227 MB 89.3 us with plain and 93.3 with streaming stores, 341 MB 127.5 and 131.8, 681 MB 232
+// and 249, 909 MB 315 and 328.  k_eval_best, which nothing reads after (the memory-side cache holds 256 MB): 135 MB
 // 123.6 and 126.0 us for the whole step, 270 MB 134.5 and 143.3, 350 MB 209.9 and 205.8, 540 MB 238.9 and 226.8, 900 MB
-// 390.0 and 363.4.  The reason bytes keep plain stores: streamed as well, 350 MB take 164 us instead of 135.
+// 390.0 and 363.4.
 constexpr uint64_t EVAL_STREAM_BYTES = 64ull << 20, EVAL_BEST_STREAM_BYTES = 320ull << 20;
 template <bool STREAM>
 __device__ __forceinline__ void store_thr(float *to, const v4f &v) {
@@ -570,8 +573,7 @@ int32_t rk_eval_candidates(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_table
     const JobDev jd = job_dev(jobs);
     const TableDev td = table_dev(table);
     const GridDev gd = grid_dev(grid);
-    const bool stream = need * 4 > EVAL_STREAM_BYTES;
-    auto *kernel = feas ? (stream ? k_eval<true, true> : k_eval<true, false>) : (stream ? k_eval<false, true> : k_eval<false, false>);
+    auto *kernel = !feas ? k_eval<false, false> : need * 4 > EVAL_STREAM_BYTES ? k_eval<true, true> : k_eval<true, false>;
     kernel<<<g3, EVAL_THREADS, feas ? grid->n_mem * EVAL_THREADS * 4 : 0, ctx->stream>>>(jd, td, gd, *env, jb, table->option_mask,
                                                                                     c_per_block, thr, feas);
     RK_CHECK_LAUNCH(ctx, "k_eval");
