@@ -28,14 +28,14 @@ HBM_PEAK_GBS = 8000.0
 KERNEL_SOURCES = ("paper_2408_08586_amd/csrc/rk_eval.hip", "paper_2408_08586_amd/csrc/rk_model.h")
 MEASURED_TRAFFIC = {
     # digest: {kernel: bytes per launch}
-    "1423354867608e90": {"k_eval_best": 946947057, "k_eval": 919033525, "k_best_plan": 932066203},
+    "41ef5ae9c6b20739": {"k_eval_best": 951096173, "k_eval": 919058272, "k_best_plan": 932082219},
 }
 
 
 # Vector-ALU instructions per launch of the fused kernel on the stress workload (rocprofv3 --pmc SQ_INSTS_VALU,
 # profiles/valu_stress.txt: wavefront instructions, 64 lanes each), keyed by the digest of its sources.
 FUSED_SOURCES = ("paper_2408_08586_amd/csrc/rk_fused.hip", "paper_2408_08586_amd/csrc/rk_model.h")
-MEASURED_FUSED_VALU = {"96841afc7d46df23": 28481029}
+MEASURED_FUSED_VALU = {"f8e6e35c8871e32b": 28481029}
 # 256 compute units x 4 SIMDs x 16 lanes x 2.4 GHz: vector instructions per lane and second (an FMA is one of them,
 # so this is half of the 78.6 TFLOP/s of unpacked FP32 and a quarter of the 157.3 TFLOP/s with packed FP32)
 VALU_PEAK_LANE_INSTR = 256 * 4 * 16 * 2.4e9

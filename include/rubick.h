@@ -574,10 +574,11 @@ typedef struct {
  *   - a job holding GPUs pays owed seconds out of the tick, then trains at the
  *     round's throughput; it finishes inside the tick at t + paid + remaining/thr.
  * Times and progress are float64.  Runs in order with the work on the context's
- * stream (policies 1 and 2, and policy 0 with more than about 1,000 jobs, on a
- * stream of its own: the first tick eagerly, the others as replays of one
- * captured HIP graph); with more than one tick the call returns when the
- * simulation has finished. */
+ * stream: policy 0 with up to about 1,000 jobs and policy 2 while nodes and jobs
+ * fit the LDS of one compute unit (about 1,300 jobs) run many ticks per launch;
+ * the others use a stream of their own, the first tick eagerly and the rest as
+ * replays of one captured HIP graph.  With more than one tick the call returns
+ * when the simulation has finished. */
 int32_t rk_simulate(rk_ctx *ctx, const float *ref_thr, const rk_plan_table *table,
                     const rk_alloc_grid *grid, const rk_cluster *cluster,
                     const float *best_thr, const uint32_t *best_plan, const float *curve_thr,
