@@ -574,11 +574,14 @@ typedef struct {
  *   - a job holding GPUs pays owed seconds out of the tick, then trains at the
  *     round's throughput; it finishes inside the tick at t + paid + remaining/thr.
  * Times and progress are float64.  Runs in order with the work on the context's
- * stream: policy 0 with up to about 1,000 jobs and policy 2 while nodes and jobs
- * fit the LDS of one compute unit (about 1,300 jobs) run many ticks per launch;
- * the others use a stream of their own, the first tick eagerly and the rest as
- * replays of one captured HIP graph.  With more than one tick the call returns
- * when the simulation has finished. */
+ * stream.  Policy 0 has rounds for few jobs (256, or 128 / 64 where a job has
+ * more than 16 / 32 GPU counts) in one workgroup, many ticks per launch; a
+ * simulation of up to 1,024 jobs of at most 64 GPU counts has the others as
+ * launches in between.  Policy 2 runs many ticks per launch while nodes and jobs
+ * fit the LDS of one compute unit (about 1,300 jobs).  Everything else, and the
+ * ticks in between, are on a stream of the simulation's own, the first tick
+ * eagerly and the rest as replays of one captured HIP graph.  With more than one
+ * tick the call returns when the simulation has finished. */
 int32_t rk_simulate(rk_ctx *ctx, const float *ref_thr, const rk_plan_table *table,
                     const rk_alloc_grid *grid, const rk_cluster *cluster,
                     const float *best_thr, const uint32_t *best_plan, const float *curve_thr,

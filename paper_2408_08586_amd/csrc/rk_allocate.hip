@@ -1527,14 +1527,15 @@ constexpr int FEW_THREADS = 1024, FEW_WAVES = FEW_THREADS / 64;
 constexpr uint32_t FEW_JOBS = FEW_THREADS;        // at most a job per thread
 constexpr uint32_t FEW_GPU_LANES = 2048, FEW_CPU_LANES = 4096;   // of a round: jobs times lanes of a job
 constexpr uint32_t FEW_BINS = 1024, FEW_FINE = 128;
-constexpr uint32_t FEW_SIM_LANES = 16384;         // of a simulation (most of its jobs have come and gone, or are yet to come)
+constexpr uint32_t FEW_TICK_LANES = 4096;         // of a tick of a simulation (k_sim_few): jobs that take part times lanes of a job
+constexpr uint32_t FEW_TICK_WALK = 64;            // ... steps over CPU levels that a wavefront walks, one job or group of jobs after the other
 constexpr size_t FEW_SIM_LDS = 152 * 1024;
 
 struct FewMem {                  // per round, in LDS
     unsigned long long *hc;      // histogram of a pass: CPUs and GPUs of the steps per bin
     uint32_t *hg;
     uint32_t *lvl;               // CPU levels
-    uint32_t *range;             // highest and lowest key of the pass's walks
+    uint32_t *range;             // highest and lowest key of the pass's walks; most steps that a wavefront walked
     // per job of the round: where its segments are, its reference throughput, what it holds
     uint32_t *s0, *ns;
     float *ref;
@@ -1649,7 +1650,7 @@ __device__ __forceinline__ uint32_t few_bin_at(uint32_t b) { return (b % (FEW_BI
 
 __device__ __forceinline__ void few_clear(const FewMem &M) {
     for (uint32_t i = threadIdx.x; i < FEW_BINS; i += FEW_THREADS) { M.hg[i] = 0u; M.hc[i] = 0ull; }
-    if (threadIdx.x == 0) { M.range[0] = 0u; M.range[1] = 0xFFFFFFFFu; }
+    if (threadIdx.x == 0) { M.range[0] = 0u; M.range[1] = 0xFFFFFFFFu; M.range[2] = 0u; }
 }
 
 // One wavefront: the first bin (bin 0 holds the highest keys) whose steps, with everything before it, no longer fit
@@ -1696,7 +1697,7 @@ __device__ __forceinline__ void few_pass(const Ctx &X, const FewMem &M, const Fe
     static_assert(FEW_JOBS <= FEW_THREADS, "a job per thread");
 
     // the walks (k_hull_groups).  Costs by their low words: a step within the capacity fits a word.
-    uint32_t high = 0, low = 0xFFFFFFFFu;
+    uint32_t high = 0, low = 0xFFFFFFFFu, walked = 0;
     for (uint32_t p0 = wave * per; p0 < P; p0 += FEW_WAVES * per) {
         const bool valid = p0 + mine < P;
         const uint32_t p = valid ? p0 + mine : P - 1u, j = M.part[p];
@@ -1732,6 +1733,7 @@ __device__ __forceinline__ void few_pass(const Ctx &X, const FewMem &M, const Fe
         float prev = __uint_as_float(0x7F800000u);
         bool walking = valid;
         while (__ballot(walking)) {
+            if (PASS == 1) ++walked;
             uint32_t best = 0;
             if (walking && can && (int32_t)sub > cur_i && v > cur) {
                 float sl = (v - cur) / ref;
@@ -1777,6 +1779,7 @@ __device__ __forceinline__ void few_pass(const Ctx &X, const FewMem &M, const Fe
     high = wave_max_u32_rows(high);
     low = wave_min_u32_rows(low);
     if (lane == 0 && high) { atomicMax(&M.range[0], high); atomicMin(&M.range[1], low); }
+    if (PASS == 1 && lane == 0) atomicMax(&M.range[2], walked);
     __syncthreads();
     // The threshold: steps whose key lies less than `limit` below the highest one.  Any threshold whose whole set of steps
     // fits selects a prefix of the order: FEW_BINS bins over the keys that occur, and what is left of the bin where the
@@ -2025,14 +2028,27 @@ __device__ __forceinline__ void few_pass_anywhere(const Ctx &X, const FewMem &M,
     else few_pass<PASS>(X, M, few_lane_mem(far, n_far), P, lanes, first_seg, freeG, freeC);
 }
 
-// Ticks [tick, end) of a simulation of at most FEW_JOBS jobs under the greedy, in one workgroup: what a job does between
+// Ticks of a simulation of at most FEW_JOBS jobs under the greedy, in one workgroup: what a job does between
 // the ticks stays in its thread's registers, a round is k_round_few's.  A tick that starts from what the last round started
 // from has that round's result.  As launches of their own (the round's four kernels and k_sim_step, replayed as a graph)
 // a tick with a round took 40 us, most of it launches and what one kernel leaves for the next in memory: 406 jobs on 64
-// GPUs, 720 ticks 19.3 ms then, 10.1 now; 30 jobs 8.2 us per tick and 2.7.  Every job queued at once is its longest: up to
-// 1,000 jobs on 64 GPUs, 300 ticks, 10.6 and 9.5 ms, on 512 GPUs 12.6 and 12.3, which is where FEW_SIM_LANES ends it.
+// GPUs, 720 ticks 19.2 ms then, 9.4 now; 30 jobs 8.2 us per tick and 2.7.
+// The walks of a round for many jobs keep one workgroup busy for longer than that: such a tick, and every one after it, is
+// left to the launches until the rounds are for fewer jobs again.  So are the ticks after one that walked long over the CPU
+// levels, for a while (as many lanes cost 4 us where curves are flat there, as the model's mostly are, and 100 where every
+// level gains).  FEW_TICK_LANES and FEW_TICK_WALK are where that pays: us per tick as launches, and in this kernel alone
+// whatever the round is for, on curves that gain at every amount and every CPU level, with one GPU for eight jobs, one and
+// eight GPUs per job, at 5 and at 64 CPU levels:
+//     4,096 lanes   256 jobs of 16   31 and 20, 56 and 40, 56 and 25    36 and 21, 97 and 79, 122 and 87
+//                   128 jobs of 32   17 and 9, 41 and 25, 72 and 34     20 and 11, 48 and 34, 131 and 62
+//                   64 jobs of 64    18 and 7, 43 and 30, 71 and 32     20 and 7, 55 and 34, 127 and 53
+//     8,192 lanes   512 jobs of 16   44 and 60, 62 and 68, 57 and 30    51 and 60, 124 and 153, 129 and 150
+//                   256 jobs of 32   28 and 32, 57 and 81, 82 and 49    37 and 37, 93 and 118, 141 and 102
+//                   128 jobs of 64   17 and 15, 43 and 41, 81 and 47    21 and 16, 51 and 49, 132 and 77
+//     16,000 lanes  1,000 jobs of 16 58 and 132, 67 and 115, 63 and 48  62 and 145, 135 and 311, 145 and 286
+// With both lines every one of these takes what the faster way takes, give or take 4 %; 406 jobs on 64 GPUs keep 9.4 ms.
 // first: the simulation begins with this launch; otherwise the state is where the launch before left it.
-__global__ __launch_bounds__(FEW_THREADS) void k_sim_few(Ctx X, SimArgs A, uint32_t tick, uint32_t end, uint32_t first, uint32_t lanes0,
+__global__ __launch_bounds__(FEW_THREADS) void k_sim_few(Ctx X, SimArgs A, uint32_t first, uint32_t go_on, uint32_t most, uint32_t lanes0,
                                                          uint32_t lanes1, uint32_t near, uint32_t *far, uint32_t n_far,
                                                          rk_assign *__restrict__ assign, float *__restrict__ tick_total) {
     extern __shared__ __align__(16) unsigned long long lds_few[];
@@ -2040,6 +2056,9 @@ __global__ __launch_bounds__(FEW_THREADS) void k_sim_few(Ctx X, SimArgs A, uint3
     __shared__ unsigned long long frozen_c[2];
     __shared__ uint32_t frozen_g[2], frozen_n[2], used_g[2];   // of a tick, in two copies used in turn
     const uint32_t tid = threadIdx.x, J = A.n_jobs, first_seg = X.tb.seg_off[0];
+    uint32_t tick = first ? 0u : A.tick[0];
+    if (tick >= A.n_ticks || (go_on && A.tick[1])) return;     // (the simulation is over; the launch before was stopped)
+    const uint32_t end = A.n_ticks - tick > SIM_FEW_TICKS ? tick + SIM_FEW_TICKS : A.n_ticks;
     uint32_t *lds_lanes;
     const FewMem M = few_mem(lds_few, J, &lds_lanes);
     few_jobs(X, M, 0u, J);
@@ -2060,8 +2079,9 @@ __global__ __launch_bounds__(FEW_THREADS) void k_sim_few(Ctx X, SimArgs A, uint3
     Floor fl = {-1, 0u, RK_JOB_OUT};
     rk_assign a = {0u, 0u, 0.f, RK_NO_PLAN, 0.f};
     float total = 0.f;
+    bool stop = false;
     __syncthreads();
-    for (bool known = false; tick < end; ++tick, known = true) {
+    for (bool known = false; tick < end && !stop; ++tick, known = true) {
         const double t = (double)tick * A.dt;
         const uint32_t half = tick & 1u;
         // opens the tick: who takes part, who is frozen and what they hold
@@ -2088,12 +2108,15 @@ __global__ __launch_bounds__(FEW_THREADS) void k_sim_few(Ctx X, SimArgs A, uint3
             }
             few_clear(M);
             uint32_t P = few_compact(M, J, [&](uint32_t) { return fl.state == RK_JOB_NORMAL && freeG != 0; });
+            stop = P > most;
+            if (stop) break;                                   // (nothing of this tick is in the state yet)
             if (P) few_pass_anywhere<0>(X, M, lds_lanes, near, far, n_far, P, lanes0, first_seg, freeG, freeC);
             few_clear(M);
             P = few_compact(M, J, [&](uint32_t j) { return fl.state == RK_JOB_NORMAL && M.gi[j] >= 0 && freeC != 0; });
             if (P) few_pass_anywhere<1>(X, M, lds_lanes, near, far, n_far, P, lanes1, first_seg, freeG, freeC);
             a = few_memory(X, M, 0u, J, first_seg, sums, assign, tick_total);
             __syncthreads();                                   // the round is closed
+            stop = M.range[2] > FEW_TICK_WALK;                 // (the next one is as long, as a rule)
             if (M.box[0] && mine) a = assign[tid];             // ... by decisions in job order
             if (tid == 0) total = *tick_total;                 // (its own store)
         }
@@ -2118,6 +2141,13 @@ __global__ __launch_bounds__(FEW_THREADS) void k_sim_few(Ctx X, SimArgs A, uint3
         A.S.g[tid] = s.g; A.S.c[tid] = s.c; A.S.plan[tid] = s.plan; A.S.seg[tid] = seg; A.S.lvl[tid] = lvl;
         A.S.owed[tid] = s.owed; A.S.done[tid] = s.done ? 1 : 0;
         A.held[tid] = s.held; A.progress[tid] = s.progress; A.finish[tid] = s.finish; A.n_reconf[tid] = s.n_reconf;
+    }
+    if (tid == 0) {
+        A.tick[0] = tick; A.tick[1] = stop ? 1u : 0u;
+        if (A.h_tick) {
+            __hip_atomic_store(A.h_tick + 1, M.range[2] > FEW_TICK_WALK ? SIM_LONG_WALK : 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            __hip_atomic_store(A.h_tick, tick, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
     }
 }
 
@@ -2980,13 +3010,13 @@ int32_t rk_allocate_setup(rk_ctx *ctx) {
 }
 
 // jobs of a round that may hold GPUs
-static uint32_t few_holders(uint32_t max_jobs, const rk_cluster *one_cluster, bool given) {
-    return one_cluster && !given && one_cluster->G < max_jobs ? one_cluster->G : max_jobs;
+static uint32_t few_holders(uint32_t max_jobs, const rk_cluster *one_cluster) {
+    return one_cluster && one_cluster->G < max_jobs ? one_cluster->G : max_jobs;
 }
-bool rk_round_is_few(const rk_alloc_grid *grid, uint32_t max_jobs, uint32_t max_segs_per_job, const rk_cluster *one_cluster, bool given) {
+bool rk_round_is_few(const rk_alloc_grid *grid, uint32_t max_jobs, uint32_t max_segs_per_job, const rk_cluster *one_cluster) {
     return max_jobs > 0 && max_jobs <= FEW_JOBS && max_segs_per_job <= 64u &&
            (uint64_t)max_jobs * few_lanes(max_segs_per_job) <= FEW_GPU_LANES &&
-           (uint64_t)few_holders(max_jobs, one_cluster, given) * few_lanes(grid->n_cpu) <= FEW_CPU_LANES;
+           (uint64_t)few_holders(max_jobs, one_cluster) * few_lanes(grid->n_cpu) <= FEW_CPU_LANES;
 }
 
 int32_t rk_launch_allocate(rk_ctx *ctx, const float *ref_thr, const TableDev &tb, const rk_alloc_grid *grid,
@@ -3013,8 +3043,9 @@ int32_t rk_launch_allocate(rk_ctx *ctx, const float *ref_thr, const TableDev &tb
     if (H.width == 0) H.width = 1;
     // Rounds of few jobs take one launch, and none of the walk buffers and histograms.
     const uint32_t lanes0 = few_lanes(max_segs_per_job), lanes1 = few_lanes(grid->n_cpu);
-    const uint32_t holders = few_holders(max_jobs, one_cluster, given != nullptr);
-    const bool few = rk_round_is_few(grid, max_jobs, max_segs_per_job, one_cluster, given != nullptr);
+    const uint32_t holders = few_holders(max_jobs, one_cluster);
+    // (a simulation's tick that one workgroup takes well does not come here: k_sim_few)
+    const bool few = !given && rk_round_is_few(grid, max_jobs, max_segs_per_job, one_cluster);
     if (guard && !few) return rk_fail(ctx, RK_ERR_UNSUPPORTED, "only the one launch of small rounds takes a guard");
     const size_t entries = few ? 0 : (size_t)H.stride * H.width;
     if ((rc = scratch_typed(ctx, arena, SL_HULL_KEY, entries, &H.key))) return rc;
@@ -3092,27 +3123,34 @@ int32_t rk_launch_allocate(rk_ctx *ctx, const float *ref_thr, const TableDev &tb
     return RK_OK;
 }
 
+SimFew rk_sim_few(uint32_t n_jobs, uint32_t max_segs_per_job, const rk_alloc_grid *grid, const rk_cluster *cluster, uint32_t *most) {
+    *most = 0;
+    if (n_jobs > FEW_JOBS || max_segs_per_job > 64u) return SIM_NOT_FEW;
+    *most = FEW_TICK_LANES / few_lanes(max_segs_per_job);
+    const uint32_t holders = cluster->G < n_jobs ? cluster->G : n_jobs, lanes = few_lanes(grid->n_cpu);
+    const uint32_t turns = (holders * lanes + FEW_THREADS - 1u) / FEW_THREADS;
+    return n_jobs <= *most && turns * grid->n_cpu <= FEW_TICK_WALK ? SIM_ALWAYS_FEW : SIM_OFTEN_FEW;
+}
+
 int32_t rk_launch_sim_few(rk_ctx *ctx, const SimArgs &A, const float *ref_thr, const rk_alloc_grid *grid, uint32_t max_segs_per_job,
-                          const float *best_thr, const uint32_t *best_plan, const float *curve_thr, rk_assign *assign, bool *taken) {
+                          const float *best_thr, const uint32_t *best_plan, const float *curve_thr, rk_assign *assign,
+                          uint32_t n_launches, bool begin, uint32_t most) {
     const uint32_t J = A.n_jobs, lanes0 = few_lanes(max_segs_per_job), lanes1 = few_lanes(grid->n_cpu);
-    *taken = J <= FEW_JOBS && max_segs_per_job <= 64u && J * lanes0 <= FEW_SIM_LANES;
-    if (!*taken) return RK_OK;
     Ctx X;
     X.ref_thr = ref_thr; X.tb = A.tb; X.grid = A.grid; X.jb = 0; X.jmap = nullptr;
     X.best_thr = best_thr; X.best_plan = best_plan; X.curve_thr = curve_thr;
     X.R = RoundArgs{nullptr, nullptr, 1u, 1u, 0u, J, A.cl};
-    const uint32_t holders = A.cl.G < J ? A.cl.G : J, gpu = J * lanes0, cpu = holders * lanes1, most = gpu > cpu ? gpu : cpu;
+    const uint32_t part = J < most ? J : most, holders = A.cl.G < part ? A.cl.G : part, gpu = part * lanes0, cpu = holders * lanes1;
+    const uint32_t need = gpu > cpu ? gpu : cpu;
     const size_t job_lds = FEW_FIXED_BYTES + (size_t)((J + 3u) & ~3u) * FEW_JOB_BYTES;
-    const uint32_t room = (uint32_t)((FEW_SIM_LDS - job_lds) / FEW_LANE_BYTES) & ~63u, near = most < room ? most : room;
+    const uint32_t room = (uint32_t)((FEW_SIM_LDS - job_lds) / FEW_LANE_BYTES) & ~63u, near = need < room ? need : room;
     uint32_t *far = nullptr;
     int32_t rc;
-    if (most > near && (rc = rk_scratch(ctx, SL_HULL_KEY, (size_t)most * FEW_LANE_BYTES, (void **)&far))) return rc;
-    for (uint32_t t = 0; t < A.n_ticks;) {
-        const uint32_t end = A.n_ticks - t > SIM_FEW_TICKS ? t + SIM_FEW_TICKS : A.n_ticks;
-        k_sim_few<<<1, FEW_THREADS, job_lds + (size_t)near * FEW_LANE_BYTES, ctx->stream>>>(X, A, t, end, t == 0 ? 1u : 0u, lanes0, lanes1,
-                                                                                         near, far, most, assign, A.tick_total);
+    if (need > near && (rc = rk_scratch(ctx, SL_HULL_KEY, (size_t)need * FEW_LANE_BYTES, (void **)&far))) return rc;
+    for (uint32_t i = 0; i < n_launches; ++i) {
+        k_sim_few<<<1, FEW_THREADS, job_lds + (size_t)near * FEW_LANE_BYTES, ctx->stream>>>(X, A, begin && i == 0 ? 1u : 0u, i ? 1u : 0u, most, lanes0,
+                                                                                         lanes1, near, far, need, assign, A.tick_total);
         RK_CHECK_LAUNCH(ctx, "k_sim_few");
-        t = end;
     }
     return RK_OK;
 }

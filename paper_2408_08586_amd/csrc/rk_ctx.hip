@@ -139,6 +139,11 @@ int32_t rk_sync(rk_ctx *ctx) {
     return RK_OK;
 }
 
+int32_t rk_ctx_ways(const rk_ctx *ctx, uint32_t *ways) {
+    for (int i = 0; i < WAY_COUNT; ++i) ways[i] = ctx->ways[i];
+    return WAY_COUNT;
+}
+
 const char *rk_last_error(const rk_ctx *ctx) { return ctx ? ctx->err : "null context"; }
 
 }  // extern "C"

@@ -11,6 +11,11 @@
 
 enum { RK_SCRATCH_SLOTS = 64 };
 
+// How often a context's calls went which way: for tests of the rules that choose (rk_ctx_ways, not in rubick.h).
+enum { WAY_ROUND_AHEAD, WAY_ROUND_AHEAD_TAKEN,          // rounds sent before their table was known; those it was right for
+       WAY_SIM_FEW, WAY_SIM_LAUNCHES, WAY_SIM_NODES,    // turns of a simulation's ticks: k_sim_few, launches, k_sim_nodes
+       WAY_COUNT };
+
 struct rk_ctx {
     int device;
     hipStream_t stream;
@@ -24,6 +29,7 @@ struct rk_ctx {
     uint32_t seen_t[2], seen_s[2];          // ... most triples and segments of a job in the last two calls (0: none)
     bool enum_clear;                        // enumeration: the device's counter of finished searches is known to be zero
     size_t enum_tab_clear;                  // ... and so many words of the leaders' table
+    uint32_t ways[WAY_COUNT];
     hipEvent_t counts_ev;                   // enumeration: the counts have reached the host (made on demand)
     hipStream_t sim_stream;                 // simulation: its own stream (a tick is captured as a graph), made on demand
     hipEvent_t sim_ev[4];                   // ... ordered after and before the context's stream with the first two; its batches of ticks
@@ -175,7 +181,7 @@ int32_t rk_launch_allocate(rk_ctx *ctx, const float *ref_thr, const TableDev &tb
                            const float *curve_thr, const SlaDev *sla, const FloorsDev *given, const uint32_t *d_jmap,
                            rk_assign *assign, float *totals, bool static_scratch = false, const TableGuard *guard = nullptr);
 // Whether a single round takes the one launch of small rounds (only that one takes a guard).
-bool rk_round_is_few(const rk_alloc_grid *grid, uint32_t max_jobs, uint32_t max_segs_per_job, const rk_cluster *one_cluster, bool given);
+bool rk_round_is_few(const rk_alloc_grid *grid, uint32_t max_jobs, uint32_t max_segs_per_job, const rk_cluster *one_cluster);
 // static_scratch: the working buffers are pieces of the library's static device array (nothing is allocated; a
 // round that needs more than the array holds is refused) instead of the context's grow-only buffers.
 // Once per context, device current: finds this device's copy of that array and raises the LDS limits of the

@@ -103,7 +103,7 @@ int32_t schedule_rounds(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_bounds *
         const uint32_t most_s = few_amounts(ctx->seen_s[0]), most_t = (ctx->seen_t[0] + 63u) & ~63u;
         bool sent = n_rounds == 1 && !sla && !round_jobs && !keep && J > 0 && J <= SPECULATE_JOBS && most_s <= 64u && most_t <= 1024u &&
                     ctx->seen_s[0] > 0 && few_amounts(ctx->seen_s[1]) == most_s && ((ctx->seen_t[1] + 63u) & ~63u) == most_t &&
-                    rk_round_is_few(grid, J, most_s, &clusters[0], false);
+                    rk_round_is_few(grid, J, most_s, &clusters[0]);
         if (sent) {
             const uint64_t segs = (uint64_t)J * most_s < cap_s ? (uint64_t)J * most_s : cap_s;
             const TableGuard guard = {P.totals, cap_t, segs, most_t, most_s};

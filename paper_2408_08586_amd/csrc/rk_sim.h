@@ -4,7 +4,8 @@
 #include "rk_internal.h"
 #include "rk_model.h"
 
-constexpr uint32_t SIM_FEW_TICKS = 128;        // ticks of a launch of k_sim_few
+constexpr uint32_t SIM_FEW_TICKS = 128;        // ticks of a launch of k_sim_few, at most
+constexpr uint32_t SIM_LONG_WALK = 0xFFFFFFFFu;
 
 struct SimState {               // per job, between the ticks
     uint32_t *g, *c, *plan;     // what the job holds (g = 0: nothing)
@@ -25,8 +26,9 @@ struct SimArgs {
     SimState S;
     FloorsDev F;
     const rk_assign *assign;
-    uint32_t *tick;             // device counter: the tick whose round comes next
-    uint32_t *h_tick;           // its copy in pinned host memory
+    uint32_t *tick;             // device counter: the tick whose round comes next; behind it: a launch of k_sim_few was stopped
+    uint32_t *h_tick;           // its copy in pinned host memory (may be null); behind it: how many jobs that round is for, or
+                                // (k_sim_few) SIM_LONG_WALK when the last round walked long over the CPU levels
     float *tick_total;          // the allocation's total of the current tick
     rk_sim_result out;
     double *held;               // result arrays or scratch when the caller passes none
@@ -138,13 +140,14 @@ __device__ __forceinline__ bool sim_placed(const SimArgs &A) {
 // A workgroup closes tick `tick`, whose round has run (first: there is none yet), and opens the next one; ticks that start
 // from exactly what the last round started from are closed at once.  True: the tick `tick` is open and needs a round
 // (round_needed: it does in any case); false: there are no more ticks.  What a thread writes of its jobs only it reads.
-template <int THREADS>
-__device__ __forceinline__ bool sim_ticks(const SimArgs &A, uint32_t &tick, bool first, bool round_needed) {
+// COUNT: thread 0 finds in part how many jobs the round is for, those that are frozen not among them.
+template <int THREADS, bool COUNT = false>
+__device__ __forceinline__ bool sim_ticks(const SimArgs &A, uint32_t &tick, bool first, bool round_needed, uint32_t *part = nullptr) {
     __shared__ unsigned long long sum_g, sum_c;
-    __shared__ uint32_t sum_f, sum_used, moved;
+    __shared__ uint32_t sum_f, sum_used, moved, sum_p;
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
     for (;;) {
-        if (tid == 0) { sum_g = 0ull; sum_c = 0ull; sum_f = 0u; sum_used = 0u; moved = 0u; }
+        if (tid == 0) { sum_g = 0ull; sum_c = 0ull; sum_f = 0u; sum_used = 0u; moved = 0u; sum_p = 0u; }
         __syncthreads();
         if (!first) {
             const double t = (double)tick * A.dt;
@@ -166,7 +169,7 @@ __device__ __forceinline__ bool sim_ticks(const SimArgs &A, uint32_t &tick, bool
         }
         const double t = (double)tick * A.dt;
         unsigned long long held_g = 0, held_c = 0;
-        uint32_t n_frozen = 0;
+        uint32_t n_frozen = 0, n_part = 0;
         bool other = false;
         for (uint32_t j = tid; j < A.n_jobs; j += THREADS) {
             const bool active = A.arrival[j] <= t && !A.S.done[j];
@@ -192,7 +195,9 @@ __device__ __forceinline__ bool sim_ticks(const SimArgs &A, uint32_t &tick, bool
                 A.F.ci[j] = ci;
                 other = true;
             }
+            if (COUNT) n_part += (uint32_t)__popcll(__ballot(state == RK_JOB_NORMAL));    // (lane 0 has every turn of its wavefront)
         }
+        if (COUNT && lane == 0 && n_part) atomicAdd(&sum_p, n_part);
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) {
             held_g += __shfl_xor(held_g, off, 64);
@@ -206,15 +211,22 @@ __device__ __forceinline__ bool sim_ticks(const SimArgs &A, uint32_t &tick, bool
             A.F.cap0[0] = hg < A.cl.G ? A.cl.G - hg : 0ull;   // frozen jobs are charged first
             A.F.cap0[1] = hc < A.cl.C ? A.cl.C - hc : 0ull;
             if (A.out.frozen) A.out.frozen[tick] = sum_f;
+            if (COUNT) *part = sum_p;
         }
         if (round_needed) return true;
         __syncthreads();                                      // the sums are read before they are cleared
     }
 }
 
-// Ticks [t0, t1) of a simulation under the greedy, on the context's stream; false in *taken: not a simulation for it.
+// Ticks of a simulation under the greedy in one workgroup, on the context's stream: SIM_NOT_FEW: none; SIM_ALWAYS_FEW: all of
+// them; SIM_OFTEN_FEW: those whose rounds are for at most `most` jobs that do not walk long over the CPU levels.
+enum SimFew { SIM_NOT_FEW, SIM_OFTEN_FEW, SIM_ALWAYS_FEW };
+SimFew rk_sim_few(uint32_t n_jobs, uint32_t max_segs_per_job, const rk_alloc_grid *grid, const rk_cluster *cluster, uint32_t *most);
+// n_launches of SIM_FEW_TICKS ticks each from the one that *A.tick says (begin: from the first one).  A tick whose round is for
+// more than `most` jobs ends them, and stays open; one whose walks were long ends them when it is closed.
 int32_t rk_launch_sim_few(rk_ctx *ctx, const SimArgs &A, const float *ref_thr, const rk_alloc_grid *grid, uint32_t max_segs_per_job,
-                          const float *best_thr, const uint32_t *best_plan, const float *curve_thr, rk_assign *assign, bool *taken);
+                          const float *best_thr, const uint32_t *best_plan, const float *curve_thr, rk_assign *assign,
+                          uint32_t n_launches, bool begin, uint32_t most);
 
 // Whether a simulation over these nodes has its ticks in one workgroup's LDS, and all its ticks (rk_nodes.hip).
 bool rk_sim_nodes_fit(uint32_t n_jobs, const rk_nodes *nodes);

@@ -14,10 +14,12 @@
 // tick as well instead of handing it to the round's kernels (720 ticks: 35.9 ->
 // 27.1 ms under the greedy, 73.0 -> 46.3 ms over the nodes, of which one kernel
 // launch less per tick is about 2 ms).
-// Under the greedy up to about 1,000 jobs need none of this: k_sim_few runs
-// whole ticks in one workgroup (rk_allocate.hip).  Over nodes up to about 1,300
-// jobs need none of it either: k_sim_nodes has nodes and jobs in LDS from tick
-// to tick (rk_nodes.hip).
+// Under the greedy a round for few jobs needs none of this: k_sim_few runs
+// whole ticks in one workgroup (rk_allocate.hip).  A simulation of few jobs has
+// only such rounds.  One of up to 1,024 jobs has them most of the time: the host
+// looks at the counter, and k_sim_few and the launches take turns as the rounds
+// get smaller and larger.  Over nodes up to about 1,300 jobs need none of it
+// either: k_sim_nodes has nodes and jobs in LDS from tick to tick (rk_nodes.hip).
 // The tick counter lives on the device, so every tick is the same sequence of
 // launches with the same arguments: the first tick runs eagerly (it also sizes
 // the scratch memory), the sequence is then captured once as a HIP graph on a
@@ -29,7 +31,9 @@ namespace {
 
 constexpr int SIM_THREADS = 1024;
 constexpr uint32_t SIM_BATCH = 4;              // replays between two looks at the tick counter
-constexpr int H_TICK = 63;                     // word of the context's pinned memory that holds it
+constexpr uint32_t SIM_FEW_LAUNCHES = 4;       // launches of k_sim_few between two looks (those behind a round for many jobs return at once)
+constexpr uint32_t SIM_WAIT_LEAST = 32, SIM_WAIT_MOST = 256;   // ticks as launches after one whose walks were long (the look costs such a tick)
+constexpr int H_TICK = 62;                     // word of the context's pinned memory that holds it, and how many jobs the open tick is for
 
 __global__ __launch_bounds__(SIM_THREADS) void k_sim_init(SimArgs A) {
     const uint32_t j = blockIdx.x * SIM_THREADS + threadIdx.x;
@@ -50,12 +54,28 @@ __global__ __launch_bounds__(SIM_THREADS) void k_sim_step(SimArgs A, uint32_t fi
     if (tick >= A.n_ticks) return;                            // replays past the last tick have nothing to close
     bool round_needed = first != 0u;                          // the same in all threads
     if (!first && A.at_off) round_needed = sim_placed<SIM_THREADS>(A);
-    (void)sim_ticks<SIM_THREADS>(A, tick, first != 0u, round_needed);
+    uint32_t part = 0;
+    (void)sim_ticks<SIM_THREADS, true>(A, tick, first != 0u, round_needed, &part);
     if (tid == 0) {
         *A.tick = tick;
+        __hip_atomic_store(A.h_tick + 1, part, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         __hip_atomic_store(A.h_tick, tick, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
+
+// A tick's launches as a graph, which has to outlive its replays.
+struct TickGraph {
+    hipStream_t s;
+    hipGraph_t graph = nullptr;
+    hipGraphExec_t exec = nullptr;
+    explicit TickGraph(hipStream_t stream) : s(stream) {}
+    ~TickGraph() {
+        if (exec) { (void)hipStreamSynchronize(s); (void)hipGraphExecDestroy(exec); }
+        if (graph) (void)hipGraphDestroy(graph);
+    }
+    TickGraph(const TickGraph &) = delete;
+    TickGraph &operator=(const TickGraph &) = delete;
+};
 
 }  // namespace
 
@@ -137,18 +157,23 @@ extern "C" int32_t rk_simulate(rk_ctx *ctx, const float *ref_thr, const rk_plan_
 
     // a simulation that ended in an error may have left work on its way
     if (ctx->sim_failed && ctx->sim_stream) RK_HIP(ctx, hipStreamSynchronize(ctx->sim_stream));
-    if (options->policy == 0u) {                               // few jobs: whole ticks in one kernel
-        bool taken = false;
-        if ((rc = rk_launch_sim_few(ctx, A, ref_thr, grid, table->max_segs_per_job, best_thr, best_plan, curve_thr, assign, &taken))) return rc;
-        if (taken) {
-            if (options->n_ticks > 1) RK_HIP(ctx, hipStreamSynchronize(ctx->stream));
-            return RK_OK;
-        }
+    uint32_t most = 0;                                         // jobs of a round for k_sim_few
+    const SimFew few = options->policy == 0u ? rk_sim_few(J, table->max_segs_per_job, grid, cluster, &most) : SIM_NOT_FEW;
+    auto launch_few = [&](uint32_t n_launches, bool begin) {
+        return rk_launch_sim_few(ctx, A, ref_thr, grid, table->max_segs_per_job, best_thr, best_plan, curve_thr, assign, n_launches, begin, most);
+    };
+    const uint32_t n = options->n_ticks;
+    if (few == SIM_ALWAYS_FEW) {                               // whole ticks in one kernel
+        ctx->ways[WAY_SIM_FEW]++;
+        if ((rc = launch_few((n - 1u) / SIM_FEW_TICKS + 1u, true))) return rc;
+        if (n > 1) RK_HIP(ctx, hipStreamSynchronize(ctx->stream));
+        return RK_OK;
     }
     void *h_tick;
     RK_HIP(ctx, hipHostGetDevicePointer(&h_tick, ctx->h_pinned + H_TICK, 0));
     A.h_tick = static_cast<uint32_t *>(h_tick);
     if (nodes && rk_sim_nodes_fit(J, nodes)) {                 // the nodes and jobs fit a workgroup's LDS: ticks without launches between them
+        ctx->ways[WAY_SIM_NODES]++;
         k_sim_init<<<(J + SIM_THREADS - 1) / SIM_THREADS, SIM_THREADS, 0, ctx->stream>>>(A);
         RK_CHECK_LAUNCH(ctx, "k_sim_init");
         k_sim_step<<<1, SIM_THREADS, 0, ctx->stream>>>(A, 1u);
@@ -197,40 +222,80 @@ extern "C" int32_t rk_simulate(rk_ctx *ctx, const float *ref_thr, const rk_plan_
         return RK_OK;
     };
 
-    k_sim_init<<<(J + SIM_THREADS - 1) / SIM_THREADS, SIM_THREADS, 0, s>>>(A);
-    RK_CHECK_LAUNCH(ctx, "k_sim_init");
-    k_sim_step<<<1, SIM_THREADS, 0, s>>>(A, 1u);
-    RK_CHECK_LAUNCH(ctx, "k_sim_step");
-    if ((rc = tick_body())) return rc;                         // tick 0, eagerly
-    if (options->n_ticks > 1) {
-        hipGraph_t graph = nullptr;
-        hipGraphExec_t exec = nullptr;
-        RK_HIP(ctx, hipStreamBeginCapture(s, hipStreamCaptureModeRelaxed));
-        rc = tick_body();
-        const hipError_t e_end = hipStreamEndCapture(s, &graph);
-        if (rc) { if (graph) (void)hipGraphDestroy(graph); return rc; }
-        if (e_end != hipSuccess) return rk_fail(ctx, RK_ERR_DEVICE, "hipStreamEndCapture: %s", hipGetErrorString(e_end));
-        hipError_t e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
+    // Ticks as launches, from the open one until there are no more, or (n > 1) k_sim_few can take over: the first one ever
+    // eagerly, the others as replays.  closed: ticks closed so far.
+    TickGraph ticks(s);
+    uint32_t closed = 0, wait = SIM_WAIT_LEAST, wait_for = 0;  // after long walks: launches for so many ticks, until that tick
+    auto told = [&](int word) { return __atomic_load_n(ctx->h_pinned + H_TICK + word, __ATOMIC_ACQUIRE); };
+    auto few_again = [&]() {                                   // (not back and forth)
+        return few == SIM_OFTEN_FEW && closed < n && closed >= wait_for && told(1) <= most - most / 4u;
+    };
+    auto as_launches = [&]() -> int32_t {
         // Replays go out in batches, one batch ahead of the counter that is read back, never more of them than ticks
         // are left.  A replay past the last tick repeats the last round and changes nothing.
-        const uint32_t n = options->n_ticks;
-        uint32_t sent = 1, run = 0, closed = 0;                // rounds enqueued, rounds known to have run, ticks closed by then
+        uint32_t sent = 0, run = 0;                            // rounds enqueued, rounds known to have run
         uint32_t sent_by[2] = {0u, 0u};                        // rounds enqueued when an event was recorded
-        for (uint32_t b = 0; e == hipSuccess && closed < n; b ^= 1u) {
+        int32_t r;
+        if (!ticks.exec) {
+            if ((r = tick_body())) return r;
+            sent = 1;
+            if (n == 1) return RK_OK;
+            RK_HIP(ctx, hipStreamBeginCapture(s, hipStreamCaptureModeRelaxed));
+            r = tick_body();
+            const hipError_t e_end = hipStreamEndCapture(s, &ticks.graph);
+            if (r) return r;
+            if (e_end != hipSuccess) return rk_fail(ctx, RK_ERR_DEVICE, "hipStreamEndCapture: %s", hipGetErrorString(e_end));
+            const hipError_t e = hipGraphInstantiate(&ticks.exec, ticks.graph, nullptr, nullptr, 0);
+            if (e != hipSuccess) { ticks.exec = nullptr; return rk_fail(ctx, RK_ERR_DEVICE, "simulation graph: %s", hipGetErrorString(e)); }
+        }
+        const uint32_t from = closed;
+        hipError_t e = hipSuccess;
+        for (uint32_t b = 0; e == hipSuccess && closed < n && (closed == from || !few_again()); b ^= 1u) {
             const uint32_t before = sent;
-            for (uint32_t k = 0; e == hipSuccess && k < SIM_BATCH && sent - run < n - closed; ++k, ++sent) e = hipGraphLaunch(exec, s);
+            for (uint32_t k = 0; e == hipSuccess && k < SIM_BATCH && sent - run < n - closed; ++k, ++sent) e = hipGraphLaunch(ticks.exec, s);
             if (e == hipSuccess) e = hipEventRecord(ctx->sim_ev[2 + b], s);
             sent_by[b] = sent;
             const uint32_t w = sent > before ? b ^ 1u : b;     // the batch before this one; this one where nothing could be sent
             if (e == hipSuccess) e = hipEventSynchronize(ctx->sim_ev[2 + w]);
             run = sent_by[w] > run ? sent_by[w] : run;
-            closed = __atomic_load_n(ctx->h_pinned + H_TICK, __ATOMIC_ACQUIRE);
+            closed = told(0);
         }
-        const hipError_t e_sync = hipStreamSynchronize(s);     // the graph must outlive its launches
-        if (e == hipSuccess) e = e_sync;
-        if (exec) (void)hipGraphExecDestroy(exec);
-        (void)hipGraphDestroy(graph);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
         if (e != hipSuccess) return rk_fail(ctx, RK_ERR_DEVICE, "simulation graph: %s", hipGetErrorString(e));
+        closed = told(0);
+        return RK_OK;
+    };
+
+    bool turn_few = few == SIM_OFTEN_FEW && n > 1;
+    if (!turn_few) {
+        k_sim_init<<<(J + SIM_THREADS - 1) / SIM_THREADS, SIM_THREADS, 0, s>>>(A);
+        RK_CHECK_LAUNCH(ctx, "k_sim_init");
+        k_sim_step<<<1, SIM_THREADS, 0, s>>>(A, 1u);
+        RK_CHECK_LAUNCH(ctx, "k_sim_step");
+    }
+    for (bool begin = true; closed < n; begin = false) {
+        if (turn_few) {
+            const uint32_t from = closed;
+            ctx->ways[WAY_SIM_FEW]++;
+            ctx->stream = s;
+            rc = launch_few(SIM_FEW_LAUNCHES, begin);
+            ctx->stream = user;
+            if (rc) return rc;
+            RK_HIP(ctx, hipStreamSynchronize(s));
+            closed = told(0);
+            turn_few = closed - from == SIM_FEW_LAUNCHES * SIM_FEW_TICKS;     // nothing came in the way
+            if (closed - from > wait) wait = SIM_WAIT_LEAST;
+            if (told(1) == SIM_LONG_WALK) { wait_for = closed + wait; wait = wait < SIM_WAIT_MOST ? 2u * wait : wait; turn_few = false; }
+            if (closed < n && !turn_few) {
+                k_sim_step<<<1, SIM_THREADS, 0, s>>>(A, 1u);   // opens the tick for the launches
+                RK_CHECK_LAUNCH(ctx, "k_sim_step");
+            }
+        } else {
+            ctx->ways[WAY_SIM_LAUNCHES]++;
+            if ((rc = as_launches())) return rc;
+            if (n == 1) break;
+            turn_few = few_again();
+        }
     }
     RK_HIP(ctx, hipEventRecord(ctx->sim_ev[1], s));
     RK_HIP(ctx, hipStreamWaitEvent(user, ctx->sim_ev[1], 0));

@@ -79,6 +79,58 @@ def test_ticks_in_one_launch(orc, n_jobs, n_ticks, scarce):
     run.close()
 
 
+def long_walks(orc, n_jobs, kind, g_max, n_cpu, per_gpu, rng):
+    """Curves that gain at every amount and every CPU level, less and less: walks as long as they can be."""
+    ot = orc.enumerate_plans(np.repeat(np.array([kind], np.uint32), n_jobs, axis=0), workloads.Bounds(g_max=g_max))
+    g = ot.seg_g[:ot.seg_off[1]].astype(np.float64)[None, None, :]
+    c = np.arange(1, n_cpu + 1)[None, :, None]
+    a, b = rng.uniform(0.5, 0.9, (n_jobs, 1, 1)), rng.uniform(0.5, 0.9, (n_jobs, 1, 1))
+    bt = (g ** a * (1 + 0.05 * c ** b)).astype(np.float32).reshape(-1)
+    grid = workloads.Grid(np.arange(1, n_cpu + 1, dtype=np.uint32), per_gpu, np.array([64.0], np.float32), 0)
+    return ot, grid, bt, np.ones(bt.size, np.uint32)
+
+
+# n_jobs, kind of job, g_max, GPU counts per job, CPU levels, per GPU, GPUs per job of the cluster, ways: k_sim_few, launches
+TURNS = [(256, (96, 1680, 1), 16, 16, 5, 1, 1.0, "f"), (257, (96, 1680, 1), 16, 16, 5, 1, 0.25, "fl"), (128, (96, 1680, 1), 64, 32, 5, 1, 2.0, "f"),
+         (129, (96, 1680, 1), 64, 32, 16, 0, 1.0, "fl"), (64, (96, 1680, 1), 256, 64, 16, 0, 8.0, "f"), (65, (96, 1680, 1), 256, 64, 17, 0, 8.0, "fl"),
+         (256, (96, 1680, 1), 16, 16, 64, 0, 8.0, "fl"), (64, (96, 1680, 1), 64, 32, 64, 0, 8.0, "fl"), (30, (96, 1680, 1), 256, 64, 33, 0, 0.4, "f"),
+         (700, (96, 1680, 1), 16, 16, 33, 0, 0.5, "fl"), (1024, (96, 1680, 1), 16, 16, 5, 1, 0.5, "fl"), (1025, (96, 1680, 1), 16, 16, 5, 1, 0.5, "l"),
+         (40, (96, 50400, 1), 512, 128, 5, 1, 4.0, "l")]
+
+
+@pytest.mark.parametrize("n_jobs,kind,g_max,counts,n_cpu,per_gpu,gpus,ways_want", TURNS)
+@pytest.mark.parametrize("thaw", [False, True])
+def test_ticks_take_turns(orc, n_jobs, kind, g_max, counts, n_cpu, per_gpu, gpus, ways_want, thaw):
+    """Simulations around the lines between k_sim_few and ticks as launches: 16, 32, 64 lanes per job in either pass, per-lane
+    words in LDS and beyond.  All jobs come at the start, of more than 400 a quarter later, so that rounds get small, and large
+    again; thaw: nobody is ever frozen."""
+    from gpu_harness import DeviceRun, ways
+    from test_gpu_sim import run_on_gpu, same
+    rng = np.random.default_rng(n_jobs + n_cpu)
+    ot, grid, bt, bp = long_walks(orc, n_jobs, kind, g_max, n_cpu, per_gpu, rng)
+    assert counts // 2 < np.diff(ot.seg_off).max() <= counts
+    base = workloads.tiny()
+    coef = np.tile(base.coef[:1], (n_jobs, 1))
+    coef[:, 16] = rng.uniform(0.5, 4.0, n_jobs).astype(np.float32)
+    G = int(gpus * n_jobs)
+    cluster = workloads.Cluster(G, 6 * G if per_gpu else n_cpu * n_jobs // 2, 1e9)
+    wl = workloads.Workload("turns", coef, np.repeat(np.array([kind], np.uint32), n_jobs, axis=0), workloads.Bounds(g_max=g_max), grid,
+                            base.env, cluster)
+    n_ticks = 90
+    arrival = np.where((n_jobs > 400) & (np.arange(n_jobs) % 4 == 0), 60.0 * 60, 0.0)
+    work = np.median(bt) * 60.0 * rng.uniform(0.5, 30.0, n_jobs)
+    delta = np.zeros(n_jobs) if thaw else rng.uniform(0.0, 90.0, n_jobs)
+    want = orc.simulator.simulate(coef[:, 16], ot, grid, cluster, bt, bp, bt, arrival, work, delta, 60.0, n_ticks, gate=0.9)
+    run = DeviceRun(wl)
+    run.enumerate()
+    curves = (run.dev_f32(bt), run.dev_u32(bp), run.dev_f32(bt))
+    for _ in range(2):                                          # (the second one finds the first one's working memory)
+        same(run_on_gpu(run, None, arrival, work, delta, 60.0, n_ticks, 0.9, curves=curves), want)
+    got = ways(run.ctx)
+    assert (got["sim_few"] > 0, got["sim_launches"] > 0) == ("f" in ways_want, "l" in ways_want), got
+    run.close()
+
+
 @pytest.mark.parametrize("n_jobs,n_ticks,gpn", [(1, 1, 8), (30, 64, 4), (60, 200, 8), (256, 65, 6), (257, 130, 8), (700, 60, 16), (1600, 20, 8)])
 @pytest.mark.parametrize("scarce", [False, True])
 def test_ticks_over_nodes_in_one_launch(orc, n_jobs, n_ticks, gpn, scarce):
