@@ -29,6 +29,7 @@ int32_t rk_scratch(rk_ctx *ctx, int slot, size_t bytes, void **out) {
         want = (want + 255) & ~(size_t)255;
         RK_HIP(ctx, hipMalloc(&ctx->scratch[slot], want));
         ctx->scratch_bytes[slot] = want;
+        ctx->ways[WAY_GREW]++;
     }
     *out = ctx->scratch[slot];
     return RK_OK;

@@ -14,6 +14,7 @@ enum { RK_SCRATCH_SLOTS = 64 };
 // How often a context's calls went which way: for tests of the rules that choose (rk_ctx_ways, not in rubick.h).
 enum { WAY_ROUND_AHEAD, WAY_ROUND_AHEAD_TAKEN,          // rounds sent before their table was known; those it was right for
        WAY_SIM_FEW, WAY_SIM_LAUNCHES, WAY_SIM_NODES,    // turns of a simulation's ticks: k_sim_few, launches, k_sim_nodes
+       WAY_GREW,                                        // working buffers that were made or grew
        WAY_COUNT };
 
 struct rk_ctx {

@@ -16,8 +16,6 @@ struct RoundKeep {
     bool curves_only;        // set by the caller: stop after the curves, no allocation
 };
 
-// Jobs of a round whose kernels may go out before the table's size is known: those whose counts one workgroup scans.
-constexpr uint32_t SPECULATE_JOBS = 256;
 // the kinds of tables that the kernels of small rounds tell apart
 inline uint32_t few_amounts(uint32_t segs) { return segs <= 16u ? 16u : segs <= 32u ? 32u : segs <= 64u ? 64u : 0xFFFFFFFFu; }
 
@@ -80,6 +78,18 @@ int32_t schedule_rounds(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_bounds *
         return rk_scratch(ctx, SL_CURVE_G, n * 4, (void **)&curve_g);
     };
 
+    // A round that takes one launch, with at most `most` GPU counts per job, may be sent before its table is known: the
+    // outputs' room is then most_s per job, and a round of the same kind that is not sent takes as much, so that buffers grow
+    // in the first call of a kind and not between the two halves of a later one's enumeration (66 us instead of 48).
+    auto may_go_ahead = [&](uint32_t most) {
+        return n_rounds == 1 && !sla && !round_jobs && !keep && J > 0 && most <= 64u && rk_round_is_few(grid, J, most, &clusters[0]);
+    };
+    auto have_room = [&](size_t n) {
+        for (int slot : {SL_BEST_THR, SL_BEST_PLAN, SL_CURVE_THR, SL_CURVE_PLAN, SL_CURVE_G})
+            if (ctx->scratch_bytes[slot] < n * 4) return false;
+        return true;
+    };
+
     // internal plan table in scratch memory; grown on demand
     rk_plan_table tb;
     memset(&tb, 0, sizeof(tb));
@@ -99,13 +109,14 @@ int32_t schedule_rounds(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_bounds *
         // A small round waits longer for the host to see the table's size than for anything else it does.  When the last two
         // enumerations found tables of the same kind, evaluation and allocation go out at once, prepared for a table like
         // these; the kernels leave any other one alone, and the round is then launched again for the one there is.  Rounds
-        // of 8 and 64 jobs 40.0 -> 36.7 and 50.8 -> 47.0 us; from 257 jobs on the fill pass takes as long as the wait.
+        // of 20 and 60 jobs 41 -> 36 and 45 -> 40 us, 46 and 50 where the guess was wrong: calls in turn from two kinds, two of
+        // each, are back at 43.
         const uint32_t most_s = few_amounts(ctx->seen_s[0]), most_t = (ctx->seen_t[0] + 63u) & ~63u;
-        bool sent = n_rounds == 1 && !sla && !round_jobs && !keep && J > 0 && J <= SPECULATE_JOBS && most_s <= 64u && most_t <= 1024u &&
-                    ctx->seen_s[0] > 0 && few_amounts(ctx->seen_s[1]) == most_s && ((ctx->seen_t[1] + 63u) & ~63u) == most_t &&
-                    rk_round_is_few(grid, J, most_s, &clusters[0]);
+        const bool sent = may_go_ahead(most_s) && most_t <= 1024u && ctx->seen_s[0] > 0 && few_amounts(ctx->seen_s[1]) == most_s &&
+                          ((ctx->seen_t[1] + 63u) & ~63u) == most_t && have_room(n_rows * J * most_s);
         if (sent) {
             const uint64_t segs = (uint64_t)J * most_s < cap_s ? (uint64_t)J * most_s : cap_s;
+            ctx->ways[WAY_ROUND_AHEAD]++;
             const TableGuard guard = {P.totals, cap_t, segs, most_t, most_s};
             rk_plan_table like = tb;
             like.max_triples_per_job = most_t; like.max_segs_per_job = most_s;
@@ -118,7 +129,10 @@ int32_t schedule_rounds(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_bounds *
             const int32_t rc_sent = rc;
             rc = rk_enumerate_end(ctx, &tb, P);
             if (!rc) rc = rc_sent;
-            if (!rc && P.whole && tb.n_segs <= segs && tb.max_triples_per_job <= most_t && tb.max_segs_per_job <= most_s) return RK_OK;
+            if (!rc && P.whole && tb.n_segs <= segs && tb.max_triples_per_job <= most_t && tb.max_segs_per_job <= most_s) {
+                ctx->ways[WAY_ROUND_AHEAD_TAKEN]++;
+                return RK_OK;
+            }
         } else {
             rc = rk_enumerate_end(ctx, &tb, P);
         }
@@ -131,7 +145,8 @@ int32_t schedule_rounds(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_bounds *
 
     float *best_thr, *curve_thr;
     uint32_t *best_plan, *curve_plan, *curve_g;
-    if ((rc = outputs((size_t)(n_rows * tb.n_segs), best_thr, best_plan, curve_thr, curve_plan, curve_g))) return rc;
+    const uint32_t most = few_amounts(tb.max_segs_per_job);
+    if ((rc = outputs((size_t)(n_rows * (may_go_ahead(most) ? (uint64_t)J * most : tb.n_segs)), best_thr, best_plan, curve_thr, curve_plan, curve_g))) return rc;
     if ((rc = rk_launch_fused(ctx, jobs, &tb, grid, env, 0, J, best_thr, best_plan, curve_thr, curve_plan, curve_g))) return rc;
     if (keep) {
         keep->tb = tb; keep->best_thr = best_thr; keep->best_plan = best_plan; keep->curve_thr = curve_thr; keep->min_seg = nullptr;

@@ -10,9 +10,9 @@ import paper_2408_08586_amd as rk
 def ways(ctx):
     """How often the context's calls went which way (the counters of the library's internal header)."""
     import ctypes
-    counts = (ctypes.c_uint32 * 5)()
-    assert rk.load_library().rk_ctx_ways(ctx, counts) == 5
-    return dict(zip(("ahead", "ahead_taken", "sim_few", "sim_launches", "sim_nodes"), counts))
+    counts = (ctypes.c_uint32 * 6)()
+    assert rk.load_library().rk_ctx_ways(ctx, counts) == 6
+    return dict(zip(("ahead", "ahead_taken", "sim_few", "sim_launches", "sim_nodes", "grew"), counts))
 
 
 class DeviceRun:

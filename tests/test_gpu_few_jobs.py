@@ -228,6 +228,7 @@ def test_small_rounds_sent_before_their_table_is_known():
     alone."""
     import torch
     import paper_2408_08586_amd as rk
+    from gpu_harness import ways
     ctx = rk.rk_create(0)
     base = workloads.tiny()
     small, wide, wider = np.array([[12, 32, 1]], np.uint32), np.array([[96, 128, 1]], np.uint32), np.array([[96, 1680, 1]], np.uint32)
@@ -258,7 +259,45 @@ def test_small_rounds_sent_before_their_table_is_known():
         rk.rk_destroy(fresh)
         assert got[0] == want[0] and np.array_equal(got[1], want[1]) and got[2] == want[2], i
         if kind is bad:
+            bad_at = ways(ctx)["ahead"]
             assert got[0] == rk.RK_ERR_UNSUPPORTED and (got[1] == 77).all() and got[2] == -1.0
         else:
             assert got[0] == 0 and got[2] > 0
+    seen = ways(ctx)
+    assert bad_at > 0 and seen["ahead_taken"] >= 4 and seen["ahead"] - seen["ahead_taken"] >= 3      # sent and taken, sent and refused
+    rk.rk_destroy(ctx)
+
+
+def test_a_steady_round_is_sent_ahead_and_its_buffers_stay():
+    """Calls of one kind: the first makes the working buffers, none after it does, and from the third on rounds go out before
+    their table is known.  A round of another kind after them is refused once and launched again."""
+    import torch
+    import paper_2408_08586_amd as rk
+    from gpu_harness import ways
+    ctx = rk.rk_create(0)
+    base = workloads.tiny()
+
+    def call(kind, n_jobs, g_max):
+        wl = workloads.Workload("steady", np.tile(base.coef[:1], (n_jobs, 1)), np.tile(np.array([kind], np.uint32), (n_jobs, 1)),
+                                workloads.Bounds(g_max=g_max), base.grid, base.env, workloads.Cluster(3 * n_jobs, 12 * n_jobs, 1e4))
+        assign, total = rk.new_assign(n_jobs, "cuda:0"), torch.zeros(1, device="cuda:0")
+        rk.rk_schedule_round(ctx, rk.Jobs(wl.coef, wl.ints, "cuda:0"), rk.make_bounds(wl.bounds), rk.make_grid(wl.grid), rk.make_env(wl.env),
+                             rk.make_cluster(wl.cluster), assign, total)
+        rk.rk_sync(ctx)
+        return ways(ctx)
+    kinds = [((12, 32, 1), 60, 64), ((96, 1680, 1), 30, 64), ((96, 1680, 1), 30, 256), ((12, 32, 1), 60, 64)]
+    ahead = taken = 0
+    for i, kind in enumerate(kinds):
+        grew = None
+        for k in range(6):
+            w = call(*kind)
+            ahead += 0 if (i == 0 and k < 2) or (i > 0 and k == 1) else 1       # (the last two calls were of one kind)
+            taken += 0 if k < 2 else 1
+            assert (w["ahead"], w["ahead_taken"]) == (ahead, taken) or (i > 0 and k == 0), (i, k)
+            if i > 0 and k == 0:                                # sent for the kind before, when its buffers had room for these jobs
+                assert w["ahead"] in (ahead, ahead - 1) and w["ahead_taken"] == taken
+                ahead = w["ahead"]
+            assert grew is None or w["grew"] == grew, (i, k)
+            grew = w["grew"]
+    assert ahead > taken > 0                                    # (one guess at least was refused)
     rk.rk_destroy(ctx)
