@@ -1904,7 +1904,7 @@ __device__ __forceinline__ void few_pass(const Ctx &X, const FewMem &M, const Fe
                     M.to[p] = nx.tgt | nx.dg << 16;
                     M.dc[p] = dc;
                 }
-                __builtin_amdgcn_wave_barrier();               // the lanes read each other's words in the next turn
+                rs_wave_order();                               // the lanes read each other's words in the next turn
             }
             if (lane == 0) {
                 M.box[0] = freeG;
