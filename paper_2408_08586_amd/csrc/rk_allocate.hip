@@ -2731,6 +2731,7 @@ __global__ __launch_bounds__(THREADS) void k_reschedule(RsArgs B) {
                     asm volatile("" ::: "memory");
                 }
                 changed_once = ~0u;
+                __syncthreads();                             // (the levels have been read: the next step writes them before it knows whether it stands)
                 continue;
             }
             const uint32_t mine = lane < changed ? sh_upd[lane][0] : NONE;   // the threads that have these jobs
