@@ -2389,7 +2389,7 @@ __global__ void k_rs_prepare(RsArgs B) {
     const int32_t fl = rs_fl_s(A, j);
     const bool below = fl >= 0 && gi < fl;
     const uint32_t so = A.X.tb.seg_off[j], ns = A.X.tb.seg_off[j + 1] - so;
-    const RsKept k = rs_keep<LANES>(A, j, so, ns, gi, ci, -1, lane, true, true, A.gives + j, nullptr);
+    const RsKept k = rs_keep<LANES>(A, j, so, ns, gi, ci, -1, lane, RS_ALL_PARTS, A.gives + j, nullptr);
     if (lane == 0) {
         const bool part = rs_part(A, j);
         A.st.gi[j] = gi; A.st.ci[j] = ci; A.st.g[j] = k.g;
@@ -2413,7 +2413,10 @@ static inline uint32_t rs_near(size_t J) {
 // what it gives, 2.5 us for a committed step's new values (a job's rows come from memory that other chiplets wrote), 4 us
 // for a look after one.  10,000 jobs on 4,096 GPUs, 15 jobs on the full path, 22 steps committed, 49 shrinks: 374 -> 242 us;
 // 9,999 jobs with floors, several hundred steps: 4.2 -> 3.4 ms; while all wavefronts searched all jobs, with a barrier on
-// either side of every decision, and a look read seven values of every job from memory.
+// either side of every decision, and a look read seven values of every job from memory.  Where thousands hold something a
+// search by one wavefront takes longer than one by all: 4,486 holders, 5,297 steps 74.3 ms then and 70.3 now (95.3 with
+// every search in two passes of single loads), 42,980 steps of a CPU level 223 and 260 (329); 1,348 holders, 13,119 such
+// steps 62.7 and 65.5 (75.6); 29 holders, 244 steps 0.92 and 0.93 (1.03 with two wavefronts per changed job at all times).
 template <int THREADS, int PER>
 __global__ __launch_bounds__(THREADS) void k_reschedule(RsArgs B) {
     constexpr uint32_t WAVES = THREADS / 64, NONE = 0xFFFFFFFFu, JOB = (1u << RS_JOB_BITS) - 1u, MARK = 0x8000u;
@@ -2493,30 +2496,39 @@ __global__ __launch_bounds__(THREADS) void k_reschedule(RsArgs B) {
     __syncthreads();
 
     // A wavefront finds the place with the lowest slope (the lower job among equal slopes); false: nobody gives.  Four places
-    // per lane and load; a list of at most 256 places is looked at once.
+    // per lane and load, two loads on their way (four: 3 % slower, the code grows); only where several places have the slope are they looked for again.
+    const float4 NOBODY = {INF, INF, INF, INF};
     auto lowest = [&](const float *low, uint32_t n, float &slope, uint32_t &place) -> bool {
         const uint32_t n4 = (n + 3u) / 4u;
         const float4 *const q4 = reinterpret_cast<const float4 *>(low);
-        float4 q = lane < n4 ? q4[lane] : float4{INF, INF, INF, INF};
+        float4 q = lane < n4 ? q4[lane] : NOBODY;            // the lane's first quad with its lowest slope, and where that is
         float least = fminf(fminf(q.x, q.y), fminf(q.z, q.w));
-        for (uint32_t i = lane + 64u; i < n4; i += 64u) {
-            const float4 r = q4[i];
-            least = fminf(least, fminf(fminf(r.x, r.y), fminf(r.z, r.w)));
+        uint32_t quad = lane;
+        bool more = false;                                   // ... and another quad has it as well
+        for (uint32_t i = lane + 64u; i < n4; i += 128u) {
+            float4 r[2];
+#pragma unroll
+            for (uint32_t u = 0; u < 2; ++u) r[u] = i + 64u * u < n4 ? q4[i + 64u * u] : NOBODY;
+#pragma unroll
+            for (uint32_t u = 0; u < 2; ++u) {
+                const float m = fminf(fminf(r[u].x, r[u].y), fminf(r[u].z, r[u].w));
+                more = m < least ? false : more | (m == least);
+                if (m < least) { least = m; quad = i + 64u * u; }
+            }
         }
+        if (quad != lane) q = q4[quad];
         const uint32_t top = wave_min_u32_rows(least < INF ? rs_ordered(least) : NONE);
         if (top == NONE) return false;
         slope = rs_unordered(top);
-        uint32_t job = NONE, at = 0u;
-        if (n4 <= 64u) {
-            const unsigned long long mx = __ballot(q.x == slope), my = __ballot(q.y == slope), mz = __ballot(q.z == slope), mw = __ballot(q.w == slope);
-            const unsigned long long any = mx | my | mz | mw;
-            if (!(any & (any - 1ull)) && !((mx & my) | ((mx | my) & mz) | ((mx | my | mz) & mw))) {      // one place has it
-                place = 4u * ((uint32_t)__ffsll((long long)any) - 1u) + (mx ? 0u : my ? 1u : mz ? 2u : 3u);
-                return true;
-            }
+        const unsigned long long mx = __ballot(q.x == slope), my = __ballot(q.y == slope), mz = __ballot(q.z == slope), mw = __ballot(q.w == slope);
+        const unsigned long long any = mx | my | mz | mw;
+        if (!(any & (any - 1ull)) && !((mx & my) | ((mx | my) & mz) | ((mx | my | mz) & mw)) && !(__ballot(more) & any)) {   // one place has it
+            place = 4u * wave_lane_u32(quad, (uint32_t)__ffsll((long long)any) - 1u) + (mx ? 0u : my ? 1u : mz ? 2u : 3u);
+            return true;
         }
+        uint32_t job = NONE, at = 0u;
         for (uint32_t i = lane; i < n4; i += 64u) {
-            if (i != lane) q = q4[i];
+            q = q4[i];
             const float x[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
             for (uint32_t c = 0; c < 4; ++c)
@@ -2528,6 +2540,27 @@ __global__ __launch_bounds__(THREADS) void k_reschedule(RsArgs B) {
         const uint32_t first = wave_min_u32_rows(job);
         place = wave_lane_u32(at, (uint32_t)__ffsll((long long)__ballot(job == first)) - 1u);
         return true;
+    };
+    // ... and the lowest slope but that place's
+    auto lowest_but = [&](const float *low, uint32_t n, uint32_t place) -> float {
+        const uint32_t n4 = (n + 3u) / 4u;
+        const float4 *const q4 = reinterpret_cast<const float4 *>(low);
+        float rest = INF;
+        for (uint32_t i = lane; i < n4; i += 128u) {
+            float4 r[2];
+#pragma unroll
+            for (uint32_t u = 0; u < 2; ++u) r[u] = i + 64u * u < n4 ? q4[i + 64u * u] : NOBODY;
+#pragma unroll
+            for (uint32_t u = 0; u < 2; ++u) {
+                const uint32_t c = i + 64u * u == place / 4u ? place % 4u : 4u;
+                if (c == 0u) r[u].x = INF;
+                if (c == 1u) r[u].y = INF;
+                if (c == 2u) r[u].z = INF;
+                if (c == 3u) r[u].w = INF;
+                rest = fminf(rest, fminf(fminf(r[u].x, r[u].y), fminf(r[u].z, r[u].w)));
+            }
+        }
+        return rs_unordered(wave_min_u32_rows(rs_ordered(rest)));
     };
 
     // ---- the first wavefront's part: a step of ScheduleJob(j).  Values without a lane are the same in all lanes.
@@ -2690,27 +2723,30 @@ __global__ __launch_bounds__(THREADS) void k_reschedule(RsArgs B) {
             turn ^= 1u;
             if (!changed) return any;
             any = true;
-            for (uint32_t i = wave; i < 2u * changed; i += WAVES) {          // two wavefronts per job: GPUs, CPUs
-                const uint32_t at = i >> 1;
-                const bool far = at >= RS_TOUCHED, gpus = (i & 1u) == 0u;
+            // Four wavefronts per job where there are enough, one per step, otherwise two: GPUs, CPUs.
+            const uint32_t each = 4u * changed <= WAVES ? 2u : 1u;           // (log2)
+            for (uint32_t i = wave; i < changed << each; i += WAVES) {
+                const uint32_t at = i >> each, parts = each == 2u ? 1u << (i & 3u) : i & 1u ? RS_UP_C | RS_DOWN_C : RS_UP_G | RS_DOWN_G;
+                const bool far = at >= RS_TOUCHED;
                 const uint32_t e = one(far ? A.touched[at] : sh_touched[at].x), v = e & JOB, place = e >> RS_JOB_BITS;
                 const uint32_t now = one(far ? ((uint32_t)A.st.gi[v] << 16) | A.st.ci[v] : sh_now[at]);
                 const int32_t gi = (int32_t)(int16_t)(now >> 16);
                 const uint32_t so = one(far ? A.X.tb.seg_off[v] : sh_so[at]), ns = one(far ? A.X.tb.seg_off[v + 1] - so : (uint32_t)sh_ns[at]);
-                const RsKept k = rs_keep<64>(A, v, so, ns, gi, now & 0xFFFFu, (int32_t)place, lane, gpus, !gpus,
+                const RsKept k = rs_keep<64>(A, v, so, ns, gi, now & 0xFFFFu, (int32_t)place, lane, parts,
                                              place < near ? near_gives + place : A.gives + v, v == j ? &sh_next : nullptr);
                 if (lane == 0) {
                     uint32_t *const u = at < RS_UPDATES ? sh_upd[at] : nullptr;
-                    if (gpus) {
-                        low_g[place] = k.ds_g; A.st.g[v] = k.g;
+                    if (parts & RS_UP_G) {
+                        A.st.g[v] = k.g;
                         if (u) { u[0] = v; u[1] = __float_as_uint(k.ug); u[2] = k.dg | ((now & 0xFFFFu) << 16) | (gi >= 0 ? RS_HOLDS : 0u); }
-                    } else {
-                        low_c[place] = k.ds_c;
-                        if (u) u[3] = k.uc > 0.f ? RS_HAS_CPU : 0u;
                     }
-                    if (!others) {                           // (the order is not yet fixed)
+                    if (parts & RS_DOWN_G) low_g[place] = k.ds_g;
+                    if ((parts & RS_UP_C) && u) u[3] = k.uc > 0.f ? RS_HAS_CPU : 0u;
+                    if (parts & RS_DOWN_C) low_c[place] = k.ds_c;
+                    if (!others && rs_part(A, v) && !A.first[v]) {           // (the order is not yet fixed)
                         uint32_t *const key = reinterpret_cast<uint32_t *>(A.okey + v);
-                        if (rs_part(A, v) && !A.first[v]) key[gpus ? 1 : 0] = rs_ordered(gpus ? k.ug : k.uc);
+                        if (parts & RS_UP_G) key[1] = rs_ordered(k.ug);
+                        if (parts & RS_UP_C) key[0] = rs_ordered(k.uc);
                     }
                     // (what is read behind the barrier that follows; the rest is waited for before the next one)
                     if (place >= near || changed > RS_UPDATES) __threadfence_block();
@@ -2831,9 +2867,7 @@ __global__ __launch_bounds__(THREADS) void k_reschedule(RsArgs B) {
                 uint32_t place;
                 if (lowest(low, n, m.m1, place)) {
                     m.i1 = one(who[place]);
-                    float rest = INF;
-                    for (uint32_t i = lane; i < n; i += 64u) rest = i != place ? fminf(rest, low[i]) : rest;
-                    m.m2 = rs_unordered(wave_min_u32_rows(rs_ordered(rest)));
+                    m.m2 = lowest_but(low, n, place);
                 }
                 if (lane == 0) sh_min[wave] = m;
             }

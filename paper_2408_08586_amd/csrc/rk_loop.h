@@ -437,7 +437,7 @@ __device__ __forceinline__ RsShrunk rs_shrink_wave(const Args &A, uint32_t v, ui
 
 // What the loop over totals keeps of a job in the state a step finds it in, so that neither its own next steps nor the
 // first step down that it is asked for wait for its rows: both steps up, and both steps down with the slopes after them.
-// The halves are written by whoever finds the steps in GPUs and in CPUs, 16 bytes at a time.
+// Whoever finds one of the four steps writes its two pieces, 16 bytes at a time.
 struct __align__(16) RsNext {
     float ug; uint32_t dg; float gain_g; int32_t tgt_g;              // the GPU step (tgt_g -1: none)
     uint32_t lvl_g, below_ns; unsigned long long dcg;                // below_ns: its number of amounts, RS_BELOW when it is below its floor
@@ -454,12 +454,15 @@ static_assert(sizeof(RsNext) == 64 && sizeof(RsGives) == 64, "four pieces each")
 constexpr uint32_t RS_BELOW = 0x80000000u;
 struct RsKept { float ds_g, ds_c, ug, uc; uint32_t dg, g; };
 
-// Finds and stores it for job v, which holds (gi, ci); LANES: the 64 of a wavefront, which has the rows
-// of a job of at most 64 amounts at once, or 1.  so, ns: where the job's amounts begin and how many they are; with_g, with_c:
-// the halves to do; gives: where the steps down go; also: where else the steps up go, or null.  (g: the GPUs it holds, with_g.)
+// The parts of it: steps up and down in GPUs and in CPUs, each found and stored by itself.
+constexpr uint32_t RS_UP_G = 1u, RS_DOWN_G = 2u, RS_UP_C = 4u, RS_DOWN_C = 8u, RS_ALL_PARTS = 15u;
+
+// Finds and stores the given parts for job v, which holds (gi, ci); LANES: the 64 of a wavefront, which has the rows
+// of a job of at most 64 amounts at once, or 1.  so, ns: where the job's amounts begin and how many they are; gives: where
+// the steps down go; also: where else the steps up go, or null.  (g, the GPUs it holds: with the step up in GPUs.)
 template <uint32_t LANES, class Args>
 __device__ __forceinline__ RsKept rs_keep(const Args &A, uint32_t v, uint32_t so, uint32_t ns, int32_t gi, uint32_t ci, int32_t slot, uint32_t lane,
-                                          bool with_g, bool with_c, RsGives *gives, RsNext *also) {
+                                          uint32_t parts, RsGives *gives, RsNext *also) {
     const float INF = __int_as_float(0x7F800000);
     const int32_t fl = rs_fl_s(A, v);
     const bool below = fl >= 0 && gi < fl, rows = LANES == 64u && ns <= 64u && !below;
@@ -467,14 +470,10 @@ __device__ __forceinline__ RsKept rs_keep(const Args &A, uint32_t v, uint32_t so
     if (rows) R = rs_rows(A, v, so, ns, gi, ci, lane);
     RsKept k = {INF, INF, 0.f, 0.f, 0u, 0u};
     auto store = [](void *to, uint32_t a, uint32_t b, uint32_t c, uint32_t d) { *static_cast<uint4 *>(to) = uint4{a, b, c, d}; };
-    if (with_g) {
-        const RsGive a = rows ? rs_down_gpu_rows(A, R, R.curve, gi, ci, lane) : rs_down_gpu_at(A, v, gi, ci, lane, LANES);
+    if (parts & RS_UP_G) {
         const RsStep u = rows ? rs_up_gpu_rows(A, R, gi, ci, lane) : rs_up_gpu(A, v, gi, ci, lane, LANES);
         k.g = rows ? rs_lane_u(R.g, gi) : (uint32_t)rs_g(A, v, gi);
-        k.ds_g = a.any ? a.slope : INF;
         k.ug = u.any ? u.slope : 0.f; k.dg = (uint32_t)u.dg;
-        RsShrunk s = {a, -1, 0u, INF, INF};
-        if (a.any) s = rows ? rs_shrunk_rows(A, R, 0, gi, ci, a, lane) : rs_shrunk_at(A, v, 0, gi, ci, a, lane, LANES);
         if (lane == 0) {
             auto up = [&](RsNext *to) {
                 store(&to->ug, __float_as_uint(k.ug), k.dg, __float_as_uint(u.gain), u.any ? (uint32_t)u.tgt : 0xFFFFFFFFu);
@@ -482,20 +481,21 @@ __device__ __forceinline__ RsKept rs_keep(const Args &A, uint32_t v, uint32_t so
             };
             up(A.next + v);
             if (also) up(also);
-            if (gi >= 0) {
-                RsGives *to = gives;
-                store(&to->dg0, (uint32_t)a.dg, __float_as_uint(a.loss), ((uint32_t)gi << 16) | ((uint32_t)s.gi & 0xFFFFu), __float_as_uint(s.ds_g));
-                store(&to->ds_c0, __float_as_uint(s.ds_c), __float_as_uint(k.ds_g), (uint32_t)a.dc, (uint32_t)(a.dc >> 32));
-            }
         }
     }
-    if (with_c) {
-        const RsGive b = rows ? rs_down_cpu_rows(A, R, gi, ci, rs_lane_f(R.best, gi), rs_lane_f(R.best_lo, gi)) : rs_down_cpu_at(A, v, gi, ci);
+    if (parts & RS_DOWN_G) {
+        const RsGive a = rows ? rs_down_gpu_rows(A, R, R.curve, gi, ci, lane) : rs_down_gpu_at(A, v, gi, ci, lane, LANES);
+        k.ds_g = a.any ? a.slope : INF;
+        RsShrunk s = {a, -1, 0u, INF, INF};
+        if (a.any) s = rows ? rs_shrunk_rows(A, R, 0, gi, ci, a, lane) : rs_shrunk_at(A, v, 0, gi, ci, a, lane, LANES);
+        if (lane == 0 && gi >= 0) {
+            store(&gives->dg0, (uint32_t)a.dg, __float_as_uint(a.loss), ((uint32_t)gi << 16) | ((uint32_t)s.gi & 0xFFFFu), __float_as_uint(s.ds_g));
+            store(&gives->ds_c0, __float_as_uint(s.ds_c), __float_as_uint(k.ds_g), (uint32_t)a.dc, (uint32_t)(a.dc >> 32));
+        }
+    }
+    if (parts & RS_UP_C) {
         const RsStep u = rows ? rs_up_cpu_rows(A, R, gi, ci, lane) : rs_up_cpu(A, v, gi, ci, lane, LANES);
-        k.ds_c = b.any ? b.slope : INF;
         k.uc = u.any ? u.slope : 0.f;
-        RsShrunk s = {b, -1, 0u, INF, INF};
-        if (b.any) s = rows ? rs_shrunk_rows(A, R, 1, gi, ci, b, lane) : rs_shrunk_at(A, v, 1, gi, ci, b, lane, LANES);
         if (lane == 0) {
             auto up = [&](RsNext *to) {
                 store(&to->uc, __float_as_uint(k.uc), __float_as_uint(u.gain), u.lvl, (uint32_t)slot);
@@ -503,11 +503,16 @@ __device__ __forceinline__ RsKept rs_keep(const Args &A, uint32_t v, uint32_t so
             };
             up(A.next + v);
             if (also) up(also);
-            if (gi >= 0) {
-                RsGives *to = gives;
-                store(&to->loss1, __float_as_uint(b.loss), __float_as_uint(s.ds_g), __float_as_uint(s.ds_c), __float_as_uint(k.ds_c));
-                store(&to->dc1, (uint32_t)b.dc, (uint32_t)(b.dc >> 32), ci | (ns << 8), so);
-            }
+        }
+    }
+    if (parts & RS_DOWN_C) {
+        const RsGive b = rows ? rs_down_cpu_rows(A, R, gi, ci, rs_lane_f(R.best, gi), rs_lane_f(R.best_lo, gi)) : rs_down_cpu_at(A, v, gi, ci);
+        k.ds_c = b.any ? b.slope : INF;
+        RsShrunk s = {b, -1, 0u, INF, INF};
+        if (b.any) s = rows ? rs_shrunk_rows(A, R, 1, gi, ci, b, lane) : rs_shrunk_at(A, v, 1, gi, ci, b, lane, LANES);
+        if (lane == 0 && gi >= 0) {
+            store(&gives->loss1, __float_as_uint(b.loss), __float_as_uint(s.ds_g), __float_as_uint(s.ds_c), __float_as_uint(k.ds_c));
+            store(&gives->dc1, (uint32_t)b.dc, (uint32_t)(b.dc >> 32), ci | (ns << 8), so);
         }
     }
     return k;

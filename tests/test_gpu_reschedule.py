@@ -404,6 +404,41 @@ def test_a_step_that_many_jobs_give_to(gpu, orc, J, take, each):
     assert want[0]["g"][0] == take and np.sum(want[0]["g"][1:] < each) >= take // 2
 
 
+@pytest.mark.parametrize("J,n_cpu,per_gpu,ties", [(60, 4, 1, False), (255, 4, 1, True), (257, 4, 1, False), (511, 2, 0, False), (513, 2, 0, True),
+                                                  (1100, 4, 1, False), (1300, 2, 0, True), (3000, 2, 1, False)])
+@pytest.mark.parametrize("floors", [False, True])
+def test_lists_of_many_holders(gpu, orc, J, n_cpu, per_gpu, ties, floors):
+    """Nearly every job holds something, on less than they hold: searches over lists of one load per lane, of two and of
+    more, slopes that one place has or (ties) many; steps that change few jobs and many."""
+    rng = np.random.default_rng(J + n_cpu)
+    bounds = workloads.Bounds(g_max=16)
+    ints = np.tile(np.array([[96, 1680, 1]], np.uint32), (J, 1))
+    tb = orc.enumerate_plans(ints, bounds)
+    ns = int(tb.seg_off[1])
+    g, c = tb.seg_g[:ns].astype(np.float64)[None, None, :], np.arange(1, n_cpu + 1)[None, :, None]
+    a, b = rng.uniform(0.5, 0.9, (J, 1, 1)), rng.uniform(0.5, 0.9, (J, 1, 1))
+    bt = (g ** a * (1 + 0.05 * c ** b)).reshape(-1)
+    bt = (np.round(bt * 4) / 4 if ties else bt).astype(np.float32)
+    bp = rng.integers(0, 1000, bt.size).astype(np.uint32)
+    grid = workloads.Grid(np.arange(1, n_cpu + 1, dtype=np.uint32), per_gpu, np.array([64.0], np.float32), 0)
+    ct, _, _ = orc.curves(tb, grid, bt, bp)
+    cur_seg = np.where(rng.uniform(size=J) < 0.95, rng.integers(0, 4, J), -1).astype(np.int32)
+    cur_c = np.where(cur_seg >= 0, rng.integers(0, n_cpu, J), 0).astype(np.uint32)
+    held = tb.seg_g[np.maximum(cur_seg, 0)] * (cur_seg >= 0)
+    cpus = ((cur_c + 1) * (held if per_gpu else cur_seg >= 0)).sum()
+    cl = workloads.Cluster(int(held.sum() * 0.97), int(cpus * 0.97), 1e9)
+    floor_seg = np.where(rng.uniform(size=J) < 0.2, rng.integers(0, 3, J), -1).astype(np.int32) if floors else None
+    floor_c = np.zeros(J, np.uint32) if floors else None
+    coef = np.tile(workloads.tiny().coef[:1], (J, 1))
+    coef[:, 16] = 1.0 if ties else rng.uniform(0.5, 4.0, J)
+    wl = workloads.Workload("holders", coef, ints, bounds, grid, workloads.Env(), cl)
+    want = orc.reschedule(coef[:, 16], tb, grid, cl, bt, bp, ct, cur_seg, cur_c, floor_seg, floor_c)
+    run = gpu(wl)
+    run.enumerate()
+    same(on_gpu(run, bt, bp, ct, cl, cur_seg, cur_c, floor_seg, floor_c, None), want)
+    run.close()
+
+
 def test_argument_errors(gpu, orc):
     import paper_2408_08586_amd as rk
     wl = workloads.tiny()
