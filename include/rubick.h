@@ -574,7 +574,7 @@ typedef struct {
  *   - a job holding GPUs pays owed seconds out of the tick, then trains at the
  *     round's throughput; it finishes inside the tick at t + paid + remaining/thr.
  * Times and progress are float64.  Runs in order with the work on the context's
- * stream.  Policy 0 has rounds for few jobs (256, or 128 / 64 where a job has
+ * stream.  Policy 0 has rounds for few jobs (about 300, or 128 / 64 where a job has
  * more than 16 / 32 GPU counts) in one workgroup, many ticks per launch; a
  * simulation of up to 1,024 jobs of at most 64 GPU counts has the others as
  * launches in between.  Policy 2 runs many ticks per launch while nodes and jobs

@@ -1528,6 +1528,7 @@ constexpr uint32_t FEW_JOBS = FEW_THREADS;        // at most a job per thread
 constexpr uint32_t FEW_GPU_LANES = 2048, FEW_CPU_LANES = 4096;   // of a round: jobs times lanes of a job
 constexpr uint32_t FEW_BINS = 1024, FEW_FINE = 128;
 constexpr uint32_t FEW_TICK_LANES = 4096;         // of a tick of a simulation (k_sim_few): jobs that take part times lanes of a job
+constexpr uint32_t FEW_TICK_LANES_16 = 5120;      // ... where no walk has more than 16 steps
 constexpr uint32_t FEW_TICK_WALK = 64;            // ... steps over CPU levels that a wavefront walks, one job or group of jobs after the other
 constexpr size_t FEW_SIM_LDS = 152 * 1024;
 
@@ -1535,7 +1536,7 @@ struct FewMem {                  // per round, in LDS
     unsigned long long *hc;      // histogram of a pass: CPUs and GPUs of the steps per bin
     uint32_t *hg;
     uint32_t *lvl;               // CPU levels
-    uint32_t *range;             // highest and lowest key of the pass's walks; most steps that a wavefront walked
+    uint32_t *range;             // highest and lowest key of the pass's walks; steps that the first wavefront walked
     // per job of the round: where its segments are, its reference throughput, what it holds
     uint32_t *s0, *ns;
     float *ref;
@@ -1682,8 +1683,9 @@ __device__ __forceinline__ uint32_t few_cut(const FewMem &M, unsigned long long 
 }
 
 // A pass over the P jobs in M.part.  On entry the histogram is clear; on return (behind a barrier) M.gi, M.g and M.ci
-// hold what the pass leaves, freeG / freeC what is left.
-template <int PASS>
+// hold what the pass leaves, freeG / freeC what is left.  COUNT: M.range[2] is how many steps the first wavefront walked (the
+// others have as many jobs, or a turn less).
+template <int PASS, bool COUNT = false>
 __device__ __forceinline__ void few_pass(const Ctx &X, const FewMem &M, const FewLanes &L, uint32_t P, uint32_t lanes,
                                          uint32_t first_seg, unsigned long long &freeG, unsigned long long &freeC) {
     const GridDev &grid = X.grid;
@@ -1733,7 +1735,7 @@ __device__ __forceinline__ void few_pass(const Ctx &X, const FewMem &M, const Fe
         float prev = __uint_as_float(0x7F800000u);
         bool walking = valid;
         while (__ballot(walking)) {
-            if (PASS == 1) ++walked;
+            if (COUNT) ++walked;
             uint32_t best = 0;
             if (walking && can && (int32_t)sub > cur_i && v > cur) {
                 float sl = (v - cur) / ref;
@@ -1779,7 +1781,7 @@ __device__ __forceinline__ void few_pass(const Ctx &X, const FewMem &M, const Fe
     high = wave_max_u32_rows(high);
     low = wave_min_u32_rows(low);
     if (lane == 0 && high) { atomicMax(&M.range[0], high); atomicMin(&M.range[1], low); }
-    if (PASS == 1 && lane == 0) atomicMax(&M.range[2], walked);
+    if (COUNT && tid == 0) M.range[2] = walked;
     __syncthreads();
     // The threshold: steps whose key lies less than `limit` below the highest one.  Any threshold whose whole set of steps
     // fits selects a prefix of the order: FEW_BINS bins over the keys that occur, and what is left of the bin where the
@@ -2019,20 +2021,11 @@ __global__ __launch_bounds__(FEW_THREADS) void k_round_few(Ctx X, JobState st, u
     few_memory(X, M, rnd, nj, first_seg, sums, assign + jrel0, totals);
 }
 
-// A pass whose per-lane words lie in LDS where they fit, else in memory.
-template <int PASS>
-__device__ __forceinline__ void few_pass_anywhere(const Ctx &X, const FewMem &M, uint32_t *lds_lanes, uint32_t near, uint32_t *far,
-                                                  uint32_t n_far, uint32_t P, uint32_t lanes, uint32_t first_seg,
-                                                  unsigned long long &freeG, unsigned long long &freeC) {
-    if (P * lanes <= near) few_pass<PASS>(X, M, few_lane_mem(lds_lanes, near), P, lanes, first_seg, freeG, freeC);
-    else few_pass<PASS>(X, M, few_lane_mem(far, n_far), P, lanes, first_seg, freeG, freeC);
-}
-
 // Ticks of a simulation of at most FEW_JOBS jobs under the greedy, in one workgroup: what a job does between
 // the ticks stays in its thread's registers, a round is k_round_few's.  A tick that starts from what the last round started
 // from has that round's result.  As launches of their own (the round's four kernels and k_sim_step, replayed as a graph)
 // a tick with a round took 40 us, most of it launches and what one kernel leaves for the next in memory: 406 jobs on 64
-// GPUs, 720 ticks 19.2 ms then, 9.4 now; 30 jobs 8.2 us per tick and 2.7.
+// GPUs, 720 ticks 19.2 ms then, 9.1 now; 30 jobs 8.2 us per tick and 2.7.
 // The walks of a round for many jobs keep one workgroup busy for longer than that: such a tick, and every one after it, is
 // left to the launches until the rounds are for fewer jobs again.  So are the ticks after one that walked long over the CPU
 // levels, for a while (as many lanes cost 4 us where curves are flat there, as the model's mostly are, and 100 where every
@@ -2042,12 +2035,18 @@ __device__ __forceinline__ void few_pass_anywhere(const Ctx &X, const FewMem &M,
 //     4,096 lanes   256 jobs of 16   31 and 20, 56 and 40, 56 and 25    36 and 21, 97 and 79, 122 and 87
 //                   128 jobs of 32   17 and 9, 41 and 25, 72 and 34     20 and 11, 48 and 34, 131 and 62
 //                   64 jobs of 64    18 and 7, 43 and 30, 71 and 32     20 and 7, 55 and 34, 127 and 53
+//     5,120 lanes   320 jobs of 16   27 and 20, 57 and 44, 54 and 26    37 and 26, 110 and 90, 122 and 94
 //     8,192 lanes   512 jobs of 16   44 and 60, 62 and 68, 57 and 30    51 and 60, 124 and 153, 129 and 150
 //                   256 jobs of 32   28 and 32, 57 and 81, 82 and 49    37 and 37, 93 and 118, 141 and 102
 //                   128 jobs of 64   17 and 15, 43 and 41, 81 and 47    21 and 16, 51 and 49, 132 and 77
 //     16,000 lanes  1,000 jobs of 16 58 and 132, 67 and 115, 63 and 48  62 and 145, 135 and 311, 145 and 286
-// With both lines every one of these takes what the faster way takes, give or take 4 %; 406 jobs on 64 GPUs keep 9.4 ms.
+// (where nobody is ever frozen 160 jobs of 32 take 37 us here and 29 as launches, 128 of them 30 and 28).  With both lines
+// every one of these takes what the faster way takes, give or take 2 %, or up to 10 % of 100 ticks where they begin with
+// long walks.  406 jobs on 64 GPUs over 720 ticks: 19.2 ms as launches, 9.1.
 // first: the simulation begins with this launch; otherwise the state is where the launch before left it.
+// OFTEN: rounds for more than `most` jobs and long walks may occur; FAR: a CPU pass may have more lanes than LDS (`near`), its
+// words are in memory then (n_far of them).
+template <bool OFTEN, bool FAR>
 __global__ __launch_bounds__(FEW_THREADS) void k_sim_few(Ctx X, SimArgs A, uint32_t first, uint32_t go_on, uint32_t most, uint32_t lanes0,
                                                          uint32_t lanes1, uint32_t near, uint32_t *far, uint32_t n_far,
                                                          rk_assign *__restrict__ assign, float *__restrict__ tick_total) {
@@ -2056,11 +2055,13 @@ __global__ __launch_bounds__(FEW_THREADS) void k_sim_few(Ctx X, SimArgs A, uint3
     __shared__ unsigned long long frozen_c[2];
     __shared__ uint32_t frozen_g[2], frozen_n[2], used_g[2];   // of a tick, in two copies used in turn
     const uint32_t tid = threadIdx.x, J = A.n_jobs, first_seg = X.tb.seg_off[0];
-    uint32_t tick = first ? 0u : A.tick[0];
-    if (tick >= A.n_ticks || (go_on && A.tick[1])) return;     // (the simulation is over; the launch before was stopped)
-    const uint32_t end = A.n_ticks - tick > SIM_FEW_TICKS ? tick + SIM_FEW_TICKS : A.n_ticks;
+    uint32_t tick = first ? 0u : (uint32_t)__builtin_amdgcn_readfirstlane((int)A.tick[0]);
+    if (tick >= A.n_ticks) return;                             // (the simulation is over)
+    if (OFTEN && go_on && A.tick[1]) return;                   // (the launch before was stopped)
+    uint32_t end = A.n_ticks - tick > SIM_FEW_TICKS ? tick + SIM_FEW_TICKS : A.n_ticks;
     uint32_t *lds_lanes;
     const FewMem M = few_mem(lds_few, J, &lds_lanes);
+    const FewLanes L = few_lane_mem(lds_lanes, near);
     few_jobs(X, M, 0u, J);
     SimJob s = {0u, 0u, RK_NO_PLAN, 0u, 0.0, 0.0, 0.0, -1.0, false};
     int32_t seg = -1;
@@ -2079,9 +2080,9 @@ __global__ __launch_bounds__(FEW_THREADS) void k_sim_few(Ctx X, SimArgs A, uint3
     Floor fl = {-1, 0u, RK_JOB_OUT};
     rk_assign a = {0u, 0u, 0.f, RK_NO_PLAN, 0.f};
     float total = 0.f;
-    bool stop = false;
     __syncthreads();
-    for (bool known = false; tick < end && !stop; ++tick, known = true) {
+    if (OFTEN && tid == 0) A.tick[1] = 0u;                     // (all have read it)
+    for (bool known = false; tick < end; ++tick, known = true) {
         const double t = (double)tick * A.dt;
         const uint32_t half = tick & 1u;
         // opens the tick: who takes part, who is frozen and what they hold
@@ -2108,15 +2109,21 @@ __global__ __launch_bounds__(FEW_THREADS) void k_sim_few(Ctx X, SimArgs A, uint3
             }
             few_clear(M);
             uint32_t P = few_compact(M, J, [&](uint32_t) { return fl.state == RK_JOB_NORMAL && freeG != 0; });
-            stop = P > most;
-            if (stop) break;                                   // (nothing of this tick is in the state yet)
-            if (P) few_pass_anywhere<0>(X, M, lds_lanes, near, far, n_far, P, lanes0, first_seg, freeG, freeC);
+            if (OFTEN && (uint32_t)__builtin_amdgcn_readfirstlane((int)P) > most) {                           // (nothing of this tick is in the state yet)
+                if (tid == 0) A.tick[1] = 1u;
+                break;
+            }
+            if (P) few_pass<0>(X, M, L, P, lanes0, first_seg, freeG, freeC);
             few_clear(M);
             P = few_compact(M, J, [&](uint32_t j) { return fl.state == RK_JOB_NORMAL && M.gi[j] >= 0 && freeC != 0; });
-            if (P) few_pass_anywhere<1>(X, M, lds_lanes, near, far, n_far, P, lanes1, first_seg, freeG, freeC);
+            if (FAR && P * lanes1 > near) few_pass<1, OFTEN>(X, M, few_lane_mem(far, n_far), P, lanes1, first_seg, freeG, freeC);
+            else if (P) few_pass<1, OFTEN>(X, M, L, P, lanes1, first_seg, freeG, freeC);
             a = few_memory(X, M, 0u, J, first_seg, sums, assign, tick_total);
             __syncthreads();                                   // the round is closed
-            stop = M.range[2] > FEW_TICK_WALK;                 // (the next one is as long, as a rule)
+            if (OFTEN && (uint32_t)__builtin_amdgcn_readfirstlane((int)M.range[2]) > FEW_TICK_WALK) {         // (the next one is as long, as a rule)
+                if (tid == 0) A.tick[1] = 1u;
+                end = tick + 1u;
+            }
             if (M.box[0] && mine) a = assign[tid];             // ... by decisions in job order
             if (tid == 0) total = *tick_total;                 // (its own store)
         }
@@ -2143,8 +2150,8 @@ __global__ __launch_bounds__(FEW_THREADS) void k_sim_few(Ctx X, SimArgs A, uint3
         A.held[tid] = s.held; A.progress[tid] = s.progress; A.finish[tid] = s.finish; A.n_reconf[tid] = s.n_reconf;
     }
     if (tid == 0) {
-        A.tick[0] = tick; A.tick[1] = stop ? 1u : 0u;
-        if (A.h_tick) {
+        A.tick[0] = tick;
+        if (OFTEN) {
             __hip_atomic_store(A.h_tick + 1, M.range[2] > FEW_TICK_WALK ? SIM_LONG_WALK : 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
             __hip_atomic_store(A.h_tick, tick, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
         }
@@ -3039,7 +3046,9 @@ int32_t rk_allocate_setup(rk_ctx *ctx) {
                            reinterpret_cast<const void *>(k_select_small<0, 1, TAIL_THREADS>), reinterpret_cast<const void *>(k_select_small<1, 1, TAIL_THREADS>),
                            reinterpret_cast<const void *>(k_select_small<0, 1, TAIL_THREADS / 2>), reinterpret_cast<const void *>(k_select_small<1, 1, TAIL_THREADS / 2>)};
     RK_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(k_round_few), hipFuncAttributeMaxDynamicSharedMemorySize, 144 * 1024));
-    RK_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(k_sim_few), hipFuncAttributeMaxDynamicSharedMemorySize, FEW_SIM_LDS));
+    const void *sim[] = {reinterpret_cast<const void *>(k_sim_few<false, false>), reinterpret_cast<const void *>(k_sim_few<true, false>),
+                         reinterpret_cast<const void *>(k_sim_few<true, true>)};
+    for (const void *f : sim) RK_HIP(ctx, hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, FEW_SIM_LDS));
     for (const void *f : small) RK_HIP(ctx, hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024));
     return RK_OK;
 }
@@ -3158,33 +3167,37 @@ int32_t rk_launch_allocate(rk_ctx *ctx, const float *ref_thr, const TableDev &tb
     return RK_OK;
 }
 
+// LDS of k_sim_few but the words per lane, and the lanes that fit beside it.
+static size_t few_sim_job_lds(uint32_t n_jobs) { return FEW_FIXED_BYTES + (size_t)((n_jobs + 3u) & ~3u) * FEW_JOB_BYTES; }
+static uint32_t few_sim_room(uint32_t n_jobs) { return (uint32_t)((FEW_SIM_LDS - few_sim_job_lds(n_jobs)) / FEW_LANE_BYTES) & ~63u; }
+
 SimFew rk_sim_few(uint32_t n_jobs, uint32_t max_segs_per_job, const rk_alloc_grid *grid, const rk_cluster *cluster, uint32_t *most) {
     *most = 0;
     if (n_jobs > FEW_JOBS || max_segs_per_job > 64u) return SIM_NOT_FEW;
-    *most = FEW_TICK_LANES / few_lanes(max_segs_per_job);
-    const uint32_t holders = cluster->G < n_jobs ? cluster->G : n_jobs, lanes = few_lanes(grid->n_cpu);
-    const uint32_t turns = (holders * lanes + FEW_THREADS - 1u) / FEW_THREADS;
-    return n_jobs <= *most && turns * grid->n_cpu <= FEW_TICK_WALK ? SIM_ALWAYS_FEW : SIM_OFTEN_FEW;
+    const uint32_t lanes0 = few_lanes(max_segs_per_job), line = lanes0 == 16u ? FEW_TICK_LANES_16 : FEW_TICK_LANES, room = few_sim_room(n_jobs);
+    *most = (line < room ? line : room) / lanes0;              // (the GPU pass is in LDS)
+    const uint32_t holders = cluster->G < n_jobs ? cluster->G : n_jobs, lanes = holders * few_lanes(grid->n_cpu);
+    const uint32_t turns = (lanes + FEW_THREADS - 1u) / FEW_THREADS;
+    return n_jobs <= *most && lanes <= room && turns * grid->n_cpu <= FEW_TICK_WALK ? SIM_ALWAYS_FEW : SIM_OFTEN_FEW;
 }
 
 int32_t rk_launch_sim_few(rk_ctx *ctx, const SimArgs &A, const float *ref_thr, const rk_alloc_grid *grid, uint32_t max_segs_per_job,
                           const float *best_thr, const uint32_t *best_plan, const float *curve_thr, rk_assign *assign,
-                          uint32_t n_launches, bool begin, uint32_t most) {
+                          uint32_t n_launches, bool begin, bool often, uint32_t most) {
     const uint32_t J = A.n_jobs, lanes0 = few_lanes(max_segs_per_job), lanes1 = few_lanes(grid->n_cpu);
     Ctx X;
     X.ref_thr = ref_thr; X.tb = A.tb; X.grid = A.grid; X.jb = 0; X.jmap = nullptr;
     X.best_thr = best_thr; X.best_plan = best_plan; X.curve_thr = curve_thr;
     X.R = RoundArgs{nullptr, nullptr, 1u, 1u, 0u, J, A.cl};
     const uint32_t part = J < most ? J : most, holders = A.cl.G < part ? A.cl.G : part, gpu = part * lanes0, cpu = holders * lanes1;
-    const uint32_t need = gpu > cpu ? gpu : cpu;
-    const size_t job_lds = FEW_FIXED_BYTES + (size_t)((J + 3u) & ~3u) * FEW_JOB_BYTES;
-    const uint32_t room = (uint32_t)((FEW_SIM_LDS - job_lds) / FEW_LANE_BYTES) & ~63u, near = need < room ? need : room;
+    const uint32_t need = gpu > cpu ? gpu : cpu, room = few_sim_room(J), near = need < room ? need : room;
     uint32_t *far = nullptr;
     int32_t rc;
-    if (need > near && (rc = rk_scratch(ctx, SL_HULL_KEY, (size_t)need * FEW_LANE_BYTES, (void **)&far))) return rc;
+    if (cpu > near && (rc = rk_scratch(ctx, SL_HULL_KEY, (size_t)cpu * FEW_LANE_BYTES, (void **)&far))) return rc;
+    auto *kernel = !often ? k_sim_few<false, false> : far ? k_sim_few<true, true> : k_sim_few<true, false>;      // (always in LDS: rk_sim_few)
     for (uint32_t i = 0; i < n_launches; ++i) {
-        k_sim_few<<<1, FEW_THREADS, job_lds + (size_t)near * FEW_LANE_BYTES, ctx->stream>>>(X, A, begin && i == 0 ? 1u : 0u, i ? 1u : 0u, most, lanes0,
-                                                                                         lanes1, near, far, need, assign, A.tick_total);
+        kernel<<<1, FEW_THREADS, few_sim_job_lds(J) + (size_t)near * FEW_LANE_BYTES, ctx->stream>>>(
+            X, A, begin && i == 0 ? 1u : 0u, i ? 1u : 0u, most, lanes0, lanes1, near, far, cpu, assign, A.tick_total);
         RK_CHECK_LAUNCH(ctx, "k_sim_few");
     }
     return RK_OK;

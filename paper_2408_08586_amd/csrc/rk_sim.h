@@ -147,7 +147,7 @@ __device__ __forceinline__ bool sim_ticks(const SimArgs &A, uint32_t &tick, bool
     __shared__ uint32_t sum_f, sum_used, moved, sum_p;
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
     for (;;) {
-        if (tid == 0) { sum_g = 0ull; sum_c = 0ull; sum_f = 0u; sum_used = 0u; moved = 0u; sum_p = 0u; }
+        if (tid == 0) { sum_g = 0ull; sum_c = 0ull; sum_f = 0u; sum_used = 0u; moved = 0u; if (COUNT) sum_p = 0u; }
         __syncthreads();
         if (!first) {
             const double t = (double)tick * A.dt;
@@ -226,7 +226,7 @@ SimFew rk_sim_few(uint32_t n_jobs, uint32_t max_segs_per_job, const rk_alloc_gri
 // more than `most` jobs ends them, and stays open; one whose walks were long ends them when it is closed.
 int32_t rk_launch_sim_few(rk_ctx *ctx, const SimArgs &A, const float *ref_thr, const rk_alloc_grid *grid, uint32_t max_segs_per_job,
                           const float *best_thr, const uint32_t *best_plan, const float *curve_thr, rk_assign *assign,
-                          uint32_t n_launches, bool begin, uint32_t most);
+                          uint32_t n_launches, bool begin, bool often, uint32_t most);
 
 // Whether a simulation over these nodes has its ticks in one workgroup's LDS, and all its ticks (rk_nodes.hip).
 bool rk_sim_nodes_fit(uint32_t n_jobs, const rk_nodes *nodes);

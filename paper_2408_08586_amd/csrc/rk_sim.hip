@@ -160,7 +160,8 @@ extern "C" int32_t rk_simulate(rk_ctx *ctx, const float *ref_thr, const rk_plan_
     uint32_t most = 0;                                         // jobs of a round for k_sim_few
     const SimFew few = options->policy == 0u ? rk_sim_few(J, table->max_segs_per_job, grid, cluster, &most) : SIM_NOT_FEW;
     auto launch_few = [&](uint32_t n_launches, bool begin) {
-        return rk_launch_sim_few(ctx, A, ref_thr, grid, table->max_segs_per_job, best_thr, best_plan, curve_thr, assign, n_launches, begin, most);
+        return rk_launch_sim_few(ctx, A, ref_thr, grid, table->max_segs_per_job, best_thr, best_plan, curve_thr, assign, n_launches, begin,
+                                 few == SIM_OFTEN_FEW, most);
     };
     const uint32_t n = options->n_ticks;
     if (few == SIM_ALWAYS_FEW) {                               // whole ticks in one kernel
@@ -228,7 +229,7 @@ extern "C" int32_t rk_simulate(rk_ctx *ctx, const float *ref_thr, const rk_plan_
     uint32_t closed = 0, wait = SIM_WAIT_LEAST, wait_for = 0;  // after long walks: launches for so many ticks, until that tick
     auto told = [&](int word) { return __atomic_load_n(ctx->h_pinned + H_TICK + word, __ATOMIC_ACQUIRE); };
     auto few_again = [&]() {                                   // (not back and forth)
-        return few == SIM_OFTEN_FEW && closed < n && closed >= wait_for && told(1) <= most - most / 4u;
+        return few == SIM_OFTEN_FEW && closed < n && closed >= wait_for && told(1) <= most - most / 8u;
     };
     auto as_launches = [&]() -> int32_t {
         // Replays go out in batches, one batch ahead of the counter that is read back, never more of them than ticks

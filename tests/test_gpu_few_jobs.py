@@ -91,7 +91,7 @@ def long_walks(orc, n_jobs, kind, g_max, n_cpu, per_gpu, rng):
 
 
 # n_jobs, kind of job, g_max, GPU counts per job, CPU levels, per GPU, GPUs per job of the cluster, ways: k_sim_few, launches
-TURNS = [(256, (96, 1680, 1), 16, 16, 5, 1, 1.0, "f"), (257, (96, 1680, 1), 16, 16, 5, 1, 0.25, "fl"), (128, (96, 1680, 1), 64, 32, 5, 1, 2.0, "f"),
+TURNS = [(320, (96, 1680, 1), 16, 16, 5, 1, 1.0, "f"), (321, (96, 1680, 1), 16, 16, 5, 1, 0.25, "fl"), (128, (96, 1680, 1), 64, 32, 5, 1, 2.0, "f"),
          (129, (96, 1680, 1), 64, 32, 16, 0, 1.0, "fl"), (64, (96, 1680, 1), 256, 64, 16, 0, 8.0, "f"), (65, (96, 1680, 1), 256, 64, 17, 0, 8.0, "fl"),
          (256, (96, 1680, 1), 16, 16, 64, 0, 8.0, "fl"), (64, (96, 1680, 1), 64, 32, 64, 0, 8.0, "fl"), (30, (96, 1680, 1), 256, 64, 33, 0, 0.4, "f"),
          (700, (96, 1680, 1), 16, 16, 33, 0, 0.5, "fl"), (1024, (96, 1680, 1), 16, 16, 5, 1, 0.5, "fl"), (1025, (96, 1680, 1), 16, 16, 5, 1, 0.5, "l"),
