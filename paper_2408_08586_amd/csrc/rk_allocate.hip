@@ -1234,9 +1234,9 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_tail(Ctx X, uint32_t max_jobs,
 // ------------------------------------------------------------------ selection of a pass in one workgroup
 // For rounds of at most SMALL_ROUND_JOBS jobs the histograms, the threshold,
 // the application and the step-by-step tail of a pass run in one workgroup per
-// round, with the histograms in LDS: one launch instead of six (KMAX = jobs per
-// thread = 2).  The workgroup of the CPU pass also takes the memory step that
-// ends the round.  Larger rounds use the same kernel for their CPU pass
+// round, with the histograms in LDS: one launch instead of six (a job per thread
+// of 512 or 1,024, above 1,024 jobs two: KMAX).  The workgroup of the CPU pass
+// also takes the memory step that ends the round.  Larger rounds use the same kernel for their CPU pass
 // (KMAX = TAIL_KMAX, without the memory step) as long as all CPU walks together
 // are short, which the host can tell from the grid:
 // (CPU levels - 1) * jobs <= CPU_ONE_WG_STEPS.
@@ -1522,7 +1522,14 @@ __global__ __launch_bounds__(64) void k_mem_finish(Ctx X, JobState st, rk_assign
 // of its own over the whole chip takes 4 to 5 us for any number of jobs that comes into question.  Whole rounds on jobs
 // with up to 16 GPU counts, four launches and one: 8 jobs 48 and 39 us, 64 jobs 56 and 44, 128 jobs 58 and 52, 192 jobs
 // 64 and 62, 256 jobs 67 and 72.  Leaving the walks of larger rounds to a launch in front of this one brings nothing:
-// their threads wait for memory in every step instead (500 jobs 68 and 74 us, 1,000 jobs 79 and 92).
+// their threads wait for memory in every step instead (500 jobs 68 and 74 us, 1,000 jobs 79 and 92).  The same line holds
+// for many rounds in a call: 256 rounds of 64 jobs 132 and 103, 1,024 of 128 jobs 587 and 530, 4,096 of 8 jobs 572 and 555.
+// Jobs with up to 32 and 64 counts, the allocation alone on walks as long as they can be: 64 jobs of 31 49 and 50, 32 of 53
+// 52 and 37.
+// A round at FEW_CPU_LANES, 128 jobs at 32 CPU levels, is 60 and 48 us on the model's curves, 75 and 53 where nothing but
+// offload fits the GPUs; only where every one of the jobs holds GPUs and gains at every level, which curves handed in by
+// the caller can say and the model's do not, are its CPU walks too long for one workgroup: the allocation alone 59 and
+// 102, 64 jobs at 64 levels 91 and 154 (at half the lanes, 64 jobs at 32 levels, 60 and 54).
 constexpr int FEW_THREADS = 1024, FEW_WAVES = FEW_THREADS / 64;
 constexpr uint32_t FEW_JOBS = FEW_THREADS;        // at most a job per thread
 constexpr uint32_t FEW_GPU_LANES = 2048, FEW_CPU_LANES = 4096;   // of a round: jobs times lanes of a job

@@ -175,6 +175,7 @@ extern "C" int32_t rk_simulate(rk_ctx *ctx, const float *ref_thr, const rk_plan_
     A.h_tick = static_cast<uint32_t *>(h_tick);
     if (nodes && rk_sim_nodes_fit(J, nodes)) {                 // the nodes and jobs fit a workgroup's LDS: ticks without launches between them
         ctx->ways[WAY_SIM_NODES]++;
+        __atomic_store_n(ctx->h_pinned + H_TICK, 0u, __ATOMIC_RELEASE);    // (not what an earlier simulation ended with)
         k_sim_init<<<(J + SIM_THREADS - 1) / SIM_THREADS, SIM_THREADS, 0, ctx->stream>>>(A);
         RK_CHECK_LAUNCH(ctx, "k_sim_init");
         k_sim_step<<<1, SIM_THREADS, 0, ctx->stream>>>(A, 1u);

@@ -131,12 +131,13 @@ def test_ticks_take_turns(orc, n_jobs, kind, g_max, counts, n_cpu, per_gpu, gpus
     run.close()
 
 
-@pytest.mark.parametrize("n_jobs,n_ticks,gpn", [(1, 1, 8), (30, 64, 4), (60, 200, 8), (256, 65, 6), (257, 130, 8), (700, 60, 16), (1600, 20, 8)])
+@pytest.mark.parametrize("n_jobs,n_ticks,gpn", [(1, 1, 8), (30, 64, 4), (60, 200, 8), (256, 65, 6), (257, 130, 8), (700, 60, 16), (1600, 20, 8), (1416, 20, 8),
+                                                (1417, 20, 8)])
 @pytest.mark.parametrize("scarce", [False, True])
 def test_ticks_over_nodes_in_one_launch(orc, n_jobs, n_ticks, gpn, scarce):
     """k_sim_nodes: rounds around the end of a launch, one job per thread and more, jobs whose values fit LDS and (1,600 of
     them) do not; jobs that finish, thaw and lose their memory between the rounds."""
-    from gpu_harness import DeviceRun
+    from gpu_harness import DeviceRun, ways
     from test_gpu_sim import run_on_gpu, same
     base = workloads.trace_scale()
     coef, ints = np.resize(base.coef, (n_jobs, base.coef.shape[1])), np.resize(base.ints, (n_jobs, base.ints.shape[1]))
@@ -157,6 +158,9 @@ def test_ticks_over_nodes_in_one_launch(orc, n_jobs, n_ticks, gpn, scarce):
                                   delta, 60.0, n_ticks, gate=0.9, policy="nodes", nodes=nodes)
     for _ in range(2):                                          # (the second one finds the first one's working memory)
         same(run_on_gpu(run, r, arrival, work, delta, 60.0, n_ticks, 0.9, policy=2, nodes=nodes), want)
+    got = ways(run.ctx)                                         # (1,416 jobs on 10 nodes of 8 GPUs are the last that fit LDS, 1,421 on 3)
+    fits = n_jobs <= (1421 if scarce else 1416)
+    assert (got["sim_nodes"], got["sim_launches"]) == ((2, 0) if fits else (0, 2))
     run.close()
 
 
