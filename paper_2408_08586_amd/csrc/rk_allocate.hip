@@ -1526,13 +1526,15 @@ __global__ __launch_bounds__(64) void k_mem_finish(Ctx X, JobState st, rk_assign
 // for many rounds in a call: 256 rounds of 64 jobs 132 and 103, 1,024 of 128 jobs 587 and 530, 4,096 of 8 jobs 572 and 555.
 // Jobs with up to 32 and 64 counts, the allocation alone on walks as long as they can be: 64 jobs of 31 49 and 50, 32 of 53
 // 52 and 37.
-// A round at FEW_CPU_LANES, 128 jobs at 32 CPU levels, is 60 and 48 us on the model's curves, 75 and 53 where nothing but
-// offload fits the GPUs; only where every one of the jobs holds GPUs and gains at every level, which curves handed in by
-// the caller can say and the model's do not, are its CPU walks too long for one workgroup: the allocation alone 59 and
-// 102, 64 jobs at 64 levels 91 and 154 (at half the lanes, 64 jobs at 32 levels, 60 and 54).
+// CPU walks are too long for one workgroup where every one of many jobs holds GPUs and gains at every level, as curves
+// handed in by the caller may say: the allocation alone 59 and 102 us for 128 jobs at 32 levels, 91 and 154 for 64 at 64; at
+// FEW_CPU_LANES, 64 jobs at 32 levels and 128 at 16, 60 and 54, 48 and 48.  The curves of a round that evaluates the model
+// itself do not: at FEW_CPU_LANES_MODEL, whole rounds of 128 jobs at 32 levels 60 and 48, where nothing but offload fits the
+// GPUs 75 and 53, and 82 and 80 where only offload is allowed and every job that holds GPUs takes all CPUs.
 constexpr int FEW_THREADS = 1024, FEW_WAVES = FEW_THREADS / 64;
 constexpr uint32_t FEW_JOBS = FEW_THREADS;        // at most a job per thread
-constexpr uint32_t FEW_GPU_LANES = 2048, FEW_CPU_LANES = 4096;   // of a round: jobs times lanes of a job
+constexpr uint32_t FEW_GPU_LANES = 2048;          // of a round: jobs times lanes of a job, in the pass over GPUs
+constexpr uint32_t FEW_CPU_LANES = 2048, FEW_CPU_LANES_MODEL = 4096;   // ... and over CPUs, on curves handed in and on the model's
 constexpr uint32_t FEW_BINS = 1024, FEW_FINE = 128;
 constexpr uint32_t FEW_TICK_LANES = 4096;         // of a tick of a simulation (k_sim_few): jobs that take part times lanes of a job
 constexpr uint32_t FEW_TICK_LANES_16 = 5120;      // ... where no walk has more than 16 steps
@@ -3064,10 +3066,10 @@ int32_t rk_allocate_setup(rk_ctx *ctx) {
 static uint32_t few_holders(uint32_t max_jobs, const rk_cluster *one_cluster) {
     return one_cluster && one_cluster->G < max_jobs ? one_cluster->G : max_jobs;
 }
-bool rk_round_is_few(const rk_alloc_grid *grid, uint32_t max_jobs, uint32_t max_segs_per_job, const rk_cluster *one_cluster) {
+bool rk_round_is_few(const rk_alloc_grid *grid, uint32_t max_jobs, uint32_t max_segs_per_job, const rk_cluster *one_cluster, bool model_curves) {
     return max_jobs > 0 && max_jobs <= FEW_JOBS && max_segs_per_job <= 64u &&
            (uint64_t)max_jobs * few_lanes(max_segs_per_job) <= FEW_GPU_LANES &&
-           (uint64_t)few_holders(max_jobs, one_cluster) * few_lanes(grid->n_cpu) <= FEW_CPU_LANES;
+           (uint64_t)few_holders(max_jobs, one_cluster) * few_lanes(grid->n_cpu) <= (model_curves ? FEW_CPU_LANES_MODEL : FEW_CPU_LANES);
 }
 
 int32_t rk_launch_allocate(rk_ctx *ctx, const float *ref_thr, const TableDev &tb, const rk_alloc_grid *grid,
@@ -3075,7 +3077,7 @@ int32_t rk_launch_allocate(rk_ctx *ctx, const float *ref_thr, const TableDev &tb
                            const rk_cluster *one_cluster, uint32_t jb, uint32_t n_jobs, uint32_t max_jobs,
                            uint32_t max_segs_per_job, const float *best_thr, const uint32_t *best_plan,
                            const float *curve_thr, const SlaDev *sla, const FloorsDev *given, const uint32_t *d_jmap,
-                           rk_assign *assign, float *totals, bool static_scratch, const TableGuard *guard) {
+                           rk_assign *assign, float *totals, bool static_scratch, bool model_curves, const TableGuard *guard) {
     if (n_rounds == 0) return RK_OK;
     Arena arena = {nullptr, 0, 0};
     if (static_scratch) {
@@ -3096,7 +3098,7 @@ int32_t rk_launch_allocate(rk_ctx *ctx, const float *ref_thr, const TableDev &tb
     const uint32_t lanes0 = few_lanes(max_segs_per_job), lanes1 = few_lanes(grid->n_cpu);
     const uint32_t holders = few_holders(max_jobs, one_cluster);
     // (a simulation's tick that one workgroup takes well does not come here: k_sim_few)
-    const bool few = !given && rk_round_is_few(grid, max_jobs, max_segs_per_job, one_cluster);
+    const bool few = !given && rk_round_is_few(grid, max_jobs, max_segs_per_job, one_cluster, model_curves);
     if (guard && !few) return rk_fail(ctx, RK_ERR_UNSUPPORTED, "only the one launch of small rounds takes a guard");
     const size_t entries = few ? 0 : (size_t)H.stride * H.width;
     if ((rc = scratch_typed(ctx, arena, SL_HULL_KEY, entries, &H.key))) return rc;

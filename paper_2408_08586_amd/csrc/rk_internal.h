@@ -180,9 +180,11 @@ int32_t rk_launch_allocate(rk_ctx *ctx, const float *ref_thr, const TableDev &tb
                            const rk_cluster *one_cluster, uint32_t jb, uint32_t n_jobs, uint32_t max_jobs,
                            uint32_t max_segs_per_job, const float *best_thr, const uint32_t *best_plan,
                            const float *curve_thr, const SlaDev *sla, const FloorsDev *given, const uint32_t *d_jmap,
-                           rk_assign *assign, float *totals, bool static_scratch = false, const TableGuard *guard = nullptr);
-// Whether a single round takes the one launch of small rounds (only that one takes a guard).
-bool rk_round_is_few(const rk_alloc_grid *grid, uint32_t max_jobs, uint32_t max_segs_per_job, const rk_cluster *one_cluster);
+                           rk_assign *assign, float *totals, bool static_scratch = false, bool model_curves = false,
+                           const TableGuard *guard = nullptr);
+// model_curves: best_thr and curve_thr are what the model gives for the round's jobs, not what a caller handed in.
+// Whether a round takes the one launch of small rounds (only that one takes a guard).
+bool rk_round_is_few(const rk_alloc_grid *grid, uint32_t max_jobs, uint32_t max_segs_per_job, const rk_cluster *one_cluster, bool model_curves);
 // static_scratch: the working buffers are pieces of the library's static device array (nothing is allocated; a
 // round that needs more than the array holds is refused) instead of the context's grow-only buffers.
 // Once per context, device current: finds this device's copy of that array and raises the LDS limits of the

@@ -82,7 +82,7 @@ int32_t schedule_rounds(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_bounds *
     // outputs' room is then most_s per job, and a round of the same kind that is not sent takes as much, so that buffers grow
     // in the first call of a kind and not between the two halves of a later one's enumeration (66 us instead of 48).
     auto may_go_ahead = [&](uint32_t most) {
-        return n_rounds == 1 && !sla && !round_jobs && !keep && J > 0 && most <= 64u && rk_round_is_few(grid, J, most, &clusters[0]);
+        return n_rounds == 1 && !sla && !round_jobs && !keep && J > 0 && most <= 64u && rk_round_is_few(grid, J, most, &clusters[0], true);
     };
     auto have_room = [&](size_t n) {
         for (int slot : {SL_BEST_THR, SL_BEST_PLAN, SL_CURVE_THR, SL_CURVE_PLAN, SL_CURVE_G})
@@ -125,7 +125,7 @@ int32_t schedule_rounds(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_bounds *
             rc = outputs((size_t)(n_rows * segs), best_thr, best_plan, curve_thr, curve_plan, curve_g);
             if (!rc) rc = rk_launch_fused(ctx, jobs, &like, grid, env, 0, J, best_thr, best_plan, curve_thr, curve_plan, curve_g, &guard);
             if (!rc) rc = rk_launch_allocate(ctx, jobs->ref_thr, table_dev(&like), grid, 1, nullptr, nullptr, &clusters[0], 0, J, J, most_s,
-                                             best_thr, best_plan, curve_thr, nullptr, nullptr, nullptr, assign, totals, false, &guard);
+                                             best_thr, best_plan, curve_thr, nullptr, nullptr, nullptr, assign, totals, false, true, &guard);
             const int32_t rc_sent = rc;
             rc = rk_enumerate_end(ctx, &tb, P);
             if (!rc) rc = rc_sent;
@@ -168,7 +168,7 @@ int32_t schedule_rounds(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_bounds *
                               d_meta ? reinterpret_cast<const rk_cluster *>(d_meta + off_bytes) : nullptr,
                               n_rounds == 1 ? &clusters[0] : nullptr, 0, round_jobs ? n_slots : J, max_jobs,
                               tb.max_segs_per_job, best_thr, best_plan, curve_thr, (sla && J > 0) ? &S : nullptr, nullptr,
-                              d_jmap, assign, totals);
+                              d_jmap, assign, totals, false, true);
 }
 
 }  // namespace

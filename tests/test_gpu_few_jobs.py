@@ -305,3 +305,29 @@ def test_a_steady_round_is_sent_ahead_and_its_buffers_stay():
             grew = w["grew"]
     assert ahead > taken > 0                                    # (one guess at least was refused)
     rk.rk_destroy(ctx)
+
+
+@pytest.mark.parametrize("n_jobs,n_cpu,gpus,few", [(64, 32, 8.0, True), (128, 32, 8.0, True), (128, 33, 0.5, True), (128, 33, 8.0, False),
+                                                   (65, 64, 8.0, False), (64, 64, 8.0, True), (129, 17, 8.0, False)])
+def test_rounds_from_descriptors_at_the_cpu_line(orc, n_jobs, n_cpu, gpus, few):
+    """Rounds whose jobs may only offload, so that every job that holds GPUs walks all CPU levels, at the most lanes that one
+    launch takes and beyond: the records are the oracle's greedy on the device's own curves."""
+    import paper_2408_08586_amd as rk
+    from gpu_harness import DeviceRun, ways
+    coef, ints = workloads.draw_jobs(7, 11, 0, np.arange(n_jobs), param_buckets=[(1.0, 1e9, 4e9)], layer_choices=(12, 24, 32, 40))
+    G = int(gpus * n_jobs)
+    wl = workloads.Workload("offload", coef, ints, workloads.Bounds(g_max=16 if n_jobs > 64 else 64, off_mask=2),
+                            workloads.Grid(np.arange(1, n_cpu + 1, dtype=np.uint32), 0, np.array([64.0, 1024.0], np.float32), 0),
+                            workloads.Env(gpu_mem_cap=16e9), workloads.Cluster(G, n_cpu * n_jobs // 3, 3e4))
+    run = DeviceRun(wl)
+    for _ in range(3):
+        assign, total = run.schedule_round()
+    assert ways(run.ctx)["ahead_taken"] == (1 if few else 0)    # (what is sent ahead takes the one launch)
+    run.enumerate()
+    bt, bp, ct, _, _, n = run.fused()
+    ot = orc.enumerate_plans(wl.ints, wl.bounds)
+    assert np.diff(ot.seg_off.astype(np.int64)).max() <= 16
+    want, want_total, _ = orc.greedy(coef[:, 16], ot, wl.grid, wl.cluster, run.host(bt, n), run.host(bp, n).view(np.uint32), run.host(ct, n))
+    assert np.array_equal(assign, want) and total == pytest.approx(want_total, rel=1e-6)
+    assert (want["g"] > 0).sum() > 4 and want["c"].max() == n_cpu
+    run.close()
