@@ -2419,7 +2419,11 @@ __global__ void k_rs_prepare(RsArgs B) {
 // jobs in the first places give, as many as there is room for up to RS_NEAR (the others' is in memory).
 constexpr size_t RS_LDS_MOST = 136 * 1024;                  // 160 KiB less what the kernel declares
 constexpr uint32_t RS_NEAR = 512;
-static inline size_t rs_list_bytes(size_t J) { return ((J + 7) & ~(size_t)7) * (2 * sizeof(float) + sizeof(uint16_t)); }
+// Lists are whole rounds of a wavefront's loads long, infinite behind the holders: no load asks whether it is inside.
+constexpr uint32_t RS_LIST = 512;
+static_assert(RK_MAX_JOBS_PER_ROUND % RS_LIST == 0, "the longest list is not longer for it");
+__host__ __device__ inline uint32_t rs_list(uint32_t J) { return J ? (J + RS_LIST - 1u) & ~(RS_LIST - 1u) : RS_LIST; }
+static inline size_t rs_list_bytes(size_t J) { return (size_t)rs_list((uint32_t)J) * (2 * sizeof(float) + sizeof(uint16_t)); }
 static inline uint32_t rs_near(size_t J) {
     const size_t fit = (RS_LDS_MOST - rs_list_bytes(J)) / sizeof(RsGives), most = J < RS_NEAR ? J : RS_NEAR;
     return (uint32_t)(fit < most ? fit : most);
@@ -2430,9 +2434,11 @@ static inline uint32_t rs_near(size_t J) {
 // for a look after one.  10,000 jobs on 4,096 GPUs, 15 jobs on the full path, 22 steps committed, 49 shrinks: 374 -> 242 us;
 // 9,999 jobs with floors, several hundred steps: 4.2 -> 3.4 ms; while all wavefronts searched all jobs, with a barrier on
 // either side of every decision, and a look read seven values of every job from memory.  Where thousands hold something a
-// search by one wavefront takes longer than one by all: 4,486 holders, 5,297 steps 74.3 ms then and 70.3 now (95.3 with
-// every search in two passes of single loads), 42,980 steps of a CPU level 223 and 260 (329); 1,348 holders, 13,119 such
-// steps 62.7 and 65.5 (75.6); 29 holders, 244 steps 0.92 and 0.93 (1.03 with two wavefronts per changed job at all times).
+// search by one wavefront takes longer than one by all: 4,486 holders, 5,297 steps 74.0 ms then and 60.7 now (95.3 with
+// every search in two passes of single loads), 42,980 steps of a CPU level 222 and 235 (329); 1,348 holders, 13,119 such
+// steps 62.7 and 62.6 (75.6); 29 holders, 244 steps 0.93 and 0.93 (1.03 with two wavefronts per changed job at all times).
+// (A load that asks whether it is inside the list, and takes a constant where it is not, becomes flat loads from either
+// place: 70 and 260 ms.)
 template <int THREADS, int PER>
 __global__ __launch_bounds__(THREADS) void k_reschedule(RsArgs B) {
     constexpr uint32_t WAVES = THREADS / 64, NONE = 0xFFFFFFFFu, JOB = (1u << RS_JOB_BITS) - 1u, MARK = 0x8000u;
@@ -2451,7 +2457,7 @@ __global__ __launch_bounds__(THREADS) void k_reschedule(RsArgs B) {
     __shared__ RsMin sh_min[2];
     __shared__ uint32_t sh_holders, sh_changed[2], sh_nb;
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
-    const uint32_t J = A.n_jobs, room = (J + 7u) & ~7u, near = B.near;
+    const uint32_t J = A.n_jobs, room = rs_list(J), near = B.near;
     const float INF = __int_as_float(0x7F800000);
     // a place in the list of holders: what its job loses per GPU and per CPU it gives (infinite: nothing to give, or nobody
     // here), and the job, marked when the step under way has changed it
@@ -2512,27 +2518,28 @@ __global__ __launch_bounds__(THREADS) void k_reschedule(RsArgs B) {
     __syncthreads();
 
     // A wavefront finds the place with the lowest slope (the lower job among equal slopes); false: nobody gives.  Four places
-    // per lane and load, two loads on their way (four: 3 % slower, the code grows); only where several places have the slope are they looked for again.
-    const float4 NOBODY = {INF, INF, INF, INF};
+    // per lane and load, two loads on their way; only where several places have the slope are they looked for again.
     auto lowest = [&](const float *low, uint32_t n, float &slope, uint32_t &place) -> bool {
         const uint32_t n4 = (n + 3u) / 4u;
         const float4 *const q4 = reinterpret_cast<const float4 *>(low);
-        float4 q = lane < n4 ? q4[lane] : NOBODY;            // the lane's first quad with its lowest slope, and where that is
+        float4 q = q4[lane];                                 // the lane's first quad with its lowest slope, and where that is
         float least = fminf(fminf(q.x, q.y), fminf(q.z, q.w));
         uint32_t quad = lane;
         bool more = false;                                   // ... and another quad has it as well
-        for (uint32_t i = lane + 64u; i < n4; i += 128u) {
-            float4 r[2];
-#pragma unroll
-            for (uint32_t u = 0; u < 2; ++u) r[u] = i + 64u * u < n4 ? q4[i + 64u * u] : NOBODY;
-#pragma unroll
-            for (uint32_t u = 0; u < 2; ++u) {
-                const float m = fminf(fminf(r[u].x, r[u].y), fminf(r[u].z, r[u].w));
-                more = m < least ? false : more | (m == least);
-                if (m < least) { least = m; quad = i + 64u * u; }
+        auto look_at = [&](const float4 &r, uint32_t at) {
+            const float m = fminf(fminf(r.x, r.y), fminf(r.z, r.w));
+            more = m < least ? false : more | (m == least);
+            if (m < least) { least = m; quad = at; }
+        };
+        if (n4 > 64u) {
+            look_at(q4[64u + lane], 64u + lane);
+            for (uint32_t i = 128u; i < n4; i += 128u) {
+                const float4 r0 = q4[i + lane], r1 = q4[i + 64u + lane];
+                look_at(r0, i + lane);
+                look_at(r1, i + 64u + lane);
             }
+            if (quad != lane) q = q4[quad];
         }
-        if (quad != lane) q = q4[quad];
         const uint32_t top = wave_min_u32_rows(least < INF ? rs_ordered(least) : NONE);
         if (top == NONE) return false;
         slope = rs_unordered(top);
@@ -2562,13 +2569,13 @@ __global__ __launch_bounds__(THREADS) void k_reschedule(RsArgs B) {
         const uint32_t n4 = (n + 3u) / 4u;
         const float4 *const q4 = reinterpret_cast<const float4 *>(low);
         float rest = INF;
-        for (uint32_t i = lane; i < n4; i += 128u) {
+        for (uint32_t i = 0u; i < n4; i += 128u) {
             float4 r[2];
 #pragma unroll
-            for (uint32_t u = 0; u < 2; ++u) r[u] = i + 64u * u < n4 ? q4[i + 64u * u] : NOBODY;
+            for (uint32_t u = 0; u < 2; ++u) r[u] = q4[i + 64u * u + lane];
 #pragma unroll
             for (uint32_t u = 0; u < 2; ++u) {
-                const uint32_t c = i + 64u * u == place / 4u ? place % 4u : 4u;
+                const uint32_t c = i + 64u * u + lane == place / 4u ? place % 4u : 4u;
                 if (c == 0u) r[u].x = INF;
                 if (c == 1u) r[u].y = INF;
                 if (c == 2u) r[u].z = INF;

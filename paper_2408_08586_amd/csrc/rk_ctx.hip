@@ -141,6 +141,7 @@ int32_t rk_sync(rk_ctx *ctx) {
 }
 
 int32_t rk_ctx_ways(const rk_ctx *ctx, uint32_t *ways) {
+    if (!ctx || !ways) return 0;
     for (int i = 0; i < WAY_COUNT; ++i) ways[i] = ctx->ways[i];
     return WAY_COUNT;
 }

@@ -405,7 +405,8 @@ def test_a_step_that_many_jobs_give_to(gpu, orc, J, take, each):
 
 
 @pytest.mark.parametrize("J,n_cpu,per_gpu,ties", [(60, 4, 1, False), (255, 4, 1, True), (257, 4, 1, False), (511, 2, 0, False), (513, 2, 0, True),
-                                                  (1100, 4, 1, False), (1300, 2, 0, True), (3000, 2, 1, False)])
+                                                  (1100, 4, 1, False), (1300, 2, 0, True), (3000, 2, 1, False), (256, 2, 1, False),
+                                                  (512, 2, 1, True), (512, 2, 1, False), (1024, 2, 1, False)])
 @pytest.mark.parametrize("floors", [False, True])
 def test_lists_of_many_holders(gpu, orc, J, n_cpu, per_gpu, ties, floors):
     """Nearly every job holds something, on less than they hold: searches over lists of one load per lane, of two and of
@@ -422,7 +423,7 @@ def test_lists_of_many_holders(gpu, orc, J, n_cpu, per_gpu, ties, floors):
     bp = rng.integers(0, 1000, bt.size).astype(np.uint32)
     grid = workloads.Grid(np.arange(1, n_cpu + 1, dtype=np.uint32), per_gpu, np.array([64.0], np.float32), 0)
     ct, _, _ = orc.curves(tb, grid, bt, bp)
-    cur_seg = np.where(rng.uniform(size=J) < 0.95, rng.integers(0, 4, J), -1).astype(np.int32)
+    cur_seg = np.where(rng.uniform(size=J) < (1.0 if J % 256 == 0 else 0.95), rng.integers(0, 4, J), -1).astype(np.int32)    # (full lists)
     cur_c = np.where(cur_seg >= 0, rng.integers(0, n_cpu, J), 0).astype(np.uint32)
     held = tb.seg_g[np.maximum(cur_seg, 0)] * (cur_seg >= 0)
     cpus = ((cur_c + 1) * (held if per_gpu else cur_seg >= 0)).sum()
