@@ -224,7 +224,7 @@ enum { SLOT_IDLE, SLOT_CURRENT, SLOT_START, SLOT_TRIAL };   // nothing; the curr
 // the slowest of the four models of its wavefront (850 iterations where a model needs 361 on average); 12.7 ms with the
 // solutions taken by one wavefront for all slots of a workgroup, a lane each, between two barriers; 9.6 ms with the
 // matrix rows spread over the group's lanes and no barrier at all; 9.0 ms with the overlaps dealt out to the lanes.
-// 20 models: 8.1 -> 3.4 ms.  Limiting the registers to three wavefronts per SIMD spills: 12.1 ms.
+// 20 models: 8.1 -> 3.4 ms.  Kicks that would repeat an earlier one are not made again: 9.1 -> 8.5 ms.  Limiting the registers to three wavefronts per SIMD spills: 12.1 ms.
 template <int W>
 __global__ __launch_bounds__(FIT_THREADS, 2) void k_fit(FitArgs A) {
     constexpr double GTOL = 1e-14, XTOL = 1e-13, KICK_TO = 0.3;
@@ -238,6 +238,7 @@ __global__ __launch_bounds__(FIT_THREADS, 2) void k_fit(FitArgs A) {
     // the best end point among the starting points of a model under way
     __shared__ double rec_x[WAVES][RECS][NR], rec_F[WAVES][RECS];
     __shared__ uint32_t rec_start[WAVES][RECS], rec_iters[WAVES][RECS], rec_done[WAVES][RECS];
+    __shared__ uint32_t rec_kick[WAVES][RECS][3];         // of its last kick per exponent: the iterations
 
     const uint32_t wave = threadIdx.x >> 6, wlane = threadIdx.x & 63u, slot = wlane / W, lane = wlane % W;
     const uint32_t own = wlane & 7u;                      // the component (7: the right-hand side) this lane has
@@ -260,6 +261,7 @@ __global__ __launch_bounds__(FIT_THREADS, 2) void k_fit(FitArgs A) {
     uint32_t n_runs = 0, n_tasks = 0, off_rank = 0;       // of the slot's model; which of its offloaded runs the lane's is
     uint32_t state = SLOT_IDLE, model = NONE, start = 0, rec = 0, it = 0, iters = 0, into = 0;
     uint32_t kick = NONE;                                 // NONE: a descent from a starting point; 0..5: which kick
+    uint32_t unmoved = 0, kick_from = 0;                  // kicks since the best point last moved; iterations before this kick
     double lam = 0.0, nu = 0.0, pred = 0.0, F = 0.0, F0 = 0.0, best_F = 0.0;
     bool ok = false, improved = false, refit = false, want_item = true, opening = true;
     double x = 0.0, xn = 0.0, D = 0.0, best = 0.0;        // component `own` of the point, the point evaluated, the scaling, the best
@@ -394,25 +396,34 @@ __global__ __launch_bounds__(FIT_THREADS, 2) void k_fit(FitArgs A) {
                 best = improved ? rec_x[wave][rec][own] : x0;
                 iters = refit ? rec_iters[wave][rec] : 0u;
                 kick = 0;
+                unmoved = 0;
             } else {
+                rec_kick[wave][rec][kick % 3u] = iters - kick_from;
+                ++unmoved;
                 if (F < best_F) {
                     best_F = F;
                     improved = true;
                     best = x;
+                    unmoved = 0;
                 }
                 ++kick;
             }
             // An overlap exponent that ended on a bound sits on a plateau (at k = 32 the overlap function no longer feels
-            // k): try again from the best point with that exponent moved back inside, twice over the three exponents.
+            // k): try again from the best point with that exponent moved back inside, twice over the three exponents.  A kick
+            // from the point from which that exponent was last kicked ends as that one did, which is known: only its
+            // iterations are counted again.
             const uint32_t bound = (uint32_t)(__ballot(refit && exponent && (best <= lower * (1.0 + 1e-9) || best >= 1.0 - 1e-9)) >> row0);
-            for (; kick < 6u; ++kick) {
+            for (; kick < 6u; ++kick, ++unmoved) {
                 const uint32_t i = kick % 3u == 0u ? TH_SYNC : kick % 3u == 1u ? TH_OFF : TH_SWAP;
-                if (bound >> i & 1u) {
+                if (!(bound >> i & 1u)) continue;
+                if (unmoved < 3u) {
                     xn = own == i ? KICK_TO : best;
                     break;
                 }
+                iters += rec_kick[wave][rec][kick % 3u];
             }
             if (kick < 6u) {
+                kick_from = iters;
                 state = SLOT_START;
             } else {
                 const uint32_t S = C.sample_off[model + 1] - C.sample_off[model];
