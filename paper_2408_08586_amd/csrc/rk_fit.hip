@@ -209,12 +209,26 @@ __device__ __forceinline__ const FitArgs &cold_args() {
     return *(const FitArgs *)p;
 }
 
+// An exponent's kick is known by the version of the best point it starts from: what it ends with is kept, and the kicks
+// of a model are gone through in order with what is known.
+struct Rec {
+    double x[NR], F, F0;                                  // the best point, its error; the error of the model's parameters
+    double kick_x[3][NR], kick_F[3];                      // per exponent: where its last kick ended,
+    uint32_t kick_iters[3], kick_of[3];                   // after how many iterations, from which version of the best point
+    uint32_t model, start, iters, done;                   // `start`: the start the best point is from; `done`: starts that have ended
+    uint32_t phase, version;                              // PHASE_STARTS, the kick that decides next (0..5), PHASE_DONE; of x, from 1
+    uint32_t running, bound;                              // exponents whose kick from this version is under way; those on a bound
+    uint32_t improved;
+};
+enum : uint32_t { PHASE_STARTS = 0xFFFFFFFEu, PHASE_DONE = 0xFFFFFFFFu };
+
 // What a slot's next evaluation is for.
 enum { SLOT_IDLE, SLOT_CURRENT, SLOT_START, SLOT_TRIAL };   // nothing; the current parameters; a descent's first point; a step
 
 // A wavefront has 64/W slots with a descent under way in each.  A model's descents from its starting points are items of
 // their own (the slots take them in order); the slot that finishes a model's last one goes on with its kicks, which build
-// on one another.  What belongs to a slot as a whole is held by all lanes of its group alike; lane i = 0..6 of every row
+// on one another.  When no model is left, slots without an item make kicks ahead from the best point there is; they count
+// if that point is still the best one when their turn comes.  What belongs to a slot as a whole is held by all lanes of its group alike; lane i = 0..6 of every row
 // of 16 (and lane 8 + i) also has component i of the vectors.  Nothing is shared between wavefronts but the number of the
 // next model.
 //
@@ -224,7 +238,8 @@ enum { SLOT_IDLE, SLOT_CURRENT, SLOT_START, SLOT_TRIAL };   // nothing; the curr
 // the slowest of the four models of its wavefront (850 iterations where a model needs 361 on average); 12.7 ms with the
 // solutions taken by one wavefront for all slots of a workgroup, a lane each, between two barriers; 9.6 ms with the
 // matrix rows spread over the group's lanes and no barrier at all; 9.0 ms with the overlaps dealt out to the lanes.
-// 20 models: 8.1 -> 3.4 ms.  Kicks that would repeat an earlier one are not made again: 9.1 -> 8.5 ms.  Limiting the registers to three wavefronts per SIMD spills: 12.1 ms.
+// 20 models: 8.1 -> 3.4 ms.  Kicks that would repeat an earlier one are not made again: 9.1 -> 8.5 ms; kicks made ahead
+// by slots that have nothing else left: 8.3 ms, 20 models (other ones) 4.3 -> 3.1 ms.  Limiting the registers to three wavefronts per SIMD spills: 12.1 ms.
 template <int W>
 __global__ __launch_bounds__(FIT_THREADS, 2) void k_fit(FitArgs A) {
     constexpr double GTOL = 1e-14, XTOL = 1e-13, KICK_TO = 0.3;
@@ -235,10 +250,8 @@ __global__ __launch_bounds__(FIT_THREADS, 2) void k_fit(FitArgs A) {
     // per slot: the overlaps of the model's runs (at most three each), and the results of those of the offload
     __shared__ __align__(16) Task sh_task[WAVES][SLOTS][3 * W];
     __shared__ __align__(16) Overlap sh_over[WAVES][SLOTS][2 * W];
-    // the best end point among the starting points of a model under way
-    __shared__ double rec_x[WAVES][RECS][NR], rec_F[WAVES][RECS];
-    __shared__ uint32_t rec_start[WAVES][RECS], rec_iters[WAVES][RECS], rec_done[WAVES][RECS];
-    __shared__ uint32_t rec_kick[WAVES][RECS][3];         // of its last kick per exponent: the iterations
+    // models under way: the best end point among the starting points, then among the kicks
+    __shared__ Rec sh_rec[WAVES][RECS];
 
     const uint32_t wave = threadIdx.x >> 6, wlane = threadIdx.x & 63u, slot = wlane / W, lane = wlane % W;
     const uint32_t own = wlane & 7u;                      // the component (7: the right-hand side) this lane has
@@ -260,14 +273,15 @@ __global__ __launch_bounds__(FIT_THREADS, 2) void k_fit(FitArgs A) {
     bool has_run = false;
     uint32_t n_runs = 0, n_tasks = 0, off_rank = 0;       // of the slot's model; which of its offloaded runs the lane's is
     uint32_t state = SLOT_IDLE, model = NONE, start = 0, rec = 0, it = 0, iters = 0, into = 0;
-    uint32_t kick = NONE;                                 // NONE: a descent from a starting point; 0..5: which kick
-    uint32_t unmoved = 0, kick_from = 0;                  // kicks since the best point last moved; iterations before this kick
-    double lam = 0.0, nu = 0.0, pred = 0.0, F = 0.0, F0 = 0.0, best_F = 0.0;
-    bool ok = false, improved = false, refit = false, want_item = true, opening = true;
-    double x = 0.0, xn = 0.0, D = 0.0, best = 0.0;        // component `own` of the point, the point evaluated, the scaling, the best
+    uint32_t kick = NONE, version = 0;                    // NONE: a descent from a starting point; 0..2: the kick of that exponent, from that version
+    double lam = 0.0, nu = 0.0, pred = 0.0, F = 0.0, F0 = 0.0;
+    bool ok = false, refit = false, want_item = true, opening = true;
+    double x = 0.0, xn = 0.0, D = 0.0;                    // component `own` of the point, the point evaluated, the scaling
     // where the next items come from, the same in all lanes: a model, its next starting point, its record
     uint32_t src_model = NONE, src_start = NONE, src_rec = 0, free_recs = (1u << RECS) - 1u;
     bool src_dry = false;
+    if (wlane < RECS) sh_rec[wave][wlane].phase = PHASE_DONE;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 
     // the lane's component of the model's current parameters on the feasible set, and as a search point (exponents as 1/k)
     auto current = [&](const FitArgs &C, uint32_t m, double &th, double &sx) {
@@ -365,95 +379,137 @@ __global__ __launch_bounds__(FIT_THREADS, 2) void k_fit(FitArgs A) {
             ended = converged || small;
             state = SLOT_TRIAL;
         }
-        // a descent from a starting point has ended: its model's best so far (the lowest error, the earlier start on ties)
-        bool kicks = ended && kick != NONE;
-        for (unsigned long long todo = __ballot(ended && kick == NONE); todo;) {
+        // without further models a kick whose model's best point has moved meanwhile is given up at once
+        if (src_dry && kick != NONE && state != SLOT_IDLE) ended = ended || version != sh_rec[wave][rec].version;
+        // Descents that have ended.  From a starting point: the model's best so far (the lowest error, the earlier start on
+        // ties).  The slot that ends the last of them, or a kick, goes through the kicks as far as they are known.
+        uint32_t freed = NONE;                            // the record of a model that is finished
+        const unsigned long long any_ended = __ballot(ended);
+        for (unsigned long long todo = any_ended; todo;) {
             const uint32_t who = ((uint32_t)__ffsll((long long)todo) - 1u) / W;
             if (slot == who) {
-                if (refit) {
-                    if (F < rec_F[wave][rec] || (F == rec_F[wave][rec] && start < rec_start[wave][rec])) {
-                        rec_x[wave][rec][own] = x;
-                        rec_F[wave][rec] = F;
-                        rec_start[wave][rec] = start;
+                Rec &m = sh_rec[wave][rec];
+                bool decide = false;
+                want_item = true;
+                if (kick != NONE) {
+                    decide = version == m.version;
+                    if (decide) {
+                        m.kick_x[kick][own] = x;
+                        m.kick_F[kick] = F;
+                        m.kick_iters[kick] = iters;
+                        m.kick_of[kick] = version;
                     }
-                    rec_iters[wave][rec] += iters;        // (all lanes of the group add the same number to the same word)
+                } else {
+                    if (refit) {
+                        if (F < m.F || (F == m.F && start < m.start)) {
+                            m.x[own] = x;
+                            m.F = F;
+                            m.start = start;
+                        }
+                        m.iters += iters;                 // (all lanes of the group add the same number to the same word)
+                    }
+                    const uint32_t done = m.done;
+                    m.done = done + 1u;
+                    decide = done == A.n_starts;
+                    if (decide) {                         // every start has been tried
+                        double th, x0;
+                        current(cold_args(), model, th, x0);
+                        const bool better = refit && m.F < F0;
+                        if (!better) m.x[own] = x0;
+                        m.F = better ? m.F : F0;
+                        m.F0 = F0;
+                        m.improved = better ? 1u : 0u;
+                        m.iters = refit ? m.iters : 0u;
+                        m.phase = 0u;
+                        m.version = 1u;
+                        m.running = 0u;
+#pragma unroll
+                        for (int i = 0; i < 3; ++i) m.kick_of[i] = 0u;
+                    }
                 }
-                const uint32_t done = rec_done[wave][rec];
-                rec_done[wave][rec] = done + 1u;
-                if (done == A.n_starts) kicks = true;
-                else want_item = true;
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                if (decide) {
+                    // An overlap exponent that ended on a bound sits on a plateau (at k = 32 the overlap function no longer
+                    // feels k): try again from the best point with that exponent moved back inside, twice over the three
+                    // exponents.  A kick from the point from which that exponent was last kicked ends as that one did.
+                    double best = m.x[own], best_F = m.F;
+                    uint32_t next = m.phase, v = m.version, sum = m.iters, running = m.running, improved = m.improved;
+                    auto on_bound = [&]() {
+                        const uint32_t b = (uint32_t)(__ballot(refit && exponent && (best <= lower * (1.0 + 1e-9) || best >= 1.0 - 1e-9)) >> row0);
+                        return (b >> TH_SYNC & 1u) | (b >> TH_OFF & 1u) << 1 | (b >> TH_SWAP & 1u) << 2;
+                    };
+                    uint32_t bound = on_bound();
+                    for (; next < 6u; ++next) {
+                        const uint32_t e = next % 3u;
+                        if (!(bound >> e & 1u)) continue;
+                        if (m.kick_of[e] != v) break;
+                        sum += m.kick_iters[e];
+                        if (m.kick_F[e] < best_F) {
+                            best_F = m.kick_F[e];
+                            best = m.kick_x[e][own];
+                            improved = 1u;
+                            ++v;
+                            running = 0u;
+                            bound = on_bound();
+                        }
+                    }
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                    const uint32_t e = next % 3u;
+                    if (next < 6u) {
+                        if (!(running >> e & 1u)) {       // (otherwise another slot is at it and goes on from there)
+                            running |= 1u << e;
+                            want_item = false;
+                            kick = e;
+                            version = v;
+                            iters = 0;
+                            xn = own == (e == 0u ? TH_SYNC : e == 1u ? TH_OFF : TH_SWAP) ? KICK_TO : best;
+                            state = SLOT_START;
+                        }
+                    } else {
+                        const FitArgs &C = cold_args();
+                        const uint32_t S = C.sample_off[model + 1] - C.sample_off[model];
+                        const double inv_S = S ? 1.0 / (double)S : 0.0, before = m.F0;
+                        double th, x0;
+                        current(C, model, th, x0);
+                        if (improved) th = exponent ? 1.0 / best : best;
+                        const rk_fit_result &o = C.out;
+                        float *const dst[NP] = {o.k_bwd, o.k_sync, o.k_opt, o.k_opt_off, o.k_off, o.k_swap, o.k_const};
+                        float *to = dst[0];
+#pragma unroll
+                        for (int i = 1; i < NP; ++i) to = own == (uint32_t)i ? dst[i] : to;
+                        if (lane < (uint32_t)NP) {
+                            if (to) to[model] = (float)th;
+                            if (o.theta) o.theta[(size_t)model * NP + own] = th;
+                        } else if (lane == (uint32_t)NP) {
+                            if (o.rmsle_before) o.rmsle_before[model] = (float)sqrt(before * inv_S);
+                            if (o.rmsle_after) o.rmsle_after[model] = (float)sqrt(best_F * inv_S);
+                            // (more runs than the caller announced: left alone, flagged)
+                            if (o.iters) o.iters[model] = S > C.most_runs ? 0xFFFFFFFFu : sum;
+                        }
+                        next = PHASE_DONE;
+                        v = 0u;                           // (a kick of it that still runs ahead is of no use)
+                        freed = rec;
+                    }
+                    m.x[own] = best;
+                    m.F = best_F;
+                    m.phase = next;
+                    m.version = v;
+                    m.iters = sum;
+                    m.running = running;
+                    m.bound = bound;
+                    m.improved = improved;
+                }
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");       // the next slot may work on the same record
             todo &= ~((W == 64 ? ~0ull : ((1ull << (W & 63)) - 1ull)) << (who * W));
         }
-        if (kicks) {
+        // the next items: the current model's remaining starts, then another model, then kicks that may be needed
+        if ((opening || any_ended) && __ballot(want_item)) {
             const FitArgs &C = cold_args();
-            if (kick == NONE) {                           // every start has been tried: this slot goes on with the model
-                double th, x0;
-                current(C, model, th, x0);
-                improved = refit && rec_F[wave][rec] < F0;
-                best_F = improved ? rec_F[wave][rec] : F0;
-                best = improved ? rec_x[wave][rec][own] : x0;
-                iters = refit ? rec_iters[wave][rec] : 0u;
-                kick = 0;
-                unmoved = 0;
-            } else {
-                rec_kick[wave][rec][kick % 3u] = iters - kick_from;
-                ++unmoved;
-                if (F < best_F) {
-                    best_F = F;
-                    improved = true;
-                    best = x;
-                    unmoved = 0;
-                }
-                ++kick;
+            for (uint32_t who = 0; who < SLOTS; ++who) {
+                const uint32_t r = (uint32_t)__builtin_amdgcn_readlane((int)freed, (int)(who * W));
+                if (r != NONE) free_recs |= 1u << r;
             }
-            // An overlap exponent that ended on a bound sits on a plateau (at k = 32 the overlap function no longer feels
-            // k): try again from the best point with that exponent moved back inside, twice over the three exponents.  A kick
-            // from the point from which that exponent was last kicked ends as that one did, which is known: only its
-            // iterations are counted again.
-            const uint32_t bound = (uint32_t)(__ballot(refit && exponent && (best <= lower * (1.0 + 1e-9) || best >= 1.0 - 1e-9)) >> row0);
-            for (; kick < 6u; ++kick, ++unmoved) {
-                const uint32_t i = kick % 3u == 0u ? TH_SYNC : kick % 3u == 1u ? TH_OFF : TH_SWAP;
-                if (!(bound >> i & 1u)) continue;
-                if (unmoved < 3u) {
-                    xn = own == i ? KICK_TO : best;
-                    break;
-                }
-                iters += rec_kick[wave][rec][kick % 3u];
-            }
-            if (kick < 6u) {
-                kick_from = iters;
-                state = SLOT_START;
-            } else {
-                const uint32_t S = C.sample_off[model + 1] - C.sample_off[model];
-                const double inv_S = S ? 1.0 / (double)S : 0.0;
-                double th, x0;
-                current(C, model, th, x0);
-                if (improved) th = exponent ? 1.0 / best : best;
-                const rk_fit_result &o = C.out;
-                float *const dst[NP] = {o.k_bwd, o.k_sync, o.k_opt, o.k_opt_off, o.k_off, o.k_swap, o.k_const};
-                float *to = dst[0];
-#pragma unroll
-                for (int i = 1; i < NP; ++i) to = own == (uint32_t)i ? dst[i] : to;
-                if (lane < (uint32_t)NP) {
-                    if (to) to[model] = (float)th;
-                    if (o.theta) o.theta[(size_t)model * NP + own] = th;
-                } else if (lane == (uint32_t)NP) {
-                    if (o.rmsle_before) o.rmsle_before[model] = (float)sqrt(F0 * inv_S);
-                    if (o.rmsle_after) o.rmsle_after[model] = (float)sqrt(best_F * inv_S);
-                    // (more runs than the caller announced: left alone, flagged)
-                    if (o.iters) o.iters[model] = S > C.most_runs ? 0xFFFFFFFFu : iters;
-                }
-                want_item = true;
-            }
-        }
-        // the next items: the current model's remaining starts, then another model
-        if (__ballot(want_item)) {
-            const FitArgs &C = cold_args();
-            const bool freed = kicks && want_item;        // the record of a finished model is free again
-            for (uint32_t who = 0; who < SLOTS; ++who)
-                if (__builtin_amdgcn_readlane(freed ? 1 : 0, (int)(who * W))) free_recs |= 1u << (uint32_t)__builtin_amdgcn_readlane((int)rec, (int)(who * W));
             for (uint32_t who = 0; who < SLOTS; ++who) {
                 if (!__builtin_amdgcn_readlane(want_item ? 1 : 0, (int)(who * W))) continue;
                 if (!src_dry && (src_start == NONE || src_start > A.n_starts)) {
@@ -467,29 +523,52 @@ __global__ __launch_bounds__(FIT_THREADS, 2) void k_fit(FitArgs A) {
                         src_start = 0;
                         src_rec = (uint32_t)__ffs((int)free_recs) - 1u;
                         free_recs &= free_recs - 1u;
-                        rec_F[wave][src_rec] = __builtin_huge_val();
-                        rec_start[wave][src_rec] = NONE;
-                        rec_iters[wave][src_rec] = 0u;
-                        rec_done[wave][src_rec] = 0u;
+                        Rec &q = sh_rec[wave][src_rec];
+                        q.F = __builtin_huge_val();
+                        q.model = m;
+                        q.start = NONE;
+                        q.iters = 0u;
+                        q.done = 0u;
+                        q.phase = PHASE_STARTS;
+                    }
+                }
+                // With no model left, a kick that the one under way may make necessary: of an exponent on a bound that has
+                // not been kicked from the best point and comes up again.  (Whole wavefront: the records are the same to all.)
+                uint32_t ahead = NONE, ahead_rec = 0;
+                if (src_dry) {
+                    for (uint32_t r = 0; r < RECS && ahead == NONE; ++r) {
+                        const Rec &m = sh_rec[wave][r];
+                        for (uint32_t k = m.phase; k < 6u && k < m.phase + 3u; ++k) {
+                            const uint32_t e = k % 3u;
+                            if (ahead == NONE && (m.bound >> e & 1u) && !(m.running >> e & 1u) && m.kick_of[e] != m.version) {
+                                ahead = e;
+                                ahead_rec = r;
+                            }
+                        }
+                    }
+                    if (ahead != NONE) {
+                        const uint32_t running = sh_rec[wave][ahead_rec].running | 1u << ahead;
+                        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                        sh_rec[wave][ahead_rec].running = running;
+                        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                     }
                 }
                 if (slot == who) {
                     want_item = false;
-                    kick = NONE;
+                    kick = ahead;
                     iters = 0;
-                    if (src_dry) {
+                    if (src_dry && ahead == NONE) {
                         state = SLOT_IDLE;
-                        model = NONE;
-                        has_run = false;
-                        n_tasks = 0;
+                        want_item = true;                 // a kick may come up for it
                     } else {
-                        if (src_model != model) {         // the lane's run and the group's overlaps
-                            const uint32_t s0 = C.sample_off[src_model];
-                            n_runs = C.sample_off[src_model + 1] - s0;
+                        const uint32_t take = src_dry ? sh_rec[wave][ahead_rec].model : src_model;
+                        if (take != model) {              // the lane's run and the group's overlaps
+                            const uint32_t s0 = C.sample_off[take];
+                            n_runs = C.sample_off[take + 1] - s0;
                             if (n_runs > C.most_runs) n_runs = C.most_runs;
                             has_run = lane < n_runs;      // a lane without a run contributes nothing at all
                             R = Run{};
-                            if (has_run) R = load_run(C, src_model, s0 + lane);
+                            if (has_run) R = load_run(C, take, s0 + lane);
                             const unsigned long long off = (__ballot(R.off) >> (slot * W)) & (W == 64 ? ~0ull : ((1ull << (W & 63)) - 1ull));
                             off_rank = (uint32_t)__popcll(off & ((1ull << lane) - 1ull));
                             n_tasks = n_runs + 2u * (uint32_t)__popcll(off);
@@ -499,12 +578,21 @@ __global__ __launch_bounds__(FIT_THREADS, 2) void k_fit(FitArgs A) {
                                 task[n_runs + 2u * off_rank + 1u] = Task{R.opt_scale, 0.0, R.Toff, TH_OPT_OFF, TH_SWAP};
                             }
                         }
-                        state = SLOT_CURRENT;
-                        model = src_model;
-                        start = src_start;
-                        rec = src_rec;
-                        double th;
-                        current(C, model, th, xn);
+                        model = take;
+                        if (src_dry) {
+                            const Rec &m = sh_rec[wave][ahead_rec];
+                            rec = ahead_rec;
+                            version = m.version;
+                            refit = true;                 // (only a refitted model has exponents to kick)
+                            xn = own == (ahead == 0u ? TH_SYNC : ahead == 1u ? TH_OFF : TH_SWAP) ? KICK_TO : m.x[own];
+                            state = SLOT_START;
+                        } else {
+                            state = SLOT_CURRENT;
+                            start = src_start;
+                            rec = src_rec;
+                            double th;
+                            current(C, model, th, xn);
+                        }
                     }
                 }
                 if (!src_dry) ++src_start;
@@ -518,15 +606,16 @@ __global__ __launch_bounds__(FIT_THREADS, 2) void k_fit(FitArgs A) {
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         Overlap sync = {};
         double Tb = 0.0;
-        for (uint32_t t = lane; __ballot(t < n_tasks); t += W) {
+        const uint32_t tasks = state != SLOT_IDLE ? n_tasks : 0u;
+        for (uint32_t t = lane; __ballot(t < tasks); t += W) {
             Task q = {};
-            if (t < n_tasks) q = task[t];
+            if (t < tasks) q = task[t];
             Overlap o;
             o.k = 1.0 / point[q.exp];
             const double first = point[q.var] * q.a + q.b;
             overlap(o.k, first, q.y, o.f, o.fx, o.fk);
             if (t < (uint32_t)W) { sync = o; Tb = first; }
-            if (t >= n_runs && t < n_tasks) over[t - n_runs] = o;
+            if (t >= n_runs && t < tasks) over[t - n_runs] = o;
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         // then the residual ln(1+pred) - ln(1+y) of the lane's run and its derivatives by the search variables

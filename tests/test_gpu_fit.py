@@ -237,3 +237,25 @@ def test_a_models_fit_does_not_depend_on_its_neighbours(gpu, orc, n_samples, n_o
             assert np.array_equal(alone[key], whole[key][lo:hi]), (key, lo, hi)
     e = [case.oracle_rmsle(j, whole["theta"][j]) for j in range(0, 700, 50)]
     assert np.all(np.abs(whole["after"][::50] - e) <= 1e-6 * (1 + np.array(e)))
+
+
+@pytest.mark.parametrize("n_samples,n_offload", [(16, 5), (24, 5), (40, 3)])
+def test_copies_of_a_model_end_alike(gpu, orc, n_samples, n_offload):
+    """While models wait, a slot makes a model's kicks one after the other; when none is left, idle slots make kicks ahead
+    that may turn out not to be needed.  Ten copies of 300 models, more than the wavefronts of the launch: the early copies
+    go the first way and the late ones the second, with the same results, bit for bit, and the same iterations counted."""
+    case = FitCase(orc, 300, n_samples, sigma=0.05, n_offload=n_offload)
+    alone = case.fit_on_gpu(gpu)
+    many = FitCase.__new__(FitCase)
+    many.__dict__.update(case.__dict__)
+    copies = 10
+    many.n_models = 300 * copies
+    ids = np.tile(np.arange(300), copies)
+    many.wl = workloads.Workload("fit", case.wl.coef[ids], case.wl.ints[ids], case.wl.bounds, case.wl.grid, case.wl.env, case.wl.cluster)
+    many.coef0, many.theta0, many.y = case.coef0[ids], case.theta0[ids], case.y[ids]
+    many.d, many.t, many.p = case.d[ids], case.t[ids], case.p[ids]
+    many.dr = workloads.FitDraws(*(getattr(case.dr, f)[ids] if f != "start_offsets" else case.dr.start_offsets
+                                   for f in ("u_triple", "option", "cpus", "noise_z", "start_factor", "start_offsets")))
+    got = many.fit_on_gpu(gpu)
+    for key in ("theta", "before", "after", "iters"):
+        assert np.array_equal(got[key], np.concatenate([alone[key]] * copies)), key
