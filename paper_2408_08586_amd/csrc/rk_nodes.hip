@@ -296,6 +296,66 @@ __global__ void k_nd_prepare(NdKernArgs K) {
     nd_refresh_wave(A, j, gi, ci, lane);
 }
 
+// What is kept of a job in a state (nothing or one of its amounts, a CPU level) does not depend on the other jobs, and a
+// simulation's jobs have few states: they are all found once, over the whole chip, before the first tick.
+// ND_STATE_WORDS words per state, in the order of NdField, and a record of what the job would run as at its best tier
+// (throughput, plan, tier or ND_NONE, GPUs).  A job's states, `per_job` places: nothing at every level (only level 0 is
+// used), then its amounts, each at every level.
+enum NdField : uint32_t { ND_UG, ND_UDG, ND_GAIN_G, ND_TGT_G, ND_UC, ND_GAIN_C, ND_LVL_C, ND_DC_LO, ND_DC_HI, ND_DS_G, ND_DS_C,
+                          ND_GIVES, ND_LOSS, ND_TO, ND_DS_G1, ND_DS_C1, ND_STATE_WORDS };
+struct NdStates { uint32_t *words; uint4 *best; uint32_t per_job; };
+__device__ __forceinline__ size_t nd_state_at(const NdStates &T, uint32_t j, uint32_t n_cpu, int32_t gi, uint32_t ci) {
+    return j * T.per_job + (uint32_t)(gi + 1) * n_cpu + (gi < 0 ? 0u : ci);
+}
+// A workgroup per job and CPU level, a wavefront per amount.  406 jobs of up to 16 amounts at 5 levels: 34,000 states.
+__global__ __launch_bounds__(256) void k_nd_states(NdKernArgs K, NdStates to) {
+    const NdArgs A(K.b, K.X);
+    const uint32_t j = blockIdx.x, ci = blockIdx.y, lane = threadIdx.x & 63u;
+    const uint32_t so = A.seg_off[j], ns = A.seg_off[j + 1] - so, n_cpu = A.X.grid.n_cpu, n_mem = A.X.grid.n_mem;
+    const float INF = __int_as_float(0x7F800000);
+    for (int32_t gi = (int32_t)(threadIdx.x >> 6) - 1; gi < (int32_t)ns; gi += 4) {
+        if (gi < 0 && ci > 0) continue;
+        RsGive a, b;
+        RsStep ug, uc;
+        RsShrunk s;
+        if (ns <= 64u) {
+            const RsRows R = rs_rows(A, j, so, ns, gi, ci, lane);
+            a = rs_down_gpu_rows(A, R, R.curve, gi, ci, lane);
+            b = rs_down_cpu_rows(A, R, gi, ci, rs_lane_f(R.best, gi), rs_lane_f(R.best_lo, gi));
+            ug = rs_up_gpu_rows(A, R, gi, ci, lane);
+            uc = rs_up_cpu_rows(A, R, gi, ci, lane);
+            s = RsShrunk{a, -1, 0u, 0.f, 0.f};
+            if (a.any) s = rs_shrunk_rows(A, R, 0, gi, ci, a, lane);
+        } else {
+            a = rs_down_gpu_at(A, j, gi, ci, lane, 64);
+            b = rs_down_cpu_at(A, j, gi, ci);
+            ug = rs_up_gpu(A, j, gi, ci, lane, 64);
+            uc = rs_up_cpu(A, j, gi, ci, lane, 64);
+            s = RsShrunk{a, -1, 0u, 0.f, 0.f};
+            if (a.any) s = rs_shrunk_at(A, j, 0, gi, ci, a, lane, 64);
+        }
+        const size_t at = nd_state_at(to, j, n_cpu, gi, ci);
+        uint4 best = {0u, RK_NO_PLAN, ND_NONE, 0u};
+        if (gi >= 0) {
+            best.w = A.X.tb.seg_g[so + (uint32_t)gi];
+            float top = 0.f;
+            for (uint32_t m = 0; m < n_mem; ++m) {
+                const uint64_t slot = (uint64_t)n_cpu * n_mem * so + ((uint64_t)ci * n_mem + m) * ns + (uint32_t)gi;
+                const float v = A.X.best_thr[slot];
+                if (v > top) { top = v; best.x = __float_as_uint(v); best.y = A.X.best_plan[slot]; best.z = m; }
+            }
+        }
+        if (lane == 0) {
+            uint4 *const w = reinterpret_cast<uint4 *>(to.words + at * ND_STATE_WORDS);
+            w[0] = uint4{__float_as_uint(ug.any ? ug.slope : 0.f), (uint32_t)ug.dg, __float_as_uint(ug.gain), (uint32_t)ug.tgt};
+            w[1] = uint4{__float_as_uint(uc.any ? uc.slope : 0.f), __float_as_uint(uc.gain), uc.lvl, (uint32_t)uc.dc};
+            w[2] = uint4{(uint32_t)(uc.dc >> 32), __float_as_uint(a.any ? a.slope : INF), __float_as_uint(b.any ? b.slope : INF), (uint32_t)a.dg};
+            w[3] = uint4{__float_as_uint(a.loss), (uint32_t)s.gi, __float_as_uint(s.ds_g), __float_as_uint(s.ds_c)};
+            to.best[at] = best;
+        }
+    }
+}
+
 // exclusive prefix sum over the threads of the workgroup (thread order) and the sum of all; all threads call it
 template <int THREADS>
 __device__ __forceinline__ uint32_t nd_block_scan(uint32_t val, uint32_t &all, uint32_t *sh_scan) {
@@ -577,6 +637,13 @@ static inline size_t nd_lds_words(size_t J, size_t N, size_t nodes_words, bool l
     return 2 * nodes_words + 2 * (J + 1) + N + (J + 31) / 32 + (lj ? ND_LDS_JOB_WORDS * J + 1 : 0) + (sim ? ND_LDS_SIM_WORDS * J : 0);
 }
 
+// Where every state of every job is found before the first tick (k_nd_states) the ticks of a simulation need in LDS, beside
+// those words, who is on the nodes when a round begins, every job's state and, per job on the nodes, what its memory costs and
+// its GPUs; with few nodes also what every job asks of every node (share).
+constexpr uint32_t ND_SHARES = 2048;
+static inline size_t nd_share_words(size_t N, size_t gpus) { return N <= 64 && N * gpus <= ND_SHARES ? N * gpus : 0; }
+static inline size_t nd_states_words(size_t J, size_t N, size_t gpus) { return 3 * gpus + nd_share_words(N, gpus) + (J + 3) / 4 + 1; }
+
 // The loop with the nodes in LDS.  It is a chain of small decisions, so what bounds it is the latency of one after
 // the other.  Here the first wavefront makes a whole step of ScheduleJob by itself, a node per lane on the walk, a
 // resident per lane where somebody is shrunk, 64 entries of the nodes' tables at a time where a job's parts are
@@ -591,9 +658,9 @@ static inline size_t nd_lds_words(size_t J, size_t N, size_t nodes_words, bool l
 // where they are, and only jobs that came, went or thawed have theirs found again.  As launches of their own, replayed as
 // a graph, the preparation, the round and the tick took 5, 102 and 9 us with 9 us between them, of which loading the
 // nodes and jobs was 5; 406 jobs, 720 ticks: 57.4 -> 46.7 ms, 60 jobs, 100 ticks: 2.59 -> 1.56 ms.
-template <int THREADS, bool LJ, bool SIM, class KernArgs>
+template <int THREADS, bool LJ, bool SIM, bool TAB, class KernArgs>
 __device__ __forceinline__ void nodes_lds(const KernArgs &K) {
-    static_assert(LJ || !SIM, "ticks of a simulation have the jobs in LDS");
+    static_assert((LJ || !SIM) && (SIM || !TAB), "ticks of a simulation have the jobs in LDS; the states are found for them");
     extern __shared__ uint4 sh_raw[];
     constexpr uint32_t WAVES = THREADS / 64;
     __shared__ uint32_t sh_scan[WAVES], sh_take[RK_MAX_CPU_LEVELS], sh_free_c, sh_cpl[RK_MAX_CPU_LEVELS], sh_list;
@@ -656,6 +723,17 @@ __device__ __forceinline__ void nodes_lds(const KernArgs &K) {
     if constexpr (SIM) {                                     // (what the next round needs again is not working memory of this one's end)
         fin_np = take(J); fin_off = take(J); fin_list = take(J); old_state = take(J);
         for (uint32_t j = tid; j < J; j += THREADS) old_state[j] = A.state[j];
+    }
+    uint32_t *start_res = nullptr, *held_g = nullptr;        // (TAB)
+    float *held_cost = nullptr, *share = nullptr;
+    uint8_t *state8 = nullptr;
+    if constexpr (TAB) {
+        start_res = take(gpus); held_cost = reinterpret_cast<float *>(take(gpus)); held_g = take(gpus);
+        if (K.shares) share = reinterpret_cast<float *>(take((size_t)N * gpus));
+        state8 = reinterpret_cast<uint8_t *>(take((J + 3u) / 4u));
+        for (uint32_t j = tid; j < J; j += THREADS) state8[j] = A.state[j];
+        A.state = state8;
+        A.lvl_g = A.st.ci;                                   // (nobody has a floor: a GPU step stays on the level)
     }
     uint32_t bad = 0, any_first = 0;
     for (uint32_t j = tid; j < J; j += THREADS) {
@@ -938,9 +1016,15 @@ __device__ __forceinline__ void nodes_lds(const KernArgs &K) {
                     remember(who, gi0, ci0);
                 } else {
                     gi0 = one_i(A.st.gi[who]); ci0 = one(A.st.ci[who]);
-                    const uint32_t so = one(A.seg_off[who]), ns = one(A.seg_off[who + 1]) - so;
-                    const RsShrunk sk = rs_shrink_wave(A, who, so, ns, 0, gi0, ci0, lane);
-                    dg = one((uint32_t)sk.gv.dg); loss = sk.gv.loss; gi1 = sk.gi; ds_g1 = sk.ds_g; ds_c1 = sk.ds_c;
+                    if constexpr (TAB) {
+                        const uint32_t w = K.states.words[nd_state_at(K.states, who, A.X.grid.n_cpu, gi0, ci0) * ND_STATE_WORDS + (lane & 15u)];
+                        dg = wave_lane_u32(w, ND_GIVES); loss = __uint_as_float(wave_lane_u32(w, ND_LOSS)); gi1 = (int32_t)wave_lane_u32(w, ND_TO);
+                        ds_g1 = __uint_as_float(wave_lane_u32(w, ND_DS_G1)); ds_c1 = __uint_as_float(wave_lane_u32(w, ND_DS_C1));
+                    } else {
+                        const uint32_t so = one(A.seg_off[who]), ns = one(A.seg_off[who + 1]) - so;
+                        const RsShrunk sk = rs_shrink_wave(A, who, so, ns, 0, gi0, ci0, lane);
+                        dg = one((uint32_t)sk.gv.dg); loss = sk.gv.loss; gi1 = sk.gi; ds_g1 = sk.ds_g; ds_c1 = sk.ds_c;
+                    }
                 }
                 const uint32_t slot = (uint32_t)__ffsll((long long)__ballot(lane < cf && rv == who)) - 1u;
                 const uint32_t here_has = wave_lane_u32(word, slot) & 0xFFFFu, per_v = sh_cpl[ci0];
@@ -1239,7 +1323,387 @@ __device__ __forceinline__ void nodes_lds(const KernArgs &K) {
         fresh = __syncthreads_or(is_first || (wave == 0 && moves != before)) != 0;
     }
     };
-    if constexpr (!SIM) {
+    if constexpr (TAB) {
+
+        // Ticks of a simulation whose jobs' states are all known: the first wavefront makes a round by itself, without barriers,
+        // since what a committed step changes of a job is a look into the table; what it has of the jobs it looks for the
+        // next one in the list of those that take part.  A job per thread has in registers what the ticks need of it.
+        const SimArgs &S = K.S;
+        __shared__ uint32_t sh_open[3], sh_used, sh_gone;
+        __shared__ double sh_part[ND_WAVES];
+        const uint32_t n_cpu = A.X.grid.n_cpu, n_mem = A.X.grid.n_mem;
+        const bool mine = tid < J;
+        auto barrier = [&]() { rs_lds_barrier(); };          // (what the wavefronts tell each other lies in LDS)
+        // where a state's word (lane & 15) goes: the job's place in an array of words from `nodes` on
+        const uint32_t field = lane & 15u;
+        uint32_t to = 0, stride = 1u;
+        {
+            auto at_word = [&](const void *p) { return (uint32_t)(reinterpret_cast<const uint32_t *>(p) - nodes); };
+            const uint32_t places[ND_STATE_WORDS] = {at_word(A.ug), at_word(A.udg), at_word(A.gain_g), at_word(A.tgt_g), at_word(A.uc), at_word(A.gain_c),
+                                                     at_word(A.lvl_c), at_word(A.udc_c), at_word(A.udc_c) + 1u, at_word(A.ds_g), at_word(A.ds_c),
+                                                     at_word(A.give), at_word(A.give) + 1u, at_word(A.give) + 2u, at_word(A.give) + 3u, at_word(A.give_c)};
+#pragma unroll
+            for (uint32_t f = 0; f < ND_STATE_WORDS; ++f) to = field == f ? places[f] : to;
+            if (field == ND_DC_LO || field == ND_DC_HI) stride = 2u;
+            if (field == ND_GIVES || field == ND_LOSS || field == ND_TO || field == ND_DS_G1) stride = 4u;
+        }
+        const bool slope = field == ND_DS_G || field == ND_DS_C;
+        auto refresh = [&](uint32_t v, bool on) {            // job v of the lane's row of 16, from what it holds
+            const int32_t gi = A.st.gi[v];
+            const uint32_t ci = A.st.ci[v], state = state8[v];
+            if (!on) return;
+            uint32_t w = K.states.words[nd_state_at(K.states, v, n_cpu, gi, ci) * ND_STATE_WORDS + field];
+            if (slope && state != RK_JOB_NORMAL) w = __float_as_uint(INF);     // (who takes no part gives nothing)
+            nodes[to + v * stride] = w;
+        };
+        auto copy_alone = [&](uint32_t *dst, const uint32_t *src) {            // the nodes, by the first wavefront
+            for (uint32_t i = lane; i < A.nodes_words / 4u; i += 64u) reinterpret_cast<uint4 *>(dst)[i] = reinterpret_cast<const uint4 *>(src)[i];
+            rs_wave_order();
+        };
+        uint32_t *const list = fin_list;                     // the jobs that may be served, their places in the order in okey
+        auto round_alone = [&](uint32_t n_list) {
+            unsigned long long last_key = ~0ull;
+            uint32_t last_j = 0u, free_c = 0;
+            bool fresh = true;
+            RsMin low[2];
+            low[0] = low[1] = RsMin{INF, INF, ND_NONE};
+            for (;;) {
+                if (fresh) {
+                    // what the nodes can give at every CPU level, and all free CPUs (four sums at a time); a lane ends with its level's
+                    uint32_t give = 0;
+                    for (uint32_t l0 = 0; l0 <= n_cpu; l0 += 4u) {
+                        uint32_t t[4] = {0u, 0u, 0u, 0u};
+                        float rcp[4];
+#pragma unroll
+                        for (uint32_t u = 0; u < 4; ++u) rcp[u] = l0 + u < n_cpu ? sh_rcp[l0 + u] : 1.f;
+                        for (uint32_t n = lane; n < N; n += 64u) {
+                            const uint32_t fg = A.free_g[n], fc = A.free_c[n];
+#pragma unroll
+                            for (uint32_t u = 0; u < 4; ++u) {
+                                const uint32_t by_cpu = l0 + u < n_cpu ? over(fc, rcp[u]) : fc;
+                                t[u] += l0 + u >= n_cpu || by_cpu < fg ? by_cpu : fg;
+                            }
+                        }
+#pragma unroll
+                        for (uint32_t u = 0; u < 4; ++u) {
+                            const uint32_t sum = nd_wave_sum(t[u]);
+                            if (l0 + u == n_cpu) free_c = sum;
+                            else if (lane == l0 + u) give = sum;
+                        }
+                    }
+                    if (lane < n_cpu) sh_take[lane] = give;
+                    // the two lowest slopes and whose the lowest is, among those who are on the nodes (nobody else gives)
+                    float a[2] = {INF, INF}, b[2] = {INF, INF};
+                    uint32_t ia[2] = {ND_NONE, ND_NONE};
+                    for (uint32_t i = lane; i < gpus; i += 64u) {
+                        const uint32_t v = A.res[i] >> 16;   // (nobody: infinite slopes)
+#pragma unroll
+                        for (uint32_t r = 0; r < 2; ++r) {
+                            const float y = sh_ds[r * (J + 1) + v];
+                            if (!(y < INF)) continue;
+                            if (y < a[r] || (y == a[r] && v < ia[r])) { if (ia[r] != v) b[r] = a[r]; a[r] = y; ia[r] = v; }
+                            else if (v != ia[r]) b[r] = fminf(b[r], y);
+                        }
+                    }
+#pragma unroll
+                    for (uint32_t r = 0; r < 2; ++r) {
+                        const uint32_t x = rs_ordered(a[r]), least = wave_min_u32_rows(x);
+                        const uint32_t whose = wave_min_u32_rows(x == least ? ia[r] : ND_NONE);
+                        const uint32_t second = wave_min_u32_rows(ia[r] != ND_NONE && ia[r] == whose ? rs_ordered(b[r]) : x);
+                        low[r] = RsMin{rs_unordered(least), rs_unordered(second), whose};
+                    }
+                    rs_wave_order();
+                }
+                // the first job of the list in the order that is still to be served and finds something to do
+                unsigned long long my_key = 0ull;
+                uint32_t my_j = ND_NONE;
+                constexpr uint32_t UN = 4;
+                for (uint32_t p0 = lane; p0 < n_list; p0 += UN * 64u) {
+                    unsigned long long key[UN], dc[UN];
+                    float ug[UN], uc[UN];
+                    uint32_t jj[UN], dg[UN], take[UN];
+#pragma unroll
+                    for (uint32_t k = 0; k < UN; ++k) {
+                        const uint32_t p = p0 + k * 64u < n_list ? p0 + k * 64u : p0;
+                        jj[k] = list[p]; key[k] = A.okey[p];
+                    }
+#pragma unroll
+                    for (uint32_t k = 0; k < UN; ++k) {
+                        ug[k] = A.ug[jj[k]]; uc[k] = A.uc[jj[k]]; dg[k] = A.udg[jj[k]]; dc[k] = A.udc_c[jj[k]];
+                        take[k] = sh_take[A.st.ci[jj[k]]];
+                    }
+#pragma unroll
+                    for (uint32_t k = 0; k < UN; ++k) {
+                        const float lowest_g = jj[k] == low[0].i1 ? low[0].m2 : low[0].m1, lowest_c = jj[k] == low[1].i1 ? low[1].m2 : low[1].m1;
+                        const bool gpu_idle = !(ug[k] > 0.f) || (take[k] < dg[k] && !(ug[k] > lowest_g));
+                        const bool cpu_idle = !(uc[k] > 0.f) || (free_c < dc[k] && !(uc[k] > lowest_c));
+                        const bool served = key[k] > last_key || (key[k] == last_key && jj[k] <= last_j);
+                        if ((gpu_idle && cpu_idle) || served) continue;
+                        if (key[k] > my_key || (key[k] == my_key && jj[k] < my_j)) { my_key = key[k]; my_j = jj[k]; }
+                    }
+                }
+                const uint32_t hi = (uint32_t)(my_key >> 32), lo = (uint32_t)my_key;
+                const uint32_t top_hi = wave_max_u32_rows(hi), top_lo = wave_max_u32_rows(hi == top_hi ? lo : 0u);
+                last_key = ((unsigned long long)top_hi << 32) | top_lo;
+                last_j = wave_min_u32_rows(hi == top_hi && lo == top_lo ? my_j : ND_NONE);
+                if (last_j == ND_NONE) break;
+                // ScheduleJob
+                const uint32_t j = last_j, before = moves;
+                bool gpus_done = false;
+                for (;;) {
+                    uint32_t did = DID_NOTHING;
+                    if (!gpus_done) {
+                        did = gpu_step(j);
+                        if (did == DID_NOTHING) {
+                            gpus_done = true;
+                            if (dirty) copy_alone(nodes, keep);
+                        }
+                    }
+                    if (did == DID_NOTHING) {
+                        did = cpu_step(j);
+                        if (did == DID_NOTHING) {
+                            if (dirty) copy_alone(nodes, keep);
+                            break;
+                        }
+                    }
+                    rs_wave_order();
+                    for (uint32_t i0 = 0; i0 <= touched; i0 += 4u) {           // a row of lanes per job whose state changed
+                        const uint32_t i = i0 + (lane >> 4);
+                        refresh(i < touched ? A.touched[i] : j, i <= touched);
+                    }
+                    copy_alone(keep, nodes);
+                }
+                fresh = moves != before;
+            }
+        };
+
+        SimJob s = {0u, 0u, RK_NO_PLAN, 0u, 0.0, 0.0, 0.0, -1.0, false};
+        int32_t seg = -1;
+        uint32_t lvl = 0, state = RK_JOB_OUT;
+        double arrival = 0.0, work = 0.0, delta = 0.0;
+        float ref = 1.f;
+        if (mine) {
+            arrival = S.arrival[tid]; work = S.work[tid]; delta = S.delta[tid]; ref = A.X.ref_thr[tid];
+            s = SimJob{S.S.g[tid], S.S.c[tid], S.S.plan[tid], S.n_reconf[tid], S.S.owed[tid], S.held[tid], S.progress[tid], S.finish[tid],
+                       S.S.done[tid] != 0};
+            seg = S.S.seg[tid]; lvl = S.S.lvl[tid]; state = state8[tid];
+        }
+        if (tid < 3u) sh_open[tid] = 0u;
+        if (tid == 0) { sh_list = 0u; sh_used = 0u; sh_gone = 0u; }
+        rk_assign a = {0u, 0u, 0.f, RK_NO_PLAN, 0.f};
+        float total = 0.f;
+        uint32_t turn = 0;
+        __syncthreads();
+        for (uint32_t done = 0;;) {
+            // ---- a round: who may be served, and who is where when it begins
+            for (uint32_t i = tid; i < gpus; i += THREADS) start_res[i] = A.res[i];
+            for (uint32_t n = tid; n < N; n += THREADS) sh_mem[n] = 0.f;
+            if (share) for (uint32_t i = tid; i < N * gpus; i += THREADS) share[i] = 0.f;
+            {
+                const float ug = mine ? A.ug[tid] : 0.f, uc = mine ? A.uc[tid] : 0.f;
+                const bool in = state == RK_JOB_NORMAL && (ug > 0.f || uc > 0.f || A.st.gi[tid] >= 0);
+                const unsigned long long m = __ballot(in);
+                uint32_t base = 0;
+                if (lane == 0 && m) base = atomicAdd(&sh_list, (uint32_t)__popcll(m));
+                base = one(base);
+                if (in) {
+                    const uint32_t p = base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+                    list[p] = tid;
+                    A.okey[p] = ((unsigned long long)rs_ordered(ug) << 32) | rs_ordered(uc);
+                }
+            }
+            barrier();
+            if (wave == 0) round_alone(one(sh_list));
+            barrier();
+            // ---- memory, then the record of every job that holds something, in job order
+            const int32_t gi = mine ? A.st.gi[tid] : -1;
+            const uint32_t ci = mine ? A.st.ci[tid] : 0u;
+            const bool holds = gi >= 0;
+            uint4 best = {0u, RK_NO_PLAN, ND_NONE, 0u};
+            float cost = 0.f;
+            if (holds) best = K.states.best[nd_state_at(K.states, tid, n_cpu, gi, ci)];
+            if (holds && best.z != ND_NONE) { cost = A.X.grid.mem_levels_gb[best.z]; if (A.X.grid.mem_mode) cost = cost * (float)best.w; }
+            const unsigned long long holders = __ballot(holds);
+            if (lane == 0) sh_scan[wave] = (uint32_t)__popcll(holders);
+            if (tid == 0) { sh_list = 0u; sh_used = 0u; }
+            barrier();
+            uint32_t h = (uint32_t)__popcll(holders & ((1ull << lane) - 1ull)), n_holders = 0;
+#pragma unroll
+            for (uint32_t w = 0; w < WAVES; ++w) { const uint32_t n = sh_scan[w]; h += w < wave ? n : 0u; n_holders += n; }
+            if (holds) {                                     // (each is on a node: at most as many as GPUs)
+                fin_off[tid] = h;
+                held_cost[h] = best.z == ND_NONE ? -1.f : cost;
+                held_g[h] = best.w;
+            }
+            barrier();
+            for (uint32_t i = tid; i < gpus; i += THREADS) {
+                const uint32_t n = i / gpn;
+                if (i - n * gpn < A.cnt[n]) {
+                    const uint32_t word = A.res[i], hv = fin_off[word >> 16];
+                    const float c = held_cost[hv];
+                    if (c >= 0.f) {
+                        const float asks = (c * (float)(word & 0xFFFFu)) / (float)held_g[hv];
+                        atomicAdd(&sh_mem[n], asks);
+                        if (share) share[hv * N + n] = asks;
+                    }
+                }
+            }
+            barrier();
+            uint32_t short_of = 0;
+            for (uint32_t n = lane; n < N; n += 64u) short_of |= !(sh_mem[n] <= A.mem_gb * 0.999f) ? 1u : 0u;
+            bool dropped = holds && best.z == ND_NONE;
+            if (__ballot(short_of != 0u)) {                  // (the same in all wavefronts) some node's memory can bind: job by job
+                if (n_mem == 1u && share) {
+                    if (wave == 0) {
+                        float left = A.mem_gb, next = lane < N && n_holders ? share[lane] : 0.f;
+                        for (uint32_t q = 0; q < n_holders; ++q) {
+                            const float asks = next;
+                            next = lane < N && q + 1u < n_holders ? share[(q + 1u) * N + lane] : 0.f;
+                            const bool bad = __ballot(!(asks <= left)) != 0ull;
+                            if (!bad) left = left - asks;
+                            else if (lane == 0) held_g[q] = 0u;
+                        }
+                    }
+                    barrier();
+                    dropped = dropped || (holds && held_g[h] == 0u);
+                } else {
+                    nd_finish<THREADS>(A, fin_np, fin_off, keep, A.touched, fin_list, sh_mem, sh_scan);
+                    __syncthreads();
+                    if (mine) a = A.assign[tid];
+                    dropped = holds && a.g == 0u;
+                    best.x = __float_as_uint(a.thr); best.y = a.plan; cost = a.mem_gb;
+                }
+            }
+            a = rk_assign{0u, 0u, 0.f, RK_NO_PLAN, 0.f};
+            if (holds && !dropped) { a.g = best.w; a.c = sh_cpl[ci] * best.w; a.mem_gb = cost; a.plan = best.y; a.thr = __uint_as_float(best.x); }
+            if (dropped) A.st.gi[tid] = -1;               // (its parts are still on the nodes, and its level is theirs)
+            // the total: the additions of nd_finish, a job per thread
+            {
+                double x = a.g ? (double)a.thr / (double)ref : 0.0;
+#pragma unroll
+                for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o, 64);
+                const uint32_t used = nd_wave_sum(state != RK_JOB_OUT ? a.g : 0u);
+                if (lane == 0) { sh_part[wave] = x; if (used) atomicAdd(&sh_used, used); }
+            }
+            barrier();
+            // ---- is anybody somewhere else than when the round began?
+            bool other = false;
+            for (uint32_t i = tid; i < gpus; i += THREADS) {
+                uint32_t word = A.res[i];
+                const uint32_t v = word >> 16;
+                if (v < J && A.st.gi[v] < 0) word = EMPTY;
+                other |= word != start_res[i];
+            }
+            if (tid == 0) {
+                double sum = 0.0;
+#pragma unroll
+                for (uint32_t w = 0; w < WAVES; ++w) sum += sh_part[w];
+                total = (float)sum;
+            }
+            const uint32_t used = sh_used;
+            // ---- the tick is closed and the next one opened, and those after it that start from what this round started from
+            const uint32_t round_state = state;
+            bool more = true;
+            for (;;) {
+                const double t = (double)tick * S.dt;
+                if (state != RK_JOB_OUT && sim_close(s, a, t, S.dt, delta, work)) {
+                    other = true;
+                    seg = s.g ? gi : -1;
+                    lvl = s.g ? ci : 0u;
+                }
+                if (tid == 0) {
+                    if (S.out.gpus_in_use) S.out.gpus_in_use[tick] = used;
+                    if (S.out.totals) S.out.totals[tick] = total;
+                }
+                if (++tick == S.n_ticks) { more = false; break; }
+                const double t1 = (double)tick * S.dt;
+                uint32_t now = RK_JOB_OUT;
+                if (mine && arrival <= t1 && !s.done) now = sim_frozen(s.g, s.held, s.n_reconf, delta, S.gate) ? RK_JOB_FROZEN : RK_JOB_NORMAL;
+                other |= now != state;
+                state = now;
+                const uint32_t frozen = (uint32_t)__popcll(__ballot(now == RK_JOB_FROZEN));
+                const bool any = __ballot(other) != 0ull;
+                if (lane == 0 && frozen) atomicAdd(&sh_open[turn], frozen);
+                if (lane == 0 && any) atomicOr(&sh_open[turn], 0x80000000u);
+                if (tid == 0) sh_open[turn == 2u ? 0u : turn + 1u] = 0u;       // (read by all before the barrier before)
+                barrier();
+                const uint32_t open = sh_open[turn];
+                turn = turn == 2u ? 0u : turn + 1u;
+                if (tid == 0 && S.out.frozen) S.out.frozen[tick] = open & 0x7FFFFFFFu;
+                if (open & 0x80000000u) break;
+            }
+            if (!more || ++done == K.rounds) break;
+            // ---- what the next round starts from: those who leave free their parts, changed jobs' values are looked up
+            {
+                const bool stays = state != RK_JOB_OUT && seg >= 0;
+                const int32_t gi_now = mine ? A.st.gi[tid] : -1;
+                const bool leaves = gi >= 0 && !stays;       // (dropped, or it has come to its end)
+                if (mine) {
+                    if (state != round_state || leaves) {
+                        fin_np[atomicAdd(&sh_list, 1u)] = tid;
+                        state8[tid] = (uint8_t)state;
+                    }
+                    if (leaves) { if (gi_now >= 0) A.st.gi[tid] = -1; sh_gone = 1u; }
+                }
+                barrier();
+                const uint32_t n_changed = sh_list;
+                if (sh_gone)
+                    for (uint32_t n = tid; n < N; n += THREADS) {
+                        uint32_t c = A.cnt[n], fg = 0, fc = 0;
+                        for (uint32_t i = 0; i < c;) {
+                            const uint32_t word = A.res[n * gpn + i], v = word >> 16;
+                            if (A.st.gi[v] >= 0) { ++i; continue; }
+                            fg += word & 0xFFFFu; fc += (word & 0xFFFFu) * sh_cpl[A.st.ci[v]];
+                            c -= 1u;
+                            A.res[n * gpn + i] = A.res[n * gpn + c];
+                            A.res[n * gpn + c] = EMPTY;
+                        }
+                        if (fg) { A.cnt[n] = c; A.free_g[n] += fg; A.free_c[n] += fc; }
+                    }
+                for (uint32_t i0 = 4u * wave; i0 < n_changed; i0 += 4u * WAVES) {
+                    const uint32_t i = i0 + (lane >> 4);
+                    refresh(fin_np[i < n_changed ? i : i0], i < n_changed);
+                }
+                barrier();
+                if (leaves) A.st.ci[tid] = 0u;
+                if (tid == 0) { sh_list = 0u; sh_gone = 0u; }
+                copy_nodes(keep, nodes);
+                barrier();
+            }
+        }
+        // ---- the state, for the next launch
+        if (mine) {
+            S.S.g[tid] = s.g; S.S.c[tid] = s.c; S.S.plan[tid] = s.plan; S.S.seg[tid] = seg; S.S.lvl[tid] = lvl;
+            S.S.owed[tid] = s.owed; S.S.done[tid] = s.done ? 1 : 0;
+            S.held[tid] = s.held; S.progress[tid] = s.progress; S.finish[tid] = s.finish; S.n_reconf[tid] = s.n_reconf;
+            S.F.state[tid] = (uint8_t)state;
+        }
+        {                                                    // where the jobs are: a job's parts in node order
+            const bool on = mine && A.st.gi[tid] >= 0;
+            auto parts = [&](uint32_t at, bool write) {
+                uint32_t p = 0;
+                for (uint32_t n = 0; n < N; ++n)
+                    for (uint32_t i = 0; i < A.cnt[n]; ++i) {
+                        const uint32_t word = A.res[n * gpn + i];
+                        if ((word >> 16) != tid) continue;
+                        const uint32_t k = word & 0xFFFFu;
+                        if (write) S.at_ent[at + p] = rk_place_entry{n, k, sh_cpl[A.st.ci[tid]] * k, 0.f};
+                        ++p;
+                    }
+                return p;
+            };
+            const uint32_t p = on ? parts(0u, false) : 0u;
+            uint32_t all;
+            const uint32_t at = nd_block_scan<THREADS>(p, all, sh_scan);
+            if (mine) S.at_off[tid] = at;
+            if (tid == 0) S.at_off[J] = all;
+            if (on) (void)parts(at, true);
+        }
+        if (tid == 0) {
+            *S.tick = tick;
+            __hip_atomic_store(S.h_tick, tick, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+    } else if constexpr (!SIM) {
         round();
         nd_finish<THREADS>(A, fin_np, fin_off, keep, A.touched, fin_list, sh_mem, sh_scan);
         if (tid == 0 && A.stats) { A.stats[0] = moves; A.stats[1] = full; A.stats[2] = shrinks; A.stats[3] = undone; A.stats[4] = 0u; }
@@ -1296,11 +1760,11 @@ __device__ __forceinline__ void nodes_lds(const KernArgs &K) {
 }
 
 template <int THREADS, bool LJ>
-__global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) { nodes_lds<THREADS, LJ, false>(K); }
+__global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) { nodes_lds<THREADS, LJ, false, false>(K); }
 
-struct NdSimArgs : NdKernArgs { SimArgs S; uint32_t rounds; };     // rounds of a launch, at most
-template <int THREADS>
-__global__ __launch_bounds__(THREADS) void k_sim_nodes(NdSimArgs K) { nodes_lds<THREADS, true, true>(K); }
+struct NdSimArgs : NdKernArgs { SimArgs S; uint32_t rounds, shares; NdStates states; };     // rounds of a launch, at most; TAB: shares, states
+template <int THREADS, bool TAB>
+__global__ __launch_bounds__(THREADS) void k_sim_nodes(NdSimArgs K) { nodes_lds<THREADS, true, true, TAB>(K); }
 
 __global__ __launch_bounds__(ND_THREADS) void k_reschedule_nodes(NdKernArgs K) {
     // what every job loses per GPU / CPU it gives, [2][n_jobs]: read at every look at a node's residents and at every
@@ -1845,8 +2309,9 @@ static int32_t nd_raise_lds(rk_ctx *ctx) {
     if (ctx->nodes_lds_raised) return RK_OK;
     const auto most = hipFuncAttributeMaxDynamicSharedMemorySize;
     const void *const fs[] = {reinterpret_cast<const void *>(k_nodes_lds<ND_SMALL_THREADS, true>), reinterpret_cast<const void *>(k_nodes_lds<ND_FEW_THREADS, true>),
-                              reinterpret_cast<const void *>(k_nodes_lds<ND_THREADS, false>), reinterpret_cast<const void *>(k_sim_nodes<ND_SMALL_THREADS>),
-                              reinterpret_cast<const void *>(k_sim_nodes<ND_FEW_THREADS>)};
+                              reinterpret_cast<const void *>(k_nodes_lds<ND_THREADS, false>), reinterpret_cast<const void *>(k_sim_nodes<ND_SMALL_THREADS, false>),
+                              reinterpret_cast<const void *>(k_sim_nodes<ND_FEW_THREADS, false>), reinterpret_cast<const void *>(k_sim_nodes<ND_THREADS, true>),
+                              reinterpret_cast<const void *>(k_sim_nodes<ND_SMALL_THREADS, true>), reinterpret_cast<const void *>(k_sim_nodes<ND_FEW_THREADS, true>)};
     for (const void *f : fs) RK_HIP(ctx, hipFuncSetAttribute(f, most, (int)ND_LDS_MOST));
     RK_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(k_reschedule_nodes), most, 2 * RK_MAX_JOBS_PER_ROUND * sizeof(float)));
     ctx->nodes_lds_raised = true;
@@ -1890,6 +2355,8 @@ int32_t rk_launch_reschedule_nodes(rk_ctx *ctx, const float *ref_thr, const rk_p
 // Ticks of a simulation whose rounds search node by node, from the one that *A.tick says (k_sim_init and k_sim_step have
 // opened it): enough launches on the context's stream for all of them, a launch past the last tick returns at once.
 constexpr uint32_t SIM_NODES_ROUNDS = 64;        // rounds of a launch
+constexpr uint64_t ND_STATES_MOST = 1u << 19;    // states of all jobs that are found beforehand (80 bytes each)
+constexpr uint32_t ND_STATES_PER_TICK = 16384;
 
 bool rk_sim_nodes_fit(uint32_t n_jobs, const rk_nodes *nodes) {
     const size_t N = nodes->n_nodes, gpus = N * nodes->gpus_per_node;
@@ -1910,13 +2377,34 @@ int32_t rk_launch_sim_nodes(rk_ctx *ctx, const SimArgs &S, const float *ref_thr,
     K.rounds = SIM_NODES_ROUNDS;
     K.b.book = false;
     const uint32_t J = K.b.n_jobs;
-    const size_t lds = nd_lds_words(J, K.b.n_nodes, K.b.nodes_words, true, true) * sizeof(uint32_t);
+    const size_t N = K.b.n_nodes, gpus = N * K.b.gpn;
+    size_t lds = nd_lds_words(J, N, K.b.nodes_words, true, true) * sizeof(uint32_t);
     const NdKernArgs prepare = K;
+    // With a job per thread, and where it pays to find all states of the jobs beforehand: STATES
+    const uint64_t per_job = ((uint64_t)table->max_segs_per_job + 1u) * grid->n_cpu, states = J * per_job;
+    const size_t lds_tab = lds + nd_states_words(J, N, gpus) * sizeof(uint32_t);
+    const bool tab = J <= ND_THREADS && lds_tab <= ND_LDS_MOST && states <= ND_STATES_MOST && states <= (uint64_t)ND_STATES_PER_TICK * S.n_ticks;
+    if (tab) {
+        lds = lds_tab;
+        char *mem;
+        if ((rc = rk_scratch(ctx, SL_ND_STATES, states * (ND_STATE_WORDS * sizeof(uint32_t) + sizeof(uint4)), (void **)&mem))) return rc;
+        K.states.words = reinterpret_cast<uint32_t *>(mem);
+        K.states.best = reinterpret_cast<uint4 *>(mem + states * ND_STATE_WORDS * sizeof(uint32_t));
+        K.states.per_job = (uint32_t)per_job;
+        K.shares = nd_share_words(N, gpus) ? 1u : 0u;
+        NdKernArgs all = prepare;
+        all.b.state = nullptr;                               // (as if everybody took part)
+        k_nd_states<<<dim3(J, grid->n_cpu), 256, 0, ctx->stream>>>(all, K.states);
+        RK_CHECK_LAUNCH(ctx, "k_nd_states");
+    }
     for (uint32_t t = 0; t < S.n_ticks; t = S.n_ticks - t > SIM_NODES_ROUNDS ? t + SIM_NODES_ROUNDS : S.n_ticks) {
         k_nd_prepare<<<(J + 3) / 4, 256, 0, ctx->stream>>>(prepare);
         RK_CHECK_LAUNCH(ctx, "k_nd_prepare");
-        if (J <= ND_FEW_THREADS) k_sim_nodes<ND_FEW_THREADS><<<1, ND_FEW_THREADS, lds, ctx->stream>>>(K);
-        else k_sim_nodes<ND_SMALL_THREADS><<<1, ND_SMALL_THREADS, lds, ctx->stream>>>(K);
+        if (tab && J > ND_SMALL_THREADS) k_sim_nodes<ND_THREADS, true><<<1, ND_THREADS, lds, ctx->stream>>>(K);
+        else if (tab && J > ND_FEW_THREADS) k_sim_nodes<ND_SMALL_THREADS, true><<<1, ND_SMALL_THREADS, lds, ctx->stream>>>(K);
+        else if (tab) k_sim_nodes<ND_FEW_THREADS, true><<<1, ND_FEW_THREADS, lds, ctx->stream>>>(K);
+        else if (J <= ND_FEW_THREADS) k_sim_nodes<ND_FEW_THREADS, false><<<1, ND_FEW_THREADS, lds, ctx->stream>>>(K);
+        else k_sim_nodes<ND_SMALL_THREADS, false><<<1, ND_SMALL_THREADS, lds, ctx->stream>>>(K);
         RK_CHECK_LAUNCH(ctx, "k_sim_nodes");
     }
     return RK_OK;

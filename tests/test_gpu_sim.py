@@ -287,3 +287,34 @@ def test_simulations_one_after_the_other_without_waiting(gpu, orc):
         got.update({k: getattr(res, k).cpu().numpy()[:n] for k in ("gpus_in_use", "totals", "frozen")})
         same({k: v.view(np.uint32) if v.dtype == np.int32 else v for k, v in got.items()}, want)
     run.close()
+
+
+@pytest.mark.parametrize("jobs,nodes,gpn,levels,tiers,mem,gate", [
+    (1, 1, 64, 5, (64.0,), 512.0, 0.97),                     # one job, one wide node
+    (256, 9, 7, 5, (64.0,), 100.0, 0.97),                    # the last job of 256 threads; nodes of an odd size; memory binds
+    (257, 3, 4, 5, (0.0, 64.0, 1024.0), 1100.0, 0.97),       # ... and the first of 512; several tiers, job by job
+    (513, 32, 8, 5, (2048.0,), 2048.0, -np.inf),             # 1,024 threads; too many nodes for shares by job and node
+    (40, 8, 8, 64, (64.0,), 4096.0, 0.97),                   # long CPU steps
+    (1025, 8, 8, 5, (2048.0,), 2048.0, 0.97),                # more jobs than threads: states are not found beforehand
+])
+def test_simulation_over_nodes_at_the_sizes_it_is_laid_out_for(gpu, orc, jobs, nodes, gpn, levels, tiers, mem, gate):
+    """A simulation over nodes finds the states of its jobs beforehand, gives a job to a thread and a round to a wavefront;
+    memory is dealt out by node where it binds.  The same trajectories as the oracle's at the edges of all of that."""
+    coef, ints = workloads.draw_jobs(7, 11, 0, np.arange(jobs), param_buckets=[(0.5, 0.1e9, 1.3e9), (0.5, 1.3e9, 20e9)],
+                                     layer_choices=(12, 24, 32, 40))
+    ratios = np.array([1, 2, 4, 8, 16], np.uint32) if levels == 5 else np.arange(1, levels + 1, dtype=np.uint32)
+    gpus, cpn = nodes * gpn, 16 * gpn
+    wl = workloads.Workload("nodes", coef, ints, workloads.Bounds(g_max=gpus), workloads.Grid(ratios, 1, np.array(tiers, np.float32), 0),
+                            workloads.Env(), workloads.Cluster(gpus, cpn * nodes, mem * nodes))
+    r = orc.schedule_round(wl, n_threads=16)
+    n_ticks, dt = 41, 120.0
+    tr = workloads.trace(jobs, horizon_s=n_ticks * dt)
+    work = workloads.job_lengths_s(tr.u_duration) * wl.coef[:, 16]
+    want = orc.simulator.simulate(wl.coef[:, 16], r["table"], wl.grid, wl.cluster, r["best_thr"], r["best_plan"], r["curve_thr"],
+                                  tr.arrival, work, tr.delta, dt, n_ticks, gate=gate, policy="nodes", nodes=(nodes, gpn, cpn, mem))
+    run = gpu(wl)
+    run.enumerate()
+    for _ in range(2):
+        same(run_on_gpu(run, r, tr.arrival, work, tr.delta, dt, n_ticks, gate, policy=2, nodes=(nodes, gpn, cpn, mem)), want)
+    assert want["gpus_in_use"].max() > 0
+    run.close()
