@@ -641,8 +641,11 @@ static inline size_t nd_lds_words(size_t J, size_t N, size_t nodes_words, bool l
 // those words, who is on the nodes when a round begins, every job's state and, per job on the nodes, what its memory costs and
 // its GPUs; with few nodes also what every job asks of every node (share).
 constexpr uint32_t ND_SHARES = 2048;
+constexpr uint32_t ND_CHANGED = 48;                        // jobs whose place in the order is found one by one; more: all are sorted
 static inline size_t nd_share_words(size_t N, size_t gpus) { return N <= 64 && N * gpus <= ND_SHARES ? N * gpus : 0; }
-static inline size_t nd_states_words(size_t J, size_t N, size_t gpus) { return 3 * gpus + nd_share_words(N, gpus) + (J + 3) / 4 + 1; }
+static inline size_t nd_tab_words(size_t threads, size_t N, size_t gpus, size_t nodes_words) {     // a job per thread
+    return nd_lds_words(threads, N, nodes_words, true, true) + 3 * gpus + nd_share_words(N, gpus) + threads / 4 + 8;
+}
 
 // The loop with the nodes in LDS.  It is a chain of small decisions, so what bounds it is the latency of one after
 // the other.  Here the first wavefront makes a whole step of ScheduleJob by itself, a node per lane on the walk, a
@@ -658,7 +661,8 @@ static inline size_t nd_states_words(size_t J, size_t N, size_t gpus) { return 3
 // where they are, and only jobs that came, went or thawed have theirs found again.  As launches of their own, replayed as
 // a graph, the preparation, the round and the tick took 5, 102 and 9 us with 9 us between them, of which loading the
 // nodes and jobs was 5; 406 jobs, 720 ticks: 57.4 -> 46.7 ms, 60 jobs, 100 ticks: 2.59 -> 1.56 ms.
-template <int THREADS, bool LJ, bool SIM, bool TAB, class KernArgs>
+// GPN: the GPUs of a node where they are known (0: not): divisions by it are shifts, loops over a node's residents are unrolled.
+template <int THREADS, bool LJ, bool SIM, bool TAB, uint32_t GPN, class KernArgs>
 __device__ __forceinline__ void nodes_lds(const KernArgs &K) {
     static_assert((LJ || !SIM) && (SIM || !TAB), "ticks of a simulation have the jobs in LDS; the states are found for them");
     extern __shared__ uint4 sh_raw[];
@@ -670,7 +674,8 @@ __device__ __forceinline__ void nodes_lds(const KernArgs &K) {
     __shared__ uint32_t sh_did, sh_touched;                 // what the first wavefront's steps ended in
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
     NdArgs A(K.b, K.X);
-    const uint32_t J = A.n_jobs, N = A.n_nodes, gpn = A.gpn, gpus = N * gpn;
+    if constexpr (TAB) { A.floor_seg = nullptr; A.floor_c = nullptr; }      // (nobody has a floor in a simulation)
+    const uint32_t J = A.n_jobs, N = A.n_nodes, gpn = GPN ? GPN : A.gpn, gpus = N * gpn;
     const uint32_t EMPTY = (J << 16) | 0xFFFFu;              // no resident: a job that has no index, whose slopes are infinite
     const float INF = __int_as_float(0x7F800000);
     uint32_t tick = 0;
@@ -679,17 +684,37 @@ __device__ __forceinline__ void nodes_lds(const KernArgs &K) {
         if (tick >= K.S.n_ticks) return;                     // (the simulation is over)
     }
 
-    // ---- everything into LDS
-    uint32_t *const nodes = reinterpret_cast<uint32_t *>(sh_raw);
-    uint32_t *const keep = nodes + A.nodes_words;
-    uint32_t *at = keep + A.nodes_words;
+    // ---- everything into LDS.  TAB: room for a job per thread, and what the jobs have comes first, so that the addresses
+    // are known beforehand (a wavefront that works alone pays for every instruction).
+    const uint32_t JL = TAB ? (uint32_t)THREADS : J;
+    uint32_t *at = reinterpret_cast<uint32_t *>(sh_raw);
     auto take = [&](size_t words) { uint32_t *p = at; at += words; return p; };
-    A.free_g = nodes; A.free_c = nodes + N; A.cnt = nodes + 2 * N; A.res = nodes + ((3 * N + 3) & ~3u);
-    if constexpr (LJ) A.give = reinterpret_cast<uint4 *>(take(4 * (size_t)J));
-    if constexpr (LJ) { A.udc_c = reinterpret_cast<unsigned long long *>(take(2 * (size_t)J)); A.okey = reinterpret_cast<unsigned long long *>(take(2 * (size_t)J)); }
-    float *const sh_ds = reinterpret_cast<float *>(take(2 * ((size_t)J + 1)));
+    uint32_t *nodes = at;
+    if constexpr (!TAB) at += 2 * A.nodes_words;
+    if constexpr (LJ) A.give = reinterpret_cast<uint4 *>(take(4 * (size_t)JL));
+    if constexpr (LJ) { A.udc_c = reinterpret_cast<unsigned long long *>(take(2 * (size_t)JL)); A.okey = reinterpret_cast<unsigned long long *>(take(2 * (size_t)JL)); }
+    float *const sh_ds = reinterpret_cast<float *>(take(2 * ((size_t)JL + 1)));
+    if constexpr (LJ) {
+        auto words = [&](auto &p) { p = reinterpret_cast<std::decay_t<decltype(p)>>(take(JL)); };        // a per-job array of words in LDS
+        words(A.st.gi); words(A.st.ci); words(A.ug); words(A.uc); words(A.udg); words(A.gain_g); words(A.gain_c);
+        words(A.tgt_g); words(A.lvl_g); words(A.lvl_c); words(A.first);
+        words(A.touched); words(A.give_c);
+    }
+    uint32_t *const so = LJ ? take((size_t)JL + 1) : nullptr;
+    uint32_t *fin_np = reinterpret_cast<uint32_t *>(sh_ds), *fin_off = fin_np + J, *fin_list = nullptr, *old_state = nullptr;
+    if constexpr (SIM) { fin_np = take(JL); fin_off = take(JL); fin_list = take(JL); if (!TAB) old_state = take(JL); }   // (what the next round needs again is not working memory of this one's end)
+    uint8_t *state8 = nullptr;
+    if constexpr (TAB) {
+        state8 = reinterpret_cast<uint8_t *>(take(THREADS / 4));
+        at += (4u - (uint32_t)(at - nodes) % 4u) % 4u;       // (whole pieces)
+        nodes = take(2 * A.nodes_words);
+    }
+    uint32_t *const keep = nodes + A.nodes_words;
     float *const sh_mem = reinterpret_cast<float *>(take(N));
     uint32_t *const sh_mark = take((J + 31u) / 32u);         // a bit per job: changed by the step under way and remembered in memory
+    uint32_t *start_res = nullptr, *held_g = nullptr;        // (TAB)
+    float *held_cost = nullptr, *share = nullptr;
+    A.free_g = nodes; A.free_c = nodes + N; A.cnt = nodes + 2 * N; A.res = nodes + ((3 * N + 3) & ~3u);
     for (uint32_t i = tid; i < (J + 31u) / 32u; i += THREADS) sh_mark[i] = 0u;
     for (uint32_t i = tid; i < A.nodes_words; i += THREADS) nodes[i] = i < N ? gpn : i < 2 * N ? A.cpn : i < 3 * N ? 0u : EMPTY;
     if (tid < A.X.grid.n_cpu) {
@@ -698,11 +723,6 @@ __device__ __forceinline__ void nodes_lds(const KernArgs &K) {
     }
     if (tid == 0) sh_list = 0u;
     if constexpr (LJ) {
-        auto words = [&](auto &p) { p = reinterpret_cast<std::decay_t<decltype(p)>>(take(J)); };         // a per-job array of words in LDS
-        words(A.st.gi); words(A.st.ci); words(A.ug); words(A.uc); words(A.udg); words(A.gain_g); words(A.gain_c);
-        words(A.tgt_g); words(A.lvl_g); words(A.lvl_c); words(A.first);
-        words(A.touched); words(A.give_c);
-        uint32_t *const so = take((size_t)J + 1);
         for (uint32_t j = tid; j < J; j += THREADS) {        // (all of a job's loads before the first store)
             const NdBody &b = K.b;
             const int32_t gi = b.st.gi[j], tgt = b.tgt_g[j];
@@ -719,29 +739,22 @@ __device__ __forceinline__ void nodes_lds(const KernArgs &K) {
         if (tid == 0) so[J] = A.X.tb.seg_off[J];
         A.seg_off = so;
     }
-    uint32_t *fin_np = reinterpret_cast<uint32_t *>(sh_ds), *fin_off = fin_np + J, *fin_list = A.res, *old_state = nullptr;
-    if constexpr (SIM) {                                     // (what the next round needs again is not working memory of this one's end)
-        fin_np = take(J); fin_off = take(J); fin_list = take(J); old_state = take(J);
-        for (uint32_t j = tid; j < J; j += THREADS) old_state[j] = A.state[j];
-    }
-    uint32_t *start_res = nullptr, *held_g = nullptr;        // (TAB)
-    float *held_cost = nullptr, *share = nullptr;
-    uint8_t *state8 = nullptr;
+    if constexpr (!SIM) fin_list = A.res;
+    if constexpr (SIM && !TAB) for (uint32_t j = tid; j < J; j += THREADS) old_state[j] = A.state[j];
     if constexpr (TAB) {
         start_res = take(gpus); held_cost = reinterpret_cast<float *>(take(gpus)); held_g = take(gpus);
         if (K.shares) share = reinterpret_cast<float *>(take((size_t)N * gpus));
-        state8 = reinterpret_cast<uint8_t *>(take((J + 3u) / 4u));
         for (uint32_t j = tid; j < J; j += THREADS) state8[j] = A.state[j];
         A.state = state8;
-        A.lvl_g = A.st.ci;                                   // (nobody has a floor: a GPU step stays on the level)
+        A.lvl_g = A.st.ci;                                   // (a GPU step stays on the level)
     }
     uint32_t bad = 0, any_first = 0;
     for (uint32_t j = tid; j < J; j += THREADS) {
-        sh_ds[j] = A.ds_g[j]; sh_ds[J + 1 + j] = A.ds_c[j];
+        sh_ds[j] = A.ds_g[j]; sh_ds[JL + 1 + j] = A.ds_c[j];
         bad |= A.first[j] & 2u; any_first |= A.first[j] & 1u;
     }
-    A.ds_g = sh_ds; A.ds_c = sh_ds + J + 1;
-    if (tid == 0) sh_ds[J] = sh_ds[2 * J + 1] = INF;
+    A.ds_g = sh_ds; A.ds_c = sh_ds + JL + 1;
+    if (tid == 0) sh_ds[J] = sh_ds[JL + 1 + J] = INF;
     __syncthreads();
     // the jobs' parts are booked (k_nd_prepare has checked them): a job per thread, or a wavefront where a job has many.
     // These are listed where the copy of the nodes will be; parts that fit the nodes are three GPUs or more a job, so a
@@ -891,6 +904,7 @@ __device__ __forceinline__ void nodes_lds(const KernArgs &K) {
     // a / b from 1 / b for a < 2^21: (a + 1/2) / b is further from a whole number than the product's error
     auto over = [&](uint32_t a, float rcp) { return (uint32_t)(((float)a + 0.5f) * rcp); };
     const float rcp_gpn = 1.f / (float)gpn;
+    auto node_of = [&](uint32_t i) { if constexpr (GPN != 0u) return i / GPN; else return over(i, rcp_gpn); };
     enum : uint32_t { DID_NOTHING = 0, DID_GPUS = 1, DID_CPUS = 2, DID_UNDO = 4 };
     // A GPU step of job j: DID_GPUS when it is committed, else DID_NOTHING (jobs put back; the nodes are `dirty` or as before)
     auto gpu_step = [&](uint32_t j) -> uint32_t {
@@ -899,7 +913,7 @@ __device__ __forceinline__ void nodes_lds(const KernArgs &K) {
         if (!st.any) return DID_NOTHING;
         begin_jobs();
         const int32_t fl = rs_fl_s(A, j), gi_j = A.st.gi[j];
-        const uint32_t ci_j = A.st.ci[j];
+        const uint32_t ci_j = TAB ? st.lvl : A.st.ci[j];
         const bool below_min = fl >= 0 && gi_j < fl;
         const uint32_t per_gpu = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh_cpl[st.lvl]);
         const float rcp = sh_rcp[st.lvl];
@@ -911,7 +925,7 @@ __device__ __forceinline__ void nodes_lds(const KernArgs &K) {
             for_parts(j, std::false_type{}, [&](uint32_t i, uint32_t word, unsigned long long m) {
                 bool short_of = false;
                 if ((m >> lane) & 1ull) {
-                    const uint32_t n = over(i, rcp_gpn), have = A.free_c[n];
+                    const uint32_t n = node_of(i), have = A.free_c[n];
                     const unsigned long long need = (unsigned long long)more * (word & 0xFFFFu);
                     if (have < need) short_of = true;
                     else A.free_c[n] = have - (uint32_t)need;
@@ -1062,7 +1076,7 @@ __device__ __forceinline__ void nodes_lds(const KernArgs &K) {
                         const uint32_t k = (m >> lane) & 1ull ? w & 0xFFFFu : 0u, upto = nd_wave_scan(k), all = wave_lane_u32(upto, 63u);
                         const uint32_t behind = all - upto;  // what the entries after this one have
                         if (k && behind < rest) {
-                            const uint32_t give = k < rest - behind ? k : rest - behind, n1 = over(i, rcp_gpn);
+                            const uint32_t give = k < rest - behind ? k : rest - behind, n1 = node_of(i);
                             A.free_g[n1] += give; A.free_c[n1] += give * per_v;
                             if (give < k) A.res[i] = w - give;
                             else {                           // (a job is on a node once: no other lane's node, no entry still to come)
@@ -1097,7 +1111,7 @@ __device__ __forceinline__ void nodes_lds(const KernArgs &K) {
         bool ok = true;
         for_parts(j, std::false_type{}, [&](uint32_t i, uint32_t word, unsigned long long m) {
             while (m) {
-                const uint32_t s = (uint32_t)__ffsll((long long)m) - 1u, n = over(wave_lane_u32(i, s), rcp_gpn);
+                const uint32_t s = (uint32_t)__ffsll((long long)m) - 1u, n = node_of(wave_lane_u32(i, s));
                 m &= m - 1ull;
                 const unsigned long long need = (unsigned long long)more * (wave_lane_u32(word, s) & 0xFFFFu);
                 for (;;) {
@@ -1125,7 +1139,7 @@ __device__ __forceinline__ void nodes_lds(const KernArgs &K) {
                     }
                     const uint32_t less = sh_cpl[ci0] - sh_cpl[ci0 - 1u];
                     for_parts(who, std::false_type{}, [&](uint32_t i2, uint32_t w2, unsigned long long m2) {     // it gives a level on all its nodes
-                        if ((m2 >> lane) & 1ull) A.free_c[over(i2, rcp_gpn)] += less * (w2 & 0xFFFFu);
+                        if ((m2 >> lane) & 1ull) A.free_c[node_of(i2)] += less * (w2 & 0xFFFFu);
                         return true;
                     });
                     rs_wave_order();
@@ -1228,7 +1242,7 @@ __device__ __forceinline__ void nodes_lds(const KernArgs &K) {
             for (uint32_t v = tid; v < J; v += THREADS)
 #pragma unroll
                 for (uint32_t r = 0; r < 2; ++r) {           // ascending jobs: the lower one stays among equals
-                    const float y = sh_ds[r * (J + 1) + v];
+                    const float y = sh_ds[r * (JL + 1) + v];
                     if (y < a[r]) { b[r] = a[r]; a[r] = y; ia[r] = v; }
                     else if (y < b[r]) b[r] = y;
                 }
@@ -1326,19 +1340,25 @@ __device__ __forceinline__ void nodes_lds(const KernArgs &K) {
     if constexpr (TAB) {
 
         // Ticks of a simulation whose jobs' states are all known: the first wavefront makes a round by itself, without barriers,
-        // since what a committed step changes of a job is a look into the table; what it has of the jobs it looks for the
-        // next one in the list of those that take part.  A job per thread has in registers what the ticks need of it.
+        // since what a committed step changes of a job is a look into the table, and who comes next is found in a list that
+        // is in order before the round.  A job per thread has in registers what the ticks need of it.  What bounds it is how
+        // many instructions that one wavefront needs, 6.7 cycles each: addresses that are known beforehand, nodes of eight GPUs
+        // as a case of their own, and the order kept from round to round took a third of them away.  406 jobs on 8 nodes, 720
+        // ticks: 41.0 ms with searches between barriers, 28.5 with the states looked up, 18.8 now; 200 jobs on 16 nodes, 60
+        // ticks: 1.81 and 0.78 ms; 900 on 128 nodes: 27.1 and 19.2.
         const SimArgs &S = K.S;
-        __shared__ uint32_t sh_open[3], sh_used, sh_gone;
+        __shared__ uint32_t sh_open[3], sh_used, sh_gone, sh_changed[WAVES], sh_who[ND_CHANGED], sh_before[ND_CHANGED];
+        __shared__ unsigned long long sh_was[ND_CHANGED], sh_now[ND_CHANGED];
         __shared__ double sh_part[ND_WAVES];
         const uint32_t n_cpu = A.X.grid.n_cpu, n_mem = A.X.grid.n_mem;
         const bool mine = tid < J;
         auto barrier = [&]() { rs_lds_barrier(); };          // (what the wavefronts tell each other lies in LDS)
-        // where a state's word (lane & 15) goes: the job's place in an array of words from `nodes` on
+        // where a state's word (lane & 15) goes: the job's place in an array of words
         const uint32_t field = lane & 15u;
         uint32_t to = 0, stride = 1u;
+        uint32_t *const words0 = reinterpret_cast<uint32_t *>(sh_raw);
         {
-            auto at_word = [&](const void *p) { return (uint32_t)(reinterpret_cast<const uint32_t *>(p) - nodes); };
+            auto at_word = [&](const void *p) { return (uint32_t)(reinterpret_cast<const uint32_t *>(p) - words0); };
             const uint32_t places[ND_STATE_WORDS] = {at_word(A.ug), at_word(A.udg), at_word(A.gain_g), at_word(A.tgt_g), at_word(A.uc), at_word(A.gain_c),
                                                      at_word(A.lvl_c), at_word(A.udc_c), at_word(A.udc_c) + 1u, at_word(A.ds_g), at_word(A.ds_c),
                                                      at_word(A.give), at_word(A.give) + 1u, at_word(A.give) + 2u, at_word(A.give) + 3u, at_word(A.give_c)};
@@ -1348,111 +1368,112 @@ __device__ __forceinline__ void nodes_lds(const KernArgs &K) {
             if (field == ND_GIVES || field == ND_LOSS || field == ND_TO || field == ND_DS_G1) stride = 4u;
         }
         const bool slope = field == ND_DS_G || field == ND_DS_C;
+        auto state_word = [&](uint32_t v, int32_t gi, uint32_t ci) { return K.states.words[nd_state_at(K.states, v, n_cpu, gi, ci) * ND_STATE_WORDS + field]; };
         auto refresh = [&](uint32_t v, bool on) {            // job v of the lane's row of 16, from what it holds
             const int32_t gi = A.st.gi[v];
             const uint32_t ci = A.st.ci[v], state = state8[v];
             if (!on) return;
-            uint32_t w = K.states.words[nd_state_at(K.states, v, n_cpu, gi, ci) * ND_STATE_WORDS + field];
+            uint32_t w = state_word(v, gi, ci);
             if (slope && state != RK_JOB_NORMAL) w = __float_as_uint(INF);     // (who takes no part gives nothing)
-            nodes[to + v * stride] = w;
+            words0[to + v * stride] = w;
         };
         auto copy_alone = [&](uint32_t *dst, const uint32_t *src) {            // the nodes, by the first wavefront
             for (uint32_t i = lane; i < A.nodes_words / 4u; i += 64u) reinterpret_cast<uint4 *>(dst)[i] = reinterpret_cast<const uint4 *>(src)[i];
             rs_wave_order();
         };
-        uint32_t *const list = fin_list;                     // the jobs that may be served, their places in the order in okey
+        const uint32_t NO_SLOPE = 0xFF800000u;               // an infinite slope as a word that orders like it
+        uint32_t *const list = fin_list;                     // the jobs that may be served, in the loop's order
         auto round_alone = [&](uint32_t n_list) {
-            unsigned long long last_key = ~0ull;
-            uint32_t last_j = 0u, free_c = 0;
-            bool fresh = true;
+            uint32_t pos = 0, free_c = 0;                    // the first job of the list that has not been looked at
+            bool fresh = true, with_c = false;               // (with_c: the CPUs' slopes are those of the present state)
             RsMin low[2];
             low[0] = low[1] = RsMin{INF, INF, ND_NONE};
+            // the two lowest slopes of a resource and whose the lowest is, among those who are on the nodes (nobody else gives)
+            auto lowest = [&](uint32_t r) {
+                const float *const ds = sh_ds + r * (JL + 1);
+                uint32_t v = A.res[lane < gpus ? lane : 0u] >> 16, x = rs_ordered(ds[v]), y = NO_SLOPE;    // (nobody: infinite slopes)
+                for (uint32_t i = lane + 64u; i < gpus; i += 64u) {
+                    const uint32_t w = A.res[i] >> 16, z = rs_ordered(ds[w]);
+                    const bool first = z < x || (z == x && w < v);
+                    const uint32_t behind = first ? x : z;   // the one that is not, if it is another job's
+                    y = w != v && behind < y ? behind : y;
+                    if (first) { x = z; v = w; }
+                }
+                const uint32_t least = wave_min_u32_rows(x), whose = wave_min_u32_rows(x == least ? v : ND_NONE);
+                const uint32_t second = wave_min_u32_rows(v == whose ? y : x);
+                low[r] = RsMin{rs_unordered(least), rs_unordered(second), least == NO_SLOPE ? ND_NONE : whose};
+            };
             for (;;) {
                 if (fresh) {
-                    // what the nodes can give at every CPU level, and all free CPUs (four sums at a time); a lane ends with its level's
-                    uint32_t give = 0;
-                    for (uint32_t l0 = 0; l0 <= n_cpu; l0 += 4u) {
-                        uint32_t t[4] = {0u, 0u, 0u, 0u};
-                        float rcp[4];
-#pragma unroll
-                        for (uint32_t u = 0; u < 4; ++u) rcp[u] = l0 + u < n_cpu ? sh_rcp[l0 + u] : 1.f;
-                        for (uint32_t n = lane; n < N; n += 64u) {
-                            const uint32_t fg = A.free_g[n], fc = A.free_c[n];
-#pragma unroll
-                            for (uint32_t u = 0; u < 4; ++u) {
-                                const uint32_t by_cpu = l0 + u < n_cpu ? over(fc, rcp[u]) : fc;
-                                t[u] += l0 + u >= n_cpu || by_cpu < fg ? by_cpu : fg;
+                    // what the nodes can give at every CPU level, and all free CPUs
+                    if (n_cpu > 16u) {                       // a level per lane, one node after the other
+                        const float rcp = lane < n_cpu ? sh_rcp[lane] : 1.f;
+                        uint32_t t = 0, all = 0;
+                        for (uint32_t n = 0; n < N; ++n) {
+                            const uint32_t fg = A.free_g[n], fc = A.free_c[n], by_cpu = over(fc, rcp);
+                            t += by_cpu < fg ? by_cpu : fg;
+                            all += fc;
+                        }
+                        if (lane < n_cpu) sh_take[lane] = t;
+                        free_c = one(all);
+                    } else if (N <= 16u) {                   // a level per row of lanes, a node per lane
+                        const uint32_t n = lane & 15u, fg = n < N ? A.free_g[n] : 0u, fc = n < N ? A.free_c[n] : 0u;
+                        for (uint32_t l0 = 0; l0 <= n_cpu; l0 += 4u) {
+                            const uint32_t l = l0 + (lane >> 4);
+                            const uint32_t by_cpu = l < n_cpu ? over(fc, sh_rcp[l]) : fc;
+                            uint32_t t = l >= n_cpu || by_cpu < fg ? by_cpu : fg;
+                            t += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)t, 0x111, 0xF, 0xF, true);     // row_shr:1, 2, 4, 8
+                            t += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)t, 0x112, 0xF, 0xF, true);
+                            t += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)t, 0x114, 0xF, 0xF, true);
+                            t += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)t, 0x118, 0xF, 0xF, true);
+                            if (n == 15u && l < n_cpu) sh_take[l] = t;
+                            if (l0 + 4u > n_cpu) free_c = wave_lane_u32(t, (n_cpu - l0) * 16u + 15u);
+                        }
+                    } else {
+                        for (uint32_t l = 0; l <= n_cpu; ++l) {
+                            const float rcp = l < n_cpu ? sh_rcp[l] : 1.f;
+                            uint32_t t = 0;
+                            for (uint32_t n = lane; n < N; n += 64u) {
+                                const uint32_t fg = A.free_g[n], fc = A.free_c[n], by_cpu = l < n_cpu ? over(fc, rcp) : fc;
+                                t += l >= n_cpu || by_cpu < fg ? by_cpu : fg;
                             }
-                        }
-#pragma unroll
-                        for (uint32_t u = 0; u < 4; ++u) {
-                            const uint32_t sum = nd_wave_sum(t[u]);
-                            if (l0 + u == n_cpu) free_c = sum;
-                            else if (lane == l0 + u) give = sum;
+                            t = nd_wave_sum(t);
+                            if (l < n_cpu) sh_take[l] = t;
+                            else free_c = t;
                         }
                     }
-                    if (lane < n_cpu) sh_take[lane] = give;
-                    // the two lowest slopes and whose the lowest is, among those who are on the nodes (nobody else gives)
-                    float a[2] = {INF, INF}, b[2] = {INF, INF};
-                    uint32_t ia[2] = {ND_NONE, ND_NONE};
-                    for (uint32_t i = lane; i < gpus; i += 64u) {
-                        const uint32_t v = A.res[i] >> 16;   // (nobody: infinite slopes)
-#pragma unroll
-                        for (uint32_t r = 0; r < 2; ++r) {
-                            const float y = sh_ds[r * (J + 1) + v];
-                            if (!(y < INF)) continue;
-                            if (y < a[r] || (y == a[r] && v < ia[r])) { if (ia[r] != v) b[r] = a[r]; a[r] = y; ia[r] = v; }
-                            else if (v != ia[r]) b[r] = fminf(b[r], y);
-                        }
-                    }
-#pragma unroll
-                    for (uint32_t r = 0; r < 2; ++r) {
-                        const uint32_t x = rs_ordered(a[r]), least = wave_min_u32_rows(x);
-                        const uint32_t whose = wave_min_u32_rows(x == least ? ia[r] : ND_NONE);
-                        const uint32_t second = wave_min_u32_rows(ia[r] != ND_NONE && ia[r] == whose ? rs_ordered(b[r]) : x);
-                        low[r] = RsMin{rs_unordered(least), rs_unordered(second), whose};
-                    }
+                    lowest(0);
+                    with_c = false;
                     rs_wave_order();
                 }
-                // the first job of the list in the order that is still to be served and finds something to do
-                unsigned long long my_key = 0ull;
-                uint32_t my_j = ND_NONE;
-                constexpr uint32_t UN = 4;
-                for (uint32_t p0 = lane; p0 < n_list; p0 += UN * 64u) {
-                    unsigned long long key[UN], dc[UN];
-                    float ug[UN], uc[UN];
-                    uint32_t jj[UN], dg[UN], take[UN];
-#pragma unroll
-                    for (uint32_t k = 0; k < UN; ++k) {
-                        const uint32_t p = p0 + k * 64u < n_list ? p0 + k * 64u : p0;
-                        jj[k] = list[p]; key[k] = A.okey[p];
-                    }
-#pragma unroll
-                    for (uint32_t k = 0; k < UN; ++k) {
-                        ug[k] = A.ug[jj[k]]; uc[k] = A.uc[jj[k]]; dg[k] = A.udg[jj[k]]; dc[k] = A.udc_c[jj[k]];
-                        take[k] = sh_take[A.st.ci[jj[k]]];
-                    }
-#pragma unroll
-                    for (uint32_t k = 0; k < UN; ++k) {
-                        const float lowest_g = jj[k] == low[0].i1 ? low[0].m2 : low[0].m1, lowest_c = jj[k] == low[1].i1 ? low[1].m2 : low[1].m1;
-                        const bool gpu_idle = !(ug[k] > 0.f) || (take[k] < dg[k] && !(ug[k] > lowest_g));
-                        const bool cpu_idle = !(uc[k] > 0.f) || (free_c < dc[k] && !(uc[k] > lowest_c));
-                        const bool served = key[k] > last_key || (key[k] == last_key && jj[k] <= last_j);
-                        if ((gpu_idle && cpu_idle) || served) continue;
-                        if (key[k] > my_key || (key[k] == my_key && jj[k] < my_j)) { my_key = key[k]; my_j = jj[k]; }
-                    }
+                // the next job of the list that finds something to do
+                uint32_t last_j = ND_NONE;
+                while (pos < n_list) {
+                    const bool in = pos + lane < n_list;
+                    const uint32_t jj = list[in ? pos + lane : pos];
+                    const float ug = A.ug[jj], uc = A.uc[jj];
+                    const uint32_t dg = A.udg[jj], ci = A.st.ci[jj];
+                    const unsigned long long dc = A.udc_c[jj];
+                    const float lowest_g = jj == low[0].i1 ? low[0].m2 : low[0].m1;
+                    bool busy = ug > 0.f && (sh_take[ci] >= dg || ug > lowest_g);
+                    if (__ballot(uc > 0.f && free_c < dc) && !with_c) { lowest(1); with_c = true; }
+                    const float lowest_c = jj == low[1].i1 ? low[1].m2 : low[1].m1;
+                    busy = busy || (uc > 0.f && (free_c >= dc || uc > lowest_c));
+                    const unsigned long long m = __ballot(in && busy);
+                    if (!m) { pos += 64u; continue; }
+                    const uint32_t s = (uint32_t)__ffsll((long long)m) - 1u;
+                    pos += s + 1u;
+                    last_j = wave_lane_u32(jj, s);
+                    break;
                 }
-                const uint32_t hi = (uint32_t)(my_key >> 32), lo = (uint32_t)my_key;
-                const uint32_t top_hi = wave_max_u32_rows(hi), top_lo = wave_max_u32_rows(hi == top_hi ? lo : 0u);
-                last_key = ((unsigned long long)top_hi << 32) | top_lo;
-                last_j = wave_min_u32_rows(hi == top_hi && lo == top_lo ? my_j : ND_NONE);
                 if (last_j == ND_NONE) break;
                 // ScheduleJob
                 const uint32_t j = last_j, before = moves;
                 bool gpus_done = false;
                 for (;;) {
-                    uint32_t did = DID_NOTHING;
+                    uint32_t did = DID_NOTHING, after = 0;   // after: the job's values if the step is committed, on their way meanwhile
                     if (!gpus_done) {
+                        after = state_word(j, A.tgt_g[j], A.st.ci[j]);
                         did = gpu_step(j);
                         if (did == DID_NOTHING) {
                             gpus_done = true;
@@ -1467,10 +1488,13 @@ __device__ __forceinline__ void nodes_lds(const KernArgs &K) {
                         }
                     }
                     rs_wave_order();
-                    for (uint32_t i0 = 0; i0 <= touched; i0 += 4u) {           // a row of lanes per job whose state changed
+                    for (uint32_t i0 = 0; i0 < touched; i0 += 4u) {            // a row of lanes per job that gave something
                         const uint32_t i = i0 + (lane >> 4);
-                        refresh(i < touched ? A.touched[i] : j, i <= touched);
+                        refresh(A.touched[i < touched ? i : i0], i < touched);
                     }
+                    if (did == DID_CPUS) refresh(j, lane < 16u);
+                    else if (lane < 16u) words0[to + j * stride] = after;      // (who takes a step takes part)
+                    rs_wave_order();
                     copy_alone(keep, nodes);
                 }
                 fresh = moves != before;
@@ -1492,28 +1516,92 @@ __device__ __forceinline__ void nodes_lds(const KernArgs &K) {
         if (tid == 0) { sh_list = 0u; sh_used = 0u; sh_gone = 0u; }
         rk_assign a = {0u, 0u, 0.f, RK_NO_PLAN, 0.f};
         float total = 0.f;
-        uint32_t turn = 0;
+        uint32_t turn = 0, place = 0;
+        unsigned long long place_key = 0ull;                 // the job's key in the order (0: not in it) and its place
         __syncthreads();
         for (uint32_t done = 0;;) {
             // ---- a round: who may be served, and who is where when it begins
             for (uint32_t i = tid; i < gpus; i += THREADS) start_res[i] = A.res[i];
             for (uint32_t n = tid; n < N; n += THREADS) sh_mem[n] = 0.f;
             if (share) for (uint32_t i = tid; i < N * gpus; i += THREADS) share[i] = 0.f;
+            // The jobs that find something to do now, by both slopes descending, then the lower job; then those that only may
+            // (they hold something and have no step up), whose slopes are all zero.  From round to round few jobs' slopes
+            // change: the others move past those that left their place or came to one (144 jobs, 10 of them changed: 3,500
+            // cycles; counting what comes before each of them 12,000).
+            uint32_t n_list = 0, n_idle = 0;
             {
                 const float ug = mine ? A.ug[tid] : 0.f, uc = mine ? A.uc[tid] : 0.f;
-                const bool in = state == RK_JOB_NORMAL && (ug > 0.f || uc > 0.f || A.st.gi[tid] >= 0);
-                const unsigned long long m = __ballot(in);
-                uint32_t base = 0;
-                if (lane == 0 && m) base = atomicAdd(&sh_list, (uint32_t)__popcll(m));
-                base = one(base);
-                if (in) {
-                    const uint32_t p = base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
-                    list[p] = tid;
-                    A.okey[p] = ((unsigned long long)rs_ordered(ug) << 32) | rs_ordered(uc);
+                const bool in = state == RK_JOB_NORMAL && (ug > 0.f || uc > 0.f), idle = state == RK_JOB_NORMAL && !in && A.st.gi[tid] >= 0;
+                const unsigned long long key = in ? ((unsigned long long)rs_ordered(ug) << 32) | rs_ordered(uc) : 0ull;
+                const bool changed = key != place_key;
+                const unsigned long long m = __ballot(in), m_idle = __ballot(idle), m_changed = __ballot(changed), below = (1ull << lane) - 1ull;
+                if (lane == 0) {
+                    sh_scan[wave] = (uint32_t)__popcll(m) | (uint32_t)__popcll(m_idle) << 16;
+                    sh_changed[wave] = (uint32_t)__popcll(m_changed);
                 }
+                barrier();
+                uint32_t p = (uint32_t)__popcll(m & below), p_idle = (uint32_t)__popcll(m_idle & below), p_changed = (uint32_t)__popcll(m_changed & below);
+                uint32_t n_changed = 0;
+#pragma unroll
+                for (uint32_t w = 0; w < WAVES; ++w) {
+                    const uint32_t n = sh_scan[w], before = w < wave ? n : 0u, c = sh_changed[w];
+                    p += before & 0xFFFFu; p_idle += before >> 16; p_changed += w < wave ? c : 0u;
+                    n_list += n & 0xFFFFu; n_idle += n >> 16; n_changed += c;
+                }
+                n_list = one(n_list); n_idle = one(n_idle); n_changed = one(n_changed);
+                if (idle) list[n_list + p_idle] = tid;
+                if (n_changed <= ND_CHANGED) {
+                    if (changed) { sh_was[p_changed] = place_key; sh_now[p_changed] = key; sh_who[p_changed] = tid; sh_before[p_changed] = 0u; }
+                    barrier();
+                    const bool stays = in && !changed;
+                    for (uint32_t c = 0; c < n_changed; ++c) {
+                        const unsigned long long was = sh_was[c], now = sh_now[c];
+                        const bool lower = sh_who[c] < tid;
+                        const bool left = was > key || (was == key && lower), came = now > key || (now == key && lower);
+                        place += (came ? 1u : 0u) - (left ? 1u : 0u);
+                        const unsigned long long ahead = __ballot(stays && !came);
+                        if (lane == 0 && ahead) atomicAdd(&sh_before[c], (uint32_t)__popcll(ahead));
+                    }
+                    if (n_changed) barrier();
+                    if (in && changed) {
+                        place = sh_before[p_changed];
+                        for (uint32_t c = 0; c < n_changed; ++c) {
+                            const unsigned long long now = sh_now[c];
+                            place += now > key || (now == key && sh_who[c] < tid) ? 1u : 0u;
+                        }
+                    }
+                    if (in) list[place] = tid;
+                } else {
+                    if (in) { A.okey[p] = key; list[p] = tid; }
+                    barrier();
+                    uint32_t most = 128u;
+                    while (most < n_list) most <<= 1;
+                    // bitonic, every step the same way round (what is beyond the list comes last and never moves); steps that
+                    // stay within the 128 places of a wavefront need no barrier
+                    auto exchange = [&](uint32_t x, uint32_t y) {
+                        if (y >= n_list) return;
+                        const unsigned long long kx = A.okey[x], ky = A.okey[y];
+                        const uint32_t jx = list[x], jy = list[y];
+                        if (kx > ky || (kx == ky && jx < jy)) return;
+                        A.okey[x] = ky; A.okey[y] = kx;
+                        list[x] = jy; list[y] = jx;
+                    };
+                    for (uint32_t k = 2u; k <= most; k <<= 1)
+                        for (uint32_t d = k >> 1; d > 0; d >>= 1) {
+                            if (tid < most / 2u) {
+                                const uint32_t x = 2u * d * (tid / d) + tid % d;       // (powers of two)
+                                exchange(x, d == k >> 1 ? x - tid % d + k - 1u - tid % d : x + d);
+                            }
+                            if ((k > 128u && (d >= 128u || d == k >> 1)) || (d == 1u && k >= 128u)) barrier(); else rs_wave_order();
+                        }
+                    for (uint32_t i = tid; i < n_list; i += THREADS) fin_np[list[i]] = i;
+                    barrier();
+                    if (in) place = fin_np[tid];
+                }
+                place_key = key;
             }
             barrier();
-            if (wave == 0) round_alone(one(sh_list));
+            if (wave == 0) round_alone(n_list + n_idle);
             barrier();
             // ---- memory, then the record of every job that holds something, in job order
             const int32_t gi = mine ? A.st.gi[tid] : -1;
@@ -1760,11 +1848,11 @@ __device__ __forceinline__ void nodes_lds(const KernArgs &K) {
 }
 
 template <int THREADS, bool LJ>
-__global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) { nodes_lds<THREADS, LJ, false, false>(K); }
+__global__ __launch_bounds__(THREADS) void k_nodes_lds(NdKernArgs K) { nodes_lds<THREADS, LJ, false, false, 0u>(K); }
 
 struct NdSimArgs : NdKernArgs { SimArgs S; uint32_t rounds, shares; NdStates states; };     // rounds of a launch, at most; TAB: shares, states
-template <int THREADS, bool TAB>
-__global__ __launch_bounds__(THREADS) void k_sim_nodes(NdSimArgs K) { nodes_lds<THREADS, true, true, TAB>(K); }
+template <int THREADS, bool TAB, uint32_t GPN>
+__global__ __launch_bounds__(THREADS) void k_sim_nodes(NdSimArgs K) { nodes_lds<THREADS, true, true, TAB, GPN>(K); }
 
 __global__ __launch_bounds__(ND_THREADS) void k_reschedule_nodes(NdKernArgs K) {
     // what every job loses per GPU / CPU it gives, [2][n_jobs]: read at every look at a node's residents and at every
@@ -2309,9 +2397,11 @@ static int32_t nd_raise_lds(rk_ctx *ctx) {
     if (ctx->nodes_lds_raised) return RK_OK;
     const auto most = hipFuncAttributeMaxDynamicSharedMemorySize;
     const void *const fs[] = {reinterpret_cast<const void *>(k_nodes_lds<ND_SMALL_THREADS, true>), reinterpret_cast<const void *>(k_nodes_lds<ND_FEW_THREADS, true>),
-                              reinterpret_cast<const void *>(k_nodes_lds<ND_THREADS, false>), reinterpret_cast<const void *>(k_sim_nodes<ND_SMALL_THREADS, false>),
-                              reinterpret_cast<const void *>(k_sim_nodes<ND_FEW_THREADS, false>), reinterpret_cast<const void *>(k_sim_nodes<ND_THREADS, true>),
-                              reinterpret_cast<const void *>(k_sim_nodes<ND_SMALL_THREADS, true>), reinterpret_cast<const void *>(k_sim_nodes<ND_FEW_THREADS, true>)};
+                              reinterpret_cast<const void *>(k_nodes_lds<ND_THREADS, false>), reinterpret_cast<const void *>(k_sim_nodes<ND_SMALL_THREADS, false, 0u>),
+                              reinterpret_cast<const void *>(k_sim_nodes<ND_FEW_THREADS, false, 0u>), reinterpret_cast<const void *>(k_sim_nodes<ND_THREADS, true, 0u>),
+                              reinterpret_cast<const void *>(k_sim_nodes<ND_SMALL_THREADS, true, 0u>), reinterpret_cast<const void *>(k_sim_nodes<ND_FEW_THREADS, true, 0u>),
+                              reinterpret_cast<const void *>(k_sim_nodes<ND_THREADS, true, 8u>), reinterpret_cast<const void *>(k_sim_nodes<ND_SMALL_THREADS, true, 8u>),
+                              reinterpret_cast<const void *>(k_sim_nodes<ND_FEW_THREADS, true, 8u>)};
     for (const void *f : fs) RK_HIP(ctx, hipFuncSetAttribute(f, most, (int)ND_LDS_MOST));
     RK_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(k_reschedule_nodes), most, 2 * RK_MAX_JOBS_PER_ROUND * sizeof(float)));
     ctx->nodes_lds_raised = true;
@@ -2356,7 +2446,7 @@ int32_t rk_launch_reschedule_nodes(rk_ctx *ctx, const float *ref_thr, const rk_p
 // opened it): enough launches on the context's stream for all of them, a launch past the last tick returns at once.
 constexpr uint32_t SIM_NODES_ROUNDS = 64;        // rounds of a launch
 constexpr uint64_t ND_STATES_MOST = 1u << 19;    // states of all jobs that are found beforehand (80 bytes each)
-constexpr uint32_t ND_STATES_PER_TICK = 16384;
+constexpr uint32_t ND_STATES_PER_TICK = 65536;   // ... that a tick pays for
 
 bool rk_sim_nodes_fit(uint32_t n_jobs, const rk_nodes *nodes) {
     const size_t N = nodes->n_nodes, gpus = N * nodes->gpus_per_node;
@@ -2380,10 +2470,14 @@ int32_t rk_launch_sim_nodes(rk_ctx *ctx, const SimArgs &S, const float *ref_thr,
     const size_t N = K.b.n_nodes, gpus = N * K.b.gpn;
     size_t lds = nd_lds_words(J, N, K.b.nodes_words, true, true) * sizeof(uint32_t);
     const NdKernArgs prepare = K;
-    // With a job per thread, and where it pays to find all states of the jobs beforehand: STATES
+    // With a job per thread, all states of the jobs are found beforehand where they are not too many for memory and for the
+    // ticks: 0.4 us per 1,000 states, and a round is at least 25 us shorter (a simulation of one tick may have nothing to do: 42
+    // and 55 us; two ticks of 300 jobs on 64 GPUs 214 and 131, of 900 on 1,024 GPUs, 207,000 states, 5.86 and 4.40 ms).
     const uint64_t per_job = ((uint64_t)table->max_segs_per_job + 1u) * grid->n_cpu, states = J * per_job;
-    const size_t lds_tab = lds + nd_states_words(J, N, gpus) * sizeof(uint32_t);
-    const bool tab = J <= ND_THREADS && lds_tab <= ND_LDS_MOST && states <= ND_STATES_MOST && states <= (uint64_t)ND_STATES_PER_TICK * S.n_ticks;
+    const uint32_t threads = J <= ND_FEW_THREADS ? ND_FEW_THREADS : J <= ND_SMALL_THREADS ? ND_SMALL_THREADS : ND_THREADS;
+    const size_t lds_tab = nd_tab_words(threads, N, gpus, K.b.nodes_words) * sizeof(uint32_t);
+    const bool tab = J <= ND_THREADS && lds_tab <= ND_LDS_MOST && states <= ND_STATES_MOST && S.n_ticks > 1u && states <= (uint64_t)ND_STATES_PER_TICK * S.n_ticks;
+    const bool eight = K.b.gpn == 8u;
     if (tab) {
         lds = lds_tab;
         char *mem;
@@ -2400,11 +2494,11 @@ int32_t rk_launch_sim_nodes(rk_ctx *ctx, const SimArgs &S, const float *ref_thr,
     for (uint32_t t = 0; t < S.n_ticks; t = S.n_ticks - t > SIM_NODES_ROUNDS ? t + SIM_NODES_ROUNDS : S.n_ticks) {
         k_nd_prepare<<<(J + 3) / 4, 256, 0, ctx->stream>>>(prepare);
         RK_CHECK_LAUNCH(ctx, "k_nd_prepare");
-        if (tab && J > ND_SMALL_THREADS) k_sim_nodes<ND_THREADS, true><<<1, ND_THREADS, lds, ctx->stream>>>(K);
-        else if (tab && J > ND_FEW_THREADS) k_sim_nodes<ND_SMALL_THREADS, true><<<1, ND_SMALL_THREADS, lds, ctx->stream>>>(K);
-        else if (tab) k_sim_nodes<ND_FEW_THREADS, true><<<1, ND_FEW_THREADS, lds, ctx->stream>>>(K);
-        else if (J <= ND_FEW_THREADS) k_sim_nodes<ND_FEW_THREADS, false><<<1, ND_FEW_THREADS, lds, ctx->stream>>>(K);
-        else k_sim_nodes<ND_SMALL_THREADS, false><<<1, ND_SMALL_THREADS, lds, ctx->stream>>>(K);
+        if (tab && threads == ND_THREADS) { if (eight) k_sim_nodes<ND_THREADS, true, 8u><<<1, ND_THREADS, lds, ctx->stream>>>(K); else k_sim_nodes<ND_THREADS, true, 0u><<<1, ND_THREADS, lds, ctx->stream>>>(K); }
+        else if (tab && threads == ND_SMALL_THREADS) { if (eight) k_sim_nodes<ND_SMALL_THREADS, true, 8u><<<1, ND_SMALL_THREADS, lds, ctx->stream>>>(K); else k_sim_nodes<ND_SMALL_THREADS, true, 0u><<<1, ND_SMALL_THREADS, lds, ctx->stream>>>(K); }
+        else if (tab) { if (eight) k_sim_nodes<ND_FEW_THREADS, true, 8u><<<1, ND_FEW_THREADS, lds, ctx->stream>>>(K); else k_sim_nodes<ND_FEW_THREADS, true, 0u><<<1, ND_FEW_THREADS, lds, ctx->stream>>>(K); }
+        else if (J <= ND_FEW_THREADS) k_sim_nodes<ND_FEW_THREADS, false, 0u><<<1, ND_FEW_THREADS, lds, ctx->stream>>>(K);
+        else k_sim_nodes<ND_SMALL_THREADS, false, 0u><<<1, ND_SMALL_THREADS, lds, ctx->stream>>>(K);
         RK_CHECK_LAUNCH(ctx, "k_sim_nodes");
     }
     return RK_OK;
