@@ -143,12 +143,6 @@ __device__ __forceinline__ uint32_t round_index_of(const RoundArgs &R, uint32_t 
 }
 
 
-__device__ __forceinline__ double wave_sum_f64(double v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
-
 // A histogram in memory: its bins, then the sums of every GROUP_BINS neighbouring ones.
 constexpr uint32_t GROUP_BINS = 64, GROUPS = BINS / GROUP_BINS, HIST_WORDS = BINS + GROUPS;
 static_assert(GROUPS == 64 && GROUP_BINS == 64, "a wavefront looks at the groups, then at the bins of one");
@@ -1532,7 +1526,7 @@ __global__ __launch_bounds__(64) void k_mem_finish(Ctx X, JobState st, rk_assign
 // itself do not: at FEW_CPU_LANES_MODEL, whole rounds of 128 jobs at 32 levels 60 and 48, where nothing but offload fits the
 // GPUs 75 and 53, and 82 and 80 where only offload is allowed and every job that holds GPUs takes all CPUs.
 constexpr int FEW_THREADS = 1024, FEW_WAVES = FEW_THREADS / 64;
-constexpr uint32_t FEW_JOBS = FEW_THREADS;        // at most a job per thread
+constexpr uint32_t FEW_JOBS = FEW_THREADS;        // at most a job per thread (T: threads of the workgroup, 256, 512 or FEW_THREADS)
 constexpr uint32_t FEW_GPU_LANES = 2048;          // of a round: jobs times lanes of a job, in the pass over GPUs
 constexpr uint32_t FEW_CPU_LANES = 2048, FEW_CPU_LANES_MODEL = 4096;   // ... and over CPUs, on curves handed in and on the model's
 constexpr uint32_t FEW_BINS = 1024, FEW_FINE = 128;
@@ -1540,6 +1534,8 @@ constexpr uint32_t FEW_TICK_LANES = 4096;         // of a tick of a simulation (
 constexpr uint32_t FEW_TICK_LANES_16 = 5120;      // ... where no walk has more than 16 steps
 constexpr uint32_t FEW_TICK_WALK = 64;            // ... steps over CPU levels that a wavefront walks, one job or group of jobs after the other
 constexpr size_t FEW_SIM_LDS = 152 * 1024;
+constexpr uint64_t FEW_WALK_BYTES = 32ull << 20;  // walks that are found before the first tick, at most
+constexpr uint32_t FEW_WALKS_PER_TICK = 8192;     // ... that a tick pays for
 
 struct FewMem {                  // per round, in LDS
     unsigned long long *hc;      // histogram of a pass: CPUs and GPUs of the steps per bin
@@ -1639,8 +1635,8 @@ __device__ __forceinline__ Step few_search(const GridDev &grid, const uint32_t *
     return out;
 }
 
-// The jobs of the round with take(job) in job order; returns how many.  Two barriers per FEW_THREADS jobs.
-template <class F>
+// The jobs of the round with take(job) in job order; returns how many.  Two barriers.
+template <int T, class F>
 __device__ __forceinline__ uint32_t few_compact(const FewMem &M, uint32_t nj, F take) {
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     const bool in = tid < nj && take(tid);
@@ -1649,7 +1645,7 @@ __device__ __forceinline__ uint32_t few_compact(const FewMem &M, uint32_t nj, F 
     __syncthreads();
     uint32_t before = 0, all = 0;
 #pragma unroll
-    for (uint32_t w = 0; w < FEW_WAVES; ++w) { const uint32_t n = M.cnt[w]; before += w < wave ? n : 0u; all += n; }
+    for (uint32_t w = 0; w < T / 64; ++w) { const uint32_t n = M.cnt[w]; before += w < wave ? n : 0u; all += n; }
     if (in) M.part[before + (uint32_t)__popcll(b & ((1ull << lane) - 1ull))] = tid;
     __syncthreads();
     return all;
@@ -1658,8 +1654,9 @@ __device__ __forceinline__ uint32_t few_compact(const FewMem &M, uint32_t nj, F 
 // Where bin b is kept: lane l of few_cut takes the FEW_BINS / 64 bins from (FEW_BINS / 64) l on, one at a time.
 __device__ __forceinline__ uint32_t few_bin_at(uint32_t b) { return (b % (FEW_BINS / 64u)) * 64u + b / (FEW_BINS / 64u); }
 
+template <int T>
 __device__ __forceinline__ void few_clear(const FewMem &M) {
-    for (uint32_t i = threadIdx.x; i < FEW_BINS; i += FEW_THREADS) { M.hg[i] = 0u; M.hc[i] = 0ull; }
+    for (uint32_t i = threadIdx.x; i < FEW_BINS; i += T) { M.hg[i] = 0u; M.hc[i] = 0ull; }
     if (threadIdx.x == 0) { M.range[0] = 0u; M.range[1] = 0xFFFFFFFFu; M.range[2] = 0u; }
 }
 
@@ -1691,12 +1688,121 @@ __device__ __forceinline__ uint32_t few_cut(const FewMem &M, unsigned long long 
     return l0 * PER + i0;
 }
 
+// The walk of the job whose lanes these are (k_hull_groups): from an amount (start, its value cur and cost cost_cur; -1: from
+// nothing) always to the one with the highest slope, among the amounts whose lanes `can`.  v, cost: the lane's value and cost.
+// Lane k ends with step k: its key (the lowest slope so far), slope, target, the amount before it and both costs; n: steps.
+struct FewWalk { uint32_t n, key, raw, at, from, to; int32_t before, last; };
+template <bool COUNT>
+__device__ __forceinline__ FewWalk few_walk(uint32_t lanes, bool walking, bool can, float v, uint32_t cost, int32_t start, float cur,
+                                            uint32_t cost_cur, float ref, uint32_t &walked) {
+    const uint32_t lane = threadIdx.x & 63u, sub = lane & (lanes - 1u), base = lane - sub;
+    FewWalk W = {0u, 0u, 0u, 0u, 0u, 0u, -1, start};
+    float prev = __uint_as_float(0x7F800000u);
+    while (__ballot(walking)) {
+        if (COUNT) ++walked;
+        uint32_t best = 0;
+        if (walking && can && (int32_t)sub > W.last && v > cur) {
+            float sl = (v - cur) / ref;
+            sl = sl / (float)(cost - cost_cur);
+            best = __float_as_uint(sl);
+        }
+        const uint32_t top = few_max(best, lanes, lane);
+        walking = walking && top != 0u;
+        const uint32_t holder = few_bits(__ballot(best == top), base, lanes);
+        const int src = (int)(base + (holder ? holder - 1u : 0u));
+        const uint32_t top_cost = (uint32_t)__shfl((int)cost, src, 64);
+        const float top_val = __shfl(v, src, 64);
+        if (walking) {
+            prev = __uint_as_float(top) < prev ? __uint_as_float(top) : prev;
+            if (sub == W.n) {
+                W.key = __float_as_uint(prev); W.raw = top; W.at = (uint32_t)src - base;
+                W.before = W.last; W.from = cost_cur; W.to = top_cost;
+            }
+            cur = top_val;
+            W.last = src - (int)base;
+            cost_cur = top_cost;
+            ++W.n;
+        }
+    }
+    return W;
+}
+
+// What a simulation's jobs do in rounds from nothing does not depend on the other jobs, and there are few answers per job: they
+// are all found before the first tick (k_few_states).
+struct FewStates {
+    const uint4 *walk;           // per job, number of amounts that the capacity allows (`rows` of them) and lane: step (key, slope,
+                                 // target | GPUs << 16) of the lane's number on the walk over GPUs; the lane's value
+    const uint4 *cpu;            // per job and amount, after the walk over all CPU levels: throughput and plan of the best memory tier,
+                                 // tier (FEW_NO_TIER: none) | level << 8, CPUs the walk costs
+    const uint8_t *allowed;      // per GPUs (up to most_g) and job: how many of its amounts are not larger
+    uint32_t rows, most_g;
+};
+constexpr uint32_t FEW_NO_TIER = 0xFFu;
+constexpr uint32_t FEW_MANY_CPUS = 1u << 20;      // (a walk that costs that many counts as one that does not fit)
+
+// A workgroup per job; 406 jobs of up to 16 amounts: 6,900 walks.
+__global__ __launch_bounds__(256) void k_few_states(Ctx X, uint32_t lanes0, uint32_t lanes1, FewStates T, uint4 *walk, uint4 *cpu, uint8_t *allowed) {
+    const GridDev &grid = X.grid;
+    const uint32_t j = blockIdx.x, tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    const uint32_t s0 = X.tb.seg_off[j], ns = X.tb.seg_off[j + 1] - s0, first_seg = X.tb.seg_off[0];
+    const uint32_t n_mem = grid.n_mem, m_top = n_mem - 1u, n_cpu = grid.n_cpu;
+    const uint64_t jbase = (uint64_t)n_cpu * n_mem * (s0 - first_seg);
+    const float ref = X.ref_thr[j];
+    uint32_t walked = 0;
+    {
+        const uint32_t sub = lane & (lanes0 - 1u), per = 64u / lanes0, mine = lane / lanes0;
+        const uint32_t amt = sub < ns ? X.tb.seg_g[s0 + sub] : 0u;
+        const float v = sub < ns ? X.curve_thr[jbase + (uint64_t)m_top * ns + sub] : 0.f;
+        const uint32_t cost = amt;
+        for (uint32_t a0 = wave * per; a0 <= ns; a0 += 4u * per) {
+            const uint32_t a = a0 + mine;
+            const FewWalk W = few_walk<false>(lanes0, a <= ns, sub < a, v, cost, -1, 0.f, 0u, ref, walked);
+            if (a > ns) continue;
+            const bool on = sub < W.n;
+            walk[((size_t)j * T.rows + a) * lanes0 + sub] = make_uint4(on ? W.key : 0u, W.raw, W.at | (on ? W.to - W.from : 0u) << 16, __float_as_uint(v));
+        }
+    }
+    {
+        const uint32_t sub = lane & (lanes1 - 1u), per = 64u / lanes1, mine = lane / lanes1;
+        for (uint32_t i0 = wave * per; i0 < ns; i0 += 4u * per) {
+            const bool valid = i0 + mine < ns;
+            const uint32_t gi = valid ? i0 + mine : ns - 1u, g = X.tb.seg_g[s0 + gi];
+            const float v = sub < n_cpu ? X.best_thr[jbase + (uint64_t)(sub * n_mem + m_top) * ns + gi] : 0.f;
+            const uint32_t cost = (sub < n_cpu ? grid.cpu_levels[sub] : 0u) * (grid.cpu_mode ? g : 1u);
+            const uint32_t cost_at = (uint32_t)__shfl((int)cost, (int)(lane - sub), 64);
+            const float v_at = __shfl(v, (int)(lane - sub), 64);
+            const FewWalk W = few_walk<false>(lanes1, valid, sub < n_cpu, v, cost, 0, v_at, cost_at, ref, walked);
+            const uint32_t level = (uint32_t)W.last;
+            const unsigned long long end = cpu_cost(grid, level, g) - cpu_cost(grid, 0u, g);
+            if (!valid || sub != 0) continue;
+            uint4 out = {0u, RK_NO_PLAN, FEW_NO_TIER | level << 8, end < FEW_MANY_CPUS && cpu_cost(grid, n_cpu - 1u, g) <= 0xFFFFFFFFull ? (uint32_t)end : FEW_MANY_CPUS};
+            float best = 0.f;
+            for (uint32_t m = 0; m < n_mem; ++m) {
+                const uint64_t at = jbase + (uint64_t)(level * n_mem + m) * ns + gi;
+                const float x = X.best_thr[at];
+                if (x > best) { best = x; out.x = __float_as_uint(x); out.y = X.best_plan[at]; out.z = m | level << 8; }
+            }
+            cpu[(size_t)j * (T.rows - 1u) + gi] = out;
+        }
+    }
+    for (uint32_t g = tid; g <= T.most_g; g += 256u) {
+        uint32_t lo = 0, hi = ns;
+        while (lo < hi) {
+            const uint32_t mid = (lo + hi) >> 1;
+            if (X.tb.seg_g[s0 + mid] <= g) lo = mid + 1u; else hi = mid;
+        }
+        allowed[(size_t)g * gridDim.x + j] = (uint8_t)lo;
+    }
+}
+
 // A pass over the P jobs in M.part.  On entry the histogram is clear; on return (behind a barrier) M.gi, M.g and M.ci
 // hold what the pass leaves, freeG / freeC what is left.  COUNT: M.range[2] is how many steps the first wavefront walked (the
-// others have as many jobs, or a turn less).
-template <int PASS, bool COUNT = false>
+// others have as many jobs, or a turn less), as if there were FEW_THREADS.  KNOWN: the walks are in S, all from nothing.
+template <int T, int PASS, bool COUNT = false, bool KNOWN = false>
 __device__ __forceinline__ void few_pass(const Ctx &X, const FewMem &M, const FewLanes &L, uint32_t P, uint32_t lanes,
-                                         uint32_t first_seg, unsigned long long &freeG, unsigned long long &freeC) {
+                                         uint32_t first_seg, unsigned long long &freeG, unsigned long long &freeC,
+                                         const FewStates *S = nullptr) {
+    constexpr uint32_t WAVES = T / 64;
     const GridDev &grid = X.grid;
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
     const uint32_t sub = lane & (lanes - 1u), base = lane - sub, per = 64u / lanes, mine = base / lanes;
@@ -1704,12 +1810,34 @@ __device__ __forceinline__ void few_pass(const Ctx &X, const FewMem &M, const Fe
     const unsigned long long capG = freeG, capC = freeC;
     const float *__restrict__ vals = PASS == 0 ? X.curve_thr : X.best_thr;
     // a job per thread: the jobs in turn over the wavefronts, so that few jobs are spread over all of them
-    const uint32_t own = lane * FEW_WAVES + wave;
-    static_assert(FEW_JOBS <= FEW_THREADS, "a job per thread");
+    const uint32_t own = lane * WAVES + wave;
 
-    // the walks (k_hull_groups).  Costs by their low words: a step within the capacity fits a word.
+    // the walks.  Costs by their low words: a step within the capacity fits a word.
     uint32_t high = 0, low = 0xFFFFFFFFu, walked = 0;
-    for (uint32_t p0 = wave * per; p0 < P; p0 += FEW_WAVES * per) {
+    if constexpr (KNOWN) {                                     // (a job's own row of the table: M.dc holds how many amounts are allowed)
+        constexpr uint32_t UN = T <= 512 ? 4 : 2;              // turns whose loads are in flight (1,024 threads have the registers for two)
+        for (uint32_t p0 = wave * per; p0 < P; p0 += UN * WAVES * per) {
+            uint4 w[UN];
+            uint32_t amt[UN];
+#pragma unroll
+            for (uint32_t u = 0; u < UN; ++u) {
+                const uint32_t p = p0 + u * WAVES * per + mine, j = M.part[p < P ? p : P - 1u];
+                w[u] = S->walk[((size_t)j * S->rows + M.dc[j]) * lanes + sub];
+                amt[u] = sub < M.ns[j] ? X.tb.seg_g[M.s0[j] + sub] : 0u;
+            }
+#pragma unroll
+            for (uint32_t u = 0; u < UN; ++u) {
+                const uint32_t p = p0 + u * WAVES * per + mine, e = p * lanes + sub;
+                if (p >= P) continue;
+                const uint32_t dg = w[u].z >> 16;
+                if (w[u].x) { high = w[u].x > high ? w[u].x : high; low = w[u].x < low ? w[u].x : low; }
+                L.val[e] = __uint_as_float(w[u].w);
+                L.amt[e] = amt[u];
+                L.step[e] = make_uint4(w[u].x, w[u].y, w[u].z, w[u].x ? M.lvl[0] * (grid.cpu_mode ? dg : sub == 0 ? 1u : 0u) : 0u);
+            }
+        }
+    } else
+    for (uint32_t p0 = wave * per; p0 < P; p0 += WAVES * per) {
         const bool valid = p0 + mine < P;
         const uint32_t p = valid ? p0 + mine : P - 1u, j = M.part[p];
         const float ref = M.ref[j];
@@ -1727,7 +1855,7 @@ __device__ __forceinline__ void few_pass(const Ctx &X, const FewMem &M, const Fe
         const int32_t start = PASS == 0 ? M.gi[j] : (int32_t)ci;
         const int from = (int)(base + (start < 0 ? 0u : (uint32_t)start));
         const float v_at = __shfl(v, from, 64);
-        float cur = start < 0 ? 0.f : v_at;
+        const float cur = start < 0 ? 0.f : v_at;
         // the amount's cost in the pass's resource and in CPUs, and those of what the job holds (paid for already)
         const uint32_t level = M.lvl[PASS == 0 ? ci : sub];
         const uint32_t times = PASS == 0 ? (grid.cpu_mode ? amt : 1u) : (grid.cpu_mode ? g_held : 1u);
@@ -1736,61 +1864,31 @@ __device__ __forceinline__ void few_pass(const Ctx &X, const FewMem &M, const Fe
         const uint32_t cost_at = (uint32_t)__shfl((int)cost, from, 64);
         const unsigned long long cpus_at = ((unsigned long long)(uint32_t)__shfl((int)(uint32_t)(cpus >> 32), from, 64) << 32) |
                                            (uint32_t)__shfl((int)(uint32_t)cpus, from, 64);
-        uint32_t cost_cur = start < 0 ? 0u : cost_at;
+        const uint32_t cost_cur = start < 0 ? 0u : cost_at;
         const bool can = sub < npts && (PASS == 1 || amt <= capG + cost_cur) && cpus <= capC + (start < 0 ? 0ull : cpus_at);
-        int32_t cur_i = start;
-        uint32_t k = 0, my_key = 0, my_raw = 0, my_at = 0, my_from = 0, my_to = 0;
-        int32_t my_before = -1;
-        float prev = __uint_as_float(0x7F800000u);
-        bool walking = valid;
-        while (__ballot(walking)) {
-            if (COUNT) ++walked;
-            uint32_t best = 0;
-            if (walking && can && (int32_t)sub > cur_i && v > cur) {
-                float sl = (v - cur) / ref;
-                sl = sl / (float)(cost - cost_cur);
-                best = __float_as_uint(sl);
-            }
-            const uint32_t top = few_max(best, lanes, lane);
-            walking = walking && top != 0u;
-            const uint32_t holder = few_bits(__ballot(best == top), base, lanes);
-            const int src = (int)(base + (holder ? holder - 1u : 0u));
-            const uint32_t top_cost = (uint32_t)__shfl((int)cost, src, 64);
-            const float top_val = __shfl(v, src, 64);
-            if (walking) {
-                prev = __uint_as_float(top) < prev ? __uint_as_float(top) : prev;
-                if (sub == k) {
-                    my_key = __float_as_uint(prev); my_raw = top; my_at = (uint32_t)src - base;
-                    my_before = cur_i; my_from = cost_cur; my_to = top_cost;
-                }
-                cur = top_val;
-                cur_i = src - (int)base;
-                cost_cur = top_cost;
-                ++k;
-            }
-        }
+        const FewWalk W = few_walk<COUNT>(lanes, valid, can, v, cost, start, cur, cost_cur, ref, walked);
         if (valid) {
             uint32_t dg = 0, dc = 0;
-            if (sub < k) {
+            if (sub < W.n) {
                 if (PASS == 0) {
-                    dg = my_to - my_from;
-                    dc = M.lvl[ci] * (grid.cpu_mode ? dg : my_before < 0 ? 1u : 0u);
+                    dg = W.to - W.from;
+                    dc = M.lvl[ci] * (grid.cpu_mode ? dg : W.before < 0 ? 1u : 0u);
                 } else {
-                    dc = my_to - my_from;
+                    dc = W.to - W.from;
                 }
-                high = my_key > high ? my_key : high;
-                low = my_key < low ? my_key : low;
+                high = W.key > high ? W.key : high;
+                low = W.key < low ? W.key : low;
             }
             const uint32_t e = p * lanes + sub;
             L.val[e] = v;
             if (PASS == 0) L.amt[e] = amt;
-            L.step[e] = make_uint4(sub < k ? my_key : 0u, my_raw, my_at | dg << 16, dc);
+            L.step[e] = make_uint4(sub < W.n ? W.key : 0u, W.raw, W.at | dg << 16, dc);
         }
     }
     high = wave_max_u32_rows(high);
     low = wave_min_u32_rows(low);
     if (lane == 0 && high) { atomicMax(&M.range[0], high); atomicMin(&M.range[1], low); }
-    if (COUNT && tid == 0) M.range[2] = walked;
+    if (COUNT && tid == 0) M.range[2] = walked * T / FEW_THREADS;
     __syncthreads();
     // The threshold: steps whose key lies less than `limit` below the highest one.  Any threshold whose whole set of steps
     // fits selects a prefix of the order: FEW_BINS bins over the keys that occur, and what is left of the bin where the
@@ -1809,7 +1907,7 @@ __device__ __forceinline__ void few_pass(const Ctx &X, const FewMem &M, const Fe
     };
     unsigned long long limit;
     for (uint32_t level = 0;; ++level) {
-        for (uint32_t e = tid; e < P * lanes; e += FEW_THREADS) {
+        for (uint32_t e = tid; e < P * lanes; e += T) {
             const uint4 s = L.step[e];
             if (s.x) count(s);
         }
@@ -1827,11 +1925,12 @@ __device__ __forceinline__ void few_pass(const Ctx &X, const FewMem &M, const Fe
         if (level == 1u || cut == FEW_BINS || shift == 0u || P <= FEW_FINE) break;
         from = (uint32_t)limit;                                // the bin that did not fit, divided
         shift = shift > 10u ? shift - 10u : 0u;
-        for (uint32_t i = tid; i < FEW_BINS; i += FEW_THREADS) { M.hg[i] = 0u; M.hc[i] = 0ull; }
+        for (uint32_t i = tid; i < FEW_BINS; i += T) { M.hg[i] = 0u; M.hc[i] = 0ull; }
         __syncthreads();
     }
     // the prefix goes to every job at once; its next step: the walk's if it still fits, else a search (apply_job)
-    for (uint32_t p0 = wave * per; p0 < P; p0 += FEW_WAVES * per) {
+    const bool some = PASS == 0 ? freeG != 0 : freeC != 0;     // (every step costs something of the pass's resource)
+    for (uint32_t p0 = wave * per; p0 < P; p0 += WAVES * per) {
         const bool valid = p0 + mine < P;
         const uint32_t p = valid ? p0 + mine : P - 1u, j = M.part[p], e0 = p * lanes;
         const uint4 s = L.step[e0 + sub];
@@ -1843,7 +1942,7 @@ __device__ __forceinline__ void few_pass(const Ctx &X, const FewMem &M, const Fe
         Step nx = {0.f, 0u, 0u};
         uint32_t dc = next.w;
         bool search = false;
-        if (next.x) {
+        if (next.x && some) {
             nx = Step{__uint_as_float(next.y), next.z & 0xFFFFu, next.z >> 16};
             search = nx.dg > freeG || dc > freeC;
         }
@@ -1864,6 +1963,7 @@ __device__ __forceinline__ void few_pass(const Ctx &X, const FewMem &M, const Fe
         }
     }
     __syncthreads();
+    if (!some) return;
     // Step by step on what is left, by the first wavefront: the highest slope, the lower job among equals.  A step that
     // no longer fits stays as an upper bound of what its job can still do; where a bound comes out highest, all
     // wavefronts make the bounds that could win exact (tail_run's rule).
@@ -1941,7 +2041,7 @@ __device__ __forceinline__ void few_pass(const Ctx &X, const FewMem &M, const Fe
                 if (g == mine) l = first;
             }
             const bool need = l < 64u;
-            const uint32_t p = (need ? l : 0u) * FEW_WAVES + wave, j = M.part[need ? p : 0u];
+            const uint32_t p = (need ? l : 0u) * WAVES + wave, j = M.part[need ? p : 0u];
             uint32_t dc;
             const int32_t at = PASS == 0 ? M.gi[j] : (int32_t)M.ci[j];
             const uint32_t ci = M.ci[j], g_held = PASS == 0 ? 0u : M.g[j];
@@ -1971,33 +2071,30 @@ __device__ __forceinline__ void few_jobs(const Ctx &X, const FewMem &M, uint32_t
     }
 }
 
-// The memory step that ends a round: every thread writes its job's wish (a record per job of the round in `assign`), the
-// first wavefront closes the round.  The thread's wish is returned; M.box[0], behind the next barrier: the records in `assign`
-// are others.  sums: 2 * FEW_WAVES doubles in LDS.
-__device__ __forceinline__ rk_assign few_memory(const Ctx &X, const FewMem &M, uint32_t rnd, uint32_t nj, uint32_t first_seg,
-                                                double *sums, rk_assign *assign, float *totals) {
+// The memory step that ends a round, from every thread's wish (mem_wish, its cost and normalised throughput): the first
+// wavefront closes the round.  M.box[0], behind the next barrier: the records in `assign` replace the wishes.
+// sums: 2 * FEW_WAVES doubles in LDS.
+template <int T>
+__device__ __forceinline__ void few_memory(const Ctx &X, const FewMem &M, uint32_t rnd, double cost_d, double val_d, double *sums,
+                                           rk_assign *assign, float *totals) {
     const uint32_t tid = threadIdx.x;
-    double cost_d = 0.0, val_d = 0.0;
-    rk_assign out = {0u, 0u, 0.f, RK_NO_PLAN, 0.f};
-    if (tid < nj) {
-        out = mem_wish(X, M.gi[tid], M.g[tid], M.ci[tid], M.lvl[M.ci[tid]], M.s0[tid], M.ns[tid], first_seg, M.ref[tid], cost_d, val_d);
-        assign[tid] = out;
-    }
-    cost_d = wave_sum_f64(cost_d);
-    val_d = wave_sum_f64(val_d);
+    if (__ballot(val_d != 0.0 || cost_d != 0.0)) { cost_d = wave_sum_f64(cost_d); val_d = wave_sum_f64(val_d); }
     if ((tid & 63u) == 0) { sums[tid >> 6] = cost_d; sums[FEW_WAVES + (tid >> 6)] = val_d; }
     __syncthreads();
     if (tid < 64u) {
-        const bool has = tid < FEW_WAVES;
+        const bool has = tid < T / 64;
         const double wish = wave_sum_f64(has ? sums[tid] : 0.0), val = wave_sum_f64(has ? sums[FEW_WAVES + tid] : 0.0);
         const bool anew = mem_close_round(X, M.gi, M.g, M.ci, rnd, wish, val, assign, totals);
         if (tid == 0) M.box[0] = anew ? 1ull : 0ull;
     }
-    return out;
+}
+__device__ __forceinline__ rk_assign few_wish(const Ctx &X, const FewMem &M, uint32_t j, uint32_t first_seg, double &cost_d, double &val_d) {
+    return mem_wish(X, M.gi[j], M.g[j], M.ci[j], M.lvl[M.ci[j]], M.s0[j], M.ns[j], first_seg, M.ref[j], cost_d, val_d);
 }
 
 // One workgroup per round; near: per-lane words in LDS.
-__global__ __launch_bounds__(FEW_THREADS) void k_round_few(Ctx X, JobState st, uint32_t max_jobs, uint32_t lanes0, uint32_t lanes1,
+template <int T>
+__global__ __launch_bounds__(T) void k_round_few(Ctx X, JobState st, uint32_t max_jobs, uint32_t lanes0, uint32_t lanes1,
                                                            uint32_t near, rk_assign *__restrict__ assign,
                                                            float *__restrict__ totals, TableGuard guard) {
     extern __shared__ __align__(16) unsigned long long lds_few[];
@@ -2021,20 +2118,24 @@ __global__ __launch_bounds__(FEW_THREADS) void k_round_few(Ctx X, JobState st, u
     }
     unsigned long long freeG, freeC;
     pass_caps<0>(X.R, cl, st, rnd, freeG, freeC);
-    few_clear(M);
-    uint32_t P = few_compact(M, nj, [&](uint32_t) { return fl.state == RK_JOB_NORMAL && freeG != 0; });
-    if (P) few_pass<0>(X, M, L, P, lanes0, first_seg, freeG, freeC);
-    few_clear(M);
-    P = few_compact(M, nj, [&](uint32_t j) { return fl.state == RK_JOB_NORMAL && M.gi[j] >= 0 && freeC != 0; });
-    if (P) few_pass<1>(X, M, L, P, lanes1, first_seg, freeG, freeC);
-    few_memory(X, M, rnd, nj, first_seg, sums, assign + jrel0, totals);
+    few_clear<T>(M);
+    uint32_t P = few_compact<T>(M, nj, [&](uint32_t) { return fl.state == RK_JOB_NORMAL && freeG != 0; });
+    if (P) few_pass<T, 0>(X, M, L, P, lanes0, first_seg, freeG, freeC);
+    few_clear<T>(M);
+    P = few_compact<T>(M, nj, [&](uint32_t j) { return fl.state == RK_JOB_NORMAL && M.gi[j] >= 0 && freeC != 0; });
+    if (P) few_pass<T, 1>(X, M, L, P, lanes1, first_seg, freeG, freeC);
+    double cost_d = 0.0, val_d = 0.0;
+    if (tid < nj) assign[jrel0 + tid] = few_wish(X, M, tid, first_seg, cost_d, val_d);
+    few_memory<T>(X, M, rnd, cost_d, val_d, sums, assign + jrel0, totals);
 }
 
 // Ticks of a simulation of at most FEW_JOBS jobs under the greedy, in one workgroup: what a job does between
 // the ticks stays in its thread's registers, a round is k_round_few's.  A tick that starts from what the last round started
 // from has that round's result.  As launches of their own (the round's four kernels and k_sim_step, replayed as a graph)
 // a tick with a round took 40 us, most of it launches and what one kernel leaves for the next in memory: 406 jobs on 64
-// GPUs, 720 ticks 19.2 ms then, 9.1 now; 30 jobs 8.2 us per tick and 2.7.
+// GPUs, 720 ticks 19.2 ms then, 9.1 in one kernel; 30 jobs 8.2 us per tick and 2.7.
+// With the walks known beforehand (KNOWN: 11,000 of a round's 44,000 cycles, and 8,000 for the pass over CPUs, which then seldom
+// has to be made), 512 threads where they are enough (their registers hold a job's state) and sums by lane swaps: 5.9 ms.
 // The walks of a round for many jobs keep one workgroup busy for longer than that: such a tick, and every one after it, is
 // left to the launches until the rounds are for fewer jobs again.  So are the ticks after one that walked long over the CPU
 // levels, for a while (as many lanes cost 4 us where curves are flat there, as the model's mostly are, and 100 where every
@@ -2051,22 +2152,28 @@ __global__ __launch_bounds__(FEW_THREADS) void k_round_few(Ctx X, JobState st, u
 //     16,000 lanes  1,000 jobs of 16 58 and 132, 67 and 115, 63 and 48  62 and 145, 135 and 311, 145 and 286
 // (where nobody is ever frozen 160 jobs of 32 take 37 us here and 29 as launches, 128 of them 30 and 28).  With both lines
 // every one of these takes what the faster way takes, give or take 2 %, or up to 10 % of 100 ticks where they begin with
-// long walks.  406 jobs on 64 GPUs over 720 ticks: 19.2 ms as launches, 9.1.
+// long walks.  (All of these were measured without KNOWN; the lines still lie where the lanes' words fit the LDS.)
 // first: the simulation begins with this launch; otherwise the state is where the launch before left it.
 // OFTEN: rounds for more than `most` jobs and long walks may occur; FAR: a CPU pass may have more lanes than LDS (`near`), its
 // words are in memory then (n_far of them).
-template <bool OFTEN, bool FAR>
-__global__ __launch_bounds__(FEW_THREADS) void k_sim_few(Ctx X, SimArgs A, uint32_t first, uint32_t go_on, uint32_t most, uint32_t lanes0,
+// KNOWN: the walks over GPUs, and what a job would take of the CPUs if there were enough, are in F: where all of it fits, the pass
+// over CPUs is what every job does on its own.
+template <int T, bool OFTEN, bool FAR, bool KNOWN>
+__global__ __launch_bounds__(T) void k_sim_few(Ctx X, SimArgs A, FewStates F, uint32_t first, uint32_t go_on, uint32_t most, uint32_t lanes0,
                                                          uint32_t lanes1, uint32_t near, uint32_t *far, uint32_t n_far,
-                                                         rk_assign *__restrict__ assign, float *__restrict__ tick_total) {
+                                                         rk_assign *__restrict__ assign) {
     extern __shared__ __align__(16) unsigned long long lds_few[];
     __shared__ double sums[2 * FEW_WAVES];
-    __shared__ unsigned long long frozen_c[2];
-    __shared__ uint32_t frozen_g[2], frozen_n[2], used_g[2];   // of a tick, in two copies used in turn
+    __shared__ unsigned long long frozen[2];                   // of a tick, in two copies used in turn: CPUs | GPUs << 32
+    __shared__ uint32_t frozen_n[2], used_g, wanted_c[2];
+    __shared__ float round_total;
+    __shared__ uint32_t out_used[SIM_FEW_TICKS], out_frozen[SIM_FEW_TICKS];
+    __shared__ float out_total[SIM_FEW_TICKS];                 // the ticks' figures, written to memory when the launch ends
     const uint32_t tid = threadIdx.x, J = A.n_jobs, first_seg = X.tb.seg_off[0];
     uint32_t tick = first ? 0u : (uint32_t)__builtin_amdgcn_readfirstlane((int)A.tick[0]);
     if (tick >= A.n_ticks) return;                             // (the simulation is over)
     if (OFTEN && go_on && A.tick[1]) return;                   // (the launch before was stopped)
+    const uint32_t begin = tick;
     uint32_t end = A.n_ticks - tick > SIM_FEW_TICKS ? tick + SIM_FEW_TICKS : A.n_ticks;
     uint32_t *lds_lanes;
     const FewMem M = few_mem(lds_few, J, &lds_lanes);
@@ -2085,10 +2192,14 @@ __global__ __launch_bounds__(FEW_THREADS) void k_sim_few(Ctx X, SimArgs A, uint3
             seg = A.S.seg[tid]; lvl = A.S.lvl[tid];
         }
     }
-    if (tid < 2u) { frozen_c[tid] = 0ull; frozen_g[tid] = 0u; frozen_n[tid] = 0u; used_g[tid] = 0u; }
+    if (tid < 2u) { frozen[tid] = 0ull; frozen_n[tid] = 0u; wanted_c[tid] = 0u; }
     Floor fl = {-1, 0u, RK_JOB_OUT};
+    // the job's record; the amounts it is the wish for (-1: none, or another one by decisions in job order); (KNOWN) for which
+    // amount the walk over the CPUs is known: CPUs it costs | level it ends on << 24; the number of amounts allowed, for which limit
     rk_assign a = {0u, 0u, 0.f, RK_NO_PLAN, 0.f};
-    float total = 0.f;
+    int32_t wish_gi = -1, end_gi = -1;
+    uint32_t wish_ci = 0, end_of = 0, limit = 0xFFFFFFFFu, allowed = 0, turn = 0;
+    const uint32_t lane = tid & 63u;
     __syncthreads();
     if (OFTEN && tid == 0) A.tick[1] = 0u;                     // (all have read it)
     for (bool known = false; tick < end; ++tick, known = true) {
@@ -2100,58 +2211,116 @@ __global__ __launch_bounds__(FEW_THREADS) void k_sim_few(Ctx X, SimArgs A, uint3
             now.state = RK_JOB_NORMAL;
             if (sim_frozen(s.g, s.held, s.n_reconf, delta, A.gate)) now = Floor{seg, lvl, RK_JOB_FROZEN};
         }
-        const bool frozen = now.state == RK_JOB_FROZEN;
-        if (frozen) {
-            atomicAdd(&frozen_g[half], s.g);
-            atomicAdd(&frozen_c[half], (unsigned long long)M.lvl[lvl] * (X.grid.cpu_mode ? s.g : 1u));
-            atomicAdd(&frozen_n[half], 1u);
-        }
+        const bool is_frozen = now.state == RK_JOB_FROZEN;
+        if (is_frozen)                                         // (what jobs hold is within the cluster, whose CPUs and GPUs are words)
+            atomicAdd(&frozen[half], ((unsigned long long)s.g << 32) | (unsigned long long)M.lvl[lvl] * (X.grid.cpu_mode ? s.g : 1u));
+        const unsigned long long frozen_m = __ballot(is_frozen);
+        if (lane == 0 && frozen_m) atomicAdd(&frozen_n[half], (uint32_t)__popcll(frozen_m));
         const bool other = now.state != fl.state || now.gi != fl.gi || now.ci != fl.ci;
         fl = now;
         if (__syncthreads_or(other || !known)) {
-            const unsigned long long hg = frozen_g[half], hc = frozen_c[half];
+            const unsigned long long held = frozen[half], hg = held >> 32, hc = held & 0xFFFFFFFFull;
             unsigned long long freeG = hg < A.cl.G ? A.cl.G - hg : 0ull, freeC = hc < A.cl.C ? A.cl.C - hc : 0ull;
             if (mine) {
                 M.gi[tid] = fl.gi;
-                M.g[tid] = frozen ? s.g : 0u;
+                M.g[tid] = is_frozen ? s.g : 0u;
                 M.ci[tid] = fl.ci;
+                if constexpr (KNOWN) {                         // the amounts that fit: GPUs, and CPUs at the lowest level
+                    const uint32_t free_g = (uint32_t)freeG, free_c = (uint32_t)freeC, level = M.lvl[0];
+                    const uint32_t by_cpu = X.grid.cpu_mode ? free_c / level : level <= free_c ? 0xFFFFFFFFu : 0u;
+                    const uint32_t fits = by_cpu < free_g ? by_cpu : free_g;
+                    if (fits != limit) { limit = fits; allowed = F.allowed[(size_t)fits * J + tid]; }
+                    M.dc[tid] = allowed;
+                }
             }
-            few_clear(M);
-            uint32_t P = few_compact(M, J, [&](uint32_t) { return fl.state == RK_JOB_NORMAL && freeG != 0; });
+            if (tid == 0) used_g = 0u;
+            few_clear<T>(M);
+            uint32_t P = few_compact<T>(M, J, [&](uint32_t) { return fl.state == RK_JOB_NORMAL && freeG != 0; });
             if (OFTEN && (uint32_t)__builtin_amdgcn_readfirstlane((int)P) > most) {                           // (nothing of this tick is in the state yet)
                 if (tid == 0) A.tick[1] = 1u;
                 break;
             }
-            if (P) few_pass<0>(X, M, L, P, lanes0, first_seg, freeG, freeC);
-            few_clear(M);
-            P = few_compact(M, J, [&](uint32_t j) { return fl.state == RK_JOB_NORMAL && M.gi[j] >= 0 && freeC != 0; });
-            if (FAR && P * lanes1 > near) few_pass<1, OFTEN>(X, M, few_lane_mem(far, n_far), P, lanes1, first_seg, freeG, freeC);
-            else if (P) few_pass<1, OFTEN>(X, M, L, P, lanes1, first_seg, freeG, freeC);
-            a = few_memory(X, M, 0u, J, first_seg, sums, assign, tick_total);
+            if (P) few_pass<T, 0, false, KNOWN>(X, M, L, P, lanes0, first_seg, freeG, freeC, &F);
+            bool all_fit = false;                              // every job has all the CPUs it would take
+            const bool takes = fl.state == RK_JOB_NORMAL && mine && M.gi[tid] >= 0;
+            if constexpr (KNOWN) {
+                const int32_t gi = takes ? M.gi[tid] : -1;
+                if (takes && gi != end_gi) {                   // ... and what the job would like there
+                    const uint4 rec = F.cpu[(size_t)tid * (F.rows - 1u) + (uint32_t)gi];
+                    const uint32_t tier = rec.z & 0xFFu, level = rec.z >> 8, g = M.g[tid];
+                    end_gi = gi; end_of = rec.w | level << 24;
+                    a = rk_assign{0u, 0u, 0.f, RK_NO_PLAN, 0.f};
+                    if (tier != FEW_NO_TIER) {
+                        float cost = X.grid.mem_levels_gb[tier];
+                        if (X.grid.mem_mode) cost = cost * (float)g;
+                        a = rk_assign{g, X.grid.cpu_mode ? M.lvl[level] * g : M.lvl[level], cost, rec.y, __uint_as_float(rec.x)};
+                    }
+                    wish_gi = gi; wish_ci = level;
+                }
+                uint32_t c = takes ? end_of & 0xFFFFFFu : 0u;
+                if (__ballot(c != 0u)) {
+                    c = wave_sum_u32(c);
+                    if (lane == 0) atomicAdd(&wanted_c[turn], c);
+                }
+                if (tid == 0) { wanted_c[turn ^ 1u] = 0u; M.range[2] = 0u; }
+                __syncthreads();
+                const uint32_t wanted = wanted_c[turn];
+                turn ^= 1u;
+                all_fit = wanted < FEW_MANY_CPUS && wanted <= freeC;
+                if (all_fit && takes) M.ci[tid] = end_of >> 24;
+            }
+            if (!all_fit) {
+                few_clear<T>(M);
+                P = few_compact<T>(M, J, [&](uint32_t j) { return fl.state == RK_JOB_NORMAL && M.gi[j] >= 0 && freeC != 0; });
+                if (FAR && P * lanes1 > near) few_pass<T, 1, OFTEN>(X, M, few_lane_mem(far, n_far), P, lanes1, first_seg, freeG, freeC);
+                else if (P) few_pass<T, 1, OFTEN>(X, M, L, P, lanes1, first_seg, freeG, freeC);
+            }
+            // memory: what the job would like, found again only where it holds something else than the last time
+            double cost_d = 0.0, val_d = 0.0;
+            if (mine) {
+                const int32_t gi = M.gi[tid];
+                const uint32_t ci = M.ci[tid];
+                if (gi < 0) {
+                    a = rk_assign{0u, 0u, 0.f, RK_NO_PLAN, 0.f};
+                } else if (gi != wish_gi || ci != wish_ci) {
+                    double unused_c = 0.0, unused_v = 0.0;
+                    a = few_wish(X, M, tid, first_seg, unused_c, unused_v);
+                }
+                wish_gi = gi; wish_ci = ci;
+                if (a.g) { cost_d = (double)a.mem_gb; val_d = (double)a.thr / (double)M.ref[tid]; }
+            }
+            few_memory<T>(X, M, 0u, cost_d, val_d, sums, assign, &round_total);
             __syncthreads();                                   // the round is closed
             if (OFTEN && (uint32_t)__builtin_amdgcn_readfirstlane((int)M.range[2]) > FEW_TICK_WALK) {         // (the next one is as long, as a rule)
                 if (tid == 0) A.tick[1] = 1u;
                 end = tick + 1u;
             }
-            if (M.box[0] && mine) a = assign[tid];             // ... by decisions in job order
-            if (tid == 0) total = *tick_total;                 // (its own store)
-        }
-        // closes it
-        if (fl.state != RK_JOB_OUT) {
-            if (a.g) atomicAdd(&used_g[half], a.g);
-            if (sim_close(s, a, t, A.dt, delta, work)) {
-                seg = s.g ? M.gi[tid] : -1;
-                lvl = s.g ? M.ci[tid] : 0u;
+            if (M.box[0] && mine) { a = assign[tid]; wish_gi = -1; end_gi = -1; }             // ... by decisions in job order
+            uint32_t used = fl.state != RK_JOB_OUT ? a.g : 0u;
+            if (__ballot(used != 0u)) {
+                used = wave_sum_u32(used);
+                if (lane == 0) atomicAdd(&used_g, used);
             }
         }
-        if (tid < 1u) { frozen_c[half ^ 1u] = 0ull; frozen_g[half ^ 1u] = 0u; }
+        // closes it
+        if (fl.state != RK_JOB_OUT && sim_close(s, a, t, A.dt, delta, work)) {
+            seg = s.g ? M.gi[tid] : -1;
+            lvl = s.g ? M.ci[tid] : 0u;
+        }
+        if (tid == 0) frozen[half ^ 1u] = 0ull;
         __syncthreads();
         if (tid == 0) {
-            if (A.out.gpus_in_use) A.out.gpus_in_use[tick] = used_g[half];
-            if (A.out.totals) A.out.totals[tick] = total;
-            if (A.out.frozen) A.out.frozen[tick] = frozen_n[half];
-            used_g[half] = 0u; frozen_n[half] = 0u;
+            out_used[tick - begin] = used_g;
+            out_total[tick - begin] = round_total;
+            out_frozen[tick - begin] = frozen_n[half];
+            frozen_n[half] = 0u;
         }
+    }
+    __syncthreads();
+    for (uint32_t i = tid; i < tick - begin; i += T) {
+        if (A.out.gpus_in_use) A.out.gpus_in_use[begin + i] = out_used[i];
+        if (A.out.totals) A.out.totals[begin + i] = out_total[i];
+        if (A.out.frozen) A.out.frozen[begin + i] = out_frozen[i];
     }
     if (mine) {
         A.S.g[tid] = s.g; A.S.c[tid] = s.c; A.S.plan[tid] = s.plan; A.S.seg[tid] = seg; A.S.lvl[tid] = lvl;
@@ -3061,9 +3230,14 @@ int32_t rk_allocate_setup(rk_ctx *ctx) {
                            reinterpret_cast<const void *>(k_select_small<1, SMALL_ROUND_JOBS / TAIL_THREADS, TAIL_THREADS>),
                            reinterpret_cast<const void *>(k_select_small<0, 1, TAIL_THREADS>), reinterpret_cast<const void *>(k_select_small<1, 1, TAIL_THREADS>),
                            reinterpret_cast<const void *>(k_select_small<0, 1, TAIL_THREADS / 2>), reinterpret_cast<const void *>(k_select_small<1, 1, TAIL_THREADS / 2>)};
-    RK_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(k_round_few), hipFuncAttributeMaxDynamicSharedMemorySize, 144 * 1024));
-    const void *sim[] = {reinterpret_cast<const void *>(k_sim_few<false, false>), reinterpret_cast<const void *>(k_sim_few<true, false>),
-                         reinterpret_cast<const void *>(k_sim_few<true, true>)};
+    const void *rounds[] = {reinterpret_cast<const void *>(k_round_few<256>), reinterpret_cast<const void *>(k_round_few<FEW_THREADS>)};
+    for (const void *f : rounds) RK_HIP(ctx, hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 144 * 1024));
+    constexpr int ALL = FEW_THREADS, HALF = FEW_THREADS / 2;
+    const void *sim[] = {reinterpret_cast<const void *>(k_sim_few<ALL, false, false, false>), reinterpret_cast<const void *>(k_sim_few<ALL, true, false, false>),
+                         reinterpret_cast<const void *>(k_sim_few<ALL, true, true, false>), reinterpret_cast<const void *>(k_sim_few<ALL, false, false, true>),
+                         reinterpret_cast<const void *>(k_sim_few<ALL, true, false, true>), reinterpret_cast<const void *>(k_sim_few<ALL, true, true, true>),
+                         reinterpret_cast<const void *>(k_sim_few<HALF, false, false, true>), reinterpret_cast<const void *>(k_sim_few<HALF, true, false, true>),
+                         reinterpret_cast<const void *>(k_sim_few<HALF, true, true, true>)};
     for (const void *f : sim) RK_HIP(ctx, hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, FEW_SIM_LDS));
     for (const void *f : small) RK_HIP(ctx, hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024));
     return RK_OK;
@@ -3163,8 +3337,12 @@ int32_t rk_launch_allocate(rk_ctx *ctx, const float *ref_thr, const TableDev &tb
     }
     if (few) {
         const uint32_t jobs = (max_jobs + 3u) & ~3u, gpu = max_jobs * lanes0, cpu = holders * lanes1, near = gpu > cpu ? gpu : cpu;
+        // fewer wavefronts at the barriers where four have all the lanes (8 jobs 36.3 and 35.6 us a round; 64 jobs of 16 lanes
+        // 41.1, with 512 threads 42.8, with 256 48.2)
+        const int threads = gpu <= 256u && cpu <= 256u && max_jobs <= 256u ? 256 : FEW_THREADS;
         const size_t few_lds = FEW_FIXED_BYTES + (size_t)jobs * FEW_JOB_BYTES + (size_t)near * FEW_LANE_BYTES;
-        k_round_few<<<n_rounds, FEW_THREADS, few_lds, s>>>(X, st, max_jobs, lanes0, lanes1, near, assign, totals, guard ? *guard : TableGuard{});
+        auto *kernel = threads == 256 ? k_round_few<256> : k_round_few<FEW_THREADS>;
+        kernel<<<n_rounds, threads, few_lds, s>>>(X, st, max_jobs, lanes0, lanes1, near, assign, totals, guard ? *guard : TableGuard{});
         RK_CHECK_LAUNCH(ctx, "k_round_few");
         return RK_OK;
     }
@@ -3210,10 +3388,32 @@ int32_t rk_launch_sim_few(rk_ctx *ctx, const SimArgs &A, const float *ref_thr, c
     uint32_t *far = nullptr;
     int32_t rc;
     if (cpu > near && (rc = rk_scratch(ctx, SL_HULL_KEY, (size_t)cpu * FEW_LANE_BYTES, (void **)&far))) return rc;
-    auto *kernel = !often ? k_sim_few<false, false> : far ? k_sim_few<true, true> : k_sim_few<true, false>;      // (always in LDS: rk_sim_few)
-    for (uint32_t i = 0; i < n_launches; ++i) {
-        kernel<<<1, FEW_THREADS, few_sim_job_lds(J) + (size_t)near * FEW_LANE_BYTES, ctx->stream>>>(
-            X, A, begin && i == 0 ? 1u : 0u, i ? 1u : 0u, most, lanes0, lanes1, near, far, cpu, assign, A.tick_total);
+    // What the jobs do in a round from nothing is found beforehand where that is not too much for memory or for the ticks: 6,900
+    // walks take 10 us, a round is 8 us shorter.
+    FewStates T = {nullptr, nullptr, nullptr, max_segs_per_job + 1u, A.cl.G};
+    const uint64_t walks = (uint64_t)J * T.rows, walk_bytes = walks * lanes0 * sizeof(uint4), cpu_bytes = (uint64_t)J * max_segs_per_job * sizeof(uint4);
+    const uint64_t allowed_bytes = ((uint64_t)A.cl.G + 1u) * J;
+    const bool known = A.n_ticks > 1u && max_segs_per_job > 0u && walk_bytes <= FEW_WALK_BYTES && allowed_bytes <= FEW_WALK_BYTES / 8u &&
+                       walks <= (uint64_t)FEW_WALKS_PER_TICK * A.n_ticks;
+    if (known) {
+        char *mem;
+        if ((rc = rk_scratch(ctx, SL_FEW_STATES, walk_bytes + cpu_bytes + allowed_bytes, (void **)&mem))) return rc;
+        uint4 *walk = reinterpret_cast<uint4 *>(mem), *cpu_end = reinterpret_cast<uint4 *>(mem + walk_bytes);
+        uint8_t *allowed = reinterpret_cast<uint8_t *>(mem + walk_bytes + cpu_bytes);
+        T.walk = walk; T.cpu = cpu_end; T.allowed = allowed;
+        if (begin) {
+            k_few_states<<<J, 256, 0, ctx->stream>>>(X, lanes0, lanes1, T, walk, cpu_end, allowed);
+            RK_CHECK_LAUNCH(ctx, "k_few_states");
+        }
+    }
+    constexpr int ALL = FEW_THREADS, HALF = FEW_THREADS / 2;
+    const bool half = known && J <= HALF;
+    auto *kernel = !often ? (half ? k_sim_few<HALF, false, false, true> : known ? k_sim_few<ALL, false, false, true> : k_sim_few<ALL, false, false, false>)
+                   : far  ? (half ? k_sim_few<HALF, true, true, true> : known ? k_sim_few<ALL, true, true, true> : k_sim_few<ALL, true, true, false>)
+                          : (half ? k_sim_few<HALF, true, false, true> : known ? k_sim_few<ALL, true, false, true> : k_sim_few<ALL, true, false, false>);
+    for (uint32_t i = 0; i < n_launches; ++i) {                // (the pass over GPUs is always in LDS: rk_sim_few)
+        kernel<<<1, half ? HALF : ALL, few_sim_job_lds(J) + (size_t)near * FEW_LANE_BYTES, ctx->stream>>>(
+            X, A, T, begin && i == 0 ? 1u : 0u, i ? 1u : 0u, most, lanes0, lanes1, near, far, cpu, assign);
         RK_CHECK_LAUNCH(ctx, "k_sim_few");
     }
     return RK_OK;

@@ -67,6 +67,7 @@ enum {
     SL_SIM_PLACES,                                       // simulation over nodes: where the jobs are, where they go
     SL_ND_NODES, SL_ND_U32, SL_ND_F32, SL_ND_U64, SL_ND_GIVES,   // the Schedule loop over nodes: node tables and their copy; per-job words; steps down
     SL_ND_STATES,                                        // ... in a simulation: what is kept of every job in every state
+    SL_FEW_STATES,                                       // simulation from scratch: the walks of all jobs
     SL_FIT_NEXT,                                         // model fitting: the next model to take
     SL_COUNT
 };

@@ -599,9 +599,7 @@ __device__ __forceinline__ void nd_finish(const NdArgs &A, uint32_t *np, uint32_
         }
     }
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1)
-#pragma unroll
-        for (uint32_t k = 0; k < PER; ++k) sum[k] += __shfl_xor(sum[k], o, 64);
+    for (uint32_t k = 0; k < PER; ++k) sum[k] = wave_sum_f64(sum[k]);
 #pragma unroll
     for (uint32_t k = 0; k < PER; ++k) if (lane == 0) sh_sum[k * WAVES + wave] = sum[k];
     __syncthreads();
@@ -1668,8 +1666,7 @@ __device__ __forceinline__ void nodes_lds(const KernArgs &K) {
             // the total: the additions of nd_finish, a job per thread
             {
                 double x = a.g ? (double)a.thr / (double)ref : 0.0;
-#pragma unroll
-                for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o, 64);
+                if (__ballot(x != 0.0)) x = wave_sum_f64(x);
                 const uint32_t used = nd_wave_sum(state != RK_JOB_OUT ? a.g : 0u);
                 if (lane == 0) { sh_part[wave] = x; if (used) atomicAdd(&sh_used, used); }
             }

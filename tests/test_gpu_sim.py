@@ -318,3 +318,35 @@ def test_simulation_over_nodes_at_the_sizes_it_is_laid_out_for(gpu, orc, jobs, n
         same(run_on_gpu(run, r, tr.arrival, work, tr.delta, dt, n_ticks, gate, policy=2, nodes=(nodes, gpn, cpn, mem)), want)
     assert want["gpus_in_use"].max() > 0
     run.close()
+
+
+@pytest.mark.parametrize("jobs,gpus,g_max,levels,per_gpu,cpus,tiers,mem", [
+    (1, 64, 64, 32, 0, 64, (64.0,), 4096.0),                 # one job
+    (40, 16, 16, 8, 0, 20, (64.0,), 1e6),                    # CPUs for few of the steps: the pass over them is needed
+    (120, 64, 64, 16, 1, 300, (0.0, 64.0, 1024.0), 3000.0),  # CPUs per GPU; several tiers, memory in job order
+    (512, 96, 48, 32, 0, 700, (64.0,), 1e6),                 # the last job of 512 threads; rounds for too many jobs among them
+    (513, 96, 48, 32, 0, 700, (64.0,), 2000.0),              # ... and the first of 1,024
+    (60, 512, 512, 64, 1, 9000, (64.0, 2048.0), 1e6),        # walks of more than 32 amounts and of 64 CPU levels
+    (100, 4096, 100, 5, 1, 16384, (64.0,), 1e6),             # more GPUs than all jobs can hold
+])
+def test_simulation_from_scratch_at_the_sizes_it_is_laid_out_for(gpu, orc, jobs, gpus, g_max, levels, per_gpu, cpus, tiers, mem):
+    """The walks of all jobs are found before the first tick, for every number of amounts that the capacity allows, and what
+    they would take of the CPUs; where they cannot all have it, or memory binds, a tick does what a round does."""
+    coef, ints = workloads.draw_jobs(9, 11, 0, np.arange(jobs), param_buckets=[(0.5, 0.1e9, 1.3e9), (0.5, 1.3e9, 20e9)],
+                                     layer_choices=(12, 24, 32, 40))
+    ratios = np.array([1, 2, 4, 8, 16], np.uint32) if levels == 5 else np.arange(1, levels + 1, dtype=np.uint32)
+    wl = workloads.Workload("scratch", coef, ints, workloads.Bounds(g_max=g_max), workloads.Grid(ratios, per_gpu, np.array(tiers, np.float32), 0),
+                            workloads.Env(), workloads.Cluster(gpus, cpus, mem))
+    r = orc.schedule_round(wl, n_threads=16)
+    n_ticks, dt = 61, 120.0
+    tr = workloads.trace(jobs, horizon_s=n_ticks * dt)
+    work = workloads.job_lengths_s(tr.u_duration) * wl.coef[:, 16]
+    run = gpu(wl)
+    run.enumerate()
+    for arrival in (tr.arrival, np.zeros(jobs)):
+        want = orc.simulator.simulate(wl.coef[:, 16], r["table"], wl.grid, wl.cluster, r["best_thr"], r["best_plan"], r["curve_thr"],
+                                      arrival, work, tr.delta, dt, n_ticks)
+        for _ in range(2):
+            same(run_on_gpu(run, r, arrival, work, tr.delta, dt, n_ticks, 0.97), want)
+        assert want["gpus_in_use"].max() > 0
+    run.close()
