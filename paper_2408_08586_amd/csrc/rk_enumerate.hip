@@ -45,8 +45,6 @@ enum { MODE_COUNT = 0, MODE_FILL_SEARCH = 1 };
 // a job's word in cnt_t: its triples and the flags its search raised (so nothing has to be cleared between calls)
 constexpr uint32_t CNT_MASK = 0xFFFFFFu, CNT_FLAGS = 24u;
 static_assert(MAX_T <= CNT_MASK, "the count and the flags share a word");
-// GPUs of a triple's word: a segment of a job's table begins where they differ from those of the word before
-__device__ __forceinline__ uint32_t word_gpus(uint32_t w) { return __umul24(w & 0xFFFFu, (w >> 18) & 0xFFFu) << ((w >> 16) & 3u); }
 
 // What the scan of the counts leaves: offsets in the table, totals for the fill pass, and both for the host.
 struct ScanOut {
@@ -609,7 +607,16 @@ __global__ void k_zero_words(uint32_t *p, uint32_t n) {
 
 }  // namespace
 
-int32_t rk_enumerate_begin(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_bounds *bounds, rk_plan_table *table, EnumPending &P) {
+static int32_t launch_fill(rk_ctx *ctx, const rk_plan_table *table, const EnumPending &P) {
+    constexpr uint32_t PER = FILL_THREADS / 64;
+    const uint32_t J = table->n_jobs;
+    k_fill<<<(J + PER - 1) / PER, FILL_THREADS, 0, ctx->stream>>>(J, P.leader, P.park, P.park_stride, P.off_t, P.off_s, table->triples,
+                                                                 table->seg_g, table->seg_first, P.totals, table->cap_triples, table->cap_segs);
+    RK_CHECK_LAUNCH(ctx, "k_fill");
+    return RK_OK;
+}
+
+int32_t rk_enumerate_begin(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_bounds *bounds, rk_plan_table *table, EnumPending &P, bool leave_content) {
     if (!jobs || !bounds || !table) return rk_fail(ctx, RK_ERR_INVALID_ARG, "null argument");
     if (jobs->n_jobs > 0 && (!jobs->layers || !jobs->gbatch || !jobs->mbatch)) return rk_fail(ctx, RK_ERR_INVALID_ARG, "job arrays are null");
     if (bounds->g_max < 1 || bounds->g_max > RK_MAX_G) return rk_fail(ctx, RK_ERR_UNSUPPORTED, "g_max must be in 1..%u", RK_MAX_G);
@@ -719,15 +726,9 @@ int32_t rk_enumerate_begin(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_bound
     RK_HIP(ctx, hipEventRecord(ctx->counts_ev, ctx->stream));
     // The fill pass goes out before the host knows the totals, so that the device does not wait for the
     // round trip: the kernel itself checks the flags and the table's capacity.
-    if (fill && J > 0) {
-        constexpr uint32_t PER = FILL_THREADS / 64;
-        k_fill<<<(J + PER - 1) / PER, FILL_THREADS, 0, ctx->stream>>>(J, leader, park, park_stride, off_t, off_s, table->triples,
-                                                                     table->seg_g, table->seg_first, totals, table->cap_triples,
-                                                                     table->cap_segs);
-        RK_CHECK_LAUNCH(ctx, "k_fill");
-    }
-    P = EnumPending{jobs, *bounds, leader, cnt_t, cnt_s, park, off_t, off_s, totals, park_stride, gmap_bytes, tab_clear, fill, mirrors, share, false};
-    return RK_OK;
+    P = EnumPending{jobs, *bounds, leader, cnt_t, cnt_s, park, off_t, off_s, totals, park_stride, gmap_bytes, tab_clear, fill, mirrors, share, false,
+                    false, false, TableGuard{}};
+    return fill && J > 0 && !leave_content ? launch_fill(ctx, table, P) : RK_OK;
 }
 
 int32_t rk_enumerate_end(rk_ctx *ctx, rk_plan_table *table, EnumPending &P) {
@@ -748,6 +749,7 @@ int32_t rk_enumerate_end(rk_ctx *ctx, rk_plan_table *table, EnumPending &P) {
     table->max_segs_per_job = h[TOT_MAX_S];
     ctx->seen_t[1] = ctx->seen_t[0]; ctx->seen_s[1] = ctx->seen_s[0];
     ctx->seen_t[0] = h[TOT_MAX_T]; ctx->seen_s[0] = h[TOT_MAX_S];
+    ctx->seen_segs = ns; ctx->seen_jobs = J;
     const bool parked = !(h[TOT_ERR] & ERR_PARK_FULL);
     if (!parked) {                                            // next time the slots will be wide enough
         uint32_t want = h[TOT_MAX_T] + h[TOT_MAX_T] / 4;
@@ -756,6 +758,8 @@ int32_t rk_enumerate_end(rk_ctx *ctx, rk_plan_table *table, EnumPending &P) {
     }
 
     P.whole = h[TOT_ERR] == 0u;
+    const TableGuard &G = P.guard;                            // (what table_usable asks)
+    P.taken = P.ahead && P.whole && nt <= G.cap_triples && ns <= G.cap_segs && h[TOT_MAX_T] <= G.most_t && h[TOT_MAX_S] <= G.most_s;
     if (!P.fill) return RK_OK;
     if (table->cap_triples < nt || table->cap_segs < ns)
         return rk_fail(ctx, RK_ERR_CAPACITY, "table too small: need %llu triples and %llu segments",
@@ -764,6 +768,8 @@ int32_t rk_enumerate_end(rk_ctx *ctx, rk_plan_table *table, EnumPending &P) {
         memcpy(table->h_triple_off, h + 16, ((size_t)J + 1) * 4);
         memcpy(table->h_seg_off, h + 16 + J + 1, ((size_t)J + 1) * 4);
     }
+    int32_t rc;
+    if (J > 0 && P.ahead && !P.taken && parked && (rc = launch_fill(ctx, table, P))) return rc;
     if (J > 0 && !parked) {                                   // the parked keys were incomplete: search again
         const rk_jobs *const jobs = P.jobs;
         k_enumerate<MODE_FILL_SEARCH><<<J, ENUM_THREADS, P.gmap_bytes, ctx->stream>>>(

@@ -14,7 +14,10 @@
 // packs the triples with a usable offload plan, so that the lanes of phase 2
 // (a lane per packed triple and up to six CPU levels) are all busy; quotients
 // by the same divisor share its reciprocal.  Many jobs take a wavefront each
-// (DIRECT), whose lanes go from phase 1 straight to the CPU levels.  The
+// (DIRECT), whose lanes go from phase 1 straight to the CPU levels.  In a round
+// the kernel also makes the plan table's content from what the enumeration's
+// searches left: under the arithmetic that costs nothing that can be measured,
+// as a launch of its own 3 us for few jobs and 30 for 128,000.  The
 // 128,000 jobs of 256 rounds took 808 us in the first form (a lane per triple
 // and level, a key per tier), 10,000 jobs on the full grid of 20 rows 117 us;
 // now 402 and 69 us.
@@ -67,7 +70,7 @@ __global__ __launch_bounds__(THREADS) void k_fused(JobDev jobs, TableDev tb, Gri
                                                          float *__restrict__ best_thr, uint32_t *__restrict__ best_plan,
                                                          float *__restrict__ curve_thr, uint32_t *__restrict__ curve_plan,
                                                          uint32_t *__restrict__ curve_g,
-                                                    TableGuard guard) {
+                                                    TableGuard guard, ParkedWords parked) {
     if (!table_usable(guard)) return;
     extern __shared__ unsigned long long lds64[];
     uint32_t &n_packed = *reinterpret_cast<uint32_t *>(lds64);               // triples packed so far
@@ -94,6 +97,36 @@ __global__ __launch_bounds__(THREADS) void k_fused(JobDev jobs, TableDev tb, Gri
 
     // per segment: nothing found yet, its GPU count, and its number in the info word of each of its triples
     if (tid == 0) n_packed = 0u;
+    const uint32_t *words = tb.triples + t0;
+    if (parked.words) {
+        // The table's content is made here, from the words that the search left (k_fill): a segment begins where the GPUs
+        // change.  Every wavefront counts through all words, 64 at a time, and takes every THREADS / 64-th time its share.
+        words = parked.words + (size_t)(parked.leader ? parked.leader[j] : j) * parked.stride;
+        const bool write = blockIdx.y == 0;
+        uint32_t seg = 0, before = 0;                        // segments so far, GPUs of the last word (no word has 0)
+        for (uint32_t base = 0; base < nt; base += 64u) {
+            const uint32_t t = base + lane, w = t < nt ? words[t] : 0u, g = word_gpus(w);
+            const uint32_t g_before = (uint32_t)__builtin_amdgcn_update_dpp((int)before, (int)g, 0x138, 0xF, 0xF, false);      // wave_shr:1
+            const bool starts = t < nt && g != g_before;
+            const unsigned long long m = __ballot(starts);
+            if (THREADS == 64 || (base / 64u) % (THREADS / 64u) == tid / 64u) {
+                const uint32_t s = seg + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+                if (starts) {
+                    seg_plain[s] = 0ull;
+                    l_segg[s] = g;
+                    if (write) parked.seg_g[s0 + s] = g;
+                    if (write && parked.seg_first) parked.seg_first[s0 + s] = t;
+                }
+                if (t < nt) {
+                    const uint32_t own = starts ? s : s - 1u;
+                    if (DIRECT) t_16[t] = (uint16_t)own; else t_info[t] = own;
+                    if (write && parked.triples) parked.triples[t0 + t] = w;
+                }
+            }
+            seg += (uint32_t)__popcll(m);
+            before = (uint32_t)__builtin_amdgcn_readlane((int)g, 63);
+        }
+    } else
     for (uint32_t s = tid; s < ns; s += THREADS) {
         seg_plain[s] = 0ull;
         l_segg[s] = tb.seg_g[s0 + s];
@@ -128,7 +161,7 @@ __global__ __launch_bounds__(THREADS) void k_fused(JobDev jobs, TableDev tb, Gri
         uint32_t ok = 0, info = 0;
         Offload O = {};
         if (tl < nt) {
-            const Triple T = triple_terms(J, env, tb.triples[t0 + tl]);
+            const Triple T = triple_terms(J, env, words[tl]);
             const uint32_t seg = DIRECT ? t_16[tl] : t_info[tl];
             // without offload: a stage above 0 does not change the throughput, so of those the lowest that fits
             unsigned long long k = 0;
@@ -289,7 +322,7 @@ __global__ __launch_bounds__(THREADS) void k_fused(JobDev jobs, TableDev tb, Gri
 
 int32_t rk_launch_fused(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_table *table, const rk_alloc_grid *grid,
                         const rk_env *env, uint32_t jb, uint32_t je, float *best_thr, uint32_t *best_plan,
-                        float *curve_thr, uint32_t *curve_plan, uint32_t *curve_g, const TableGuard *guard) {
+                        float *curve_thr, uint32_t *curve_plan, uint32_t *curve_g, const TableGuard *guard, const ParkedWords *parked) {
     if (je == jb) return RK_OK;
     FusedLds L;
     L.max_nt = table->max_triples_per_job ? table->max_triples_per_job : 1;
@@ -326,7 +359,8 @@ int32_t rk_launch_fused(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_table *t
     auto *kernel = direct ? k_fused<64, true> : k_fused<FEW_JOBS, false>;
     kernel<<<blocks, direct ? 64 : FEW_JOBS, lds, ctx->stream>>>(job_dev(jobs), table_dev(table), grid_dev(grid), *env, jb,
                                                                      table->option_mask, L, c_per_block, c_per_pass, m_per_pass,
-                                                                     best_thr, best_plan, curve_thr, curve_plan, curve_g, guard ? *guard : TableGuard{});
+                                                                     best_thr, best_plan, curve_thr, curve_plan, curve_g, guard ? *guard : TableGuard{},
+                                                                     parked ? *parked : ParkedWords{});
     RK_CHECK_LAUNCH(ctx, "k_fused");
     return RK_OK;
 }

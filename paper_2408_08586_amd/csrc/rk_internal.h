@@ -28,6 +28,8 @@ struct rk_ctx {
     size_t h_stage_words;
     uint32_t park_stride;                   // enumeration: words per job between its two passes
     uint32_t seen_t[2], seen_s[2];          // ... most triples and segments of a job in the last two calls (0: none)
+    uint64_t seen_segs;                     // ... segments of all jobs in the last call, and its jobs
+    uint32_t seen_jobs;
     bool enum_clear;                        // enumeration: the device's counter of finished searches is known to be zero
     size_t enum_tab_clear;                  // ... and so many words of the leaders' table
     uint32_t ways[WAY_COUNT];
@@ -130,6 +132,18 @@ __device__ __forceinline__ bool table_usable(const TableGuard &G) {
     return T[TOT_ERR] == 0u && nt <= G.cap_triples && ns <= G.cap_segs && T[TOT_MAX_T] <= G.most_t && T[TOT_MAX_S] <= G.most_s;
 }
 
+// GPUs of a triple's word: a segment of a job's table begins where they differ from those of the word before
+__device__ __forceinline__ uint32_t word_gpus(uint32_t w) { return __umul24(w & 0xFFFFu, (w >> 18) & 0xFFFu) << ((w >> 16) & 3u); }
+
+// Where an enumeration's searches left their words, for a kernel that makes the table's content itself (k_fused): of job j at
+// words + stride * (leader ? leader[j] : j).  words null: the table is there.  seg_g goes to the table in any case, triples and
+// seg_first where they are not null.
+struct ParkedWords {
+    const uint32_t *words, *leader;
+    uint32_t stride;
+    uint32_t *triples, *seg_g, *seg_first;
+};
+
 // An enumeration in two halves: what goes out to the device, and, when its counts have come back, what the host makes of
 // them.  rk_enumerate_plans is one after the other; nothing of the context's enumeration may come between them but
 // launches that a TableGuard protects.
@@ -141,8 +155,13 @@ struct EnumPending {
     size_t gmap_bytes, tab_clear;
     bool fill, mirrors, share;
     bool whole;                 // set by the second half: no job's search has to be repeated
+    bool ahead;                 // set between the halves: a kernel behind `guard` makes the table's content; ...
+    bool taken;                 // ... set by the second half: it has (otherwise the second half does)
+    TableGuard guard;
 };
-int32_t rk_enumerate_begin(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_bounds *bounds, rk_plan_table *table, EnumPending &P);
+// leave_content: the first half ends with the offsets; the caller sets ahead and guard and launches what makes the content.
+int32_t rk_enumerate_begin(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_bounds *bounds, rk_plan_table *table, EnumPending &P,
+                           bool leave_content = false);
 int32_t rk_enumerate_end(rk_ctx *ctx, rk_plan_table *table, EnumPending &P);
 
 // service-level inputs of the allocation; min_seg / min_c are indexed from the call's first job
@@ -170,7 +189,7 @@ struct FloorsDev {
 int32_t rk_launch_fused(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_table *table,
                         const rk_alloc_grid *grid, const rk_env *env, uint32_t jb, uint32_t je,
                         float *best_thr, uint32_t *best_plan, float *curve_thr, uint32_t *curve_plan,
-                        uint32_t *curve_g, const TableGuard *guard = nullptr);
+                        uint32_t *curve_g, const TableGuard *guard = nullptr, const ParkedWords *parked = nullptr);
 // one_cluster != NULL: a single round over [jb, jb + n_jobs) with that cluster, carried in the
 // kernel arguments; otherwise n_rounds rounds described by the device arrays.
 // sla != NULL: service-level floors first (the quotas apply to every round alike);

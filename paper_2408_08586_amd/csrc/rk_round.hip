@@ -96,6 +96,7 @@ int32_t schedule_rounds(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_bounds *
     uint64_t cap_t = ctx->scratch_bytes[SL_TB_TRIPLES] / 4, cap_s = ctx->scratch_bytes[SL_TB_SEGG] / 4;
     if (cap_t < (uint64_t)J * 256) cap_t = (uint64_t)J * 256;
     if (cap_s < (uint64_t)J * 32) cap_s = (uint64_t)J * 32;
+    bool evaluated = false;                                   // the curves are there
     for (int attempt = 0; attempt < 2; ++attempt) {
         if ((rc = rk_scratch(ctx, SL_TB_TOFF, ((size_t)J + 1) * 4, (void **)&tb.triple_off))) return rc;
         if ((rc = rk_scratch(ctx, SL_TB_SOFF, ((size_t)J + 1) * 4, (void **)&tb.seg_off))) return rc;
@@ -104,37 +105,54 @@ int32_t schedule_rounds(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_bounds *
         if ((rc = rk_scratch(ctx, SL_TB_SEGF, cap_s * 4, (void **)&tb.seg_first))) return rc;
         tb.cap_triples = cap_t;
         tb.cap_segs = cap_s;
+        // The host waits for the table's size while the device has nothing to do.  When the last two enumerations found tables
+        // of the same kind, the evaluation goes out at once, prepared for a table like these, and makes the table's content
+        // itself; it leaves any other table alone, and the round is then evaluated again for the one there is.  A round
+        // that takes one launch waits longer for that than for anything else it does: its allocation goes out as well.
+        // Rounds of 20 and 60 jobs 41 -> 36 and 45 -> 40 us, 46 and 50 where the guess was wrong: calls in turn from two
+        // kinds, two of each, are back at 43.
+        // With the content made by the evaluation instead of a launch in front of it, and with every kind of round evaluated
+        // ahead: 8 jobs 36.1 and 31.2 us, 64 jobs 40.2 and 35.0, 1,000 jobs 105.8 and 97.1, 10,000 jobs 201.7 and 194.0, 256 rounds of
+        // 500 jobs 611 and 581, a placed round of 1,000 jobs 261 and 251; two kinds in turn, or two of each, take what they took.
+        const uint32_t few_s = few_amounts(ctx->seen_s[0]), few_t = (ctx->seen_t[0] + 63u) & ~63u;
+        const bool seen = ctx->seen_s[0] > 0 && J > 0;
+        const bool sent = seen && may_go_ahead(few_s) && few_t <= 1024u && few_amounts(ctx->seen_s[1]) == few_s &&
+                          ((ctx->seen_t[1] + 63u) & ~63u) == few_t && have_room(n_rows * J * few_s);
+        const uint64_t like_last = n_rows * ctx->seen_segs;    // entries of the outputs if this call is like the last one
+        const bool ahead = sent || (seen && ctx->seen_jobs == J && ctx->seen_s[1] == ctx->seen_s[0] && ctx->seen_t[1] == ctx->seen_t[0] && have_room(like_last));
         EnumPending P;
-        if ((rc = rk_enumerate_begin(ctx, jobs, bounds, &tb, P))) break;
-        // A small round waits longer for the host to see the table's size than for anything else it does.  When the last two
-        // enumerations found tables of the same kind, evaluation and allocation go out at once, prepared for a table like
-        // these; the kernels leave any other one alone, and the round is then launched again for the one there is.  Rounds
-        // of 20 and 60 jobs 41 -> 36 and 45 -> 40 us, 46 and 50 where the guess was wrong: calls in turn from two kinds, two of
-        // each, are back at 43.
-        const uint32_t most_s = few_amounts(ctx->seen_s[0]), most_t = (ctx->seen_t[0] + 63u) & ~63u;
-        const bool sent = may_go_ahead(most_s) && most_t <= 1024u && ctx->seen_s[0] > 0 && few_amounts(ctx->seen_s[1]) == most_s &&
-                          ((ctx->seen_t[1] + 63u) & ~63u) == most_t && have_room(n_rows * J * most_s);
-        if (sent) {
-            const uint64_t segs = (uint64_t)J * most_s < cap_s ? (uint64_t)J * most_s : cap_s;
-            ctx->ways[WAY_ROUND_AHEAD]++;
-            const TableGuard guard = {P.totals, cap_t, segs, most_t, most_s};
+        if ((rc = rk_enumerate_begin(ctx, jobs, bounds, &tb, P, ahead))) break;
+        int32_t rc_sent = RK_OK;
+        if (ahead) {
+            uint64_t segs = cap_s;                             // that the outputs have room for
+            for (int slot : {SL_BEST_THR, SL_BEST_PLAN, SL_CURVE_THR, SL_CURVE_PLAN, SL_CURVE_G}) {
+                const uint64_t n = ctx->scratch_bytes[slot] / 4 / n_rows;
+                segs = n < segs ? n : segs;
+            }
+            if (sent && segs > (uint64_t)J * few_s) segs = (uint64_t)J * few_s;
+            P.ahead = true;
+            P.guard = TableGuard{P.totals, cap_t, segs, sent ? few_t : ctx->seen_t[0], sent ? few_s : ctx->seen_s[0]};
             rk_plan_table like = tb;
-            like.max_triples_per_job = most_t; like.max_segs_per_job = most_s;
+            like.max_triples_per_job = P.guard.most_t; like.max_segs_per_job = P.guard.most_s;
+            const ParkedWords parked = {P.park, P.leader, P.park_stride, keep ? tb.triples : nullptr, tb.seg_g, keep ? tb.seg_first : nullptr};
             float *best_thr, *curve_thr;
             uint32_t *best_plan, *curve_plan, *curve_g;
-            rc = outputs((size_t)(n_rows * segs), best_thr, best_plan, curve_thr, curve_plan, curve_g);
-            if (!rc) rc = rk_launch_fused(ctx, jobs, &like, grid, env, 0, J, best_thr, best_plan, curve_thr, curve_plan, curve_g, &guard);
-            if (!rc) rc = rk_launch_allocate(ctx, jobs->ref_thr, table_dev(&like), grid, 1, nullptr, nullptr, &clusters[0], 0, J, J, most_s,
-                                             best_thr, best_plan, curve_thr, nullptr, nullptr, nullptr, assign, totals, false, true, &guard);
-            const int32_t rc_sent = rc;
-            rc = rk_enumerate_end(ctx, &tb, P);
-            if (!rc) rc = rc_sent;
-            if (!rc && P.whole && tb.n_segs <= segs && tb.max_triples_per_job <= most_t && tb.max_segs_per_job <= most_s) {
-                ctx->ways[WAY_ROUND_AHEAD_TAKEN]++;
-                return RK_OK;
+            rc_sent = outputs((size_t)(n_rows * segs), best_thr, best_plan, curve_thr, curve_plan, curve_g);
+            if (!rc_sent) rc_sent = rk_launch_fused(ctx, jobs, &like, grid, env, 0, J, best_thr, best_plan, curve_thr, curve_plan, curve_g, &P.guard, &parked);
+            if (rc_sent) P.guard.cap_triples = 0;              // (nothing went out: the second half makes the content)
+            if (sent) {
+                ctx->ways[WAY_ROUND_AHEAD]++;
+                if (!rc_sent)
+                    rc_sent = rk_launch_allocate(ctx, jobs->ref_thr, table_dev(&like), grid, 1, nullptr, nullptr, &clusters[0], 0, J, J, few_s,
+                                                 best_thr, best_plan, curve_thr, nullptr, nullptr, nullptr, assign, totals, false, true, &P.guard);
             }
-        } else {
-            rc = rk_enumerate_end(ctx, &tb, P);
+        }
+        rc = rk_enumerate_end(ctx, &tb, P);
+        if (!rc) rc = rc_sent;
+        evaluated = !rc && P.taken;
+        if (evaluated && sent) {
+            ctx->ways[WAY_ROUND_AHEAD_TAKEN]++;
+            return RK_OK;
         }
         if (rc != RK_ERR_CAPACITY) break;
         cap_t = tb.n_triples;
@@ -147,7 +165,7 @@ int32_t schedule_rounds(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_bounds *
     uint32_t *best_plan, *curve_plan, *curve_g;
     const uint32_t most = few_amounts(tb.max_segs_per_job);
     if ((rc = outputs((size_t)(n_rows * (may_go_ahead(most) ? (uint64_t)J * most : tb.n_segs)), best_thr, best_plan, curve_thr, curve_plan, curve_g))) return rc;
-    if ((rc = rk_launch_fused(ctx, jobs, &tb, grid, env, 0, J, best_thr, best_plan, curve_thr, curve_plan, curve_g))) return rc;
+    if (!evaluated && (rc = rk_launch_fused(ctx, jobs, &tb, grid, env, 0, J, best_thr, best_plan, curve_thr, curve_plan, curve_g))) return rc;
     if (keep) {
         keep->tb = tb; keep->best_thr = best_thr; keep->best_plan = best_plan; keep->curve_thr = curve_thr; keep->min_seg = nullptr;
         if (keep->curves_only) return RK_OK;
