@@ -117,15 +117,22 @@ __device__ __forceinline__ uint32_t search_hash(uint32_t kl, uint32_t kn) {
 constexpr int LEAD_THREADS = 256;
 constexpr uint32_t SHARE_MIN_JOBS = 2048;                  // calls with fewer jobs do not look for equal ones
 constexpr uint32_t SCAN_MOST_TILES = 4096;                 // beyond 2^20 jobs one workgroup scans (every tile reads all before it)
-constexpr uint32_t ENUM_SELF_SCAN = ENUM_THREADS;          // a thread per job; more would queue at the counter as well
+// A thread scans two neighbouring jobs.  Of more jobs the workgroups queue at the counter: a round of 500 jobs took 90.9 us
+// with the scan in here and 95.0 with one of its own, one of 1,000 jobs 101.3 and 98.3, one of 2,000 139.6 and 128.8.
+constexpr uint32_t ENUM_SELF_SCAN = 2 * ENUM_THREADS;
+// Beyond this many jobs the leaders are listed and so many workgroups take them in turn.  With a workgroup per job, of which
+// nearly all have nothing to do, 128,000 jobs of 45 kinds took 117 us, now 96, of 3,000 kinds 129 and 112, 60,000 of 45 kinds
+// 76 and 67; where nearly all jobs are kinds of their own, which is not what jobs are like, the list costs more than it saves
+// (128,000 of 100,000 kinds 280 and 303, with 2,048 workgroups 378: searches differ in length).  10,000 jobs: 48.9 and 50.9.
+constexpr uint32_t ENUM_TURNS = 16384;
 constexpr size_t BACK_DIRECT_WORDS = 4096;
 
 __global__ __launch_bounds__(LEAD_THREADS) void k_enum_leaders(const uint32_t *__restrict__ layers,
                                                                const uint32_t *__restrict__ gbatch,
                                                                const uint32_t *__restrict__ mbatch, uint32_t n_jobs,
                                                                uint32_t *__restrict__ tab, uint32_t tab_mask,
-                                                               uint32_t *__restrict__ leader) {
-    __shared__ uint32_t ltab[2 * LEAD_THREADS], s_kl[LEAD_THREADS], s_kn[LEAD_THREADS], s_lead[LEAD_THREADS];
+                                                               uint32_t *__restrict__ leader, uint32_t *__restrict__ list, uint32_t *n_list) {
+    __shared__ uint32_t ltab[2 * LEAD_THREADS], s_kl[LEAD_THREADS], s_kn[LEAD_THREADS], s_lead[LEAD_THREADS], s_n, s_at;
     const uint32_t tid = threadIdx.x, j = blockIdx.x * LEAD_THREADS + tid;
     const bool valid = j < n_jobs;
     uint32_t kl = 0, kn = 0;
@@ -134,6 +141,7 @@ __global__ __launch_bounds__(LEAD_THREADS) void k_enum_leaders(const uint32_t *_
     s_kn[tid] = kn;
     ltab[tid] = 0u;
     ltab[tid + LEAD_THREADS] = 0u;
+    if (tid == 0) s_n = 0u;
     __syncthreads();
     const uint32_t h = search_hash(kl, kn);
     uint32_t rep = tid;                                     // the thread that speaks for this job's kind
@@ -146,11 +154,12 @@ __global__ __launch_bounds__(LEAD_THREADS) void k_enum_leaders(const uint32_t *_
             slot = (slot + 1u) & (2u * LEAD_THREADS - 1u);
         }
     }
+    uint32_t at = UINT32_MAX;                               // a leader's place among those of the workgroup
     if (valid && rep == tid) {
         uint32_t slot = h & tab_mask, lead = j;
         for (;;) {
             const uint32_t old = atomicCAS(&tab[slot], 0u, j + 1u);
-            if (old == 0u) break;
+            if (old == 0u) { if (list) at = atomicAdd(&s_n, 1u); break; }
             const uint32_t o = old - 1u;
             uint32_t ol, on;
             search_key(layers[o], gbatch[o], mbatch[o], ol, on);
@@ -161,6 +170,10 @@ __global__ __launch_bounds__(LEAD_THREADS) void k_enum_leaders(const uint32_t *_
     }
     __syncthreads();
     if (valid) leader[j] = s_lead[rep];
+    if (!list || s_n == 0u) return;
+    if (tid == 0) s_at = atomicAdd(n_list, s_n);            // (one by one they took 40 us for 100,000 leaders)
+    __syncthreads();
+    if (at != UINT32_MAX) list[s_at + at] = j;
 }
 
 // the counts of a job that did not search are its leader's; sums and maxima of every workgroup's jobs for k_scan_tiles
@@ -168,7 +181,9 @@ struct TileSum { unsigned long long t, s; uint32_t mt, ms, err, pad; };
 
 __global__ __launch_bounds__(LEAD_THREADS) void k_spread_counts(const uint32_t *__restrict__ leader, uint32_t n_jobs,
                                                                 uint32_t *__restrict__ cnt_t, uint32_t *__restrict__ cnt_s,
-                                                                TileSum *__restrict__ sums, uint32_t *__restrict__ tab, uint32_t tab_slots) {
+                                                                TileSum *__restrict__ sums, uint32_t *__restrict__ tab, uint32_t tab_slots,
+                                                                uint32_t *__restrict__ n_list) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) *n_list = 0u;     // (all searches have been made)
     // the leaders' table has been read: zero for the next call (a launch of its own before it took 5 us)
     for (uint32_t i = blockIdx.x * LEAD_THREADS + threadIdx.x; i < tab_slots / 4u; i += gridDim.x * LEAD_THREADS)
         reinterpret_cast<uint4 *>(tab)[i] = uint4{0u, 0u, 0u, 0u};
@@ -238,14 +253,15 @@ __global__ __launch_bounds__(LEAD_THREADS) void k_scan_tiles(const uint32_t *__r
     if (last && tid == 0) write_totals(S, n_jobs, bt + all_t, bs + all_s, mt, ms, err);
 }
 
-// self_scan != 0: the workgroup that ends last also scans the counts (n_jobs <= ENUM_SELF_SCAN = ENUM_THREADS, no leaders).
+// LISTED: the workgroups take the jobs in list, *n_list of them, in turn; else job blockIdx.x, if it is a leader.
+// self_scan != 0: the workgroup that ends last also scans the counts (n_jobs <= ENUM_SELF_SCAN, no leaders).
 // The counter of finished workgroups starts at zero and is left at zero by the one that ends last: what it has to be is
 // known on the device alone, whatever became of the calls before (one that ended in an error, one that was only recorded).
-template <int MODE>
+template <int MODE, bool LISTED>
 __global__ __launch_bounds__(ENUM_THREADS) void k_enumerate(
     const uint32_t *__restrict__ layers, const uint32_t *__restrict__ gbatch,
     const uint32_t *__restrict__ mbatch, rk_plan_bounds bounds, const uint32_t *__restrict__ leader,
-    uint32_t *cnt_t, uint32_t *cnt_s, uint32_t *__restrict__ park, uint32_t park_stride,
+    const uint32_t *__restrict__ list, const uint32_t *__restrict__ n_list, uint32_t *cnt_t, uint32_t *cnt_s, uint32_t *__restrict__ park, uint32_t park_stride,
     const uint32_t *__restrict__ triple_off, const uint32_t *__restrict__ seg_off,
     uint32_t *__restrict__ triples, uint32_t *__restrict__ seg_g, uint32_t *__restrict__ seg_first,
     uint32_t self_scan, ScanOut S) {
@@ -261,8 +277,11 @@ __global__ __launch_bounds__(ENUM_THREADS) void k_enumerate(
     __shared__ uint32_t scan_tmp[ENUM_THREADS];
     __shared__ uint32_t nd, np, nk;
 
-    const uint32_t j = blockIdx.x, tid = threadIdx.x;
-    if (MODE == MODE_COUNT && leader && leader[j] != j) return;   // (whole workgroup) the leader searches for this job
+    const uint32_t tid = threadIdx.x, n_search = LISTED ? *n_list : 0u;
+    for (uint32_t turn = blockIdx.x; !LISTED || turn < n_search; turn += gridDim.x) {
+    const uint32_t j = LISTED ? list[turn] : turn;
+    if (MODE == MODE_COUNT && !LISTED && leader && leader[j] != j) return;   // (whole workgroup) the leader searches for this job
+    if (LISTED && turn != blockIdx.x) __syncthreads();                    // (the turn before has read its arrays)
     uint32_t cnt, err = 0;
     const uint32_t *fin = keys;                                 // the keys in order
     {
@@ -428,8 +447,9 @@ __global__ __launch_bounds__(ENUM_THREADS) void k_enumerate(
     }
     if (MODE != MODE_COUNT) return;
     if (!room) err |= ERR_PARK_FULL;
-    if (!self_scan) {
+    if (LISTED || !self_scan) {
         if (tid == 0) { cnt_t[j] = cnt | (err << CNT_FLAGS); cnt_s[j] = nseg; }
+        if (LISTED) continue;
         return;
     }
     // Counts, then the counter, at the device's scope (the workgroups sit on several L2 caches): a count is on its way to where
@@ -445,15 +465,28 @@ __global__ __launch_bounds__(ENUM_THREADS) void k_enumerate(
     __syncthreads();
     if (ends != gridDim.x - 1u) return;
     if (tid == 0) S.totals[TOT_DONE] = 0u;                      // (for the next launch)
-    uint32_t ct = 0, cs = 0;
-    if (tid < gridDim.x) {
-        ct = __hip_atomic_load(&cnt_t[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        cs = __hip_atomic_load(&cnt_s[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    constexpr uint32_t OWN = ENUM_SELF_SCAN / ENUM_THREADS;     // neighbouring jobs of a thread, at most
+    const uint32_t own = (gridDim.x + ENUM_THREADS - 1u) / ENUM_THREADS, first = tid * own;
+    uint32_t ct[OWN], cs[OWN], sum_t = 0, sum_s = 0, mt = 0, ms = 0, flags = 0, all_t, all_s;
+#pragma unroll
+    for (uint32_t i = 0; i < OWN; ++i) {
+        const bool in = i < own && first + i < gridDim.x;
+        ct[i] = in ? __hip_atomic_load(&cnt_t[first + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+        cs[i] = in ? __hip_atomic_load(&cnt_s[first + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
     }
-    uint32_t mt = ct & CNT_MASK, ms = cs, flags = ct >> CNT_FLAGS, all_t, all_s;
-    ct &= CNT_MASK;
-    const uint32_t et = block_excl_scan(ct, scan_tmp, &all_t), es = block_excl_scan(cs, scan_tmp, &all_s);
-    if (tid < gridDim.x) write_offsets(S, gridDim.x, tid, et, es);
+#pragma unroll
+    for (uint32_t i = 0; i < OWN; ++i) {
+        flags |= ct[i] >> CNT_FLAGS;
+        ct[i] &= CNT_MASK;
+        sum_t += ct[i]; sum_s += cs[i];
+        mt = ct[i] > mt ? ct[i] : mt; ms = cs[i] > ms ? cs[i] : ms;
+    }
+    uint32_t et = block_excl_scan(sum_t, scan_tmp, &all_t), es = block_excl_scan(sum_s, scan_tmp, &all_s);
+#pragma unroll
+    for (uint32_t i = 0; i < OWN; ++i) {
+        if (i < own && first + i < gridDim.x) write_offsets(S, gridDim.x, first + i, et, es);
+        et += ct[i]; es += cs[i];
+    }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
         const uint32_t a = __shfl_xor(mt, off, 64), b = __shfl_xor(ms, off, 64);
@@ -469,6 +502,8 @@ __global__ __launch_bounds__(ENUM_THREADS) void k_enumerate(
             flags |= scan_tmp[8 + w];
         }
         write_totals(S, gridDim.x, all_t, all_s, mt, ms, flags);
+    }
+    return;
     }
 }
 
@@ -668,7 +703,7 @@ int32_t rk_enumerate_begin(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_bound
     while (tab_slots < 2 * (uint64_t)J) tab_slots <<= 1;
     const uint32_t job_blocks = (J + LEAD_THREADS - 1) / LEAD_THREADS;
     const bool tiles = share && job_blocks <= SCAN_MOST_TILES;
-    uint32_t *tab = nullptr, *leader = nullptr;
+    uint32_t *tab = nullptr, *leader = nullptr, *list = nullptr;
     TileSum *sums = nullptr;
     // The counter in the totals is zero where the last call came to its end (set below); otherwise it is cleared first.
     if ((rc = rk_scratch(ctx, SL_TOTALS, 16 * sizeof(uint32_t), (void **)&totals))) return rc;
@@ -680,7 +715,8 @@ int32_t rk_enumerate_begin(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_bound
     if (share) {
         const size_t had = ctx->scratch_bytes[SL_ENUM_TAB];
         if ((rc = rk_scratch(ctx, SL_ENUM_TAB, (size_t)tab_slots * 4, (void **)&tab))) return rc;
-        if ((rc = rk_scratch(ctx, SL_ENUM_LEADER, ((size_t)J + 1) * 4, (void **)&leader))) return rc;
+        if ((rc = rk_scratch(ctx, SL_ENUM_LEADER, ((J > ENUM_TURNS ? 2 : 1) * (size_t)J + 1) * 4, (void **)&leader))) return rc;
+        if (J > ENUM_TURNS) list = leader + J;
         if ((rc = rk_scratch(ctx, SL_ENUM_SUMS, (size_t)job_blocks * sizeof(TileSum), (void **)&sums))) return rc;
         if (ctx->scratch_bytes[SL_ENUM_TAB] != had) ctx->enum_tab_clear = 0;         // new memory
     }
@@ -713,7 +749,7 @@ int32_t rk_enumerate_begin(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_bound
     const ScanOut S = {off_t, off_s, totals, back, mirrors ? 1u : 0u};
 
     const size_t gmap_bytes = (size_t)((bounds->g_max >> 5) + 1u) * 2 * sizeof(uint32_t);   // bitmap + word prefixes
-    const bool self_scan = J > 0 && J <= ENUM_SELF_SCAN;
+    const bool self_scan = J > 0 && J <= ENUM_SELF_SCAN && !share;
     size_t tab_clear = 0;
     if (share) {
         // the table is zero where earlier calls came to their end; otherwise it is cleared first
@@ -725,17 +761,18 @@ int32_t rk_enumerate_begin(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_bound
         }
         tab_clear = clear < tab_slots ? (size_t)tab_slots : clear;
         k_enum_leaders<<<job_blocks, LEAD_THREADS, 0, ctx->stream>>>(jobs->layers, jobs->gbatch, jobs->mbatch, J, tab,
-                                                                    (uint32_t)(tab_slots - 1), leader);
+                                                                    (uint32_t)(tab_slots - 1), leader, list, totals + TOT_LEADERS);
         RK_CHECK_LAUNCH(ctx, "k_enum_leaders");
     }
     if (J > 0) {
-        k_enumerate<MODE_COUNT><<<J, ENUM_THREADS, gmap_bytes, ctx->stream>>>(
-            jobs->layers, jobs->gbatch, jobs->mbatch, *bounds, leader, cnt_t, cnt_s, park, park_stride,
+        const auto count = list ? k_enumerate<MODE_COUNT, true> : k_enumerate<MODE_COUNT, false>;
+        count<<<list ? ENUM_TURNS : J, ENUM_THREADS, gmap_bytes, ctx->stream>>>(
+            jobs->layers, jobs->gbatch, jobs->mbatch, *bounds, leader, list, totals + TOT_LEADERS, cnt_t, cnt_s, park, park_stride,
             nullptr, nullptr, nullptr, nullptr, nullptr, self_scan ? 1u : 0u, S);
         RK_CHECK_LAUNCH(ctx, "k_enumerate<count>");
     }
     if (share) {
-        k_spread_counts<<<job_blocks, LEAD_THREADS, 0, ctx->stream>>>(leader, J, cnt_t, cnt_s, sums, tab, (uint32_t)tab_slots);
+        k_spread_counts<<<job_blocks, LEAD_THREADS, 0, ctx->stream>>>(leader, J, cnt_t, cnt_s, sums, tab, (uint32_t)tab_slots, totals + TOT_LEADERS);
         RK_CHECK_LAUNCH(ctx, "k_spread_counts");
     }
     if (tiles) k_scan_tiles<<<job_blocks, LEAD_THREADS, 0, ctx->stream>>>(cnt_t, cnt_s, J, sums, S);
@@ -791,8 +828,8 @@ int32_t rk_enumerate_end(rk_ctx *ctx, rk_plan_table *table, EnumPending &P) {
     if (J > 0 && P.ahead && !P.taken && parked && (rc = launch_fill(ctx, table, P))) return rc;
     if (J > 0 && !parked) {                                   // the parked keys were incomplete: search again
         const rk_jobs *const jobs = P.jobs;
-        k_enumerate<MODE_FILL_SEARCH><<<J, ENUM_THREADS, P.gmap_bytes, ctx->stream>>>(
-            jobs->layers, jobs->gbatch, jobs->mbatch, P.bounds, P.leader, P.cnt_t, P.cnt_s, P.park, P.park_stride,
+        k_enumerate<MODE_FILL_SEARCH, false><<<J, ENUM_THREADS, P.gmap_bytes, ctx->stream>>>(
+            jobs->layers, jobs->gbatch, jobs->mbatch, P.bounds, nullptr, nullptr, nullptr, P.cnt_t, P.cnt_s, P.park, P.park_stride,
             P.off_t, P.off_s, table->triples, table->seg_g, table->seg_first, 0u, ScanOut{});
         RK_CHECK_LAUNCH(ctx, "k_enumerate<fill>");
     }

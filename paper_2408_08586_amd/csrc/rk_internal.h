@@ -116,7 +116,7 @@ static inline TableDev table_dev(const rk_plan_table *t) {
 }
 
 // Where the enumeration leaves what the scan of the counts found, on the device and for the host.
-enum { TOT_NT_LO = 0, TOT_NT_HI, TOT_NS_LO, TOT_NS_HI, TOT_MAX_T, TOT_MAX_S, TOT_ERR, TOT_DONE, TOT_WORDS };
+enum { TOT_NT_LO = 0, TOT_NT_HI, TOT_NS_LO, TOT_NS_HI, TOT_MAX_T, TOT_MAX_S, TOT_ERR, TOT_DONE, TOT_LEADERS, TOT_WORDS };
 
 // Kernels that are launched behind an enumeration before the host has seen its totals: the sizes they are prepared for.
 // A table that is beyond them (or none, after an error) is left alone.

@@ -1013,6 +1013,27 @@ def test_enumeration_at_the_job_counts_where_the_scan_changes(gpu, orc):
     run.close()
 
 
+@pytest.mark.parametrize("n,n_kinds", [(511, 40), (512, 512), (513, 40), (16384, 45), (16385, 1), (16385, 3000), (40000, 33000)])
+def test_enumeration_around_the_listed_searches(gpu, orc, n, n_kinds):
+    """Up to 512 jobs are scanned by the last search, two to a thread; beyond 16,384 the searches are taken from a list, in
+    more than one turn where there are more kinds than that."""
+    import paper_2408_08586_amd as rk
+    rng = np.random.default_rng(n + n_kinds)
+    at = rng.choice(120 * 600, size=n_kinds, replace=False)
+    kinds = np.stack([at % 120, at // 120 * 2, np.full(n_kinds, 2)], axis=1).astype(np.uint32)      # (layers 0 and batch 0 among them)
+    ints = np.concatenate([kinds, kinds[rng.integers(0, n_kinds, size=n - n_kinds)]])[rng.permutation(n)]
+    bounds = workloads.Bounds(g_max=48, tp_max=8, pp_max=8, mu_mask=0b10)
+    run = gpu(workloads.tiny())
+    jobs = rk.Jobs(np.ones((n, 17), np.float32), ints, run.device)
+    expected = orc.enumerate_plans(ints, bounds)
+    for _ in range(2):                                     # (the second call finds the table and the counters as the first left them)
+        t = rk.enumerate_to_table(run.ctx, jobs, rk.make_bounds(bounds), run.device)
+        got = dict(triple_off=rk.u32(t.triple_off), triples=t.unpack_triples(), seg_off=rk.u32(t.seg_off),
+                   seg_g=rk.u32(t.seg_g), seg_first=rk.u32(t.seg_first))
+        oracle_table_equal(got, expected)
+    run.close()
+
+
 @pytest.mark.parametrize("wide", [0, 1])
 def test_scratch_of_an_enumeration(gpu, orc, wide):
     """What the counting pass parks takes a word per triple: 512 words per job at first, and the widest job's triples and a
