@@ -125,7 +125,6 @@ constexpr uint32_t ENUM_SELF_SCAN = 2 * ENUM_THREADS;
 // 76 and 67; where nearly all jobs are kinds of their own, which is not what jobs are like, the list costs more than it saves
 // (128,000 of 100,000 kinds 280 and 303, with 2,048 workgroups 378: searches differ in length).  10,000 jobs: 48.9 and 50.9.
 constexpr uint32_t ENUM_TURNS = 16384;
-constexpr size_t BACK_DIRECT_WORDS = 4096;
 
 __global__ __launch_bounds__(LEAD_THREADS) void k_enum_leaders(const uint32_t *__restrict__ layers,
                                                                const uint32_t *__restrict__ gbatch,
@@ -741,11 +740,10 @@ int32_t rk_enumerate_begin(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_bound
     if (!ctx->counts_ev) RK_HIP(ctx, hipEventCreateWithFlags(&ctx->counts_ev, hipEventDisableTiming));
 
     const bool mirrors = fill && table->h_triple_off && table->h_seg_off;
-    // Few words go straight to the host; the offsets of many jobs in one copy (single words over the bus are slow).
-    const bool direct = words_back <= BACK_DIRECT_WORDS || !mirrors;
+    // All of them go straight to the host, a wavefront's words in one piece.  As a copy that the host sends for, behind the scan,
+    // they cost an enumeration of 3,333 jobs 44 instead of 30 us, of 10,000 jobs 48 and 33, of 128,000 jobs 93 and 78.
     uint32_t *back;
-    if (direct) RK_HIP(ctx, hipHostGetDevicePointer((void **)&back, h, 0));
-    else if ((rc = rk_scratch(ctx, SL_ENUM_BACK, words_back * 4, (void **)&back))) return rc;
+    RK_HIP(ctx, hipHostGetDevicePointer((void **)&back, h, 0));
     const ScanOut S = {off_t, off_s, totals, back, mirrors ? 1u : 0u};
 
     const size_t gmap_bytes = (size_t)((bounds->g_max >> 5) + 1u) * 2 * sizeof(uint32_t);   // bitmap + word prefixes
@@ -778,7 +776,6 @@ int32_t rk_enumerate_begin(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_bound
     if (tiles) k_scan_tiles<<<job_blocks, LEAD_THREADS, 0, ctx->stream>>>(cnt_t, cnt_s, J, sums, S);
     else if (!self_scan) k_scan_counts<<<1, 1024, 0, ctx->stream>>>(cnt_t, cnt_s, J, S);
     RK_CHECK_LAUNCH(ctx, "k_scan_counts");
-    if (!direct) RK_HIP(ctx, hipMemcpyAsync(h, back, words_back * 4, hipMemcpyDeviceToHost, ctx->stream));
     RK_HIP(ctx, hipEventRecord(ctx->counts_ev, ctx->stream));
     // The fill pass goes out before the host knows the totals, so that the device does not wait for the
     // round trip: the kernel itself checks the flags and the table's capacity.

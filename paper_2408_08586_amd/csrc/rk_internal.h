@@ -59,7 +59,6 @@ enum {
     SL_MIN_SEG, SL_MIN_C, SL_MIN_M,                      // minimum demands of a round
     SL_SIM_STATE, SL_SIM_ASSIGN,                         // simulation: per-job state, the tick's assignment
     SL_JMAP,                                             // rounds that share jobs: slot -> job
-    SL_ENUM_BACK,                                        // enumeration: totals and offsets in one piece for the host
     SL_PLACE_RESULT,                                     // placement: its four summary words
     SL_ENUM_LEADER, SL_ENUM_TAB, SL_ENUM_SUMS,           // enumeration: the job whose search a job shares, their hash table, sums per workgroup
     SL_RS_U32, SL_RS_U64, SL_RS_NEXT, SL_RS_GIVES,       // the Schedule loop: slopes, order and marks; places in the order; steps up and down
