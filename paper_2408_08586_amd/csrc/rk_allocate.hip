@@ -24,8 +24,8 @@
 //           next step (the walk's next step if it still fits, otherwise a fresh
 //           search within the capacity that is left).
 //  k_tail   the plain step-by-step loop on the little capacity that is left:
-//           one workgroup per round, argmax over the cached steps, which each
-//           thread keeps in registers for the jobs it owns.
+//           one workgroup per round, whose first wavefront takes steps from a
+//           list of the best cached ones, which all wavefronts keep and find.
 //  When no job's CPU walk has a step, the CPU pass's k_hist, k_apply and k_tail
 //  return at once (a per-round flag raised by its k_hull).
 //
@@ -917,35 +917,28 @@ __device__ __forceinline__ Step best_step_wave(const Ctx &X, uint32_t j, int32_t
     return out;
 }
 
-// What a wavefront has read of the job with its best step: a lane per amount, in registers.
-struct TailJob {
-    uint32_t jl;             // the job (~0: none); with more than 64 amounts it is not kept
-    uint32_t g;              // GPU pass: GPUs of the lane's amount
-    float v, ref;            // value of the lane's amount; the job's reference throughput
-};
-
-// best_step_wave from what has been read: the same search, `at` = the amount the job is at.
+// The same search over amounts that lie in LDS, a lane each: v, g = the lane's amount's value and GPUs, `at` = the amount the
+// job is at (-1: it holds nothing).
 template <int PASS>
-__device__ __forceinline__ Step best_step_kept(const Ctx &X, const TailJob &T, uint32_t at, uint32_t ns, uint32_t g_held, uint32_t ci,
-                                               unsigned long long freeG, unsigned long long freeC) {
-    const GridDev &grid = X.grid;
+__device__ __forceinline__ Step best_step_listed(const GridDev &grid, const uint32_t *lvl, float v, uint32_t g, float ref, int32_t at, uint32_t ns,
+                                                 uint32_t g_held, uint32_t ci, uint32_t roomG, uint32_t roomC) {
     const uint32_t lane = threadIdx.x & 63u;
-    const float cur = __uint_as_float(wave_lane_u32(__float_as_uint(T.v), at));
+    const float cur = at < 0 ? 0.f : __uint_as_float(wave_lane_u32(__float_as_uint(v), (uint32_t)at));
     uint32_t mine = 0, dg = 0;
     if (PASS == 0) {
-        const uint32_t g_cur = wave_lane_u32(T.g, at);
-        dg = T.g - g_cur;
-        if (lane > at && lane < ns && T.v > cur && dg <= freeG &&
-            cpu_cost(grid, ci, g_cur + dg) - cpu_cost(grid, ci, g_cur) <= freeC) {
-            float sl = (T.v - cur) / T.ref;
+        dg = g - (at < 0 ? 0u : wave_lane_u32(g, (uint32_t)at));
+        const unsigned long long dc = (unsigned long long)lvl[ci] * (grid.cpu_mode ? dg : (at < 0 ? 1u : 0u));
+        if ((int32_t)lane > at && lane < ns && v > cur && dg <= roomG && dc <= roomC) {
+            float sl = (v - cur) / ref;
             sl = sl / (float)dg;
             mine = __float_as_uint(sl);
         }
-    } else if (lane > at && lane < grid.n_cpu && T.v > cur) {
-        const unsigned long long dc = cpu_cost(grid, lane, g_held) - cpu_cost(grid, at, g_held);
-        if (dc <= freeC) {
-            float sl = (T.v - cur) / T.ref;
-            sl = sl / (float)dc;
+    } else if ((int32_t)lane > at && lane < ns && v > cur) {
+        const unsigned long long times = grid.cpu_mode ? g_held : 1u;
+        const unsigned long long dc = (unsigned long long)lvl[lane] * times - (unsigned long long)lvl[at] * times;
+        if (dc <= roomC) {
+            float sl = (v - cur) / ref;
+            sl = sl / (float)(uint32_t)dc;
             mine = __float_as_uint(sl);
         }
     }
@@ -959,46 +952,61 @@ __device__ __forceinline__ Step best_step_kept(const Ctx &X, const TailJob &T, u
     return out;
 }
 
-// A barrier that orders LDS only: loads from memory that are on their way stay there.
+// A barrier that orders LDS only.
 __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// LDS words tail_run needs beside its per-job scratch: what every wavefront offers, in two copies used in turn, and the
-// CPU levels.
-struct TailOffer { uint32_t slope, job, dg, dc, bound, bound_job; };
-constexpr int tail_red_words(int threads) { return (2 * (threads / 64) * (int)sizeof(TailOffer) + RK_MAX_CPU_LEVELS * 4) / 8; }
+// The list that the first wavefront works on, a job per lane: the jobs, their cached steps, the steps behind those (next_tgt
+// TAIL_NONE: not known), how many amounts they have, and per wavefront the best step that is not in the list; and what the
+// first wavefront leaves for the others.
+constexpr uint32_t TAIL_LIST = 64, TAIL_PER = 4, TAIL_NONE = 0xFFFFFFFFu;
+struct TailShared {
+    unsigned long long free_g, free_c, best, moved;
+    float slope[TAIL_LIST], next_slope[TAIL_LIST], ref[TAIL_LIST];
+    uint32_t job[TAIL_LIST], dg[TAIL_LIST], dc[TAIL_LIST], next_tgt[TAIL_LIST], next_dg[TAIL_LIST], next_dc[TAIL_LIST], ns[TAIL_LIST];
+    uint32_t rest[TAIL_THREADS / 64], rest_job[TAIL_THREADS / 64], lvl[RK_MAX_CPU_LEVELS], what;
+};
+enum { TAIL_END = 0, TAIL_LOOK = 1, TAIL_SEARCH = 2 };
+// dynamic LDS of tail_run: 8 bytes per job, then values and GPUs of the list's amounts
+__host__ __device__ constexpr size_t tail_scratch_bytes(uint32_t max_jobs) { return ((size_t)max_jobs * 8 + 15) & ~(size_t)15; }
+__host__ __device__ constexpr size_t tail_lds_bytes(uint32_t max_jobs) { return tail_scratch_bytes(max_jobs) + TAIL_LIST * 64 * 8; }
 
-// Workgroup of T threads; lds = max_jobs * 12 bytes of scratch, red =
-// tail_red_words(T) words; at most KMAX * T jobs.  Starts from the
-// state k_apply / apply_job left in st.  Thread t owns jobs t, t +
-// T, ...: their cached steps stay in its registers, and only it
-// (and, for the winner's new search, its wavefront) touches their LDS entries.
+// Workgroup of T threads; lds = tail_lds_bytes(max_jobs) of scratch; at most KMAX * T jobs.  Starts from the state k_apply /
+// apply_job left in st.  A thread owns every T-th job, whose cached steps stay in its registers.
 //
-// A step is a chain that nothing else hides, so what counts is its length: one
-// barrier, of LDS alone (every wavefront offers its best step with its costs,
-// and each finds the best offer for itself); a wavefront looks through its jobs
-// again only when its best step was taken or no longer fits; and what it needs
-// to find its best job's next step is on its way before that job wins (without
-// this 65 us instead of 56 for 256 rounds of 500 jobs, the CPU and GPU passes
-// of the selection; 31 instead of 29 for 10,000 jobs, where the nine turns are
-// mostly looks through all jobs).
+// A step is a chain that nothing else hides, so what counts is its length.  The wavefronts find the jobs with the best steps
+// together, TAIL_PER each, the steps behind those, and lay the jobs' amounts into LDS; the first wavefront then takes steps from
+// this list by itself, a job per lane, without barriers, for as long as the best of the list comes before everything that is
+// not in it.  Which steps are in the list does not change the result: a step that is not among the best of its wavefront ends
+// the list's turn before it could have been taken.  28 steps of 3,333 jobs 70 -> 28 us, 10 steps and 5 bounds of 10,000
+// jobs 39 -> 18 us; before, every step was a turn of all wavefronts: an offer of each, a barrier, and a look of the
+// winner's through its registers (2.3 us a step).  A list costs about 3 us, so a round of 500 or 1,000 jobs with one or two
+// steps here takes up to 2 us longer than it did, with forty of them 37 less.
+// Neighbours of jobs that are all alike come first one after the other: in rounds of up to 2,048 jobs, where the loads are few,
+// a wavefront has only TAIL_PER neighbours each, and all of them are in one list (250 steps of 1,000 such jobs 141 us instead of
+// 415; 364 before); 10,000 jobs read that way take 6 us more.
 template <int PASS, int KMAX, int T>
 __device__ __forceinline__ void tail_run(const Ctx &X, const JobState &st, uint32_t rnd, uint32_t J0, uint32_t J1,
                                          unsigned long long freeG, unsigned long long freeC, uint32_t max_jobs,
-                                         float *lds, unsigned long long *red) {
-    uint16_t *tgt = reinterpret_cast<uint16_t *>(lds);             // target of the cached step (segment index or CPU level)
+                                         void *lds, TailShared &S) {
+    constexpr uint32_t WAVES = T / 64, PER = TAIL_PER, NONE = TAIL_NONE;
+    constexpr uint32_t MANY = 8;                                   // bounds that lists make exact one by one
+    static_assert(WAVES <= 16 && PER * WAVES <= TAIL_LIST, "lists of whole wavefronts");
+    uint16_t *tgt = static_cast<uint16_t *>(lds);                  // target of the cached step (segment index or CPU level)
     int16_t *gi = reinterpret_cast<int16_t *>(tgt + max_jobs);     // granted segment index, -1 = none
     uint16_t *ci = reinterpret_cast<uint16_t *>(gi + max_jobs);    // granted CPU level
-    uint16_t *gh = ci + max_jobs;                                  // GPUs held (CPU pass); GPUs of a new step (GPU pass)
-    float *found = reinterpret_cast<float *>(gh + max_jobs);       // slope of a new step on its way to the registers
-    TailOffer *offers = reinterpret_cast<TailOffer *>(red);
-    uint32_t *lvl = reinterpret_cast<uint32_t *>(offers + 2 * (T / 64));   // CPU levels, for indexing by lane
+    uint16_t *gh = ci + max_jobs;                                  // GPUs held (CPU pass)
+    float *const amount_v = reinterpret_cast<float *>(static_cast<unsigned char *>(lds) + tail_scratch_bytes(max_jobs));
+    uint32_t *const amount_g = reinterpret_cast<uint32_t *>(amount_v + TAIL_LIST * 64);
+    uint32_t *const lvl = S.lvl;                                   // CPU levels, for indexing by lane
 
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     const uint32_t nj = J1 - J0, jrel0 = J0 - X.jb;
+    // the thread's first job: jobs of a wavefront are PER neighbours each where that costs no more loads to speak of
+    const uint32_t own = KMAX <= 2 ? (lane / PER * WAVES + wave) * PER + lane % PER : tid;
     const GridDev &grid = X.grid;
 
     // CPUs a step costs (saturated to 32 bits: the free CPUs fit in 32)
@@ -1026,7 +1034,7 @@ __device__ __forceinline__ void tail_run(const Ctx &X, const JobState &st, uint3
         uint32_t c_i[KMAX], target[KMAX], gpus[KMAX];
 #pragma unroll
         for (int k = 0; k < KMAX; ++k) {                           // all loads go out before the first is used
-            const uint32_t jl = tid + (uint32_t)k * T;
+            const uint32_t jl = own + (uint32_t)k * T;
             const uint32_t at = jrel0 + (jl < nj ? jl : nj - 1u);
             g_i[k] = st.gi[at];
             c_i[k] = st.ci[at];
@@ -1037,7 +1045,7 @@ __device__ __forceinline__ void tail_run(const Ctx &X, const JobState &st, uint3
         __syncthreads();                                           // the levels are in LDS
 #pragma unroll
         for (int k = 0; k < KMAX; ++k) {
-            const uint32_t jl = tid + (uint32_t)k * T;
+            const uint32_t jl = own + (uint32_t)k * T;
             const bool have = jl < nj;
             const uint32_t need = need_cpus(g_i[k], c_i[k], target[k], gpus[k]);
             slope[k] = have ? slope[k] : 0.f;
@@ -1055,151 +1063,224 @@ __device__ __forceinline__ void tail_run(const Ctx &X, const JobState &st, uint3
     // A cached step that stops fitting is not searched anew at once: it is
     // kept, negated, as an upper bound of whatever the job can still do (the
     // job's state is unchanged and the capacity only shrank).  A step is
-    // taken when the best exact entry beats every such bound under the tie
-    // rule (lower job index first); bounds that could win are made exact
-    // first, all of them in one go.
+    // taken when it comes before every other step and every such bound under
+    // the tie rule (lower job index first); a bound that comes first is made
+    // exact.
     auto key_of = [](float v, uint32_t jl) -> unsigned long long {
         return ((unsigned long long)__float_as_uint(v) << 32) | (0xFFFFFFFFu - jl);
     };
-    uint32_t turn = 0, moved = 0;                               // moved: bit k = the thread's k-th job took a step here
+    auto one = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); };
+    auto room = [&](unsigned long long x) { return one(x > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)x); };
+    uint32_t asked = 0;                                         // (the first wavefront's) bounds made exact one by one
+    uint32_t moved = 0;                                         // bit k = the thread's k-th job took a step here
     const uint32_t n_mem = grid.n_mem, n_rows = grid.n_cpu * n_mem, first_seg = X.tb.seg_off[X.jb];
-    TailJob kept = {~0u, 0u, 0.f, 1.f};
-    uint32_t seen = ~0u, seg_lo = 0, seg_hi = 0, kept_ns = 0;   // the job last looked up and where its GPU counts are
-    bool asked = false;
-    // The thread's best exact step and best bound, and the wavefront's: they stand until the step no longer fits, or a job
-    // of theirs took a step or was searched anew (a step that stops fitting below the thread's best one is not missed: as
-    // a bound it would be below that one too).
-    float vf = 0.f, vs = 0.f;
-    uint32_t jf = 0, js = 0, df = 0, cf = 0;
-    uint32_t mf = 0, ms = 0, jm = 0, jb = 0, dgm = 0, dcm = 0;
-    bool stale = true;
-    for (;;) {
+    // (no job has a step, as in most CPU passes of small rounds: asked once, since a list says whether there is more)
+    const bool none = KMAX == 1 && __syncthreads_or(slope[0] > 0.f) == 0;
+    while (!none) {
         if (PASS == 0 ? freeG == 0 : freeC == 0) break;         // nothing can fit any more
-        const uint32_t roomG = freeG > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)freeG;
-        const uint32_t roomC = freeC > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)freeC;
-        stale = stale || (vf > 0.f && ((PASS == 0 && df > roomG) || cf > roomC));
-        if (__ballot(stale)) {
-            // plain float compares (a thread's jobs come in rising order, so the first of equal slopes is the lower job)
-            vf = 0.f; vs = 0.f;
-            jf = 0; js = 0; df = 0; cf = 0;
+        const uint32_t roomG = room(freeG), roomC = room(freeC);
+        // ---- the thread's best step or bound and its second (a thread's jobs come in rising order, so the first of equal
+        // slopes is the lower job)
+        float a1 = 0.f, a2 = 0.f;
+        uint32_t k1 = 0, k2 = 0;
 #pragma unroll
-            for (int k = 0; k < KMAX; ++k) {
-                const uint32_t jl = tid + (uint32_t)k * T;
-                float v = slope[k];
-                const bool stopped = v > 0.f && ((PASS == 0 && dg[k] > roomG) || dc[k] > roomC);
-                v = stopped ? -v : v;
-                slope[k] = v;
-                if (v > vf) { vf = v; jf = jl; df = dg[k]; cf = dc[k]; }
-                if (-v > vs) { vs = -v; js = jl; }
-            }
-            stale = false;
-            // word by word: the wavefront's highest slope, then the lowest job among those that have it
-            const uint32_t bf = __float_as_uint(vf), bs = __float_as_uint(vs);
-            mf = wave_max_u32_rows(bf);
-            ms = wave_max_u32_rows(bs);
-            if (mf) {
-                jm = wave_min_u32_rows(bf == mf ? jf : 0xFFFFFFFFu);
-                const uint32_t at = jm & 63u;                   // (thread t owns jobs t + k * T: a multiple of 64)
-                dgm = wave_lane_u32(df, at);
-                dcm = wave_lane_u32(cf, at);
-            }
-            if (ms) jb = wave_min_u32_rows(bs == ms ? js : 0xFFFFFFFFu);
+        for (int k = 0; k < KMAX; ++k) {
+            const float v = slope[k], a = fabsf(v);
+            if (v > 0.f && ((PASS == 0 && dg[k] > roomG) || dc[k] > roomC)) slope[k] = -v;
+            if (a > a1) { a2 = a1; k2 = k1; a1 = a; k1 = (uint32_t)k; }
+            else if (a > a2) { a2 = a; k2 = (uint32_t)k; }
         }
-        turn ^= 1u;
-        if (lane == 0) offers[turn * (T / 64) + wave] = TailOffer{mf, jm, dgm, dcm, ms, jb};
-        // What this wavefront will need should its best job win: where the job's counts are and, a turn later (in the first
-        // turn at once), amounts and values.  Nothing waits for the loads here: they are made by all lanes, even of what is
-        // the same for all, so that what comes through LDS does not wait for them, and the barrier is one for LDS alone.
-        if (mf && seen != jm) {
-            uint32_t slot = J0 + jm;
-            asm volatile("" : "+v"(slot));
-            slot = job_of(X, slot);
-            kept.ref = X.ref_thr[slot];
-            kept.jl = ~0u;
-            asked = seen == ~0u;
-            seg_lo = X.tb.seg_off[slot];
-            seg_hi = X.tb.seg_off[slot + 1];
-            seen = jm;
-        } else {
-            asked = mf != 0u && kept.jl == ~0u;
+        // ---- the wavefront's best, word by word: the highest slope, then the lowest job among those that have it
+        const uint32_t j1 = own + k1 * T;
+        uint32_t mine = NONE, job = NONE;                       // the thread's place in the list; lane p: the job of place p
+        uint32_t left = __float_as_uint(a1);
+#pragma unroll
+        for (uint32_t p = 0; p < PER; ++p) {
+            const uint32_t top = wave_max_u32_rows(left);
+            if (!top) break;
+            const uint32_t jm = wave_min_u32_rows(left == top ? j1 : NONE);
+            if (left == top && j1 == jm) { mine = wave * PER + p; left = 0u; }
+            if (lane == p) job = jm;
         }
-        if (asked) {
-            const uint32_t s0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)seg_lo);
-            const uint32_t ns = (uint32_t)__builtin_amdgcn_readfirstlane((int)(seg_hi - seg_lo));
-            if (ns <= 64u || PASS == 1) {
-                const uint64_t base = (uint64_t)n_rows * (s0 - first_seg);
-                kept.jl = jm;
-                kept_ns = ns;
+        {
+            const uint32_t r = mine == NONE ? left : __float_as_uint(a2), rj = own + (mine == NONE ? k1 : k2) * T;
+            const uint32_t top = wave_max_u32_rows(r);
+            const uint32_t jm = top ? wave_min_u32_rows(r == top ? rj : NONE) : NONE;
+            if (lane == 0) { S.rest[wave] = top; S.rest_job[wave] = jm; }
+        }
+        if (mine != NONE) {
+#pragma unroll
+            for (int k = 0; k < KMAX; ++k)
+                if ((uint32_t)k == k1) { S.slope[mine] = slope[k]; S.dg[mine] = dg[k]; S.dc[mine] = dc[k]; }
+        }
+        // ---- their amounts go into LDS
+        rs_wave_order();
+        uint32_t s0 = 0, ns = 0, row = 0, to = 0, held = 0, step_g = 0, step_c = 0;
+        float ref = 1.f, step = 0.f;
+        if (job != NONE) {
+            const uint32_t slot = job_of(X, J0 + job);
+            ref = X.ref_thr[slot];
+            s0 = X.tb.seg_off[slot];
+            ns = X.tb.seg_off[slot + 1] - s0;
+            row = PASS == 0 ? (uint32_t)ci[job] : (uint32_t)(int32_t)gi[job];
+            S.ref[wave * PER + lane] = ref;
+            to = tgt[job];
+            held = PASS == 1 ? gh[job] : 0u;
+            step = S.slope[wave * PER + lane]; step_g = S.dg[wave * PER + lane]; step_c = S.dc[wave * PER + lane];
+        }
+        if (lane < PER) { S.job[wave * PER + lane] = job; S.ns[wave * PER + lane] = ns; }
+        {
+            float v[PER];
+            uint32_t g[PER];
+#pragma unroll
+            for (uint32_t p = 0; p < PER; ++p) {
+                const uint32_t n = wave_lane_u32(ns, p), s = wave_lane_u32(s0, p), r = wave_lane_u32(row, p);
+                v[p] = 0.f; g[p] = 0u;
+                if (n == 0u) continue;
+                const uint64_t base = (uint64_t)n_rows * (s - first_seg);
                 if (PASS == 0) {
-                    const uint32_t s = lane < ns ? lane : ns - 1u;
-                    kept.g = X.tb.seg_g[s0 + s];
-                    kept.v = X.curve_thr[base + (uint64_t)(ci[jm] * n_mem + n_mem - 1u) * ns + s];
+                    const uint32_t i = lane < n ? lane : n - 1u;
+                    g[p] = X.tb.seg_g[s + i];
+                    v[p] = X.curve_thr[base + (uint64_t)(r * n_mem + n_mem - 1u) * n + i];
                 } else {
                     const uint32_t c = lane < grid.n_cpu ? lane : grid.n_cpu - 1u;
-                    kept.v = X.best_thr[base + (uint64_t)(c * n_mem + n_mem - 1u) * ns + (uint32_t)gi[jm]];
+                    v[p] = X.best_thr[base + (uint64_t)(c * n_mem + n_mem - 1u) * n + r];
                 }
+            }
+#pragma unroll
+            for (uint32_t p = 0; p < PER; ++p) {
+                amount_v[(wave * PER + p) * 64u + lane] = v[p];
+                if (PASS == 0) amount_g[(wave * PER + p) * 64u + lane] = g[p];
+            }
+            // The step behind a job's step, as if it were the next one taken: a step that others' leave no room for is a bound
+            // like any other (one that still fits then is the best that fits).
+            float next = 0.f;
+            uint32_t next_tgt = NONE, next_g = 0, next_c = 0;
+#pragma unroll
+            for (uint32_t p = 0; p < PER; ++p) {
+                const uint32_t n = wave_lane_u32(ns, p), dg_p = wave_lane_u32(step_g, p), dc_p = wave_lane_u32(step_c, p);
+                if (!((int32_t)wave_lane_u32(__float_as_uint(step), p) > 0) || dg_p > roomG || dc_p > roomC || (PASS == 0 && n > 64u)) continue;
+                const uint32_t to_p = wave_lane_u32(to, p), held_p = wave_lane_u32(held, p);
+                const uint32_t level = PASS == 0 ? wave_lane_u32(row, p) : to_p;
+                const Step nx = best_step_listed<PASS>(grid, lvl, v[p], g[p], __uint_as_float(wave_lane_u32(__float_as_uint(ref), p)), (int32_t)to_p,
+                                                       PASS == 0 ? n : grid.n_cpu, held_p, level, roomG - dg_p, roomC - dc_p);
+                if (lane == p) {
+                    next = nx.slope > 0.f ? nx.slope : 0.f; next_tgt = nx.tgt; next_g = nx.dg;     // (not a number: none)
+                    next_c = need_cpus((int32_t)to_p, level, nx.tgt, PASS == 0 ? nx.dg : held_p);
+                }
+            }
+            if (lane < PER) {
+                const uint32_t e = wave * PER + lane;
+                S.next_slope[e] = next; S.next_tgt[e] = next_tgt; S.next_dg[e] = next_g; S.next_dc[e] = next_c;
             }
         }
         lds_barrier();
-        const TailOffer o = offers[turn * (T / 64) + (lane & ((T / 64) - 1))];   // every row of 16 lanes has all of them
-        const uint32_t top = (uint32_t)__builtin_amdgcn_readfirstlane((int)row_max_u32(o.slope));
-        const uint32_t jw = (uint32_t)__builtin_amdgcn_readfirstlane((int)row_min_u32(o.slope == top ? o.job : 0xFFFFFFFFu));
-        const uint32_t bound = (uint32_t)__builtin_amdgcn_readfirstlane((int)row_max_u32(o.bound));
-        const uint32_t jbound = (uint32_t)__builtin_amdgcn_readfirstlane((int)row_min_u32(o.bound == bound ? o.bound_job : 0xFFFFFFFFu));
-        if (bound && (bound > top || (bound == top && jbound < jw))) {   // a bound could still win: make those exact
-            const unsigned long long kf = top ? key_of(__uint_as_float(top), jw) : 0ull;
+        // ---- the first wavefront takes steps from the list
+        if (wave == 0) {
+            const uint32_t jl = lane < PER * WAVES ? S.job[lane] : NONE, n_l = S.ns[lane];
+            const bool have = jl != NONE;
+            float v = have ? S.slope[lane] : 0.f;
+            const float ref_l = have ? S.ref[lane] : 1.f, next_v = S.next_slope[lane];
+            uint32_t d = have ? S.dg[lane] : 0u, c = have ? S.dc[lane] : 0u, t = have ? tgt[jl] : 0u, c_l = have ? ci[jl] : 0u;
+            const uint32_t held_l = PASS == 1 && have ? gh[jl] : 0u, next_d = S.next_dg[lane], next_c = S.next_dc[lane];
+            uint32_t next_t = S.next_tgt[lane];
+            int32_t g_l = have ? gi[jl] : -1;
+            const uint32_t r = lane < WAVES ? S.rest[lane] : 0u, rest = wave_max_u32_rows(r);
+            const uint32_t rest_job = wave_min_u32_rows(lane < WAVES && r == rest ? S.rest_job[lane] : NONE);
+            uint32_t what = TAIL_END, fg = roomG, fc = roomC;     // (what is free fits in 32 bits)
+            bool took = false;
+            for (;;) {
+                if (PASS == 0 ? fg == 0u : fc == 0u) break;
+                if (v > 0.f && ((PASS == 0 && d > fg) || c > fc)) v = -v;
+                const uint32_t bits = __float_as_uint(fabsf(v)), top = wave_max_u32_rows(bits);
+                if (!top) { what = rest ? TAIL_LOOK : TAIL_END; break; }
+                const unsigned long long tops = __ballot(bits == top);
+                uint32_t w = (uint32_t)__ffsll((long long)tops) - 1u, jw = wave_lane_u32(jl, w);
+                if (tops & (tops - 1ull)) {                      // several have it: the lowest job
+                    jw = wave_min_u32_rows(bits == top ? jl : NONE);
+                    w = (uint32_t)__ffsll((long long)__ballot(bits == top && jl == jw)) - 1u;
+                }
+                if (top < rest || (top == rest && rest_job < jw)) { what = TAIL_LOOK; break; }
+                const bool exact = (int32_t)wave_lane_u32(__float_as_uint(v), w) > 0;
+                if (exact) {
+                    if (PASS == 0) fg -= wave_lane_u32(d, w);
+                    fc -= wave_lane_u32(c, w);
+                    const bool known = wave_lane_u32(next_t, w) != NONE;
+                    if (lane == w) {
+                        took = true;
+                        if (PASS == 0) g_l = (int32_t)t; else c_l = t;
+                        v = next_v; t = next_t; d = next_d; c = next_c;
+                        next_t = NONE;
+                    }
+                    if (known) continue;
+                } else {                                         // a bound: are there others before the best exact step?
+                    const uint32_t best = wave_max_u32_rows(v > 0.f ? bits : 0u);
+                    if (__popcll(__ballot(v < 0.f && bits > best)) > 2 || ++asked > MANY) {
+                        what = TAIL_SEARCH;
+                        asked = 0;
+                        break;
+                    }
+                }
+                const int32_t g_w = (int32_t)wave_lane_u32((uint32_t)g_l, w);
+                const uint32_t c_w = wave_lane_u32(c_l, w), held_w = PASS == 1 ? wave_lane_u32(held_l, w) : 0u, n = wave_lane_u32(n_l, w);
+                Step nx;
+                if (PASS == 1 || n <= 64u)
+                    nx = best_step_listed<PASS>(grid, lvl, amount_v[w * 64u + lane], PASS == 0 ? amount_g[w * 64u + lane] : 0u,
+                                                __uint_as_float(wave_lane_u32(__float_as_uint(ref_l), w)), PASS == 0 ? g_w : (int32_t)c_w,
+                                                PASS == 0 ? n : grid.n_cpu, held_w, c_w, fg, fc);
+                else
+                    nx = best_step_wave<PASS>(X, J0 + jw, g_w, held_w, c_w, fg, fc);
+                if (lane == w) {
+                    t = nx.tgt;
+                    v = nx.slope > 0.f ? nx.slope : 0.f; d = nx.dg;             // (not a number: none)
+                    c = need_cpus(g_w, c_w, nx.tgt, PASS == 0 ? nx.dg : held_w);
+                }
+            }
+            freeG = PASS == 0 ? fg : freeG; freeC = fc;
+            if (have) {
+                S.slope[lane] = v; S.dg[lane] = d; S.dc[lane] = c;
+                tgt[jl] = (uint16_t)t; gi[jl] = (int16_t)g_l; ci[jl] = (uint16_t)c_l;
+            }
+            unsigned long long best = 0;
+            if (what == TAIL_SEARCH) {                           // the list's best exact step
+                const uint32_t bits = v > 0.f ? __float_as_uint(v) : 0u, top = wave_max_u32_rows(bits);
+                if (top) best = key_of(__uint_as_float(top), wave_min_u32_rows(bits == top ? jl : NONE));
+            }
+            const unsigned long long m = __ballot(took);
+            if (lane == 0) { S.free_g = freeG; S.free_c = freeC; S.best = best; S.moved = m; S.what = what; }
+        }
+        lds_barrier();
+        freeG = S.free_g; freeC = S.free_c;
+        const uint32_t what = S.what;
+        if (mine != NONE) {
+            if ((S.moved >> mine) & 1ull) moved |= 1u << k1;
+#pragma unroll
+            for (int k = 0; k < KMAX; ++k)
+                if ((uint32_t)k == k1) { slope[k] = S.slope[mine]; dg[k] = S.dg[mine]; dc[k] = S.dc[mine]; }
+        }
+        if (what == TAIL_END) break;
+        if (what == TAIL_SEARCH) {                              // many bounds could win: their threads make all of those exact
+            const unsigned long long best = S.best;
             uint32_t todo = 0;
 #pragma unroll
             for (int k = 0; k < KMAX; ++k) {
                 const float v = slope[k];
-                if (v < 0.f && key_of(-v, tid + (uint32_t)k * T) > kf) todo |= 1u << k;
+                if (v < 0.f && key_of(-v, own + (uint32_t)k * T) > best) todo |= 1u << k;
             }
-            // the searches go through LDS so that the register arrays are only ever indexed by constants
-            for (uint32_t rest = todo; rest; rest &= rest - 1u) {
-                const uint32_t jl = tid + ((uint32_t)__ffs((int)rest) - 1u) * T;
-                const Step nx = best_step<PASS>(X, J0 + jl, gi[jl], PASS == 0 ? 0u : gh[jl], ci[jl], freeG, freeC);
-                found[jl] = nx.slope;
+            for (; todo; todo &= todo - 1u) {                   // (the register arrays are only ever indexed by constants)
+                const uint32_t at = (uint32_t)__ffs((int)todo) - 1u, jl = own + at * T;
+                const uint32_t held = PASS == 0 ? 0u : gh[jl];
+                const Step nx = best_step<PASS>(X, J0 + jl, gi[jl], held, ci[jl], freeG, freeC);
+                const uint32_t need = need_cpus(gi[jl], ci[jl], nx.tgt, PASS == 0 ? nx.dg : held);
                 tgt[jl] = (uint16_t)nx.tgt;
-                if (PASS == 0) gh[jl] = (uint16_t)nx.dg;
-            }
-#pragma unroll
-            for (int k = 0; k < KMAX; ++k) {
-                if (todo >> k & 1u) {
-                    const uint32_t jl = tid + (uint32_t)k * T;
-                    slope[k] = found[jl];
-                    if (PASS == 0) dg[k] = gh[jl];
-                    dc[k] = need_cpus(gi[jl], ci[jl], tgt[jl], gh[jl]);
-                }
-            }
-            stale = todo != 0u;
-            continue;
-        }
-        if (!top) break;                                        // no positive slope left
-        const uint32_t owner = jw % T, kw = jw / T;
-        const uint32_t won = owner / 64u;                       // the wavefront whose offer it was
-        if (PASS == 0) freeG -= wave_lane_u32(o.dg, won);
-        freeC -= wave_lane_u32(o.dc, won);
-        if (wave == won) {                                      // ... finds the winner's next step
-            int32_t g_i = gi[jw];
-            uint32_t c_i = ci[jw];
-            if (PASS == 0) g_i = (int32_t)tgt[jw]; else c_i = tgt[jw];
-            const uint32_t held = PASS == 0 ? 0u : gh[jw];
-            const Step nx = kept.jl == jw ? best_step_kept<PASS>(X, kept, PASS == 0 ? (uint32_t)g_i : c_i, kept_ns, held, c_i, freeG, freeC)
-                                          : best_step_wave<PASS>(X, J0 + jw, g_i, held, c_i, freeG, freeC);
-            if (tid == owner) {
-                if (PASS == 0) gi[jw] = (int16_t)g_i; else ci[jw] = (uint16_t)c_i;
-                moved |= 1u << kw;
-                stale = true;
-                tgt[jw] = (uint16_t)nx.tgt;
-                const uint32_t need = need_cpus(g_i, c_i, nx.tgt, PASS == 0 ? nx.dg : held);
 #pragma unroll
                 for (int k = 0; k < KMAX; ++k)
-                    if ((uint32_t)k == kw) { slope[k] = nx.slope; dg[k] = PASS == 0 ? nx.dg : 0u; dc[k] = need; }
+                    if ((uint32_t)k == at) { slope[k] = nx.slope; dg[k] = PASS == 0 ? nx.dg : 0u; dc[k] = need; }
             }
         }
     }
     for (; moved; moved &= moved - 1u) {                        // only the jobs that took a step here changed since k_apply
-        const uint32_t jl = tid + ((uint32_t)__ffs((int)moved) - 1u) * T;
+        const uint32_t jl = own + ((uint32_t)__ffs((int)moved) - 1u) * T;
         if (PASS == 0) {
             const int32_t s_i = gi[jl];
             st.gi[jrel0 + jl] = s_i;
@@ -1215,14 +1296,14 @@ constexpr int TAIL_KMAX = (RK_MAX_JOBS_PER_ROUND + TAIL_THREADS - 1) / TAIL_THRE
 
 template <int PASS>
 __global__ __launch_bounds__(TAIL_THREADS) void k_tail(Ctx X, uint32_t max_jobs, JobState st) {
-    extern __shared__ float lds_dyn[];
-    __shared__ unsigned long long red[tail_red_words(TAIL_THREADS)];
+    extern __shared__ uint4 lds_dyn[];
+    __shared__ TailShared shared;
     const uint32_t rnd = blockIdx.x;
     if (PASS == 1 && st.cpu_steps[rnd] == 0u) return;       // empty pass
     uint32_t J0, J1;
     rk_cluster cl;
     round_of(X.R, rnd, J0, J1, cl);
-    tail_run<PASS, TAIL_KMAX, TAIL_THREADS>(X, st, rnd, J0, J1, st.free_g[rnd], st.free_g[X.R.n_rounds + rnd], max_jobs, lds_dyn, red);
+    tail_run<PASS, TAIL_KMAX, TAIL_THREADS>(X, st, rnd, J0, J1, st.free_g[rnd], st.free_g[X.R.n_rounds + rnd], max_jobs, lds_dyn, shared);
 }
 
 // ------------------------------------------------------------------ selection of a pass in one workgroup
@@ -1234,7 +1315,7 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_tail(Ctx X, uint32_t max_jobs,
 // (KMAX = TAIL_KMAX, without the memory step) as long as all CPU walks together
 // are short, which the host can tell from the grid:
 // (CPU levels - 1) * jobs <= CPU_ONE_WG_STEPS.
-// The histogram (48 KiB) and the tail's scratch (12 bytes per job) share the
+// The histogram (48 KiB) and the tail's scratch share the
 // dynamic LDS: the tail starts when the threshold is known.
 constexpr uint32_t SMALL_ROUND_JOBS = 2048;
 constexpr uint64_t CPU_ONE_WG_STEPS = 65536;
@@ -1252,7 +1333,7 @@ __global__ __launch_bounds__(T) void k_select_small(Ctx X, uint32_t max_jobs, Jo
     unsigned long long *hc = lds_sel;                           // one histogram, used for level 0 and then level 1
     uint32_t *hg = reinterpret_cast<uint32_t *>(hc + BINS);
     __shared__ CutScratch cs;
-    __shared__ unsigned long long red[tail_red_words(T)];
+    __shared__ TailShared shared;
     __shared__ double sums[2 * (T / 64)];
     const uint32_t rnd = blockIdx.x, tid = threadIdx.x;
     uint32_t J0, J1;
@@ -1309,7 +1390,7 @@ __global__ __launch_bounds__(T) void k_select_small(Ctx X, uint32_t max_jobs, Jo
         }
         __syncthreads();                                        // the state in st is read back by the whole workgroup; the
                                                                 // histogram's LDS passes to the tail
-        tail_run<PASS, KMAX, T>(X, st, rnd, J0, J1, sel.freeG, sel.freeC, max_jobs, reinterpret_cast<float *>(lds_sel), red);
+        tail_run<PASS, KMAX, T>(X, st, rnd, J0, J1, sel.freeG, sel.freeC, max_jobs, lds_sel, shared);
     }
     if (PASS == 0 || KMAX == TAIL_KMAX) return;                 // (large rounds: a thread per job does it faster, k_mem_wish)
     // memory: every thread writes the wishes of its jobs, the first wavefront closes the round
@@ -3357,7 +3438,7 @@ int32_t rk_launch_allocate(rk_ctx *ctx, const float *ref_thr, const TableDev &tb
     X.R.cl = one_cluster ? *one_cluster : rk_cluster{0u, 0u, 0.f};
 
     const uint32_t mj = max_jobs ? ((max_jobs + 1u) & ~1u) : 2u;
-    const size_t lds = (size_t)mj * (2 + 2 + 2 + 2 + 4);
+    const size_t lds = tail_lds_bytes(mj);
     // (the kernels' dynamic LDS limits were raised when the context was made: rk_allocate_setup)
     hipStream_t s = ctx->stream;
     // Histograms start at zero: the first walk kernel clears them for both passes on its way (fill code, no

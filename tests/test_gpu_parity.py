@@ -364,6 +364,46 @@ def test_allocate_many_jobs_random_curves(gpu, orc, n_jobs, n_cpu):
     run.close()
 
 
+@pytest.mark.parametrize("n_jobs", [511, 512, 513, 1024, 1025, 2048, 2049, 6000])
+@pytest.mark.parametrize("alike", [0, 1])
+def test_allocate_steps_taken_from_lists(gpu, orc, n_jobs, alike):
+    """What the threshold leaves is taken step by step from lists of 64 jobs, at the sizes where a job more or less is another
+    workgroup or another job per thread.  Jobs that are all alike leave everything to the lists (equal slopes are cut
+    together): a list then ends after the few of its jobs that one wavefront has, and once fewer GPUs are left than the step
+    that all want, more steps than a list searches anew no longer fit.  With jobs drawn from coarse values steps of one job
+    follow on each other, beyond the one that a list knows beforehand."""
+    import paper_2408_08586_amd as rk
+    rng = np.random.default_rng(n_jobs)
+    base = workloads.stress(n_jobs=n_jobs)
+    ints = np.tile(np.array([[24, 64, 1]], np.uint32), (n_jobs, 1)) if alike else base.ints
+    coef = base.coef.copy()
+    coef[:, 16] = 1.0 if alike else rng.choice([0.5, 1.0, 2.0], n_jobs)
+    grid = workloads.Grid(np.arange(1, 7, dtype=np.uint32), base.grid.cpu_mode, base.grid.mem_levels_gb, base.grid.mem_mode)
+    wl = workloads.Workload("lists", coef, ints, workloads.Bounds(g_max=64), grid, base.env, workloads.Cluster(4096, 30000, 1.0e9))
+    ot = orc.enumerate_plans(wl.ints, wl.bounds)
+    n_rows = 6 * len(grid.mem_levels_gb)
+    seg_g = [ot.seg_g[ot.seg_off[j]:ot.seg_off[j + 1]] for j in range(n_jobs)]
+    if alike:                                              # 8 GPUs at once are worth most per GPU, then 1, and one level more each
+        per_row = [np.where(g >= 8, 64.0, g * 0.5) + lvl for g in seg_g[:1] for lvl in np.repeat(np.arange(6), len(grid.mem_levels_gb))]
+        bt = np.tile(np.concatenate(per_row), n_jobs)
+    else:
+        g_of = np.concatenate([np.tile(g, n_rows) for g in seg_g])
+        bt = np.round(g_of ** rng.uniform(0.5, 0.9, len(g_of)) * 2) / 2
+    bt = bt.astype(np.float32)
+    bp = rng.integers(0, 1000, len(bt)).astype(np.uint32)
+    ct, _, _ = orc.curves(ot, wl.grid, bt, bp)
+    run = gpu(wl)
+    run.enumerate()
+    d_bt, d_bp, d_ct = run.dev_f32(bt), run.dev_u32(bp), run.dev_f32(ct)
+    for G, Cc in ((8 * 40 + 5, 10 ** 6), (8 * 40 + 5, 700), (57, 300), (3, 3), (1 << 20, 8 * n_jobs + 77)):
+        cl = workloads.Cluster(G, Cc, 1.0e9)
+        e_assign, e_total, _ = orc.greedy(wl.coef[:, 16], ot, wl.grid, cl, bt, bp, ct)
+        assign, total = run.allocate(d_bt, d_bp, d_ct, cluster=rk.make_cluster(cl))
+        assert np.array_equal(assign, e_assign), (G, Cc)
+        assert total == pytest.approx(e_total, rel=1e-6)
+    run.close()
+
+
 @pytest.mark.parametrize("g_max", [128, 1024])
 def test_allocate_jobs_with_many_gpu_counts(gpu, orc, g_max):
     """Jobs with more than 32 (one wavefront per job) and more than 64 valid GPU
