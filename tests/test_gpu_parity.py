@@ -1071,6 +1071,7 @@ def test_enumeration_around_the_listed_searches(gpu, orc, n, n_kinds):
         got = dict(triple_off=rk.u32(t.triple_off), triples=t.unpack_triples(), seg_off=rk.u32(t.seg_off),
                    seg_g=rk.u32(t.seg_g), seg_first=rk.u32(t.seg_first))
         oracle_table_equal(got, expected)
+        assert np.array_equal(t.h_triple_off, expected.triple_off) and np.array_equal(t.h_seg_off, expected.seg_off)
     run.close()
 
 
