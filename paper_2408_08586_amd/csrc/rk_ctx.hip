@@ -145,6 +145,11 @@ int32_t rk_ctx_ways(const rk_ctx *ctx, uint32_t *ways) {
     for (int i = 0; i < WAY_COUNT; ++i) ways[i] = ctx->ways[i];
     return WAY_COUNT;
 }
+int32_t rk_ctx_ways_eval(const rk_ctx *ctx, uint32_t *ways) {
+    if (!ctx || !ways) return 0;
+    for (int i = WAY_COUNT; i < WAY_ALL; ++i) ways[i - WAY_COUNT] = ctx->ways[i];
+    return WAY_ALL - WAY_COUNT;
+}
 
 const char *rk_last_error(const rk_ctx *ctx) { return ctx ? ctx->err : "null context"; }
 

@@ -11,11 +11,14 @@
 
 enum { RK_SCRATCH_SLOTS = 64 };
 
-// How often a context's calls went which way: for tests of the rules that choose (rk_ctx_ways, not in rubick.h).
+// How often a context's calls went which way: for tests of the rules that choose (rk_ctx_ways and, for those behind
+// WAY_COUNT, rk_ctx_ways_eval; not in rubick.h).
 enum { WAY_ROUND_AHEAD, WAY_ROUND_AHEAD_TAKEN,          // rounds sent before their table was known; those it was right for
        WAY_SIM_FEW, WAY_SIM_LAUNCHES, WAY_SIM_NODES,    // turns of a simulation's ticks: k_sim_few, launches, k_sim_nodes
        WAY_GREW,                                        // working buffers that were made or grew
-       WAY_COUNT };
+       WAY_COUNT,
+       WAY_EVAL_AHEAD = WAY_COUNT, WAY_EVAL_AHEAD_TAKEN, // rounds of which only the evaluation was sent; those it was right for
+       WAY_ALL };
 
 struct rk_ctx {
     int device;
@@ -32,7 +35,7 @@ struct rk_ctx {
     uint32_t seen_jobs;
     bool enum_clear;                        // enumeration: the device's counter of finished searches is known to be zero
     size_t enum_tab_clear;                  // ... and so many words of the leaders' table
-    uint32_t ways[WAY_COUNT];
+    uint32_t ways[WAY_ALL];
     hipEvent_t counts_ev;                   // enumeration: the counts have reached the host (made on demand)
     hipStream_t sim_stream;                 // simulation: its own stream (a tick is captured as a graph), made on demand
     hipEvent_t sim_ev[4];                   // ... ordered after and before the context's stream with the first two; its batches of ticks

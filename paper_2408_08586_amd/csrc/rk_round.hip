@@ -79,8 +79,8 @@ int32_t schedule_rounds(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_bounds *
     };
 
     // A round that takes one launch, with at most `most` GPU counts per job, may be sent before its table is known: the
-    // outputs' room is then most_s per job, and a round of the same kind that is not sent takes as much, so that buffers grow
-    // in the first call of a kind and not between the two halves of a later one's enumeration (66 us instead of 48).
+    // outputs' room is then `most` per job.  A round of that kind that is evaluated behind its enumeration takes as much, so that
+    // buffers grow in the first call of a kind and not between the two halves of a later one's enumeration (66 us instead of 48).
     auto may_go_ahead = [&](uint32_t most) {
         return n_rounds == 1 && !sla && !round_jobs && !keep && J > 0 && most <= 64u && rk_round_is_few(grid, J, most, &clusters[0], true);
     };
@@ -96,6 +96,9 @@ int32_t schedule_rounds(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_bounds *
     uint64_t cap_t = ctx->scratch_bytes[SL_TB_TRIPLES] / 4, cap_s = ctx->scratch_bytes[SL_TB_SEGG] / 4;
     if (cap_t < (uint64_t)J * 256) cap_t = (uint64_t)J * 256;
     if (cap_s < (uint64_t)J * 32) cap_s = (uint64_t)J * 32;
+    // the curves: what grows a buffer frees what was in it, so from the launch that writes them on these pointers stay
+    float *best_thr, *curve_thr;
+    uint32_t *best_plan, *curve_plan, *curve_g;
     bool evaluated = false;                                   // the curves are there
     for (int attempt = 0; attempt < 2; ++attempt) {
         if ((rc = rk_scratch(ctx, SL_TB_TOFF, ((size_t)J + 1) * 4, (void **)&tb.triple_off))) return rc;
@@ -118,7 +121,9 @@ int32_t schedule_rounds(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_bounds *
         const bool seen = ctx->seen_s[0] > 0 && J > 0;
         const bool sent = seen && may_go_ahead(few_s) && few_t <= 1024u && few_amounts(ctx->seen_s[1]) == few_s &&
                           ((ctx->seen_t[1] + 63u) & ~63u) == few_t && have_room(n_rows * J * few_s);
-        const uint64_t like_last = n_rows * ctx->seen_segs;    // entries of the outputs if this call is like the last one
+        // entries of the outputs if this call is like the last one; of a kind that can be sent, what sending it takes (without
+        // that room it is evaluated behind its enumeration, once, and the next one is sent)
+        const uint64_t like_last = n_rows * (may_go_ahead(few_s) ? (uint64_t)J * few_s : ctx->seen_segs);
         const bool ahead = sent || (seen && ctx->seen_jobs == J && ctx->seen_s[1] == ctx->seen_s[0] && ctx->seen_t[1] == ctx->seen_t[0] && have_room(like_last));
         EnumPending P;
         if ((rc = rk_enumerate_begin(ctx, jobs, bounds, &tb, P, ahead))) break;
@@ -135,13 +140,11 @@ int32_t schedule_rounds(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_bounds *
             rk_plan_table like = tb;
             like.max_triples_per_job = P.guard.most_t; like.max_segs_per_job = P.guard.most_s;
             const ParkedWords parked = {P.park, P.leader, P.park_stride, keep ? tb.triples : nullptr, tb.seg_g, keep ? tb.seg_first : nullptr};
-            float *best_thr, *curve_thr;
-            uint32_t *best_plan, *curve_plan, *curve_g;
             rc_sent = outputs((size_t)(n_rows * segs), best_thr, best_plan, curve_thr, curve_plan, curve_g);
             if (!rc_sent) rc_sent = rk_launch_fused(ctx, jobs, &like, grid, env, 0, J, best_thr, best_plan, curve_thr, curve_plan, curve_g, &P.guard, &parked);
             if (rc_sent) P.guard.cap_triples = 0;              // (nothing went out: the second half makes the content)
+            ctx->ways[sent ? WAY_ROUND_AHEAD : WAY_EVAL_AHEAD]++;
             if (sent) {
-                ctx->ways[WAY_ROUND_AHEAD]++;
                 if (!rc_sent)
                     rc_sent = rk_launch_allocate(ctx, jobs->ref_thr, table_dev(&like), grid, 1, nullptr, nullptr, &clusters[0], 0, J, J, few_s,
                                                  best_thr, best_plan, curve_thr, nullptr, nullptr, nullptr, assign, totals, false, true, &P.guard);
@@ -150,10 +153,8 @@ int32_t schedule_rounds(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_bounds *
         rc = rk_enumerate_end(ctx, &tb, P);
         if (!rc) rc = rc_sent;
         evaluated = !rc && P.taken;
-        if (evaluated && sent) {
-            ctx->ways[WAY_ROUND_AHEAD_TAKEN]++;
-            return RK_OK;
-        }
+        if (evaluated) ctx->ways[sent ? WAY_ROUND_AHEAD_TAKEN : WAY_EVAL_AHEAD_TAKEN]++;
+        if (evaluated && sent) return RK_OK;
         if (rc != RK_ERR_CAPACITY) break;
         cap_t = tb.n_triples;
         cap_s = tb.n_segs;
@@ -161,11 +162,11 @@ int32_t schedule_rounds(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_bounds *
     if (rc) return rc;
     if (tb.max_segs_per_job > 32767u) return rk_fail(ctx, RK_ERR_UNSUPPORTED, "more than 32767 segments per job");
 
-    float *best_thr, *curve_thr;
-    uint32_t *best_plan, *curve_plan, *curve_g;
-    const uint32_t most = few_amounts(tb.max_segs_per_job);
-    if ((rc = outputs((size_t)(n_rows * (may_go_ahead(most) ? (uint64_t)J * most : tb.n_segs)), best_thr, best_plan, curve_thr, curve_plan, curve_g))) return rc;
-    if (!evaluated && (rc = rk_launch_fused(ctx, jobs, &tb, grid, env, 0, J, best_thr, best_plan, curve_thr, curve_plan, curve_g))) return rc;
+    if (!evaluated) {
+        const uint32_t most = few_amounts(tb.max_segs_per_job);
+        if ((rc = outputs((size_t)(n_rows * (may_go_ahead(most) ? (uint64_t)J * most : tb.n_segs)), best_thr, best_plan, curve_thr, curve_plan, curve_g))) return rc;
+        if ((rc = rk_launch_fused(ctx, jobs, &tb, grid, env, 0, J, best_thr, best_plan, curve_thr, curve_plan, curve_g))) return rc;
+    }
     if (keep) {
         keep->tb = tb; keep->best_thr = best_thr; keep->best_plan = best_plan; keep->curve_thr = curve_thr; keep->min_seg = nullptr;
         if (keep->curves_only) return RK_OK;
