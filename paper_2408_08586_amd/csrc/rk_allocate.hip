@@ -25,7 +25,8 @@
 //           search within the capacity that is left).
 //  k_tail   the plain step-by-step loop on the little capacity that is left:
 //           one workgroup per round, whose first wavefront takes steps from a
-//           list of the best cached ones, which all wavefronts keep and find.
+//           list of the best cached ones, which all wavefronts keep and find;
+//           in smaller rounds a few steps are taken one by one instead.
 //  When no job's CPU walk has a step, the CPU pass's k_hist, k_apply and k_tail
 //  return at once (a per-round flag raised by its k_hull).
 //
@@ -952,7 +953,7 @@ __device__ __forceinline__ Step best_step_listed(const GridDev &grid, const uint
     return out;
 }
 
-// A barrier that orders LDS only.
+// A barrier that orders LDS only: loads from memory that are on their way stay there.
 __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
     __builtin_amdgcn_s_barrier();
@@ -961,13 +962,17 @@ __device__ __forceinline__ void lds_barrier() {
 
 // The list that the first wavefront works on, a job per lane: the jobs, their cached steps, the steps behind those (next_tgt
 // TAIL_NONE: not known), how many amounts they have, and per wavefront the best step that is not in the list; and what the
-// first wavefront leaves for the others.
+// first wavefront leaves for the others.  Where steps are taken one by one: what every wavefront offers, its best exact step with its
+// costs and its best bound, in two copies used in turn.
+struct TailOffer { uint32_t slope, job, dg, dc, bound, bound_job; };
 constexpr uint32_t TAIL_LIST = 64, TAIL_PER = 4, TAIL_NONE = 0xFFFFFFFFu;
+constexpr uint32_t TAIL_SINGLY = 5, TAIL_MANY_STEPS = 4;          // steps taken one by one, at most; that go to lists, if so many will come
 struct TailShared {
     unsigned long long free_g, free_c, best, moved;
     float slope[TAIL_LIST], next_slope[TAIL_LIST], ref[TAIL_LIST];
     uint32_t job[TAIL_LIST], dg[TAIL_LIST], dc[TAIL_LIST], next_tgt[TAIL_LIST], next_dg[TAIL_LIST], next_dc[TAIL_LIST], ns[TAIL_LIST];
     uint32_t rest[TAIL_THREADS / 64], rest_job[TAIL_THREADS / 64], lvl[RK_MAX_CPU_LEVELS], what;
+    TailOffer offers[2][TAIL_THREADS / 64];
 };
 enum { TAIL_END = 0, TAIL_LOOK = 1, TAIL_SEARCH = 2 };
 // dynamic LDS of tail_run: 8 bytes per job, then values and GPUs of the list's amounts
@@ -982,9 +987,16 @@ __host__ __device__ constexpr size_t tail_lds_bytes(uint32_t max_jobs) { return 
 // this list by itself, a job per lane, without barriers, for as long as the best of the list comes before everything that is
 // not in it.  Which steps are in the list does not change the result: a step that is not among the best of its wavefront ends
 // the list's turn before it could have been taken.  28 steps of 3,333 jobs 70 -> 28 us, 10 steps and 5 bounds of 10,000
-// jobs 39 -> 18 us; before, every step was a turn of all wavefronts: an offer of each, a barrier, and a look of the
-// winner's through its registers (2.3 us a step).  A list costs about 3 us, so a round of 500 or 1,000 jobs with one or two
-// steps here takes up to 2 us longer than it did, with forty of them 37 less.
+// jobs 39 -> 18 us.
+// A list costs about 3 us, a step of its own 1.3 in a round of up to 2,048 jobs (2.3 with 12 jobs per thread): all wavefronts
+// offer their best, find the best offer behind one barrier, and the winner finds its next step from what was on its way
+// meanwhile.  So those rounds take steps one by one as long as there will be few of them: what is free divided by what the
+// offered steps need on average foretells how many, four and more go to lists (of 22 rounds of jobs of the model, those below
+// four had one to five steps, one had eleven; those above it five to 24), and so does the sixth.  Where a list has many bounds
+// to search it is given up and the steps are few again.  All steps from lists, all one by one, and this way: 300 jobs, one step
+// 41.1, 38.4 and 38.4 us a round's allocation; 500 jobs, four steps 45.6, 45.8 and 45.8, with four groups of bounds 71.5, 57.9 and 57.7;
+// 1,000 jobs, three steps and two groups 59.6, 50.1 and 50.9; 2,000 jobs, three and three 91.8, 74.8 and 77.3; 150 jobs, eleven
+// steps 48.0, 54.4 and 51.7; 800 jobs, 24 steps 59.8, 76.5 and 61.1; 1,000 alike, 250 steps 144, 363 and 143.
 // Neighbours of jobs that are all alike come first one after the other: in rounds of up to 2,048 jobs, where the loads are few,
 // a wavefront has only TAIL_PER neighbours each, and all of them are in one list (250 steps of 1,000 such jobs 141 us instead of
 // 415; 364 before); 10,000 jobs read that way take 6 us more.
@@ -1029,6 +1041,9 @@ __device__ __forceinline__ void tail_run(const Ctx &X, const JobState &st, uint3
     if (tid < RK_MAX_CPU_LEVELS) lvl[tid] = grid.cpu_levels[tid];
     float slope[KMAX];                                             // cached best step of the thread's jobs:
     uint32_t dg[KMAX], dc[KMAX];                                   // > 0 exact, < 0 an upper bound, 0 none; its GPUs, CPUs
+    constexpr bool SMALL = KMAX <= 2;
+    uint32_t seg_lo[SMALL ? KMAX : 1], seg_hi[SMALL ? KMAX : 1];   // where the jobs' amounts are
+    float ref_thr[SMALL ? KMAX : 1];
     {
         int32_t g_i[KMAX];
         uint32_t c_i[KMAX], target[KMAX], gpus[KMAX];
@@ -1041,6 +1056,15 @@ __device__ __forceinline__ void tail_run(const Ctx &X, const JobState &st, uint3
             target[k] = st.step_tgt[at];
             gpus[k] = PASS == 0 ? st.step_dg[at] : st.g[at];
             slope[k] = st.step_slope[at];
+        }
+        if constexpr (SMALL) {                                     // (not waited for before a step needs them)
+#pragma unroll
+            for (int k = 0; k < KMAX; ++k) {
+                const uint32_t jl = own + (uint32_t)k * T, slot = job_of(X, J0 + (jl < nj ? jl : nj - 1u));
+                seg_lo[k] = X.tb.seg_off[slot];
+                seg_hi[k] = X.tb.seg_off[slot + 1];
+                ref_thr[k] = X.ref_thr[slot];
+            }
         }
         __syncthreads();                                           // the levels are in LDS
 #pragma unroll
@@ -1074,11 +1098,121 @@ __device__ __forceinline__ void tail_run(const Ctx &X, const JobState &st, uint3
     uint32_t asked = 0;                                         // (the first wavefront's) bounds made exact one by one
     uint32_t moved = 0;                                         // bit k = the thread's k-th job took a step here
     const uint32_t n_mem = grid.n_mem, n_rows = grid.n_cpu * n_mem, first_seg = X.tb.seg_off[X.jb];
+    // their threads make the bounds that could win exact: those whose key comes before that of the best exact step
+    auto search = [&](unsigned long long best) {
+        uint32_t todo = 0;
+#pragma unroll
+        for (int k = 0; k < KMAX; ++k) {
+            const float v = slope[k];
+            if (v < 0.f && key_of(-v, own + (uint32_t)k * T) > best) todo |= 1u << k;
+        }
+        for (; todo; todo &= todo - 1u) {                       // (the register arrays are only ever indexed by constants)
+            const uint32_t at = (uint32_t)__ffs((int)todo) - 1u, jl = own + at * T;
+            const uint32_t held = PASS == 0 ? 0u : gh[jl];
+            const Step nx = best_step<PASS>(X, J0 + jl, gi[jl], held, ci[jl], freeG, freeC);
+            const uint32_t need = need_cpus(gi[jl], ci[jl], nx.tgt, PASS == 0 ? nx.dg : held);
+            tgt[jl] = (uint16_t)nx.tgt;
+#pragma unroll
+            for (int k = 0; k < KMAX; ++k)
+                if ((uint32_t)k == at) { slope[k] = nx.slope; dg[k] = PASS == 0 ? nx.dg : 0u; dc[k] = need; }
+        }
+    };
+    // What the wavefront has read of the job with its best step: a lane per amount (GPU pass: its GPUs too).
+    uint32_t kept_job = NONE, kept_g = 0, kept_n = 0, turn = 0, singly = 0;
+    float kept_v = 0.f, kept_ref = 1.f;
+    bool one_by_one = SMALL;
     // (no job has a step, as in most CPU passes of small rounds: asked once, since a list says whether there is more)
     const bool none = KMAX == 1 && __syncthreads_or(slope[0] > 0.f) == 0;
     while (!none) {
         if (PASS == 0 ? freeG == 0 : freeC == 0) break;         // nothing can fit any more
         const uint32_t roomG = room(freeG), roomC = room(freeC);
+        if constexpr (SMALL) {
+            if (one_by_one) {
+                // ---- one step, by all wavefronts: the thread's best exact step and best bound, then the wavefront's
+                float vf = 0.f, vs = 0.f;
+                uint32_t kf = 0, ks = 0;
+#pragma unroll
+                for (int k = 0; k < KMAX; ++k) {
+                    float v = slope[k];
+                    v = v > 0.f && ((PASS == 0 && dg[k] > roomG) || dc[k] > roomC) ? -v : v;
+                    slope[k] = v;
+                    if (v > vf) { vf = v; kf = (uint32_t)k; }
+                    if (-v > vs) { vs = -v; ks = (uint32_t)k; }
+                }
+                const bool second = KMAX > 1 && kf != 0u;
+                const uint32_t jf = own + kf * T, js = own + ks * T, bf = __float_as_uint(vf), bs = __float_as_uint(vs);
+                const uint32_t mf = wave_max_u32_rows(bf), ms = wave_max_u32_rows(bs);
+                uint32_t jm = NONE, jb = NONE, dgm = 0, dcm = 0;
+                if (mf) {
+                    jm = wave_min_u32_rows(bf == mf ? jf : NONE);
+                    const uint32_t at = (uint32_t)__ffsll((long long)__ballot(bf == mf && jf == jm)) - 1u;
+                    dgm = wave_lane_u32(second ? dg[KMAX - 1] : dg[0], at);
+                    dcm = wave_lane_u32(second ? dc[KMAX - 1] : dc[0], at);
+                    if (jm != kept_job) {                       // what its next step needs is on its way before it wins
+                        const uint32_t s0 = wave_lane_u32(second ? seg_lo[KMAX - 1] : seg_lo[0], at), n = wave_lane_u32(second ? seg_hi[KMAX - 1] : seg_hi[0], at) - s0;
+                        kept_ref = __uint_as_float(wave_lane_u32(__float_as_uint(second ? ref_thr[KMAX - 1] : ref_thr[0]), at));
+                        kept_job = jm;
+                        kept_n = n;
+                        const uint64_t base = (uint64_t)n_rows * (s0 - first_seg);
+                        if (PASS == 0) {
+                            const uint32_t i = lane < n ? lane : n - 1u;
+                            kept_g = X.tb.seg_g[s0 + i];
+                            kept_v = X.curve_thr[base + (uint64_t)(one(ci[jm]) * n_mem + n_mem - 1u) * n + i];
+                        } else {
+                            const uint32_t c = lane < grid.n_cpu ? lane : grid.n_cpu - 1u;
+                            kept_v = X.best_thr[base + (uint64_t)(c * n_mem + n_mem - 1u) * n + one((uint32_t)(int32_t)gi[jm])];
+                        }
+                    }
+                }
+                if (ms) jb = wave_min_u32_rows(bs == ms ? js : NONE);
+                turn ^= 1u;
+                if (lane == 0) S.offers[turn][wave] = TailOffer{mf, jm, dgm, dcm, ms, jb};
+                lds_barrier();
+                const TailOffer o = S.offers[turn][lane & (WAVES - 1u)];          // every row of 16 lanes has all of them
+                const uint32_t top = one(row_max_u32(o.slope)), jw = one(row_min_u32(o.slope == top ? o.job : NONE));
+                const uint32_t bound = one(row_max_u32(o.bound)), jbound = one(row_min_u32(o.bound == bound ? o.bound_job : NONE));
+                if (bound && (bound > top || (bound == top && jbound < jw))) {    // a bound could win: make those exact
+                    search(top ? key_of(__uint_as_float(top), jw) : 0ull);
+                    continue;
+                }
+                if (!top) break;
+                if (singly == 0u) {                             // is there room for as many steps like those offered?
+                    const uint32_t n = (uint32_t)__popcll(__ballot(o.slope != 0u) & 0xFFFFull), sum_g = one(row_sum_u32(o.slope ? o.dg : 0u));
+                    const uint32_t sum_c = one(row_sum_u32(o.slope ? o.dc : 0u));        // (each fits what is free)
+                    one_by_one = (unsigned long long)roomG * n < (unsigned long long)sum_g * TAIL_MANY_STEPS ||
+                                 (unsigned long long)roomC * n < (unsigned long long)sum_c * TAIL_MANY_STEPS;
+                }
+                if (one_by_one) {
+                    const uint32_t won = (uint32_t)__ffsll((long long)__ballot(o.slope == top && o.job == jw)) - 1u;       // (below WAVES)
+                    freeG -= wave_lane_u32(o.dg, won);              // (CPU pass: 0)
+                    freeC -= wave_lane_u32(o.dc, won);
+                    if (wave == won) {
+                        const bool owner = jf == jw && bf == top;
+                        int32_t g_i = gi[jw];
+                        uint32_t c_i = ci[jw];
+                        if (PASS == 0) g_i = (int32_t)tgt[jw]; else c_i = tgt[jw];
+                        const uint32_t held = PASS == 0 ? 0u : gh[jw];
+                        Step nx = {0.f, 0u, 0u};
+                        if (PASS == 0 ? freeG != 0 : freeC != 0)
+                            nx = PASS == 1 || kept_n <= 64u
+                                     ? best_step_listed<PASS>(grid, lvl, kept_v, kept_g, kept_ref, PASS == 0 ? (int32_t)one((uint32_t)g_i) : (int32_t)one(c_i),
+                                                              PASS == 0 ? kept_n : grid.n_cpu, one(held), one(c_i), room(freeG), room(freeC))
+                                     : best_step_wave<PASS>(X, J0 + jw, g_i, held, c_i, freeG, freeC);
+                        if (owner) {
+                            if (PASS == 0) gi[jw] = (int16_t)g_i; else ci[jw] = (uint16_t)c_i;
+                            moved |= 1u << kf;
+                            tgt[jw] = (uint16_t)nx.tgt;
+                            const uint32_t need = need_cpus(g_i, c_i, nx.tgt, PASS == 0 ? nx.dg : held);
+#pragma unroll
+                            for (int k = 0; k < KMAX; ++k)
+                                if ((uint32_t)k == kf) { slope[k] = nx.slope; dg[k] = PASS == 0 ? nx.dg : 0u; dc[k] = need; }
+                        }
+                    }
+                    one_by_one = ++singly < TAIL_SINGLY;
+                    continue;
+                }
+            }
+        }
         // ---- the thread's best step or bound and its second (a thread's jobs come in rising order, so the first of equal
         // slopes is the lower job)
         float a1 = 0.f, a2 = 0.f;
@@ -1259,32 +1393,20 @@ __device__ __forceinline__ void tail_run(const Ctx &X, const JobState &st, uint3
                 if ((uint32_t)k == k1) { slope[k] = S.slope[mine]; dg[k] = S.dg[mine]; dc[k] = S.dc[mine]; }
         }
         if (what == TAIL_END) break;
-        if (what == TAIL_SEARCH) {                              // many bounds could win: their threads make all of those exact
-            const unsigned long long best = S.best;
-            uint32_t todo = 0;
-#pragma unroll
-            for (int k = 0; k < KMAX; ++k) {
-                const float v = slope[k];
-                if (v < 0.f && key_of(-v, own + (uint32_t)k * T) > best) todo |= 1u << k;
-            }
-            for (; todo; todo &= todo - 1u) {                   // (the register arrays are only ever indexed by constants)
-                const uint32_t at = (uint32_t)__ffs((int)todo) - 1u, jl = own + at * T;
-                const uint32_t held = PASS == 0 ? 0u : gh[jl];
-                const Step nx = best_step<PASS>(X, J0 + jl, gi[jl], held, ci[jl], freeG, freeC);
-                const uint32_t need = need_cpus(gi[jl], ci[jl], nx.tgt, PASS == 0 ? nx.dg : held);
-                tgt[jl] = (uint16_t)nx.tgt;
-#pragma unroll
-                for (int k = 0; k < KMAX; ++k)
-                    if ((uint32_t)k == at) { slope[k] = nx.slope; dg[k] = PASS == 0 ? nx.dg : 0u; dc[k] = need; }
-            }
+        if (what == TAIL_SEARCH) {                               // many bounds could win
+            search(S.best);
+            one_by_one = SMALL;
+            singly = 0;
         }
     }
     for (; moved; moved &= moved - 1u) {                        // only the jobs that took a step here changed since k_apply
-        const uint32_t jl = own + ((uint32_t)__ffs((int)moved) - 1u) * T;
+        const uint32_t k = (uint32_t)__ffs((int)moved) - 1u, jl = own + k * T;
         if (PASS == 0) {
             const int32_t s_i = gi[jl];
+            uint32_t s0;
+            if constexpr (SMALL) s0 = KMAX > 1 && k ? seg_lo[KMAX - 1] : seg_lo[0]; else s0 = X.tb.seg_off[job_of(X, J0 + jl)];
             st.gi[jrel0 + jl] = s_i;
-            st.g[jrel0 + jl] = s_i < 0 ? 0u : X.tb.seg_g[X.tb.seg_off[job_of(X, J0 + jl)] + s_i];
+            st.g[jrel0 + jl] = s_i < 0 ? 0u : X.tb.seg_g[s0 + s_i];
         } else {
             st.ci[jrel0 + jl] = ci[jl];
         }

@@ -72,6 +72,12 @@ __device__ __forceinline__ uint32_t row_max_u32(uint32_t v) {
     v = rs_max_u32(v, rs_dpp_u32<0x141, 0xF>(0u, v));
     return rs_max_u32(v, rs_dpp_u32<0x140, 0xF>(0u, v));
 }
+__device__ __forceinline__ uint32_t row_sum_u32(uint32_t v) {                        // row_ror:8, 4, 2, 1
+    v += rs_dpp_u32<0x128, 0xF>(0u, v);
+    v += rs_dpp_u32<0x124, 0xF>(0u, v);
+    v += rs_dpp_u32<0x122, 0xF>(0u, v);
+    return v + rs_dpp_u32<0x121, 0xF>(0u, v);
+}
 __device__ __forceinline__ uint32_t wave_max_u32_rows(uint32_t v) {
     v = row_max_u32(v);
     v = rs_max_u32(v, rs_dpp_u32<0x142, 0xA>(0u, v));
@@ -102,11 +108,7 @@ __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
     const auto a = __builtin_amdgcn_permlane32_swap(v, v, false, false);
     v = a[0] + a[1];
     const auto b = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-    v = b[0] + b[1];
-    v += rs_dpp_u32<0x128, 0xF>(0u, v);
-    v += rs_dpp_u32<0x124, 0xF>(0u, v);
-    v += rs_dpp_u32<0x122, 0xF>(0u, v);
-    return v + rs_dpp_u32<0x121, 0xF>(0u, v);
+    return row_sum_u32(b[0] + b[1]);
 }
 
 // Lane s of a value whose index is the same in all lanes (through a scalar register).

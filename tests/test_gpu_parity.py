@@ -1053,6 +1053,43 @@ def test_enumeration_at_the_job_counts_where_the_scan_changes(gpu, orc):
     run.close()
 
 
+@pytest.mark.parametrize("n_jobs,g_max", [(300, 64), (512, 64), (513, 64), (1025, 64), (2048, 64), (70, 1024), (600, 1024)])
+def test_allocate_few_steps_behind_the_threshold(gpu, orc, n_jobs, g_max):
+    """Rounds of up to 2,048 jobs take up to five steps one by one and go to lists where there would be more, or after a list
+    that had many bounds to search back again: capacities that leave from none to some dozens of steps to either pass, with
+    equal slopes, bounds and jobs of more than 64 amounts among them."""
+    import paper_2408_08586_amd as rk
+    rng = np.random.default_rng(n_jobs + g_max)
+    base = workloads.stress(n_jobs=n_jobs)
+    coef = base.coef.copy()
+    coef[:, 16] = rng.choice([0.5, 1.0, 2.0], n_jobs)
+    grid = workloads.Grid(np.arange(1, 7, dtype=np.uint32), base.grid.cpu_mode, np.array([64.0], np.float32), base.grid.mem_mode)
+    ints = base.ints.copy()
+    if g_max > 64:
+        ints[::2] = (96, 1680, 1)                          # jobs of more than 64 amounts
+    wl = workloads.Workload("steps", coef, ints, workloads.Bounds(g_max=g_max), grid, base.env, workloads.Cluster(4096, 30000, 1.0e9))
+    ot = orc.enumerate_plans(wl.ints, wl.bounds)
+    g_of = np.concatenate([np.tile(ot.seg_g[ot.seg_off[j]:ot.seg_off[j + 1]], 6) for j in range(n_jobs)])
+    level = np.concatenate([np.repeat(np.arange(6), ot.seg_off[j + 1] - ot.seg_off[j]) for j in range(n_jobs)])
+    bt = (np.round(g_of ** rng.uniform(0.5, 0.9, len(g_of)) * 2) / 2 + level * rng.integers(0, 2, len(g_of))).astype(np.float32)
+    bp = rng.integers(0, 1000, len(bt)).astype(np.uint32)
+    ct, _, _ = orc.curves(ot, wl.grid, bt, bp)
+    run = gpu(wl)
+    run.enumerate()
+    assert (run.table.c.max_segs_per_job > 64) == (g_max > 64)
+    d_bt, d_bp, d_ct = run.dev_f32(bt), run.dev_u32(bp), run.dev_f32(ct)
+    clusters = [(G, 10 ** 6) for G in (1, 2, 3, 5, 8, n_jobs // 3, n_jobs // 2, n_jobs + 3)]
+    clusters += [(int(rng.integers(n_jobs // 4, 3 * n_jobs)), int(rng.integers(n_jobs, 9 * n_jobs))) for _ in range(16)]
+    clusters += [(1 << 20, int(rng.integers(n_jobs, 20 * n_jobs))) for _ in range(6)]
+    for G, Cc in clusters:
+        cl = workloads.Cluster(G, Cc, 1.0e9)
+        e_assign, e_total, _ = orc.greedy(wl.coef[:, 16], ot, wl.grid, cl, bt, bp, ct)
+        assign, total = run.allocate(d_bt, d_bp, d_ct, cluster=rk.make_cluster(cl))
+        assert np.array_equal(assign, e_assign), (G, Cc)
+        assert total == pytest.approx(e_total, rel=1e-6)
+    run.close()
+
+
 @pytest.mark.parametrize("n,n_kinds", [(511, 40), (512, 512), (513, 40), (16384, 45), (16385, 1), (16385, 3000), (40000, 33000)])
 def test_enumeration_around_the_listed_searches(gpu, orc, n, n_kinds):
     """Up to 512 jobs are scanned by the last search, two to a thread; beyond 16,384 the searches are taken from a list, in
