@@ -683,7 +683,8 @@ __device__ __forceinline__ void nodes_lds(const KernArgs &K) {
     }
 
     // ---- everything into LDS.  TAB: room for a job per thread, and what the jobs have comes first, so that the addresses
-    // are known beforehand (a wavefront that works alone pays for every instruction).
+    // are known beforehand (a wavefront that works alone pays for every instruction).  Otherwise what every node has comes before
+    // the jobs' words (behind them 900 jobs on 512 nodes took 62.6 ms instead of 62.0).
     const uint32_t JL = TAB ? (uint32_t)THREADS : J;
     uint32_t *at = reinterpret_cast<uint32_t *>(sh_raw);
     auto take = [&](size_t words) { uint32_t *p = at; at += words; return p; };
@@ -692,6 +693,9 @@ __device__ __forceinline__ void nodes_lds(const KernArgs &K) {
     if constexpr (LJ) A.give = reinterpret_cast<uint4 *>(take(4 * (size_t)JL));
     if constexpr (LJ) { A.udc_c = reinterpret_cast<unsigned long long *>(take(2 * (size_t)JL)); A.okey = reinterpret_cast<unsigned long long *>(take(2 * (size_t)JL)); }
     float *const sh_ds = reinterpret_cast<float *>(take(2 * ((size_t)JL + 1)));
+    float *sh_mem = nullptr;
+    uint32_t *sh_mark = nullptr;
+    if constexpr (!TAB) { sh_mem = reinterpret_cast<float *>(take(N)); sh_mark = take((J + 31u) / 32u); }
     if constexpr (LJ) {
         auto words = [&](auto &p) { p = reinterpret_cast<std::decay_t<decltype(p)>>(take(JL)); };        // a per-job array of words in LDS
         words(A.st.gi); words(A.st.ci); words(A.ug); words(A.uc); words(A.udg); words(A.gain_g); words(A.gain_c);
@@ -708,8 +712,7 @@ __device__ __forceinline__ void nodes_lds(const KernArgs &K) {
         nodes = take(2 * A.nodes_words);
     }
     uint32_t *const keep = nodes + A.nodes_words;
-    float *const sh_mem = reinterpret_cast<float *>(take(N));
-    uint32_t *const sh_mark = take((J + 31u) / 32u);         // a bit per job: changed by the step under way and remembered in memory
+    if constexpr (TAB) { sh_mem = reinterpret_cast<float *>(take(N)); sh_mark = take((J + 31u) / 32u); }         // a bit per job: changed by the step under way and remembered in memory
     uint32_t *start_res = nullptr, *held_g = nullptr;        // (TAB)
     float *held_cost = nullptr, *share = nullptr;
     A.free_g = nodes; A.free_c = nodes + N; A.cnt = nodes + 2 * N; A.res = nodes + ((3 * N + 3) & ~3u);
@@ -2444,6 +2447,7 @@ int32_t rk_launch_reschedule_nodes(rk_ctx *ctx, const float *ref_thr, const rk_p
 constexpr uint32_t SIM_NODES_ROUNDS = 64;        // rounds of a launch
 constexpr uint64_t ND_STATES_MOST = 1u << 19;    // states of all jobs that are found beforehand (80 bytes each)
 constexpr uint32_t ND_STATES_PER_TICK = 65536;   // ... that a tick pays for
+constexpr uint32_t ND_STATES_NODES_WORDS = 5632; // ... words of the nodes' tables that one wavefront copies no slower than all
 
 bool rk_sim_nodes_fit(uint32_t n_jobs, const rk_nodes *nodes) {
     const size_t N = nodes->n_nodes, gpus = N * nodes->gpus_per_node;
@@ -2470,10 +2474,15 @@ int32_t rk_launch_sim_nodes(rk_ctx *ctx, const SimArgs &S, const float *ref_thr,
     // With a job per thread, all states of the jobs are found beforehand where they are not too many for memory and for the
     // ticks: 0.4 us per 1,000 states, and a round is at least 25 us shorter (a simulation of one tick may have nothing to do: 42
     // and 55 us; two ticks of 300 jobs on 64 GPUs 214 and 131, of 900 on 1,024 GPUs, 207,000 states, 5.86 and 4.40 ms).
+    // One wavefront copies the nodes' tables and looks through the residents, which costs it more the more of them there are:
+    // 24 ticks of 100, 300 and 500 jobs on 256 nodes of 8 GPUs 5.8 and 4.7, 19.3 and 14.9, 25.9 and 20.0 ms, on 512 (5,632 words) 8.2 and
+    // 7.7, 22.3 and 19.7, 36.2 and 31.9; 12 ticks of 60 and 250 jobs on 256 nodes of 16 (4,864) 2.87 and 2.74, 8.31 and 8.03, on 1,024 of 2
+    // (5,120) 5.67 and 5.62, 12.5 and 12.0, on 768 of 5 (6,144) 4.90 and 5.08, 13.6 and 13.7, on 1,024 of 4 (7,168) 4.59 and 4.92, 12.8
+    // and 13.0, on 2,048 of 1 (8,192) 13.8 and 13.6, 22.2 and 22.5, of 500 jobs there 21.8 and 22.8.
     const uint64_t per_job = ((uint64_t)table->max_segs_per_job + 1u) * grid->n_cpu, states = J * per_job;
     const uint32_t threads = J <= ND_FEW_THREADS ? ND_FEW_THREADS : J <= ND_SMALL_THREADS ? ND_SMALL_THREADS : ND_THREADS;
     const size_t lds_tab = nd_tab_words(threads, N, gpus, K.b.nodes_words) * sizeof(uint32_t);
-    const bool tab = J <= ND_THREADS && lds_tab <= ND_LDS_MOST && states <= ND_STATES_MOST && S.n_ticks > 1u && states <= (uint64_t)ND_STATES_PER_TICK * S.n_ticks;
+    const bool tab = J <= ND_THREADS && K.b.nodes_words <= ND_STATES_NODES_WORDS && lds_tab <= ND_LDS_MOST && states <= ND_STATES_MOST && S.n_ticks > 1u && states <= (uint64_t)ND_STATES_PER_TICK * S.n_ticks;
     const bool eight = K.b.gpn == 8u;
     if (tab) {
         lds = lds_tab;

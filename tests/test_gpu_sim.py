@@ -320,6 +320,13 @@ def test_simulation_over_nodes_at_the_sizes_it_is_laid_out_for(gpu, orc, jobs, n
     run.close()
 
 
+@pytest.mark.parametrize("jobs,nodes,gpn", [(60, 512, 8), (60, 513, 8), (300, 1024, 2), (300, 1024, 3)])
+def test_simulation_over_so_many_nodes_that_one_wavefront_is_not_the_faster(gpu, orc, jobs, nodes, gpn):
+    """The last and the first tables of nodes (5,632 words, and more) on either side of the line at which all wavefronts make a
+    round again."""
+    test_simulation_over_nodes_at_the_sizes_it_is_laid_out_for(gpu, orc, jobs, nodes, gpn, 5, (64.0,), 100.0 * gpn, 0.97)
+
+
 @pytest.mark.parametrize("jobs,gpus,g_max,levels,per_gpu,cpus,tiers,mem", [
     (1, 64, 64, 32, 0, 64, (64.0,), 4096.0),                 # one job
     (40, 16, 16, 8, 0, 20, (64.0,), 1e6),                    # CPUs for few of the steps: the pass over them is needed
