@@ -82,6 +82,7 @@ class Call:
 def test_rounds_evaluated_before_their_size_is_known(jobs, kind, per_gpu, tiers):
     import torch
     import paper_2408_08586_amd as rk
+    from gpu_harness import ways
     assert torch.cuda.is_available(), "these tests need the GPU"
     kinds = [(64, 1), (64, 1), (64, 1), (64, 1), (200, 7), (200, 7), (64, 1), (200, 7), (200, 7), (200, 7)]
     ctx = rk.rk_create(0)
@@ -92,6 +93,9 @@ def test_rounds_evaluated_before_their_size_is_known(jobs, kind, per_gpu, tiers)
         want = call(fresh)
         rk.rk_destroy(fresh)
         assert got == want, (i, g_max, mu_mask)
+    whole = ways(ctx)
+    ahead, taken = (np.array(eval_ways(ctx)) + (whole["ahead"], whole["ahead_taken"])).tolist()
+    assert taken >= 2 and ahead > taken                     # guesses that were right, and one at least that was refused
     rk.rk_destroy(ctx)
 
 
