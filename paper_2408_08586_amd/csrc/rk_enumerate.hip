@@ -5,21 +5,24 @@
 // lists of b/mu (data-parallel sizes) and of the layer count (pipeline sizes),
 // forms the products d*t*p <= g_max with t in {1,2,4,8} for every allowed
 // micro-batch shift v (d must divide b/(mu*2^v)), and orders them by the key
-// (g, t, p, v) in LDS: a bitmap of the GPU counts that occur gives every key
-// its segment (rank of its g among the distinct counts = a population count),
-// the keys are gathered by segment, and only the few keys of one segment are
-// compared with each other.  The counting pass also parks the triples it found,
-// in the table's own words, in a scratch buffer (512 words per job at first,
-// then the widest job's triples and a quarter more, at most 2,048); after the
-// exclusive scan of the counts the fill pass (k_fill) copies them into place, a
-// wavefront per job, and marks where a new GPU count begins (the search is
-// repeated only when the scratch buffer was too small).
+// (g, t, p, v) in LDS.  Up to 256 keys, as most jobs have, find their places by
+// counting the smaller ones, a thread per key.  More of them go by a bitmap of
+// the GPU counts that occur: it gives every key its segment (rank of its g among
+// the distinct counts = a population count), the keys are gathered by segment,
+// and only the few keys of one segment are compared with each other.
+// The counting pass also parks the triples it found, in the table's own words,
+// in a scratch buffer (512 words per job at first, then the widest job's triples
+// and a quarter more, at most 2,048).  After the exclusive scan of the counts the
+// table's content is made from the parked words: by the fill pass (k_fill, a
+// wavefront per job, which marks where a new GPU count begins), or in a scheduling
+// round that is evaluated ahead by k_fused.  Either is launched while the counts are
+// still on their way to the host: it checks on the device that the table is
+// large enough and leaves it alone otherwise.  (The search is repeated only when
+// the scratch buffer was too small.)
 // Jobs whose searches would be identical (same layer count, same number of
 // micro-batches per step) share one: a hash table names a leader for each such
 // group, only leaders search, the others take the leader's counts and copy the
-// leader's parked words.  The fill pass is launched while the counts are still
-// on their way to the host: it checks on the device that the table is large
-// enough and leaves it alone otherwise.
+// leader's parked words.
 //
 // Small calls are bound by their launches, so up to ENUM_SELF_SCAN jobs are
 // scanned by the workgroup that finishes its search last, which also writes
@@ -124,6 +127,7 @@ constexpr uint32_t ENUM_SELF_SCAN = 2 * ENUM_THREADS;
 // nearly all have nothing to do, 128,000 jobs of 45 kinds took 117 us, now 96, of 3,000 kinds 129 and 112, 60,000 of 45 kinds
 // 76 and 67; where nearly all jobs are kinds of their own, which is not what jobs are like, the list costs more than it saves
 // (128,000 of 100,000 kinds 280 and 303, with 2,048 workgroups 378: searches differ in length).  10,000 jobs: 48.9 and 50.9.
+// (All of these with the offsets still copied to the host, which took another 15 us.)
 constexpr uint32_t ENUM_TURNS = 16384;
 
 __global__ __launch_bounds__(LEAD_THREADS) void k_enum_leaders(const uint32_t *__restrict__ layers,
@@ -451,9 +455,11 @@ __global__ __launch_bounds__(ENUM_THREADS) void k_enumerate(
         if (LISTED) continue;
         return;
     }
-    // Counts, then the counter, at the device's scope (the workgroups sit on several L2 caches): a count is on its way to where
-    // all of them see it and has arrived when the counter is raised; the workgroup that brings the counter to its end reads
-    // them all from there.  Nothing else is handed over here, so no cache has to be written back or emptied.
+    // Counts, then the counter, at the device's scope (the workgroups sit on several L2 caches).  A release at the counter would
+    // write a whole L2 back for two words.  Instead this rests on what gfx950 does with atomic stores and loads at that scope,
+    // not on the language's ordering of relaxed operations: a store is written through to where all of the device sees it and counts as done
+    // only there, so when the wait before the counter is over the counts have arrived; the loads of the workgroup
+    // that brings the counter to its end read from there too.  Nothing else is handed over here.
     __shared__ uint32_t ends;
     if (tid == 0) {
         __hip_atomic_store(&cnt_t[j], cnt | (err << CNT_FLAGS), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -777,8 +783,8 @@ int32_t rk_enumerate_begin(rk_ctx *ctx, const rk_jobs *jobs, const rk_plan_bound
     else if (!self_scan) k_scan_counts<<<1, 1024, 0, ctx->stream>>>(cnt_t, cnt_s, J, S);
     RK_CHECK_LAUNCH(ctx, "k_scan_counts");
     RK_HIP(ctx, hipEventRecord(ctx->counts_ev, ctx->stream));
-    // The fill pass goes out before the host knows the totals, so that the device does not wait for the
-    // round trip: the kernel itself checks the flags and the table's capacity.
+    // The fill pass (or what the caller launches instead) goes out before the host knows the totals, so that the device does not
+    // wait for the round trip: the kernel itself checks the flags and the table's capacity.
     P = EnumPending{jobs, *bounds, leader, cnt_t, cnt_s, park, off_t, off_s, totals, park_stride, gmap_bytes, tab_clear, fill, mirrors, share, false,
                     false, false, TableGuard{}};
     return fill && J > 0 && !leave_content ? launch_fill(ctx, table, P) : RK_OK;

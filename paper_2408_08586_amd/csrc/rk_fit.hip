@@ -228,9 +228,9 @@ enum { SLOT_IDLE, SLOT_CURRENT, SLOT_START, SLOT_TRIAL };   // nothing; the curr
 // A wavefront has 64/W slots with a descent under way in each.  A model's descents from its starting points are items of
 // their own (the slots take them in order); the slot that finishes a model's last one goes on with its kicks, which build
 // on one another.  When no model is left, slots without an item make kicks ahead from the best point there is; they count
-// if that point is still the best one when their turn comes.  What belongs to a slot as a whole is held by all lanes of its group alike; lane i = 0..6 of every row
-// of 16 (and lane 8 + i) also has component i of the vectors.  Nothing is shared between wavefronts but the number of the
-// next model.
+// if that point is still the best one when their turn comes.  What belongs to a slot as a whole is held by all lanes of its
+// group alike; lane i = 0..6 of every row of 16 (and lane 8 + i) also has component i of the vectors.  Nothing is shared
+// between wavefronts but the number of the next model.
 //
 // Bound: the dependent float64 instructions of an iteration (about 2,700 for a wavefront of four slots, 7 us), first in
 // number, then, when the models run out, in the longest chain of descents.  10,000 models x 16 runs, 5 starting points:
@@ -239,7 +239,8 @@ enum { SLOT_IDLE, SLOT_CURRENT, SLOT_START, SLOT_TRIAL };   // nothing; the curr
 // solutions taken by one wavefront for all slots of a workgroup, a lane each, between two barriers; 9.6 ms with the
 // matrix rows spread over the group's lanes and no barrier at all; 9.0 ms with the overlaps dealt out to the lanes.
 // 20 models: 8.1 -> 3.4 ms.  Kicks that would repeat an earlier one are not made again: 9.1 -> 8.5 ms; kicks made ahead
-// by slots that have nothing else left: 8.3 ms, 20 models (other ones) 4.3 -> 3.1 ms.  Limiting the registers to three wavefronts per SIMD spills: 12.1 ms.
+// by slots that have nothing else left: 8.3 ms, 20 models (other ones) 4.3 -> 3.1 ms.  Limiting the registers to three
+// wavefronts per SIMD spills: 12.1 ms.
 template <int W>
 __global__ __launch_bounds__(FIT_THREADS, 2) void k_fit(FitArgs A) {
     constexpr double GTOL = 1e-14, XTOL = 1e-13, KICK_TO = 0.3;
