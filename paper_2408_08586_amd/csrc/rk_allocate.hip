@@ -966,13 +966,16 @@ __device__ __forceinline__ void lds_barrier() {
 // costs and its best bound, in two copies used in turn.
 struct TailOffer { uint32_t slope, job, dg, dc, bound, bound_job; };
 constexpr uint32_t TAIL_LIST = 64, TAIL_PER = 4, TAIL_NONE = 0xFFFFFFFFu;
-constexpr uint32_t TAIL_SINGLY = 5, TAIL_MANY_STEPS = 4;          // steps taken one by one, at most; that go to lists, if so many will come
+// Steps taken one by one, at most.  Room for so many halves of a step, like all there are or, behind the first, like those
+// offered, goes to lists (more CPUs of a step do not count: the sums stay words).
+constexpr uint32_t TAIL_SINGLY = 5, TAIL_MANY_STEPS = 7, TAIL_MANY_OFFERED = 4, TAIL_MOST_CPUS = 1u << 20;
 struct TailShared {
     unsigned long long free_g, free_c, best, moved;
     float slope[TAIL_LIST], next_slope[TAIL_LIST], ref[TAIL_LIST];
     uint32_t job[TAIL_LIST], dg[TAIL_LIST], dc[TAIL_LIST], next_tgt[TAIL_LIST], next_dg[TAIL_LIST], next_dc[TAIL_LIST], ns[TAIL_LIST];
     uint32_t rest[TAIL_THREADS / 64], rest_job[TAIL_THREADS / 64], lvl[RK_MAX_CPU_LEVELS], what;
     TailOffer offers[2][TAIL_THREADS / 64];
+    uint32_t steps[TAIL_THREADS / 64], steps_g[TAIL_THREADS / 64], steps_c[TAIL_THREADS / 64];   // of a wavefront: exact steps, their GPUs and CPUs
 };
 enum { TAIL_END = 0, TAIL_LOOK = 1, TAIL_SEARCH = 2 };
 // dynamic LDS of tail_run: 8 bytes per job, then values and GPUs of the list's amounts
@@ -990,13 +993,15 @@ __host__ __device__ constexpr size_t tail_lds_bytes(uint32_t max_jobs) { return 
 // jobs 39 -> 18 us.
 // A list costs about 3 us, a step of its own 1.3 in a round of up to 2,048 jobs (2.3 with 12 jobs per thread): all wavefronts
 // offer their best, find the best offer behind one barrier, and the winner finds its next step from what was on its way
-// meanwhile.  So those rounds take steps one by one as long as there will be few of them: what is free divided by what the
-// offered steps need on average foretells how many, four and more go to lists (of 22 rounds of jobs of the model, those below
-// four had one to five steps, one had eleven; those above it five to 24), and so does the sixth.  Where a list has many bounds
-// to search it is given up and the steps are few again.  All steps from lists, all one by one, and this way: 300 jobs, one step
-// 41.1, 38.4 and 38.4 us a round's allocation; 500 jobs, four steps 45.6, 45.8 and 45.8, with four groups of bounds 71.5, 57.9 and 57.7;
-// 1,000 jobs, three steps and two groups 59.6, 50.1 and 50.9; 2,000 jobs, three and three 91.8, 74.8 and 77.3; 150 jobs, eleven
-// steps 48.0, 54.4 and 51.7; 800 jobs, 24 steps 59.8, 76.5 and 61.1; 1,000 alike, 250 steps 144, 363 and 143.
+// meanwhile.  So those rounds take steps one by one where there will be few.  How many is foretold by what is free divided by what
+// the steps of all jobs need on average, and again, when the first is known, from what is free behind it and from the steps
+// that the wavefronts offer.  The lines lie at 3.5 steps and at two more: of 99 rounds of drawn sizes, those below both took one to
+// six steps, with few exceptions, and up to 5.7 us less one by one, those above either four to 35 and up to 27 us less from
+// lists.  The sixth step goes to a list in any case, and where a list has many bounds to search it is given up and the steps
+// are few again.  All steps from lists, all one by one, and this way: 300 jobs, one step 41.1, 38.4 and 38.5 us a round's allocation;
+// 500 jobs on coarse curves, one step 40.7, 38.2 and 37.9, four groups of bounds 70.6, 57.0 and 60.0; 2,000 jobs, three groups 91.3, 73.9 and 81.9; 800
+// jobs, 24 steps 59.0, 75.4 and 59.0; 1,000 alike, 250 steps 144, 362 and 144; the 56 drawn rounds of up to 512 jobs 2.45,
+// 2.57 and 2.43 ms together, the 29 of up to 1,024 1.58, 1.68 and 1.56, the 25 of more 1.65, 1.77 and 1.66.
 // Neighbours of jobs that are all alike come first one after the other: in rounds of up to 2,048 jobs, where the loads are few,
 // a wavefront has only TAIL_PER neighbours each, and all of them are in one list (250 steps of 1,000 such jobs 141 us instead of
 // 415; 364 before); 10,000 jobs read that way take 6 us more.
@@ -1044,6 +1049,15 @@ __device__ __forceinline__ void tail_run(const Ctx &X, const JobState &st, uint3
     constexpr bool SMALL = KMAX <= 2;
     uint32_t seg_lo[SMALL ? KMAX : 1], seg_hi[SMALL ? KMAX : 1];   // where the jobs' amounts are
     float ref_thr[SMALL ? KMAX : 1];
+    auto find_amounts = [&]() {                                    // (not waited for before a wavefront knows its best step)
+#pragma unroll
+        for (int k = 0; k < (SMALL ? KMAX : 0); ++k) {
+            const uint32_t jl = own + (uint32_t)k * T, slot = job_of(X, J0 + (jl < nj ? jl : nj - 1u));
+            seg_lo[k] = X.tb.seg_off[slot];
+            seg_hi[k] = X.tb.seg_off[slot + 1];
+            ref_thr[k] = X.ref_thr[slot];
+        }
+    };
     {
         int32_t g_i[KMAX];
         uint32_t c_i[KMAX], target[KMAX], gpus[KMAX];
@@ -1057,15 +1071,7 @@ __device__ __forceinline__ void tail_run(const Ctx &X, const JobState &st, uint3
             gpus[k] = PASS == 0 ? st.step_dg[at] : st.g[at];
             slope[k] = st.step_slope[at];
         }
-        if constexpr (SMALL) {                                     // (not waited for before a step needs them)
-#pragma unroll
-            for (int k = 0; k < KMAX; ++k) {
-                const uint32_t jl = own + (uint32_t)k * T, slot = job_of(X, J0 + (jl < nj ? jl : nj - 1u));
-                seg_lo[k] = X.tb.seg_off[slot];
-                seg_hi[k] = X.tb.seg_off[slot + 1];
-                ref_thr[k] = X.ref_thr[slot];
-            }
-        }
+        if constexpr (KMAX == 1) find_amounts();                   // (with two jobs per thread only where steps are taken one by one: lists would wait for it)
         __syncthreads();                                           // the levels are in LDS
 #pragma unroll
         for (int k = 0; k < KMAX; ++k) {
@@ -1120,9 +1126,34 @@ __device__ __forceinline__ void tail_run(const Ctx &X, const JobState &st, uint3
     // What the wavefront has read of the job with its best step: a lane per amount (GPU pass: its GPUs too).
     uint32_t kept_job = NONE, kept_g = 0, kept_n = 0, turn = 0, singly = 0;
     float kept_v = 0.f, kept_ref = 1.f;
-    bool one_by_one = SMALL;
-    // (no job has a step, as in most CPU passes of small rounds: asked once, since a list says whether there is more)
-    const bool none = KMAX == 1 && __syncthreads_or(slope[0] > 0.f) == 0;
+    bool one_by_one = false;
+    // is there room for so many halves of a step, if steps are like these?
+    auto room_for = [&](uint32_t halves, uint32_t n, uint32_t sum_g, uint32_t sum_c, uint32_t roomG, uint32_t roomC) {
+        return 2ull * roomG * n >= (unsigned long long)sum_g * halves && 2ull * roomC * n >= (unsigned long long)sum_c * halves;
+    };
+    bool none = false;                                          // (no job has a step, as in most CPU passes of small rounds)
+    if constexpr (SMALL) {
+        uint32_t n = 0, sum_g = 0, sum_c = 0;
+#pragma unroll
+        for (int k = 0; k < KMAX; ++k) {
+            const bool step = slope[k] > 0.f;
+            n += (uint32_t)__popcll(__ballot(step));
+            sum_g += step ? dg[k] : 0u;
+            sum_c += step ? (dc[k] < TAIL_MOST_CPUS ? dc[k] : TAIL_MOST_CPUS) : 0u;
+        }
+        if (n) { if (PASS == 0) sum_g = wave_sum_u32(sum_g); sum_c = wave_sum_u32(sum_c); }
+        if (lane == 0) { S.steps[wave] = n; S.steps_g[wave] = sum_g; S.steps_c[wave] = sum_c; }
+        lds_barrier();
+        const bool in = (lane & 15u) < WAVES;                   // (sums over a row of lanes: a wavefront's in each)
+        n = one(row_sum_u32(in ? S.steps[lane & (WAVES - 1u)] : 0u));
+        none = n == 0u;
+        if (!none) {
+            sum_g = PASS == 0 ? one(row_sum_u32(in ? S.steps_g[lane & (WAVES - 1u)] : 0u)) : 0u;
+            sum_c = one(row_sum_u32(in ? S.steps_c[lane & (WAVES - 1u)] : 0u));
+            one_by_one = !room_for(TAIL_MANY_STEPS, n, sum_g, sum_c, room(freeG), room(freeC));
+            if (KMAX > 1 && one_by_one) find_amounts();
+        }
+    }
     while (!none) {
         if (PASS == 0 ? freeG == 0 : freeC == 0) break;         // nothing can fit any more
         const uint32_t roomG = room(freeG), roomC = room(freeC);
@@ -1176,16 +1207,14 @@ __device__ __forceinline__ void tail_run(const Ctx &X, const JobState &st, uint3
                     continue;
                 }
                 if (!top) break;
-                if (singly == 0u) {                             // is there room for as many steps like those offered?
-                    const uint32_t n = (uint32_t)__popcll(__ballot(o.slope != 0u) & 0xFFFFull), sum_g = one(row_sum_u32(o.slope ? o.dg : 0u));
-                    const uint32_t sum_c = one(row_sum_u32(o.slope ? o.dc : 0u));        // (each fits what is free)
-                    one_by_one = (unsigned long long)roomG * n < (unsigned long long)sum_g * TAIL_MANY_STEPS ||
-                                 (unsigned long long)roomC * n < (unsigned long long)sum_c * TAIL_MANY_STEPS;
-                }
+                const uint32_t won = (uint32_t)__ffsll((long long)__ballot(o.slope == top && o.job == jw)) - 1u;       // (below WAVES)
+                const uint32_t dg_won = wave_lane_u32(o.dg, won), dc_won = wave_lane_u32(o.dc, won);                   // (CPU pass: no GPUs)
+                if (singly == 0u)                               // behind the best step, of those that are offered
+                    one_by_one = !room_for(TAIL_MANY_OFFERED, (uint32_t)__popcll(__ballot(o.slope != 0u) & 0xFFFFull), one(row_sum_u32(o.slope ? o.dg : 0u)),
+                                           one(row_sum_u32(o.slope ? (o.dc < TAIL_MOST_CPUS ? o.dc : TAIL_MOST_CPUS) : 0u)), roomG - dg_won, roomC - dc_won);
                 if (one_by_one) {
-                    const uint32_t won = (uint32_t)__ffsll((long long)__ballot(o.slope == top && o.job == jw)) - 1u;       // (below WAVES)
-                    freeG -= wave_lane_u32(o.dg, won);              // (CPU pass: 0)
-                    freeC -= wave_lane_u32(o.dc, won);
+                    freeG -= dg_won;
+                    freeC -= dc_won;
                     if (wave == won) {
                         const bool owner = jf == jw && bf == top;
                         int32_t g_i = gi[jw];
@@ -1397,14 +1426,15 @@ __device__ __forceinline__ void tail_run(const Ctx &X, const JobState &st, uint3
             search(S.best);
             one_by_one = SMALL;
             singly = 0;
+            if constexpr (SMALL && KMAX > 1) find_amounts();
         }
     }
     for (; moved; moved &= moved - 1u) {                        // only the jobs that took a step here changed since k_apply
-        const uint32_t k = (uint32_t)__ffs((int)moved) - 1u, jl = own + k * T;
+        const uint32_t jl = own + ((uint32_t)__ffs((int)moved) - 1u) * T;
         if (PASS == 0) {
             const int32_t s_i = gi[jl];
             uint32_t s0;
-            if constexpr (SMALL) s0 = KMAX > 1 && k ? seg_lo[KMAX - 1] : seg_lo[0]; else s0 = X.tb.seg_off[job_of(X, J0 + jl)];
+            if constexpr (KMAX == 1) s0 = seg_lo[0]; else s0 = X.tb.seg_off[job_of(X, J0 + jl)];
             st.gi[jrel0 + jl] = s_i;
             st.g[jrel0 + jl] = s_i < 0 ? 0u : X.tb.seg_g[s0 + s_i];
         } else {

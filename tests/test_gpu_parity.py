@@ -1055,9 +1055,9 @@ def test_enumeration_at_the_job_counts_where_the_scan_changes(gpu, orc):
 
 @pytest.mark.parametrize("n_jobs,g_max", [(300, 64), (512, 64), (513, 64), (1025, 64), (2048, 64), (70, 1024), (600, 1024)])
 def test_allocate_few_steps_behind_the_threshold(gpu, orc, n_jobs, g_max):
-    """Rounds of up to 2,048 jobs take up to five steps one by one and go to lists where there would be more, or after a list
-    that had many bounds to search back again: capacities that leave from none to some dozens of steps to either pass, with
-    equal slopes, bounds and jobs of more than 64 amounts among them."""
+    """Rounds of up to 2,048 jobs take up to five steps one by one, go to lists where there would be more, and come back from a
+    list that had many bounds to search: capacities that leave from none to some dozens of steps to either pass, with equal
+    slopes, bounds and jobs of more than 64 amounts among them."""
     import paper_2408_08586_amd as rk
     rng = np.random.default_rng(n_jobs + g_max)
     base = workloads.stress(n_jobs=n_jobs)
