@@ -1397,6 +1397,7 @@ __device__ __forceinline__ void tail_run(const Ctx &X, const JobState &st, uint3
                     t = nx.tgt;
                     v = nx.slope > 0.f ? nx.slope : 0.f; d = nx.dg;             // (not a number: none)
                     c = need_cpus(g_w, c_w, nx.tgt, PASS == 0 ? nx.dg : held_w);
+                    next_t = NONE;                               // (what is behind the step that it was listed with is not behind this one)
                 }
             }
             freeG = PASS == 0 ? fg : freeG; freeC = fc;

@@ -1090,6 +1090,46 @@ def test_allocate_few_steps_behind_the_threshold(gpu, orc, n_jobs, g_max):
     run.close()
 
 
+@pytest.mark.parametrize("n_jobs", [300, 600, 1500, 2500, 12288])
+@pytest.mark.parametrize("cpus", [0, 1])
+def test_a_listed_step_that_no_longer_fits_is_replaced_with_what_follows_it(gpu, orc, n_jobs, cpus):
+    """Five jobs take one unit each from the ten that are left, a sixth wanted eight at once and takes single ones instead: what it does after
+    the first of them follows from that one, not from the eight it was listed with.  The slopes differ by less than a bin of the
+    threshold, so that all of it happens in a list; over GPUs and, with a GPU per job, over CPU levels."""
+    import paper_2408_08586_amd as rk
+    base = workloads.stress(n_jobs=n_jobs)
+    ints = np.tile(np.array([[24, 64, 1]], np.uint32), (n_jobs, 1))
+    coef = base.coef.copy()
+    coef[:, 16] = 1.0
+    grid = workloads.Grid(np.arange(1, 12, dtype=np.uint32), 1, np.array([64.0], np.float32), 0)
+    wl = workloads.Workload("behind", coef, ints, workloads.Bounds(g_max=1 if cpus else 64), grid, base.env, workloads.Cluster(8, 8, 1.0e9))
+    ot = orc.enumerate_plans(wl.ints, wl.bounds)
+    g = ot.seg_g[:ot.seg_off[1]].astype(np.float64)             # the same GPU counts for all jobs
+    assert np.array_equal(g, [1.0]) if cpus else {1, 2, 4, 8} <= set(g.tolist())
+    units = np.repeat(np.arange(11.0)[:, None], len(g), axis=1) if cpus else np.repeat(g[None, :], 11, axis=0)     # of the pass's resource, by row and count
+    high = np.where(units >= 1, np.float32(1.0 + 2.0 ** -18), 0.0)
+    wants_eight = np.where(units >= 8, 8.0, 0.9375 * units)
+    rest = np.where(units >= 1, 0.5, 0.0)
+    rng = np.random.default_rng(n_jobs)
+    who = rng.permutation(n_jobs)
+    value = np.repeat(rest[None], n_jobs, axis=0)
+    value[who[:5]] = high
+    value[who[5]] = wants_eight
+    value[who[6:20]] = np.where(units >= 1, 0.875, 0.0)
+    bt = (value + (1.0 if cpus else 0.0)).astype(np.float32).reshape(-1)            # (a GPU each, whatever the CPUs)
+    bp = rng.integers(0, 1000, len(bt)).astype(np.uint32)
+    ct, _, _ = orc.curves(ot, grid, bt, bp)
+    cl = workloads.Cluster(n_jobs, n_jobs + 10, 1.0e9) if cpus else workloads.Cluster(10, 10 ** 6, 1.0e9)
+    e_assign, e_total, _ = orc.greedy(coef[:, 16], ot, grid, cl, bt, bp, ct)
+    run = gpu(wl)
+    run.enumerate()
+    assign, total = run.allocate(run.dev_f32(bt), run.dev_u32(bp), run.dev_f32(ct), cluster=rk.make_cluster(cl))
+    assert e_assign["c" if cpus else "g"][who[5]] == (5 if cpus else 4) + cpus      # (more than the one it would stop at)
+    assert np.array_equal(assign, e_assign)
+    assert total == pytest.approx(e_total, rel=1e-6)
+    run.close()
+
+
 @pytest.mark.parametrize("n,n_kinds", [(511, 40), (512, 512), (513, 40), (16384, 45), (16385, 1), (16385, 3000), (40000, 33000)])
 def test_enumeration_around_the_listed_searches(gpu, orc, n, n_kinds):
     """Up to 512 jobs are scanned by the last search, two to a thread; beyond 16,384 the searches are taken from a list, in
