@@ -35,7 +35,7 @@ MEASURED_TRAFFIC = {
 # Vector-ALU instructions per launch of the fused kernel on the stress workload (rocprofv3 --pmc SQ_INSTS_VALU,
 # profiles/valu_stress.txt: wavefront instructions, 64 lanes each), keyed by the digest of its sources.
 FUSED_SOURCES = ("paper_2408_08586_amd/csrc/rk_fused.hip", "paper_2408_08586_amd/csrc/rk_model.h")
-MEASURED_FUSED_VALU = {"f8e6e35c8871e32b": 28481029}
+MEASURED_FUSED_VALU = {"d1158ffc1863b378": 28533154}
 # 256 compute units x 4 SIMDs x 16 lanes x 2.4 GHz: vector instructions per lane and second (an FMA is one of them,
 # so this is half of the 78.6 TFLOP/s of unpacked FP32 and a quarter of the 157.3 TFLOP/s with packed FP32)
 VALU_PEAK_LANE_INSTR = 256 * 4 * 16 * 2.4e9
